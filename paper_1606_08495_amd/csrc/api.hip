@@ -21,6 +21,7 @@ void build_keep_thresholds_host(const uint64_t* counts, uint32_t V, double t, ui
 }  // namespace w2v
 
 using namespace w2v;
+static_assert(W2V_S_MAX <= ROW_PARTS_MAX, "an export moves all shards in one launch");
 
 // ---------------------------------------------------------------------------------------------
 // errors
@@ -839,8 +840,8 @@ extern "C" int w2v_shard_get_rows(w2v_shard* sh, int which, const uint32_t* rows
     if (which != 0 && which != 1) return fail(W2V_ERR_ARG, "which must be 0 (U) or 1 (W)");
     int rc = check_device(sh);
     if (rc) return rc;
-    launch_gather_rows(which ? sh->W : sh->U, sh->g, sh->d_slice, rows, m, sh->V, dst, sh->err,
-                       (hipStream_t)stream);
+    const RowPart part{which ? sh->W : sh->U, sh->g.stride4, 0, sh->d_slice, sh->err};
+    launch_get_rows(&part, 1, dst, sh->d_slice, rows, m, sh->V, (hipStream_t)stream);
     HIP_TRY(hipGetLastError());
     return W2V_OK;
 }
@@ -851,8 +852,8 @@ extern "C" int w2v_shard_set_rows(w2v_shard* sh, int which, const uint32_t* rows
     if (which != 0 && which != 1) return fail(W2V_ERR_ARG, "which must be 0 (U) or 1 (W)");
     int rc = check_device(sh);
     if (rc) return rc;
-    launch_scatter_rows(which ? sh->W : sh->U, sh->g, sh->d_slice, rows, m, sh->V, src, sh->err,
-                        (hipStream_t)stream);
+    const RowPart part{which ? sh->W : sh->U, sh->g.stride4, 0, sh->d_slice, sh->err};
+    launch_set_rows(part, src, rows, m, sh->V, (hipStream_t)stream);
     HIP_TRY(hipGetLastError());
     return W2V_OK;
 }
@@ -1697,11 +1698,11 @@ extern "C" int w2v_export_rows(w2v_shard* const* shards, uint32_t S, int which,
     int rc = check_device(shards[0]);
     if (rc) return rc;
     hipStream_t st = (hipStream_t)stream;
-    for (uint32_t s = 0; s < S; ++s) {
-        w2v_shard* sh = shards[s];
-        launch_export_rows(which ? sh->W : sh->U, sh->g, sh->d_slice, rows, m, sh->V, dst,
-                           sh->d_total, sh->col_begin, sh->err, st);
-    }
+    RowPart parts[W2V_S_MAX];
+    for (uint32_t s = 0; s < S; ++s)
+        parts[s] = RowPart{which ? shards[s]->W : shards[s]->U, shards[s]->g.stride4, shards[s]->col_begin,
+                           shards[s]->d_slice, shards[s]->err};
+    launch_get_rows(parts, S, dst, shards[0]->d_total, rows, m, shards[0]->V, st);
     HIP_TRY(hipGetLastError());
     return W2V_OK;
 }

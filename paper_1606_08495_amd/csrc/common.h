@@ -59,10 +59,15 @@ struct NoiseTable { const uint2* bins; uint32_t V; };   // {keep threshold, alia
 
 void launch_init(float* M, uint32_t V, RowGeom g, uint32_t d_slice, uint32_t d_total,
                  uint32_t col_begin, uint64_t seed, uint32_t matrix, bool zero, hipStream_t st);
-void launch_gather_rows(const float* M, RowGeom g, uint32_t d_slice, const uint32_t* rows,
-                        uint32_t m, uint32_t V, float* dst, uint32_t* err, hipStream_t st);
-void launch_scatter_rows(float* M, RowGeom g, uint32_t d_slice, const uint32_t* rows, uint32_t m,
-                         uint32_t V, const float* src, uint32_t* err, hipStream_t st);
+// Listed rows between matrices and the caller's row array: row i of the array starts at i * pitch, and
+// the columns of a part's matrix (row stride stride4 float4) stand at col .. col + width in it.  A word
+// >= V raises the part's error flag; it is read as word 0 and not written.  One launch for all parts.
+constexpr uint32_t ROW_PARTS_MAX = 32;
+struct RowPart { float* M; uint32_t stride4, col, width; uint32_t* err; };
+void launch_get_rows(const RowPart* parts, uint32_t S, float* dst, uint32_t pitch, const uint32_t* rows,
+                     uint32_t m, uint32_t V, hipStream_t st);
+void launch_set_rows(const RowPart& part, const float* src, const uint32_t* rows, uint32_t m, uint32_t V,
+                     hipStream_t st);
 
 // keys[p*T + 0] = out_idx[p], keys[p*T + j] = negative j.  An output word >= V raises *err and is
 // replaced by 0.  in_safe[p] (launch_check_inputs) is the checked copy of in_idx[p] that every
@@ -226,10 +231,7 @@ struct PairArgs {
 size_t pairs_scratch_u32(uint32_t n_tokens, bool interleave);
 void launch_make_pairs(const PairArgs& a, hipStream_t st);
 
-// ---- export and retrieval ----------------------------------------------------------------------------
-void launch_export_rows(const float* M, RowGeom g, uint32_t d_slice, const uint32_t* rows, uint32_t m,
-                        uint32_t V, float* dst, uint32_t d_total, uint32_t col_begin, uint32_t* err,
-                        hipStream_t st);
+// ---- retrieval ----------------------------------------------------------------------------
 // Workspace of the top-K search for rounds of `round_candidates` candidates, and the largest round a
 // given workspace allows (multiple of 128; 0: too small).
 size_t topk_workspace_bytes(uint32_t Q, uint32_t N, uint32_t round_candidates);

@@ -57,48 +57,110 @@ void launch_init(float* M, uint32_t V, RowGeom g, uint32_t d_slice, uint32_t d_t
 }
 
 // ---------------------------------------------------------------------------------------------
-// get / set of listed rows, dense [m][d_slice] on the caller's side.
+// Listed rows between a matrix and the caller's row array (get, set, and the column slices of an
+// export).  Bound by memory: a block moves a whole number of rows, MOVE_ITEMS accesses per thread, each
+// as wide as the widths, the pitch and the caller's pointer allow (16 bytes when the row length is a
+// multiple of four floats), four of them in flight; the words are read and range-checked once per row.
+// (One 4-byte access per thread, a division and a word load each, before: reading back 1.0 M + 2.4 M
+// rows of 1200 bytes took 3.11 ms, now 1.56 ms, 5.2 TB/s read and written.)
 // ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void gather_rows_kernel(const float* __restrict__ M,
-                                                          uint32_t stride, uint32_t d_slice,
-                                                          const uint32_t* __restrict__ rows,
-                                                          uint32_t m, uint32_t V,
-                                                          float* __restrict__ dst,
-                                                          uint32_t* err) {
-    uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (uint64_t)m * d_slice) return;
-    uint32_t r = (uint32_t)(i / d_slice), c = (uint32_t)(i % d_slice);
-    uint32_t w = rows[r];
-    if (w >= V) { if (c == 0) atomicOr(err, 1u); w = 0; }
-    dst[i] = M[(uint64_t)w * stride + c];
+constexpr int MOVE_ITEMS = 8;
+constexpr int MOVE_ROWS_MAX = 1024;               // rows of a block, at most (their words sit in LDS)
+enum MoveDir { MOVE_OUT, MOVE_IN };
+
+struct MovePart {                                 // one matrix and its columns on the caller's side
+    float* M; uint32_t stride;                    // stride in floats (a multiple of 4)
+    uint32_t col, width;                          // row r starts at ext + r * pitch + col
+    uint32_t magic;                               // ceil(2^32 / (width / VEC)): exact below 2^22 items a block
+    uint32_t* err;
+};
+template <int PARTS> struct MoveRows {
+    float* ext; uint32_t pitch, m, V, rows_per_block;
+    const uint32_t* rows;
+    MovePart part[PARTS];                         // one per blockIdx.y
+};
+
+template <int VEC> struct MoveWord;
+template <> struct MoveWord<1> { typedef float type; };
+template <> struct MoveWord<2> { typedef float type __attribute__((ext_vector_type(2))); };
+template <> struct MoveWord<4> { typedef v4f type; };
+
+template <int VEC, MoveDir DIR, int PARTS>
+__global__ __launch_bounds__(256) void move_rows_kernel(MoveRows<PARTS> a) {
+    typedef typename MoveWord<VEC>::type word;
+    __shared__ uint32_t s_row[MOVE_ROWS_MAX];
+    const MovePart& part = a.part[PARTS > 1 ? blockIdx.y : 0u];
+    const uint32_t r0 = blockIdx.x * a.rows_per_block;           // < m: the grid covers m rows exactly
+    const uint32_t nr = min(a.rows_per_block, a.m - r0);
+    for (uint32_t i = threadIdx.x; i < nr; i += 256) {
+        uint32_t w = a.rows[r0 + i];
+        if (w >= a.V) { atomicOr(part.err, 1u); w = DIR == MOVE_OUT ? 0u : KEY_NONE; }
+        s_row[i] = w;
+    }
+    __syncthreads();
+    const uint32_t dv = part.width / VEC, count = nr * dv;
+    for (uint32_t i0 = threadIdx.x; i0 < count; i0 += 4 * 256) {
+        word x[4];                       // (vectors of the compiler's own: an array of structs lands in LDS)
+        word* to[4];
+        bool on[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t i = min(i0 + e * 256, count - 1);     // (past the end: a load that is not stored)
+            const uint32_t r = dv == 1 ? i : __umulhi(i, part.magic), c = i - r * dv;
+            const uint32_t w = s_row[r];
+            word* ext = (word*)(a.ext + (uint64_t)(r0 + r) * a.pitch + part.col) + c;
+            word* mat = (word*)(part.M + (uint64_t)(w == KEY_NONE ? 0u : w) * part.stride) + c;
+            const word* from = DIR == MOVE_OUT ? mat : ext;
+            x[e] = *from;
+            to[e] = DIR == MOVE_OUT ? ext : mat;
+            on[e] = i0 + e * 256 < count && w != KEY_NONE;       // (a word outside is not written)
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (on[e]) *to[e] = x[e];
+    }
 }
 
-__global__ __launch_bounds__(256) void scatter_rows_kernel(float* __restrict__ M, uint32_t stride,
-                                                           uint32_t d_slice,
-                                                           const uint32_t* __restrict__ rows,
-                                                           uint32_t m, uint32_t V,
-                                                           const float* __restrict__ src,
-                                                           uint32_t* err) {
-    uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (uint64_t)m * d_slice) return;
-    uint32_t r = (uint32_t)(i / d_slice), c = (uint32_t)(i % d_slice);
-    uint32_t w = rows[r];
-    if (w >= V) { if (c == 0) atomicOr(err, 1u); return; }
-    M[(uint64_t)w * stride + c] = src[i];
-}
-
-void launch_gather_rows(const float* M, RowGeom g, uint32_t d_slice, const uint32_t* rows,
-                        uint32_t m, uint32_t V, float* dst, uint32_t* err, hipStream_t st) {
+// (PARTS = 1 keeps the kernel's arguments short for a plain get or set)
+template <MoveDir DIR, int PARTS>
+static void launch_move_rows(const RowPart* parts, uint32_t S, float* ext, uint32_t pitch,
+                             const uint32_t* rows, uint32_t m, uint32_t V, hipStream_t st) {
     if (m == 0) return;
-    hipLaunchKernelGGL(gather_rows_kernel, dim3(blocks_for((uint64_t)m * d_slice, 256)), dim3(256),
-                       0, st, M, g.stride4 * 4, d_slice, rows, m, V, dst, err);
+    MoveRows<PARTS> a{};
+    a.ext = ext; a.pitch = pitch; a.m = m; a.V = V; a.rows = rows;
+    uint32_t mix = pitch | (uint32_t)((uintptr_t)ext / 4), width = 0;
+    for (uint32_t s = 0; s < S; ++s) {
+        mix |= parts[s].width | parts[s].col;
+        width = std::max(width, parts[s].width);
+    }
+    const uint32_t vec = (uintptr_t)ext % 4 ? 1 : (mix % 4 == 0 ? 4 : (mix % 2 == 0 ? 2 : 1));
+    for (uint32_t s = 0; s < S; ++s) {
+        const uint32_t dv = parts[s].width / vec;                 // (dv = 1: the magic is not used)
+        a.part[s] = MovePart{parts[s].M, parts[s].stride4 * 4, parts[s].col, parts[s].width,
+                             (uint32_t)(((1ull << 32) + dv - 1) / dv), parts[s].err};
+    }
+    // as many rows as give every thread MOVE_ITEMS accesses, fewer (down to one access per thread) while
+    // that leaves the chip short of blocks
+    const uint32_t dv_max = width / vec;
+    const uint32_t most = std::min((uint32_t)MOVE_ROWS_MAX, std::max(1u, 256u * MOVE_ITEMS / dv_max));
+    const uint32_t least = std::min(most, std::max(1u, 256u / dv_max));
+    const uint32_t rb = std::min(most, std::max(least, (uint32_t)((uint64_t)m * S / 2048u)));
+    a.rows_per_block = rb;
+    const dim3 grid(blocks_for(m, rb), S), block(256);
+    if (vec == 4) hipLaunchKernelGGL((move_rows_kernel<4, DIR, PARTS>), grid, block, 0, st, a);
+    else if (vec == 2) hipLaunchKernelGGL((move_rows_kernel<2, DIR, PARTS>), grid, block, 0, st, a);
+    else hipLaunchKernelGGL((move_rows_kernel<1, DIR, PARTS>), grid, block, 0, st, a);
 }
 
-void launch_scatter_rows(float* M, RowGeom g, uint32_t d_slice, const uint32_t* rows, uint32_t m,
-                         uint32_t V, const float* src, uint32_t* err, hipStream_t st) {
-    if (m == 0) return;
-    hipLaunchKernelGGL(scatter_rows_kernel, dim3(blocks_for((uint64_t)m * d_slice, 256)), dim3(256),
-                       0, st, M, g.stride4 * 4, d_slice, rows, m, V, src, err);
+void launch_get_rows(const RowPart* parts, uint32_t S, float* dst, uint32_t pitch, const uint32_t* rows,
+                     uint32_t m, uint32_t V, hipStream_t st) {
+    if (S == 1) launch_move_rows<MOVE_OUT, 1>(parts, S, dst, pitch, rows, m, V, st);
+    else launch_move_rows<MOVE_OUT, ROW_PARTS_MAX>(parts, S, dst, pitch, rows, m, V, st);
+}
+
+void launch_set_rows(const RowPart& part, const float* src, const uint32_t* rows, uint32_t m, uint32_t V,
+                     hipStream_t st) {
+    launch_move_rows<MOVE_IN, 1>(&part, 1, const_cast<float*>(src), part.width, rows, m, V, st);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -412,28 +412,4 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
     return err;
 }
 
-// Column slice of the listed rows written into full-width vectors: dst[i][col_begin + c] =
-// M[rows[i]][c] (Section 6.1.4: partial vectors of the shards joined into whole vectors).
-__global__ __launch_bounds__(256) void export_rows_kernel(const float* __restrict__ M,
-                                                          uint32_t stride, uint32_t d_slice,
-                                                          const uint32_t* __restrict__ rows,
-                                                          uint32_t m, uint32_t V,
-                                                          float* __restrict__ dst, uint32_t d_total,
-                                                          uint32_t col_begin, uint32_t* err) {
-    const uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= (uint64_t)m * d_slice) return;
-    const uint32_t r = (uint32_t)(i / d_slice), c = (uint32_t)(i % d_slice);
-    uint32_t w = rows[r];
-    if (w >= V) { if (c == 0) atomicOr(err, 1u); w = 0; }
-    dst[(uint64_t)r * d_total + col_begin + c] = M[(uint64_t)w * stride + c];
-}
-
-void launch_export_rows(const float* M, RowGeom g, uint32_t d_slice, const uint32_t* rows, uint32_t m,
-                        uint32_t V, float* dst, uint32_t d_total, uint32_t col_begin, uint32_t* err,
-                        hipStream_t st) {
-    if (m == 0) return;
-    hipLaunchKernelGGL(export_rows_kernel, dim3(blocks_for((uint64_t)m * d_slice, 256)), dim3(256), 0,
-                       st, M, g.stride4 * 4, d_slice, rows, m, V, dst, d_total, col_begin, err);
-}
-
 }  // namespace w2v
