@@ -1725,11 +1725,10 @@ extern "C" int w2v_topk_cosine(const float* queries, uint32_t Q, const float* ca
     if (N >= 0xFFFFFF00u || Q >= 0xFFFFFF00u) return fail(W2V_ERR_ARG, "Q and N must stay below 2^32 - 256");
     if (!(tau == tau)) return fail(W2V_ERR_ARG, "tau is not a number");
     if ((uintptr_t)workspace % 256) return fail(W2V_ERR_ARG, "workspace must be 256-byte aligned");
-    const uint32_t cap = topk_round_capacity(Q, N, workspace_bytes);
-    if (cap == 0)
+    if (!topk_workspace_fits(Q, N, workspace_bytes))
         return fail(W2V_ERR_ARG, "workspace of %zu bytes is too small: %zu are needed for rounds of "
                     "128 candidates", workspace_bytes, topk_workspace_bytes(Q, N, 128));
-    launch_topk_cosine(queries, Q, cands, N, d, K, tau, out_idx, out_score, out_count, workspace, cap,
+    launch_topk_cosine(queries, Q, cands, N, d, K, tau, out_idx, out_score, out_count, workspace, workspace_bytes,
                        (hipStream_t)stream);
     HIP_TRY(hipGetLastError());
     return W2V_OK;

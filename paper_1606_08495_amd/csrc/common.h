@@ -232,13 +232,13 @@ size_t pairs_scratch_u32(uint32_t n_tokens, bool interleave);
 void launch_make_pairs(const PairArgs& a, hipStream_t st);
 
 // ---- retrieval ----------------------------------------------------------------------------
-// Workspace of the top-K search for rounds of `round_candidates` candidates, and the largest round a
-// given workspace allows (multiple of 128; 0: too small).
+// Workspace of the top-K search for rounds of `round_candidates` candidates, and whether a given one
+// holds the shortest rounds (128).
 size_t topk_workspace_bytes(uint32_t Q, uint32_t N, uint32_t round_candidates);
-uint32_t topk_round_capacity(uint32_t Q, uint32_t N, size_t workspace_bytes);
+bool topk_workspace_fits(uint32_t Q, uint32_t N, size_t workspace_bytes);
 uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint32_t N, uint32_t d,
                              uint32_t K, float tau, uint32_t* out_idx, float* out_score,
-                             uint32_t* out_count, void* workspace, uint32_t cap, hipStream_t st);
+                             uint32_t* out_count, void* workspace, size_t workspace_bytes, hipStream_t st);
 
 // ---- continuous bag of words ----------------------------------------------------------------------
 // Per context entry: checked word, example number, weight 1/|C|; offsets are validated (error flag).

@@ -1,9 +1,29 @@
 // Retrieval by cosine similarity (Section 2; Section 7.3: K = 30, threshold tau): for every query
-// vector the K most similar candidate vectors.  The similarities are a dense contraction
-// (Q x d) . (d x N) and run on the fp32 matrix cores; they are never written out -- a tile's scores
-// are compared with the query's current K-th best right in the accumulators, and only the few that
-// pass are appended to the query's pending list, which a small selection kernel folds into the
-// sorted best list after every round of candidates.
+// vector the K most similar candidate vectors.
+//
+// Candidates are taken in rounds, in index order.  A round's scores are screened: every (query,
+// candidate) pair that may beat the query's current K-th best is put on the query's pending list, and
+// topk_fold_kernel gives each listed pair its similarity in fp32, folds those that do beat the K-th
+// best into the sorted best list and raises the threshold.  The similarity of a pair is
+// fl(fl(dot * 1/|q|) * 1/|c|) with dot one fused-multiply-add chain over the columns in order -- whoever
+// forms it, so results depend neither on the round length nor on which screen listed the pair.
+//
+// The screen need not be exact, only never miss: two of the three work in 16 bits on the matrix cores,
+// sixteen times the rate of fp32 there, with a margin that covers their error for certain (below):
+//   wide    (Q > 128): a round's candidates are normalised and rounded to fp16 once, in the order in
+//           which the matrix cores take them, and multiplied tile by tile.
+//   stream  (Q <= 128): bound by reading the candidates; a wavefront reads 32 of them once, rounds them
+//           to bf16 in registers (no scale is known yet; bf16 has fp32's range), and forms norms,
+//           rounding errors and products with all queries on the way.
+//   fp32    exact scores from the fp32 matrix cores; only where the workspace is too small for the
+//           rounded queries.
+//
+// Margin.  Let a = q/|q|, b = c/|c| in fp32 and a', b' their rounded forms.  |a.b - a'.b'| <=
+// |a - a'| |b| + |a'| |b - b'|, and the norms of the two rounding errors are computed per row
+// (about 2e-4 for fp16, 9e-4 for bf16: a tenth of the distance to the K-th best that a crowded list
+// has).  What fp32 arithmetic adds on either side (products summed in any order, norms, the two
+// scalings) is at most a few d 2^-24; TK_ROUND(d) below holds twice that.  Rows whose squared length
+// is too small to be precise are always listed.
 #include "common.h"
 
 #include <math.h>
@@ -15,8 +35,10 @@ static inline unsigned blocks_for(uint64_t items, unsigned per_block) {
 }
 
 typedef float v16f __attribute__((ext_vector_type(16)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef __bf16 v8b __attribute__((ext_vector_type(8)));
 
-constexpr int TK_BQ = 128;          // queries per block tile (2 x 2 wavefronts x 2 x 2 tiles of 32)
+constexpr int TK_BQ = 128;          // fp32 screen: queries per block tile (2 x 2 wavefronts x 2 x 2 tiles of 32)
 constexpr int TK_BC = 128;          // candidates per block tile; granularity of a round
 constexpr int TK_BK = 16;           // columns per panel; two panels are held in LDS
 constexpr int TK_LD = TK_BK + 1;    // LDS row pitch (odd: conflict-free column reads)
@@ -24,50 +46,18 @@ constexpr int TK_THREADS = 256;     // four wavefronts
 constexpr int TK_RPM = TK_THREADS / (TK_BK / 4);            // rows covered by one move of the block
 constexpr int TK_LIST = 64;         // slots of a query's best list (K <= 64)
 constexpr uint32_t TK_NONE = 0xFFFFFFFFu;
+constexpr uint32_t TK_STREAM_Q = 128;     // most queries of the stream screen's tile
+constexpr int TK_KS = 16;                 // columns of one 16-bit matrix-core step
+constexpr float TK_F16_SCALE = 256.f;     // fp16 rows are stored times this: components below 2.4e-7 of the
+                                          // row's length (fp16 subnormals) are taken as zero
+constexpr float TK_TINY = 1e-30f;         // squared lengths below this are not precise
+// More hits than this in a 32 x 32 tile: its similarities are formed at once on the fp32 matrix cores
+// and tested exactly (some 10 000 cycles), instead of listing pairs at about 75 cycles each for the
+// fold.  Bounds the cost on data whose similarities all lie closer together than the margin.
+constexpr int TK_DENSE = 128;
 
-// ---------------------------------------------------------------------------------------------
-// 1 / |row| (0 for an all-zero row): one wavefront per row.
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void inv_norm_kernel(const float* __restrict__ M, uint32_t rows,
-                                                       uint32_t d, float* __restrict__ inv) {
-    const uint32_t r = (blockIdx.x * 256u + threadIdx.x) / 64u;
-    const int lane = threadIdx.x % 64;
-    if (r >= rows) return;                                  // whole wavefronts leave together
-    const float* row = M + (uint64_t)r * d;
-    float s = 0.f;
-    for (uint32_t i = lane; i < d; i += 64) s = fmaf(row[i], row[i], s);
-    for (int o = 32; o >= 1; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) inv[r] = s > 0.f ? 1.0f / sqrtf(s) : 0.f;
-}
-
-__global__ __launch_bounds__(256) void topk_init_kernel(uint32_t Q, float theta0,
-                                                        float* __restrict__ theta,
-                                                        uint32_t* __restrict__ cnt,
-                                                        uint32_t* __restrict__ best_cnt,
-                                                        uint32_t* __restrict__ err) {
-    uint32_t q = blockIdx.x * 256 + threadIdx.x;
-    if (q == 0) *err = 0u;
-    if (q >= Q) return;
-    theta[q] = theta0;
-    cnt[q] = 0u;
-    best_cnt[q] = 0u;
-}
-
-// ---------------------------------------------------------------------------------------------
-// Scores of 128 queries x 128 candidates over all d columns, then the filter.
-// Block b of the grid is mapped so that the blocks an XCD receives (b mod 8) walk through the
-// query tiles of one candidate tile after the other: the candidate tile stays in that XCD's L2.
-// v_mfma_f32_32x32x2_f32: lane l feeds A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32];
-// accumulator register v of lane l is D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32].
-// ---------------------------------------------------------------------------------------------
-struct TopkArgs {
-    const float* Qm; const float* Cm; uint32_t Q, N, d;
-    uint32_t c_begin, c_end;            // candidates of this round
-    uint32_t nq_tiles, nc_tiles;
-    const float* invq; const float* invc; const float* theta;
-    uint32_t* cnt; uint2* pend; uint32_t cap;
-    uint32_t* err;
-};
+__host__ __device__ inline uint32_t topk_steps(uint32_t d) { return 2 * ((d + 2 * TK_KS - 1) / (2 * TK_KS)); }   // even
+__device__ __forceinline__ float topk_rounding(uint32_t d) { return (float)(d + 64) * 0x1p-22f; }
 
 template <bool VEC4>
 __device__ __forceinline__ float4 load_cols(const float* __restrict__ row, bool row_ok, uint32_t k,
@@ -85,6 +75,419 @@ __device__ __forceinline__ float4 load_cols(const float* __restrict__ row, bool 
     return r;
 }
 
+// Squared length of a row: sixteen chains by column number mod 16, then a fixed tree -- the same bits
+// from one lane that walks the whole row and from two lanes that take alternate groups of eight.
+__device__ __forceinline__ void square8(const float4& a, const float4& b, float (&s)[8]) {
+    s[0] = fmaf(a.x, a.x, s[0]); s[1] = fmaf(a.y, a.y, s[1]); s[2] = fmaf(a.z, a.z, s[2]); s[3] = fmaf(a.w, a.w, s[3]);
+    s[4] = fmaf(b.x, b.x, s[4]); s[5] = fmaf(b.y, b.y, s[5]); s[6] = fmaf(b.z, b.z, s[6]); s[7] = fmaf(b.w, b.w, s[7]);
+}
+__device__ __forceinline__ float tree8(const float (&s)[8]) {
+    return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
+}
+__device__ __forceinline__ float inv_length(float square) { return square > 0.f ? 1.0f / sqrtf(square) : 0.f; }
+
+// The same of row `row` by a lane pair (l, l ^ 32): the half fk takes columns 16 i + 8 fk + 0..7.
+template <bool VEC4>
+__device__ __forceinline__ float pair_square(const float* __restrict__ row, bool ok, uint32_t d, int fk) {
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (uint32_t k = 8 * fk; k < d + 8 * fk; k += TK_KS)
+        square8(load_cols<VEC4>(row, ok, k, d), load_cols<VEC4>(row, ok, k + 4, d), s);
+    const float own = tree8(s);
+    return own + __shfl_xor(own, 32, 64);
+}
+
+struct TopkArgs {
+    const float* Qm; const float* Cm; uint32_t Q, N, d;
+    uint32_t c_begin, c_end;            // candidates of this round
+    uint32_t nq_tiles, nc_tiles;
+    const float* invq; const float* invc; const float* theta;
+    uint32_t* cnt; uint32_t* pend; uint32_t cap;
+    uint32_t* err;
+    // 16-bit screens
+    const void* qfrag; const float* qmargin;     // rounded queries, and what to lower their thresholds by
+    const void* cfrag; const float* cmargin;     // wide: the round's rounded candidates and their margins
+    bool dense_test;                             // try the exact test on tiles with many hits
+};
+
+// A row's normalised form, rounded, in matrix-core order: tile of 32 rows, step of 16 columns, lane
+// (row, half) its eight columns; and the norm of what rounding took away.  One wavefront per tile.
+// HOLD > 0: rows of up to HOLD steps stay in registers, every load in flight at once, between the norm
+// and the rounding; else they are read twice.
+constexpr int TK_HOLD = 20;                                   // steps (d <= 320)
+template <bool F16>
+__device__ __forceinline__ void round_step(const float4& x, const float4& y, float inv, bool on, void* __restrict__ frag,
+                                           uint64_t at, float& e2) {
+    const float scale = F16 ? TK_F16_SCALE : 1.f;
+    const float v[8] = {x.x, x.y, x.z, x.w, y.x, y.y, y.z, y.w};
+    v8h h; v8b g;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        const float t = on ? (v[e] * inv) * scale : 0.f;      // (times a power of two: exact)
+        float back;
+        if (F16) { h[e] = (_Float16)(fabsf(t) < 6.2e-5f ? 0.f : t); back = (float)h[e]; }
+        else { g[e] = (__bf16)t; back = (float)g[e]; }
+        e2 = fmaf(t - back, t - back, e2);
+    }
+    if (F16) ((v8h*)frag)[at] = h; else ((v8b*)frag)[at] = g;
+}
+
+template <bool F16, bool VEC4, int HOLD>
+__device__ __forceinline__ void round_rows(const float* __restrict__ M, uint32_t row, bool ok, uint32_t d,
+                                           uint32_t steps, void* __restrict__ frag, uint32_t tile, int lane,
+                                           float& square, float& inv, float& lost) {
+    const int fk = lane >> 5;
+    const float* p = M + (uint64_t)(ok ? row : 0u) * d;
+    const uint64_t at = (uint64_t)tile * steps * 64 + lane;
+    float e2 = 0.f;
+    if constexpr (HOLD > 0) {
+        float4 x[HOLD], y[HOLD];
+        float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int i = 0; i < HOLD; ++i) {
+            x[i] = load_cols<VEC4>(p, ok, i * TK_KS + 8 * fk, d);
+            y[i] = load_cols<VEC4>(p, ok, i * TK_KS + 8 * fk + 4, d);
+        }
+#pragma unroll
+        for (int i = 0; i < HOLD; ++i) square8(x[i], y[i], s);       // (zeros past d leave the sums alone)
+        const float own = tree8(s);
+        square = own + __shfl_xor(own, 32, 64);
+        inv = inv_length(square);
+        const bool on = square >= TK_TINY && inv > 0.f;       // else the rounded row is zero
+#pragma unroll
+        for (int i = 0; i < HOLD; ++i)
+            if ((uint32_t)i < steps) round_step<F16>(x[i], y[i], inv, on, frag, at + (uint64_t)i * 64, e2);
+    } else {
+        square = pair_square<VEC4>(p, ok, d, fk);
+        inv = inv_length(square);
+        const bool on = square >= TK_TINY && inv > 0.f;
+        for (uint32_t i = 0; i < steps; ++i) {
+            const uint32_t k = i * TK_KS + 8 * fk;
+            round_step<F16>(load_cols<VEC4>(p, ok, k, d), load_cols<VEC4>(p, ok, k + 4, d), inv, on, frag,
+                            at + (uint64_t)i * 64, e2);
+        }
+    }
+    e2 += __shfl_xor(e2, 32, 64);
+    lost = sqrtf(e2) / (F16 ? TK_F16_SCALE : 1.f) * 1.004f;
+    if (square > 0.f && square < TK_TINY) lost = INFINITY;     // always listed
+}
+
+// Queries: 1/|q|, rounded rows, margins; the state of an empty search.  Margin < 0: a query without
+// length (every similarity is 0).
+template <bool F16, bool VEC4>
+__global__ __launch_bounds__(64) void topk_queries_kernel(const float* __restrict__ Qm, uint32_t Q, uint32_t d,
+                                                          float theta0, float* __restrict__ invq,
+                                                          float* __restrict__ theta, uint32_t* __restrict__ cnt,
+                                                          uint32_t* __restrict__ best_cnt, void* __restrict__ frag,
+                                                          float* __restrict__ margin, uint32_t* __restrict__ err) {
+    const int lane = threadIdx.x;
+    const uint32_t q = blockIdx.x * 32u + (lane & 31);
+    float square, inv, lost;
+    if (frag) {
+        round_rows<F16, VEC4, 0>(Qm, q, q < Q, d, topk_steps(d), frag, blockIdx.x, lane, square, inv, lost);
+        if (lane < 32) margin[q] = inv > 0.f ? lost + topk_rounding(d) : -1.f;
+    } else {
+        square = pair_square<VEC4>(Qm + (uint64_t)(q < Q ? q : 0u) * d, q < Q, d, lane >> 5);
+        inv = inv_length(square);
+    }
+    if (lane < 32 && q < Q) { invq[q] = inv; theta[q] = theta0; cnt[q] = 0u; best_cnt[q] = 0u; }
+    if (blockIdx.x == 0 && lane == 0) *err = 0u;
+}
+
+// The wide screen's candidates of one round (rows c_end .. the end of the last tile are zero and have
+// a margin that no threshold meets).  Bound by memory: 4 d bytes read (a second time, for the rounding,
+// out of the caches) and 2 d written per row.
+template <bool VEC4, int HOLD>
+__global__ __launch_bounds__(64) void topk_round_kernel(const float* __restrict__ Cm, uint32_t c_begin,
+                                                         uint32_t c_end, uint32_t d,
+                                                         float* __restrict__ invc, void* __restrict__ frag,
+                                                         float* __restrict__ margin) {
+    const uint32_t tile = blockIdx.x;
+    const int lane = threadIdx.x;
+    const uint32_t c = c_begin + tile * 32 + (lane & 31);
+    float square, inv, lost;
+    round_rows<true, VEC4, HOLD>(Cm, c, c < c_end, d, topk_steps(d), frag, tile, lane, square, inv, lost);
+    if (lane < 32) {
+        margin[tile * 32 + lane] = c < c_end ? lost * (TK_F16_SCALE * TK_F16_SCALE) : -INFINITY;
+        if (c < c_end) invc[c] = inv;
+    }
+}
+
+// 1 / |row| alone, for the fp32 screen: one wavefront per 32 rows.
+template <bool VEC4>
+__global__ __launch_bounds__(256) void inv_length_kernel(const float* __restrict__ M, uint32_t rows, uint32_t d,
+                                                         float* __restrict__ inv) {
+    const uint32_t r = (blockIdx.x * 4 + threadIdx.x / 64) * 32u + (threadIdx.x & 31);
+    const float s = pair_square<VEC4>(M + (uint64_t)(r < rows ? r : 0u) * d, r < rows, d, (threadIdx.x & 63) >> 5);
+    if ((threadIdx.x & 32) == 0 && r < rows) inv[r] = inv_length(s);
+}
+
+// What a 16-bit product must reach before the candidate's own margin: the query's threshold less its
+// margin, in units of the product.
+__device__ __forceinline__ float screen_level(float theta, float margin, float unit) {
+    if (margin < 0.f) return theta < 0.f ? -INFINITY : INFINITY;          // every similarity is 0
+    const float t = (theta - margin) * unit;
+    return fabsf(t) < INFINITY ? t - fabsf(t) * 0x1p-20f : t;
+}
+
+// A slot on its query's pending list for every set bit: bit v of lane (fr, fk) is the pair of query
+// q0 + 8 (v / 4) + 4 fk + v % 4 and the lane's candidate.  Lane (v, fk) reserves the slots of that
+// query for the tile: one atomic instruction, one round trip for all 32 lists.
+__device__ __forceinline__ void append_tile(const TopkArgs& a, uint32_t bits, uint32_t q0, uint32_t c, int lane) {
+    const int fr = lane & 31, fk = lane >> 5;
+    uint32_t mine = 0, base = 0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const uint64_t both = __ballot((bits >> v) & 1u);
+        if (fr == v) mine = (uint32_t)__popc(fk ? (uint32_t)(both >> 32) : (uint32_t)both);
+    }
+    if (mine) base = atomicAdd(&a.cnt[q0 + 8 * (fr / 4) + 4 * fk + fr % 4], mine);   // (fr < 16)
+    bool lost = false;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const bool pass = (bits >> v) & 1u;
+        const uint64_t both = __ballot(pass);
+        if (both == 0) continue;
+        const uint32_t half = fk ? (uint32_t)(both >> 32) : (uint32_t)both;
+        const uint32_t slot = __shfl(base, v + 32 * fk, 64) + (uint32_t)__popc(half & ((1u << fr) - 1u));
+        const uint32_t q = q0 + 8 * (v / 4) + 4 * fk + v % 4;
+        if (pass && slot < a.cap) a.pend[(uint64_t)q * a.cap + slot] = c;
+        lost |= pass && slot >= a.cap;                        // (a list holds a whole round: cannot happen)
+    }
+    if (lost) atomicOr(a.err, 1u);
+}
+
+// fp32 products of a 32 x 32 tile of queries and candidates straight from the caller's rows.
+// v_mfma_f32_32x32x2_f32: lane l feeds A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32];
+// accumulator register v of lane l is D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32], and each element is
+// the fused-multiply-add chain over its columns in order.
+template <bool VEC4>
+__device__ __forceinline__ v16f exact_tile(const TopkArgs& a, uint32_t q, bool q_ok, uint32_t c, bool c_ok, int fk) {
+    const float* qr = a.Qm + (uint64_t)(q_ok ? q : 0u) * a.d;
+    const float* cr = a.Cm + (uint64_t)(c_ok ? c : 0u) * a.d;
+    v16f acc;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
+#pragma unroll 2
+    for (uint32_t k = 0; k < a.d; k += 4) {
+        const float4 x = load_cols<VEC4>(qr, q_ok, k, a.d), y = load_cols<VEC4>(cr, c_ok, k, a.d);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fk ? x.y : x.x, fk ? y.y : y.x, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fk ? x.w : x.z, fk ? y.w : y.z, acc, 0, 0, 0);
+    }
+    return acc;
+}
+
+// A tile's 16-bit products against the thresholds.  Most tiles hold no hit once the thresholds have
+// risen: two instructions per element tell.  level: LDS, the 32 levels of the tile's queries; `unit_c`
+// scales this lane's products (its candidate) into the levels' units; `own` is the candidate's margin
+// there, -inf for a lane without a candidate.
+template <bool VEC4>
+__device__ __forceinline__ void screen_tile(const TopkArgs& a, const v16f& acc, float unit_c, float own,
+                                            const float* level, uint32_t q0, uint32_t c, float ic, int lane) {
+    const int fk = lane >> 5;
+    float lv[16];
+#pragma unroll
+    for (int v4 = 0; v4 < 4; ++v4) {
+        const float4 t = *reinterpret_cast<const float4*>(level + 4 * fk + 8 * v4);
+        lv[4 * v4 + 0] = t.x; lv[4 * v4 + 1] = t.y; lv[4 * v4 + 2] = t.z; lv[4 * v4 + 3] = t.w;
+    }
+    float over = -INFINITY;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) over = fmaxf(over, fmaf(acc[v], unit_c, -lv[v]));
+    if (__ballot(over + own >= 0.f) == 0) return;             // uniform per wavefront
+    const bool c_ok = own > -INFINITY;
+    uint32_t bits = 0;
+    int hits = 0;
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const bool p = c_ok && fmaf(acc[v], unit_c, -lv[v]) + own >= 0.f;
+        bits |= p ? 1u << v : 0u;
+        hits += __popcll(__ballot(p));
+    }
+    if (hits > TK_DENSE && a.dense_test) {
+        const uint32_t q = q0 + (lane & 31);
+        const v16f dot = exact_tile<VEC4>(a, q, q < a.Q, c, c_ok, fk);
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const uint32_t qv = min(q0 + 8 * (v / 4) + 4 * fk + v % 4, a.Q - 1);
+            if (!(dot[v] * a.invq[qv] * ic > a.theta[qv])) bits &= ~(1u << v);
+        }
+    }
+    append_tile(a, bits, q0, c, lane);                        // (queries past Q carry +inf levels: no bits)
+}
+
+// ---------------------------------------------------------------------------------------------
+// Wide screen: WM x WN wavefronts, each TM x TN matrix-core tiles of 32 x 32.  Operands come in
+// matrix-core order, so staging is a straight copy and LDS reads are 16 adjacent bytes per lane.
+// Panels of two steps (32 columns) go through two LDS buffers: while one is multiplied, the next is
+// written from registers and the one after is on its way from memory; one barrier per panel.
+// Block b is mapped so that the blocks an XCD receives (b mod 8) walk through the query tiles of one
+// candidate tile after the other: that tile and the queries stay in its L2.
+// ---------------------------------------------------------------------------------------------
+template <int TM, int TN, int WM, int WN, int WPE, bool VEC4>
+__global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a) {
+    constexpr int THREADS = 64 * WM * WN, QT = TM * WM, CT = TN * WN, KC = 2;
+    constexpr int PANEL = (QT + CT) * KC * 64;               // 16-byte units
+    constexpr int MOVES = PANEL / THREADS;
+    static_assert(PANEL % THREADS == 0, "whole moves");
+    __shared__ v8h s_panel[2][PANEL];
+    __shared__ __align__(16) float s_level[QT * 32];
+    const uint32_t total = a.nq_tiles * a.nc_tiles;
+    const uint32_t per_xcd = (total + 7u) / 8u;
+    const uint32_t logical = (blockIdx.x % 8u) * per_xcd + blockIdx.x / 8u;
+    if (logical >= total) return;                            // uniform per block, before any barrier
+    const uint32_t qt0 = (logical % a.nq_tiles) * QT, ct0 = (logical / a.nq_tiles) * CT;
+    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+    const int wm = wave / WN, wn = wave % WN;
+    const uint32_t steps = topk_steps(a.d), panels = steps / KC;
+    for (int i = tid; i < QT * 32; i += THREADS) {
+        const uint32_t q = qt0 * 32 + i;
+        s_level[i] = q < a.Q ? screen_level(a.theta[q], a.qmargin[q], TK_F16_SCALE * TK_F16_SCALE) : INFINITY;
+    }
+    // unit u of a panel: tile u / (KC 64) -- queries first -- then step and lane
+    const v8h* from[MOVES];
+#pragma unroll
+    for (int i = 0; i < MOVES; ++i) {
+        const uint32_t u = tid + i * THREADS, t = u / (KC * 64), w = u % (KC * 64);
+        from[i] = t < (uint32_t)QT ? (const v8h*)a.qfrag + (uint64_t)(qt0 + t) * steps * 64 + w
+                                   : (const v8h*)a.cfrag + (uint64_t)(ct0 + t - QT) * steps * 64 + w;
+    }
+    v8h r[MOVES];
+    auto fetch = [&](uint32_t p) {
+#pragma unroll
+        for (int i = 0; i < MOVES; ++i) r[i] = from[i][(uint64_t)p * (KC * 64)];
+    };
+    auto stash = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < MOVES; ++i) s_panel[buf][tid + i * THREADS] = r[i];
+    };
+    v16f acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    fetch(0);
+    stash(0);
+    if (panels > 1) fetch(1);
+    __syncthreads();
+    for (uint32_t p = 0; p < panels; ++p) {
+        const int cur = p & 1;
+        if (p + 1 < panels) {
+            stash(cur ^ 1);
+            if (p + 2 < panels) fetch(p + 2);
+        }
+#pragma unroll
+        for (int k = 0; k < KC; ++k) {
+            v8h av[TM], bv[TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) av[i] = s_panel[cur][((wm * TM + i) * KC + k) * 64 + lane];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) bv[j] = s_panel[cur][((QT + wn * TN + j) * KC + k) * 64 + lane];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[i], bv[j], acc[i][j], 0, 0, 0);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int j = 0; j < TN; ++j) {
+        const uint32_t row = (ct0 + wn * TN + j) * 32 + (lane & 31), c = a.c_begin + row;
+        const float own = a.cmargin[row];
+        const float ic = c < a.c_end ? a.invc[c] : 0.f;
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+            screen_tile<VEC4>(a, acc[i][j], 1.f, own, s_level + (wm * TM + i) * 32, (qt0 + wm * TM + i) * 32, c, ic, lane);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// Stream screen: a wavefront takes 32 candidates and TQ tiles of 32 queries (blockIdx.y: which).  The
+// lane pair (l, l ^ 32) walks candidate l % 32, eight columns at a time each; the rounded columns are
+// a matrix-core operand as they stand.  Four steps of candidate columns are in flight ahead of the
+// four in work; the queries' operands come from L2.
+// ---------------------------------------------------------------------------------------------
+constexpr int TK_AHEAD = 4;
+template <int TQ, bool VEC4>
+__global__ __launch_bounds__(256) void topk_stream_kernel(TopkArgs a) {
+    __shared__ __align__(16) float s_level[TQ * 32];
+    const int tid = threadIdx.x, lane = tid % 64, fk = lane >> 5;
+    const uint32_t qt0 = blockIdx.y * TQ;
+    for (int i = tid; i < TQ * 32; i += 256) {
+        const uint32_t q = qt0 * 32 + i;
+        s_level[i] = q < a.Q ? screen_level(a.theta[q], a.qmargin[q], 1.f) : INFINITY;
+    }
+    __syncthreads();
+    const uint32_t tile = blockIdx.x * 4 + tid / 64;
+    if (tile >= a.nc_tiles) return;                          // whole wavefronts, after the only barrier
+    const uint32_t c = a.c_begin + tile * 32 + (lane & 31);
+    const bool c_ok = c < a.c_end;
+    const float* row = a.Cm + (uint64_t)(c_ok ? c : 0u) * a.d;
+    const uint32_t steps = topk_steps(a.d);
+    const v8b* qf = (const v8b*)a.qfrag + (uint64_t)qt0 * steps * 64 + lane;
+    v16f acc[TQ];
+#pragma unroll
+    for (int t = 0; t < TQ; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+    float sq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, e2 = 0.f;
+    float4 x[TK_AHEAD][2], nx[TK_AHEAD][2];
+    auto fetch = [&](float4 (&r)[TK_AHEAD][2], uint32_t ks) {
+#pragma unroll
+        for (int i = 0; i < TK_AHEAD; ++i) {
+            const uint32_t k = (ks + i) * TK_KS + 8 * fk;
+            r[i][0] = load_cols<VEC4>(row, c_ok, k, a.d);    // (zero past the last column)
+            r[i][1] = load_cols<VEC4>(row, c_ok, k + 4, a.d);
+        }
+    };
+    fetch(x, 0);
+    for (uint32_t ks0 = 0; ks0 < steps; ks0 += TK_AHEAD) {
+        fetch(nx, ks0 + TK_AHEAD);
+#pragma unroll
+        for (int i = 0; i < TK_AHEAD; ++i) {
+            const uint32_t ks = ks0 + i;
+            if (ks < steps) {
+                const float v[8] = {x[i][0].x, x[i][0].y, x[i][0].z, x[i][0].w, x[i][1].x, x[i][1].y, x[i][1].z, x[i][1].w};
+                v8b g;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    g[e] = (__bf16)v[e];
+                    const float lost = v[e] - (float)g[e];
+                    e2 = fmaf(lost, lost, e2);
+                }
+                square8(x[i][0], x[i][1], sq);
+#pragma unroll
+                for (int t = 0; t < TQ; ++t)
+                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[((uint64_t)t * steps + ks) * 64], g, acc[t], 0, 0, 0);
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < TK_AHEAD; ++i) { x[i][0] = nx[i][0]; x[i][1] = nx[i][1]; }
+    }
+    const float half = tree8(sq);
+    const float square = half + __shfl_xor(half, 32, 64);
+    const float ic = inv_length(square);
+    e2 += __shfl_xor(e2, 32, 64);
+    float own = sqrtf(e2) * ic * 1.004f;
+    if (square > 0.f && (square < TK_TINY || ic == 0.f)) own = INFINITY;   // imprecise, or too long to square
+    if (!(own >= 0.f)) own = INFINITY;
+    if (!c_ok) own = -INFINITY;
+#pragma unroll
+    for (int t = 0; t < TQ; ++t) {
+        if (own == INFINITY || ic == 0.f)                    // products that may not be finite: the margin decides
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+        screen_tile<VEC4>(a, acc[t], ic, own, s_level + t * 32, (qt0 + t) * 32, c, ic, lane);
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
+// fp32 screen: scores of 128 queries x 128 candidates over all d columns, then the filter; blocks
+// mapped to XCDs as above.
+// ---------------------------------------------------------------------------------------------
 // The block is 2 x 2 wavefronts; a wavefront owns TM x TN matrix-core tiles of 32 x 32, so the
 // block tile is (64 TM) queries x (64 TN) candidates.  WPE = wavefronts per SIMD the register
 // budget is set for.
@@ -194,12 +597,10 @@ __global__ __launch_bounds__(TK_THREADS, WPE) void topk_scores_kernel(TopkArgs a
         __syncthreads();
     }
 
-    // filter: a score at or above the query's threshold joins the query's pending list.  For a
-    // given accumulator register the 32 lanes of a half-wavefront hold 32 candidates of one query,
-    // so each half reserves its slots with a single atomic.
-    // Most tiles hold no such score once the thresholds have risen, so each 32 x 32 tile is first
-    // screened with two instructions per element (raw product against the lowered threshold);
-    // only a tile with a hit goes through the exact test.
+    // filter: a score above the query's threshold joins the query's pending list.  Most tiles hold no
+    // such score once the thresholds have risen, so each 32 x 32 tile is first screened with two
+    // instructions per element (raw product against the lowered threshold); only a tile with a hit
+    // goes through the exact test.
 #pragma unroll
     for (int ti = 0; ti < TM; ++ti) {
         const int qbase = wm * 32 * TM + ti * 32 + 4 * fk;   // this lane's queries: qbase + 8 (v/4) + v%4
@@ -218,107 +619,132 @@ __global__ __launch_bounds__(TK_THREADS, WPE) void topk_scores_kernel(TopkArgs a
 #pragma unroll
             for (int v = 0; v < 16; ++v) over = fmaxf(over, fmaf(acc[ti][tj][v], ic, -tq[v]));
             if (__ballot(over >= 0.f) == 0) continue;        // uniform per wavefront
+            uint32_t bits = 0;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 const int ql = qbase + 8 * (v / 4) + (v % 4);
                 const float s = acc[ti][tj][v] * s_invq[ql] * ic;
-                const bool pass = c_ok && s >= s_theta[ql];  // padded queries carry +inf: never
-                const uint64_t both = __ballot(pass);
-                const uint32_t half = fk ? (uint32_t)(both >> 32) : (uint32_t)both;
-                if (half) {
-                    const uint32_t q = q0 + ql;
-                    const int leader = __ffs(half) - 1 + 32 * fk;
-                    uint32_t base = 0;
-                    if (lane == leader) base = atomicAdd(&a.cnt[q], (uint32_t)__popc(half));
-                    base = __shfl(base, leader, 64);
-                    if (pass) {
-                        const uint32_t slot = base + (uint32_t)__popc(half & ((1u << fr) - 1u));
-                        if (slot < a.cap)
-                            a.pend[(uint64_t)q * a.cap + slot] = make_uint2(__float_as_uint(s), c);
-                        else
-                            atomicOr(a.err, 1u);
-                    }
-                }
+                bits |= c_ok && s > s_theta[ql] ? 1u << v : 0u;       // padded queries carry +inf: never
             }
+            append_tile(a, bits, q0 + wm * 32 * TM + ti * 32, c, lane);
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
-// Selection: one wavefront per query folds the pending entries, 64 at a time, into the sorted best
-// list (bitonic sort of 128 in LDS; order: higher score first, equal scores by lower index), then
-// raises the query's threshold to its K-th best and empties the pending list.
+// Fold: one block per query gives the listed pairs their similarities -- a lane per candidate, one
+// 128-byte line of its row at a time -- and merges those above the threshold into the sorted best list
+// (higher score first, equal scores by lower index), then raises the threshold to the K-th best and
+// empties the list.  Rounds come in index order, so a later candidate that only equals the K-th best
+// never enters.  Each wavefront keeps its own 64 best, sorted across its lanes; the lists are merged
+// through LDS at the end.  `out_idx` (last round): the results are written as well.
 // ---------------------------------------------------------------------------------------------
-__device__ __forceinline__ bool ranks_before(float sa, uint32_t ia, float sb, uint32_t ib) {
-    return sa > sb || (sa == sb && ia < ib);
+// (score, index) as one number that grows with the rank: order-preserving bits of the score, then ~index
+__device__ __forceinline__ uint64_t rank_key(float s, uint32_t c) {
+    const uint32_t b = __float_as_uint(s + 0.f);             // (-0 and 0 are equal scores)
+    return ((uint64_t)((b & 0x80000000u) ? ~b : b | 0x80000000u) << 32) | (uint32_t)~c;
+}
+__device__ __forceinline__ float key_score(uint64_t k) {
+    const uint32_t b = (uint32_t)(k >> 32);
+    return __uint_as_float((b & 0x80000000u) ? b & 0x7FFFFFFFu : ~b);
+}
+__device__ __forceinline__ uint64_t lane_xor(uint64_t k, int m) {
+    return ((uint64_t)(uint32_t)__shfl_xor((int)(k >> 32), m, 64) << 32) | (uint32_t)__shfl_xor((int)(uint32_t)k, m, 64);
+}
+__device__ __forceinline__ uint64_t sort64(uint64_t k, int lane) {             // descending over the lanes
+    for (int size = 2; size <= 64; size <<= 1)
+        for (int j = size >> 1; j > 0; j >>= 1) {
+            const uint64_t o = lane_xor(k, j);
+            const bool keep_max = ((lane & j) == 0) == ((lane & size) == 0 || size == 64);
+            k = (k > o) == keep_max ? k : o;
+        }
+    return k;
+}
+// the 64 largest of a sorted list and `rev`, a sorted list read backwards
+__device__ __forceinline__ uint64_t merge64(uint64_t list, uint64_t rev, int lane) {
+    uint64_t k = list > rev ? list : rev;
+    for (int j = 32; j > 0; j >>= 1) {
+        const uint64_t o = lane_xor(k, j);
+        k = (k > o) == ((lane & j) == 0) ? k : o;
+    }
+    return k;
 }
 
-__global__ __launch_bounds__(64) void topk_select_kernel(uint32_t Q, uint32_t K, uint32_t cap,
-                                                         uint32_t* __restrict__ cnt,
-                                                         const uint2* __restrict__ pend,
-                                                         uint2* __restrict__ best,
-                                                         uint32_t* __restrict__ best_cnt,
-                                                         float* __restrict__ theta) {
-    __shared__ float s_sc[2 * TK_LIST];
-    __shared__ uint32_t s_ix[2 * TK_LIST];
-    const uint32_t q = blockIdx.x;
-    const int t = threadIdx.x;
-    if (q >= Q) return;
-    const uint32_t n_new = min(cnt[q], cap);
-    if (n_new == 0) return;
-    const uint32_t bc = best_cnt[q];
-    {
-        const uint2 e = (uint32_t)t < bc ? best[(uint64_t)q * TK_LIST + t] : make_uint2(0u, TK_NONE);
-        s_sc[t] = (uint32_t)t < bc ? __uint_as_float(e.x) : -INFINITY;
-        s_ix[t] = e.y;
+template <bool VEC4>
+__device__ __forceinline__ float exact_score(const float* __restrict__ q, const float* __restrict__ c, uint32_t d,
+                                             float iq) {
+    float dot = 0.f, lo[8], hi[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { lo[e] = 0.f; hi[e] = 0.f; }
+    float4 x[8], nx[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = load_cols<VEC4>(c, true, 4 * i, d);
+    for (uint32_t k0 = 0; k0 < d; k0 += 32) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) nx[i] = load_cols<VEC4>(c, true, k0 + 32 + 4 * i, d);   // (zero past the row's end)
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+            const float4 y = load_cols<VEC4>(q, true, k0 + 4 * i, d);
+            dot = fmaf(y.x, x[i].x, dot); dot = fmaf(y.y, x[i].y, dot);
+            dot = fmaf(y.z, x[i].z, dot); dot = fmaf(y.w, x[i].w, dot);
+        }
+        square8(x[0], x[1], lo); square8(x[2], x[3], hi);
+        square8(x[4], x[5], lo); square8(x[6], x[7], hi);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) x[i] = nx[i];
     }
-    for (uint32_t base = 0; base < n_new; base += TK_LIST) {
-        const uint32_t e = base + t;
-        const uint2 p = e < n_new ? pend[(uint64_t)q * cap + e] : make_uint2(0u, TK_NONE);
-        s_sc[TK_LIST + t] = e < n_new ? __uint_as_float(p.x) : -INFINITY;
-        s_ix[TK_LIST + t] = p.y;
+    return dot * iq * inv_length(tree8(lo) + tree8(hi));
+}
+
+template <int WAVES, bool VEC4>
+__global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint32_t K, float tau,
+                                                               uint64_t* __restrict__ best,
+                                                               uint32_t* __restrict__ best_cnt,
+                                                               float* __restrict__ theta,
+                                                               uint32_t* __restrict__ out_idx,
+                                                               float* __restrict__ out_score,
+                                                               uint32_t* __restrict__ out_count) {
+    __shared__ uint64_t s_list[WAVES][64];
+    const uint32_t q = blockIdx.x;
+    const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const uint32_t n_new = min(a.cnt[q], a.cap), bc = best_cnt[q];
+    if (n_new == 0 && !out_idx) return;                      // uniform per block
+    const bool alone = n_new <= 64;                          // one wavefront has them all
+    if (alone && wave) return;
+    const float th = theta[q], iq = a.invq[q];
+    // (key 0 is below that of every score: an empty place)
+    uint64_t list = wave == 0 && (uint32_t)lane < bc ? best[(uint64_t)q * TK_LIST + lane] : 0ull;
+    for (uint32_t base = wave * 64u; base < n_new; base += 64u * WAVES) {
+        uint64_t k = 0;
+        if (base + lane < n_new) {
+            const uint32_t c = a.pend[(uint64_t)q * a.cap + base + lane];
+            const float s = exact_score<VEC4>(a.Qm + (uint64_t)q * a.d, a.Cm + (uint64_t)c * a.d, a.d, iq);
+            if (s > th) k = rank_key(s, c);                  // (a similarity that is no number never passes)
+        }
+        if (__ballot(k != 0)) list = merge64(list, __shfl((unsigned long long)sort64(k, lane), 63 - lane, 64), lane);
+    }
+    for (int w = alone ? 0 : WAVES / 2; w >= 1; w >>= 1) {
         __syncthreads();
-        for (int k = 2; k <= 2 * TK_LIST; k <<= 1) {
-            for (int j = k >> 1; j > 0; j >>= 1) {
-                const int i = 2 * t - (t & (j - 1)), l = i + j;
-                const bool up = (i & k) == 0;
-                const float si = s_sc[i], sl = s_sc[l];
-                const uint32_t ii = s_ix[i], il = s_ix[l];
-                const bool swap = up ? ranks_before(sl, il, si, ii) : ranks_before(si, ii, sl, il);
-                if (swap) { s_sc[i] = sl; s_ix[i] = il; s_sc[l] = si; s_ix[l] = ii; }
-                __syncthreads();
-            }
+        if (wave >= w && wave < 2 * w) s_list[wave][63 - lane] = list;
+        __syncthreads();
+        if (wave < w) list = merge64(list, s_list[wave + w][lane], lane);
+    }
+    if (wave) return;
+    const uint32_t have = min(K, (uint32_t)__popcll(__ballot(list != 0)));
+    if ((uint32_t)lane >= have) list = 0;
+    best[(uint64_t)q * TK_LIST + lane] = list;
+    const float s = key_score(list);
+    if (lane == 0) { best_cnt[q] = have; a.cnt[q] = 0u; }
+    if (have == K && (uint32_t)lane == K - 1) theta[q] = s;
+    if (out_idx) {
+        const bool ok = list != 0 && s > tau;
+        if ((uint32_t)lane < K) {
+            out_idx[(uint64_t)q * K + lane] = ok ? (uint32_t)~(uint32_t)list : TK_NONE;
+            out_score[(uint64_t)q * K + lane] = ok ? s : 0.f;
         }
+        const uint64_t mask = __ballot(ok);
+        if (lane == 0 && out_count) out_count[q] = (uint32_t)__popcll(mask);
     }
-    const uint32_t have = min((uint64_t)K, (uint64_t)bc + n_new);
-    best[(uint64_t)q * TK_LIST + t] = make_uint2(__float_as_uint(s_sc[t]), s_ix[t]);
-    if (t == 0) {
-        best_cnt[q] = have;
-        if (have == K) theta[q] = s_sc[K - 1];
-        cnt[q] = 0u;
-    }
-}
-
-// Result: the first K of the best list with similarity > tau; unused slots get TK_NONE and 0.
-__global__ __launch_bounds__(64) void topk_finish_kernel(uint32_t Q, uint32_t K, float tau,
-                                                         const uint2* __restrict__ best,
-                                                         const uint32_t* __restrict__ best_cnt,
-                                                         uint32_t* __restrict__ out_idx,
-                                                         float* __restrict__ out_score,
-                                                         uint32_t* __restrict__ out_count) {
-    const uint32_t q = blockIdx.x;
-    const uint32_t t = threadIdx.x;
-    if (q >= Q) return;
-    const uint32_t bc = best_cnt[q];
-    const uint2 e = t < bc ? best[(uint64_t)q * TK_LIST + t] : make_uint2(0u, TK_NONE);
-    const float s = __uint_as_float(e.x);
-    const bool ok = t < bc && t < K && s > tau;
-    if (t < K) {
-        out_idx[(uint64_t)q * K + t] = ok ? e.y : TK_NONE;
-        out_score[(uint64_t)q * K + t] = ok ? s : 0.f;
-    }
-    const uint64_t mask = __ballot(ok);
-    if (t == 0 && out_count) out_count[q] = (uint32_t)__popcll(mask);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -338,78 +764,145 @@ static TopkLayout topk_layout(uint32_t Q, uint32_t N) {
     L.cnt = take(sizeof(uint32_t) * Q);
     L.best_cnt = take(sizeof(uint32_t) * Q);
     L.err = take(256);
-    L.best = take(sizeof(uint2) * (size_t)Q * TK_LIST);
+    L.best = take(sizeof(uint64_t) * (size_t)Q * TK_LIST);
     L.pend = off;
     L.fixed_bytes = off;
     return L;
 }
 
+// (sized for eight bytes per query and candidate of a round; what the pending lists do not take -- four
+// bytes each -- holds the rounded rows)
 size_t topk_workspace_bytes(uint32_t Q, uint32_t N, uint32_t round_candidates) {
     uint32_t cap = ((round_candidates + TK_BC - 1) / TK_BC) * TK_BC;
-    return topk_layout(Q, N).fixed_bytes + sizeof(uint2) * (size_t)Q * cap;
+    return topk_layout(Q, N).fixed_bytes + 8 * (size_t)Q * cap;
 }
 
-uint32_t topk_round_capacity(uint32_t Q, uint32_t N, size_t workspace_bytes) {
-    const size_t fixed = topk_layout(Q, N).fixed_bytes;
-    if (workspace_bytes <= fixed) return 0;
-    size_t cap = (workspace_bytes - fixed) / (sizeof(uint2) * (size_t)Q);
-    cap = (cap / TK_BC) * TK_BC;
-    const size_t all = ((size_t)N + TK_BC - 1) / TK_BC * TK_BC;
-    return (uint32_t)(cap < all ? cap : all);
+bool topk_workspace_fits(uint32_t Q, uint32_t N, size_t workspace_bytes) {
+    return workspace_bytes >= topk_workspace_bytes(Q, N, TK_BC);
 }
 
 uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint32_t N, uint32_t d,
                              uint32_t K, float tau, uint32_t* out_idx, float* out_score,
-                             uint32_t* out_count, void* workspace, uint32_t cap, hipStream_t st) {
+                             uint32_t* out_count, void* workspace, size_t workspace_bytes, hipStream_t st) {
     const TopkLayout L = topk_layout(Q, N);
     char* ws = (char*)workspace;
-    float* invq = (float*)(ws + L.invq);
-    float* invc = (float*)(ws + L.invc);
     float* theta = (float*)(ws + L.theta);
-    uint32_t* cnt = (uint32_t*)(ws + L.cnt);
     uint32_t* best_cnt = (uint32_t*)(ws + L.best_cnt);
-    uint32_t* err = (uint32_t*)(ws + L.err);
-    uint2* best = (uint2*)(ws + L.best);
-    uint2* pend = (uint2*)(ws + L.pend);
-
-    hipLaunchKernelGGL(inv_norm_kernel, dim3(blocks_for((uint64_t)Q * 64, 256)), dim3(256), 0, st, Qm,
-                       Q, d, invq);
-    hipLaunchKernelGGL(inv_norm_kernel, dim3(blocks_for((uint64_t)N * 64, 256)), dim3(256), 0, st, Cm,
-                       N, d, invc);
-    // nothing below the threshold is ever wanted; without one, every cosine passes (-2 < -1)
-    const float theta0 = tau > -2.0f ? tau : -2.0f;
-    hipLaunchKernelGGL(topk_init_kernel, dim3(blocks_for(Q, 256)), dim3(256), 0, st, Q, theta0, theta,
-                       cnt, best_cnt, err);
+    uint64_t* best = (uint64_t*)(ws + L.best);
     TopkArgs a{};
     a.Qm = Qm; a.Cm = Cm; a.Q = Q; a.N = N; a.d = d;
-    a.invq = invq; a.invc = invc; a.theta = theta; a.cnt = cnt; a.pend = pend; a.cap = cap;
-    a.err = err;
-    // 2 x 2 tiles per wavefront at four wavefronts per SIMD (128 registers, accumulators included)
-    // measured best: 2 x 4 and 4 x 2 tiles (two wavefronts per SIMD) ran 9 % slower, 4 x 4 (one) 2.3
-    // times slower -- this kernel lives on having other wavefronts to switch to at its barriers.
-    constexpr int TK_TM = 2, TK_TN = 2, TK_WPE = 4;
-    constexpr int BQ = 64 * TK_TM, BC = 64 * TK_TN;
-    a.nq_tiles = (Q + BQ - 1) / BQ;
-    // The first rounds are short and grow fourfold: with a threshold from the first few hundred
-    // candidates only a small share of a full round's scores reaches the pending lists.
-    uint64_t len = TK_BC;
-    for (uint64_t begin = 0; begin < N; begin += len, len = (len * 4 < cap ? len * 4 : cap)) {
+    a.invq = (float*)(ws + L.invq); a.invc = (float*)(ws + L.invc); a.theta = theta;
+    a.cnt = (uint32_t*)(ws + L.cnt); a.err = (uint32_t*)(ws + L.err);
+    const bool vec4 = d % 4 == 0 && ((uintptr_t)Qm % 16 == 0) && ((uintptr_t)Cm % 16 == 0);
+
+    // The wide screen's tile: 256 queries x 128 candidates by eight wavefronts of 64 x 64, four to a SIMD.
+    // (Measured on 4096 x 2^20 x 300, whole search: 4.75 ms; 128 x 128 by four wavefronts 4.87, 256 x 256 by
+    // sixteen 4.84; wavefronts of 128 x 64, two to a SIMD, 5.05 - 5.5; of 128 x 128 alone on a SIMD 33.)
+    constexpr int TM = 2, TN = 2, WM = 4, WN = 2, WPE = 4;
+    constexpr uint32_t WIDE_Q = 32 * TM * WM, WIDE_C = 32 * TN * WN;
+    const uint64_t row_bytes = (uint64_t)topk_steps(d) * TK_KS * 2;
+    const uint64_t n_up = ((uint64_t)N + 255) / 256 * 256;
+    const uint64_t free_bytes = workspace_bytes - L.fixed_bytes;          // (fits 128 candidates of eight bytes)
+    // Which screen, and how many candidates its rounds can hold.  Up to one tile of queries the stream
+    // screen reads every candidate once; beyond, reading and rounding them again for each further tile
+    // costs more than rounding them once into the workspace -- unless that leaves only short rounds.
+    enum { FP32, STREAM, WIDE } screen = FP32;
+    uint64_t cap = free_bytes / (8ull * Q) / TK_BC * TK_BC;
+    const uint64_t q_up = ((uint64_t)Q + WIDE_Q - 1) / WIDE_Q * WIDE_Q;   // (a whole number of either screen's tiles)
+    const uint64_t q_bytes = q_up * (row_bytes + 4) + 512;
+    if (free_bytes > q_bytes) {
+        const uint64_t rest = free_bytes - q_bytes;
+        const uint64_t cap_wide = rest / (4ull * Q + row_bytes + 4) / 256 * 256, cap_stream = rest / (4ull * Q) / TK_BC * TK_BC;
+        if (Q > TK_STREAM_Q && (cap_wide >= n_up || cap_wide >= 8192)) { screen = WIDE; cap = cap_wide; }
+        else if (cap_stream >= n_up || cap_stream >= 2 * TK_BC) { screen = STREAM; cap = cap_stream; }
+    }
+    cap = cap < n_up ? cap : n_up;
+    char* at = ws + L.pend;
+    a.pend = (uint32_t*)at;
+    a.cap = (uint32_t)cap;
+    at += (cap * Q * 4 + 255) / 256 * 256;
+    void* qfrag = nullptr; float* qmargin = nullptr; void* cfrag = nullptr; float* cmargin = nullptr;
+    if (screen != FP32) {
+        qfrag = at; at += q_up * row_bytes;
+        qmargin = (float*)at; at += q_up * 4;
+        if (screen == WIDE) { cfrag = at; at += cap * row_bytes; cmargin = (float*)at; at += cap * 4; }
+    }
+    a.qfrag = qfrag; a.qmargin = qmargin; a.cfrag = cfrag; a.cmargin = cmargin;
+
+    // nothing below the threshold is ever wanted; without one, every cosine passes (-2 < -1)
+    const float theta0 = tau > -2.0f ? tau : -2.0f;
+    {
+        const dim3 grid(blocks_for(qfrag ? q_up : Q, 32)), block(64);
+#define W2V_QUERIES(F16, VEC4)                                                                             \
+    hipLaunchKernelGGL((topk_queries_kernel<F16, VEC4>), grid, block, 0, st, Qm, Q, d, theta0, (float*)a.invq, \
+                       theta, a.cnt, best_cnt, qfrag, qmargin, a.err)
+        if (screen == WIDE) { if (vec4) W2V_QUERIES(true, true); else W2V_QUERIES(true, false); }
+        else { if (vec4) W2V_QUERIES(false, true); else W2V_QUERIES(false, false); }
+#undef W2V_QUERIES
+    }
+    if (screen == FP32) {
+        const dim3 grid(blocks_for(N, 128)), block(256);
+        if (vec4) hipLaunchKernelGGL(inv_length_kernel<true>, grid, block, 0, st, Cm, N, d, (float*)a.invc);
+        else hipLaunchKernelGGL(inv_length_kernel<false>, grid, block, 0, st, Cm, N, d, (float*)a.invc);
+    }
+    // Short rounds first: with a threshold from the first few hundred candidates only a small share of a
+    // full round's scores reaches the pending lists.  Many queries: rounds grow fourfold from 256 (every
+    // pair listed costs a row read).  Few: sixteenfold from 1024 -- there launches cost more than pairs.
+    const uint64_t growth = screen == STREAM ? 16 : 4;
+    uint64_t len = screen == FP32 ? TK_BC : (screen == STREAM ? 1024 : 256);
+    for (uint64_t begin = 0; begin < N; begin += len, len = len * growth < cap ? len * growth : cap) {
         if (len > cap) len = cap;
         a.c_begin = (uint32_t)begin;
         a.c_end = (uint32_t)(begin + len < N ? begin + len : N);
-        a.nc_tiles = (a.c_end - a.c_begin + BC - 1) / BC;
-        const uint32_t total = a.nq_tiles * a.nc_tiles;
-        const dim3 grid(((total + 7u) / 8u) * 8u), block(TK_THREADS);
-        if (d % 4 == 0 && ((uintptr_t)Qm % 16 == 0) && ((uintptr_t)Cm % 16 == 0))
-            hipLaunchKernelGGL((topk_scores_kernel<TK_TM, TK_TN, TK_WPE, true>), grid, block, 0, st, a);
-        else
-            hipLaunchKernelGGL((topk_scores_kernel<TK_TM, TK_TN, TK_WPE, false>), grid, block, 0, st, a);
-        hipLaunchKernelGGL(topk_select_kernel, dim3(Q), dim3(64), 0, st, Q, K, cap, cnt, pend, best,
-                           best_cnt, theta);
+        const uint32_t m = a.c_end - a.c_begin;
+        a.dense_test = begin >= 32ull * K;         // (earlier, hits are many because the thresholds are low)
+        if (screen == WIDE) {
+            a.nq_tiles = (Q + WIDE_Q - 1) / WIDE_Q;
+            a.nc_tiles = (m + WIDE_C - 1) / WIDE_C;
+            const uint32_t tiles = a.nc_tiles * (WIDE_C / 32), total = a.nq_tiles * a.nc_tiles;
+            const dim3 grid(((total + 7u) / 8u) * 8u), block(64 * WM * WN);
+#define W2V_ROUND(VEC4, HOLD)                                                                              \
+    hipLaunchKernelGGL((topk_round_kernel<VEC4, HOLD>), dim3(tiles), dim3(64), 0, st, Cm, a.c_begin, a.c_end, d, \
+                       (float*)a.invc, cfrag, cmargin)
+            if (vec4 && topk_steps(d) <= TK_HOLD) W2V_ROUND(true, TK_HOLD);
+            else if (vec4) W2V_ROUND(true, 0);
+            else W2V_ROUND(false, 0);
+#undef W2V_ROUND
+            if (vec4) hipLaunchKernelGGL((topk_wide_kernel<TM, TN, WM, WN, WPE, true>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((topk_wide_kernel<TM, TN, WM, WN, WPE, false>), grid, block, 0, st, a);
+        } else if (screen == STREAM) {
+            const uint32_t tq = Q <= 32 ? 1 : (Q <= 64 ? 2 : 4);
+            a.nc_tiles = (m + 31) / 32;
+            const dim3 grid(blocks_for(a.nc_tiles, 4), blocks_for(Q, 32 * tq)), block(256);
+#define W2V_STREAM(TQ)                                                                                     \
+    do {                                                                                                   \
+        if (vec4) hipLaunchKernelGGL((topk_stream_kernel<TQ, true>), grid, block, 0, st, a);               \
+        else hipLaunchKernelGGL((topk_stream_kernel<TQ, false>), grid, block, 0, st, a);                   \
+    } while (0)
+            if (tq == 1) W2V_STREAM(1); else if (tq == 2) W2V_STREAM(2); else W2V_STREAM(4);
+#undef W2V_STREAM
+        } else {
+            // 2 x 2 tiles per wavefront at four wavefronts per SIMD (128 registers, accumulators included)
+            // measured best: 2 x 4 and 4 x 2 tiles (two wavefronts per SIMD) ran 9 % slower, 4 x 4 (one) 2.3
+            // times slower -- this kernel lives on having other wavefronts to switch to at its barriers.
+            constexpr int TK_TM = 2, TK_TN = 2, TK_WPE = 4;
+            a.nq_tiles = (Q + TK_BQ - 1) / TK_BQ;
+            a.nc_tiles = (m + TK_BC - 1) / TK_BC;
+            const uint32_t total = a.nq_tiles * a.nc_tiles;
+            const dim3 grid(((total + 7u) / 8u) * 8u), block(TK_THREADS);
+            if (vec4) hipLaunchKernelGGL((topk_scores_kernel<TK_TM, TK_TN, TK_WPE, true>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((topk_scores_kernel<TK_TM, TK_TN, TK_WPE, false>), grid, block, 0, st, a);
+        }
+        const bool last = begin + len >= N;
+        uint32_t* oi = last ? out_idx : nullptr;
+#define W2V_FOLD(WAVES, VEC4)                                                                              \
+    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4>), dim3(Q), dim3(64 * WAVES), 0, st, a, K, tau, best, \
+                       best_cnt, theta, oi, out_score, out_count)
+        if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(4, true); else W2V_FOLD(4, false); }
+        else { if (vec4) W2V_FOLD(16, true); else W2V_FOLD(16, false); }
+#undef W2V_FOLD
     }
-    hipLaunchKernelGGL(topk_finish_kernel, dim3(Q), dim3(64), 0, st, Q, K, tau, best, best_cnt,
-                       out_idx, out_score, out_count);
-    return err;
+    return a.err;
 }
 
 }  // namespace w2v

@@ -187,3 +187,66 @@ def test_export_rows_bit_exact():
     assert e.value.code == -6
     for sh in shards + fresh:
         sh.destroy()
+
+
+# ---- the screens: which pairs are looked at must not show in the results --------------------------
+
+
+def screens_agree(Qm, C, K, tau):
+    """The default workspace (16-bit screens) and the smallest (fp32 scores, rounds of 128): same bits."""
+    q, c = torch.from_numpy(Qm).cuda(), torch.from_numpy(C).cuda()
+    small = torch.empty(int(w2v.lib().w2v_topk_cosine_workspace(Qm.shape[0], C.shape[0], 128)),
+                        dtype=torch.uint8, device="cuda")
+    a = [t.cpu().numpy() for t in w2v.topk_cosine(q, c, K, tau)]
+    b = [t.cpu().numpy() for t in w2v.topk_cosine(q, c, K, tau, workspace=small)]
+    for x, y in zip(a, b):
+        assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+    return a[0].view(np.uint32), a[1], a[2]
+
+
+@pytest.mark.parametrize("Q", [1, 31, 33, 65, 128, 129, 257])          # tiles of 32, 64, 128 (stream), 256 (wide)
+@pytest.mark.parametrize("N,d", [(129, 3), (1025, 16), (5000, 300), (20001, 102), (3000, 324), (1500, 1000)])
+def test_screens_list_every_pair_that_counts(Q, N, d):
+    Qm = workloads.embedding_like(Q, d, 11, n_clusters=40)
+    C = workloads.embedding_like(N, d, 12, n_clusters=40)
+    gi, gs, gc = screens_agree(Qm, C, 30, -2.0)
+    if N * Q * d < 10 ** 9:
+        check_topk(Qm, C, 30, -2.0, gi, gs, gc)
+    screens_agree(Qm, C, 64, 0.2)
+
+
+@pytest.mark.parametrize("Q,N", [(7, 9000), (200, 9000)])
+@pytest.mark.parametrize("spread", [0.0, 1e-4, 1e-2])
+def test_crowded_similarities(Q, N, spread):
+    """Similarities closer together than the 16-bit margin, down to equal ones (ranked by index)."""
+    rng = np.random.default_rng(5)
+    base = rng.standard_normal(60)
+    Qm = (base + spread * rng.standard_normal((Q, 60))).astype(np.float32)
+    C = (base + spread * rng.standard_normal((N, 60))).astype(np.float32)
+    gi, gs, _ = screens_agree(Qm, C, 30, -2.0)
+    if spread == 0.0:
+        assert np.array_equal(gi, np.tile(np.arange(30, dtype=np.uint32), (Q, 1)))
+
+
+@pytest.mark.parametrize("Q", [40, 140])
+def test_rows_without_a_usable_length(Q):
+    """Zero, tiny, huge, infinite and NaN rows on either side."""
+    rng = np.random.default_rng(6)
+    d, N = 50, 4000
+    Qm, C = rng.standard_normal((Q, d)).astype(np.float32), rng.standard_normal((N, d)).astype(np.float32)
+    for M in (Qm, C):
+        M[1] = 0
+        M[2] *= 1e-17                      # squares underflow in part
+        M[3] *= 1e-25                      # and altogether
+        M[4] *= 3e19                       # squares overflow
+        M[5, 7] = np.inf
+        M[6, 7] = np.nan
+        M[7, :] = 1e-44
+        M[8] *= 1e18
+        M[9, 3:] = 0
+        M[10, 1:] *= 1e-9
+    C[2000:2100] = C[100]
+    C[3000:] = 0
+    for tau in (-2.0, 0.0, 0.1):
+        _, gs, _ = screens_agree(Qm, C, 40, tau)
+        assert not np.isnan(gs).any()
