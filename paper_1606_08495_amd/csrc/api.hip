@@ -155,7 +155,7 @@ struct w2v_shard {
     // `side` so that the current step's own second-stream work does not queue up behind it
     hipStream_t ahead = nullptr;
     hipEvent_t ev_fork = nullptr, ev_keys = nullptr, ev_join = nullptr;
-    hipEvent_t ev_coeffs = nullptr, ev_wdone = nullptr, ev_tails = nullptr;
+    hipEvent_t ev_coeffs = nullptr, ev_tails = nullptr;
     bool overlap = true;
     bool own_rows = true;           // fused step: singly named output rows updated by the input side
     bool last_update_fused = true;  // what the last update on this shard was: an announced minibatch
@@ -301,9 +301,9 @@ Plan make_plan(char* base, uint32_t n, uint32_t k, uint32_t stride4_max, uint32_
         p.delta = c.take<float>((size_t)n * row);
         p.dkey = c.take<uint32_t>(n);
         p.slots_u1 = slots_after(n, useg_pairs_per_chunk(p.T, 1, n));    // the most any shard needs
-        p.slots_w1 = slots_after(p.M, wseg_entries_per_chunk());
-        uint32_t s2u = slots_after(p.slots_u1, tail_entries_per_chunk());
-        uint32_t s2w = slots_after(p.slots_w1, tail_entries_per_chunk());
+        p.slots_w1 = slots_after(p.M, wseg_entries_per_chunk(p.M));
+        uint32_t s2u = slots_after(p.slots_u1, tail_entries_least());    // the most any shard needs
+        uint32_t s2w = slots_after(p.slots_w1, tail_entries_least());
         p.slots_2 = std::max(s2u, s2w);
         p.pa_rows = c.take<float>((size_t)p.slots_u1 * row); p.pa_keys = c.take<uint32_t>(p.slots_u1 + 1);
         p.pb_rows = c.take<float>((size_t)p.slots_w1 * row); p.pb_keys = c.take<uint32_t>(p.slots_w1 + 1);
@@ -314,20 +314,14 @@ Plan make_plan(char* base, uint32_t n, uint32_t k, uint32_t stride4_max, uint32_
     return p;
 }
 
-// Reduce the partial slots of one side level by level into matrix M (in place) -- or, for the
-// input side of the skip-gram step (defer_rows given), into the delta buffer, so that these passes
-// need not wait for the output side to finish reading M.
+// Reduce the partial slots of one side level by level into matrix M (in place).
 void run_tails(w2v_shard* sh, float* M, float alpha, float* rows_a, uint32_t* keys_a, uint32_t slots,
-               float* rows_b, uint32_t* keys_b, hipStream_t st, float* defer_rows = nullptr,
-               uint32_t* defer_keys = nullptr, uint32_t cp = 0, const CallScalars* dev = nullptr) {
+               float* rows_b, uint32_t* keys_b, hipStream_t st) {
     float* src_rows = rows_a; uint32_t* src_keys = keys_a;
     float* dst_rows = rows_b; uint32_t* dst_keys = keys_b;
-    uint32_t level = 0;
     while (slots > 0) {
-        TailArgs t{M, sh->g, alpha, src_rows, src_keys, slots, dst_rows, dst_keys};
-        t.defer_rows = defer_rows; t.defer_keys = defer_keys; t.level = ++level; t.cp = cp; t.dev = dev;
-        launch_tail(t, st);
-        slots = slots_after(slots, tail_entries_per_chunk());
+        launch_tail(TailArgs{M, sh->g, alpha, src_rows, src_keys, slots, dst_rows, dst_keys}, st);
+        slots = slots_after(slots, tail_entries_per_chunk(sh->g.d4));
         std::swap(src_rows, dst_rows);
         std::swap(src_keys, dst_keys);
     }
@@ -341,7 +335,6 @@ int ensure_side_stream(w2v_shard* sh) {
     HIP_TRY(hipEventCreateWithFlags(&sh->ev_keys, hipEventDisableTiming));
     HIP_TRY(hipEventCreateWithFlags(&sh->ev_join, hipEventDisableTiming));
     HIP_TRY(hipEventCreateWithFlags(&sh->ev_coeffs, hipEventDisableTiming));
-    HIP_TRY(hipEventCreateWithFlags(&sh->ev_wdone, hipEventDisableTiming));
     HIP_TRY(hipEventCreateWithFlags(&sh->ev_tails, hipEventDisableTiming));
     return W2V_OK;
 }
@@ -379,20 +372,21 @@ int ensure_set(w2v_shard* sh, IndexSet& x, uint32_t n, uint32_t M) {
 
 // Everything adjust needs before its first row kernel: the checked input words, the destination
 // keys (positive word + regenerated negatives) and both sorts.
-// The input-side kernel needs the keys and the (small) input-side sort; the output-side sort is only
-// needed later.  So the key generation and the output-side sort are queued on the shard's second
-// stream, forked from the caller's stream by an event, while the caller's stream checks the inputs
-// and sorts the input side; the caller's stream then waits for the keys (ev_keys) and, just before
-// the first kernel that reads the output-side order, for that sort (join_output_sort).
+// The fused step's input-side kernel needs both sorts (it updates the output rows that one slot names),
+// so there everything is queued on the caller's stream, both sides' keys through the same launches.
+// With given coefficients that kernel needs the keys and the (small) input-side sort only: key
+// generation and output-side sort are queued on the shard's second stream, forked by an event, while
+// the caller's stream checks the inputs and sorts the input side; it then waits for the keys, and just
+// before the first kernel that reads the output-side order for that sort (*join, join_output_sort).
 int queue_keys_and_sorts(w2v_shard* sh, Plan& p, const uint32_t* in_idx, const uint32_t* out_idx,
                          uint32_t k, uint64_t seed, uint32_t** sku, uint32_t** perm, uint32_t** skw,
-                         uint32_t** sidx, hipStream_t st) {
+                         uint32_t** sidx, bool* join, hipStream_t st) {
     const uint32_t bits = key_bits(sh->V);
+    *join = false;
 
     const NoiseTable nt{sh->bins, sh->V};
-    if (!sh->overlap) {
-        // one stream: keys, checked inputs and both fills in one launch, then the two sides' keys
-        // through the same sort launches
+    if (!sh->overlap || p.own_rows) {
+        // keys, checked inputs and both fills in one launch
         const SortJob jobs[2] = {{p.keys, p.M, p.wb0, p.wb1, skw, sidx},
                                  {p.in_safe, p.n, p.ub0, p.ub1, sku, perm}};
         {
@@ -413,33 +407,28 @@ int queue_keys_and_sorts(w2v_shard* sh, Plan& p, const uint32_t* in_idx, const u
         if (p.own_rows) launch_mark_alone(*skw, *sidx, p.M, p.keys, st);
         return W2V_OK;
     }
-    hipStream_t wst = st;
-    if (sh->overlap) {
-        int rc = ensure_side_stream(sh);
-        if (rc) return rc;
-        HIP_TRY(hipEventRecord(sh->ev_fork, st));
-        HIP_TRY(hipStreamWaitEvent(sh->side, sh->ev_fork, 0));
-        wst = sh->side;
-    }
+    int rc = ensure_side_stream(sh);
+    if (rc) return rc;
+    hipStream_t wst = sh->side;
+    HIP_TRY(hipEventRecord(sh->ev_fork, st));
+    HIP_TRY(hipStreamWaitEvent(wst, sh->ev_fork, 0));
     {
         Phase ph(sh, W2V_PH_NEG, wst);
         launch_dest_keys(nt, out_idx, p.n, k, seed, p.keys, sh->err, wst, sh->call_dev);
     }
-    if (sh->overlap) HIP_TRY(hipEventRecord(sh->ev_keys, sh->side));
+    HIP_TRY(hipEventRecord(sh->ev_keys, wst));
     {
         Phase ph(sh, W2V_PH_SORT, wst);
         launch_sort_pairs(p.keys, p.wb0, p.wb1, p.M, bits, p.sort_tmp, skw, sidx, sh->err, wst);
-        // fused single-shard step: output rows named by one slot only are updated by the
-        // input-side kernel (which then has to wait for this sort) and skipped by the output side
-        if (p.own_rows) launch_mark_alone(*skw, *sidx, p.M, p.keys, wst);
     }
-    if (sh->overlap) HIP_TRY(hipEventRecord(sh->ev_join, sh->side));
+    HIP_TRY(hipEventRecord(sh->ev_join, wst));
     {
         Phase ph(sh, W2V_PH_SORT, st);
         launch_check_inputs(in_idx, p.n, sh->V, p.in_safe, sh->err, st);
         launch_sort_pairs(p.in_safe, p.ub0, p.ub1, p.n, bits, p.sort_tmp_u, sku, perm, sh->err, st);
     }
-    if (sh->overlap) HIP_TRY(hipStreamWaitEvent(st, p.own_rows ? sh->ev_join : sh->ev_keys, 0));
+    HIP_TRY(hipStreamWaitEvent(st, sh->ev_keys, 0));
+    *join = true;
     return W2V_OK;
 }
 
@@ -510,73 +499,105 @@ void join_output_sort(w2v_shard* sh, hipStream_t st) {
     if (sh->overlap && sh->side) (void)hipStreamWaitEvent(st, sh->ev_join, 0);
 }
 
-// First part of a shard's update, the same on one stream or several: the output-side kernel's border
-// slots are cleared here, ahead of the input-side kernel, so that the two row kernels follow each
-// other with nothing in between (unless the call's first launch has cleared them already: good for
-// one shard's update); then the input-side kernel.
-void queue_input_side(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* sku,
-                      const uint32_t* perm, const float* coeffs_in, float* coeffs_out, bool fused,
-                      float alpha, bool keep_dots, hipStream_t st) {
-    if (p.wfill_done) p.wfill_done = false;
-    else launch_wseg_fill(p.pb_keys, p.M, st);
-    Phase ph(ws_owner, W2V_PH_USIDE, st);
-    USideArgs a{};
-    a.U = sh->U; a.W = sh->W; a.g = sh->g; a.skey = sku; a.perm = perm; a.keys = p.keys;
-    a.n = p.n; a.T = p.T; a.coeffs_in = coeffs_in; a.coeffs_out = coeffs_out;
-    a.dots_out = (fused && keep_dots) ? p.dots : nullptr; a.delta = p.delta; a.dkey = p.dkey;
-    a.prows = p.pa_rows; a.pkeys = p.pa_keys; a.fused = fused;
-    if (p.own_rows) { a.W_update = sh->W; a.alpha = alpha; }
-    a.dev = ws_owner->call_dev;
-    launch_useg(a, st);
-}
-
-// The same update on ONE stream (a captured step, or a shard told not to use its second stream),
-// for the row geometries that have the joint launch: after the input-side kernel, each launch
-// carries one walk of the output side together with one higher level of the input side and one
-// step of the loss, which depend on different things; the delta buffer is written back last.
-// Same kernels' code on the same data as queue_adjust below: the same bits.
-void queue_adjust_one_stream(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* sku,
-                             const uint32_t* perm, const uint32_t* skw, const uint32_t* sidx,
-                             const float* coeffs_in, float* coeffs_out, bool fused, float alpha,
-                             double* loss_out, hipStream_t st) {
-    queue_input_side(ws_owner, sh, p, sku, perm, coeffs_in, coeffs_out, fused, alpha, loss_out != nullptr, st);
-    const uint32_t cp = useg_pairs_per_chunk(p.T, sh->g.d4, p.n);
+// The update of one shard from given coefficients (or, fused, from its own dots; loss_out: fused form
+// only).  The input-side kernel first (it also clears the output side's border slots, unless the call's
+// first launch has: good for one shard's update); then launches that each carry one walk of the output
+// side together with one higher level of the input side and one step of the loss, which depend on
+// different things.  The input side's levels park their sums in the delta buffer, which is written back
+// beside the first output-side level after they are done (and after the level-1 walk, which reads U).
+// `join_sorts`: the output-side order comes from the shard's second stream.
+void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* sku,
+                  const uint32_t* perm, const uint32_t* skw, const uint32_t* sidx,
+                  const float* coeffs_in, float* coeffs_out, bool fused, float alpha,
+                  double* loss_out, bool join_sorts, hipStream_t st) {
+    const CallScalars* dev = ws_owner->call_dev;
+    {
+        Phase ph(ws_owner, W2V_PH_USIDE, st);
+        USideArgs a{};
+        a.U = sh->U; a.W = sh->W; a.g = sh->g; a.skey = sku; a.perm = perm; a.keys = p.keys;
+        a.n = p.n; a.T = p.T; a.coeffs_in = coeffs_in; a.coeffs_out = coeffs_out;
+        a.dots_out = (fused && loss_out) ? p.dots : nullptr; a.delta = p.delta; a.dkey = p.dkey;
+        a.prows = p.pa_rows; a.pkeys = p.pa_keys; a.fused = fused;
+        if (p.own_rows) { a.W_update = sh->W; a.alpha = alpha; }
+        a.dev = dev;
+        if (!p.wfill_done) {
+            const FillJob f = wseg_fill_job(p.pb_keys, p.M);
+            a.clear_keys = f.p; a.clear_count = f.count;
+        }
+        p.wfill_done = false;
+        launch_useg(a, st);
+    }
+    if (join_sorts) join_output_sort(ws_owner, st);
+    const uint32_t cp = useg_pairs_per_chunk(p.T, sh->g.d4, p.n);      // this shard's chunk size
     struct Side { float* src_rows; uint32_t* src_keys; float* dst_rows; uint32_t* dst_keys; uint32_t slots, level; };
     Side us{p.pa_rows, p.pa_keys, p.pe_rows, p.pe_keys, slots_after(p.n, cp), 0u};
     Side ws{p.pb_rows, p.pb_keys, p.pc_rows, p.pc_keys, p.slots_w1, 0u};
     uint32_t loss_step = (loss_out && fused) ? 1u : 0u;
-    if (loss_step && (uint64_t)p.n * p.T > 256ull * adjust_stage_loss_blocks_max()) {
-        Phase ph(ws_owner, W2V_PH_COEFF, st);                 // too many terms for one final block
-        launch_loss_from_dots(p.dots, p.n, p.T, p.loss_tmp, loss_out, st);
-        loss_step = 0;
-    }
-    auto advance = [](Side& x) {
-        x.slots = slots_after(x.slots, tail_entries_per_chunk());
+    bool applied = false;
+    auto advance = [&](Side& x) {
+        x.slots = slots_after(x.slots, tail_entries_per_chunk(sh->g.d4));
         std::swap(x.src_rows, x.dst_rows);
         std::swap(x.src_keys, x.dst_keys);
     };
-    for (bool first = true; first || us.slots || ws.slots || loss_step; first = false) {
+    auto input_level = [&]() {
+        TailArgs t{sh->U, sh->g, alpha, us.src_rows, us.src_keys, us.slots, us.dst_rows, us.dst_keys};
+        t.defer_rows = p.delta; t.defer_keys = p.dkey; t.level = ++us.level; t.cp = cp; t.dev = dev;
+        return t;
+    };
+    const ApplyDelta apply{sh->U, p.delta, p.dkey, p.n, alpha, dev};
+    WSideArgs w{};
+    w.U = sh->U; w.W = sh->W; w.g = sh->g; w.skey = skw; w.sidx = sidx; w.M = p.M; w.T = p.T;
+    w.in_idx = p.in_safe; w.coeffs = fused ? coeffs_out : coeffs_in; w.alpha = alpha;
+    w.prows = p.pb_rows; w.pkeys = p.pb_keys; w.skip_alone = p.own_rows; w.dev = dev;
+    const bool alone = adjust_walk_alone(p.M, sh->g);
+    if (alone) {
+        // A large minibatch: the input side's levels and the loss run beside the output side's walk on the
+        // second stream (the same launches on one stream: the same bits), so that only the output side's
+        // levels and the write-back follow that walk.
+        const bool two = ws_owner->overlap && ensure_side_stream(ws_owner) == W2V_OK;
+        hipStream_t side = two ? ws_owner->side : st;
+        if (two) {
+            (void)hipEventRecord(ws_owner->ev_coeffs, st);
+            (void)hipStreamWaitEvent(side, ws_owner->ev_coeffs, 0);
+        }
+        if (loss_step) {
+            Phase ph(ws_owner, W2V_PH_COEFF, side);
+            launch_loss_from_dots(p.dots, p.n, p.T, p.loss_tmp, loss_out, side);
+            loss_step = 0;
+        }
+        {
+            Phase ph(ws_owner, W2V_PH_APPLY, side);
+            while (us.slots) {
+                launch_input_tail(input_level(), side);
+                advance(us);
+            }
+        }
+        if (two) (void)hipEventRecord(ws_owner->ev_tails, side);
+        {
+            Phase ph(ws_owner, W2V_PH_WSIDE, st);
+            launch_wseg(w, st, true);
+        }
+        if (two) (void)hipStreamWaitEvent(st, ws_owner->ev_tails, 0);
+    }
+    for (bool first = !alone, any = true; any; first = false) {
         Phase ph(ws_owner, first ? W2V_PH_WSIDE : W2V_PH_APPLY, st);
         AdjustStage x;
-        WSideArgs w{};
+        x.g = sh->g;
         TailArgs wt{}, ut{};
         const bool w_level = !first && ws.slots > 0, u_level = us.slots > 0;
         if (first) {
-            w.U = sh->U; w.W = sh->W; w.g = sh->g; w.skey = skw; w.sidx = sidx; w.M = p.M; w.T = p.T;
-            w.in_idx = p.in_safe; w.coeffs = fused ? coeffs_out : coeffs_in; w.alpha = alpha;
-            w.prows = p.pb_rows; w.pkeys = p.pb_keys; w.skip_alone = p.own_rows;
-            w.dev = ws_owner->call_dev;
             x.wfirst = &w;
         } else if (w_level) {
             wt = TailArgs{sh->W, sh->g, alpha, ws.src_rows, ws.src_keys, ws.slots, ws.dst_rows, ws.dst_keys};
-            wt.level = ++ws.level; wt.dev = ws_owner->call_dev;
+            wt.level = ++ws.level; wt.dev = dev;
             x.wtail = &wt;
         }
         if (u_level) {
-            ut = TailArgs{sh->U, sh->g, alpha, us.src_rows, us.src_keys, us.slots, us.dst_rows, us.dst_keys};
-            ut.defer_rows = p.delta; ut.defer_keys = p.dkey; ut.level = ++us.level; ut.cp = cp;
-            ut.dev = ws_owner->call_dev;
+            ut = input_level();
             x.utail = &ut;
+        } else if (!first && !applied) {
+            x.apply = &apply;
+            applied = true;
         }
         if (loss_step) {
             x.loss_step = loss_step; x.dots = p.dots; x.n = p.n; x.T = p.T;
@@ -586,76 +607,8 @@ void queue_adjust_one_stream(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const 
         launch_adjust_stage(x, st);
         if (w_level) advance(ws);
         if (u_level) advance(us);
+        any = us.slots || ws.slots || loss_step || !applied;
     }
-    {
-        Phase ph(ws_owner, W2V_PH_APPLY, st);
-        launch_apply_delta(sh->U, sh->g, p.delta, p.dkey, p.n, alpha, st, ws_owner->call_dev);
-    }
-}
-
-// The update of one shard from given coefficients (or, fused, from its own dots).
-// After the input-side kernel the coefficients and the input side's partial sums exist, so the
-// minibatch loss (if asked for, fused form only) and the input side's higher reduction levels --
-// which park their results in the delta buffer and leave the input matrix alone -- run on the
-// second stream beside the output-side kernel.  After that kernel the output side's higher levels
-// follow on the caller's stream while the second stream writes the delta buffer back; the
-// caller's stream finally waits for the second one.
-void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* sku,
-                  const uint32_t* perm, const uint32_t* skw, const uint32_t* sidx,
-                  const float* coeffs_in, float* coeffs_out, bool fused, float alpha,
-                  double* loss_out, hipStream_t st) {
-    // (loss_out: fused form only; the dots it is formed from go to p.dots)
-    const bool two = ws_owner->overlap && ws_owner->side;
-    if (!two && adjust_stage_supported(sh->g.d4))
-        return queue_adjust_one_stream(ws_owner, sh, p, sku, perm, skw, sidx, coeffs_in, coeffs_out, fused,
-                                       alpha, loss_out, st);
-    hipStream_t side = two ? ws_owner->side : st;
-    queue_input_side(ws_owner, sh, p, sku, perm, coeffs_in, coeffs_out, fused, alpha, loss_out != nullptr, st);
-    // The input side's higher levels only touch its slots and the delta buffer, and the loss only
-    // reads the coefficients: both go to the second stream and run beside the output-side kernel.
-    if (two) {
-        (void)hipEventRecord(ws_owner->ev_coeffs, st);
-        (void)hipStreamWaitEvent(side, ws_owner->ev_coeffs, 0);
-    }
-    if (loss_out && fused) {
-        Phase ph(ws_owner, W2V_PH_COEFF, side);
-        launch_loss_from_dots(p.dots, p.n, p.T, p.loss_tmp, loss_out, side);
-    }
-    {
-        Phase ph(ws_owner, W2V_PH_APPLY, side);
-        const uint32_t cp = useg_pairs_per_chunk(p.T, sh->g.d4, p.n);      // this shard's chunk size
-        run_tails(sh, sh->U, alpha, p.pa_rows, p.pa_keys, slots_after(p.n, cp), p.pe_rows, p.pe_keys,
-                  side, p.delta, p.dkey, cp, ws_owner->call_dev);
-    }
-    join_output_sort(ws_owner, st);
-    {
-        Phase ph(ws_owner, W2V_PH_WSIDE, st);
-        WSideArgs w{};
-        w.U = sh->U; w.W = sh->W; w.g = sh->g; w.skey = skw; w.sidx = sidx; w.M = p.M; w.T = p.T;
-        w.in_idx = p.in_safe; w.coeffs = fused ? coeffs_out : coeffs_in; w.alpha = alpha;
-        w.prows = p.pb_rows; w.pkeys = p.pb_keys;
-        w.skip_alone = p.own_rows;
-        w.dev = ws_owner->call_dev;
-        launch_wseg(w, st, true);
-    }
-    // After the output-side kernel: its higher levels stay on the caller's stream (no wait in
-    // between), the write-back of the delta buffer goes to the second stream, behind the input
-    // side's levels there.
-    if (two) {
-        (void)hipEventRecord(ws_owner->ev_wdone, st);
-        (void)hipStreamWaitEvent(side, ws_owner->ev_wdone, 0);
-    }
-    {
-        Phase ph(ws_owner, W2V_PH_APPLY, side);
-        launch_apply_delta(sh->U, sh->g, p.delta, p.dkey, p.n, alpha, side, ws_owner->call_dev);
-    }
-    if (two) (void)hipEventRecord(ws_owner->ev_tails, side);
-    {
-        Phase ph(ws_owner, W2V_PH_APPLY, st);
-        run_tails(sh, sh->W, alpha, p.pb_rows, p.pb_keys, p.slots_w1, p.pc_rows, p.pc_keys, st, nullptr,
-                  nullptr, 0, ws_owner->call_dev);
-    }
-    if (two) (void)hipStreamWaitEvent(st, ws_owner->ev_tails, 0);
 }
 
 }  // namespace
@@ -758,7 +711,6 @@ extern "C" int w2v_shard_destroy(w2v_shard* sh) {
     if (sh->ev_keys) (void)hipEventDestroy(sh->ev_keys);
     if (sh->ev_join) (void)hipEventDestroy(sh->ev_join);
     if (sh->ev_coeffs) (void)hipEventDestroy(sh->ev_coeffs);
-    if (sh->ev_wdone) (void)hipEventDestroy(sh->ev_wdone);
     if (sh->ev_tails) (void)hipEventDestroy(sh->ev_tails);
     if (sh->ev_pfork) (void)hipEventDestroy(sh->ev_pfork);
     for (auto& x : sh->sets) {
@@ -1006,6 +958,7 @@ extern "C" int w2v_adjust(w2v_shard* sh, const uint32_t* in_idx, const uint32_t*
     if (rc) return rc;
     Plan p = make_plan(sh->ws, n, k, sh->g.stride4, 0, true, false);
     uint32_t *sku, *perm, *skw, *sidx;
+    bool join = false;
     sh->last_update_fused = false;
     const int ahead = find_prepared(sh, in_idx, out_idx, n, k, seed);
     sh->updates++;
@@ -1018,10 +971,10 @@ extern "C" int w2v_adjust(w2v_shard* sh, const uint32_t* in_idx, const uint32_t*
         p.keys = x.keys; p.in_safe = x.in_safe;
         sku = x.sku; perm = x.perm; skw = x.skw; sidx = x.sidx;
     } else {
-        rc = queue_keys_and_sorts(sh, p, in_idx, out_idx, k, seed, &sku, &perm, &skw, &sidx, st);
+        rc = queue_keys_and_sorts(sh, p, in_idx, out_idx, k, seed, &sku, &perm, &skw, &sidx, &join, st);
         if (rc) return rc;
     }
-    queue_adjust(sh, sh, p, sku, perm, skw, sidx, coeffs, nullptr, false, alpha, nullptr, st);
+    queue_adjust(sh, sh, p, sku, perm, skw, sidx, coeffs, nullptr, false, alpha, nullptr, join, st);
     HIP_TRY(hipGetLastError());
     return W2V_OK;
 }
@@ -1061,6 +1014,7 @@ extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const u
     if (rc) return rc;
     Plan p = make_plan(s0->ws, n, k, stride_max, S_dots, true, true, own);
     uint32_t *sku, *perm, *skw, *sidx;
+    bool join = false;
     // a set computed by w2v_prefetch_minibatch on shard 0 (every shard holds the same noise table)
     s0->last_update_fused = fused;
     const int ahead = find_prepared(s0, in_idx, out_idx, n, k, seed);
@@ -1072,11 +1026,11 @@ extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const u
         p.keys = x.keys; p.in_safe = x.in_safe; p.own_rows = fused && s0->prep[ahead].own_rows;
         sku = x.sku; perm = x.perm; skw = x.skw; sidx = x.sidx;
     } else {
-        rc = queue_keys_and_sorts(s0, p, in_idx, out_idx, k, seed, &sku, &perm, &skw, &sidx, st);
+        rc = queue_keys_and_sorts(s0, p, in_idx, out_idx, k, seed, &sku, &perm, &skw, &sidx, &join, st);
         if (rc) return rc;
     }
     if (fused) {
-        queue_adjust(s0, s0, p, sku, perm, skw, sidx, nullptr, p.coeffs, true, alpha, loss, st);
+        queue_adjust(s0, s0, p, sku, perm, skw, sidx, nullptr, p.coeffs, true, alpha, loss, join, st);
     } else {
         PartialPtrs pp{};
         {
@@ -1092,7 +1046,7 @@ extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const u
             launch_coeffs(pp, S, n, p.T, p.coeffs, p.loss_tmp, loss, st);
         }
         for (uint32_t s = 0; s < S; ++s)
-            queue_adjust(s0, shards[s], p, sku, perm, skw, sidx, p.coeffs, nullptr, false, alpha, nullptr, st);
+            queue_adjust(s0, shards[s], p, sku, perm, skw, sidx, p.coeffs, nullptr, false, alpha, nullptr, join, st);
     }
     HIP_TRY(hipGetLastError());
     return W2V_OK;
@@ -1283,10 +1237,10 @@ CbowPlan make_cbow_plan(char* base, uint32_t n, uint32_t k, uint32_t m, uint32_t
         p.cb0 = c.take<uint2>(m); p.cb1 = c.take<uint2>(m);
         p.sort_tmp_c = c.take<uint32_t>(sort_scratch_u32(m));
         p.slots_a = slots_after(n, useg_pairs_per_chunk(p.T, 1, n));
-        p.slots_w1 = slots_after(p.M, wseg_entries_per_chunk());
-        p.slots_c1 = slots_after(m, wseg_entries_per_chunk());
-        p.slots_2 = std::max(slots_after(p.slots_w1, tail_entries_per_chunk()),
-                             slots_after(p.slots_c1, tail_entries_per_chunk()));
+        p.slots_w1 = slots_after(p.M, wseg_entries_per_chunk(p.M));
+        p.slots_c1 = slots_after(m, wseg_entries_per_chunk(m));
+        p.slots_2 = std::max(slots_after(p.slots_w1, tail_entries_least()),
+                             slots_after(p.slots_c1, tail_entries_least()));
         p.pa_rows = c.take<float>((size_t)p.slots_a * row);  p.pa_keys = c.take<uint32_t>(p.slots_a + 1);
         p.pb_rows = c.take<float>((size_t)p.slots_w1 * row); p.pb_keys = c.take<uint32_t>(p.slots_w1 + 1);
         p.pd_rows = c.take<float>((size_t)p.slots_c1 * row); p.pd_keys = c.take<uint32_t>(p.slots_c1 + 1);
@@ -1369,7 +1323,8 @@ void queue_cbow_hidden(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
 void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint32_t* skw,
                        const uint32_t* sidx, const uint32_t* skc, const uint32_t* cidx,
                        const float* coeffs_in, float* coeffs_out, float* dots_out, bool fused,
-                       float alpha, bool join_sorts, hipStream_t st) {
+                       float alpha, double* loss_out, bool join_sorts, hipStream_t st) {
+    // (loss_out: fused form only; the dots it is formed from go to dots_out)
     // border slots of both write-back kernels, cleared ahead of the per-example pass (the second
     // stream's kernel starts behind an event recorded after that pass)
     launch_wseg_fill(p.pd_keys, p.m, st);
@@ -1389,6 +1344,10 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
     if (two) {
         (void)hipEventRecord(owner->ev_coeffs, st);
         (void)hipStreamWaitEvent(side, owner->ev_coeffs, 0);
+    }
+    if (loss_out) {
+        Phase ph(owner, W2V_PH_COEFF, side);
+        launch_loss_from_dots(dots_out, p.n, p.T, p.loss_tmp, loss_out, side);
     }
     {
         Phase ph(owner, W2V_PH_APPLY, side);
@@ -1570,7 +1529,7 @@ extern "C" int w2v_cbow_adjust(w2v_shard* sh, const uint32_t* ctx_off, const uin
     if (rc) return rc;
     queue_cbow_hidden(sh, sh, p, ctx_off, st);
     if (!prepared) cbow_wait_keys(sh, st);
-    queue_cbow_adjust(sh, sh, p, skw, sidx, skc, cidx, coeffs, nullptr, nullptr, false, alpha, !prepared, st);
+    queue_cbow_adjust(sh, sh, p, skw, sidx, skc, cidx, coeffs, nullptr, nullptr, false, alpha, nullptr, !prepared, st);
     HIP_TRY(hipGetLastError());
     return W2V_OK;
 }
@@ -1617,11 +1576,7 @@ extern "C" int w2v_cbow_train_minibatch(w2v_shard* const* shards, uint32_t S,
         queue_cbow_hidden(s0, s0, p, ctx_off, st);
         if (!prepared) cbow_wait_keys(s0, st);
         queue_cbow_adjust(s0, s0, p, skw, sidx, skc, cidx, nullptr, p.coeffs, loss ? p.dots : nullptr, true,
-                          alpha, !prepared, st);
-        if (loss) {
-            Phase ph(s0, W2V_PH_COEFF, st);
-            launch_loss_from_dots(p.dots, n, p.T, p.loss_tmp, loss, st);
-        }
+                          alpha, loss, !prepared, st);
     } else {
         // As in the two-call protocol, every shard forms its hidden vectors once for the dots and
         // once more for the update (its input vectors do not change in between).
@@ -1641,7 +1596,7 @@ extern "C" int w2v_cbow_train_minibatch(w2v_shard* const* shards, uint32_t S,
         for (uint32_t s = 0; s < S; ++s) {
             queue_cbow_hidden(s0, shards[s], p, ctx_off, st);
             queue_cbow_adjust(s0, shards[s], p, skw, sidx, skc, cidx, p.coeffs, nullptr, nullptr, false,
-                              alpha, !prepared, st);
+                              alpha, nullptr, !prepared, st);
         }
     }
     HIP_TRY(hipGetLastError());

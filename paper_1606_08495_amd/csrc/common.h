@@ -136,8 +136,9 @@ void launch_exclusive_scan(const uint32_t* in, uint32_t* out, uint32_t n, uint32
 // Chunk sizes of the segmented reductions (entries per lane group).
 uint32_t useg_pairs_per_chunk(uint32_t T, uint32_t d4, uint32_t n);   // by slots per pair, row geometry and minibatch size;
                                                           // smallest for the narrowest rows (d4 = 1)
-uint32_t wseg_entries_per_chunk();
-uint32_t tail_entries_per_chunk();
+uint32_t wseg_entries_per_chunk(uint32_t M);    // by the number of contributions
+uint32_t tail_entries_per_chunk(uint32_t d4);   // by row geometry
+uint32_t tail_entries_least();                  // the least over all of them
 
 // Input-vector side, level 1.  Sorted pairs ps = 0..n-1 (key skey[ps] = in_idx of pair perm[ps]).
 // A lane group sums coeffs[p][j] * W[keys[p][j]] over the pairs of its chunk; a run of equal keys
@@ -159,6 +160,7 @@ struct USideArgs {
     // reads or writes that row in this minibatch) and the output side must leave those slots out.
     float* W_update; float alpha;
     const CallScalars* dev;      // optional: the learning rate is read from here
+    uint32_t* clear_keys; uint32_t clear_count;   // words set to KEY_NONE on the way (wseg_fill_job)
 };
 void launch_useg(const USideArgs& a, hipStream_t st);
 // Minibatch loss from the dots of the fused step: slot 0 of a pair contributes softplus(-f), the
@@ -189,31 +191,35 @@ struct TailArgs {
     float* M; RowGeom g; float alpha;
     const float* src_rows; const uint32_t* src_keys; uint32_t entries;
     float* prows; uint32_t* pkeys;
-    // input side only: finished sums go to the delta buffer (rows, keys) instead of into M;
-    // level = 1 for the first pass over the input-side kernel's slots, cp = its pairs per chunk
+    // input side only (in a joint launch): finished sums go to the delta buffer (rows, keys) instead of
+    // into M; level = 1 for the first pass over the input-side kernel's slots, cp = its pairs per chunk
     float* defer_rows = nullptr; uint32_t* defer_keys = nullptr; uint32_t level = 0, cp = 0;
     const CallScalars* dev = nullptr;      // optional: the learning rate is read from here
 };
 void launch_tail(const TailArgs& a, hipStream_t st);
+void launch_input_tail(const TailArgs& a, hipStream_t st);       // with defer_rows
+
+// U[dkey[ps]] += alpha * delta[ps] wherever dkey[ps] != KEY_NONE.
+struct ApplyDelta {
+    float* U; const float* delta; const uint32_t* dkey; uint32_t n; float alpha;
+    const CallScalars* dev;
+};
 
 // Parts of one update that do not depend on each other, in ONE launch (each may be absent): the
 // output side's level-1 kernel (wfirst; its border slots already cleared) or one of its higher
-// levels (wtail), one higher level of the input side (utail, with defer_rows), and one step of the
-// loss of the fused form (loss_step 1: dots -> block sums in loss_tmp, needs at most
-// adjust_stage_loss_blocks_max() blocks of 256 terms; 2: block sums -> *loss_out).  Same code and
-// same bits as the separate launches.  Only for the row geometries adjust_stage_supported names.
+// levels (wtail), one higher level of the input side (utail, with defer_rows), the write-back of the
+// delta buffer (not beside wfirst, which reads U), and one step of the loss of the fused form
+// (loss_step 1: dots -> block sums in loss_tmp; 2: block sums -> *loss_out).
 struct AdjustStage {
+    RowGeom g{0, 0};
     const WSideArgs* wfirst = nullptr; const TailArgs* wtail = nullptr; const TailArgs* utail = nullptr;
+    const ApplyDelta* apply = nullptr;
     uint32_t loss_step = 0; const float* dots = nullptr; uint32_t n = 0, T = 0;
     double* loss_tmp = nullptr; double* loss_out = nullptr;
 };
-bool adjust_stage_supported(uint32_t d4);
-uint32_t adjust_stage_loss_blocks_max();
 void launch_adjust_stage(const AdjustStage& x, hipStream_t st);
-
-// U[dkey[ps]] += alpha * delta[ps] wherever dkey[ps] != KEY_NONE.
-void launch_apply_delta(float* U, RowGeom g, const float* delta, const uint32_t* dkey, uint32_t n,
-                        float alpha, hipStream_t st, const CallScalars* dev = nullptr);
+// Whether the level-1 kernel of M contributions is worth a launch of its own.
+bool adjust_walk_alone(uint32_t M, RowGeom g);
 
 // ---- pair formation ------------------------------------------------------------------------------
 struct PairArgs {

@@ -21,15 +21,21 @@ static inline unsigned blocks_for(uint64_t items, unsigned per_block) {
 // Block sizes, measured per kernel family: the input-side kernels run 6 % faster in blocks of 128
 // than of 256 (and no faster in 64); the output-side kernel is 7 % slower in 128 at one wavefront
 // per row and 8 % faster at sixteen lanes per row.
-constexpr int ADJ_THREADS = 256;                   // higher levels, write-back
 constexpr int USEG_THREADS = 128;                  // input-side kernels
-constexpr int wown_threads(int G) { return G == 16 ? 128 : 256; }     // output-side kernel
-constexpr int TAIL_C = 16;     // entries per chunk, higher levels (even, so a border's two slots
-                               // fall into one chunk)
+constexpr int adj_threads(int G) { return G == 16 ? 128 : 256; }      // everything after them
+// Higher levels: entries per block, which is their chunk (even, so a border's two slots fall into one),
+// and the block's size.  A lane group's share of the chunk is what it reads one batch after the other, so
+// a launch that holds nothing but these levels takes the largest blocks whose pieces fit LDS (shares of
+// 8 entries; 65 536 pairs, d = 100: 26 us a level with shares of 32); beside the output side's walk they
+// have that kernel's block size and its time to hide in.
+constexpr int tail_block(int G) { return G == 64 ? 128 : 256; }
+constexpr int tail_threads(int G, int NV) { return G == 16 || NV == 2 ? 512 : (NV > 2 ? 256 : 1024); }
 constexpr uint32_t NOKEY = 0xFFFFFFFFu;   // compares unequal to every masked key
 constexpr uint32_t ALONE = KEY_ALONE;
 
-uint32_t tail_entries_per_chunk() { return TAIL_C; }
+uint32_t tail_entries_per_chunk(uint32_t d4) { return d4 <= 32 ? tail_block(16) : tail_block(64); }
+static_assert(tail_block(16) == tail_block(32) && tail_block(64) < tail_block(16), "see above, and tail_entries_least");
+uint32_t tail_entries_least() { return tail_block(64); }
 // Pairs per chunk of the input-side kernel: about useg_e(G) entries (pairs x slots), 2..useg_maxp(G)
 // pairs.  Longer chunks cut fewer runs (fewer partial rows for the higher levels: -2.7 % on the
 // benchmark step, -6 % with k = 25, against chunks of 48 entries); with sixteen groups to a block
@@ -55,184 +61,215 @@ uint32_t useg_pairs_per_chunk(uint32_t T, uint32_t d4, uint32_t n) {
     return c;
 }
 
-// ---------------------------------------------------------------------------------------------
-// Generic chunk walker for entries that each name ONE source row.
-//   SRC = 0: output-vector side, level 1: source U[in_idx[sidx / T]], weight coeffs[sidx]
-//   SRC = 1: higher level: source src_rows[entry], weight 1 (or none when flagged empty)
-// C entries per group (C <= G), loads issued D entries at a time (source rows and, for runs that
-// finish inside the chunk, the destination rows as well).
-// ---------------------------------------------------------------------------------------------
 struct SegArgs {
-    const float4* src;          // SRC 0: U; SRC 1: partial rows of the previous level
+    const float4* src;          // output side, level 1: U; higher levels: partial rows of the level below
     float4* dst;                // matrix updated in place
     RowGeom g;
     const uint32_t* skey;       // destination key per entry
-    const uint32_t* sidx;       // SRC 0 only
-    const uint32_t* in_idx;     // SRC 0 only
-    const float* coeffs;        // SRC 0 only
+    const uint32_t* sidx;       // level 1 only
+    const uint32_t* in_idx;     // level 1 only
+    const float* coeffs;        // level 1 only
     uint32_t entries, T;
     float alpha;
     float4* prows; uint32_t* pkeys;    // this level's partial slots
+    uint32_t cell_log2;                // wown_kernel: cell size
     bool skip_alone;                   // wown_kernel: runs of length one are handled elsewhere
-    // DEFER: finished sums are not added to dst but parked in the input side's delta buffer
+    // input side: finished sums are not added to dst but parked in the delta buffer
     float4* defer_rows; uint32_t* defer_keys;
     uint32_t level, cp;                // level of this pass (1 = first), pairs per input-side chunk
     const CallScalars* dev;            // optional: the learning rate is read from here
 };
 
-// DEFER (higher levels of the input side): a run finished here must not touch the input matrix
-// yet -- the output side may still be reading it -- so its sum goes to the delta buffer, from
-// where apply_delta_kernel adds it with the same fma.  Its place there: every entry of a higher
-// level stands at a chunk border of the level below, and so, level by level, at a border of the
-// input-side kernel's chunk grid; the pair position right after that border lies inside the run,
-// is not the run's first pair (the run was cut there), and so holds no sum of its own.  Runs are
-// disjoint ranges of pair positions, hence no two finished runs share a place.
-// (vb: the block's number among the blocks of this walk -- the kernel below passes blockIdx.x, a
-// launch that carries several walks the block's offset within its own)
-template <int G, int NV, int C, int D, int SRC, bool DEFER = false>
-__device__ __forceinline__ void seg_body(const SegArgs& a, uint32_t vb) {
-    static_assert(C <= G && C % D == 0, "chunk must fit a lane group");
+// ---------------------------------------------------------------------------------------------
+// Higher levels: entries are partial rows src[i] (weight 1) with destination skey[i].  A block's chunk
+// is tail_block(G) entries.  Most entries hold nothing: each lane group lists the ones of its part
+// that do, walks that list with several rows in flight, finishes the runs that lie inside its part and
+// leaves what its borders cut in LDS (two pieces per part); then every group adds up the pieces of the
+// run that begins in its part, and only what the block's own borders cut goes to the slots of the next
+// level.  Bound by latency, not
+// bytes -- a level costs two or three memory round trips whatever it holds -- so what counts is how few
+// levels there are: they shrink 64 or 128 times.  (One lane group per chunk of 16 entries, shrinking
+// eightfold, before: six launches instead of three after the output side of a 2^20-pair minibatch,
+// five instead of two at 2^16 pairs.)
+//
+// DEFER (input side): a run finished here must not touch the input matrix yet -- the output side may
+// still be reading it -- so its sum goes to the delta buffer, from where apply_delta adds it with the
+// same fma.  Its place there: every entry of a higher level stands at a chunk border of the level below,
+// and so, level by level, at a border of the input-side kernel's chunk grid; the pair position right
+// after that border lies inside the run, is not the run's first pair (the run was cut there), and so
+// holds no sum of its own.  Runs are disjoint ranges of pair positions, hence no two finished runs share
+// a place.
+// (vb: the block's number among the blocks of this walk -- a launch that carries several walks passes
+// the block's offset within its own)
+// ---------------------------------------------------------------------------------------------
+enum : uint32_t { TL_POS = 0xFFFFu, TL_HAS = 1u << 16, TL_COMPLETE = 1u << 17, TL_HEAD = 1u << 18 };
+
+template <int G, int NV, int THREADS> struct TailLds {
+    static constexpr int GROUPS = THREADS / G, C = tail_block(G) / GROUPS;
+    float4 rows[2 * GROUPS][G * NV];                      // head and tail piece of every part
+    uint32_t raw[tail_block(G) + 2];                      // keys of entries base - 1 .. base + CB
+    uint32_t list[GROUPS][C];
+    uint32_t gkey[2 * GROUPS];
+    uint32_t out_key[2];                                  // the block's own head and tail slot
+};
+
+template <int G, int NV, int THREADS, bool DEFER>
+__device__ __forceinline__ void tail_body(const SegArgs& a, uint32_t vb, TailLds<G, NV, THREADS>& lds) {
+    constexpr int GROUPS = THREADS / G, CB = tail_block(G), C = CB / GROUPS;
+    constexpr int D = NV == 1 && (DEFER || C == 8) ? 8 : (NV <= 2 ? 4 : 2);
+    static_assert(C % 2 == 0, "a border's two slots fall into one part");
+    constexpr int ROW4 = G * NV;                          // float4 of a row held in LDS
+    auto& s_raw = lds.raw; auto& s_list = lds.list; auto& s_rows = lds.rows; auto& s_gkey = lds.gkey;
     const float alpha = a.dev ? a.dev->alpha : a.alpha;
-    const int l = threadIdx.x % G;
-    const uint32_t c = (vb * (uint32_t)ADJ_THREADS + threadIdx.x) / G;
-    const uint32_t nchunks = (a.entries + C - 1) / C;
-    if (c >= nchunks) return;
-    const uint32_t e0 = c * C;
-    const uint32_t cnt = min((uint32_t)C, a.entries - e0);
+    const int l = threadIdx.x % G, grp = threadIdx.x / G;
+    const uint32_t base = vb * (uint32_t)CB, count = min((uint32_t)CB, a.entries - base);
+    const bool more = base + CB < a.entries;              // a block follows
     const uint32_t d4 = a.g.d4;
     const uint64_t s4 = a.g.stride4;
-
-    // ---- per-entry facts, entry e0+l in lane l ----
-    const bool valid = (uint32_t)l < cnt;
-    uint32_t key = NOKEY, srow = 0;
-    float coef = 1.0f;
-    int has = 0;
-    if (valid) {
-        uint32_t raw = a.skey[e0 + l];
-        if (SRC == 0) {
-            key = raw;
-            uint32_t q = a.sidx[e0 + l];
-            srow = a.in_idx[q / a.T];          // range-checked copy
-            coef = a.coeffs[q];
-            has = 1;
+    int any = 0;
+    for (int i = threadIdx.x; i < CB + 2; i += THREADS) {
+        const int64_t pos = (int64_t)base - 1 + i;
+        const uint32_t raw = pos >= 0 && pos < (int64_t)a.entries ? a.skey[pos] : KEY_NONE;
+        s_raw[i] = raw;
+        any |= i > 0 && i <= (int)count && (raw & KEY_MASK) < KEY_MASK;
+    }
+    if (threadIdx.x < 2 * GROUPS) s_gkey[threadIdx.x] = KEY_NONE;
+    if (threadIdx.x < 2) lds.out_key[threadIdx.x] = KEY_NONE;
+    if (__syncthreads_or(any) == 0) {                     // nothing here, and no run passes through
+        if (threadIdx.x == 0) {
+            if (vb > 0) a.pkeys[2 * vb - 1] = KEY_NONE;
+            if (more) a.pkeys[2 * vb] = KEY_NONE;
+        }
+        return;
+    }
+    auto K = [&](int i) -> uint32_t { return s_raw[i + 1] & KEY_MASK; };      // KEY_MASK itself names no row
+    auto finish = [&](uint32_t key, uint32_t entry, const float4 (&acc)[NV], const float4 (&old)[NV]) {
+        if (DEFER) {
+            uint32_t pos = entry;
+            for (uint32_t lv = a.level; lv > 1; --lv) pos = ((pos + 2) >> 1) * (uint32_t)CB;
+            pos = ((pos + 2) >> 1) * a.cp;
+            store_row<G, NV>(a.defer_rows + (uint64_t)pos * s4, d4, l, acc);
+            if (l == 0) a.defer_keys[pos] = key;
         } else {
-            key = raw & KEY_MASK;
-            srow = e0 + l;
-            has = (raw != KEY_NONE) && !(raw & KEY_ZERO);
-        }
-    }
-    const uint32_t real_limit = (SRC == 0) ? NOKEY : KEY_MASK;   // keys >= this name no row
-    if (SRC == 1) {
-        // Most slots of a level are unused.  No run passes through a chunk of unused slots only:
-        // its own two slots are unused as well, and that is all there is to do.
-        const uint64_t any = __ballot(valid && key < real_limit);
-        const int first_lane = (int)(threadIdx.x % 64) / G * G;
-        const uint64_t group_bits = G >= 64 ? ~0ull : ((1ull << (G & 63)) - 1ull);
-        if (((any >> first_lane) & group_bits) == 0) {
-            if (l == 0) {
-                if (c > 0) a.pkeys[2 * c - 1] = KEY_NONE;
-                if (c + 1 < nchunks) a.pkeys[2 * c] = KEY_NONE;
+            float4 out[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+                out[v].x = fmaf(alpha, acc[v].x, old[v].x);
+                out[v].y = fmaf(alpha, acc[v].y, old[v].y);
+                out[v].z = fmaf(alpha, acc[v].z, old[v].z);
+                out[v].w = fmaf(alpha, acc[v].w, old[v].w);
             }
-            return;
+            store_row<G, NV>(a.dst + (uint64_t)key * s4, (uint32_t)s4, l, out);
         }
+    };
+    // ---- each group's part ----
+    const int e0 = grp * C;
+    const int n_part = min((int)count - e0, C);           // (may be zero or less)
+    const uint32_t before = K(e0 - 1);
+    int listed = 0;
+    const int lane0 = ((int)(threadIdx.x & 63) / G) * G;
+    for (int i0 = 0; i0 < C; i0 += G) {
+        const int i = i0 + l;
+        const bool inside = i < n_part;
+        const uint32_t k = inside ? K(e0 + i) : KEY_MASK;
+        const bool use = k < KEY_MASK;
+        const uint64_t wave_mask = __ballot(use);
+        const uint64_t mine = G == 64 ? wave_mask : ((wave_mask >> lane0) & ((1ull << (G & 63)) - 1ull));
+        if (use) {
+            const bool ends = K(e0 + i + 1) != k, came_in = before == k;
+            s_list[grp][listed + __popcll(mine & ((1ull << l) - 1ull))] =
+                (uint32_t)(e0 + i) | ((s_raw[e0 + i + 1] & KEY_ZERO) ? 0u : (uint32_t)TL_HAS) |
+                (ends ? (came_in ? (uint32_t)TL_HEAD : (uint32_t)TL_COMPLETE) : 0u);
+        }
+        listed += __popcll(mine);
     }
-    uint32_t key_prev = NOKEY, key_after = NOKEY;
-    if (e0 > 0) { uint32_t r = a.skey[e0 - 1]; key_prev = (SRC == 0) ? r : (r & KEY_MASK); }
-    if (e0 + cnt < a.entries) { uint32_t r = a.skey[e0 + cnt]; key_after = (SRC == 0) ? r : (r & KEY_MASK); }
-    uint32_t next = __shfl(key, l + 1, G);
-    if ((uint32_t)l + 1 >= cnt) next = key_after;
-    const uint32_t key0 = __shfl(key, 0, G);
-    const bool open_head = (key_prev == key0);
-    const int ends = valid && (next != key);
-    const int in_head = open_head && (key == key0);
-    const int real = key < real_limit;
-    const int complete = ends && !in_head && real;
-
+    __syncthreads();
     float4 acc[NV];
     clear<NV>(acc);
-    uint32_t head_key = KEY_NONE, tail_key = KEY_NONE;
-    const uint32_t head_slot = 2 * c - 1, tail_slot = 2 * c;   // used only when they exist
-
-    // Register sets srcv[t] / dstv[t] hold the source row of an entry and, when its run finishes
-    // inside the chunk, the destination row.  Entry e uses set e % D; as soon as an entry has been
-    // consumed its set is refilled with entry e + D, so D entries' rows stay in flight.
-    float4 srcv[D][NV], dstv[D][NV];
-    auto fetch = [&](int e, float4 (&sv)[NV], float4 (&dv)[NV]) {
-        uint32_t sr = __shfl(srow, e, G);
-        int h = __shfl(has, e, G);
-        int cm = __shfl(complete, e, G);
-        uint32_t dk = __shfl(key, e, G);
-        load_row_if<G, NV>(h != 0, a.src + (uint64_t)sr * s4, d4, l, sv);
-        load_row_if<G, NV>(cm != 0 && !DEFER, a.dst + (uint64_t)(cm ? dk : 0u) * s4, d4, l, dv);
-    };
+    if (listed) {
+        float4 srcv[D][NV], dstv[D][NV];
+        auto fetch = [&](int idx, float4 (&sv)[NV], float4 (&dv)[NV]) {
+            const uint32_t f = idx < listed ? s_list[grp][idx] : 0u;
+            const bool cm = !DEFER && (f & TL_COMPLETE);
+            const uint32_t i = f & TL_POS;
+            load_row_if<G, NV>((f & TL_HAS) != 0, a.src + (uint64_t)(base + i) * s4, d4, l, sv);
+            load_row_if<G, NV>(cm, a.dst + (uint64_t)(cm ? K((int)i) : 0u) * s4, d4, l, dv);
+        };
 #pragma unroll
-    for (int t = 0; t < D; ++t) fetch(t, srcv[t], dstv[t]);
+        for (int t = 0; t < D; ++t) fetch(t, srcv[t], dstv[t]);
+        for (int b = 0; b < listed; b += D) {
 #pragma unroll
-    for (int b = 0; b < C; b += D) {
-#pragma unroll
-        for (int t = 0; t < D; ++t) {
-            const int e = b + t;
-            float cf = __shfl(coef, e, G);
-            int h = __shfl(has, e, G);
-            int en = __shfl(ends, e, G);
-            int cm = __shfl(complete, e, G);
-            int ih = __shfl(in_head, e, G);
-            int rl = __shfl(real, e, G);
-            uint32_t dk = __shfl(key, e, G);
-            if (h) axpy<NV>(cf, srcv[t], acc);
-            if (en) {
-                if (cm && DEFER) {
-                    uint32_t pos = e0 + (uint32_t)e;
-                    for (uint32_t lv = a.level; lv > 1; --lv) pos = ((pos + 2) >> 1) * (uint32_t)C;
-                    pos = ((pos + 2) >> 1) * a.cp;
-                    store_row<G, NV>(a.defer_rows + (uint64_t)pos * s4, d4, l, acc);
-                    if (l == 0) a.defer_keys[pos] = dk;
-                } else if (cm) {
-                    float4 out[NV];
-#pragma unroll
-                    for (int v = 0; v < NV; ++v) {
-                        out[v].x = fmaf(alpha, acc[v].x, dstv[t][v].x);
-                        out[v].y = fmaf(alpha, acc[v].y, dstv[t][v].y);
-                        out[v].z = fmaf(alpha, acc[v].z, dstv[t][v].z);
-                        out[v].w = fmaf(alpha, acc[v].w, dstv[t][v].w);
+            for (int t = 0; t < D; ++t) {
+                if (b + t < listed) {
+                    const uint32_t f = s_list[grp][b + t], i = f & TL_POS;
+                    if (f & TL_HAS) axpy<NV>(1.0f, srcv[t], acc);
+                    if (f & TL_COMPLETE) {
+                        finish(K((int)i), base + i, acc, dstv[t]);
+                        clear<NV>(acc);
+                    } else if (f & TL_HEAD) {             // came in from the part before and ends here
+                        store_row<G, NV>(&s_rows[2 * grp][0], ROW4, l, acc);
+                        if (l == 0) s_gkey[2 * grp] = K((int)i);
+                        clear<NV>(acc);
                     }
-                    store_row<G, NV>(a.dst + (uint64_t)dk * s4, (uint32_t)s4, l, out);
-                } else if (ih && rl) {      // the run came in from the previous chunk and ends here
-                    store_row<G, NV>(a.prows + (uint64_t)head_slot * s4, d4, l, acc);
-                    head_key = dk;
                 }
-                clear<NV>(acc);
+                if (b + D < listed) fetch(b + t + D, srcv[t], dstv[t]);
             }
-            if (b + D < C) fetch(e + D, srcv[t], dstv[t]);
         }
-    }
-    // ---- the last run may go on into the next chunk ----
-    {
-        const int last = (int)cnt - 1;
-        int en = __shfl(ends, last, G);
-        int ih = __shfl(in_head, last, G);
-        int rl = __shfl(real, last, G);
-        uint32_t dk = __shfl(key, last, G);
-        if (!en && rl) {
-            if (ih) {               // one run covers the whole chunk: one partial, in the head slot
-                store_row<G, NV>(a.prows + (uint64_t)head_slot * s4, d4, l, acc);
-                head_key = dk;
-                tail_key = dk | KEY_ZERO;
-            } else {
-                store_row<G, NV>(a.prows + (uint64_t)tail_slot * s4, d4, l, acc);
-                tail_key = dk;
+        const uint32_t last = K(e0 + n_part - 1);
+        if (last < KEY_MASK && K(e0 + n_part) == last) {  // the last run goes on past the part
+            const int piece = before == last ? 2 * grp : 2 * grp + 1;
+            store_row<G, NV>(&s_rows[piece][0], ROW4, l, acc);
+            if (l == 0) {
+                s_gkey[piece] = last;
+                if (piece == 2 * grp) s_gkey[2 * grp + 1] = last | KEY_ZERO;   // it covers the whole part
             }
         }
     }
-    if (l == 0) {
-        if (c > 0) a.pkeys[head_slot] = head_key;
-        if (c + 1 < nchunks) a.pkeys[tail_slot] = tail_key;
+    __syncthreads();
+    // ---- what the parts' borders cut: the group of the part in which a run begins (group 0 for the run
+    // that comes in from before the block) walks its pieces, which are adjacent, in order ----
+    const uint32_t block_before = K(-1), block_after = K((int)count);
+    for (int start = grp == 0 ? 0 : 2 * grp + 1; start <= 2 * grp + 1; ++start) {
+        const uint32_t raw0 = s_gkey[start], k = raw0 & KEY_MASK;
+        if (k == KEY_MASK || (raw0 & KEY_ZERO)) continue; // (flagged: the run began earlier)
+        const bool came_in = block_before == k;
+        float4 old[NV];
+        load_row_if<G, NV>(!DEFER && !came_in, a.dst + (uint64_t)k * s4, d4, l, old);
+        clear<NV>(acc);
+        int i = start;
+        uint32_t raw = raw0, next;
+        for (;;) {
+            if (!(raw & KEY_ZERO)) {
+                float4 x[NV];
+                load_row<G, NV>(&s_rows[i][0], ROW4, l, x);
+                axpy<NV>(1.0f, x, acc);
+            }
+            raw = i + 1 < 2 * GROUPS ? s_gkey[i + 1] : block_after;
+            next = raw & KEY_MASK;
+            if (next != k || i + 1 == 2 * GROUPS) break;
+            ++i;
+        }
+        if (next == k || came_in) {                       // goes on past the block, or came from before it
+            store_row<G, NV>(a.prows + (uint64_t)(came_in ? 2 * vb - 1 : 2 * vb) * s4, d4, l, acc);
+            if (l == 0) {
+                if (came_in) lds.out_key[0] = k;
+                if (next == k) lds.out_key[1] = came_in ? k | KEY_ZERO : k;
+            }
+        } else {
+            finish(k, base + (uint32_t)(i / 2) * C, acc, old);       // (ends as the head piece of a later part)
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        if (vb > 0) a.pkeys[2 * vb - 1] = lds.out_key[0];
+        if (more) a.pkeys[2 * vb] = lds.out_key[1];
     }
 }
 
-template <int G, int NV, int C, int D, int SRC, bool DEFER = false>
-__global__ __launch_bounds__(ADJ_THREADS) void seg_kernel(SegArgs a) {
-    seg_body<G, NV, C, D, SRC, DEFER>(a, blockIdx.x);
+template <int G, int NV>
+__global__ __launch_bounds__(tail_threads(G, NV)) void tail_kernel(SegArgs a) {
+    __shared__ TailLds<G, NV, tail_threads(G, NV)> lds;
+    tail_body<G, NV, tail_threads(G, NV), false>(a, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -251,20 +288,23 @@ __global__ __launch_bounds__(ADJ_THREADS) void seg_kernel(SegArgs a) {
 // written unless a word collects more than L contributions or so.
 // ---------------------------------------------------------------------------------------------
 constexpr int WOWN_C = 16;
-constexpr int WOWN_L = 64;                   // cell size for long runs, a multiple of C (128: the
-                                             // output-side kernel 9 % slower, 32: more levels above)
+// Cell size for long runs, a multiple of C: 64 (128: the output-side kernel 9 % slower, 32: more rows for
+// the levels above); 32 for minibatches of up to 2^19 slots, whose time is that of the group with the most
+// entries in a row.
+static uint32_t wown_cell_log2(uint32_t M) { return M <= (1u << 19) ? 5u : 6u; }
 constexpr int WOWN_WIN = 3 * WOWN_C + 2;     // keys staged: positions base-C-1 .. base+2C
 constexpr int WOWN_E = 2 * WOWN_C;           // positions summed from LDS facts: base .. base+2C-1
 enum : uint32_t { ACT_SKIP = 0, ACT_ADD = 1, ACT_COMPLETE = 2, ACT_HEAD = 3 };
 
-uint32_t wseg_entries_per_chunk() { return WOWN_L; }
+uint32_t wseg_entries_per_chunk(uint32_t M) { return 1u << wown_cell_log2(M); }
 
 template <int G, int NV, int D>
 __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
-    constexpr int WOWN_THREADS = wown_threads(G);
+    constexpr int WOWN_THREADS = adj_threads(G);
     constexpr int GROUPS = WOWN_THREADS / G;
-    constexpr int C = WOWN_C, L = WOWN_L;
-    static_assert(L % C == 0 && C == 16 && G >= 16, "grid shapes");
+    constexpr int C = WOWN_C;
+    const int L = 1 << a.cell_log2;                        // a multiple of C
+    static_assert(C == 16 && G >= 16, "grid shapes");
     const float alpha = a.dev ? a.dev->alpha : a.alpha;
     __shared__ uint32_t s_key[GROUPS][WOWN_WIN];
     __shared__ uint32_t s_srow[GROUPS][WOWN_E];
@@ -285,7 +325,7 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
     const uint32_t kbm = K(-C - 1), kb = K(-1), k0 = K(0), kC = K(C), k2C = K(2 * C), klast = K(C - 1);
     const bool head_exists = active && kb == k0;
     const bool head_long = head_exists && !(kbm != k0 && kC != k0);
-    const bool own_head = head_long && (base % L) == 0;          // a cell begins here: the piece is ours
+    const bool own_head = head_long && (base & (L - 1)) == 0;          // a cell begins here: the piece is ours
     const bool last_in_head = head_exists && klast == k0;
     const bool ext_ok = klast != NOKEY && !last_in_head && k2C != klast;
     // does the run through the chunk's last entry go on, as a long piece that this group owns?
@@ -328,7 +368,7 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
     if (!active || count == 0) return;
     const uint32_t d4 = a.g.d4;
     const uint64_t s4 = a.g.stride4;
-    const uint32_t cell = (uint32_t)(base / L);
+    const uint32_t cell = (uint32_t)(base >> a.cell_log2);
     const uint32_t head_slot = 2 * cell - 1, tail_slot = 2 * cell;   // used only when they exist
 
     float4 acc[NV], srcv[D][NV], dstv[D][NV];
@@ -396,15 +436,18 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
             sr = a.in_idx[q / a.T];
             cf = a.coeffs[q];
         }
+        // (no destination rows here: at one float4 per lane both register sets hold source rows, 2 D in
+        // flight; at two that spills)
+        constexpr int S = NV == 1 ? 2 * D : D;
 #pragma unroll
-        for (int b = 0; b < 16; b += D) {
+        for (int b = 0; b < 16; b += S) {
             if (b < cnt) {
 #pragma unroll
-                for (int t = 0; t < D; ++t)
+                for (int t = 0; t < S; ++t)
                     load_row_if<G, NV>(b + t < cnt, a.src + (uint64_t)__shfl(sr, b + t, G) * s4, d4, l,
-                                       srcv[t]);
+                                       t < D ? srcv[t % D] : dstv[t % D]);
 #pragma unroll
-                for (int t = 0; t < D; ++t) axpy<NV>(__shfl(cf, b + t, G), srcv[t], acc);
+                for (int t = 0; t < S; ++t) axpy<NV>(__shfl(cf, b + t, G), t < D ? srcv[t % D] : dstv[t % D], acc);
             }
         }
         if (cnt < nblk) { ended = true; break; }
@@ -429,7 +472,7 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
 }
 
 template <int G, int NV, int D>
-__global__ __launch_bounds__(wown_threads(G)) void wown_kernel(SegArgs a) {
+__global__ __launch_bounds__(adj_threads(G)) void wown_kernel(SegArgs a) {
     wown_body<G, NV, D>(a, blockIdx.x);
 }
 
@@ -441,7 +484,7 @@ __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* __restrict__ x,
 
 FillJob wseg_fill_job(uint32_t* pkeys, uint32_t M) {
     // border slots of the cells: only pieces of long runs write them
-    const uint32_t ncells = (M + WOWN_L - 1) / WOWN_L;
+    const uint32_t L = wseg_entries_per_chunk(M), ncells = (M + L - 1) / L;
     return FillJob{pkeys, ncells ? 2 * (ncells - 1) : 0u, KEY_NONE};
 }
 
@@ -457,7 +500,7 @@ static SegArgs seg_args_of(const WSideArgs& w) {
     a.src = (const float4*)w.U; a.dst = (float4*)w.W; a.g = w.g; a.skey = w.skey; a.sidx = w.sidx;
     a.in_idx = w.in_idx; a.coeffs = w.coeffs; a.entries = w.M; a.T = w.T;
     a.alpha = w.alpha; a.prows = (float4*)w.prows; a.pkeys = w.pkeys; a.dev = w.dev;
-    a.skip_alone = w.skip_alone;
+    a.skip_alone = w.skip_alone; a.cell_log2 = wown_cell_log2(w.M);
     return a;
 }
 
@@ -478,8 +521,8 @@ void launch_wseg(const WSideArgs& w, hipStream_t st, bool filled) {
     uint32_t nchunks = (w.M + WOWN_C - 1) / WOWN_C;
 #define CALL(G, NV)                                                                              \
     hipLaunchKernelGGL((wown_kernel<G, NV, (NV <= 2 ? 4 : 2)>),                                   \
-                       dim3(blocks_for((uint64_t)nchunks * G, wown_threads(G))),                 \
-                       dim3(wown_threads(G)), 0,                                                 \
+                       dim3(blocks_for((uint64_t)nchunks * G, adj_threads(G))),                 \
+                       dim3(adj_threads(G)), 0,                                                 \
                        st, a)
     W2V_DISPATCH_GEOM(w.g.d4, CALL);
 #undef CALL
@@ -488,102 +531,155 @@ void launch_wseg(const WSideArgs& w, hipStream_t st, bool filled) {
 void launch_tail(const TailArgs& t, hipStream_t st) {
     if (t.entries == 0) return;
     const SegArgs a = seg_args_of(t);
-    uint32_t nchunks = (t.entries + TAIL_C - 1) / TAIL_C;
 #define CALL(G, NV)                                                                              \
-    do {                                                                                         \
-        if (t.defer_rows)                                                                        \
-            hipLaunchKernelGGL((seg_kernel<G, NV, TAIL_C, (NV <= 2 ? 4 : 2), 1, true>),          \
-                               dim3(blocks_for((uint64_t)nchunks * G, ADJ_THREADS)),             \
-                               dim3(ADJ_THREADS), 0, st, a);                                     \
-        else                                                                                     \
-            hipLaunchKernelGGL((seg_kernel<G, NV, TAIL_C, (NV <= 2 ? 4 : 2), 1>),                \
-                               dim3(blocks_for((uint64_t)nchunks * G, ADJ_THREADS)),             \
-                               dim3(ADJ_THREADS), 0, st, a);                                     \
-    } while (0)
+    hipLaunchKernelGGL((tail_kernel<G, NV>), dim3(blocks_for(t.entries, tail_block(G))),         \
+                       dim3(tail_threads(G, NV)), 0, st, a)
     W2V_DISPATCH_GEOM(t.g.d4, CALL);
 #undef CALL
 }
 
 // ---------------------------------------------------------------------------------------------
+// Write-back of the input-vector changes held in the delta buffer: U[dkey[ps]] += alpha * delta[ps]
+// wherever dkey[ps] names a row.  A lane group looks at APPLY_P sorted positions and takes the few
+// that do, four rows in flight.  (64 positions one after the other, before: 8 us for 4096 pairs.)
+// ---------------------------------------------------------------------------------------------
+constexpr int APPLY_P = 16;
+struct ApplyArgs {
+    float4* U; RowGeom g; const float4* delta; const uint32_t* dkey; uint32_t n; float alpha;
+    const CallScalars* dev;
+};
+
+template <int G, int NV, int THREADS>
+__device__ __forceinline__ void apply_body(const ApplyArgs& a, uint32_t vb) {
+    constexpr int D = NV <= 2 ? 4 : 2;
+    const float alpha = a.dev ? a.dev->alpha : a.alpha;
+    const int l = threadIdx.x % G;
+    const uint32_t base = (vb * (uint32_t)THREADS + threadIdx.x) / G * APPLY_P;
+    const uint32_t mine = l < APPLY_P && base + l < a.n ? a.dkey[base + l] : KEY_NONE;
+    const int lane0 = ((int)(threadIdx.x & 63) / G) * G;
+    uint32_t todo = (uint32_t)(__ballot(mine != KEY_NONE) >> lane0) & ((1u << APPLY_P) - 1u);
+    while (todo) {
+        float4 dv[D][NV], uv[D][NV];
+        uint32_t key[D];
+#pragma unroll
+        for (int t = 0; t < D; ++t) {
+            const bool on = todo != 0;
+            const int e = on ? __builtin_ctz(todo) : 0;
+            todo &= todo - 1;                              // (0 stays 0)
+            key[t] = on ? (uint32_t)__shfl(mine, e, G) : KEY_NONE;
+            load_row_if<G, NV>(on, a.delta + (uint64_t)(on ? base + e : 0u) * a.g.stride4, a.g.d4, l, dv[t]);
+            load_row_if<G, NV>(on, a.U + (uint64_t)(on ? key[t] : 0u) * a.g.stride4, a.g.d4, l, uv[t]);
+        }
+#pragma unroll
+        for (int t = 0; t < D; ++t) {
+            if (key[t] == KEY_NONE) continue;
+            axpy<NV>(alpha, dv[t], uv[t]);
+            store_row<G, NV>(a.U + (uint64_t)key[t] * a.g.stride4, a.g.stride4, l, uv[t]);
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------
 // One launch for parts of the update that do not depend on each other: a walk of the output side
 // (its level-1 kernel when FIRST, else one of its higher levels), one higher level of the input
-// side (which parks its sums in the delta buffer), and one step of the loss.  Each block does one
-// part, told by its number, with the same code as the kernels above, so the bits are the same.
-// On one stream a step of a few thousand pairs is a chain of launches of a few microseconds each;
-// this takes the input side's levels and the loss out of that chain.
+// side (which parks its sums in the delta buffer), one step of the loss, and -- once the output side's
+// first walk has read U and the input side's levels are done -- the write-back of the delta buffer.
+// Each block does one part, told by its number.  The update is a chain of dependent launches; this
+// keeps everything that can run beside the output side out of that chain, without a second stream
+// (whose event waits cost about 10 us each: the step of 65 536 pairs, d = 100, spent 90 us of 220 on
+// them).
 // ---------------------------------------------------------------------------------------------
 struct StageDev {
     SegArgs w, u;
-    uint32_t w_blocks, u_blocks;
+    ApplyArgs apply;
+    uint32_t w_blocks, u_blocks, apply_blocks, loss_blocks;
     uint32_t loss_step;              // 0 none, 1 terms -> block sums, 2 block sums -> loss
     const float* dots; uint32_t total, T;
     double* block_loss; uint32_t nb; double* loss_out;
 };
 
+constexpr int stage_threads(int G, int NV, bool first) { return first ? adj_threads(G) : tail_threads(G, NV); }
+
+// (at two float4 per lane the output side's walk fills 96 registers, five wavefronts per SIMD: keep it so)
 template <int G, int NV, bool FIRST>
-__global__ __launch_bounds__(ADJ_THREADS) void adjust_stage_kernel(StageDev s) {
-    constexpr int D = NV <= 2 ? 4 : 2;
-    static_assert(wown_threads(G) == ADJ_THREADS, "the parts share one block size");
-    uint32_t b = blockIdx.x;
-    if (b < s.w_blocks) {
-        if (FIRST) wown_body<G, NV, D>(s.w, b);
-        else seg_body<G, NV, TAIL_C, D, 1, false>(s.w, b);
-        return;
-    }
-    b -= s.w_blocks;
+__global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? 5 : 1)) void adjust_stage_kernel(StageDev s) {
+    constexpr int D = NV <= 2 ? 4 : 2, THREADS = stage_threads(G, NV, FIRST);
+    __shared__ TailLds<G, NV, THREADS> lds;
+    __shared__ double red[THREADS / 64];
+    uint32_t b = blockIdx.x;                               // the input side's level first: its blocks run longest
     if (b < s.u_blocks) {
-        seg_body<G, NV, TAIL_C, D, 1, true>(s.u, b);
+        tail_body<G, NV, THREADS, true>(s.u, b, lds);
         return;
     }
     b -= s.u_blocks;
-    __shared__ double red[256];
-    if (s.loss_step == 1) loss_terms_block(s.dots, s.total, s.T, s.block_loss, b, red);
-    else sum_doubles_block(s.block_loss, s.nb, s.nb, s.loss_out, 0u, red);
+    if (b < s.loss_blocks) {
+        if (s.loss_step == 1) loss_terms_block<THREADS>(s.dots, s.total, s.T, s.block_loss, b, red);
+        else sum_doubles_block<THREADS>(s.block_loss, s.nb, s.loss_out, red);
+        return;
+    }
+    b -= s.loss_blocks;
+    if (b < s.w_blocks) {
+        if (FIRST) wown_body<G, NV, D>(s.w, b);
+        else tail_body<G, NV, THREADS, false>(s.w, b, lds);
+        return;
+    }
+    b -= s.w_blocks;
+    if (!FIRST) apply_body<G, NV, THREADS>(s.apply, b);
 }
 
-bool adjust_stage_supported(uint32_t d4) { return d4 > 16; }    // (sixteen-lane groups use blocks of 128)
-uint32_t adjust_stage_loss_blocks_max() { return LOSS_SUM_SPAN; }
+// The input side's levels alone, beside the output side's walk on another stream: blocks no larger than
+// that kernel's, which fill the places its blocks leave (of 512 threads they waited for its end).
+template <int G, int NV>
+__global__ __launch_bounds__(adj_threads(G)) void input_tail_kernel(SegArgs a) {
+    __shared__ TailLds<G, NV, adj_threads(G)> lds;
+    tail_body<G, NV, adj_threads(G), true>(a, blockIdx.x, lds);
+}
+
+void launch_input_tail(const TailArgs& t, hipStream_t st) {
+    if (t.entries == 0) return;
+    const SegArgs a = seg_args_of(t);
+#define CALL(G, NV)                                                                                  \
+    hipLaunchKernelGGL((input_tail_kernel<G, NV>), dim3(blocks_for(t.entries, tail_block(G))),       \
+                       dim3(adj_threads(G)), 0, st, a)
+    W2V_DISPATCH_GEOM(t.g.d4, CALL);
+#undef CALL
+}
 
 template <int G, int NV>
-static void launch_stage_shape(StageDev s, uint32_t w_chunks, uint32_t u_chunks, uint32_t loss_blocks,
-                               bool first, hipStream_t st) {
-    if constexpr (G != 16) {
-        s.w_blocks = blocks_for((uint64_t)w_chunks * G, ADJ_THREADS);
-        s.u_blocks = blocks_for((uint64_t)u_chunks * G, ADJ_THREADS);
-        const dim3 grid(s.w_blocks + s.u_blocks + loss_blocks);
-        if (first)
-            hipLaunchKernelGGL((adjust_stage_kernel<G, NV, true>), grid, dim3(ADJ_THREADS), 0, st, s);
-        else
-            hipLaunchKernelGGL((adjust_stage_kernel<G, NV, false>), grid, dim3(ADJ_THREADS), 0, st, s);
-    }
+static void launch_stage_shape(StageDev s, bool first, hipStream_t st) {
+    if (first) s.w_blocks = blocks_for((uint64_t)((s.w.entries + WOWN_C - 1) / WOWN_C) * G, adj_threads(G));
+    else s.w_blocks = blocks_for(s.w.entries, tail_block(G));
+    s.u_blocks = blocks_for(s.u.entries, tail_block(G));
+    s.apply_blocks = blocks_for((uint64_t)blocks_for(s.apply.n, APPLY_P) * G, stage_threads(G, NV, first));
+    const dim3 grid(s.w_blocks + s.u_blocks + s.apply_blocks + s.loss_blocks);
+    if (grid.x == 0) return;
+    const dim3 block(stage_threads(G, NV, first));
+    if (first) hipLaunchKernelGGL((adjust_stage_kernel<G, NV, true>), grid, block, 0, st, s);
+    else hipLaunchKernelGGL((adjust_stage_kernel<G, NV, false>), grid, block, 0, st, s);
 }
+
+// (Its own launch keeps its registers to itself; rows of more than 128 floats: k = 25, d = 200, 2^18 pairs 4.41
+// against 4.55 ms; at sixteen lanes per row the joint launch is as fast or faster, and so it is while a
+// level takes as long as a walk.)
+bool adjust_walk_alone(uint32_t M, RowGeom g) { return M >= (1u << 20) && g.d4 > 32; }
 
 void launch_adjust_stage(const AdjustStage& x, hipStream_t st) {
     StageDev s{};
-    RowGeom g{};
-    uint32_t w_chunks = 0, u_chunks = 0, loss_blocks = 0;
-    const bool first = x.wfirst && x.wfirst->M;
-    if (first) {
-        s.w = seg_args_of(*x.wfirst); g = x.wfirst->g;
-        w_chunks = (x.wfirst->M + WOWN_C - 1) / WOWN_C;
-    } else if (x.wtail && x.wtail->entries) {
-        s.w = seg_args_of(*x.wtail); g = x.wtail->g;
-        w_chunks = (x.wtail->entries + TAIL_C - 1) / TAIL_C;
-    }
-    if (x.utail && x.utail->entries) {
-        s.u = seg_args_of(*x.utail); g = x.utail->g;
-        u_chunks = (x.utail->entries + TAIL_C - 1) / TAIL_C;
-    }
+    const bool first = x.wfirst != nullptr;                  // (then nothing is written back: FIRST has no such part)
+    if (first) s.w = seg_args_of(*x.wfirst);
+    else if (x.wtail) s.w = seg_args_of(*x.wtail);
+    if (x.utail) s.u = seg_args_of(*x.utail);
+    if (x.apply && !first)
+        s.apply = ApplyArgs{(float4*)x.apply->U, x.g, (const float4*)x.apply->delta, x.apply->dkey, x.apply->n,
+                            x.apply->alpha, x.apply->dev};
     s.loss_step = x.loss_step;
     if (x.loss_step) {
         s.dots = x.dots; s.total = x.n * x.T; s.T = x.T; s.block_loss = x.loss_tmp;
-        s.nb = blocks_for(s.total, 256); s.loss_out = x.loss_out;
-        loss_blocks = x.loss_step == 1 ? s.nb : 1u;
+        s.nb = blocks_for(s.total, LOSS_TERMS); s.loss_out = x.loss_out;
+        s.loss_blocks = x.loss_step == 1 ? s.nb : 1u;
     }
-    if (!w_chunks && !u_chunks && !loss_blocks) return;
-    if (!w_chunks && !u_chunks) g.d4 = 17;        // (only the loss part runs: any supported shape)
-#define CALL(G, NV) launch_stage_shape<G, NV>(s, w_chunks, u_chunks, loss_blocks, first, st)
-    W2V_DISPATCH_GEOM(g.d4, CALL);
+#define CALL(G, NV) launch_stage_shape<G, NV>(s, first, st)
+    W2V_DISPATCH_GEOM(x.g.d4, CALL);
 #undef CALL
 }
 
@@ -619,6 +715,9 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
     const uint32_t ps0 = active ? c * CP : 0u;
     const uint32_t cnt = active ? min(CP, a.n - ps0) : 0u;
     const uint32_t T = a.T;
+    // (the output side's border slots must be clear before its kernel: a share of them per block)
+    for (uint32_t i = blockIdx.x * USEG_THREADS + threadIdx.x; i < a.clear_count; i += gridDim.x * USEG_THREADS)
+        a.clear_keys[i] = KEY_NONE;
     for (uint32_t i = l; i < cnt; i += G) {
         s_pair[grp][i] = a.perm[ps0 + i];
         s_skey[grp][i + 1] = a.skey[ps0 + i];
@@ -785,6 +884,9 @@ __global__ __launch_bounds__(USEG_THREADS, 5) void useg_multi_kernel(USideArgs a
     const bool active = c < nchunks;
     const uint32_t ps0 = active ? c * CP : 0u;
     const uint32_t cnt = active ? min(CP, a.n - ps0) : 0u;
+    // (the output side's border slots must be clear before its kernel: a share of them per block)
+    for (uint32_t i = blockIdx.x * USEG_THREADS + threadIdx.x; i < a.clear_count; i += gridDim.x * USEG_THREADS)
+        a.clear_keys[i] = KEY_NONE;
     for (uint32_t i = l; i < cnt; i += G) {
         s_pair[grp][i] = a.perm[ps0 + i];
         s_skey[grp][i + 1] = a.skey[ps0 + i];
@@ -976,51 +1078,6 @@ void launch_useg(const USideArgs& a, hipStream_t st) {
 #define SHAPE(G, NV) launch_useg_shape<G, NV>(a, st)
     W2V_DISPATCH_GEOM(a.g.d4, SHAPE);
 #undef SHAPE
-}
-
-// ---------------------------------------------------------------------------------------------
-// Write-back of the input-vector changes held in the delta buffer.
-// ---------------------------------------------------------------------------------------------
-// A lane group looks at G consecutive sorted positions at once (one dkey per lane) and then walks
-// the few that carry a finished run.
-template <int G, int NV>
-__global__ __launch_bounds__(ADJ_THREADS) void apply_delta_kernel(float4* __restrict__ U, RowGeom g,
-                                                                  const float4* __restrict__ delta,
-                                                                  const uint32_t* __restrict__ dkey,
-                                                                  uint32_t n, float alpha_arg,
-                                                                  const CallScalars* dev) {
-    const float alpha = dev ? dev->alpha : alpha_arg;
-    const int l = threadIdx.x % G;
-    const uint32_t grp = (blockIdx.x * (uint32_t)ADJ_THREADS + threadIdx.x) / G;
-    const uint32_t base = grp * (uint32_t)G;
-    if (base >= n) return;
-    const uint32_t mine = (base + l < n) ? dkey[base + l] : KEY_NONE;
-    for (int e = 0; e < G; ++e) {
-        const uint32_t key = __shfl(mine, e, G);
-        if (key == KEY_NONE) continue;
-        const uint32_t ps = base + e;
-        float4 dv[NV], uv[NV];
-        load_row<G, NV>(delta + (uint64_t)ps * g.stride4, g.d4, l, dv);
-        load_row<G, NV>(U + (uint64_t)key * g.stride4, g.d4, l, uv);
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            uv[v].x = fmaf(alpha, dv[v].x, uv[v].x);
-            uv[v].y = fmaf(alpha, dv[v].y, uv[v].y);
-            uv[v].z = fmaf(alpha, dv[v].z, uv[v].z);
-            uv[v].w = fmaf(alpha, dv[v].w, uv[v].w);
-        }
-        store_row<G, NV>(U + (uint64_t)key * g.stride4, g.stride4, l, uv);
-    }
-}
-
-void launch_apply_delta(float* U, RowGeom g, const float* delta, const uint32_t* dkey, uint32_t n,
-                        float alpha, hipStream_t st, const CallScalars* dev) {
-    if (n == 0) return;
-#define CALL(G, NV)                                                                              \
-    hipLaunchKernelGGL((apply_delta_kernel<G, NV>), dim3(blocks_for(n, ADJ_THREADS)),            \
-                       dim3(ADJ_THREADS), 0, st, (float4*)U, g, (const float4*)delta, dkey, n, alpha, dev)
-    W2V_DISPATCH_GEOM(g.d4, CALL);
-#undef CALL
 }
 
 }  // namespace w2v

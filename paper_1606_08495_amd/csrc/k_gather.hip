@@ -61,8 +61,8 @@ void launch_init(float* M, uint32_t V, RowGeom g, uint32_t d_slice, uint32_t d_t
 // export).  Bound by memory: a block moves a whole number of rows, MOVE_ITEMS accesses per thread, each
 // as wide as the widths, the pitch and the caller's pointer allow (16 bytes when the row length is a
 // multiple of four floats), four of them in flight; the words are read and range-checked once per row.
-// (One 4-byte access per thread, a division and a word load each, before: reading back 1.0 M + 2.4 M
-// rows of 1200 bytes took 3.11 ms, now 1.56 ms, 5.2 TB/s read and written.)
+// (One 4-byte access per thread, a division and a word load each, before: reading back 0.5 M + 2.7 M
+// rows of 1200 bytes took 3.11 ms, now 1.56 ms, 4.9 TB/s read and written.)
 // ---------------------------------------------------------------------------------------------
 constexpr int MOVE_ITEMS = 8;
 constexpr int MOVE_ROWS_MAX = 1024;               // rows of a block, at most (their words sit in LDS)
@@ -360,78 +360,57 @@ void launch_dots(const float* U, const float* W, RowGeom g, const uint32_t* in_i
 // ---------------------------------------------------------------------------------------------
 // Client step between the two calls: f = sum over shards of the partial dots (shard order), then
 // the coefficient label - sigma(f), written as sigma(-f) for the positive slot so that it keeps
-// its relative accuracy when f is large.  Loss terms are softplus(-f) / softplus(f), summed per
-// block in double by a fixed tree, then over blocks in index order by one thread.
+// its relative accuracy when f is large.  Loss terms are softplus(-f) / softplus(f), summed in double
+// in a fixed order, per block and then over the blocks.
 // ---------------------------------------------------------------------------------------------
 
 __global__ __launch_bounds__(256) void coeffs_kernel(PartialPtrs parts, uint32_t S, uint32_t total,
                                                      uint32_t T, float* __restrict__ coeffs,
                                                      double* __restrict__ block_loss) {
-    __shared__ double red[256];
-    uint32_t i = blockIdx.x * 256 + threadIdx.x;
-    double term = 0.0;
-    if (i < total) {
+    __shared__ double red[4];
+    const uint32_t lo = blockIdx.x * LOSS_TERMS, hi = min(total - lo, LOSS_TERMS) + lo;
+    double sum = 0.0;
+    for (uint32_t i = lo + threadIdx.x; i < hi; i += 256) {
         float f = 0.f;
         for (uint32_t s = 0; s < S; ++s) f += parts.p[s][i];
-        uint32_t j = i % T;
-        float gcoef;
-        if (j == 0) { gcoef = 1.0f / (1.0f + expf(f)); term = (double)softplus(-f); }
-        else        { gcoef = -1.0f / (1.0f + expf(-f)); term = (double)softplus(f); }
+        float gcoef, term = 0.f;
+        if (i % T == 0) { gcoef = 1.0f / (1.0f + expf(f)); if (block_loss) term = softplus(-f); }
+        else            { gcoef = -1.0f / (1.0f + expf(-f)); if (block_loss) term = softplus(f); }
         coeffs[i] = gcoef;
+        sum += (double)term;
     }
     if (block_loss) {
-        red[threadIdx.x] = term;
-        __syncthreads();
-        for (int s = 128; s >= 1; s >>= 1) {
-            if ((int)threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-            __syncthreads();
-        }
-        if (threadIdx.x == 0) block_loss[blockIdx.x] = red[0];
+        const double s = block_tree_sum<256>(sum, red);
+        if (threadIdx.x == 0) block_loss[blockIdx.x] = s;
     }
 }
 
-// Sum of n doubles in a fixed order: block b of a grid takes the slice [b*span, (b+1)*span), its
-// thread t adds elements t, t+256, ... of the slice in order, then the block reduces by a fixed
-// tree.  Called once over the data (-> one partial per block) and once, with a single block, over
-// the partials.
 __global__ __launch_bounds__(256) void sum_doubles_kernel(const double* __restrict__ x, uint32_t n,
-                                                          uint32_t span,
                                                           double* __restrict__ out) {
-    __shared__ double red[256];
-    sum_doubles_block(x, n, span, out, blockIdx.x, red);
+    __shared__ double red[4];
+    sum_doubles_block<256>(x, n, out, red);
 }
 
-
-// x[n] -> *out, using tmp[ceil(n / LOSS_SUM_SPAN)] doubles.
-static void launch_sum_doubles(const double* x, uint32_t n, double* tmp, double* out,
-                               hipStream_t st) {
-    uint32_t nb = (n + LOSS_SUM_SPAN - 1) / LOSS_SUM_SPAN;
-    if (nb <= 1) {
-        hipLaunchKernelGGL(sum_doubles_kernel, dim3(1), dim3(256), 0, st, x, n, n ? n : 1u, out);
-        return;
-    }
-    hipLaunchKernelGGL(sum_doubles_kernel, dim3(nb), dim3(256), 0, st, x, n, LOSS_SUM_SPAN, tmp);
-    hipLaunchKernelGGL(sum_doubles_kernel, dim3(1), dim3(256), 0, st, (const double*)tmp, nb, nb,
-                       out);
+static void launch_sum_doubles(const double* x, uint32_t n, double* out, hipStream_t st) {
+    hipLaunchKernelGGL(sum_doubles_kernel, dim3(1), dim3(256), 0, st, x, n, out);
 }
 
-// doubles of scratch for the loss: the per-block (or per-pair) terms plus the second-stage partials
+// doubles of scratch for the loss: one per block of terms
 size_t coeffs_loss_scratch_doubles(uint32_t n, uint32_t T) {
-    size_t terms = std::max<size_t>(blocks_for((uint64_t)n * T, 256), n);
-    return terms + (terms + LOSS_SUM_SPAN - 1) / LOSS_SUM_SPAN + 8;
+    return blocks_for((uint64_t)n * T, LOSS_TERMS) + 8;
 }
 
 void launch_coeffs(PartialPtrs parts, uint32_t S, uint32_t n, uint32_t T, float* coeffs,
                    double* block_loss, double* loss_out, hipStream_t st) {
     uint32_t total = n * T;
     if (total == 0) {
-        if (loss_out) launch_sum_doubles(nullptr, 0, nullptr, loss_out, st);
+        if (loss_out) launch_sum_doubles(nullptr, 0, loss_out, st);
         return;
     }
-    unsigned nb = blocks_for(total, 256);
+    unsigned nb = blocks_for(total, LOSS_TERMS);
     hipLaunchKernelGGL(coeffs_kernel, dim3(nb), dim3(256), 0, st, parts, S, total, T, coeffs,
                        loss_out ? block_loss : (double*)nullptr);
-    if (loss_out) launch_sum_doubles(block_loss, nb, block_loss + nb, loss_out, st);
+    if (loss_out) launch_sum_doubles(block_loss, nb, loss_out, st);
 }
 
 // Minibatch loss of the fused step, from the dots the input-side kernel leaves behind: the same
@@ -440,17 +419,17 @@ void launch_coeffs(PartialPtrs parts, uint32_t S, uint32_t n, uint32_t T, float*
 __global__ __launch_bounds__(256) void loss_from_dots_kernel(const float* __restrict__ dots,
                                                              uint32_t total, uint32_t T,
                                                              double* __restrict__ block_loss) {
-    __shared__ double red[256];
-    loss_terms_block(dots, total, T, block_loss, blockIdx.x, red);
+    __shared__ double red[4];
+    loss_terms_block<256>(dots, total, T, block_loss, blockIdx.x, red);
 }
 
 void launch_loss_from_dots(const float* dots, uint32_t n, uint32_t T, double* tmp, double* loss_out,
                            hipStream_t st) {
     uint32_t total = n * T;
-    if (total == 0) { launch_sum_doubles(nullptr, 0, nullptr, loss_out, st); return; }
-    unsigned nb = blocks_for(total, 256);
+    if (total == 0) { launch_sum_doubles(nullptr, 0, loss_out, st); return; }
+    unsigned nb = blocks_for(total, LOSS_TERMS);
     hipLaunchKernelGGL(loss_from_dots_kernel, dim3(nb), dim3(256), 0, st, dots, total, T, tmp);
-    launch_sum_doubles(tmp, nb, tmp + nb, loss_out, st);
+    launch_sum_doubles(tmp, nb, loss_out, st);
 }
 
 }  // namespace w2v

@@ -262,6 +262,49 @@ def test_adjust_heavy_rows_many_levels():
     assert eu <= TOL1 and ew <= TOL1
 
 
+@pytest.mark.parametrize("d", [4, 64, 68, 128, 132, 256, 260, 516, 1000])       # every row geometry
+@pytest.mark.parametrize("n,k", [(255, 0), (4097, 1), (16_385, 0), (30_001, 5)])
+def test_adjust_runs_across_the_borders_of_every_level(d, n, k):
+    """Runs of every length, from one contribution to a quarter of the minibatch, so that pieces are cut
+    by lane groups' parts, blocks and levels of the reduction alike."""
+    V = 3000
+    rng = np.random.default_rng(d + n)
+    words = np.concatenate([np.full(n // 4, 5), np.full(n // 7, 6), np.repeat(np.arange(7, 40), 1 + n // 200),
+                            np.repeat(np.arange(40, 700), rng.integers(1, 9, 660))])
+    pick = lambda: rng.permutation(np.concatenate([words, rng.integers(0, V, n)]))[:n].astype(np.uint32)
+    eu, ew = run_adjust_case(V, d, n, k, pick(), pick(), label="borders")
+    assert eu <= TOL1 and ew <= TOL1
+
+
+@pytest.mark.parametrize("V,d,n,k", [(3000, 132, 180_000, 5), (3000, 300, 131_072, 7)])
+def test_large_minibatch_whose_walk_has_its_own_launch(V, d, n, k):
+    """2^20 slots and more at one wavefront per row: the input side's levels and the loss on the second
+    stream; on one stream, and replayed, the same bits."""
+    rng = np.random.default_rng(2)
+    cdf = workloads.zipf_cdf(V, 1.1)
+    a, b = dev(workloads.zipf_draw(cdf, n, rng)), dev(workloads.zipf_draw(cdf, n, rng))
+    counts = workloads.analytic_counts(V, 1.1, 10 ** 7)
+    got = []
+    for form in ("plain", "captured"):
+        sh = w2v.Shard(V, d, 3, init_mode=1)
+        sh.set_counts(counts)
+        loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+        if form == "plain":
+            w2v.train_minibatch([sh], a, b, k, 9, 0.001, loss=loss)
+        else:
+            w2v.StepGraph(sh, n, k, loss=loss).run(a, b, 9, 0.001)
+        sh.status()
+        got.append((all_rows(sh, 0), all_rows(sh, 1), loss.item()))
+        sh.destroy()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
+    assert abs(got[0][2] - got[1][2]) <= 1e-12 * abs(got[0][2])     # (summed in blocks of other sizes)
+    rows = np.arange(V, dtype=np.uint32)
+    U, W = oracle.init_rows(3, d, 0, d, 0, rows), oracle.init_rows(3, d, 0, d, 1, rows)
+    th, al = oracle.build_alias(counts)
+    oracle.train_minibatch([U], [W], w2v.index_to_numpy(a), w2v.index_to_numpy(b), k, 9, th, al, 0.001)
+    assert vec_error(got[0][0], U) <= TOL1 and vec_error(got[0][1], W) <= TOL1
+
+
 def test_adjust_reads_start_of_call_vectors():
     # the same pair twice in one call gives exactly twice the change of one call (T8)
     V, d = 6, 60
