@@ -127,10 +127,15 @@ void launch_sort_pairs(const uint32_t* keys_in, uint2* buf0, uint2* buf1, uint32
                        uint32_t* tmp, uint32_t** out_keys, uint32_t** out_vals, uint32_t* err,
                        hipStream_t st);
 
-// Exclusive prefix sum of n uint32 (in place allowed); total (may be null) gets the sum.
+// Exclusive prefix sum of many uint32 whose sums per scan_tile() consecutive elements are known: the sums
+// are scanned in place (scan_scratch_u32(n) of them; total may be null; a second array of as many rides
+// along), then out[i] = exclusive prefix of in[i] >> shift.
 size_t scan_scratch_u32(uint32_t n);
-void launch_exclusive_scan(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* tmp,
-                           uint32_t* total, hipStream_t st);
+uint32_t scan_tile();
+void launch_scan_sums(uint32_t* sums, uint32_t nb, uint32_t* total, hipStream_t st, uint32_t* sums2 = nullptr,
+                      uint32_t* total2 = nullptr);
+void launch_scan_apply(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t shift, const uint32_t* sums,
+                       hipStream_t st);
 
 // ---- adjust ------------------------------------------------------------------------------------
 // Chunk sizes of the segmented reductions (entries per lane group).
@@ -255,9 +260,5 @@ void launch_iota(uint32_t* x, uint32_t n, hipStream_t st);
 // H[p] = mean of U[ctx_safe[e]] over the entries of example p (row geometry g).
 void launch_cbow_hidden(const float* U, RowGeom g, const uint32_t* ctx_off, const uint32_t* ctx_safe,
                         uint32_t n, uint32_t m, float* H, hipStream_t st);
-void launch_cbow_examples(const uint32_t* kcnt, const uint32_t* kword, const uint32_t* poff,
-                          const uint32_t* n_kept, uint32_t n, uint32_t* flag, uint32_t* ex,
-                          uint32_t* scan_tmp, uint32_t* ctx_off, uint32_t* out_idx,
-                          uint64_t cap_examples, uint32_t* total_examples, hipStream_t st);
 
 }  // namespace w2v

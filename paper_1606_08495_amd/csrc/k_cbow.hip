@@ -129,44 +129,4 @@ void launch_cbow_hidden(const float* U, RowGeom g, const uint32_t* ctx_off, cons
 #undef CALL
 }
 
-// ---------------------------------------------------------------------------------------------
-// Examples from text, on top of the pair formation's per-survivor results: survivor q with
-// kcnt[q] > 0 context words becomes example number ex[q] (exclusive count of such survivors); its
-// context words are the pair stream's output words poff[q] .. poff[q] + kcnt[q].
-// ---------------------------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void cbow_example_flags_kernel(const uint32_t* __restrict__ kcnt,
-                                                                 const uint32_t* __restrict__ n_kept,
-                                                                 uint32_t n,
-                                                                 uint32_t* __restrict__ flag) {
-    uint32_t q = blockIdx.x * 256 + threadIdx.x;
-    if (q >= n) return;
-    flag[q] = (q < *n_kept && kcnt[q] > 0) ? 1u : 0u;
-}
-
-__global__ __launch_bounds__(256) void cbow_example_write_kernel(
-    const uint32_t* __restrict__ kcnt, const uint32_t* __restrict__ kword,
-    const uint32_t* __restrict__ poff, const uint32_t* __restrict__ ex,
-    const uint32_t* __restrict__ n_kept, uint32_t n, uint32_t* __restrict__ ctx_off,
-    uint32_t* __restrict__ out_idx, uint64_t cap_examples) {
-    uint32_t q = blockIdx.x * 256 + threadIdx.x;
-    if (q == 0) ctx_off[0] = 0;
-    if (q >= n || q >= *n_kept || kcnt[q] == 0) return;
-    const uint64_t x = ex[q];
-    if (x >= cap_examples) return;
-    out_idx[x] = kword[q];
-    ctx_off[x + 1] = poff[q] + kcnt[q];
-}
-
-void launch_cbow_examples(const uint32_t* kcnt, const uint32_t* kword, const uint32_t* poff,
-                          const uint32_t* n_kept, uint32_t n, uint32_t* flag, uint32_t* ex,
-                          uint32_t* scan_tmp, uint32_t* ctx_off, uint32_t* out_idx,
-                          uint64_t cap_examples, uint32_t* total_examples, hipStream_t st) {
-    const dim3 grid(blocks_for(n ? n : 1, 256)), block(256);
-    if (n > 0)
-        hipLaunchKernelGGL(cbow_example_flags_kernel, grid, block, 0, st, kcnt, n_kept, n, flag);
-    launch_exclusive_scan(flag, ex, n, scan_tmp, total_examples, st);
-    hipLaunchKernelGGL(cbow_example_write_kernel, grid, block, 0, st, kcnt, kword, poff, ex, n_kept, n,
-                       ctx_off, out_idx, cap_examples);
-}
-
 }  // namespace w2v

@@ -11,8 +11,8 @@ static inline unsigned blocks_for(uint64_t items, unsigned per_block) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Scan.  Blocks of 256 threads x 8 items: (1) per-block sums, (2) one block scans the sums with a
-// running carry, (3) per-block local scan plus the block's offset.
+// Scan.  Tiles of 256 threads x 8 items: (1) per-tile sums (whoever makes the elements counts them),
+// (2) one block scans the sums with a running carry, (3) per-tile local scan plus the tile's offset.
 // ---------------------------------------------------------------------------------------------
 constexpr int SCAN_THREADS = 256;
 constexpr int SCAN_ITEMS = 8;
@@ -43,30 +43,28 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* w
     return base + incl - x;
 }
 
-__global__ __launch_bounds__(SCAN_THREADS) void scan_block_sums_kernel(
-    const uint32_t* __restrict__ in, uint32_t n, uint32_t* __restrict__ sums) {
-    __shared__ uint32_t wave_sums[4];
-    __shared__ uint32_t total;
-    uint64_t base = (uint64_t)blockIdx.x * SCAN_TILE + (uint64_t)threadIdx.x * SCAN_ITEMS;
-    uint32_t s = 0;
-#pragma unroll
-    for (int e = 0; e < SCAN_ITEMS; ++e)
-        if (base + e < n) s += in[base + e];
-    block_exclusive_scan(s, wave_sums, &total);
-    if (threadIdx.x == 0) sums[blockIdx.x] = total;
-}
-
-__global__ __launch_bounds__(SCAN_THREADS) void scan_sums_kernel(uint32_t* __restrict__ sums,
-                                                                 uint32_t nb,
-                                                                 uint32_t* __restrict__ total_out) {
+// (sixteen sums per thread and step: a running carry over n / 256 of them is two steps for two million)
+constexpr int SCAN_SUMS_ITEMS = 16;
+__global__ __launch_bounds__(SCAN_THREADS) void scan_sums_kernel(uint32_t* __restrict__ sums0,
+                                                                 uint32_t* __restrict__ total0,
+                                                                 uint32_t* __restrict__ sums1,
+                                                                 uint32_t* __restrict__ total1, uint32_t nb) {
+    uint32_t* __restrict__ sums = blockIdx.x ? sums1 : sums0;
+    uint32_t* __restrict__ total_out = blockIdx.x ? total1 : total0;
     __shared__ uint32_t wave_sums[4];
     __shared__ uint32_t total;
     uint32_t carry = 0;
-    for (uint32_t start = 0; start < nb; start += SCAN_THREADS) {
-        uint32_t i = start + threadIdx.x;
-        uint32_t x = i < nb ? sums[i] : 0u;
-        uint32_t ex = block_exclusive_scan(x, wave_sums, &total);
-        if (i < nb) sums[i] = carry + ex;
+    for (uint32_t start = 0; start < nb; start += SCAN_THREADS * SCAN_SUMS_ITEMS) {
+        const uint32_t i0 = start + threadIdx.x * SCAN_SUMS_ITEMS;
+        uint32_t v[SCAN_SUMS_ITEMS], x = 0;
+#pragma unroll
+        for (int e = 0; e < SCAN_SUMS_ITEMS; ++e) { v[e] = i0 + e < nb ? sums[i0 + e] : 0u; x += v[e]; }
+        uint32_t run = carry + block_exclusive_scan(x, wave_sums, &total);
+#pragma unroll
+        for (int e = 0; e < SCAN_SUMS_ITEMS; ++e) {
+            if (i0 + e < nb) sums[i0 + e] = run;
+            run += v[e];
+        }
         carry += total;
         __syncthreads();
     }
@@ -75,7 +73,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_sums_kernel(uint32_t* __res
 
 __global__ __launch_bounds__(SCAN_THREADS) void scan_apply_kernel(const uint32_t* __restrict__ in,
                                                                   uint32_t* __restrict__ out,
-                                                                  uint32_t n,
+                                                                  uint32_t n, uint32_t shift,
                                                                   const uint32_t* __restrict__ sums) {
     __shared__ uint32_t wave_sums[4];
     __shared__ uint32_t total;
@@ -84,7 +82,7 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_apply_kernel(const uint32_t
     uint32_t s = 0;
 #pragma unroll
     for (int e = 0; e < SCAN_ITEMS; ++e) {
-        v[e] = (base + e < n) ? in[base + e] : 0u;
+        v[e] = (base + e < n) ? in[base + e] >> shift : 0u;
         s += v[e];
     }
     uint32_t run = block_exclusive_scan(s, wave_sums, &total) + sums[blockIdx.x];
@@ -97,16 +95,18 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_apply_kernel(const uint32_t
 
 size_t scan_scratch_u32(uint32_t n) { return blocks_for(n, SCAN_TILE) + 1; }
 
-void launch_exclusive_scan(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t* tmp,
-                           uint32_t* total, hipStream_t st) {
-    unsigned nb = blocks_for(n, SCAN_TILE);
-    if (n == 0) {
-        hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(SCAN_THREADS), 0, st, tmp, 0u, total);
-        return;
-    }
-    hipLaunchKernelGGL(scan_block_sums_kernel, dim3(nb), dim3(SCAN_THREADS), 0, st, in, n, tmp);
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(SCAN_THREADS), 0, st, tmp, nb, total);
-    hipLaunchKernelGGL(scan_apply_kernel, dim3(nb), dim3(SCAN_THREADS), 0, st, in, out, n, tmp);
+void launch_scan_sums(uint32_t* sums, uint32_t nb, uint32_t* total, hipStream_t st, uint32_t* sums2,
+                      uint32_t* total2) {
+    hipLaunchKernelGGL(scan_sums_kernel, dim3(sums2 ? 2 : 1), dim3(SCAN_THREADS), 0, st, sums, total, sums2, total2, nb);
+}
+
+uint32_t scan_tile() { return SCAN_TILE; }
+
+void launch_scan_apply(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t shift, const uint32_t* sums,
+                       hipStream_t st) {
+    if (n == 0) return;
+    hipLaunchKernelGGL(scan_apply_kernel, dim3(blocks_for(n, SCAN_TILE)), dim3(SCAN_THREADS), 0, st, in, out, n,
+                       shift, sums);
 }
 
 // ---------------------------------------------------------------------------------------------

@@ -885,6 +885,36 @@ def test_random_text_blocks_pairs_interleaved_pairs_and_examples(case):
     sh.destroy()
 
 
+@pytest.mark.parametrize("n_tok", [1, 255, 256, 257, 2047, 2048, 2049, 70_000])    # blocks of 256, scan tiles of 2048
+@pytest.mark.parametrize("shape", ["one sentence", "single words", "empty ones between", "long"])
+def test_formation_at_the_edges_of_blocks_and_scan_tiles(n_tok, shape):
+    rng = np.random.default_rng(n_tok)
+    V, B, t = 500, 7, 0.05
+    tokens = workloads.zipf_draw(workloads.zipf_cdf(V, 1.0), n_tok, rng)
+    counts = np.maximum(1, workloads.counted(tokens, V))
+    off = {"one sentence": np.array([0, n_tok]), "single words": np.arange(n_tok + 1),
+           "empty ones between": np.repeat(np.append(np.arange(0, n_tok, 9), n_tok), 4),
+           "long": np.append(np.arange(0, n_tok, 300), n_tok)}[shape].astype(np.uint64)
+    sh = make_shard(V, 4, 1, counts, t)
+    kt = oracle.build_keep(counts, t)
+    doff = torch.from_numpy(off.astype(np.int64)).cuda()
+    gi, go = (torch.empty(n_tok * 2 * B, dtype=torch.int32, device="cuda") for _ in range(2))
+    for inter in (False, True):
+        cnt = sh.make_pairs(dev(tokens), doff, 77, 1, 5, B, gi, go, interleaved=inter)
+        oi, oo, ocnt = oracle.make_pairs(tokens, off, 77, 1, 5, B, kt, interleaved=inter)
+        assert cnt == ocnt
+        assert np.array_equal(w2v.index_to_numpy(gi[:cnt]), oi) and np.array_equal(w2v.index_to_numpy(go[:cnt]), oo)
+    co = torch.full((n_tok + 1,), -1, dtype=torch.int32, device="cuda")
+    ce = torch.empty(n_tok, dtype=torch.int32, device="cuda")
+    n_ex, n_ctx = sh.make_cbow_examples(dev(tokens), doff, 77, 1, 5, B, co, go, ce)
+    ooff, octx, oout, ocnt, onctx = oracle.make_cbow_examples(tokens, off, 77, 1, 5, B, kt)
+    assert (n_ex, n_ctx) == (ocnt, onctx)
+    assert np.array_equal(w2v.index_to_numpy(co[:n_ex + 1]), ooff)
+    assert np.array_equal(w2v.index_to_numpy(go[:n_ctx]), octx) and np.array_equal(w2v.index_to_numpy(ce[:n_ex]), oout)
+    sh.status()
+    sh.destroy()
+
+
 # --- look-ahead ------------------------------------------------------------------------------------------
 
 def test_prefetch_gives_the_same_bits_and_a_mismatch_is_harmless():
