@@ -675,7 +675,7 @@ void launch_adjust_stage(const AdjustStage& x, hipStream_t st) {
     s.loss_step = x.loss_step;
     if (x.loss_step) {
         s.dots = x.dots; s.total = x.n * x.T; s.T = x.T; s.block_loss = x.loss_tmp;
-        s.nb = blocks_for(s.total, LOSS_TERMS); s.loss_out = x.loss_out;
+        s.nb = blocks_for(s.total, loss_terms_of(s.total)); s.loss_out = x.loss_out;
         s.loss_blocks = x.loss_step == 1 ? s.nb : 1u;
     }
 #define CALL(G, NV) launch_stage_shape<G, NV>(s, first, st)

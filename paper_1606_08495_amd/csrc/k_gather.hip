@@ -368,7 +368,7 @@ __global__ __launch_bounds__(256) void coeffs_kernel(PartialPtrs parts, uint32_t
                                                      uint32_t T, float* __restrict__ coeffs,
                                                      double* __restrict__ block_loss) {
     __shared__ double red[4];
-    const uint32_t lo = blockIdx.x * LOSS_TERMS, hi = min(total - lo, LOSS_TERMS) + lo;
+    const uint32_t terms = loss_terms_of(total), lo = blockIdx.x * terms, hi = min(total - lo, terms) + lo;
     double sum = 0.0;
     for (uint32_t i = lo + threadIdx.x; i < hi; i += 256) {
         float f = 0.f;
@@ -397,7 +397,7 @@ static void launch_sum_doubles(const double* x, uint32_t n, double* out, hipStre
 
 // doubles of scratch for the loss: one per block of terms
 size_t coeffs_loss_scratch_doubles(uint32_t n, uint32_t T) {
-    return blocks_for((uint64_t)n * T, LOSS_TERMS) + 8;
+    return blocks_for((uint64_t)n * T, loss_terms_of(n * T)) + 8;
 }
 
 void launch_coeffs(PartialPtrs parts, uint32_t S, uint32_t n, uint32_t T, float* coeffs,
@@ -407,7 +407,7 @@ void launch_coeffs(PartialPtrs parts, uint32_t S, uint32_t n, uint32_t T, float*
         if (loss_out) launch_sum_doubles(nullptr, 0, loss_out, st);
         return;
     }
-    unsigned nb = blocks_for(total, LOSS_TERMS);
+    unsigned nb = blocks_for(total, loss_terms_of(total));
     hipLaunchKernelGGL(coeffs_kernel, dim3(nb), dim3(256), 0, st, parts, S, total, T, coeffs,
                        loss_out ? block_loss : (double*)nullptr);
     if (loss_out) launch_sum_doubles(block_loss, nb, loss_out, st);
@@ -427,7 +427,7 @@ void launch_loss_from_dots(const float* dots, uint32_t n, uint32_t T, double* tm
                            hipStream_t st) {
     uint32_t total = n * T;
     if (total == 0) { launch_sum_doubles(nullptr, 0, loss_out, st); return; }
-    unsigned nb = blocks_for(total, LOSS_TERMS);
+    unsigned nb = blocks_for(total, loss_terms_of(total));
     hipLaunchKernelGGL(loss_from_dots_kernel, dim3(nb), dim3(256), 0, st, dots, total, T, tmp);
     launch_sum_doubles(tmp, nb, loss_out, st);
 }

@@ -6,10 +6,11 @@
 
 namespace w2v {
 
-// Terms per block: sixteen or more a thread, so that the block's reduction is a small part of its work
-// (256 a block, one per thread and eight barriers each, before: 0.35 ms beside the row kernels for the
-// 11.5 M terms of a search minibatch).
-constexpr uint32_t LOSS_TERMS = 4096;
+// Terms per block: a few per thread, so that the block's reduction is a small part of its work (256 a
+// block, one per thread and eight barriers each, took 0.35 ms beside the row kernels for the 11.5 M terms
+// of a search minibatch) and there are still blocks for the whole chip (4096 a block: 36 us for 600 000
+// terms over five shards against 9).  Past 2^24 terms more, for the one block that adds up the sums.
+__host__ __device__ inline uint32_t loss_terms_of(uint32_t total) { return total <= (1u << 24) ? 1024u : 16384u; }
 
 // log(1 + e^x) without overflow or cancellation
 __device__ __forceinline__ float softplus(float x) {
@@ -34,7 +35,7 @@ template <int THREADS>
 __device__ __forceinline__ void loss_terms_block(const float* __restrict__ dots, uint32_t total,
                                                  uint32_t T, double* __restrict__ block_loss,
                                                  uint32_t vb, double* red) {
-    const uint32_t lo = vb * LOSS_TERMS, hi = min(total - lo, LOSS_TERMS) + lo;
+    const uint32_t terms = loss_terms_of(total), lo = vb * terms, hi = min(total - lo, terms) + lo;
     double v = 0.0;
     for (uint32_t i = lo + threadIdx.x; i < hi; i += THREADS) {
         const float f = dots[i];
@@ -50,6 +51,7 @@ template <int THREADS>
 __device__ __forceinline__ void sum_doubles_block(const double* __restrict__ x, uint32_t n,
                                                   double* __restrict__ out, double* red) {
     double s = 0.0;
+#pragma unroll 8
     for (uint32_t i = threadIdx.x; i < n; i += THREADS) s += x[i];
     const double r = block_tree_sum<THREADS>(s, red);
     if (threadIdx.x == 0) *out = r;
