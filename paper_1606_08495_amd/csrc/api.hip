@@ -1233,7 +1233,7 @@ CbowPlan make_cbow_plan(char* base, uint32_t n, uint32_t k, uint32_t m, uint32_t
         p.E = c.take<float>((size_t)n * row);
         p.dkey = c.take<uint32_t>(n);
         p.wb0 = c.take<uint2>(p.M); p.wb1 = c.take<uint2>(p.M);
-        p.sort_tmp_w = c.take<uint32_t>(sort_scratch_u32(p.M));
+        p.sort_tmp_w = c.take<uint32_t>(sort_scratch_u32(p.M, m));       // (room for the joint sort)
         p.cb0 = c.take<uint2>(m); p.cb1 = c.take<uint2>(m);
         p.sort_tmp_c = c.take<uint32_t>(sort_scratch_u32(m));
         p.slots_a = slots_after(n, useg_pairs_per_chunk(p.T, 1, n));
@@ -1251,6 +1251,11 @@ CbowPlan make_cbow_plan(char* base, uint32_t n, uint32_t k, uint32_t m, uint32_t
     return p;
 }
 
+// Minibatches so small that every kernel takes a few microseconds.  (Per step, on several streams and on
+// one: 50 examples 163 and 81 us, 4000 175 and 110, 9000 182 and 138; at 20 000, past the line, the streams
+// stay.)
+bool cbow_small(const CbowPlan& p) { return (uint64_t)p.M + p.m < (1u << 17); }
+
 int check_cbow_batch(const w2v_shard* sh, uint32_t n, uint32_t k, uint32_t m) {
     int rc = check_batch(sh, n, k, true);
     if (rc) return rc;
@@ -1260,13 +1265,15 @@ int check_cbow_batch(const w2v_shard* sh, uint32_t n, uint32_t k, uint32_t m) {
 
 // Checked context entries, example numbers and weights, the destination keys, and (for adjust)
 // both sorts: destinations of the M output-side contributions, words of the m context entries.
-// With the second stream, the keys and the sorts are queued there (they depend on the indices
+// A small minibatch keeps to the caller's stream, both sorts in the same launches (*join false): there a
+// step is a chain of launches, and events between streams cost more than the overlap gives.
+// Else, with the second stream, the keys and the sorts are queued there (they depend on the indices
 // only) while the caller's stream forms the hidden vectors; cbow_wait_keys / join_output_sort make
 // the caller's stream wait for them where they are first needed.
 int queue_cbow_indices(w2v_shard* sh, CbowPlan& p, const uint32_t* ctx_off, const uint32_t* ctx_idx,
                        const uint32_t* out_idx, uint32_t k, uint64_t seed, bool sorts,
                        uint32_t** skw, uint32_t** sidx, uint32_t** skc, uint32_t** cidx,
-                       hipStream_t st) {
+                       bool* join, hipStream_t st) {
     {
         Phase ph(sh, W2V_PH_NEG, st);
         launch_cbow_entries(ctx_off, ctx_idx, p.n, p.m, sh->V, p.ctx_safe, p.ex_of, p.weight,
@@ -1274,7 +1281,8 @@ int queue_cbow_indices(w2v_shard* sh, CbowPlan& p, const uint32_t* ctx_off, cons
         launch_iota(p.iota, p.n, st);
     }
     hipStream_t wst = st;
-    const bool two = sorts && sh->overlap;
+    const bool two = sorts && sh->overlap && !cbow_small(p);
+    *join = two;
     if (two) {
         int rc = ensure_side_stream(sh);
         if (rc) return rc;
@@ -1291,6 +1299,13 @@ int queue_cbow_indices(w2v_shard* sh, CbowPlan& p, const uint32_t* ctx_off, cons
     {
         Phase ph(sh, W2V_PH_SORT, wst);
         const uint32_t bits = key_bits(sh->V);
+        if (cbow_small(p)) {
+            const SortJob jobs[2] = {{p.keys, p.M, p.wb0, p.wb1, skw, sidx},
+                                     {p.ctx_safe, p.m, p.cb0, p.cb1, skc, cidx}};
+            launch_sort_jobs(jobs, 2, bits, p.sort_tmp_w, sh->err, st);
+            if (p.own_rows) launch_mark_alone(*skw, *sidx, p.M, p.keys, st);
+            return W2V_OK;
+        }
         launch_sort_pairs(p.keys, p.wb0, p.wb1, p.M, bits, p.sort_tmp_w, skw, sidx, sh->err, wst);
         if (p.own_rows) {           // the per-example pass needs the marks: "keys ready" moves here
             launch_mark_alone(*skw, *sidx, p.M, p.keys, wst);
@@ -1328,7 +1343,6 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
     // border slots of both write-back kernels, cleared ahead of the per-example pass (the second
     // stream's kernel starts behind an event recorded after that pass)
     launch_wseg_fill(p.pd_keys, p.m, st);
-    launch_wseg_fill(p.pb_keys, p.M, st);
     {
         Phase ph(owner, W2V_PH_USIDE, st);
         USideArgs a{};
@@ -1337,17 +1351,15 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
         a.dots_out = fused ? dots_out : nullptr; a.delta = p.E; a.dkey = p.dkey;
         a.prows = p.pa_rows; a.pkeys = p.pa_keys; a.fused = fused;
         if (fused && p.own_rows) { a.W_update = sh->W; a.alpha = alpha; }   // source: the hidden vector
+        const FillJob f = wseg_fill_job(p.pb_keys, p.M);
+        a.clear_keys = f.p; a.clear_count = f.count;
         launch_useg(a, st);
     }
-    const bool two = owner->overlap && owner->side;
+    const bool two = owner->overlap && owner->side && !cbow_small(p);
     hipStream_t side = two ? owner->side : st;
     if (two) {
         (void)hipEventRecord(owner->ev_coeffs, st);
         (void)hipStreamWaitEvent(side, owner->ev_coeffs, 0);
-    }
-    if (loss_out) {
-        Phase ph(owner, W2V_PH_COEFF, side);
-        launch_loss_from_dots(dots_out, p.n, p.T, p.loss_tmp, loss_out, side);
     }
     {
         Phase ph(owner, W2V_PH_APPLY, side);
@@ -1358,7 +1370,6 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
         launch_wseg(u, side, true);
         run_tails(sh, sh->U, alpha, p.pd_rows, p.pd_keys, p.slots_c1, p.pe_rows, p.pe_keys, side);
     }
-    if (two) (void)hipEventRecord(owner->ev_tails, side);
     if (join_sorts) join_output_sort(owner, st);
     {
         Phase ph(owner, W2V_PH_WSIDE, st);
@@ -1370,6 +1381,11 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
         launch_wseg(w, st, true);
         run_tails(sh, sh->W, alpha, p.pb_rows, p.pb_keys, p.slots_w1, p.pc_rows, p.pc_keys, st);
     }
+    if (loss_out) {                                   // (queued after both walks: nothing waits for it)
+        Phase ph(owner, W2V_PH_COEFF, side);
+        launch_loss_from_dots(dots_out, p.n, p.T, p.loss_tmp, loss_out, side);
+    }
+    if (two) (void)hipEventRecord(owner->ev_tails, side);
     if (two) (void)hipStreamWaitEvent(st, owner->ev_tails, 0);
 }
 
@@ -1463,12 +1479,12 @@ int use_cbow_prepared(w2v_shard* sh, int which, CbowPlan& p, bool spend, bool fu
 int cbow_indices(w2v_shard* sh, CbowPlan& p, const uint32_t* ctx_off, const uint32_t* ctx_idx,
                  uint32_t m, const uint32_t* out_idx, uint32_t n, uint32_t k, uint64_t seed,
                  bool sorts, bool spend, bool fused, uint32_t** skw, uint32_t** sidx, uint32_t** skc,
-                 uint32_t** cidx, bool* prepared, hipStream_t st) {
+                 uint32_t** cidx, bool* join, hipStream_t st) {
     const int ahead = find_cbow_prepared(sh, ctx_off, ctx_idx, m, out_idx, n, k, seed);
     if (spend) sh->updates++;                             // an update call
-    *prepared = ahead >= 0;
+    *join = false;
     if (ahead >= 0) return use_cbow_prepared(sh, ahead, p, spend, fused, skw, sidx, skc, cidx, st);
-    return queue_cbow_indices(sh, p, ctx_off, ctx_idx, out_idx, k, seed, sorts, skw, sidx, skc, cidx, st);
+    return queue_cbow_indices(sh, p, ctx_off, ctx_idx, out_idx, k, seed, sorts, skw, sidx, skc, cidx, join, st);
 }
 
 int check_cbow_pointers(const uint32_t* ctx_off, const uint32_t* ctx_idx, uint32_t m,
@@ -1495,9 +1511,9 @@ extern "C" int w2v_cbow_dotprod(w2v_shard* sh, const uint32_t* ctx_off, const ui
     rc = ensure_ws(sh, sz.bytes);
     if (rc) return rc;
     CbowPlan p = make_cbow_plan(sh->ws, n, k, m, sh->g.stride4, 0, false, false);
-    bool prepared = false;              // an announced set is used and left for the update
+    bool join = false;                  // (an announced set is used and left for the update)
     rc = cbow_indices(sh, p, ctx_off, ctx_idx, m, out_idx, n, k, seed, false, false, false, nullptr,
-                      nullptr, nullptr, nullptr, &prepared, st);
+                      nullptr, nullptr, nullptr, &join, st);
     if (rc) return rc;
     queue_cbow_hidden(sh, sh, p, ctx_off, st);
     {
@@ -1523,13 +1539,13 @@ extern "C" int w2v_cbow_adjust(w2v_shard* sh, const uint32_t* ctx_off, const uin
     if (rc) return rc;
     CbowPlan p = make_cbow_plan(sh->ws, n, k, m, sh->g.stride4, 0, true, false);
     uint32_t *skw, *sidx, *skc, *cidx;
-    bool prepared = false;
+    bool join = false;                  // keys and sorts come from the second stream
     rc = cbow_indices(sh, p, ctx_off, ctx_idx, m, out_idx, n, k, seed, true, true, false, &skw, &sidx,
-                      &skc, &cidx, &prepared, st);
+                      &skc, &cidx, &join, st);
     if (rc) return rc;
     queue_cbow_hidden(sh, sh, p, ctx_off, st);
-    if (!prepared) cbow_wait_keys(sh, st);
-    queue_cbow_adjust(sh, sh, p, skw, sidx, skc, cidx, coeffs, nullptr, nullptr, false, alpha, nullptr, !prepared, st);
+    if (join) cbow_wait_keys(sh, st);
+    queue_cbow_adjust(sh, sh, p, skw, sidx, skc, cidx, coeffs, nullptr, nullptr, false, alpha, nullptr, join, st);
     HIP_TRY(hipGetLastError());
     return W2V_OK;
 }
@@ -1568,15 +1584,15 @@ extern "C" int w2v_cbow_train_minibatch(w2v_shard* const* shards, uint32_t S,
     CbowPlan p = make_cbow_plan(s0->ws, n, k, m, stride_max, S_dots, true, true);
     p.own_rows = fused && s0->own_rows;
     uint32_t *skw, *sidx, *skc, *cidx;
-    bool prepared = false;
+    bool join = false;                  // keys and sorts come from the second stream
     rc = cbow_indices(s0, p, ctx_off, ctx_idx, m, out_idx, n, k, seed, true, true, fused, &skw, &sidx,
-                      &skc, &cidx, &prepared, st);
+                      &skc, &cidx, &join, st);
     if (rc) return rc;
     if (fused) {
         queue_cbow_hidden(s0, s0, p, ctx_off, st);
-        if (!prepared) cbow_wait_keys(s0, st);
+        if (join) cbow_wait_keys(s0, st);
         queue_cbow_adjust(s0, s0, p, skw, sidx, skc, cidx, nullptr, p.coeffs, loss ? p.dots : nullptr, true,
-                          alpha, loss, !prepared, st);
+                          alpha, loss, join, st);
     } else {
         // As in the two-call protocol, every shard forms its hidden vectors once for the dots and
         // once more for the update (its input vectors do not change in between).
@@ -1584,7 +1600,7 @@ extern "C" int w2v_cbow_train_minibatch(w2v_shard* const* shards, uint32_t S,
         for (uint32_t s = 0; s < S; ++s) {
             float* d = p.dots + (size_t)s * p.M;
             queue_cbow_hidden(s0, shards[s], p, ctx_off, st);
-            if (!prepared) cbow_wait_keys(s0, st);
+            if (join) cbow_wait_keys(s0, st);
             Phase ph(s0, W2V_PH_DOT, st);
             launch_dots(p.H, shards[s]->W, shards[s]->g, p.iota, p.keys, n, p.T, d, st);
             pp.p[s] = d;
@@ -1596,7 +1612,7 @@ extern "C" int w2v_cbow_train_minibatch(w2v_shard* const* shards, uint32_t S,
         for (uint32_t s = 0; s < S; ++s) {
             queue_cbow_hidden(s0, shards[s], p, ctx_off, st);
             queue_cbow_adjust(s0, shards[s], p, skw, sidx, skc, cidx, p.coeffs, nullptr, nullptr, false,
-                              alpha, nullptr, !prepared, st);
+                              alpha, nullptr, join, st);
         }
     }
     HIP_TRY(hipGetLastError());

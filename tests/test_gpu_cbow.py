@@ -363,3 +363,36 @@ def test_announced_cbow_minibatches_give_the_same_bits(S, V, d, k, max_ctx, empt
         assert vec_error(all_rows(sh, 0), U) <= 2 * TOL1 and vec_error(all_rows(sh, 1), W) <= 2 * TOL1
         sh.status()
         sh.destroy()
+
+
+@pytest.mark.parametrize("extra", [-1, 0, 1])
+def test_both_sides_of_the_one_stream_limit(extra):
+    """M + m = 2^17 - 1, 2^17, 2^17 + 1: one stream with both sorts in the same launches, or several;
+    announced, the sorts come from a third form.  The same bits, and the oracle's update."""
+    V, d, k, n = 900, 40, 3, 20_000
+    rng = np.random.default_rng(4)
+    m = (1 << 17) + extra - n * (k + 1)
+    off = np.sort(rng.integers(0, m + 1, n - 1))
+    off = np.concatenate([[0], off, [m]]).astype(np.uint32)
+    cdf = workloads.zipf_cdf(V, 1.0)
+    ctx, out = workloads.zipf_draw(cdf, m, rng), workloads.zipf_draw(cdf, n, rng)
+    counts = workloads.analytic_counts(V, 1.0, 10 ** 7)
+    args = (w2v.as_index_tensor(off), w2v.as_index_tensor(ctx), w2v.as_index_tensor(out), k, 21)
+    got = []
+    for announced in (False, True):
+        sh = w2v.Shard(V, d, 6, init_mode=1)
+        sh.set_counts(counts)
+        loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+        if announced:
+            sh.cbow_prefetch_minibatch(*args)
+        w2v.cbow_train_minibatch([sh], *args, 0.002, loss=loss)
+        sh.status()
+        got.append((all_rows(sh, 0), all_rows(sh, 1), loss.item()))
+        sh.destroy()
+    assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1]) and got[0][2] == got[1][2]
+    rows = np.arange(V, dtype=np.uint32)
+    U, W = oracle.init_rows(6, d, 0, d, 0, rows), oracle.init_rows(6, d, 0, d, 1, rows)
+    th, al = oracle.build_alias(counts)
+    ref = oracle.cbow_train_minibatch([U], [W], off, ctx, out, k, 21, th, al, 0.002)
+    assert vec_error(got[0][0], U) <= 1e-5 and vec_error(got[0][1], W) <= 1e-5
+    assert abs(got[0][2] - ref) <= 1e-5 * abs(ref)
