@@ -155,7 +155,7 @@ struct w2v_shard {
     // `side` so that the current step's own second-stream work does not queue up behind it
     hipStream_t ahead = nullptr;
     hipEvent_t ev_fork = nullptr, ev_keys = nullptr, ev_join = nullptr;
-    hipEvent_t ev_coeffs = nullptr, ev_tails = nullptr;
+    hipEvent_t ev_coeffs = nullptr, ev_wdone = nullptr, ev_tails = nullptr;
     bool overlap = true;
     bool own_rows = true;           // fused step: singly named output rows updated by the input side
     bool last_update_fused = true;  // what the last update on this shard was: an announced minibatch
@@ -335,6 +335,7 @@ int ensure_side_stream(w2v_shard* sh) {
     HIP_TRY(hipEventCreateWithFlags(&sh->ev_keys, hipEventDisableTiming));
     HIP_TRY(hipEventCreateWithFlags(&sh->ev_join, hipEventDisableTiming));
     HIP_TRY(hipEventCreateWithFlags(&sh->ev_coeffs, hipEventDisableTiming));
+    HIP_TRY(hipEventCreateWithFlags(&sh->ev_wdone, hipEventDisableTiming));
     HIP_TRY(hipEventCreateWithFlags(&sh->ev_tails, hipEventDisableTiming));
     return W2V_OK;
 }
@@ -550,11 +551,11 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
     w.in_idx = p.in_safe; w.coeffs = fused ? coeffs_out : coeffs_in; w.alpha = alpha;
     w.prows = p.pb_rows; w.pkeys = p.pb_keys; w.skip_alone = p.own_rows; w.dev = dev;
     const bool alone = adjust_walk_alone(p.M, sh->g);
+    const bool two = alone && ws_owner->overlap && ensure_side_stream(ws_owner) == W2V_OK;
     if (alone) {
         // A large minibatch: the input side's levels and the loss run beside the output side's walk on the
-        // second stream (the same launches on one stream: the same bits), so that only the output side's
-        // levels and the write-back follow that walk.
-        const bool two = ws_owner->overlap && ensure_side_stream(ws_owner) == W2V_OK;
+        // second stream, the write-back there beside the output side's levels (the same launches on one
+        // stream: the same bits).  (Write-back and first level in one launch: 1.2 % on the benchmark step.)
         hipStream_t side = two ? ws_owner->side : st;
         if (two) {
             (void)hipEventRecord(ws_owner->ev_coeffs, st);
@@ -572,14 +573,20 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
                 advance(us);
             }
         }
-        if (two) (void)hipEventRecord(ws_owner->ev_tails, side);
         {
             Phase ph(ws_owner, W2V_PH_WSIDE, st);
             launch_wseg(w, st, true);
         }
-        if (two) (void)hipStreamWaitEvent(st, ws_owner->ev_tails, 0);
+        if (two) {
+            (void)hipEventRecord(ws_owner->ev_wdone, st);
+            (void)hipStreamWaitEvent(side, ws_owner->ev_wdone, 0);
+        }
+        Phase ph(ws_owner, W2V_PH_APPLY, side);
+        launch_apply(apply, sh->g, side);
+        applied = true;
+        if (two) (void)hipEventRecord(ws_owner->ev_tails, side);
     }
-    for (bool first = !alone, any = true; any; first = false) {
+    for (bool first = !alone, any = !alone || ws.slots; any; first = false) {
         Phase ph(ws_owner, first ? W2V_PH_WSIDE : W2V_PH_APPLY, st);
         AdjustStage x;
         x.g = sh->g;
@@ -609,6 +616,7 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
         if (u_level) advance(us);
         any = us.slots || ws.slots || loss_step || !applied;
     }
+    if (two) (void)hipStreamWaitEvent(st, ws_owner->ev_tails, 0);
 }
 
 }  // namespace
@@ -711,6 +719,7 @@ extern "C" int w2v_shard_destroy(w2v_shard* sh) {
     if (sh->ev_keys) (void)hipEventDestroy(sh->ev_keys);
     if (sh->ev_join) (void)hipEventDestroy(sh->ev_join);
     if (sh->ev_coeffs) (void)hipEventDestroy(sh->ev_coeffs);
+    if (sh->ev_wdone) (void)hipEventDestroy(sh->ev_wdone);
     if (sh->ev_tails) (void)hipEventDestroy(sh->ev_tails);
     if (sh->ev_pfork) (void)hipEventDestroy(sh->ev_pfork);
     for (auto& x : sh->sets) {

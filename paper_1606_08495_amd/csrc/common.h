@@ -209,6 +209,7 @@ struct ApplyDelta {
     float* U; const float* delta; const uint32_t* dkey; uint32_t n; float alpha;
     const CallScalars* dev;
 };
+void launch_apply(const ApplyDelta& x, RowGeom g, hipStream_t st);
 
 // Parts of one update that do not depend on each other, in ONE launch (each may be absent): the
 // output side's level-1 kernel (wfirst; its border slots already cleared) or one of its higher

@@ -579,6 +579,23 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, uint32_t vb) {
     }
 }
 
+// On its own, beside the output side's levels on another stream.
+template <int G, int NV>
+__global__ __launch_bounds__(adj_threads(G)) void apply_kernel(ApplyArgs a) {
+    apply_body<G, NV, adj_threads(G)>(a, blockIdx.x);
+}
+
+void launch_apply(const ApplyDelta& x, RowGeom g, hipStream_t st) {
+    if (x.n == 0) return;
+    const ApplyArgs a{(float4*)x.U, g, (const float4*)x.delta, x.dkey, x.n, x.alpha, x.dev};
+#define CALL(G, NV)                                                                                       \
+    hipLaunchKernelGGL((apply_kernel<G, NV>),                                                             \
+                       dim3(blocks_for((uint64_t)blocks_for(x.n, APPLY_P) * G, adj_threads(G))),          \
+                       dim3(adj_threads(G)), 0, st, a)
+    W2V_DISPATCH_GEOM(g.d4, CALL);
+#undef CALL
+}
+
 // ---------------------------------------------------------------------------------------------
 // One launch for parts of the update that do not depend on each other: a walk of the output side
 // (its level-1 kernel when FIRST, else one of its higher levels), one higher level of the input
