@@ -268,7 +268,6 @@ __device__ __forceinline__ v16f exact_tile(const TopkArgs& a, uint32_t q, bool q
     v16f acc;
 #pragma unroll
     for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-#pragma unroll 2
     for (uint32_t k = 0; k < a.d; k += 4) {
         const float4 x = load_cols<VEC4>(qr, q_ok, k, a.d), y = load_cols<VEC4>(cr, c_ok, k, a.d);
         acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fk ? x.y : x.x, fk ? y.y : y.x, acc, 0, 0, 0);
