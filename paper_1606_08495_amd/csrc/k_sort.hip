@@ -4,6 +4,8 @@
 // slot, so the order in which a row's contributions are summed is fixed by the input alone.
 #include "common.h"
 
+#include <algorithm>
+
 namespace w2v {
 
 static inline unsigned blocks_for(uint64_t items, unsigned per_block) {
@@ -367,11 +369,13 @@ __global__ __launch_bounds__(THREADS) void sort_pass_kernel(SortArgs a, uint32_t
 
 static inline uint32_t sort_tiles(uint32_t n, int shape) { return blocks_for(n, sort_tile_of(shape)); }
 
-// Scratch of one call over arrays of n0 and n1 elements (n1 = 0: one array), in uint32 (the
-// region must be 8-byte aligned).
+// Scratch of calls over arrays of up to n0 and n1 elements, together or each alone, in uint32 (the
+// region must be 8-byte aligned).  Past SORT_SMALL_N in all, one of the arrays alone (or a smaller call
+// later) may still be short enough for the small tiles, of which there are more than large ones.
 size_t sort_scratch_u32(uint32_t n0, uint32_t n1) {
     const int shape = sort_shape_for((uint64_t)n0 + n1);
-    const uint64_t tiles = (uint64_t)sort_tiles(n0, shape) + sort_tiles(n1, shape);
+    uint64_t tiles = (uint64_t)sort_tiles(n0, shape) + sort_tiles(n1, shape);
+    if (shape != 0) tiles = std::max<uint64_t>(tiles, SORT_SMALL_N / sort_tile_of(0) + 1);
     return 2 * SORT_MAX_PASSES * 256 + 8 + 2 * (size_t)(2 * tiles * 256) + 16;
 }
 

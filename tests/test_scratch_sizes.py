@@ -1,0 +1,102 @@
+"""Sizes of the library's scratch: what one call reserves must hold every launch it may make.
+
+The size rules are host functions inside the library (namespace w2v, not part of the C ABI); the CPU
+tests here call them by their linker names and compare them with the arithmetic of the launches.  The
+GPU tests run the calls at the sizes where the rules change.
+"""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1606_08495_amd import w2v, workloads
+from util import all_rows, dev, vec_error
+
+SMALL = 1 << 19              # elements from which the sort takes its large tiles
+
+
+def rule(mangled, n_args, restype=ctypes.c_size_t):
+    fn = getattr(ctypes.CDLL(w2v.LIB_PATH), mangled)
+    fn.restype, fn.argtypes = restype, [ctypes.c_uint32] * n_args
+    return fn
+
+
+def sort_scratch(n0, n1=0):
+    return rule("_ZN3w2v16sort_scratch_u32Ejj", 2)(n0, n1)
+
+
+def sort_need(n):
+    """uint32 words that a sort of n keys touches: digit totals, tickets, two rows of states per tile."""
+    tiles = -(-n // (1024 if n < SMALL else 8192))
+    return 2 * 4 * 256 + 8 + 2 * 2 * 256 * tiles
+
+
+@pytest.mark.parametrize("n0,n1", [(SMALL - 1, 1), (SMALL - 1, 0), (SMALL - 1, SMALL - 1), (480_000, 80_000), (522_000, 3_000),
+                                   (300_000, 300_000), (6_000, 522_000), (SMALL, 5), (3_000_000, 400_000), (1, 1)])
+def test_joint_sort_scratch_holds_each_array_alone(n0, n1):
+    have = sort_scratch(n0, n1)
+    assert have >= sort_need(n0) and have >= sort_need(n1)
+    assert sort_scratch(n0) >= sort_need(n0)
+
+
+SORT_EDGES = [(80_000, 5), (87_381, 5), (500_000, 0)]          # n (k + 1) < 2^19 <= n (k + 2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,k", SORT_EDGES)
+@pytest.mark.parametrize("form", ["adjust", "two shards"])
+def test_both_sides_sorted_apart_at_the_edge_of_the_small_tiles(n, k, form):
+    print("sorts apart", n, k, form, flush=True)
+    V, d, alpha = 3000, 8, 0.001
+    rng = np.random.default_rng(n + k)
+    counts = workloads.analytic_counts(V, 1.0, 10 ** 7)
+    th, al = oracle.build_alias(counts)
+    a, b = (workloads.zipf_draw(workloads.zipf_cdf(V, 1.0), n, rng) for _ in range(2))
+    rows = np.arange(V, dtype=np.uint32)
+    U, W = oracle.init_rows(3, d, 0, d, 0, rows), oracle.init_rows(3, d, 0, d, 1, rows)
+    cuts = [(0, d)] if form == "adjust" else [(0, 3), (3, 5)]
+    shards = [w2v.Shard(V, w, 3, d_total=d, col_begin=c, init_mode=1) for c, w in cuts]
+    for sh in shards:
+        sh.set_counts(counts)
+    for step in range(2):                                       # the second on states the first has left
+        if form == "adjust":
+            g = workloads.uniform_coeffs(n, k + 1, step)
+            shards[0].adjust(dev(a), dev(b), k, 40 + step, torch.from_numpy(g).cuda(), alpha)
+            oracle.adjust(U, W, a, b, k, 40 + step, th, al, g, alpha)
+        else:
+            w2v.train_minibatch(shards, dev(a), dev(b), k, 40 + step, alpha)
+            oracle.train_minibatch([U], [W], a, b, k, 40 + step, th, al, alpha)
+    for sh in shards:
+        sh.status()
+    got = [np.concatenate([all_rows(sh, which) for sh in shards], axis=1) for which in (0, 1)]
+    assert vec_error(got[0], U) <= 2e-5 and vec_error(got[1], W) <= 2e-5      # 1e-5 a minibatch
+    for sh in shards:
+        sh.destroy()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("n,k,m", [(87_000, 5, 3_000), (80_000, 5, 200_000), (60_000, 5, 500_000)])
+def test_bag_of_words_sorts_apart_at_the_edge_of_the_small_tiles(n, k, m):
+    print("bag of words, sorts apart", n, k, m, flush=True)
+    V, d, alpha = 3000, 8, 0.001
+    rng = np.random.default_rng(m)
+    counts = workloads.analytic_counts(V, 1.0, 10 ** 7)
+    th, al = oracle.build_alias(counts)
+    cdf = workloads.zipf_cdf(V, 1.0)
+    ctx, out = workloads.zipf_draw(cdf, m, rng), workloads.zipf_draw(cdf, n, rng)
+    off = np.concatenate([[0], np.sort(rng.integers(0, m + 1, n - 1)), [m]]).astype(np.uint32)
+    rows = np.arange(V, dtype=np.uint32)
+    U, W = oracle.init_rows(3, d, 0, d, 0, rows), oracle.init_rows(3, d, 0, d, 1, rows)
+    sh = w2v.Shard(V, d, 3, init_mode=1)
+    sh.set_counts(counts)
+    for step in range(2):
+        w2v.cbow_train_minibatch([sh], dev(off), dev(ctx), dev(out), k, 60 + step, alpha)
+        oracle.cbow_train_minibatch([U], [W], off, ctx, out, k, 60 + step, th, al, alpha)
+    g = workloads.uniform_coeffs(n, k + 1, 7)
+    sh.cbow_adjust(dev(off), dev(ctx), dev(out), k, 70, torch.from_numpy(g).cuda(), alpha)
+    oracle.cbow_adjust(U, W, off, ctx, out, k, 70, th, al, g, alpha)
+    sh.status()
+    assert vec_error(all_rows(sh, 0), U) <= 3e-5 and vec_error(all_rows(sh, 1), W) <= 3e-5    # 1e-5 a minibatch
+    sh.destroy()
