@@ -256,13 +256,8 @@ uint32_t key_bits(uint32_t V) {
     return bits;
 }
 
-uint32_t slots_after(uint32_t entries, uint32_t per_chunk) {
-    if (entries == 0) return 0;
-    uint32_t chunks = (entries + per_chunk - 1) / per_chunk;
-    return 2 * (chunks - 1);
-}
-
-// Everything one minibatch needs in scratch, carved in a fixed order.
+// Everything one minibatch needs in scratch, carved in a fixed order.  Every part grows with n and k, so
+// a smaller minibatch fits the scratch of a larger one.
 struct Plan {
     uint32_t n, T, M;
     uint32_t* keys; uint32_t* in_safe;
@@ -276,7 +271,7 @@ struct Plan {
     float* pb_rows; uint32_t* pb_keys;     // output side, level 1 slots
     float* pc_rows; uint32_t* pc_keys;     // level 2 slots, output side
     float* pe_rows; uint32_t* pe_keys;     // level 2 slots, input side (the two sides' tails may overlap)
-    uint32_t slots_u1, slots_w1, slots_2;
+    uint32_t slots_w1;                     // output side, level 1 slots of this minibatch
     bool wfill_done;                       // the output side's border slots are cleared already
     size_t bytes;
 };
@@ -300,15 +295,13 @@ Plan make_plan(char* base, uint32_t n, uint32_t k, uint32_t stride4_max, uint32_
         const size_t row = (size_t)stride4_max * 4;
         p.delta = c.take<float>((size_t)n * row);
         p.dkey = c.take<uint32_t>(n);
-        p.slots_u1 = slots_after(n, useg_pairs_per_chunk(p.T, 1, n));    // the most any shard needs
         p.slots_w1 = slots_after(p.M, wseg_entries_per_chunk(p.M));
-        uint32_t s2u = slots_after(p.slots_u1, tail_entries_least());    // the most any shard needs
-        uint32_t s2w = slots_after(p.slots_w1, tail_entries_least());
-        p.slots_2 = std::max(s2u, s2w);
-        p.pa_rows = c.take<float>((size_t)p.slots_u1 * row); p.pa_keys = c.take<uint32_t>(p.slots_u1 + 1);
-        p.pb_rows = c.take<float>((size_t)p.slots_w1 * row); p.pb_keys = c.take<uint32_t>(p.slots_w1 + 1);
-        p.pc_rows = c.take<float>((size_t)p.slots_2 * row);  p.pc_keys = c.take<uint32_t>(p.slots_2 + 1);
-        p.pe_rows = c.take<float>((size_t)p.slots_2 * row);  p.pe_keys = c.take<uint32_t>(p.slots_2 + 1);
+        const uint32_t su1 = useg_slots_most(p.T, n), sw1 = wseg_slots_most(p.M);
+        const uint32_t s2 = slots_after(std::max(su1, sw1), tail_entries_least());
+        p.pa_rows = c.take<float>((size_t)su1 * row); p.pa_keys = c.take<uint32_t>(su1 + 1);
+        p.pb_rows = c.take<float>((size_t)sw1 * row); p.pb_keys = c.take<uint32_t>(sw1 + 1);
+        p.pc_rows = c.take<float>((size_t)s2 * row);  p.pc_keys = c.take<uint32_t>(s2 + 1);
+        p.pe_rows = c.take<float>((size_t)s2 * row);  p.pe_keys = c.take<uint32_t>(s2 + 1);
     }
     p.bytes = c.off + 256;
     return p;
@@ -1221,7 +1214,7 @@ struct CbowPlan {
     float* pd_rows; uint32_t* pd_keys;               // input side, level 1
     float* pc_rows; uint32_t* pc_keys;               // level 2, output side
     float* pe_rows; uint32_t* pe_keys;               // level 2, input side (the two sides overlap)
-    uint32_t slots_a, slots_w1, slots_c1, slots_2;
+    uint32_t slots_w1, slots_c1;                     // level 1 slots of this minibatch
     size_t bytes;
 };
 
@@ -1245,16 +1238,15 @@ CbowPlan make_cbow_plan(char* base, uint32_t n, uint32_t k, uint32_t m, uint32_t
         p.sort_tmp_w = c.take<uint32_t>(sort_scratch_u32(p.M, m));       // (room for the joint sort)
         p.cb0 = c.take<uint2>(m); p.cb1 = c.take<uint2>(m);
         p.sort_tmp_c = c.take<uint32_t>(sort_scratch_u32(m));
-        p.slots_a = slots_after(n, useg_pairs_per_chunk(p.T, 1, n));
         p.slots_w1 = slots_after(p.M, wseg_entries_per_chunk(p.M));
         p.slots_c1 = slots_after(m, wseg_entries_per_chunk(m));
-        p.slots_2 = std::max(slots_after(p.slots_w1, tail_entries_least()),
-                             slots_after(p.slots_c1, tail_entries_least()));
-        p.pa_rows = c.take<float>((size_t)p.slots_a * row);  p.pa_keys = c.take<uint32_t>(p.slots_a + 1);
-        p.pb_rows = c.take<float>((size_t)p.slots_w1 * row); p.pb_keys = c.take<uint32_t>(p.slots_w1 + 1);
-        p.pd_rows = c.take<float>((size_t)p.slots_c1 * row); p.pd_keys = c.take<uint32_t>(p.slots_c1 + 1);
-        p.pc_rows = c.take<float>((size_t)p.slots_2 * row);  p.pc_keys = c.take<uint32_t>(p.slots_2 + 1);
-        p.pe_rows = c.take<float>((size_t)p.slots_2 * row);  p.pe_keys = c.take<uint32_t>(p.slots_2 + 1);
+        const uint32_t sa = useg_slots_most(p.T, n), sw1 = wseg_slots_most(p.M), sc1 = wseg_slots_most(m);
+        const uint32_t s2 = slots_after(std::max(sw1, sc1), tail_entries_least());
+        p.pa_rows = c.take<float>((size_t)sa * row);  p.pa_keys = c.take<uint32_t>(sa + 1);
+        p.pb_rows = c.take<float>((size_t)sw1 * row); p.pb_keys = c.take<uint32_t>(sw1 + 1);
+        p.pd_rows = c.take<float>((size_t)sc1 * row); p.pd_keys = c.take<uint32_t>(sc1 + 1);
+        p.pc_rows = c.take<float>((size_t)s2 * row);  p.pc_keys = c.take<uint32_t>(s2 + 1);
+        p.pe_rows = c.take<float>((size_t)s2 * row);  p.pe_keys = c.take<uint32_t>(s2 + 1);
     }
     p.bytes = c.off + 256;
     return p;

@@ -103,7 +103,7 @@ void launch_dots(const float* U, const float* W, RowGeom g, const uint32_t* in_s
 struct PartialPtrs { const float* p[32]; };
 void launch_coeffs(PartialPtrs parts, uint32_t S, uint32_t n, uint32_t T, float* coeffs,
                    double* block_loss, double* loss_out, hipStream_t st);
-size_t coeffs_loss_scratch_doubles(uint32_t n, uint32_t T);
+size_t coeffs_loss_scratch_doubles(uint32_t n, uint32_t T);      // of n pairs or fewer
 
 // Stable least-significant-digit radix sort of (keys_in[i], i) on `bits` key bits.  keys_in is
 // only read; the passes ping-pong between buf0 and buf1 (n 8-byte words each, 8-byte aligned), and
@@ -144,6 +144,16 @@ uint32_t useg_pairs_per_chunk(uint32_t T, uint32_t d4, uint32_t n);   // by slot
 uint32_t wseg_entries_per_chunk(uint32_t M);    // by the number of contributions
 uint32_t tail_entries_per_chunk(uint32_t d4);   // by row geometry
 uint32_t tail_entries_least();                  // the least over all of them
+// Border slots of a list cut into chunks, two per border; and the most that any minibatch of up to this
+// size leaves at level 1.  Small minibatches are cut shorter, so that may be more than this size's own;
+// scratch is sized by it, and a call never needs more than a larger one before it.
+inline uint32_t slots_after(uint32_t entries, uint32_t per_chunk) {
+    if (entries == 0) return 0;
+    uint32_t chunks = (entries + per_chunk - 1) / per_chunk;
+    return 2 * (chunks - 1);
+}
+uint32_t useg_slots_most(uint32_t T, uint32_t n);        // input side, over all row geometries
+uint32_t wseg_slots_most(uint32_t M);                    // output side
 
 // Input-vector side, level 1.  Sorted pairs ps = 0..n-1 (key skey[ps] = in_idx of pair perm[ps]).
 // A lane group sums coeffs[p][j] * W[keys[p][j]] over the pairs of its chunk; a run of equal keys

@@ -12,6 +12,8 @@
 #include "rows.h"
 #include "loss.h"
 
+#include <algorithm>
+
 namespace w2v {
 
 static inline unsigned blocks_for(uint64_t items, unsigned per_block) {
@@ -59,6 +61,13 @@ uint32_t useg_pairs_per_chunk(uint32_t T, uint32_t d4, uint32_t n) {
     const uint32_t fill = n / USEG_MIN_CHUNKS;                          // pairs per chunk that still give that many
     if (c > fill) c = fill < 2 ? 2 : fill;
     return c;
+}
+// (the narrowest rows have the shortest chunks; between two steps of the chunk size the number of chunks
+// peaks just before a step, highest before the first one, from two pairs to three)
+uint32_t useg_slots_most(uint32_t T, uint32_t n) {
+    const uint32_t before_step = std::min(n, 3 * USEG_MIN_CHUNKS - 1);
+    return std::max(slots_after(n, useg_pairs_per_chunk(T, 1, n)),
+                    slots_after(before_step, useg_pairs_per_chunk(T, 1, before_step)));
 }
 
 struct SegArgs {
@@ -291,12 +300,17 @@ constexpr int WOWN_C = 16;
 // Cell size for long runs, a multiple of C: 64 (128: the output-side kernel 9 % slower, 32: more rows for
 // the levels above); 32 for minibatches of up to 2^19 slots, whose time is that of the group with the most
 // entries in a row.
-static uint32_t wown_cell_log2(uint32_t M) { return M <= (1u << 19) ? 5u : 6u; }
+constexpr uint32_t WOWN_SHORT_CELLS = 1u << 19;
+static uint32_t wown_cell_log2(uint32_t M) { return M <= WOWN_SHORT_CELLS ? 5u : 6u; }
 constexpr int WOWN_WIN = 3 * WOWN_C + 2;     // keys staged: positions base-C-1 .. base+2C
 constexpr int WOWN_E = 2 * WOWN_C;           // positions summed from LDS facts: base .. base+2C-1
 enum : uint32_t { ACT_SKIP = 0, ACT_ADD = 1, ACT_COMPLETE = 2, ACT_HEAD = 3 };
 
 uint32_t wseg_entries_per_chunk(uint32_t M) { return 1u << wown_cell_log2(M); }
+uint32_t wseg_slots_most(uint32_t M) {
+    const uint32_t before_step = std::min(M, WOWN_SHORT_CELLS);
+    return std::max(slots_after(M, wseg_entries_per_chunk(M)), slots_after(before_step, wseg_entries_per_chunk(before_step)));
+}
 
 template <int G, int NV, int D>
 __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {

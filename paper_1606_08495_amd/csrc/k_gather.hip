@@ -395,9 +395,10 @@ static void launch_sum_doubles(const double* x, uint32_t n, double* out, hipStre
     hipLaunchKernelGGL(sum_doubles_kernel, dim3(1), dim3(256), 0, st, x, n, out);
 }
 
-// doubles of scratch for the loss: one per block of terms
+// doubles of scratch for the loss: one per block of terms (most blocks: at the end of the short ones)
 size_t coeffs_loss_scratch_doubles(uint32_t n, uint32_t T) {
-    return blocks_for((uint64_t)n * T, loss_terms_of(n * T)) + 8;
+    const uint32_t total = n * T, short_total = std::min(total, LOSS_SHORT_TERMS);
+    return std::max(blocks_for(total, loss_terms_of(total)), blocks_for(short_total, loss_terms_of(short_total))) + 8;
 }
 
 void launch_coeffs(PartialPtrs parts, uint32_t S, uint32_t n, uint32_t T, float* coeffs,

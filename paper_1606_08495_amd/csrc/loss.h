@@ -10,7 +10,8 @@ namespace w2v {
 // block, one per thread and eight barriers each, took 0.35 ms beside the row kernels for the 11.5 M terms
 // of a search minibatch) and there are still blocks for the whole chip (4096 a block: 36 us for 600 000
 // terms over five shards against 9).  Past 2^24 terms more, for the one block that adds up the sums.
-__host__ __device__ inline uint32_t loss_terms_of(uint32_t total) { return total <= (1u << 24) ? 1024u : 16384u; }
+constexpr uint32_t LOSS_SHORT_TERMS = 1u << 24;
+__host__ __device__ inline uint32_t loss_terms_of(uint32_t total) { return total <= LOSS_SHORT_TERMS ? 1024u : 16384u; }
 
 // log(1 + e^x) without overflow or cancellation
 __device__ __forceinline__ float softplus(float x) {

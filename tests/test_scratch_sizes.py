@@ -100,3 +100,61 @@ def test_bag_of_words_sorts_apart_at_the_edge_of_the_small_tiles(n, k, m):
     sh.status()
     assert vec_error(all_rows(sh, 0), U) <= 3e-5 and vec_error(all_rows(sh, 1), W) <= 3e-5    # 1e-5 a minibatch
     sh.destroy()
+
+
+def slots_after(entries, per_chunk):
+    return 2 * (-(-entries // per_chunk) - 1) if entries else 0
+
+
+def steps_of(*edges):
+    """Sizes around the edges and between them, increasing."""
+    return sorted({max(1, e + o) for e in edges for o in (-1, 0, 1)} | {int(1.31 ** i) for i in range(1, 70)})
+
+
+def test_scratch_of_a_minibatch_holds_every_smaller_one():
+    """A region grown by a large minibatch serves smaller ones without growing again: what the rules of
+    the chunk sizes ask for at any smaller size is within what is reserved, and that never falls."""
+    most_w, cell = rule("_ZN3w2v15wseg_slots_mostEj", 1, ctypes.c_uint32), rule("_ZN3w2v22wseg_entries_per_chunkEj", 1, ctypes.c_uint32)
+    sizes = [s for s in steps_of(1 << 19, 1 << 20) if s < 1 << 28]
+    held = needed = 0
+    for M in sizes:
+        needed = max(needed, slots_after(M, cell(M)))
+        assert most_w(M) >= max(needed, held)
+        held = most_w(M)
+    most_u, chunk = rule("_ZN3w2v15useg_slots_mostEjj", 2, ctypes.c_uint32), rule("_ZN3w2v20useg_pairs_per_chunkEjjj", 3, ctypes.c_uint32)
+    held_T = {}
+    for T in (1, 2, 3, 6, 11, 17, 24, 25, 26, 65):
+        held = needed = 0
+        for n in [s for s in steps_of(*(32768 * c for c in range(1, 34))) if s < 1 << 25]:
+            needed = max([needed] + [slots_after(n, chunk(T, d4, n)) for d4 in (1, 16, 17, 32, 33, 64, 256)])
+            assert most_u(T, n) >= max(needed, held, held_T.get(n, 0)), (T, n)
+            held = held_T[n] = most_u(T, n)
+    loss = rule("_ZN3w2v27coeffs_loss_scratch_doublesEjj", 2)
+    held = needed = 0
+    for n in [s for s in steps_of(1 << 24) if s < 1 << 30]:
+        needed = max(needed, -(-n // (1024 if n <= 1 << 24 else 16384)))
+        assert loss(n, 1) >= max(needed, held)
+        held = loss(n, 1)
+    for n1 in (0, 1, 5000, 700_000):
+        held = 0
+        for n0 in [s for s in steps_of(SMALL, SMALL - n1 if n1 < SMALL else SMALL) if s < 1 << 28]:
+            assert sort_scratch(n0, n1) >= held
+            held = sort_scratch(n0, n1)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,big,small,k", [(300, 20_165, 20_164, 25), (300, 98_304, 98_303, 5)])
+def test_a_smaller_minibatch_leaves_a_captured_step_valid(d, big, small, k):
+    """(n (k+1) just past 2^19, where the cells of long runs double; n where the input side's chunks grow)"""
+    print("captured", big, "then plain", small, flush=True)
+    V = 2000
+    rng = np.random.default_rng(1)
+    a, b = dev(rng.integers(0, V, big).astype(np.uint32)), dev(rng.integers(0, V, big).astype(np.uint32))
+    sh = w2v.Shard(V, d, 3)
+    sh.set_counts(np.ones(V, np.uint64))
+    graph = w2v.StepGraph(sh, big, k)
+    w2v.train_minibatch([sh], a[:small].contiguous(), b[:small].contiguous(), k, 5, 0.001)
+    graph.run(a, b, 6, 0.001)
+    sh.status()
+    graph.destroy()
+    sh.destroy()
