@@ -26,6 +26,7 @@
 // is too small to be precise are always listed.
 #include "common.h"
 
+#include <algorithm>
 #include <math.h>
 
 namespace w2v {
@@ -55,6 +56,12 @@ constexpr float TK_TINY = 1e-30f;         // squared lengths below this are not 
 // and tested exactly (some 10 000 cycles), instead of listing pairs at about 75 cycles each for the
 // fold.  Bounds the cost on data whose similarities all lie closer together than the margin.
 constexpr int TK_DENSE = 128;
+// Queries of one launch of the fold, query tiles of one launch of the stream screen, candidates of one
+// launch: a grid holds less than 2^32 threads in x (past that the runtime wraps it without an error) and
+// 2^16 blocks in y, so very long lists are served in slices.
+constexpr uint32_t TK_FOLD_SLICE = 1u << 21;
+constexpr uint32_t TK_STREAM_SLICE = 1u << 15;
+constexpr uint32_t TK_CAND_SLICE = 1u << 30;
 
 __host__ __device__ inline uint32_t topk_steps(uint32_t d) { return 2 * ((d + 2 * TK_KS - 1) / (2 * TK_KS)); }   // even
 __device__ __forceinline__ float topk_rounding(uint32_t d) { return (float)(d + 64) * 0x1p-22f; }
@@ -101,6 +108,7 @@ struct TopkArgs {
     const float* Qm; const float* Cm; uint32_t Q, N, d;
     uint32_t c_begin, c_end;            // candidates of this round
     uint32_t nq_tiles, nc_tiles;
+    uint32_t q_first;                   // first query (fold) or query tile (stream) of this launch
     const float* invq; const float* invc; const float* theta;
     uint32_t* cnt; uint32_t* pend; uint32_t cap;
     uint32_t* err;
@@ -404,7 +412,7 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a
 }
 
 // ---------------------------------------------------------------------------------------------
-// Stream screen: a wavefront takes 32 candidates and TQ tiles of 32 queries (blockIdx.y: which).  The
+// Stream screen: a wavefront takes 32 candidates and TQ tiles of 32 queries (q_first + blockIdx.y: which).  The
 // lane pair (l, l ^ 32) walks candidate l % 32, eight columns at a time each; the rounded columns are
 // a matrix-core operand as they stand.  Four steps of candidate columns are in flight ahead of the
 // four in work; the queries' operands come from L2.
@@ -414,7 +422,7 @@ template <int TQ, bool VEC4>
 __global__ __launch_bounds__(256) void topk_stream_kernel(TopkArgs a) {
     __shared__ __align__(16) float s_level[TQ * 32];
     const int tid = threadIdx.x, lane = tid % 64, fk = lane >> 5;
-    const uint32_t qt0 = blockIdx.y * TQ;
+    const uint32_t qt0 = (a.q_first + blockIdx.y) * TQ;
     for (int i = tid; i < TQ * 32; i += 256) {
         const uint32_t q = qt0 * 32 + i;
         s_level[i] = q < a.Q ? screen_level(a.theta[q], a.qmargin[q], 1.f) : INFINITY;
@@ -704,7 +712,7 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
                                                                float* __restrict__ out_score,
                                                                uint32_t* __restrict__ out_count) {
     __shared__ uint64_t s_list[WAVES][64];
-    const uint32_t q = blockIdx.x;
+    const uint32_t q = a.q_first + blockIdx.x;
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const uint32_t n_new = min(a.cnt[q], a.cap), bc = best_cnt[q];
     if (n_new == 0 && !out_idx) return;                      // uniform per block
@@ -815,7 +823,7 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
         if (Q > TK_STREAM_Q && (cap_wide >= n_up || cap_wide >= 8192)) { screen = WIDE; cap = cap_wide; }
         else if (cap_stream >= n_up || cap_stream >= 2 * TK_BC) { screen = STREAM; cap = cap_stream; }
     }
-    cap = cap < n_up ? cap : n_up;
+    cap = std::min<uint64_t>({cap, n_up, TK_CAND_SLICE});
     char* at = ws + L.pend;
     a.pend = (uint32_t*)at;
     a.cap = (uint32_t)cap;
@@ -840,9 +848,14 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
 #undef W2V_QUERIES
     }
     if (screen == FP32) {
-        const dim3 grid(blocks_for(N, 128)), block(256);
-        if (vec4) hipLaunchKernelGGL(inv_length_kernel<true>, grid, block, 0, st, Cm, N, d, (float*)a.invc);
-        else hipLaunchKernelGGL(inv_length_kernel<false>, grid, block, 0, st, Cm, N, d, (float*)a.invc);
+        for (uint64_t first = 0; first < N; first += TK_CAND_SLICE) {
+            const uint32_t rows = (uint32_t)std::min<uint64_t>(TK_CAND_SLICE, N - first);
+            const dim3 grid(blocks_for(rows, 128)), block(256);
+            const float* at = Cm + first * d;
+            float* inv = (float*)a.invc + first;
+            if (vec4) hipLaunchKernelGGL(inv_length_kernel<true>, grid, block, 0, st, at, rows, d, inv);
+            else hipLaunchKernelGGL(inv_length_kernel<false>, grid, block, 0, st, at, rows, d, inv);
+        }
     }
     // Short rounds first: with a threshold from the first few hundred candidates only a small share of a
     // full round's scores reaches the pending lists.  Many queries: rounds grow fourfold from 256 (every
@@ -872,13 +885,16 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
         } else if (screen == STREAM) {
             const uint32_t tq = Q <= 32 ? 1 : (Q <= 64 ? 2 : 4);
             a.nc_tiles = (m + 31) / 32;
-            const dim3 grid(blocks_for(a.nc_tiles, 4), blocks_for(Q, 32 * tq)), block(256);
+            const uint32_t q_tiles = blocks_for(Q, 32 * tq);
 #define W2V_STREAM(TQ)                                                                                     \
     do {                                                                                                   \
         if (vec4) hipLaunchKernelGGL((topk_stream_kernel<TQ, true>), grid, block, 0, st, a);               \
         else hipLaunchKernelGGL((topk_stream_kernel<TQ, false>), grid, block, 0, st, a);                   \
     } while (0)
-            if (tq == 1) W2V_STREAM(1); else if (tq == 2) W2V_STREAM(2); else W2V_STREAM(4);
+            for (a.q_first = 0; a.q_first < q_tiles; a.q_first += TK_STREAM_SLICE) {
+                const dim3 grid(blocks_for(a.nc_tiles, 4), std::min(TK_STREAM_SLICE, q_tiles - a.q_first)), block(256);
+                if (tq == 1) W2V_STREAM(1); else if (tq == 2) W2V_STREAM(2); else W2V_STREAM(4);
+            }
 #undef W2V_STREAM
         } else {
             // 2 x 2 tiles per wavefront at four wavefronts per SIMD (128 registers, accumulators included)
@@ -895,10 +911,12 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
         const bool last = begin + len >= N;
         uint32_t* oi = last ? out_idx : nullptr;
 #define W2V_FOLD(WAVES, VEC4)                                                                              \
-    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4>), dim3(Q), dim3(64 * WAVES), 0, st, a, K, tau, best, \
-                       best_cnt, theta, oi, out_score, out_count)
-        if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(4, true); else W2V_FOLD(4, false); }
-        else { if (vec4) W2V_FOLD(16, true); else W2V_FOLD(16, false); }
+    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first)),        \
+                       dim3(64 * WAVES), 0, st, a, K, tau, best, best_cnt, theta, oi, out_score, out_count)
+        for (a.q_first = 0; a.q_first < Q; a.q_first += TK_FOLD_SLICE) {
+            if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(4, true); else W2V_FOLD(4, false); }
+            else { if (vec4) W2V_FOLD(16, true); else W2V_FOLD(16, false); }
+        }
 #undef W2V_FOLD
     }
     return a.err;

@@ -250,3 +250,18 @@ def test_rows_without_a_usable_length(Q):
     for tau in (-2.0, 0.0, 0.1):
         _, gs, _ = screens_agree(Qm, C, 40, tau)
         assert not np.isnan(gs).any()
+
+
+def test_more_queries_than_one_launch_holds():
+    """2^24 queries and one more: the fold (a block per query) and the stream screen (a block per 128) go
+    in slices.  Queries on both sides of the slices' borders must get what they get on their own."""
+    Q, N, d, K = (1 << 24) + 1, 1000, 4, 2
+    say("queries", Q)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    q, c = torch.randn(Q, d, device="cuda", generator=g), torch.randn(N, d, device="cuda", generator=g)
+    got = w2v.topk_cosine(q, c, K, 0.2, round_candidates=256)
+    pick = torch.tensor([0, 127, (1 << 21) - 1, 1 << 21, (1 << 22) - 1, 1 << 22, (1 << 23) + 5, Q - 2, Q - 1], device="cuda")
+    want = w2v.topk_cosine(q[pick].contiguous(), c, K, 0.2)
+    for x, y in zip(got, want):
+        assert torch.equal(x[pick], y)
+    assert int(got[2].min()) >= 0 and int((got[2] == K).sum()) > Q // 2
