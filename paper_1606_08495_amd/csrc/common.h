@@ -258,6 +258,9 @@ void launch_make_pairs(const PairArgs& a, hipStream_t st);
 // holds the shortest rounds (128).
 size_t topk_workspace_bytes(uint32_t Q, uint32_t N, uint32_t round_candidates);
 bool topk_workspace_fits(uint32_t Q, uint32_t N, size_t workspace_bytes);
+// Which screen a search takes with that workspace (the results do not tell).
+enum TopkScreen : uint32_t { TOPK_FP32, TOPK_STREAM, TOPK_WIDE };
+uint32_t topk_screen(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_bytes);
 uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint32_t N, uint32_t d,
                              uint32_t K, float tau, uint32_t* out_idx, float* out_score,
                              uint32_t* out_count, void* workspace, size_t workspace_bytes, hipStream_t st);

@@ -788,6 +788,43 @@ bool topk_workspace_fits(uint32_t Q, uint32_t N, size_t workspace_bytes) {
     return workspace_bytes >= topk_workspace_bytes(Q, N, TK_BC);
 }
 
+// The wide screen's tile: 256 queries x 128 candidates by eight wavefronts of 64 x 64, four to a SIMD.
+// (Measured on 4096 x 2^20 x 300, whole search: 4.75 ms; 128 x 128 by four wavefronts 4.87, 256 x 256 by
+// sixteen 4.84; wavefronts of 128 x 64, two to a SIMD, 5.05 - 5.5; of 128 x 128 alone on a SIMD 33.)
+constexpr int TK_WTM = 2, TK_WTN = 2, TK_WWM = 4, TK_WWN = 2, TK_WWPE = 4;
+constexpr uint32_t WIDE_Q = 32 * TK_WTM * TK_WWM, WIDE_C = 32 * TK_WTN * TK_WWN;
+
+// How a search is served: by which screen, in rounds of how many candidates, and with how many rounded
+// queries (a whole number of the screen's tiles: 32, 64 or 128 for the stream screen, 256 for the wide one).
+struct TopkPlan { TopkScreen screen; uint64_t cap, q_up; };
+static uint32_t stream_tiles(uint32_t Q) { return Q <= 32 ? 1 : (Q <= 64 ? 2 : 4); }    // of 32 queries, per wavefront
+
+static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_bytes) {
+    const uint64_t row_bytes = (uint64_t)topk_steps(d) * TK_KS * 2;
+    const uint64_t n_up = ((uint64_t)N + 255) / 256 * 256;
+    const uint64_t free_bytes = workspace_bytes - topk_layout(Q, N).fixed_bytes;          // (fits 128 candidates of eight bytes)
+    // Up to one tile of queries the stream screen reads every candidate once; beyond, reading and rounding
+    // them again for each further tile costs more than rounding them once into the workspace -- unless that
+    // leaves only short rounds.
+    TopkPlan p{TOPK_FP32, free_bytes / (8ull * Q) / TK_BC * TK_BC, 0};
+    auto room = [&](uint64_t tile, uint64_t per_candidate, uint64_t granule, uint64_t least, TopkScreen screen) {
+        const uint64_t q_up = (Q + tile - 1) / tile * tile, q_bytes = q_up * (row_bytes + 4) + 512;
+        if (free_bytes <= q_bytes) return false;
+        const uint64_t cap = (free_bytes - q_bytes) / per_candidate / granule * granule;
+        if (cap < n_up && cap < least) return false;
+        p = TopkPlan{screen, cap, q_up};
+        return true;
+    };
+    if (Q <= TK_STREAM_Q || !room(WIDE_Q, 4ull * Q + row_bytes + 4, 256, 8192, TOPK_WIDE))
+        room(32 * stream_tiles(Q), 4ull * Q, TK_BC, 2 * TK_BC, TOPK_STREAM);
+    p.cap = std::min<uint64_t>({p.cap, n_up, TK_CAND_SLICE});
+    return p;
+}
+
+uint32_t topk_screen(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_bytes) {
+    return topk_plan(Q, N, d, workspace_bytes).screen;
+}
+
 uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint32_t N, uint32_t d,
                              uint32_t K, float tau, uint32_t* out_idx, float* out_score,
                              uint32_t* out_count, void* workspace, size_t workspace_bytes, hipStream_t st) {
@@ -802,37 +839,19 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
     a.cnt = (uint32_t*)(ws + L.cnt); a.err = (uint32_t*)(ws + L.err);
     const bool vec4 = d % 4 == 0 && ((uintptr_t)Qm % 16 == 0) && ((uintptr_t)Cm % 16 == 0);
 
-    // The wide screen's tile: 256 queries x 128 candidates by eight wavefronts of 64 x 64, four to a SIMD.
-    // (Measured on 4096 x 2^20 x 300, whole search: 4.75 ms; 128 x 128 by four wavefronts 4.87, 256 x 256 by
-    // sixteen 4.84; wavefronts of 128 x 64, two to a SIMD, 5.05 - 5.5; of 128 x 128 alone on a SIMD 33.)
-    constexpr int TM = 2, TN = 2, WM = 4, WN = 2, WPE = 4;
-    constexpr uint32_t WIDE_Q = 32 * TM * WM, WIDE_C = 32 * TN * WN;
     const uint64_t row_bytes = (uint64_t)topk_steps(d) * TK_KS * 2;
-    const uint64_t n_up = ((uint64_t)N + 255) / 256 * 256;
-    const uint64_t free_bytes = workspace_bytes - L.fixed_bytes;          // (fits 128 candidates of eight bytes)
-    // Which screen, and how many candidates its rounds can hold.  Up to one tile of queries the stream
-    // screen reads every candidate once; beyond, reading and rounding them again for each further tile
-    // costs more than rounding them once into the workspace -- unless that leaves only short rounds.
-    enum { FP32, STREAM, WIDE } screen = FP32;
-    uint64_t cap = free_bytes / (8ull * Q) / TK_BC * TK_BC;
-    const uint64_t q_up = ((uint64_t)Q + WIDE_Q - 1) / WIDE_Q * WIDE_Q;   // (a whole number of either screen's tiles)
-    const uint64_t q_bytes = q_up * (row_bytes + 4) + 512;
-    if (free_bytes > q_bytes) {
-        const uint64_t rest = free_bytes - q_bytes;
-        const uint64_t cap_wide = rest / (4ull * Q + row_bytes + 4) / 256 * 256, cap_stream = rest / (4ull * Q) / TK_BC * TK_BC;
-        if (Q > TK_STREAM_Q && (cap_wide >= n_up || cap_wide >= 8192)) { screen = WIDE; cap = cap_wide; }
-        else if (cap_stream >= n_up || cap_stream >= 2 * TK_BC) { screen = STREAM; cap = cap_stream; }
-    }
-    cap = std::min<uint64_t>({cap, n_up, TK_CAND_SLICE});
+    const TopkPlan plan = topk_plan(Q, N, d, workspace_bytes);
+    const TopkScreen screen = plan.screen;
+    const uint64_t cap = plan.cap, q_up = plan.q_up;
     char* at = ws + L.pend;
     a.pend = (uint32_t*)at;
     a.cap = (uint32_t)cap;
     at += (cap * Q * 4 + 255) / 256 * 256;
     void* qfrag = nullptr; float* qmargin = nullptr; void* cfrag = nullptr; float* cmargin = nullptr;
-    if (screen != FP32) {
+    if (screen != TOPK_FP32) {
         qfrag = at; at += q_up * row_bytes;
         qmargin = (float*)at; at += q_up * 4;
-        if (screen == WIDE) { cfrag = at; at += cap * row_bytes; cmargin = (float*)at; at += cap * 4; }
+        if (screen == TOPK_WIDE) { cfrag = at; at += cap * row_bytes; cmargin = (float*)at; at += cap * 4; }
     }
     a.qfrag = qfrag; a.qmargin = qmargin; a.cfrag = cfrag; a.cmargin = cmargin;
 
@@ -843,11 +862,11 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
 #define W2V_QUERIES(F16, VEC4)                                                                             \
     hipLaunchKernelGGL((topk_queries_kernel<F16, VEC4>), grid, block, 0, st, Qm, Q, d, theta0, (float*)a.invq, \
                        theta, a.cnt, best_cnt, qfrag, qmargin, a.err)
-        if (screen == WIDE) { if (vec4) W2V_QUERIES(true, true); else W2V_QUERIES(true, false); }
+        if (screen == TOPK_WIDE) { if (vec4) W2V_QUERIES(true, true); else W2V_QUERIES(true, false); }
         else { if (vec4) W2V_QUERIES(false, true); else W2V_QUERIES(false, false); }
 #undef W2V_QUERIES
     }
-    if (screen == FP32) {
+    if (screen == TOPK_FP32) {
         for (uint64_t first = 0; first < N; first += TK_CAND_SLICE) {
             const uint32_t rows = (uint32_t)std::min<uint64_t>(TK_CAND_SLICE, N - first);
             const dim3 grid(blocks_for(rows, 128)), block(256);
@@ -860,19 +879,19 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
     // Short rounds first: with a threshold from the first few hundred candidates only a small share of a
     // full round's scores reaches the pending lists.  Many queries: rounds grow fourfold from 256 (every
     // pair listed costs a row read).  Few: sixteenfold from 1024 -- there launches cost more than pairs.
-    const uint64_t growth = screen == STREAM ? 16 : 4;
-    uint64_t len = screen == FP32 ? TK_BC : (screen == STREAM ? 1024 : 256);
+    const uint64_t growth = screen == TOPK_STREAM ? 16 : 4;
+    uint64_t len = screen == TOPK_FP32 ? TK_BC : (screen == TOPK_STREAM ? 1024 : 256);
     for (uint64_t begin = 0; begin < N; begin += len, len = len * growth < cap ? len * growth : cap) {
         if (len > cap) len = cap;
         a.c_begin = (uint32_t)begin;
         a.c_end = (uint32_t)(begin + len < N ? begin + len : N);
         const uint32_t m = a.c_end - a.c_begin;
         a.dense_test = begin >= 32ull * K;         // (earlier, hits are many because the thresholds are low)
-        if (screen == WIDE) {
+        if (screen == TOPK_WIDE) {
             a.nq_tiles = (Q + WIDE_Q - 1) / WIDE_Q;
             a.nc_tiles = (m + WIDE_C - 1) / WIDE_C;
             const uint32_t tiles = a.nc_tiles * (WIDE_C / 32), total = a.nq_tiles * a.nc_tiles;
-            const dim3 grid(((total + 7u) / 8u) * 8u), block(64 * WM * WN);
+            const dim3 grid(((total + 7u) / 8u) * 8u), block(64 * TK_WWM * TK_WWN);
 #define W2V_ROUND(VEC4, HOLD)                                                                              \
     hipLaunchKernelGGL((topk_round_kernel<VEC4, HOLD>), dim3(tiles), dim3(64), 0, st, Cm, a.c_begin, a.c_end, d, \
                        (float*)a.invc, cfrag, cmargin)
@@ -880,10 +899,10 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
             else if (vec4) W2V_ROUND(true, 0);
             else W2V_ROUND(false, 0);
 #undef W2V_ROUND
-            if (vec4) hipLaunchKernelGGL((topk_wide_kernel<TM, TN, WM, WN, WPE, true>), grid, block, 0, st, a);
-            else hipLaunchKernelGGL((topk_wide_kernel<TM, TN, WM, WN, WPE, false>), grid, block, 0, st, a);
-        } else if (screen == STREAM) {
-            const uint32_t tq = Q <= 32 ? 1 : (Q <= 64 ? 2 : 4);
+            if (vec4) hipLaunchKernelGGL((topk_wide_kernel<TK_WTM, TK_WTN, TK_WWM, TK_WWN, TK_WWPE, true>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((topk_wide_kernel<TK_WTM, TK_WTN, TK_WWM, TK_WWN, TK_WWPE, false>), grid, block, 0, st, a);
+        } else if (screen == TOPK_STREAM) {
+            const uint32_t tq = stream_tiles(Q);
             a.nc_tiles = (m + 31) / 32;
             const uint32_t q_tiles = blocks_for(Q, 32 * tq);
 #define W2V_STREAM(TQ)                                                                                     \

@@ -8,6 +8,8 @@ TOL = 1e-5 (d <= 1000).  Where the oracle's ranking is decided by a margin wider
 indices must be identical; inside such a margin any order of the tied candidates is accepted, as
 long as every returned candidate's true similarity fits its rank.
 """
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -192,15 +194,25 @@ def test_export_rows_bit_exact():
 # ---- the screens: which pairs are looked at must not show in the results --------------------------
 
 
+def screen_of(Q, N, d, nbytes):
+    """0 fp32, 1 stream, 2 wide: the library's own rule (a host function, by its linker name)."""
+    fn = ctypes.CDLL(w2v.LIB_PATH)._ZN3w2v11topk_screenEjjjm
+    fn.restype, fn.argtypes = ctypes.c_uint32, [ctypes.c_uint32] * 3 + [ctypes.c_size_t]
+    return fn(Q, N, d, nbytes)
+
+
 def screens_agree(Qm, C, K, tau):
-    """The default workspace (16-bit screens) and the smallest (fp32 scores, rounds of 128): same bits."""
+    """A workspace with room for the 16-bit screen of that many queries (stream up to 128, else wide), the
+    default one and the smallest (fp32 scores, rounds of 128): same bits."""
+    (Q, d), N = Qm.shape, C.shape[0]
     q, c = torch.from_numpy(Qm).cuda(), torch.from_numpy(C).cuda()
-    small = torch.empty(int(w2v.lib().w2v_topk_cosine_workspace(Qm.shape[0], C.shape[0], 128)),
-                        dtype=torch.uint8, device="cuda")
-    a = [t.cpu().numpy() for t in w2v.topk_cosine(q, c, K, tau)]
-    b = [t.cpu().numpy() for t in w2v.topk_cosine(q, c, K, tau, workspace=small)]
-    for x, y in zip(a, b):
-        assert np.array_equal(x.view(np.uint32), y.view(np.uint32))
+    size = lambda r: int(w2v.lib().w2v_topk_cosine_workspace(Q, N, r))
+    large, small = size(0) + (Q + N + 512) * (2 * d + 128), size(128)
+    assert screen_of(Q, N, d, large) == (1 if Q <= 128 else 2) and screen_of(Q, N, d, small) == 0
+    a, b, e = ([t.cpu().numpy() for t in w2v.topk_cosine(q, c, K, tau, workspace=ws)]
+               for ws in (torch.empty(large, dtype=torch.uint8, device="cuda"), torch.empty(small, dtype=torch.uint8, device="cuda"), None))
+    for x, y, z in zip(a, b, e):
+        assert np.array_equal(x.view(np.uint32), y.view(np.uint32)) and np.array_equal(x.view(np.uint32), z.view(np.uint32))
     return a[0].view(np.uint32), a[1], a[2]
 
 

@@ -158,3 +158,12 @@ def test_a_smaller_minibatch_leaves_a_captured_step_valid(d, big, small, k):
     sh.status()
     graph.destroy()
     sh.destroy()
+
+
+@pytest.mark.parametrize("Q,N,d", [(1, 10_000, 300), (1, 20_000, 300), (1, 1 << 19, 512), (4, 5000, 300), (7, 3000, 512),
+                                   (32, 3000, 512), (33, 5000, 300), (100, 200_003, 100), (128, 1 << 20, 1000)])
+def test_few_queries_take_the_stream_screen_with_the_default_workspace(Q, N, d):
+    """Its query tiles are 32, 64 or 128 rows: the rounded queries fit a workspace for rounds of 32768."""
+    fn = ctypes.CDLL(w2v.LIB_PATH)._ZN3w2v11topk_screenEjjjm
+    fn.restype, fn.argtypes = ctypes.c_uint32, [ctypes.c_uint32] * 3 + [ctypes.c_size_t]
+    assert fn(Q, N, d, w2v.lib().w2v_topk_cosine_workspace(Q, N, 32768)) == 1
