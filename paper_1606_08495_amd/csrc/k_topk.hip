@@ -240,8 +240,10 @@ __device__ __forceinline__ float screen_level(float theta, float margin, float u
 
 // A slot on its query's pending list for every set bit: bit v of lane (fr, fk) is the pair of query
 // q0 + 8 (v / 4) + 4 fk + v % 4 and the lane's candidate.  Lane (v, fk) reserves the slots of that
-// query for the tile: one atomic instruction, one round trip for all 32 lists.
-__device__ __forceinline__ void append_tile(const TopkArgs& a, uint32_t bits, uint32_t q0, uint32_t c, int lane) {
+// query for the tile: one atomic instruction, one round trip for all 32 lists.  SCORED: the list holds
+// (similarity, candidate), score(v) tells it.
+template <bool SCORED, typename Score>
+__device__ __forceinline__ void append_tile(const TopkArgs& a, uint32_t bits, uint32_t q0, uint32_t c, int lane, Score score) {
     const int fr = lane & 31, fk = lane >> 5;
     uint32_t mine = 0, base = 0;
 #pragma unroll
@@ -259,7 +261,10 @@ __device__ __forceinline__ void append_tile(const TopkArgs& a, uint32_t bits, ui
         const uint32_t half = fk ? (uint32_t)(both >> 32) : (uint32_t)both;
         const uint32_t slot = __shfl(base, v + 32 * fk, 64) + (uint32_t)__popc(half & ((1u << fr) - 1u));
         const uint32_t q = q0 + 8 * (v / 4) + 4 * fk + v % 4;
-        if (pass && slot < a.cap) a.pend[(uint64_t)q * a.cap + slot] = c;
+        if (pass && slot < a.cap) {
+            if (SCORED) ((uint2*)a.pend)[(uint64_t)q * a.cap + slot] = make_uint2(__float_as_uint(score(v)), c);
+            else a.pend[(uint64_t)q * a.cap + slot] = c;
+        }
         lost |= pass && slot >= a.cap;                        // (a list holds a whole round: cannot happen)
     }
     if (lost) atomicOr(a.err, 1u);
@@ -320,7 +325,7 @@ __device__ __forceinline__ void screen_tile(const TopkArgs& a, const v16f& acc, 
             if (!(dot[v] * a.invq[qv] * ic > a.theta[qv])) bits &= ~(1u << v);
         }
     }
-    append_tile(a, bits, q0, c, lane);                        // (queries past Q carry +inf levels: no bits)
+    append_tile<false>(a, bits, q0, c, lane, [](int) { return 0.f; });    // (queries past Q carry +inf levels: no bits)
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -627,20 +632,18 @@ __global__ __launch_bounds__(TK_THREADS, WPE) void topk_scores_kernel(TopkArgs a
             for (int v = 0; v < 16; ++v) over = fmaxf(over, fmaf(acc[ti][tj][v], ic, -tq[v]));
             if (__ballot(over >= 0.f) == 0) continue;        // uniform per wavefront
             uint32_t bits = 0;
+            auto score = [&](int v) { return acc[ti][tj][v] * s_invq[qbase + 8 * (v / 4) + v % 4] * ic; };
 #pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const int ql = qbase + 8 * (v / 4) + (v % 4);
-                const float s = acc[ti][tj][v] * s_invq[ql] * ic;
-                bits |= c_ok && s > s_theta[ql] ? 1u << v : 0u;       // padded queries carry +inf: never
-            }
-            append_tile(a, bits, q0 + wm * 32 * TM + ti * 32, c, lane);
+            for (int v = 0; v < 16; ++v)                     // (padded queries carry +inf: never)
+                bits |= c_ok && score(v) > s_theta[qbase + 8 * (v / 4) + v % 4] ? 1u << v : 0u;
+            append_tile<true>(a, bits, q0 + wm * 32 * TM + ti * 32, c, lane, score);
         }
     }
 }
 
 // ---------------------------------------------------------------------------------------------
 // Fold: one block per query gives the listed pairs their similarities -- a lane per candidate, one
-// 128-byte line of its row at a time -- and merges those above the threshold into the sorted best list
+// 128-byte line of its row at a time; the fp32 screen has them listed already -- and merges those above the threshold into the sorted best list
 // (higher score first, equal scores by lower index), then raises the threshold to the K-th best and
 // empties the list.  Rounds come in index order, so a later candidate that only equals the K-th best
 // never enters.  Each wavefront keeps its own 64 best, sorted across its lanes; the lists are merged
@@ -703,7 +706,7 @@ __device__ __forceinline__ float exact_score(const float* __restrict__ q, const 
     return dot * iq * inv_length(tree8(lo) + tree8(hi));
 }
 
-template <int WAVES, bool VEC4>
+template <int WAVES, bool VEC4, bool SCORED>
 __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint32_t K, float tau,
                                                                uint64_t* __restrict__ best,
                                                                uint32_t* __restrict__ best_cnt,
@@ -724,8 +727,16 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
     for (uint32_t base = wave * 64u; base < n_new; base += 64u * WAVES) {
         uint64_t k = 0;
         if (base + lane < n_new) {
-            const uint32_t c = a.pend[(uint64_t)q * a.cap + base + lane];
-            const float s = exact_score<VEC4>(a.Qm + (uint64_t)q * a.d, a.Cm + (uint64_t)c * a.d, a.d, iq);
+            const uint64_t at = (uint64_t)q * a.cap + base + lane;
+            uint32_t c;
+            float s;
+            if (SCORED) {
+                const uint2 e = ((const uint2*)a.pend)[at];
+                s = __uint_as_float(e.x); c = e.y;
+            } else {
+                c = a.pend[at];
+                s = exact_score<VEC4>(a.Qm + (uint64_t)q * a.d, a.Cm + (uint64_t)c * a.d, a.d, iq);
+            }
             if (s > th) k = rank_key(s, c);                  // (a similarity that is no number never passes)
         }
         if (__ballot(k != 0)) list = merge64(list, __shfl((unsigned long long)sort64(k, lane), 63 - lane, 64), lane);
@@ -929,12 +940,13 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
         }
         const bool last = begin + len >= N;
         uint32_t* oi = last ? out_idx : nullptr;
-#define W2V_FOLD(WAVES, VEC4)                                                                              \
-    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first)),        \
+#define W2V_FOLD(WAVES, VEC4, SCORED)                                                                      \
+    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4, SCORED>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first)), \
                        dim3(64 * WAVES), 0, st, a, K, tau, best, best_cnt, theta, oi, out_score, out_count)
         for (a.q_first = 0; a.q_first < Q; a.q_first += TK_FOLD_SLICE) {
-            if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(4, true); else W2V_FOLD(4, false); }
-            else { if (vec4) W2V_FOLD(16, true); else W2V_FOLD(16, false); }
+            if (screen == TOPK_FP32) W2V_FOLD(4, false, true);
+            else if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(4, true, false); else W2V_FOLD(4, false, false); }
+            else { if (vec4) W2V_FOLD(16, true, false); else W2V_FOLD(16, false, false); }
         }
 #undef W2V_FOLD
     }
