@@ -15,14 +15,14 @@
 //   stream  (Q <= 128): bound by reading the candidates; a wavefront reads 32 of them once, rounds them
 //           to bf16 in registers (no scale is known yet; bf16 has fp32's range), and forms norms,
 //           rounding errors and products with all queries on the way.
-//   fp32    exact scores from the fp32 matrix cores; only where the workspace is too small for the
-//           rounded queries.
+//   fp32    exact scores from the fp32 matrix cores: where the workspace is too small for the rounded
+//           queries, in the first rounds of a wide search, and in blocks whose similarities are crowded.
 //
 // Margin.  Let a = q/|q|, b = c/|c| in fp32 and a', b' their rounded forms.  |a.b - a'.b'| <=
 // |a - a'| |b| + |a'| |b - b'|, and the norms of the two rounding errors are computed per row
 // (about 2e-4 for fp16, 9e-4 for bf16: a tenth of the distance to the K-th best that a crowded list
 // has).  What fp32 arithmetic adds on either side (products summed in any order, norms, the two
-// scalings) is at most a few d 2^-24; TK_ROUND(d) below holds twice that.  Rows whose squared length
+// scalings) is at most a few d 2^-24; topk_rounding(d) below holds twice that.  Rows whose squared length
 // is too small to be precise are always listed.
 #include "common.h"
 
@@ -44,7 +44,6 @@ constexpr int TK_BC = 128;          // candidates per block tile; granularity of
 constexpr int TK_BK = 16;           // columns per panel; two panels are held in LDS
 constexpr int TK_LD = TK_BK + 1;    // LDS row pitch (odd: conflict-free column reads)
 constexpr int TK_THREADS = 256;     // four wavefronts
-constexpr int TK_RPM = TK_THREADS / (TK_BK / 4);            // rows covered by one move of the block
 constexpr int TK_LIST = 64;         // slots of a query's best list (K <= 64)
 constexpr uint32_t TK_NONE = 0xFFFFFFFFu;
 constexpr uint32_t TK_STREAM_Q = 128;     // most queries of the stream screen's tile
@@ -52,10 +51,22 @@ constexpr int TK_KS = 16;                 // columns of one 16-bit matrix-core s
 constexpr float TK_F16_SCALE = 256.f;     // fp16 rows are stored times this: components below 2.4e-7 of the
                                           // row's length (fp16 subnormals) are taken as zero
 constexpr float TK_TINY = 1e-30f;         // squared lengths below this are not precise
-// More hits than this in a 32 x 32 tile: its similarities are formed at once on the fp32 matrix cores
-// and tested exactly (some 10 000 cycles), instead of listing pairs at about 75 cycles each for the
-// fold.  Bounds the cost on data whose similarities all lie closer together than the margin.
-constexpr int TK_DENSE = 128;
+// Crowded similarities.  Where more candidates lie within the margin than a round lists in earnest, listing
+// them (a row read each in the fold) costs far more than forming all similarities in fp32 at once.  So a block
+// that finds more hits than twice what the thresholds let pass plus TK_DENSE_* drops them and does that
+// (exact_block) -- all but the first TK_SPARE, for one block alone takes longer that way; and once half of
+// the blocks so far have, the rounds that follow do not screen.
+// Vectors around one direction, noise 0.03 of the components, K = 30; us, in brackets with every pair in fp32:
+// 4096 queries over 200 000 x 300 4760 [4550], 300 1070 [880], 100 530 [700], 7 480 [485]; with hits of a
+// tile of 32 x 32 above 128 re-formed by its own wavefront, as it was, 13 200, 1970, 14 600, 390.  What the
+// count costs where nothing is crowded: a barrier per block, 2 % at most (300 queries over 200 000 x 16).
+// (TK_DENSE_WIDE 256, 1024, 2048 on the first at noise 0.1: 3.90, 3.91, 5.05 ms against 3.74.
+// TK_DENSE_STREAM 8, 16: 10 queries over 100 000 x 300, noise 0.3, 303 and 483 us against 302.
+// TK_SPARE 0, 16, 32: 1 query over 200 000 x 100, no crowd, 140, 126, 127 us, noise 0.03 187, 208, 259.)
+constexpr uint32_t TK_DENSE_WIDE = 512;           // of 256 queries x 128 candidates
+constexpr uint32_t TK_DENSE_STREAM = 4;           // per query (64 at most), of 128 candidates
+constexpr uint32_t TK_SPARE = 8;
+constexpr double TK_EXACT_ROUND = 100000;         // pairs
 // Queries of one launch of the fold, query tiles of one launch of the stream screen, candidates of one
 // launch: a grid holds less than 2^32 threads in x (past that the runtime wraps it without an error) and
 // 2^16 blocks in y, so very long lists are served in slices.
@@ -115,7 +126,11 @@ struct TopkArgs {
     // 16-bit screens
     const void* qfrag; const float* qmargin;     // rounded queries, and what to lower their thresholds by
     const void* cfrag; const float* cmargin;     // wide: the round's rounded candidates and their margins
-    bool dense_test;                             // try the exact test on tiles with many hits
+    // a block with more hits than dense_limit (TK_NONE: none has) is counted in *dense and, past the first
+    // TK_SPARE, forms its similarities in fp32.  A block that finds dense_skip (TK_NONE: never) or more
+    // counted does not screen; the first of a round's `blocks` then counts them all, so that they stay so
+    uint32_t dense_limit, dense_skip, blocks;
+    uint32_t* dense;
 };
 
 // A row's normalised form, rounded, in matrix-core order: tile of 32 rows, step of 16 columns, lane
@@ -199,7 +214,7 @@ __global__ __launch_bounds__(64) void topk_queries_kernel(const float* __restric
         inv = inv_length(square);
     }
     if (lane < 32 && q < Q) { invq[q] = inv; theta[q] = theta0; cnt[q] = 0u; best_cnt[q] = 0u; }
-    if (blockIdx.x == 0 && lane == 0) *err = 0u;
+    if (blockIdx.x == 0 && lane < 2) err[lane] = 0u;           // (err[1]: TopkArgs::dense)
 }
 
 // The wide screen's candidates of one round (rows c_end .. the end of the last tile are zero and have
@@ -230,6 +245,31 @@ __global__ __launch_bounds__(256) void inv_length_kernel(const float* __restrict
     if ((threadIdx.x & 32) == 0 && r < rows) inv[r] = inv_length(s);
 }
 
+// Whether a block goes without the screen: thread 0 asks (early: loads come back in order) and tells the
+// others by way of *s_dense before a barrier.  (An ordinary read, which may be served by a cache: what
+// matters is what earlier rounds have counted.)
+__device__ __forceinline__ uint32_t dense_so_far(const TopkArgs& a) {
+    return threadIdx.x == 0 && a.dense_skip != TK_NONE ? *a.dense : 0u;
+}
+__device__ __forceinline__ void tell_dense(const TopkArgs& a, uint32_t counted, bool first, uint32_t* s_hits, uint32_t* s_dense) {
+    if (threadIdx.x) return;
+    const bool skip = counted >= a.dense_skip;               // (TK_NONE: never reached)
+    if (skip && first) atomicAdd(a.dense, a.blocks);
+    *s_hits = 0; *s_dense = skip;
+}
+
+// Whether a block with that many hits is to drop them and form its similarities in fp32 (all threads; `hits`
+// of a wavefront, the same in its lanes; s_hits is zero before).
+__device__ __forceinline__ bool dense_block(const TopkArgs& a, int hits, uint32_t* s_hits, uint32_t* s_dense) {
+    if (a.dense_limit == TK_NONE) return false;
+    if (hits && threadIdx.x % 64 == 0) atomicAdd(s_hits, (uint32_t)hits);
+    __syncthreads();
+    if (*s_hits <= a.dense_limit) return false;
+    if (threadIdx.x == 0) *s_dense = atomicAdd(a.dense, 1u) >= TK_SPARE;
+    __syncthreads();
+    return *s_dense != 0;
+}
+
 // What a 16-bit product must reach before the candidate's own margin: the query's threshold less its
 // margin, in units of the product.
 __device__ __forceinline__ float screen_level(float theta, float margin, float unit) {
@@ -245,6 +285,7 @@ __device__ __forceinline__ float screen_level(float theta, float margin, float u
 template <bool SCORED, typename Score>
 __device__ __forceinline__ void append_tile(const TopkArgs& a, uint32_t bits, uint32_t q0, uint32_t c, int lane, Score score) {
     const int fr = lane & 31, fk = lane >> 5;
+    if (__ballot(bits != 0) == 0) return;                     // uniform per wavefront
     uint32_t mine = 0, base = 0;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -270,32 +311,13 @@ __device__ __forceinline__ void append_tile(const TopkArgs& a, uint32_t bits, ui
     if (lost) atomicOr(a.err, 1u);
 }
 
-// fp32 products of a 32 x 32 tile of queries and candidates straight from the caller's rows.
-// v_mfma_f32_32x32x2_f32: lane l feeds A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32];
-// accumulator register v of lane l is D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32], and each element is
-// the fused-multiply-add chain over its columns in order.
-template <bool VEC4>
-__device__ __forceinline__ v16f exact_tile(const TopkArgs& a, uint32_t q, bool q_ok, uint32_t c, bool c_ok, int fk) {
-    const float* qr = a.Qm + (uint64_t)(q_ok ? q : 0u) * a.d;
-    const float* cr = a.Cm + (uint64_t)(c_ok ? c : 0u) * a.d;
-    v16f acc;
-#pragma unroll
-    for (int v = 0; v < 16; ++v) acc[v] = 0.f;
-    for (uint32_t k = 0; k < a.d; k += 4) {
-        const float4 x = load_cols<VEC4>(qr, q_ok, k, a.d), y = load_cols<VEC4>(cr, c_ok, k, a.d);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fk ? x.y : x.x, fk ? y.y : y.x, acc, 0, 0, 0);
-        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fk ? x.w : x.z, fk ? y.w : y.z, acc, 0, 0, 0);
-    }
-    return acc;
-}
-
-// A tile's 16-bit products against the thresholds.  Most tiles hold no hit once the thresholds have
-// risen: two instructions per element tell.  level: LDS, the 32 levels of the tile's queries; `unit_c`
-// scales this lane's products (its candidate) into the levels' units; `own` is the candidate's margin
-// there, -inf for a lane without a candidate.
-template <bool VEC4>
-__device__ __forceinline__ void screen_tile(const TopkArgs& a, const v16f& acc, float unit_c, float own,
-                                            const float* level, uint32_t q0, uint32_t c, float ic, int lane) {
+// A tile's 16-bit products against the thresholds: the bits of append_tile, and how many (added to `hits`,
+// the same in every lane).  Most tiles hold none once the thresholds have risen: two instructions per
+// element tell.  level: LDS, the 32 levels of the tile's queries (+inf past Q: no bits); `unit_c` scales
+// this lane's products (its candidate) into the levels' units; `own` is the candidate's margin there, -inf
+// for a lane without a candidate.
+__device__ __forceinline__ uint32_t screen_tile(const v16f& acc, float unit_c, float own, const float* level, int lane,
+                                                int& hits) {
     const int fk = lane >> 5;
     float lv[16];
 #pragma unroll
@@ -306,28 +328,170 @@ __device__ __forceinline__ void screen_tile(const TopkArgs& a, const v16f& acc, 
     float over = -INFINITY;
 #pragma unroll
     for (int v = 0; v < 16; ++v) over = fmaxf(over, fmaf(acc[v], unit_c, -lv[v]));
-    if (__ballot(over + own >= 0.f) == 0) return;             // uniform per wavefront
+    if (__ballot(over + own >= 0.f) == 0) return 0;           // uniform per wavefront
     const bool c_ok = own > -INFINITY;
     uint32_t bits = 0;
-    int hits = 0;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const bool p = c_ok && fmaf(acc[v], unit_c, -lv[v]) + own >= 0.f;
         bits |= p ? 1u << v : 0u;
         hits += __popcll(__ballot(p));
     }
-    if (hits > TK_DENSE && a.dense_test) {
-        const uint32_t q = q0 + (lane & 31);
-        const v16f dot = exact_tile<VEC4>(a, q, q < a.Q, c, c_ok, fk);
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const uint32_t qv = min(q0 + 8 * (v / 4) + 4 * fk + v % 4, a.Q - 1);
-            if (!(dot[v] * a.invq[qv] * ic > a.theta[qv])) bits &= ~(1u << v);
-        }
-    }
-    append_tile<false>(a, bits, q0, c, lane, [](int) { return 0.f; });    // (queries past Q carry +inf levels: no bits)
+    return bits;
 }
 
+// ---------------------------------------------------------------------------------------------
+// Similarities of a block of 64 WM queries x 64 WN candidates in fp32 on the matrix cores, and the pairs
+// above the threshold listed.  WM x WN wavefronts, each 2 x 2 tiles of 32 x 32.
+// v_mfma_f32_32x32x2_f32: lane l feeds A[i = l % 32][k = l / 32] and B[k = l / 32][j = l % 32];
+// accumulator register v of lane l is D[8 (v / 4) + 4 (l / 32) + v % 4][l % 32], and each element is
+// the fused-multiply-add chain over its columns in order.
+// 2 x 2 tiles per wavefront at four wavefronts per SIMD (128 registers, accumulators included) measured
+// best: 2 x 4 and 4 x 2 tiles (two wavefronts per SIMD) ran 9 % slower, 4 x 4 (one) 2.3 times slower --
+// this lives on having other wavefronts to switch to at its barriers.
+// OWN_LENGTHS: the candidates' inverse lengths are formed here, else they are in a.invc.
+// ---------------------------------------------------------------------------------------------
+template <int WM, int WN> struct ExactLds {
+    struct Panels { float A[2][64 * WM][TK_LD], B[2][64 * WN][TK_LD]; };
+    struct Tables { float level[64 * WM], invq[64 * WM], theta[64 * WM], invc[64 * WN]; };
+    union { alignas(16) Panels p; Tables t; };               // (the tables once the products are done)
+    __device__ ExactLds() {}
+};
+
+template <int WM, int WN, bool VEC4, bool SCORED, bool OWN_LENGTHS>
+__device__ __forceinline__ void exact_block(const TopkArgs& a, uint32_t q0, uint32_t c0, ExactLds<WM, WN>& s) {
+    constexpr int TM = 2, TN = 2, BQ = 64 * WM, BC = 64 * WN, THREADS = 64 * WM * WN;
+    constexpr int RPM = THREADS / (TK_BK / 4);               // rows covered by one move of the block
+    constexpr int MOVES_A = BQ / RPM, MOVES_B = BC / RPM;
+    static_assert(BQ % RPM == 0 && BC % RPM == 0, "whole moves");
+    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+    const int wm = wave / WN, wn = wave % WN;
+    static_assert(THREADS >= BQ && (!OWN_LENGTHS || 32 * WM * WN == BC), "a query per thread, 32 candidates per wavefront");
+    const bool q_ok = tid < BQ && q0 + tid < a.Q;
+    const float iq = q_ok ? a.invq[q0 + tid] : 0.f, th = q_ok ? a.theta[q0 + tid] : INFINITY;
+    // Staging through two LDS buffers of TK_BK columns: while a panel is multiplied, the next one
+    // is written to the other buffer (from registers loaded during the panel before) and the one
+    // after is requested from memory; one barrier per panel.  Thread t moves float4 number t,
+    // t + THREADS, ... of a panel, i.e. the same four columns of rows srow0, srow0 + RPM, ...
+    // (One buffer of 32 columns with a barrier on either side of its refill measured 1 % slower.)
+    const int srow0 = tid / (TK_BK / 4), scol = (tid % (TK_BK / 4)) * 4;
+    const float* arow0 = a.Qm + (uint64_t)(q0 + srow0) * a.d;      // not dereferenced past Q / c_end
+    const float* brow0 = a.Cm + (uint64_t)(c0 + srow0) * a.d;
+    const uint64_t row_step = (uint64_t)RPM * a.d;
+    float4 ra[MOVES_A], rb[MOVES_B];
+    auto fetch = [&](uint32_t col0) {
+#pragma unroll
+        for (int i = 0; i < MOVES_A; ++i)
+            ra[i] = load_cols<VEC4>(arow0 + i * row_step, q0 + srow0 + i * RPM < a.Q, col0 + scol, a.d);
+#pragma unroll
+        for (int i = 0; i < MOVES_B; ++i)
+            rb[i] = load_cols<VEC4>(brow0 + i * row_step, c0 + srow0 + i * RPM < a.c_end, col0 + scol, a.d);
+    };
+    auto stash = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < MOVES_A; ++i) {
+            float* pa = &s.p.A[buf][srow0 + i * RPM][scol];
+            pa[0] = ra[i].x; pa[1] = ra[i].y; pa[2] = ra[i].z; pa[3] = ra[i].w;
+        }
+#pragma unroll
+        for (int i = 0; i < MOVES_B; ++i) {
+            float* pb = &s.p.B[buf][srow0 + i * RPM][scol];
+            pb[0] = rb[i].x; pb[1] = rb[i].y; pb[2] = rb[i].z; pb[3] = rb[i].w;
+        }
+    };
+    float inv = 0.f;
+    if (OWN_LENGTHS) {
+        const uint32_t c = c0 + wave * 32 + (lane & 31);
+        inv = inv_length(pair_square<VEC4>(a.Cm + (uint64_t)(c < a.c_end ? c : 0u) * a.d, c < a.c_end, a.d, lane >> 5));
+    }
+    v16f acc[TM][TN];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+    const int fr = lane & 31, fk = lane >> 5;
+    fetch(0);
+    stash(0);
+    if (TK_BK < a.d) fetch(TK_BK);
+    __syncthreads();
+    int cur = 0;
+    for (uint32_t kb = 0; kb < a.d; kb += TK_BK, cur ^= 1) {
+        if (kb + TK_BK < a.d) {
+            stash(cur ^ 1);
+            if (kb + 2 * TK_BK < a.d) fetch(kb + 2 * TK_BK);
+        }
+        // (columns beyond d hold zeros: skipped; so are a wavefront's queries past the last)
+        const int kmax = q0 + wm * 32 * TM < a.Q ? (int)min((uint32_t)TK_BK, a.d - kb) : 0;
+        // one step of two columns per trip (longer straight runs, which would let the compiler
+        // issue LDS reads under earlier products, measured the same; 16-byte LDS accesses on a
+        // column order that gives each lane four adjacent floats per four steps measured slower)
+#pragma unroll 1
+        for (int kk = 0; kk < kmax; kk += 2) {
+            float av[TM], bv[TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) av[i] = s.p.A[cur][wm * 32 * TM + i * 32 + fr][kk + fk];
+#pragma unroll
+            for (int j = 0; j < TN; ++j) bv[j] = s.p.B[cur][wn * 32 * TN + j * 32 + fr][kk + fk];
+#pragma unroll
+            for (int i = 0; i < TM; ++i)
+#pragma unroll
+                for (int j = 0; j < TN; ++j)
+                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
+        }
+        __syncthreads();
+    }
+
+    if (tid < BQ) {
+        s.t.invq[tid] = iq;
+        s.t.theta[tid] = th;
+        // The same threshold for the raw product dot x (1/|c|), lowered by 2^-20 of itself so that
+        // no score the exact test below accepts is missed (the two roundings of the score and the
+        // ones made here stay under 2^-22 relative); -inf sends every element to the exact test.
+        float t;
+        if (iq == 0.f) {
+            t = th <= 0.f ? -INFINITY : INFINITY;         // every score of a zero query is 0
+        } else {
+            const float r = th / iq;
+            t = fabsf(r) < INFINITY ? r - fabsf(r) * 0x1p-20f : (r > 0.f && th == INFINITY ? INFINITY : -INFINITY);
+        }
+        s.t.level[tid] = t;
+    }
+    if (OWN_LENGTHS && lane < 32) s.t.invc[wave * 32 + lane] = inv;
+    __syncthreads();
+
+    // filter: a score above the query's threshold joins the query's pending list.  Most tiles hold no
+    // such score once the thresholds have risen, so each 32 x 32 tile is first screened with two
+    // instructions per element (raw product against the lowered threshold); only a tile with a hit
+    // goes through the exact test.
+#pragma unroll
+    for (int ti = 0; ti < TM; ++ti) {
+        const int qbase = wm * 32 * TM + ti * 32 + 4 * fk;   // this lane's queries: qbase + 8 (v/4) + v%4
+        float tq[16];
+#pragma unroll
+        for (int v4 = 0; v4 < 4; ++v4) {
+            const float4 t4 = *reinterpret_cast<const float4*>(&s.t.level[qbase + 8 * v4]);
+            tq[4 * v4 + 0] = t4.x; tq[4 * v4 + 1] = t4.y; tq[4 * v4 + 2] = t4.z; tq[4 * v4 + 3] = t4.w;
+        }
+#pragma unroll
+        for (int tj = 0; tj < TN; ++tj) {
+            const uint32_t c = c0 + wn * 32 * TN + tj * 32 + fr;
+            const bool c_ok = c < a.c_end;
+            const float ic = OWN_LENGTHS ? s.t.invc[c - c0] : (c_ok ? a.invc[c] : 0.f);
+            float over = -INFINITY;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) over = fmaxf(over, fmaf(acc[ti][tj][v], ic, -tq[v]));
+            if (__ballot(over >= 0.f) == 0) continue;        // uniform per wavefront
+            uint32_t bits = 0;
+            auto score = [&](int v) { return acc[ti][tj][v] * s.t.invq[qbase + 8 * (v / 4) + v % 4] * ic; };
+#pragma unroll
+            for (int v = 0; v < 16; ++v)                     // (padded queries carry +inf: never)
+                bits |= c_ok && score(v) > s.t.theta[qbase + 8 * (v / 4) + v % 4] ? 1u << v : 0u;
+            append_tile<SCORED>(a, bits, q0 + wm * 32 * TM + ti * 32, c, lane, score);
+        }
+    }
+}
 // ---------------------------------------------------------------------------------------------
 // Wide screen: WM x WN wavefronts, each TM x TN matrix-core tiles of 32 x 32.  Operands come in
 // matrix-core order, so staging is a straight copy and LDS reads are 16 adjacent bytes per lane.
@@ -342,13 +506,18 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a
     constexpr int PANEL = (QT + CT) * KC * 64;               // 16-byte units
     constexpr int MOVES = PANEL / THREADS;
     static_assert(PANEL % THREADS == 0, "whole moves");
-    __shared__ v8h s_panel[2][PANEL];
+    union Lds { v8h panel[2][PANEL]; ExactLds<WM, WN> exact; __device__ Lds() {} };
+    __shared__ Lds lds;
+    auto& s_panel = lds.panel;
     __shared__ __align__(16) float s_level[QT * 32];
+    __shared__ uint32_t s_hits, s_dense;
+    static_assert(QT == 2 * WM && CT == 2 * WN, "the tile of exact_block");
     const uint32_t total = a.nq_tiles * a.nc_tiles;
     const uint32_t per_xcd = (total + 7u) / 8u;
     const uint32_t logical = (blockIdx.x % 8u) * per_xcd + blockIdx.x / 8u;
     if (logical >= total) return;                            // uniform per block, before any barrier
     const uint32_t qt0 = (logical % a.nq_tiles) * QT, ct0 = (logical / a.nq_tiles) * CT;
+    const uint32_t counted = dense_so_far(a);
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
     const int wm = wave / WN, wn = wave % WN;
     const uint32_t steps = topk_steps(a.d), panels = steps / KC;
@@ -382,9 +551,11 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
     fetch(0);
     stash(0);
+    tell_dense(a, counted, blockIdx.x == 0, &s_hits, &s_dense);
     if (panels > 1) fetch(1);
     __syncthreads();
-    for (uint32_t p = 0; p < panels; ++p) {
+    bool dense = s_dense != 0;                               // uniform per block
+    for (uint32_t p = dense ? panels : 0; p < panels; ++p) {
         const int cur = p & 1;
         if (p + 1 < panels) {
             stash(cur ^ 1);
@@ -405,15 +576,26 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a
         }
         __syncthreads();
     }
+    if (!dense) {
+        uint32_t bits[TM][TN];
+        int hits = 0;
 #pragma unroll
-    for (int j = 0; j < TN; ++j) {
-        const uint32_t row = (ct0 + wn * TN + j) * 32 + (lane & 31), c = a.c_begin + row;
-        const float own = a.cmargin[row];
-        const float ic = c < a.c_end ? a.invc[c] : 0.f;
+        for (int j = 0; j < TN; ++j) {
+            const float own = a.cmargin[(ct0 + wn * TN + j) * 32 + (lane & 31)];
 #pragma unroll
-        for (int i = 0; i < TM; ++i)
-            screen_tile<VEC4>(a, acc[i][j], 1.f, own, s_level + (wm * TM + i) * 32, (qt0 + wm * TM + i) * 32, c, ic, lane);
+            for (int i = 0; i < TM; ++i) bits[i][j] = screen_tile(acc[i][j], 1.f, own, s_level + (wm * TM + i) * 32, lane, hits);
+        }
+        dense = dense_block(a, hits, &s_hits, &s_dense);
+        if (!dense && hits) {
+#pragma unroll
+            for (int j = 0; j < TN; ++j)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+                    append_tile<false>(a, bits[i][j], (qt0 + wm * TM + i) * 32, a.c_begin + (ct0 + wn * TN + j) * 32 + (lane & 31), lane,
+                                       [](int) { return 0.f; });
+        }
     }
+    if (dense) exact_block<WM, WN, VEC4, false, false>(a, qt0 * 32, a.c_begin + ct0 * 32, lds.exact);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -424,221 +606,101 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a
 // ---------------------------------------------------------------------------------------------
 constexpr int TK_AHEAD = 4;
 template <int TQ, bool VEC4>
-__global__ __launch_bounds__(256) void topk_stream_kernel(TopkArgs a) {
+__global__ __launch_bounds__(256, TQ == 1 ? 4 : (TQ == 2 ? 3 : 2)) void topk_stream_kernel(TopkArgs a) {
     __shared__ __align__(16) float s_level[TQ * 32];
+    __shared__ ExactLds<2, 2> exact;
+    __shared__ uint32_t s_hits, s_dense;
     const int tid = threadIdx.x, lane = tid % 64, fk = lane >> 5;
     const uint32_t qt0 = (a.q_first + blockIdx.y) * TQ;
+    const uint32_t counted = dense_so_far(a);
     for (int i = tid; i < TQ * 32; i += 256) {
         const uint32_t q = qt0 * 32 + i;
         s_level[i] = q < a.Q ? screen_level(a.theta[q], a.qmargin[q], 1.f) : INFINITY;
     }
+    tell_dense(a, counted, a.q_first + blockIdx.y + blockIdx.x == 0, &s_hits, &s_dense);
     __syncthreads();
-    const uint32_t tile = blockIdx.x * 4 + tid / 64;
-    if (tile >= a.nc_tiles) return;                          // whole wavefronts, after the only barrier
-    const uint32_t c = a.c_begin + tile * 32 + (lane & 31);
-    const bool c_ok = c < a.c_end;
-    const float* row = a.Cm + (uint64_t)(c_ok ? c : 0u) * a.d;
-    const uint32_t steps = topk_steps(a.d);
-    const v8b* qf = (const v8b*)a.qfrag + (uint64_t)qt0 * steps * 64 + lane;
-    v16f acc[TQ];
+    bool dense = s_dense != 0;                               // uniform per block
+    const uint32_t c0 = a.c_begin + blockIdx.x * 128u;
+    if (!dense) {
+        const uint32_t c = c0 + (tid / 64) * 32 + (lane & 31);
+        const bool c_ok = c < a.c_end;
+        const float* row = a.Cm + (uint64_t)(c_ok ? c : 0u) * a.d;
+        const uint32_t steps = topk_steps(a.d);
+        const v8b* qf = (const v8b*)a.qfrag + (uint64_t)qt0 * steps * 64 + lane;
+        v16f acc[TQ];
 #pragma unroll
-    for (int t = 0; t < TQ; ++t)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-    float sq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, e2 = 0.f;
-    float4 x[TK_AHEAD][2], nx[TK_AHEAD][2];
-    auto fetch = [&](float4 (&r)[TK_AHEAD][2], uint32_t ks) {
-#pragma unroll
-        for (int i = 0; i < TK_AHEAD; ++i) {
-            const uint32_t k = (ks + i) * TK_KS + 8 * fk;
-            r[i][0] = load_cols<VEC4>(row, c_ok, k, a.d);    // (zero past the last column)
-            r[i][1] = load_cols<VEC4>(row, c_ok, k + 4, a.d);
-        }
-    };
-    fetch(x, 0);
-    for (uint32_t ks0 = 0; ks0 < steps; ks0 += TK_AHEAD) {
-        fetch(nx, ks0 + TK_AHEAD);
-#pragma unroll
-        for (int i = 0; i < TK_AHEAD; ++i) {
-            const uint32_t ks = ks0 + i;
-            if (ks < steps) {
-                const float v[8] = {x[i][0].x, x[i][0].y, x[i][0].z, x[i][0].w, x[i][1].x, x[i][1].y, x[i][1].z, x[i][1].w};
-                v8b g;
-#pragma unroll
-                for (int e = 0; e < 8; ++e) {
-                    g[e] = (__bf16)v[e];
-                    const float lost = v[e] - (float)g[e];
-                    e2 = fmaf(lost, lost, e2);
-                }
-                square8(x[i][0], x[i][1], sq);
-#pragma unroll
-                for (int t = 0; t < TQ; ++t)
-                    acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[((uint64_t)t * steps + ks) * 64], g, acc[t], 0, 0, 0);
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < TK_AHEAD; ++i) { x[i][0] = nx[i][0]; x[i][1] = nx[i][1]; }
-    }
-    const float half = tree8(sq);
-    const float square = half + __shfl_xor(half, 32, 64);
-    const float ic = inv_length(square);
-    e2 += __shfl_xor(e2, 32, 64);
-    float own = sqrtf(e2) * ic * 1.004f;
-    if (square > 0.f && (square < TK_TINY || ic == 0.f)) own = INFINITY;   // imprecise, or too long to square
-    if (!(own >= 0.f)) own = INFINITY;
-    if (!c_ok) own = -INFINITY;
-#pragma unroll
-    for (int t = 0; t < TQ; ++t) {
-        if (own == INFINITY || ic == 0.f)                    // products that may not be finite: the margin decides
+        for (int t = 0; t < TQ; ++t)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-        screen_tile<VEC4>(a, acc[t], ic, own, s_level + t * 32, (qt0 + t) * 32, c, ic, lane);
+        float sq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, e2 = 0.f;
+        float4 x[TK_AHEAD][2], nx[TK_AHEAD][2];
+        auto fetch = [&](float4 (&r)[TK_AHEAD][2], uint32_t ks) {
+#pragma unroll
+            for (int i = 0; i < TK_AHEAD; ++i) {
+                const uint32_t k = (ks + i) * TK_KS + 8 * fk;
+                r[i][0] = load_cols<VEC4>(row, c_ok, k, a.d);    // (zero past the last column)
+                r[i][1] = load_cols<VEC4>(row, c_ok, k + 4, a.d);
+            }
+        };
+        fetch(x, 0);
+        for (uint32_t ks0 = 0; ks0 < steps; ks0 += TK_AHEAD) {
+            fetch(nx, ks0 + TK_AHEAD);
+#pragma unroll
+            for (int i = 0; i < TK_AHEAD; ++i) {
+                const uint32_t ks = ks0 + i;
+                if (ks < steps) {
+                    const float v[8] = {x[i][0].x, x[i][0].y, x[i][0].z, x[i][0].w, x[i][1].x, x[i][1].y, x[i][1].z, x[i][1].w};
+                    v8b g;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        g[e] = (__bf16)v[e];
+                        const float lost = v[e] - (float)g[e];
+                        e2 = fmaf(lost, lost, e2);
+                    }
+                    square8(x[i][0], x[i][1], sq);
+#pragma unroll
+                    for (int t = 0; t < TQ; ++t)
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[((uint64_t)t * steps + ks) * 64], g, acc[t], 0, 0, 0);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < TK_AHEAD; ++i) { x[i][0] = nx[i][0]; x[i][1] = nx[i][1]; }
+        }
+        const float half = tree8(sq);
+        const float square = half + __shfl_xor(half, 32, 64);
+        const float ic = inv_length(square);
+        e2 += __shfl_xor(e2, 32, 64);
+        float own = sqrtf(e2) * ic * 1.004f;
+        if (square > 0.f && (square < TK_TINY || ic == 0.f)) own = INFINITY;   // imprecise, or too long to square
+        if (!(own >= 0.f)) own = INFINITY;
+        if (!c_ok) own = -INFINITY;
+        uint32_t bits[TQ];
+        int hits = 0;
+#pragma unroll
+        for (int t = 0; t < TQ; ++t) {
+            if (own == INFINITY || ic == 0.f)                    // products that may not be finite: the margin decides
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+            bits[t] = screen_tile(acc[t], ic, own, s_level + t * 32, lane, hits);
+        }
+        dense = dense_block(a, hits, &s_hits, &s_dense);
+        if (!dense && hits) {
+#pragma unroll
+            for (int t = 0; t < TQ; ++t) append_tile<false>(a, bits[t], (qt0 + t) * 32, c, lane, [](int) { return 0.f; });
+        }
     }
+    if (dense) exact_block<2, 2, VEC4, false, true>(a, qt0 * 32, c0, exact);
 }
 
-// ---------------------------------------------------------------------------------------------
-// fp32 screen: scores of 128 queries x 128 candidates over all d columns, then the filter; blocks
-// mapped to XCDs as above.
-// ---------------------------------------------------------------------------------------------
-// The block is 2 x 2 wavefronts; a wavefront owns TM x TN matrix-core tiles of 32 x 32, so the
-// block tile is (64 TM) queries x (64 TN) candidates.  WPE = wavefronts per SIMD the register
-// budget is set for.
-template <int TM, int TN, int WPE, bool VEC4>
-__global__ __launch_bounds__(TK_THREADS, WPE) void topk_scores_kernel(TopkArgs a) {
-    constexpr int BQ = 64 * TM, BC = 64 * TN;
-    constexpr int MOVES_A = BQ * TK_BK / 4 / TK_THREADS, MOVES_B = BC * TK_BK / 4 / TK_THREADS;
-    __shared__ float As[2][BQ][TK_LD];
-    __shared__ float Bs[2][BC][TK_LD];
-    __shared__ float s_invq[BQ];
-    __shared__ float s_theta[BQ];
-    __shared__ __align__(16) float s_tq[BQ];
-
+// The fp32 screen: nothing but such blocks, mapped to XCDs as above.
+template <bool VEC4>
+__global__ __launch_bounds__(TK_THREADS, 4) void topk_scores_kernel(TopkArgs a) {
+    __shared__ ExactLds<2, 2> lds;
     const uint32_t total = a.nq_tiles * a.nc_tiles;
     const uint32_t per_xcd = (total + 7u) / 8u;
     const uint32_t logical = (blockIdx.x % 8u) * per_xcd + blockIdx.x / 8u;
     if (logical >= total) return;                            // uniform per block, before any barrier
-    const uint32_t q0 = (logical % a.nq_tiles) * BQ;
-    const uint32_t c0 = a.c_begin + (logical / a.nq_tiles) * BC;
-
-    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
-    const int wm = wave / 2, wn = wave % 2;
-    for (int i = tid; i < BQ; i += TK_THREADS) {
-        const uint32_t q = q0 + i;
-        const float iq = q < a.Q ? a.invq[q] : 0.f;
-        const float th = q < a.Q ? a.theta[q] : INFINITY;
-        s_invq[i] = iq;
-        s_theta[i] = th;
-        // The same threshold for the raw product dot x (1/|c|), lowered by 2^-20 of itself so that
-        // no score the exact test below accepts is missed (the two roundings of the score and the
-        // ones made here stay under 2^-22 relative); -inf sends every element to the exact test.
-        float t;
-        if (iq == 0.f) {
-            t = th <= 0.f ? -INFINITY : INFINITY;         // every score of a zero query is 0
-        } else {
-            const float r = th / iq;
-            t = fabsf(r) < INFINITY ? r - fabsf(r) * 0x1p-20f : (r > 0.f && th == INFINITY ? INFINITY : -INFINITY);
-        }
-        s_tq[i] = t;
-    }
-
-    // Staging through two LDS buffers of TK_BK columns: while a panel is multiplied, the next one
-    // is written to the other buffer (from registers loaded during the panel before) and the one
-    // after is requested from memory; one barrier per panel.  Thread t moves float4 number t,
-    // t + 256, ... of a panel, i.e. the same four columns of rows srow0, srow0 + TK_RPM, ...
-    // (One buffer of 32 columns with a barrier on either side of its refill measured 1 % slower.)
-    const int srow0 = tid / (TK_BK / 4), scol = (tid % (TK_BK / 4)) * 4;
-    const float* arow0 = a.Qm + (uint64_t)(q0 + srow0) * a.d;      // not dereferenced past Q / c_end
-    const float* brow0 = a.Cm + (uint64_t)(c0 + srow0) * a.d;
-    const uint64_t row_step = (uint64_t)TK_RPM * a.d;
-    float4 ra[MOVES_A], rb[MOVES_B];
-    auto fetch = [&](uint32_t col0) {
-#pragma unroll
-        for (int i = 0; i < MOVES_A; ++i)
-            ra[i] = load_cols<VEC4>(arow0 + i * row_step, q0 + srow0 + i * TK_RPM < a.Q, col0 + scol, a.d);
-#pragma unroll
-        for (int i = 0; i < MOVES_B; ++i)
-            rb[i] = load_cols<VEC4>(brow0 + i * row_step, c0 + srow0 + i * TK_RPM < a.c_end, col0 + scol, a.d);
-    };
-    auto stash = [&](int buf) {
-#pragma unroll
-        for (int i = 0; i < MOVES_A; ++i) {
-            float* pa = &As[buf][srow0 + i * TK_RPM][scol];
-            pa[0] = ra[i].x; pa[1] = ra[i].y; pa[2] = ra[i].z; pa[3] = ra[i].w;
-        }
-#pragma unroll
-        for (int i = 0; i < MOVES_B; ++i) {
-            float* pb = &Bs[buf][srow0 + i * TK_RPM][scol];
-            pb[0] = rb[i].x; pb[1] = rb[i].y; pb[2] = rb[i].z; pb[3] = rb[i].w;
-        }
-    };
-    v16f acc[TM][TN];
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-        for (int j = 0; j < TN; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
-    const int fr = lane & 31, fk = lane >> 5;
-    fetch(0);
-    stash(0);
-    if (TK_BK < a.d) fetch(TK_BK);
-    __syncthreads();
-    int cur = 0;
-    for (uint32_t kb = 0; kb < a.d; kb += TK_BK, cur ^= 1) {
-        if (kb + TK_BK < a.d) {
-            stash(cur ^ 1);
-            if (kb + 2 * TK_BK < a.d) fetch(kb + 2 * TK_BK);
-        }
-        const int kmax = (int)min((uint32_t)TK_BK, a.d - kb);     // columns beyond d hold zeros: skipped
-        // one step of two columns per trip (longer straight runs, which would let the compiler
-        // issue LDS reads under earlier products, measured the same; 16-byte LDS accesses on a
-        // column order that gives each lane four adjacent floats per four steps measured slower)
-#pragma unroll 1
-        for (int kk = 0; kk < kmax; kk += 2) {
-            float av[TM], bv[TN];
-#pragma unroll
-            for (int i = 0; i < TM; ++i) av[i] = As[cur][wm * 32 * TM + i * 32 + fr][kk + fk];
-#pragma unroll
-            for (int j = 0; j < TN; ++j) bv[j] = Bs[cur][wn * 32 * TN + j * 32 + fr][kk + fk];
-#pragma unroll
-            for (int i = 0; i < TM; ++i)
-#pragma unroll
-                for (int j = 0; j < TN; ++j)
-                    acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[i], bv[j], acc[i][j], 0, 0, 0);
-        }
-        __syncthreads();
-    }
-
-    // filter: a score above the query's threshold joins the query's pending list.  Most tiles hold no
-    // such score once the thresholds have risen, so each 32 x 32 tile is first screened with two
-    // instructions per element (raw product against the lowered threshold); only a tile with a hit
-    // goes through the exact test.
-#pragma unroll
-    for (int ti = 0; ti < TM; ++ti) {
-        const int qbase = wm * 32 * TM + ti * 32 + 4 * fk;   // this lane's queries: qbase + 8 (v/4) + v%4
-        float tq[16];
-#pragma unroll
-        for (int v4 = 0; v4 < 4; ++v4) {
-            const float4 t4 = *reinterpret_cast<const float4*>(&s_tq[qbase + 8 * v4]);
-            tq[4 * v4 + 0] = t4.x; tq[4 * v4 + 1] = t4.y; tq[4 * v4 + 2] = t4.z; tq[4 * v4 + 3] = t4.w;
-        }
-#pragma unroll
-        for (int tj = 0; tj < TN; ++tj) {
-            const uint32_t c = c0 + wn * 32 * TN + tj * 32 + fr;
-            const bool c_ok = c < a.c_end;
-            const float ic = c_ok ? a.invc[c] : 0.f;
-            float over = -INFINITY;
-#pragma unroll
-            for (int v = 0; v < 16; ++v) over = fmaxf(over, fmaf(acc[ti][tj][v], ic, -tq[v]));
-            if (__ballot(over >= 0.f) == 0) continue;        // uniform per wavefront
-            uint32_t bits = 0;
-            auto score = [&](int v) { return acc[ti][tj][v] * s_invq[qbase + 8 * (v / 4) + v % 4] * ic; };
-#pragma unroll
-            for (int v = 0; v < 16; ++v)                     // (padded queries carry +inf: never)
-                bits |= c_ok && score(v) > s_theta[qbase + 8 * (v / 4) + v % 4] ? 1u << v : 0u;
-            append_tile<true>(a, bits, q0 + wm * 32 * TM + ti * 32, c, lane, score);
-        }
-    }
+    exact_block<2, 2, VEC4, true, false>(a, (logical % a.nq_tiles) * TK_BQ, a.c_begin + (logical / a.nq_tiles) * TK_BC, lds);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -847,7 +909,7 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
     TopkArgs a{};
     a.Qm = Qm; a.Cm = Cm; a.Q = Q; a.N = N; a.d = d;
     a.invq = (float*)(ws + L.invq); a.invc = (float*)(ws + L.invc); a.theta = theta;
-    a.cnt = (uint32_t*)(ws + L.cnt); a.err = (uint32_t*)(ws + L.err);
+    a.cnt = (uint32_t*)(ws + L.cnt); a.err = (uint32_t*)(ws + L.err); a.dense = a.err + 1;
     const bool vec4 = d % 4 == 0 && ((uintptr_t)Qm % 16 == 0) && ((uintptr_t)Cm % 16 == 0);
 
     const uint64_t row_bytes = (uint64_t)topk_steps(d) * TK_KS * 2;
@@ -877,31 +939,51 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
         else { if (vec4) W2V_QUERIES(false, true); else W2V_QUERIES(false, false); }
 #undef W2V_QUERIES
     }
-    if (screen == TOPK_FP32) {
-        for (uint64_t first = 0; first < N; first += TK_CAND_SLICE) {
-            const uint32_t rows = (uint32_t)std::min<uint64_t>(TK_CAND_SLICE, N - first);
+    auto inverse_lengths = [&](uint64_t begin, uint64_t count) {
+        for (uint64_t first = begin; first < begin + count; first += TK_CAND_SLICE) {
+            const uint32_t rows = (uint32_t)std::min<uint64_t>(TK_CAND_SLICE, begin + count - first);
             const dim3 grid(blocks_for(rows, 128)), block(256);
             const float* at = Cm + first * d;
             float* inv = (float*)a.invc + first;
             if (vec4) hipLaunchKernelGGL(inv_length_kernel<true>, grid, block, 0, st, at, rows, d, inv);
             else hipLaunchKernelGGL(inv_length_kernel<false>, grid, block, 0, st, at, rows, d, inv);
         }
-    }
+    };
+    if (screen == TOPK_FP32) inverse_lengths(0, N);
     // Short rounds first: with a threshold from the first few hundred candidates only a small share of a
     // full round's scores reaches the pending lists.  Many queries: rounds grow fourfold from 256 (every
     // pair listed costs a row read).  Few: sixteenfold from 1024 -- there launches cost more than pairs.
     const uint64_t growth = screen == TOPK_STREAM ? 16 : 4;
+    uint64_t blocks_seen = 0;                  // that screened or might have
     uint64_t len = screen == TOPK_FP32 ? TK_BC : (screen == TOPK_STREAM ? 1024 : 256);
     for (uint64_t begin = 0; begin < N; begin += len, len = len * growth < cap ? len * growth : cap) {
         if (len > cap) len = cap;
         a.c_begin = (uint32_t)begin;
         a.c_end = (uint32_t)(begin + len < N ? begin + len : N);
         const uint32_t m = a.c_end - a.c_begin;
-        a.dense_test = begin >= 32ull * K;         // (earlier, hits are many because the thresholds are low)
-        if (screen == TOPK_WIDE) {
+        // The thresholds are those of `begin` candidates: about m K / begin of this round pass.
+        const double share = begin ? std::min(1.0, (double)K / (double)begin) : 1.0;
+        const uint32_t tile_q = std::min(Q, screen == TOPK_WIDE ? WIDE_Q : TK_STREAM_Q);
+        a.dense_limit = a.dense_skip = TK_NONE;
+        if (begin > 0) {
+            a.dense_limit = (uint32_t)(2.0 * share * 128.0 * tile_q) +
+                            (screen == TOPK_WIDE ? TK_DENSE_WIDE : TK_DENSE_STREAM * std::min(tile_q, 64u));
+            if (blocks_seen) a.dense_skip = (uint32_t)std::min<uint64_t>(TK_NONE - 1, TK_SPARE + (blocks_seen + 1) / 2);
+        }
+        a.blocks = 0;
+        // An early round of a wide search that would list many pairs goes through the fp32 screen, whose fold
+        // reads no rows: listing 4096 x 256 pairs of 300 columns and folding them takes 237 us, this way 85
+        // (4096 x 20 000, K = 64: 1047 -> 614 us in all; 4096 x 200 000, K = 30: 1540 -> 1360).  Below some 10^5
+        // pairs the fp32 product is not faster: 300 x 100 000 328 us, 334 with TK_EXACT_ROUND 50 000.
+        // (Where tau prunes from the start, nothing is known of how many pairs pass: screened.)
+        const bool exact_round = screen == TOPK_FP32 || (screen == TOPK_WIDE && tau <= 0.f && 2ull * m <= cap &&
+                                                         share > 0.01 && share * m * Q > TK_EXACT_ROUND);
+        a.cap = (uint32_t)(exact_round && screen != TOPK_FP32 ? cap / 2 : cap);       // (eight bytes a pair instead of four)
+        if (screen == TOPK_WIDE && !exact_round) {
             a.nq_tiles = (Q + WIDE_Q - 1) / WIDE_Q;
             a.nc_tiles = (m + WIDE_C - 1) / WIDE_C;
             const uint32_t tiles = a.nc_tiles * (WIDE_C / 32), total = a.nq_tiles * a.nc_tiles;
+            if (begin > 0) blocks_seen += a.blocks = total;
             const dim3 grid(((total + 7u) / 8u) * 8u), block(64 * TK_WWM * TK_WWN);
 #define W2V_ROUND(VEC4, HOLD)                                                                              \
     hipLaunchKernelGGL((topk_round_kernel<VEC4, HOLD>), dim3(tiles), dim3(64), 0, st, Cm, a.c_begin, a.c_end, d, \
@@ -912,31 +994,28 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
 #undef W2V_ROUND
             if (vec4) hipLaunchKernelGGL((topk_wide_kernel<TK_WTM, TK_WTN, TK_WWM, TK_WWN, TK_WWPE, true>), grid, block, 0, st, a);
             else hipLaunchKernelGGL((topk_wide_kernel<TK_WTM, TK_WTN, TK_WWM, TK_WWN, TK_WWPE, false>), grid, block, 0, st, a);
-        } else if (screen == TOPK_STREAM) {
+        } else if (screen == TOPK_STREAM && !exact_round) {
             const uint32_t tq = stream_tiles(Q);
-            a.nc_tiles = (m + 31) / 32;
             const uint32_t q_tiles = blocks_for(Q, 32 * tq);
+            if (begin > 0) blocks_seen += a.blocks = q_tiles * blocks_for(m, 128);
 #define W2V_STREAM(TQ)                                                                                     \
     do {                                                                                                   \
         if (vec4) hipLaunchKernelGGL((topk_stream_kernel<TQ, true>), grid, block, 0, st, a);               \
         else hipLaunchKernelGGL((topk_stream_kernel<TQ, false>), grid, block, 0, st, a);                   \
     } while (0)
             for (a.q_first = 0; a.q_first < q_tiles; a.q_first += TK_STREAM_SLICE) {
-                const dim3 grid(blocks_for(a.nc_tiles, 4), std::min(TK_STREAM_SLICE, q_tiles - a.q_first)), block(256);
+                const dim3 grid(blocks_for(m, 128), std::min(TK_STREAM_SLICE, q_tiles - a.q_first)), block(256);
                 if (tq == 1) W2V_STREAM(1); else if (tq == 2) W2V_STREAM(2); else W2V_STREAM(4);
             }
 #undef W2V_STREAM
         } else {
-            // 2 x 2 tiles per wavefront at four wavefronts per SIMD (128 registers, accumulators included)
-            // measured best: 2 x 4 and 4 x 2 tiles (two wavefronts per SIMD) ran 9 % slower, 4 x 4 (one) 2.3
-            // times slower -- this kernel lives on having other wavefronts to switch to at its barriers.
-            constexpr int TK_TM = 2, TK_TN = 2, TK_WPE = 4;
+            if (screen != TOPK_FP32) inverse_lengths(a.c_begin, m);
             a.nq_tiles = (Q + TK_BQ - 1) / TK_BQ;
             a.nc_tiles = (m + TK_BC - 1) / TK_BC;
             const uint32_t total = a.nq_tiles * a.nc_tiles;
             const dim3 grid(((total + 7u) / 8u) * 8u), block(TK_THREADS);
-            if (vec4) hipLaunchKernelGGL((topk_scores_kernel<TK_TM, TK_TN, TK_WPE, true>), grid, block, 0, st, a);
-            else hipLaunchKernelGGL((topk_scores_kernel<TK_TM, TK_TN, TK_WPE, false>), grid, block, 0, st, a);
+            if (vec4) hipLaunchKernelGGL((topk_scores_kernel<true>), grid, block, 0, st, a);
+            else hipLaunchKernelGGL((topk_scores_kernel<false>), grid, block, 0, st, a);
         }
         const bool last = begin + len >= N;
         uint32_t* oi = last ? out_idx : nullptr;
@@ -944,7 +1023,7 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
     hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4, SCORED>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first)), \
                        dim3(64 * WAVES), 0, st, a, K, tau, best, best_cnt, theta, oi, out_score, out_count)
         for (a.q_first = 0; a.q_first < Q; a.q_first += TK_FOLD_SLICE) {
-            if (screen == TOPK_FP32) W2V_FOLD(4, false, true);
+            if (exact_round) W2V_FOLD(4, false, true);
             else if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(4, true, false); else W2V_FOLD(4, false, false); }
             else { if (vec4) W2V_FOLD(16, true, false); else W2V_FOLD(16, false, false); }
         }

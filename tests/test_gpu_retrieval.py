@@ -208,7 +208,8 @@ def screens_agree(Qm, C, K, tau):
     q, c = torch.from_numpy(Qm).cuda(), torch.from_numpy(C).cuda()
     size = lambda r: int(w2v.lib().w2v_topk_cosine_workspace(Q, N, r))
     large, small = size(0) + (Q + N + 512) * (2 * d + 128), size(128)
-    assert screen_of(Q, N, d, large) == (1 if Q <= 128 else 2) and screen_of(Q, N, d, small) == 0
+    assert screen_of(Q, N, d, large) == (2 if Q > 128 else 1)
+    assert screen_of(Q, N, d, small) == 0
     a, b, e = ([t.cpu().numpy() for t in w2v.topk_cosine(q, c, K, tau, workspace=ws)]
                for ws in (torch.empty(large, dtype=torch.uint8, device="cuda"), torch.empty(small, dtype=torch.uint8, device="cuda"), None))
     for x, y, z in zip(a, b, e):
@@ -227,15 +228,18 @@ def test_screens_list_every_pair_that_counts(Q, N, d):
     screens_agree(Qm, C, 64, 0.2)
 
 
-@pytest.mark.parametrize("Q,N", [(7, 9000), (200, 9000)])
+@pytest.mark.parametrize("Q,N", [(7, 9000), (7, 40_000), (200, 9000), (500, 9000)])
 @pytest.mark.parametrize("spread", [0.0, 1e-4, 1e-2])
 def test_crowded_similarities(Q, N, spread):
-    """Similarities closer together than the 16-bit margin, down to equal ones (ranked by index)."""
+    """Similarities closer together than the 16-bit margin, down to equal ones (ranked by index): blocks
+    that form them in fp32 after all, rounds that do not screen, early rounds in fp32 (500 queries)."""
     rng = np.random.default_rng(5)
     base = rng.standard_normal(60)
     Qm = (base + spread * rng.standard_normal((Q, 60))).astype(np.float32)
     C = (base + spread * rng.standard_normal((N, 60))).astype(np.float32)
     gi, gs, _ = screens_agree(Qm, C, 30, -2.0)
+    C[N // 2:] = rng.standard_normal((N - N // 2, 60))         # the second half is not crowded
+    screens_agree(Qm, C, 30, -2.0)
     if spread == 0.0:
         assert np.array_equal(gi, np.tile(np.arange(30, dtype=np.uint32), (Q, 1)))
 
