@@ -10,9 +10,9 @@
 //
 // The screen need not be exact, only never miss: two of the three work in 16 bits on the matrix cores,
 // sixteen times the rate of fp32 there, with a margin that covers their error for certain (below):
-//   wide    (Q > 128): a round's candidates are normalised and rounded to fp16 once, in the order in
+//   wide    (many queries): a round's candidates are normalised and rounded to fp16 once, in the order in
 //           which the matrix cores take them, and multiplied tile by tile.
-//   stream  (Q <= 128): bound by reading the candidates; a wavefront reads 32 of them once, rounds them
+//   stream  (few): bound by reading the candidates; a wavefront reads 32 of them once, rounds them
 //           to bf16 in registers (no scale is known yet; bf16 has fp32's range), and forms norms,
 //           rounding errors and products with all queries on the way.
 //   fp32    exact scores from the fp32 matrix cores: where the workspace is too small for the rounded
@@ -46,7 +46,7 @@ constexpr int TK_LD = TK_BK + 1;    // LDS row pitch (odd: conflict-free column 
 constexpr int TK_THREADS = 256;     // four wavefronts
 constexpr int TK_LIST = 64;         // slots of a query's best list (K <= 64)
 constexpr uint32_t TK_NONE = 0xFFFFFFFFu;
-constexpr uint32_t TK_STREAM_Q = 128;     // most queries of the stream screen's tile
+constexpr uint32_t TK_STREAM_Q = 128;     // queries of the stream screen's tile, at most
 constexpr int TK_KS = 16;                 // columns of one 16-bit matrix-core step
 constexpr float TK_F16_SCALE = 256.f;     // fp16 rows are stored times this: components below 2.4e-7 of the
                                           // row's length (fp16 subnormals) are taken as zero
@@ -876,10 +876,17 @@ static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_b
     const uint64_t row_bytes = (uint64_t)topk_steps(d) * TK_KS * 2;
     const uint64_t n_up = ((uint64_t)N + 255) / 256 * 256;
     const uint64_t free_bytes = workspace_bytes - topk_layout(Q, N).fixed_bytes;          // (fits 128 candidates of eight bytes)
-    // Up to one tile of queries the stream screen reads every candidate once; beyond, reading and rounding
-    // them again for each further tile costs more than rounding them once into the workspace -- unless that
-    // leaves only short rounds.
+    // Up to one tile of queries the stream screen reads every candidate once; with more it reads and rounds
+    // them again for each tile, which from some 256 queries on costs more than rounding them once into the
+    // workspace -- unless that leaves short rounds (us, wide and stream: 4096 over 200 000 x 300 with room for
+    // 900, 3800 candidates 4750, 5670 and 2990, 4230; 1000 with room for 3400 2230, 2150; 300 over 200 000
+    // x 60 280, 264).  With 129 to 256 the wide screen is ahead only over few candidates, whose rows it need
+    // not read twice (129 over 20 000 x 300 187, 206; over 200 000 x 60 246, 224; x 512 840, 600; x 1000
+    // 2030, 1130).  The stream screen's lists hold close to twice what the fp32 screen's do; where the rounds
+    // of many queries are short and the rounded queries take much of that, it is no longer ahead (4096 over 20 000 x 800 with room for
+    // 512 4590, fp32 3870).
     TopkPlan p{TOPK_FP32, free_bytes / (8ull * Q) / TK_BC * TK_BC, 0};
+    const uint64_t cap_fp32 = p.cap;
     auto room = [&](uint64_t tile, uint64_t per_candidate, uint64_t granule, uint64_t least, TopkScreen screen) {
         const uint64_t q_up = (Q + tile - 1) / tile * tile, q_bytes = q_up * (row_bytes + 4) + 512;
         if (free_bytes <= q_bytes) return false;
@@ -888,8 +895,11 @@ static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_b
         p = TopkPlan{screen, cap, q_up};
         return true;
     };
-    if (Q <= TK_STREAM_Q || !room(WIDE_Q, 4ull * Q + row_bytes + 4, 256, 8192, TOPK_WIDE))
-        room(32 * stream_tiles(Q), 4ull * Q, TK_BC, 2 * TK_BC, TOPK_STREAM);
+    const bool wide = Q > 2 * TK_STREAM_Q || (Q > TK_STREAM_Q && N <= (1u << 16) && topk_steps(d) <= TK_HOLD);
+    const uint64_t least_wide = std::min<uint64_t>(8192, std::max<uint64_t>(1024, (1u << 22) / Q));
+    const uint64_t least_stream = Q > TK_STREAM_Q ? std::max<uint64_t>(2 * TK_BC, cap_fp32 + cap_fp32 / 2) : 2 * TK_BC;
+    if (!wide || !room(WIDE_Q, 4ull * Q + row_bytes + 4, 256, least_wide, TOPK_WIDE))
+        room(32 * stream_tiles(Q), 4ull * Q, TK_BC, least_stream, TOPK_STREAM);
     p.cap = std::min<uint64_t>({p.cap, n_up, TK_CAND_SLICE});
     return p;
 }
@@ -953,9 +963,10 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
     // Short rounds first: with a threshold from the first few hundred candidates only a small share of a
     // full round's scores reaches the pending lists.  Many queries: rounds grow fourfold from 256 (every
     // pair listed costs a row read).  Few: sixteenfold from 1024 -- there launches cost more than pairs.
-    const uint64_t growth = screen == TOPK_STREAM ? 16 : 4;
+    const bool many = Q > 2 * TK_STREAM_Q || screen == TOPK_WIDE;
+    const uint64_t growth = many || screen == TOPK_FP32 ? 4 : 16;
     uint64_t blocks_seen = 0;                  // that screened or might have
-    uint64_t len = screen == TOPK_FP32 ? TK_BC : (screen == TOPK_STREAM ? 1024 : 256);
+    uint64_t len = screen == TOPK_FP32 ? TK_BC : (many ? 256 : 1024);
     for (uint64_t begin = 0; begin < N; begin += len, len = len * growth < cap ? len * growth : cap) {
         if (len > cap) len = cap;
         a.c_begin = (uint32_t)begin;
@@ -971,12 +982,12 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
             if (blocks_seen) a.dense_skip = (uint32_t)std::min<uint64_t>(TK_NONE - 1, TK_SPARE + (blocks_seen + 1) / 2);
         }
         a.blocks = 0;
-        // An early round of a wide search that would list many pairs goes through the fp32 screen, whose fold
+        // With many queries an early round that would list many pairs goes through the fp32 screen, whose fold
         // reads no rows: listing 4096 x 256 pairs of 300 columns and folding them takes 237 us, this way 85
         // (4096 x 20 000, K = 64: 1047 -> 614 us in all; 4096 x 200 000, K = 30: 1540 -> 1360).  Below some 10^5
         // pairs the fp32 product is not faster: 300 x 100 000 328 us, 334 with TK_EXACT_ROUND 50 000.
         // (Where tau prunes from the start, nothing is known of how many pairs pass: screened.)
-        const bool exact_round = screen == TOPK_FP32 || (screen == TOPK_WIDE && tau <= 0.f && 2ull * m <= cap &&
+        const bool exact_round = screen == TOPK_FP32 || (many && tau <= 0.f && 2ull * m <= cap &&
                                                          share > 0.01 && share * m * Q > TK_EXACT_ROUND);
         a.cap = (uint32_t)(exact_round && screen != TOPK_FP32 ? cap / 2 : cap);       // (eight bytes a pair instead of four)
         if (screen == TOPK_WIDE && !exact_round) {

@@ -202,13 +202,14 @@ def screen_of(Q, N, d, nbytes):
 
 
 def screens_agree(Qm, C, K, tau):
-    """A workspace with room for the 16-bit screen of that many queries (stream up to 128, else wide), the
-    default one and the smallest (fp32 scores, rounds of 128): same bits."""
+    """A workspace with room for the 16-bit screen of that many queries (stream up to 128; wide for more
+    than 256, and from 129 on where rows are short and few), the default one and the smallest (fp32 scores,
+    rounds of 128): same bits."""
     (Q, d), N = Qm.shape, C.shape[0]
     q, c = torch.from_numpy(Qm).cuda(), torch.from_numpy(C).cuda()
     size = lambda r: int(w2v.lib().w2v_topk_cosine_workspace(Q, N, r))
     large, small = size(0) + (Q + N + 512) * (2 * d + 128), size(128)
-    assert screen_of(Q, N, d, large) == (2 if Q > 128 else 1)
+    assert screen_of(Q, N, d, large) == (2 if Q > 256 or (Q > 128 and N <= 65536 and d <= 320) else 1)
     assert screen_of(Q, N, d, small) == 0
     a, b, e = ([t.cpu().numpy() for t in w2v.topk_cosine(q, c, K, tau, workspace=ws)]
                for ws in (torch.empty(large, dtype=torch.uint8, device="cuda"), torch.empty(small, dtype=torch.uint8, device="cuda"), None))
