@@ -505,6 +505,19 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
                   const float* coeffs_in, float* coeffs_out, bool fused, float alpha,
                   double* loss_out, bool join_sorts, hipStream_t st) {
     const CallScalars* dev = ws_owner->call_dev;
+    const bool alone = adjust_walk_alone(p.M, sh->g);
+    // From 2^22 slots on the kernels after the output side's walk are bound by memory, shared with each other
+    // and with the sorts of an announced minibatch, and not by their own chain of latencies: they take small
+    // blocks and few rows in flight (`shared`).  Benchmark step (6.3 M slots) 3.201 -> 3.185 ms; at 1.2 M
+    // slots, d = 132 to 300, the same costs 3 to 4 %.
+    // And there the border slots are cleared by a launch of their own.  It follows the wait for an announced
+    // minibatch's index work, and the input-side kernel behind it starts sooner than right after that wait:
+    // 3.185 -> 3.168 ms; with the fill ahead of the wait it does not.
+    const bool shared = alone && p.M >= (1u << 22);
+    if (shared && !p.wfill_done) {
+        launch_wseg_fill(p.pb_keys, p.M, st);
+        p.wfill_done = true;
+    }
     {
         Phase ph(ws_owner, W2V_PH_USIDE, st);
         USideArgs a{};
@@ -538,12 +551,16 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
         t.defer_rows = p.delta; t.defer_keys = p.dkey; t.level = ++us.level; t.cp = cp; t.dev = dev;
         return t;
     };
+    auto w_level = [&]() {
+        TailArgs t{sh->W, sh->g, alpha, ws.src_rows, ws.src_keys, ws.slots, ws.dst_rows, ws.dst_keys};
+        t.level = ++ws.level; t.dev = dev;
+        return t;
+    };
     const ApplyDelta apply{sh->U, p.delta, p.dkey, p.n, alpha, dev};
     WSideArgs w{};
     w.U = sh->U; w.W = sh->W; w.g = sh->g; w.skey = skw; w.sidx = sidx; w.M = p.M; w.T = p.T;
     w.in_idx = p.in_safe; w.coeffs = fused ? coeffs_out : coeffs_in; w.alpha = alpha;
     w.prows = p.pb_rows; w.pkeys = p.pb_keys; w.skip_alone = p.own_rows; w.dev = dev;
-    const bool alone = adjust_walk_alone(p.M, sh->g);
     const bool two = alone && ws_owner->overlap && ensure_side_stream(ws_owner) == W2V_OK;
     if (alone) {
         // A large minibatch: the input side's levels and the loss run beside the output side's walk on the
@@ -568,28 +585,37 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
         }
         {
             Phase ph(ws_owner, W2V_PH_WSIDE, st);
-            launch_wseg(w, st, true);
+            launch_wseg(w, st);
         }
         if (two) {
             (void)hipEventRecord(ws_owner->ev_wdone, st);
             (void)hipStreamWaitEvent(side, ws_owner->ev_wdone, 0);
         }
-        Phase ph(ws_owner, W2V_PH_APPLY, side);
-        launch_apply(apply, sh->g, side);
-        applied = true;
+        {
+            Phase ph(ws_owner, W2V_PH_APPLY, side);
+            launch_apply(apply, sh->g, shared, side);
+        }
         if (two) (void)hipEventRecord(ws_owner->ev_tails, side);
+        {
+            Phase ph(ws_owner, W2V_PH_APPLY, st);
+            while (ws.slots) {
+                launch_tail(w_level(), st, shared);
+                advance(ws);
+            }
+        }
+        if (two) (void)hipStreamWaitEvent(st, ws_owner->ev_tails, 0);
+        return;
     }
-    for (bool first = !alone, any = !alone || ws.slots; any; first = false) {
+    for (bool first = true, any = true; any; first = false) {
         Phase ph(ws_owner, first ? W2V_PH_WSIDE : W2V_PH_APPLY, st);
         AdjustStage x;
         x.g = sh->g;
         TailArgs wt{}, ut{};
-        const bool w_level = !first && ws.slots > 0, u_level = us.slots > 0;
+        const bool higher = !first && ws.slots > 0, u_level = us.slots > 0;
         if (first) {
             x.wfirst = &w;
-        } else if (w_level) {
-            wt = TailArgs{sh->W, sh->g, alpha, ws.src_rows, ws.src_keys, ws.slots, ws.dst_rows, ws.dst_keys};
-            wt.level = ++ws.level; wt.dev = dev;
+        } else if (higher) {
+            wt = w_level();
             x.wtail = &wt;
         }
         if (u_level) {
@@ -605,11 +631,10 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
             loss_step = loss_step == 1 ? 2u : 0u;
         }
         launch_adjust_stage(x, st);
-        if (w_level) advance(ws);
+        if (higher) advance(ws);
         if (u_level) advance(us);
         any = us.slots || ws.slots || loss_step || !applied;
     }
-    if (two) (void)hipStreamWaitEvent(st, ws_owner->ev_tails, 0);
 }
 
 }  // namespace
@@ -1368,7 +1393,7 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
         u.U = p.E; u.W = sh->U; u.g = sh->g; u.skey = skc; u.sidx = cidx; u.M = p.m; u.T = 1;
         u.in_idx = p.ex_of; u.coeffs = p.weight; u.alpha = alpha;
         u.prows = p.pd_rows; u.pkeys = p.pd_keys;
-        launch_wseg(u, side, true);
+        launch_wseg(u, side);
         run_tails(sh, sh->U, alpha, p.pd_rows, p.pd_keys, p.slots_c1, p.pe_rows, p.pe_keys, side);
     }
     if (join_sorts) join_output_sort(owner, st);
@@ -1379,7 +1404,7 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
         w.in_idx = p.iota; w.coeffs = fused ? coeffs_out : coeffs_in; w.alpha = alpha;
         w.prows = p.pb_rows; w.pkeys = p.pb_keys;
         w.skip_alone = fused && p.own_rows;
-        launch_wseg(w, st, true);
+        launch_wseg(w, st);
         run_tails(sh, sh->W, alpha, p.pb_rows, p.pb_keys, p.slots_w1, p.pc_rows, p.pc_keys, st);
     }
     if (loss_out) {                                   // (queued after both walks: nothing waits for it)

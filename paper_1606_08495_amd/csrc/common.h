@@ -194,11 +194,10 @@ struct WSideArgs {
     float* prows; uint32_t* pkeys;
     const CallScalars* dev;      // optional: the learning rate is read from here
 };
-// (the cells' border slots must read KEY_NONE when the kernel starts: launch_wseg_fill writes that;
-// launch_wseg does it itself unless told that the caller already has)
+// (the cells' border slots must read KEY_NONE when the kernel starts: launch_wseg_fill writes that)
 FillJob wseg_fill_job(uint32_t* pkeys, uint32_t M);
 void launch_wseg_fill(uint32_t* pkeys, uint32_t M, hipStream_t st);
-void launch_wseg(const WSideArgs& a, hipStream_t st, bool filled = false);
+void launch_wseg(const WSideArgs& a, hipStream_t st);
 
 // Higher levels (both sides): entries are partial rows src_rows[i] with destination src_keys[i]
 // (KEY_NONE = nothing, KEY_ZERO flag = belongs to the run but empty).
@@ -211,7 +210,7 @@ struct TailArgs {
     float* defer_rows = nullptr; uint32_t* defer_keys = nullptr; uint32_t level = 0, cp = 0;
     const CallScalars* dev = nullptr;      // optional: the learning rate is read from here
 };
-void launch_tail(const TailArgs& a, hipStream_t st);
+void launch_tail(const TailArgs& a, hipStream_t st, bool shared = false);    // shared: memory is, small blocks
 void launch_input_tail(const TailArgs& a, hipStream_t st);       // with defer_rows
 
 // U[dkey[ps]] += alpha * delta[ps] wherever dkey[ps] != KEY_NONE.
@@ -219,7 +218,7 @@ struct ApplyDelta {
     float* U; const float* delta; const uint32_t* dkey; uint32_t n; float alpha;
     const CallScalars* dev;
 };
-void launch_apply(const ApplyDelta& x, RowGeom g, hipStream_t st);
+void launch_apply(const ApplyDelta& x, RowGeom g, bool shared, hipStream_t st);   // shared: memory is, one row in flight
 
 // Parts of one update that do not depend on each other, in ONE launch (each may be absent): the
 // output side's level-1 kernel (wfirst; its border slots already cleared) or one of its higher

@@ -28,8 +28,9 @@ constexpr int adj_threads(int G) { return G == 16 ? 128 : 256; }      // everyth
 // Higher levels: entries per block, which is their chunk (even, so a border's two slots fall into one),
 // and the block's size.  A lane group's share of the chunk is what it reads one batch after the other, so
 // a launch that holds nothing but these levels takes the largest blocks whose pieces fit LDS (shares of
-// 8 entries; 65 536 pairs, d = 100: 26 us a level with shares of 32); beside the output side's walk they
-// have that kernel's block size and its time to hide in.
+// 8 entries; 65 536 pairs, d = 100: 26 us a level with shares of 32); beside the output side's walk, or where
+// a large minibatch's kernels share the memory, they have those kernels' block size and find room between
+// them (benchmark step: levels of 512 threads 46 us each, of 256 42; step 3.201 -> 3.194 ms).
 constexpr int tail_block(int G) { return G == 64 ? 128 : 256; }
 constexpr int tail_threads(int G, int NV) { return G == 16 || NV == 2 ? 512 : (NV > 2 ? 256 : 1024); }
 constexpr uint32_t NOKEY = 0xFFFFFFFFu;   // compares unequal to every masked key
@@ -275,10 +276,10 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, uint32_t vb, TailLds
     }
 }
 
-template <int G, int NV>
-__global__ __launch_bounds__(tail_threads(G, NV)) void tail_kernel(SegArgs a) {
-    __shared__ TailLds<G, NV, tail_threads(G, NV)> lds;
-    tail_body<G, NV, tail_threads(G, NV), false>(a, blockIdx.x, lds);
+template <int G, int NV, int THREADS>
+__global__ __launch_bounds__(THREADS) void tail_kernel(SegArgs a) {
+    __shared__ TailLds<G, NV, THREADS> lds;
+    tail_body<G, NV, THREADS, false>(a, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -291,7 +292,7 @@ __global__ __launch_bounds__(tail_threads(G, NV)) void tail_kernel(SegArgs a) {
 //    (cells).  Each piece is summed by one group -- the group of the chunk in which the run starts,
 //    or of the chunk at the cell's start -- which streams on through the cell.  A piece that is the
 //    whole run is finished at once; otherwise it is left in the cell's border slots (two per cell
-//    border, as in seg_kernel) for the higher levels.
+//    border) for the higher levels.
 // Short or long follows from the run's own extent on the chunk grid, so every group that meets a
 // run decides alike, from the keys at six fixed positions around its chunk.  No partial row is
 // written unless a word collects more than L contributions or so.
@@ -528,10 +529,9 @@ static SegArgs seg_args_of(const TailArgs& t) {
     return a;
 }
 
-void launch_wseg(const WSideArgs& w, hipStream_t st, bool filled) {
+void launch_wseg(const WSideArgs& w, hipStream_t st) {
     if (w.M == 0) return;
     const SegArgs a = seg_args_of(w);
-    if (!filled) launch_wseg_fill(w.pkeys, w.M, st);
     uint32_t nchunks = (w.M + WOWN_C - 1) / WOWN_C;
 #define CALL(G, NV)                                                                              \
     hipLaunchKernelGGL((wown_kernel<G, NV, (NV <= 2 ? 4 : 2)>),                                   \
@@ -542,20 +542,24 @@ void launch_wseg(const WSideArgs& w, hipStream_t st, bool filled) {
 #undef CALL
 }
 
-void launch_tail(const TailArgs& t, hipStream_t st) {
+void launch_tail(const TailArgs& t, hipStream_t st, bool shared) {
     if (t.entries == 0) return;
     const SegArgs a = seg_args_of(t);
+#define CALL_THREADS(G, NV, THREADS)                                                             \
+    hipLaunchKernelGGL((tail_kernel<G, NV, THREADS>), dim3(blocks_for(t.entries, tail_block(G))), \
+                       dim3(THREADS), 0, st, a)
 #define CALL(G, NV)                                                                              \
-    hipLaunchKernelGGL((tail_kernel<G, NV>), dim3(blocks_for(t.entries, tail_block(G))),         \
-                       dim3(tail_threads(G, NV)), 0, st, a)
+    do { if (shared) CALL_THREADS(G, NV, adj_threads(G)); else CALL_THREADS(G, NV, tail_threads(G, NV)); } while (0)
     W2V_DISPATCH_GEOM(t.g.d4, CALL);
 #undef CALL
+#undef CALL_THREADS
 }
 
 // ---------------------------------------------------------------------------------------------
 // Write-back of the input-vector changes held in the delta buffer: U[dkey[ps]] += alpha * delta[ps]
 // wherever dkey[ps] names a row.  A lane group looks at APPLY_P sorted positions and takes the few
-// that do, four rows in flight.  (64 positions one after the other, before: 8 us for 4096 pairs.)
+// that do, D rows in flight: four in a joint launch (64 positions one after the other, before: 8 us for
+// 4096 pairs).
 // ---------------------------------------------------------------------------------------------
 constexpr int APPLY_P = 16;
 struct ApplyArgs {
@@ -563,9 +567,8 @@ struct ApplyArgs {
     const CallScalars* dev;
 };
 
-template <int G, int NV, int THREADS>
+template <int G, int NV, int THREADS, int D>
 __device__ __forceinline__ void apply_body(const ApplyArgs& a, uint32_t vb) {
-    constexpr int D = NV <= 2 ? 4 : 2;
     const float alpha = a.dev ? a.dev->alpha : a.alpha;
     const int l = threadIdx.x % G;
     const uint32_t base = (vb * (uint32_t)THREADS + threadIdx.x) / G * APPLY_P;
@@ -593,21 +596,24 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, uint32_t vb) {
     }
 }
 
-// On its own, beside the output side's levels on another stream.
-template <int G, int NV>
+// On its own, beside the output side's levels on another stream.  Where it shares the memory with them and
+// with announced sorts, one row in flight per group (benchmark step with four 3.177 ms, two 3.179, one 3.168).
+template <int G, int NV, int D>
 __global__ __launch_bounds__(adj_threads(G)) void apply_kernel(ApplyArgs a) {
-    apply_body<G, NV, adj_threads(G)>(a, blockIdx.x);
+    apply_body<G, NV, adj_threads(G), D>(a, blockIdx.x);
 }
 
-void launch_apply(const ApplyDelta& x, RowGeom g, hipStream_t st) {
+void launch_apply(const ApplyDelta& x, RowGeom g, bool shared, hipStream_t st) {
     if (x.n == 0) return;
     const ApplyArgs a{(float4*)x.U, g, (const float4*)x.delta, x.dkey, x.n, x.alpha, x.dev};
-#define CALL(G, NV)                                                                                       \
-    hipLaunchKernelGGL((apply_kernel<G, NV>),                                                             \
+#define CALL_ROWS(G, NV, D)                                                                               \
+    hipLaunchKernelGGL((apply_kernel<G, NV, D>),                                                          \
                        dim3(blocks_for((uint64_t)blocks_for(x.n, APPLY_P) * G, adj_threads(G))),          \
                        dim3(adj_threads(G)), 0, st, a)
+#define CALL(G, NV) do { if (shared) CALL_ROWS(G, NV, 1); else CALL_ROWS(G, NV, (NV <= 2 ? 4 : 2)); } while (0)
     W2V_DISPATCH_GEOM(g.d4, CALL);
 #undef CALL
+#undef CALL_ROWS
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -655,7 +661,7 @@ __global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? 5 
         return;
     }
     b -= s.w_blocks;
-    if (!FIRST) apply_body<G, NV, THREADS>(s.apply, b);
+    if (!FIRST) apply_body<G, NV, THREADS, D>(s.apply, b);
 }
 
 // The input side's levels alone, beside the output side's walk on another stream: blocks no larger than

@@ -297,12 +297,44 @@ def test_large_minibatch_whose_walk_has_its_own_launch(V, d, n, k):
         got.append((all_rows(sh, 0), all_rows(sh, 1), loss.item()))
         sh.destroy()
     assert np.array_equal(got[0][0], got[1][0]) and np.array_equal(got[0][1], got[1][1])
-    assert abs(got[0][2] - got[1][2]) <= 1e-12 * abs(got[0][2])     # (summed in blocks of other sizes)
+    assert got[0][2] == got[1][2]
     rows = np.arange(V, dtype=np.uint32)
     U, W = oracle.init_rows(3, d, 0, d, 0, rows), oracle.init_rows(3, d, 0, d, 1, rows)
     th, al = oracle.build_alias(counts)
     oracle.train_minibatch([U], [W], w2v.index_to_numpy(a), w2v.index_to_numpy(b), k, 9, th, al, 0.001)
     assert vec_error(got[0][0], U) <= TOL1 and vec_error(got[0][1], W) <= TOL1
+
+
+@pytest.mark.parametrize("form", ["adjust", "two shards"])
+def test_large_minibatch_from_given_coefficients(form):
+    """The same walk from the two-call form and over shards that use one shard's buffers, streams and events
+    one after the other; the output side's order comes from the second stream.  Two steps."""
+    print("large minibatch,", form, flush=True)
+    V, n, k, alpha = 3000, 180_000, 5, 0.001
+    cuts = [(0, 140)] if form == "adjust" else [(0, 132), (132, 148)]
+    d = sum(w for _, w in cuts)
+    rng = np.random.default_rng(d)
+    cdf = workloads.zipf_cdf(V, 1.1)
+    counts = workloads.analytic_counts(V, 1.1, 10 ** 7)
+    th, al = oracle.build_alias(counts)
+    shards = [make_shard(V, w, 3, counts, d_total=d, col_begin=c) for c, w in cuts]
+    U, W = oracle_state(V, d, 3)
+    loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+    for step in range(2):
+        a, b = workloads.zipf_draw(cdf, n, rng), workloads.zipf_draw(cdf, n, rng)
+        if form == "adjust":
+            g = workloads.uniform_coeffs(n, k + 1, step)
+            shards[0].adjust(dev(a), dev(b), k, 50 + step, torch.from_numpy(g).cuda(), alpha)
+            oracle.adjust(U, W, a, b, k, 50 + step, th, al, g, alpha)
+        else:
+            w2v.train_minibatch(shards, dev(a), dev(b), k, 50 + step, alpha, loss=loss)
+            ref = oracle.train_minibatch([U], [W], a, b, k, 50 + step, th, al, alpha)
+            assert abs(loss.item() - ref) <= 1e-5 * abs(ref)
+    for which, M in ((0, U), (1, W)):
+        assert vec_error(np.concatenate([all_rows(sh, which) for sh in shards], axis=1), M) <= 2 * TOL1
+    for sh in shards:
+        sh.status()
+        sh.destroy()
 
 
 def test_adjust_reads_start_of_call_vectors():
