@@ -306,14 +306,15 @@ int w2v_export_rows(w2v_shard* const* shards, uint32_t S, int which, const uint3
  * similarities by increasing index; an all-zero vector has similarity 0 with everything.  Only
  * similarities strictly above tau are returned (pass tau <= -2 for no threshold):
  * out_idx_dev[q][0..count) / out_score_dev[q][0..count) hold them, the remaining slots of the K hold
- * 0xFFFFFFFF / 0, and out_count_dev[q] (may be NULL) the count.  fp32 throughout; 1 <= K <=
- * W2V_TOPK_MAX.
+ * 0xFFFFFFFF / 0, and out_count_dev[q] (may be NULL) the count.  Similarities are formed and ranked in
+ * fp32; which pairs need one may be found out with vectors rounded to 16 bits, by a test that covers the
+ * rounding and misses none, so that it does not show in the results.  1 <= K <= W2V_TOPK_MAX.
  *
  * The call allocates nothing: workspace_dev (256-byte aligned device memory, contents irrelevant
- * before and after) holds the norms, the running best lists and, per query, room for one round of
- * candidates.  w2v_topk_cosine_workspace(Q, N, r) is the size for rounds of r candidates (r = 0 or
- * r >= N: a single round); a smaller workspace means more, shorter rounds (the minimum is r = 128),
- * never a different result.  All work is queued on the stream; nothing is synchronised. */
+ * before and after) holds the norms, the running best lists, per query room for one round of candidates
+ * and, where there is room beside them, the rounded vectors.  w2v_topk_cosine_workspace(Q, N, r) is the
+ * size for rounds of r candidates (r = 0 or r >= N: a single round); a smaller workspace means more,
+ * shorter rounds (the minimum is r = 128), never a different result.  All work is queued on the stream; nothing is synchronised. */
 #define W2V_TOPK_MAX 64
 size_t w2v_topk_cosine_workspace(uint32_t Q, uint32_t N, uint32_t round_candidates);
 int w2v_topk_cosine(const float* queries_dev, uint32_t Q, const float* cands_dev, uint32_t N,

@@ -695,9 +695,11 @@ static void launch_stage_shape(StageDev s, bool first, hipStream_t st) {
     else hipLaunchKernelGGL((adjust_stage_kernel<G, NV, false>), grid, block, 0, st, s);
 }
 
-// (Its own launch keeps its registers to itself; rows of more than 128 floats: k = 25, d = 200, 2^18 pairs 4.41
-// against 4.55 ms; at sixteen lanes per row the joint launch is as fast or faster, and so it is while a
-// level takes as long as a walk.)
+// (Its own launch keeps its registers to itself, and the levels run beside it; against that, events between
+// streams.  Step in us, own launch and joint, k = 5: d = 300, 1.05, 2.1 and 6.3 M slots 634, 660; 1099, 1165;
+// 2987, 3223; d = 200 483, 472; 835, 837; 2250, 2291.  Below: 0.3 M slots d = 300 275, 262; d = 200 229, 202; at
+// 0.6 M 414, 428; 327, 309.  Rows of up to 128 floats, joint as fast or faster throughout: d = 100, 0.3 to
+// 6.3 M slots 201, 172; 260, 239; 343, 333; 578, 568; 1489, 1486.)
 bool adjust_walk_alone(uint32_t M, RowGeom g) { return M >= (1u << 20) && g.d4 > 32; }
 
 void launch_adjust_stage(const AdjustStage& x, hipStream_t st) {

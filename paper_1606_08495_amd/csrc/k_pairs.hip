@@ -9,7 +9,7 @@
 //             per PAIR_BLOCK survivors on the way
 //   emit    : a block takes PAIR_BLOCK centers, scans their pair counts in LDS and writes its stretch
 //             of the output one pair per thread
-// A block of two million tokens is a chain of seven launches bound by their latencies and, in emit, by
+// A block of two million tokens is a chain of six launches bound by their latencies and, in emit, by
 // the 8 bytes a pair has to be written.  (One center per thread with a serial loop over its pairs, full
 // scans around it: ten launches, 265 us for 2^21 tokens, 114 of them the scattered writes; now 118 and 23.)
 #include "common.h"

@@ -9,7 +9,7 @@ namespace w2v {
 // Terms per block: a few per thread, so that the block's reduction is a small part of its work (256 a
 // block, one per thread and eight barriers each, took 0.35 ms beside the row kernels for the 11.5 M terms
 // of a search minibatch) and there are still blocks for the whole chip (4096 a block: 36 us for 600 000
-// terms over five shards against 9).  Past 2^24 terms more, for the one block that adds up the sums.
+// terms over five shards against 13).  Past 2^24 terms more, for the one block that adds up the sums.
 constexpr uint32_t LOSS_SHORT_TERMS = 1u << 24;
 __host__ __device__ inline uint32_t loss_terms_of(uint32_t total) { return total <= LOSS_SHORT_TERMS ? 1024u : 16384u; }
 
