@@ -774,7 +774,7 @@ def main():
     achieved = algo[dom] / (dom_ms * 1e-3) / 1e9
     compulsory_gbs = compulsory[dom] / (dom_ms * 1e-3) / 1e9
     # L2<->fabric bytes per launch: NOT measured in this run -- read from the committed rocprofv3
-    # counter summary of the same command (counters and timing cannot share a run)
+    # counter summary of the same workload (counters and timing cannot share a run)
     traffic, traffic_source = None, None
     tfile = os.path.join(ROOT, "profiles", "%s_hbm_traffic.txt" % wl.name)
     if os.path.exists(tfile):
@@ -783,8 +783,8 @@ def main():
             if len(parts) == 3 and parts[0] == "traffic" and parts[1] == dom:
                 traffic = float(parts[2])
                 traffic_source = "profiles/%s_hbm_traffic.txt (rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE " \
-                                 "of this command in a run of its own; L2<->fabric, an upper bound on " \
-                                 "HBM bytes)" % wl.name
+                                 "of this workload, in a run of its own of fewer steps; " \
+                                 "L2<->fabric, an upper bound on HBM bytes)" % wl.name
     step_algo = 3 * (wl.k + 2) * R * n      # the paper-style logical figure: 3 (k+2) rows per pair
     # the whole step at its least: every distinct row of either matrix read once and written once
     step_compulsory = 2 * (du + dw) * R + 8 * n + (4 * M if not fused else 0)

@@ -885,8 +885,8 @@ static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_b
     // x 60 280, 264).  With 129 to 256 the wide screen is ahead only over few candidates, whose rows it need
     // not read twice (129 over 20 000 x 300 187, 206; over 200 000 x 60 246, 224; x 512 840, 600; x 1000
     // 2030, 1130).  The stream screen's lists hold close to twice what the fp32 screen's do; where the rounds
-    // of many queries are short and the rounded queries take much of that, it is no longer ahead (4096 over 20 000 x 800 with room for
-    // 512 4590, fp32 3870).
+    // of many queries are short and the rounded queries take much of that, it is no longer ahead (4096 over
+    // 20 000 x 800 with room for 512 4590, fp32 3870).
     TopkPlan p{TOPK_FP32, free_bytes / (8ull * Q) / TK_BC * TK_BC, 0};
     const uint64_t cap_fp32 = p.cap;
     auto room = [&](uint64_t tile, uint64_t per_candidate, uint64_t granule, uint64_t least, TopkScreen screen) {

@@ -276,10 +276,10 @@ def test_adjust_runs_across_the_borders_of_every_level(d, n, k):
     assert eu <= TOL1 and ew <= TOL1
 
 
-@pytest.mark.parametrize("V,d,n,k", [(3000, 132, 180_000, 5), (3000, 300, 131_072, 7)])
+@pytest.mark.parametrize("V,d,n,k", [(3000, 132, 180_000, 5), (3000, 300, 131_072, 7), (30_000, 132, 700_001, 5)])
 def test_large_minibatch_whose_walk_has_its_own_launch(V, d, n, k):
     """2^20 slots and more at one wavefront per row: the input side's levels and the loss on the second
-    stream; on one stream, and replayed, the same bits."""
+    stream (from 2^22 slots on also smaller blocks and a fill ahead); on one stream, and replayed, the same bits."""
     rng = np.random.default_rng(2)
     cdf = workloads.zipf_cdf(V, 1.1)
     a, b = dev(workloads.zipf_draw(cdf, n, rng)), dev(workloads.zipf_draw(cdf, n, rng))
