@@ -707,9 +707,9 @@ __global__ __launch_bounds__(TK_THREADS, 4) void topk_scores_kernel(TopkArgs a) 
 
 // ---------------------------------------------------------------------------------------------
 // Fold: one block per query gives the listed pairs their similarities -- a lane per candidate, one
-// 128-byte line of its row at a time; the fp32 screen has them listed already -- and merges those above the threshold into the sorted best list
-// (higher score first, equal scores by lower index), then raises the threshold to the K-th best and
-// empties the list.  Rounds come in index order, so a later candidate that only equals the K-th best
+// 128-byte line of its row at a time; the fp32 screen has them listed already -- and merges those above
+// the threshold into the sorted best list (higher score first, equal scores by lower index), then raises
+// the threshold to the K-th best and empties the list.  Rounds come in index order, so a later candidate that only equals the K-th best
 // never enters.  Each wavefront keeps its own 64 best, sorted across its lanes; the lists are merged
 // through LDS at the end.  `out_idx` (last round): the results are written as well.
 // ---------------------------------------------------------------------------------------------
