@@ -364,11 +364,25 @@ int ensure_set(w2v_shard* sh, IndexSet& x, uint32_t n, uint32_t M) {
     return W2V_OK;
 }
 
+// Both sides' keys brought into order, in the same launches.  With `marks`, *keys (what jobs[0] sorts) then
+// carries KEY_ALONE where a row is named once -- of a small minibatch in a copy.
+void sort_and_mark(const SortJob (&jobs)[2], uint32_t bits, uint32_t* sort_tmp, uint32_t* err, bool marks,
+                   bool cleared, uint32_t** keys, hipStream_t st) {
+    if (group_small(jobs[0].n, jobs[1].n)) {
+        uint32_t* copy = marks ? (uint32_t*)jobs[0].buf1 : nullptr;
+        launch_group_jobs(jobs, 2, bits, copy, st);
+        if (copy) *keys = copy;
+        return;
+    }
+    launch_sort_jobs(jobs, 2, bits, sort_tmp, err, st, cleared);
+    if (marks) launch_mark_alone(*jobs[0].out_keys, *jobs[0].out_vals, jobs[0].n, *keys, st);
+}
+
 // Everything adjust needs before its first row kernel: the checked input words, the destination
 // keys (positive word + regenerated negatives) and both sorts.
 // The fused step's input-side kernel needs both sorts (it updates the output rows that one slot names),
-// so there everything is queued on the caller's stream, both sides' keys through the same launches.
-// With given coefficients that kernel needs the keys and the (small) input-side sort only: key
+// so there everything is queued on the caller's stream, both sides' keys through the same launches; and so
+// for small minibatches, whose keys are grouped in one launch.  With given coefficients that kernel needs the keys and the (small) input-side sort only: key
 // generation and output-side sort are queued on the shard's second stream, forked by an event, while
 // the caller's stream checks the inputs and sorts the input side; it then waits for the keys, and just
 // before the first kernel that reads the output-side order for that sort (*join, join_output_sort).
@@ -379,8 +393,9 @@ int queue_keys_and_sorts(w2v_shard* sh, Plan& p, const uint32_t* in_idx, const u
     *join = false;
 
     const NoiseTable nt{sh->bins, sh->V};
-    if (!sh->overlap || p.own_rows) {
-        // keys, checked inputs and both fills in one launch
+    const bool small = group_small(p.M, p.n);
+    if (!sh->overlap || p.own_rows || small) {
+        // keys, checked inputs and the fills in one launch
         const SortJob jobs[2] = {{p.keys, p.M, p.wb0, p.wb1, skw, sidx},
                                  {p.in_safe, p.n, p.ub0, p.ub1, sku, perm}};
         {
@@ -390,15 +405,14 @@ int queue_keys_and_sorts(w2v_shard* sh, Plan& p, const uint32_t* in_idx, const u
             pro.seed_lo = (uint32_t)seed; pro.seed_hi = (uint32_t)(seed >> 32);
             pro.keys = p.keys; pro.dev = sh->call_dev; pro.in_idx = in_idx; pro.in_safe = p.in_safe;
             pro.err = sh->err;
-            pro.fill[0] = sort_clear_job(jobs, 2, p.sort_tmp);
+            if (!small) pro.fill[0] = sort_clear_job(jobs, 2, p.sort_tmp);
             pro.fill[1] = wseg_fill_job(p.pb_keys, p.M);
             p.wfill_done = true;
             if (sh->prologue_sink) *sh->prologue_sink = pro;
             else launch_index_prologue(pro, st);
         }
         Phase ph(sh, W2V_PH_SORT, st);
-        launch_sort_jobs(jobs, 2, bits, p.sort_tmp, sh->err, st, true);
-        if (p.own_rows) launch_mark_alone(*skw, *sidx, p.M, p.keys, st);
+        sort_and_mark(jobs, bits, p.sort_tmp, sh->err, p.own_rows, true, &p.keys, st);
         return W2V_OK;
     }
     int rc = ensure_side_stream(sh);
@@ -455,13 +469,12 @@ int run_prefetch_chain(w2v_shard* sh, const Prepared& want, hipStream_t st) {
         pro.nt = NoiseTable{sh->bins, sh->V}; pro.out_idx = want.out_idx; pro.n = n; pro.T = k + 1;
         pro.seed_lo = (uint32_t)want.seed; pro.seed_hi = (uint32_t)(want.seed >> 32);
         pro.keys = x.keys; pro.in_idx = want.in_idx; pro.in_safe = x.in_safe; pro.err = sh->err;
-        pro.fill[0] = sort_clear_job(jobs, 2, x.sort_tmp);
+        if (!group_small(M, n)) pro.fill[0] = sort_clear_job(jobs, 2, x.sort_tmp);
         launch_index_prologue(pro, side);
     }
     {
         Phase ph(sh, W2V_PH_SORT, side);
-        launch_sort_jobs(jobs, 2, bits, x.sort_tmp, sh->err, side, true);
-        if (marks) launch_mark_alone(x.skw, x.sidx, M, x.keys, side);
+        sort_and_mark(jobs, bits, x.sort_tmp, sh->err, marks, true, &x.keys, side);
     }
     HIP_TRY(hipEventRecord(x.ready, side));
     HIP_TRY(hipGetLastError());
@@ -1328,8 +1341,7 @@ int queue_cbow_indices(w2v_shard* sh, CbowPlan& p, const uint32_t* ctx_off, cons
         if (cbow_small(p)) {
             const SortJob jobs[2] = {{p.keys, p.M, p.wb0, p.wb1, skw, sidx},
                                      {p.ctx_safe, p.m, p.cb0, p.cb1, skc, cidx}};
-            launch_sort_jobs(jobs, 2, bits, p.sort_tmp_w, sh->err, st);
-            if (p.own_rows) launch_mark_alone(*skw, *sidx, p.M, p.keys, st);
+            sort_and_mark(jobs, bits, p.sort_tmp_w, sh->err, p.own_rows, false, &p.keys, st);
             return W2V_OK;
         }
         launch_sort_pairs(p.keys, p.wb0, p.wb1, p.M, bits, p.sort_tmp_w, skw, sidx, sh->err, wst);
@@ -1464,8 +1476,7 @@ int run_cbow_prefetch_chain(w2v_shard* sh, const CbowPrepared& want, hipStream_t
         Phase ph(sh, W2V_PH_SORT, ah);
         const SortJob jobs[2] = {{x.keys, M, x.wb0, x.wb1, &x.skw, &x.sidx},
                                  {x.ctx_safe, m, x.cb0, x.cb1, &x.skc, &x.cidx}};
-        launch_sort_jobs(jobs, 2, bits, x.sort_tmp, sh->err, ah);
-        if (sh->own_rows) launch_mark_alone(x.skw, x.sidx, M, x.keys, ah);
+        sort_and_mark(jobs, bits, x.sort_tmp, sh->err, sh->own_rows, false, &x.keys, ah);
     }
     HIP_TRY(hipEventRecord(x.ready, ah));
     HIP_TRY(hipGetLastError());

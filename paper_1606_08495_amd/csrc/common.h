@@ -127,6 +127,12 @@ void launch_sort_pairs(const uint32_t* keys_in, uint2* buf0, uint2* buf1, uint32
                        uint32_t* tmp, uint32_t** out_keys, uint32_t** out_vals, uint32_t* err,
                        hipStream_t st);
 
+// One or two small arrays in one launch and without scratch: equal keys adjacent, slots in increasing order
+// among them, keys in no particular order.  Keys and slots end up in buf0 as above; marked0 (may be null, not
+// in buf0): the keys of the first array in slot order, with KEY_ALONE on those that occur once.
+bool group_small(uint32_t n0, uint32_t n1);      // whether arrays of n0 and n1 keys are taken that way
+void launch_group_jobs(const SortJob* jobs, int njobs, uint32_t bits, uint32_t* marked0, hipStream_t st);
+
 // Exclusive prefix sum of many uint32 whose sums per scan_tile() consecutive elements are known: the sums
 // are scanned in place (scan_scratch_u32(n) of them; total may be null; a second array of as many rides
 // along), then out[i] = exclusive prefix of in[i] >> shift.

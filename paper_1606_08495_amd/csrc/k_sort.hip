@@ -459,4 +459,283 @@ void launch_sort_pairs(const uint32_t* keys_in, uint2* buf0, uint2* buf1, uint32
     launch_sort_jobs(&job, 1, bits, tmp, err, st);
 }
 
+// ---------------------------------------------------------------------------------------------
+// Small arrays: equal keys brought together in ONE launch.  A block owns a bucket of keys (a fold of the
+// key's bits: word numbers are frequency ranks, so frequent words spread over the buckets).  It reads ALL
+// keys of its array -- a few hundred kilobytes, out of the caches --, lists the slots of its own in order and
+// counts the keys of lower buckets, which is where its stretch of the output begins: no block waits for
+// another.  The list is then sorted by key, slots in increasing order among equal keys: up to GS_PAIRWISE
+// elements by counting each one's place against all others, more digit by digit in LDS.  The output is in
+// bucket order, then key order: all that the update needs is that equal keys are adjacent.
+// Each wavefront lists its stretch of the keys, at most GS_SUB of them.  Where one finds more (a very frequent
+// word), the key in the middle of that wavefront's list is written out by itself and the rest listed anew.
+// Bound by latency: a launch, three memory round trips, the fetch of its code -- hence loops that are
+// not unrolled (with the keys held in registers and everything unrolled, 8 kB of straight code, it took 18 us
+// for 28 672 keys, 13.7 this way).
+// ---------------------------------------------------------------------------------------------
+constexpr int GS_THREADS = 1024, GS_WAVES = GS_THREADS / 64;
+constexpr uint32_t GS_MOST = 1u << 16;               // keys of one array (slots fit 16 bits)
+constexpr uint32_t GS_PAIRWISE = 256;
+constexpr uint32_t GS_SUB = 512;                     // list entries of a wavefront
+constexpr uint32_t GS_LIST = GS_WAVES * GS_SUB;
+constexpr int GS_LIST_ITEMS = GS_LIST / GS_THREADS;
+constexpr int GS_QUADS = 2;                          // four keys of a lane each, per step
+constexpr uint32_t GS_STEP = GS_QUADS * 256;         // keys of a wavefront's step
+
+struct GroupJobDev {
+    const uint32_t* keys; uint32_t n; uint32_t* out_keys; uint32_t* out_vals;    // keys: 16-byte aligned, readable up to a multiple of four
+    uint32_t* marked;            // optional: the keys in slot order, KEY_ALONE on those that occur once
+    uint32_t fold;               // log2 of the buckets
+    uint32_t passes, width;      // of the bits above `fold`, digits of the same width
+};
+struct GroupArgs { GroupJobDev job[2]; uint32_t blocks0; };
+
+// bucket of a key; one above 2^31 (no key: KEY_NONE) lies past every bucket
+__host__ __device__ inline uint32_t group_bucket(uint32_t k, uint32_t fold) {
+    return (k ^ (k >> fold) ^ (k >> (2 * fold))) & (((1u << fold) - 1u) | 0x80000000u);
+}
+
+// The block's wavefronts' values (LDS, 16-byte aligned): their sum, and that of those before this one.
+__device__ __forceinline__ void wave_sums_of(const uint32_t* s_part, int wave, uint32_t& before, uint32_t& all) {
+    before = all = 0;
+#pragma unroll
+    for (int w = 0; w < GS_WAVES; w += 4) {
+        const uint4 q = *reinterpret_cast<const uint4*>(s_part + w);
+        const uint32_t v[4] = {q.x, q.y, q.z, q.w};
+#pragma unroll
+        for (int t = 0; t < 4; ++t) { before += w + t < wave ? v[t] : 0u; all += v[t]; }
+    }
+}
+
+// (64 registers, two blocks to a compute unit)
+__global__ __launch_bounds__(GS_THREADS, 8) void group_small_kernel(GroupArgs a) {
+    __shared__ __align__(16) uint32_t s_key[GS_LIST];
+    __shared__ uint16_t s_val[GS_LIST];
+    union Tables {
+        struct { uint16_t slot[GS_WAVES][GS_SUB]; } sub;      // the wavefronts' lists
+        uint32_t cnt[GS_WAVES][256];                          // once they are joined: digit counts
+    };
+    __shared__ Tables lds;
+    __shared__ uint64_t s_done[GS_MOST / 64];                 // slots written out already, a bit each
+    __shared__ __align__(16) uint32_t s_part[GS_WAVES], s_low[GS_WAVES];
+    __shared__ uint32_t wave_sums[4], total_all;
+    auto& s_sub = lds.sub.slot; auto& cnt = lds.cnt;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const bool second = blockIdx.x >= a.blocks0;
+    const GroupJobDev& jb = a.job[second ? 1 : 0];
+    const uint32_t bucket = blockIdx.x - (second ? a.blocks0 : 0u), n = jb.n, fold = jb.fold;
+    const uint32_t* __restrict__ keys = jb.keys;
+    const uint64_t below = (1ull << lane) - 1ull;
+    const uint32_t steps = (n + GS_STEP - 1) / GS_STEP;      // wavefront w takes steps w steps / 16 .. (w + 1) steps / 16
+    const uint32_t first = wave * steps / GS_WAVES, last = (wave + 1) * steps / GS_WAVES;
+    bool again = false;                                       // some keys are written out already
+    uint32_t start = 0;
+    for (;;) {
+        uint32_t lower = 0, mine = 0;
+        uint4 x[GS_QUADS], nx[GS_QUADS];
+        auto fetch = [&](uint4 (&r)[GS_QUADS], uint32_t step) {
+#pragma unroll
+            for (int u = 0; u < GS_QUADS; ++u) {
+                const uint32_t i = step * GS_STEP + u * 256 + lane * 4;
+                r[u] = make_uint4(KEY_NONE, KEY_NONE, KEY_NONE, KEY_NONE);
+                if (step < last && i < n) r[u] = *reinterpret_cast<const uint4*>(keys + i);
+            }
+        };
+        fetch(x, first);
+        fetch(nx, first + 1);
+#pragma unroll 1
+        for (uint32_t step = first; step < last; ++step) {
+            uint32_t bits = 0;                                // bit 4 u + t: this lane's key t of quad u is of the bucket
+#pragma unroll
+            for (int u = 0; u < GS_QUADS; ++u) {
+                const uint32_t k[4] = {x[u].x, x[u].y, x[u].z, x[u].w}, i = step * GS_STEP + u * 256 + lane * 4;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const uint32_t b = i + t < n ? group_bucket(k[t], fold) : KEY_NONE;
+                    lower += (uint32_t)__popcll(__ballot(b < bucket));
+                    bits |= b == bucket ? 1u << (4 * u + t) : 0u;
+                }
+                x[u] = nx[u];
+            }
+            fetch(nx, step + 2);
+            if (__ballot(bits != 0) == 0) continue;           // uniform per wavefront
+#pragma unroll 1
+            for (int u = 0; u < GS_QUADS; ++u) {
+                const uint32_t i = step * GS_STEP + u * 256 + lane * 4;
+                uint32_t own = (bits >> (4 * u)) & 15u;
+                if (again && own) own &= ~(uint32_t)(s_done[i / 64] >> (i % 64));
+                const uint32_t c = (uint32_t)__popc(own);
+                const uint64_t m0 = __ballot(c & 1u), m1 = __ballot(c & 2u), m2 = __ballot(c & 4u);
+                uint32_t at = mine + (uint32_t)__popcll(m0 & below) + 2 * (uint32_t)__popcll(m1 & below) + 4 * (uint32_t)__popcll(m2 & below);
+                for (; own; own &= own - 1, ++at)
+                    if (at < GS_SUB) s_sub[wave][at] = (uint16_t)(i + __builtin_ctz(own));
+                mine += (uint32_t)__popcll(m0) + 2 * (uint32_t)__popcll(m1) + 4 * (uint32_t)__popcll(m2);
+            }
+        }
+        if (lane == 0) { s_part[wave] = mine; s_low[wave] = lower; }
+        __syncthreads();
+        uint32_t before, count, lower_all, unused, most = 0, most_at = 0;
+        wave_sums_of(s_part, wave, before, count);
+        wave_sums_of(s_low, wave, unused, lower_all);
+#pragma unroll
+        for (int w = 0; w < GS_WAVES; ++w)
+            if (s_part[w] > most) { most = s_part[w]; most_at = w; }
+        if (!again) start = lower_all;
+        if (count == 0) return;                               // (all of these are the same in every thread)
+        if (most <= GS_SUB) {
+            for (uint32_t i = lane; i < mine; i += 64) {
+                const uint16_t slot = s_sub[wave][i];
+                s_val[before + i] = slot;
+                s_key[before + i] = keys[slot];
+            }
+            if (threadIdx.x < 4 && count + threadIdx.x < GS_LIST) s_key[count + threadIdx.x] = KEY_NONE;   // (above every key)
+            __syncthreads();                                  // (the lists are read: their place is free)
+            if (count <= GS_PAIRWISE) {                       // four threads an element
+                const uint32_t i = threadIdx.x / 4;
+                if (i >= count) return;
+                const uint32_t k = s_key[i];
+                uint32_t place = 0, equal = 0;
+#pragma unroll 1
+                for (uint32_t j = 4 * (threadIdx.x % 4); j < count; j += 16) {
+                    const uint4 y = *reinterpret_cast<const uint4*>(&s_key[j]);
+                    const uint32_t o[4] = {y.x, y.y, y.z, y.w};
+#pragma unroll
+                    for (int t = 0; t < 4; ++t) {
+                        place += o[t] < k || (o[t] == k && j + t < i) ? 1u : 0u;
+                        equal += o[t] == k ? 1u : 0u;
+                    }
+                }
+                place += __shfl_xor(place, 1, 64); equal += __shfl_xor(equal, 1, 64);
+                place += __shfl_xor(place, 2, 64); equal += __shfl_xor(equal, 2, 64);
+                if (threadIdx.x % 4) return;
+                const uint32_t slot = s_val[i];
+                jb.out_keys[start + place] = k; jb.out_vals[start + place] = slot;
+                if (jb.marked) jb.marked[slot] = equal == 1 ? k | KEY_ALONE : k;
+                return;
+            }
+            // Digit by digit (the bucket and the bits above `fold` fix the rest).  Element e of lane l of wave w is
+            // number (w items + e) 64 + l of the list.
+            const uint32_t items = (count + GS_THREADS - 1) / GS_THREADS;
+#pragma unroll 1
+            for (uint32_t p = 0; p < jb.passes; ++p) {
+                const uint32_t shift = fold + p * jb.width, dmask = (1u << jb.width) - 1u;
+                for (int i = threadIdx.x; i < GS_WAVES * 256; i += GS_THREADS) (&cnt[0][0])[i] = 0;
+                __syncthreads();
+                uint32_t k[GS_LIST_ITEMS], v[GS_LIST_ITEMS], rank[GS_LIST_ITEMS];
+#pragma unroll
+                for (int e = 0; e < GS_LIST_ITEMS; ++e) {
+                    if ((uint32_t)e >= items) continue;       // uniform
+                    const uint32_t i = (wave * items + e) * 64 + lane;
+                    const bool valid = i < count;
+                    k[e] = valid ? s_key[i] : 0u; v[e] = valid ? s_val[i] : 0u;
+                    const uint32_t d = (k[e] >> shift) & dmask;
+                    uint64_t same = __ballot(valid);
+#pragma unroll 1
+                    for (uint32_t b = 0; b < jb.width; ++b) {
+                        const uint64_t bal = __ballot((d >> b) & 1u);
+                        same &= ((d >> b) & 1u) ? bal : ~bal;
+                    }
+                    rank[e] = 0;
+                    uint32_t seen = 0;
+                    if (valid) { seen = cnt[wave][d]; rank[e] = seen + (uint32_t)__popcll(same & below); }
+                    // (every lane's read above is issued before the leader's write below: one instruction stream)
+                    if (valid && (same & below) == 0) cnt[wave][d] = seen + (uint32_t)__popcll(same);
+                }
+                __syncthreads();
+                uint32_t digit_count = 0;
+                if (threadIdx.x < 256) {
+#pragma unroll 4
+                    for (int w = 0; w < GS_WAVES; ++w) digit_count += cnt[w][threadIdx.x];
+                }
+                uint32_t run = block_exclusive_scan(digit_count, wave_sums, &total_all);
+                if (threadIdx.x < 256) {
+#pragma unroll 4
+                    for (int w = 0; w < GS_WAVES; ++w) {
+                        const uint32_t c = cnt[w][threadIdx.x];
+                        cnt[w][threadIdx.x] = run;
+                        run += c;
+                    }
+                }
+                __syncthreads();
+#pragma unroll
+                for (int e = 0; e < GS_LIST_ITEMS; ++e) {
+                    if ((uint32_t)e >= items) continue;
+                    if ((wave * items + e) * 64 + lane < count) {
+                        const uint32_t pos = cnt[wave][(k[e] >> shift) & dmask] + rank[e];
+                        s_key[pos] = k[e]; s_val[pos] = (uint16_t)v[e];
+                    }
+                }
+                __syncthreads();
+            }
+            for (uint32_t i = threadIdx.x; i < count; i += GS_THREADS) {
+                const uint32_t k = s_key[i], slot = s_val[i];
+                jb.out_keys[start + i] = k; jb.out_vals[start + i] = slot;
+                const bool lone = (i == 0 || s_key[i - 1] != k) && (i + 1 == count || s_key[i + 1] != k);
+                if (jb.marked) jb.marked[slot] = lone ? k | KEY_ALONE : k;
+            }
+            return;
+        }
+        // one key by itself: lane r of a wavefront keeps the slots of its r-th 64 keys
+        static_assert(GS_MOST / GS_WAVES <= 64 * 64, "a lane for every 64 keys of a wavefront");
+        const uint32_t pick = keys[s_sub[most_at][GS_SUB / 2]];
+        const uint32_t lo = first * GS_STEP, hi = min(last * GS_STEP, n);
+        uint64_t own = 0;
+#pragma unroll 8
+        for (uint32_t i0 = lo; i0 < hi; i0 += 64) {
+            const uint64_t m = __ballot(i0 + lane < hi && keys[min(i0 + lane, n - 1)] == pick);
+            if ((uint32_t)lane == (i0 - lo) / 64) own = m;
+        }
+        const uint32_t c = (uint32_t)__popcll(own);
+        uint32_t incl = c;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t y = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += y;
+        }
+        __syncthreads();                                      // (the counts and lists above are read)
+        if (lane == 63) s_part[wave] = incl;
+        __syncthreads();
+        uint32_t all;
+        wave_sums_of(s_part, wave, before, all);
+        const uint32_t slot0 = lo + (uint32_t)lane * 64;
+        if (slot0 < hi) s_done[slot0 / 64] = again ? s_done[slot0 / 64] | own : own;
+        for (uint32_t at = start + before + incl - c; own; own &= own - 1, ++at) {
+            const uint32_t slot = slot0 + (uint32_t)__builtin_ctzll(own);
+            jb.out_keys[at] = pick; jb.out_vals[at] = slot;
+            if (jb.marked) jb.marked[slot] = all == 1 ? pick | KEY_ALONE : pick;
+        }
+        start += all;
+        again = true;
+        __syncthreads();                                      // (s_done is written, s_part read)
+    }
+}
+
+// Up to 80 000 keys in all (a step of d = 100 in us, radix sort and marks and this way; k = 5: 500 pairs 70, 46; 4096 81, 64;
+// 10 900 96, 80; k = 1, 30 000 pairs, a skewed vocabulary: 104, 102, and with d = 300 131, 139).
+bool group_small(uint32_t n0, uint32_t n1) { return std::max(n0, n1) <= GS_MOST && n0 + n1 <= 80000u; }
+
+// Buckets of an array: about a hundred keys each, a power of two, at least 2^4 (three times that many bits are folded
+// into the bucket's number, which then covers any frequent word) and at most 2^8.
+static uint32_t group_fold(uint32_t n) {
+    uint32_t f = 4;
+    while (f < 8 && (96u << f) < n) ++f;
+    return f;
+}
+
+void launch_group_jobs(const SortJob* jobs, int njobs, uint32_t bits, uint32_t* marked0, hipStream_t st) {
+    GroupArgs a{};
+    uint32_t blocks = 0;
+    for (int i = 0; i < njobs && i < 2; ++i) {
+        const SortJob& j = jobs[i];
+        *j.out_keys = (uint32_t*)j.buf0;
+        *j.out_vals = (uint32_t*)j.buf0 + j.n;
+        const uint32_t fold = group_fold(j.n), above = bits > fold ? bits - fold : 1;
+        const uint32_t passes = (above + 7) / 8, width = (above + passes - 1) / passes;
+        a.job[i] = GroupJobDev{j.keys_in, j.n, *j.out_keys, *j.out_vals, i == 0 ? marked0 : nullptr, fold, passes, width};
+        blocks += j.n ? 1u << fold : 0u;
+        if (i == 0) a.blocks0 = blocks;
+    }
+    if (blocks) hipLaunchKernelGGL(group_small_kernel, dim3(blocks), dim3(GS_THREADS), 0, st, a);
+}
+
 }  // namespace w2v

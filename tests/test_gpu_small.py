@@ -1,0 +1,58 @@
+"""Small minibatches: keys grouped by one launch (up to 65 536 of either side, 80 000 in all), against the oracle,
+at the sizes and vocabularies where the grouping takes another way, in every form that a step has."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from paper_1606_08495_amd import w2v, workloads
+from util import all_rows, dev, vec_error
+
+pytestmark = pytest.mark.gpu
+
+
+def words(V, skew, n, rng):
+    return workloads.zipf_draw(workloads.zipf_cdf(V, skew), n, rng)
+
+
+# (V, skew, n, k): places counted pairwise (up to 256 keys a bucket), digit by digit, keys written out by themselves
+# (more than 512 of a bucket in a wavefront's stretch), both sides of the lines to the radix sort, single keys
+SHAPES = [(100_000, 1.0, 1999, 5), (100_000, 1.0, 10_922, 5), (100_000, 1.0, 10_923, 5), (3000, 1.2, 10_000, 5),
+          (300, 1.5, 9000, 6), (2, 1.0, 10_922, 5), (5, 0.5, 26_666, 1), (5, 0.5, 26_667, 1), (70, 3.0, 40_000, 0), (70, 3.0, 40_001, 0),
+          (40_000, 1.2, 20_000, 2), (1000, 1.0, 1, 0), (1000, 1.0, 97, 1), (65_537, 0.0, 8192, 7)]
+
+
+@pytest.mark.parametrize("V,skew,n,k", SHAPES)
+def test_small_minibatch_in_every_form(V, skew, n, k):
+    print("small", V, skew, n, k, flush=True)
+    d, seed = 8, 77
+    rng = np.random.default_rng(n + k)
+    counts = workloads.analytic_counts(V, skew, 10 ** 7)
+    th, al = oracle.build_alias(counts)
+    a, b = words(V, skew, n, rng), words(V, skew, n, rng)
+    alpha = float(min(0.05, 0.2 / max(1, np.bincount(b, minlength=V).max() * (k + 1), np.bincount(a, minlength=V).max() * (k + 1))))
+    rows = np.arange(V, dtype=np.uint32)
+    U, W = oracle.init_rows(3, d, 0, d, 0, rows), oracle.init_rows(3, d, 0, d, 1, rows)
+    oracle.train_minibatch([U], [W], a, b, k, seed, th, al, alpha)
+    da, db = dev(a), dev(b)
+    got = {}
+    for form in ("plain", "announced", "captured", "two calls"):
+        sh = w2v.Shard(V, d, 3, init_mode=1)
+        sh.set_counts(counts)
+        if form in ("announced", "two calls"):
+            sh.prefetch_minibatch(da, db, k, seed)
+        if form == "captured":
+            w2v.StepGraph(sh, n, k).run(da, db, seed, alpha)
+        elif form == "two calls":
+            f = sh.dotprod(da, db, k, seed)
+            sh.adjust(da, db, k, seed, sh.coeffs([f], k), alpha)
+        else:
+            w2v.train_minibatch([sh], da, db, k, seed, alpha)
+        sh.status()
+        got[form] = (all_rows(sh, 0), all_rows(sh, 1))
+        # a minibatch's bound (1e-5 of a row's largest component)
+        assert vec_error(got[form][0], U) <= 1e-5 and vec_error(got[form][1], W) <= 1e-5, form
+        torch.cuda.synchronize()
+        sh.destroy()
+    for form in ("announced", "captured"):
+        assert np.array_equal(got[form][0], got["plain"][0]) and np.array_equal(got[form][1], got["plain"][1]), form
