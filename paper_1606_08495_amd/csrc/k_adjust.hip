@@ -734,6 +734,29 @@ void launch_adjust_stage(const AdjustStage& x, hipStream_t st) {
 // when it is small.
 __device__ __forceinline__ float sigmoid_of_minus(float x) { return 1.0f / (1.0f + expf(x)); }
 
+// Coefficients of up to sixteen slots whose dots every lane holds, j0 the number of the first: lane r of every sixteen
+// takes slot r, so that the exponential and the division are issued once for all of them, and the results are
+// handed round.  `dot` and `g` are this lane's own slot's, for the stores.  (The row kernels are bound by what they
+// issue nearly as much as by memory: evaluated slot after slot in every lane, k = 25, d = 200, two steps of 2^18
+// pairs 4450 us, this way 4216; k = 10, d = 60, 2^20 pairs 4490, 4320; k = 5, d = 100, four of 65 536 715, 694.)
+template <int G, int N>
+__device__ __forceinline__ void coefficients(const float (&sdot)[N], uint32_t j0, float (&gco)[N], float& dot, float& g) {
+    static_assert(N <= 16, "a lane per slot");
+    const int r = threadIdx.x & 15;
+    dot = sdot[0];
+#pragma unroll
+    for (int j = 1; j < N; ++j) dot = r == j ? sdot[j] : dot;
+    const bool positive = j0 + r == 0;
+    const float s = sigmoid_of_minus(positive ? dot : -dot);
+    g = positive ? s : -s;
+    if constexpr (G == 64) {                     // (the wavefront's: scalars)
+#pragma unroll
+        for (int j = 0; j < N; ++j) gco[j] = lane_value(g, j);
+    } else {
+        share16<0>(g, gco);
+    }
+}
+
 
 template <int G, int NV, int TB, bool FUSED, bool OWN>
 __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_t CP) {
@@ -814,21 +837,15 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
             const uint32_t njb = last_batch ? 0u : jb + TB;
             float gco[TB];
             if (FUSED) {
-                float sdot[TB];
+                float sdot[TB], f, g;
 #pragma unroll
                 for (int t = 0; t < TB; ++t) sdot[t] = dot_part<NV>(u, w[t]);
 #pragma unroll
                 for (int t = 0; t < TB; ++t) sdot[t] = group_sum<G>(sdot[t]);
-#pragma unroll
-                for (int t = 0; t < TB; ++t) {
-                    uint32_t j = jb + t;
-                    float f = sdot[t];
-                    const float gc = (j == 0) ? sigmoid_of_minus(f) : -sigmoid_of_minus(-f);
-                    gco[t] = (j < T) ? gc : 0.f;
-                    if (l == t && j < T) {
-                        a.coeffs_out[p * T + j] = gc;
-                        if (a.dots_out) a.dots_out[p * T + j] = f;
-                    }
+                coefficients<G>(sdot, jb, gco, f, g);
+                if (l < TB && jb + l < T) {
+                    a.coeffs_out[p * T + jb + l] = g;
+                    if (a.dots_out) a.dots_out[p * T + jb + l] = f;
                 }
             } else {
 #pragma unroll
@@ -989,19 +1006,15 @@ __global__ __launch_bounds__(USEG_THREADS, 5) void useg_multi_kernel(USideArgs a
                 if (l == 0) a.dkey[ps] = KEY_NONE;
                 float gco[T];
                 if (FUSED) {
-                    float sdot[T];
+                    float sdot[T], f, g;
 #pragma unroll
                     for (int j = 0; j < T; ++j) sdot[j] = dot_part<NV>(u[b], w[b][j]);
 #pragma unroll
                     for (int j = 0; j < T; ++j) sdot[j] = group_sum<G>(sdot[j]);
-#pragma unroll
-                    for (int j = 0; j < T; ++j) {
-                        const float f = sdot[j];
-                        gco[j] = (j == 0) ? sigmoid_of_minus(f) : -sigmoid_of_minus(-f);
-                        if (l == j % G) {
-                            a.coeffs_out[p * T + j] = gco[j];
-                            if (a.dots_out) a.dots_out[p * T + j] = f;
-                        }
+                    coefficients<G>(sdot, 0, gco, f, g);
+                    if (l < T) {
+                        a.coeffs_out[p * T + l] = g;
+                        if (a.dots_out) a.dots_out[p * T + l] = f;
                     }
                 } else {
 #pragma unroll

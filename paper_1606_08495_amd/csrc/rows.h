@@ -117,6 +117,15 @@ __device__ __forceinline__ float row16_sum(float x) {
     return x;
 }
 
+// out[j] = the value of lane j of this lane's sixteen
+template <int J, int N>
+__device__ __forceinline__ void share16(float x, float (&out)[N]) {
+    if constexpr (J < N) {
+        out[J] = dpp_move<0x150 + J>(x);      // row_newbcast:J
+        share16<J + 1>(x, out);
+    }
+}
+
 __device__ __forceinline__ float lane_value(float x, int lane) {
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, x), lane));
 }
