@@ -256,6 +256,12 @@ uint32_t key_bits(uint32_t V) {
     return bits;
 }
 
+// Float4 from row to row: see w2v_shard_create_ex.
+uint32_t row_stride4(uint32_t d4) {
+    const uint32_t padded = (d4 + 7) / 8 * 8;
+    return (padded - d4) * 8 <= d4 ? padded : d4;
+}
+
 // Everything one minibatch needs in scratch, carved in a fixed order.  Every part grows with n and k, so
 // a smaller minibatch fits the scratch of a larger one.
 struct Plan {
@@ -313,7 +319,7 @@ void run_tails(w2v_shard* sh, float* M, float alpha, float* rows_a, uint32_t* ke
     float* src_rows = rows_a; uint32_t* src_keys = keys_a;
     float* dst_rows = rows_b; uint32_t* dst_keys = keys_b;
     while (slots > 0) {
-        launch_tail(TailArgs{M, sh->g, alpha, src_rows, src_keys, slots, dst_rows, dst_keys}, st);
+        launch_tail(TailArgs{M, nullptr, sh->g, alpha, src_rows, src_keys, slots, dst_rows, dst_keys}, st);
         slots = slots_after(slots, tail_entries_per_chunk(sh->g.d4));
         std::swap(src_rows, dst_rows);
         std::swap(src_keys, dst_keys);
@@ -506,19 +512,22 @@ void join_output_sort(w2v_shard* sh, hipStream_t st) {
     if (sh->overlap && sh->side) (void)hipStreamWaitEvent(st, sh->ev_join, 0);
 }
 
-// The update of one shard from given coefficients (or, fused, from its own dots; loss_out: fused form
+// What an update writes to: one shard's matrices, or (fused only) those of several side by side.
+struct Target { float* U; float* W; const Slices* slices; RowGeom g; };
+
+// The update of one target from given coefficients (or, fused, from its own dots; loss_out: fused form
 // only).  The input-side kernel first (it also clears the output side's border slots, unless the call's
 // first launch has: good for one shard's update); then launches that each carry one walk of the output
 // side together with one higher level of the input side and one step of the loss, which depend on
 // different things.  The input side's levels park their sums in the delta buffer, which is written back
 // beside the first output-side level after they are done (and after the level-1 walk, which reads U).
 // `join_sorts`: the output-side order comes from the shard's second stream.
-void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* sku,
+void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t* sku,
                   const uint32_t* perm, const uint32_t* skw, const uint32_t* sidx,
                   const float* coeffs_in, float* coeffs_out, bool fused, float alpha,
                   double* loss_out, bool join_sorts, hipStream_t st) {
     const CallScalars* dev = ws_owner->call_dev;
-    const bool alone = adjust_walk_alone(p.M, sh->g);
+    const bool alone = adjust_walk_alone(p.M, to.g);
     // From 2^22 slots on the kernels after the output side's walk are bound by memory, shared with each other
     // and with the sorts of an announced minibatch, and not by their own chain of latencies: they take small
     // blocks and few rows in flight (`shared`).  Benchmark step (6.3 M slots) 3.201 -> 3.185 ms; at 1.2 M
@@ -534,11 +543,11 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
     {
         Phase ph(ws_owner, W2V_PH_USIDE, st);
         USideArgs a{};
-        a.U = sh->U; a.W = sh->W; a.g = sh->g; a.skey = sku; a.perm = perm; a.keys = p.keys;
+        a.U = to.U; a.W = to.W; a.slices = to.slices; a.g = to.g; a.skey = sku; a.perm = perm; a.keys = p.keys;
         a.n = p.n; a.T = p.T; a.coeffs_in = coeffs_in; a.coeffs_out = coeffs_out;
         a.dots_out = (fused && loss_out) ? p.dots : nullptr; a.delta = p.delta; a.dkey = p.dkey;
         a.prows = p.pa_rows; a.pkeys = p.pa_keys; a.fused = fused;
-        if (p.own_rows) { a.W_update = sh->W; a.alpha = alpha; }
+        a.own_rows = p.own_rows; a.alpha = alpha;
         a.dev = dev;
         if (!p.wfill_done) {
             const FillJob f = wseg_fill_job(p.pb_keys, p.M);
@@ -548,30 +557,30 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
         launch_useg(a, st);
     }
     if (join_sorts) join_output_sort(ws_owner, st);
-    const uint32_t cp = useg_pairs_per_chunk(p.T, sh->g.d4, p.n);      // this shard's chunk size
+    const uint32_t cp = useg_pairs_per_chunk(p.T, to.g.d4, p.n);      // this shard's chunk size
     struct Side { float* src_rows; uint32_t* src_keys; float* dst_rows; uint32_t* dst_keys; uint32_t slots, level; };
     Side us{p.pa_rows, p.pa_keys, p.pe_rows, p.pe_keys, slots_after(p.n, cp), 0u};
     Side ws{p.pb_rows, p.pb_keys, p.pc_rows, p.pc_keys, p.slots_w1, 0u};
     uint32_t loss_step = (loss_out && fused) ? 1u : 0u;
     bool applied = false;
     auto advance = [&](Side& x) {
-        x.slots = slots_after(x.slots, tail_entries_per_chunk(sh->g.d4));
+        x.slots = slots_after(x.slots, tail_entries_per_chunk(to.g.d4));
         std::swap(x.src_rows, x.dst_rows);
         std::swap(x.src_keys, x.dst_keys);
     };
     auto input_level = [&]() {
-        TailArgs t{sh->U, sh->g, alpha, us.src_rows, us.src_keys, us.slots, us.dst_rows, us.dst_keys};
+        TailArgs t{to.U, to.slices, to.g, alpha, us.src_rows, us.src_keys, us.slots, us.dst_rows, us.dst_keys};
         t.defer_rows = p.delta; t.defer_keys = p.dkey; t.level = ++us.level; t.cp = cp; t.dev = dev;
         return t;
     };
     auto w_level = [&]() {
-        TailArgs t{sh->W, sh->g, alpha, ws.src_rows, ws.src_keys, ws.slots, ws.dst_rows, ws.dst_keys};
+        TailArgs t{to.W, to.slices, to.g, alpha, ws.src_rows, ws.src_keys, ws.slots, ws.dst_rows, ws.dst_keys};
         t.level = ++ws.level; t.dev = dev;
         return t;
     };
-    const ApplyDelta apply{sh->U, p.delta, p.dkey, p.n, alpha, dev};
+    const ApplyDelta apply{to.U, to.slices, p.delta, p.dkey, p.n, alpha, dev};
     WSideArgs w{};
-    w.U = sh->U; w.W = sh->W; w.g = sh->g; w.skey = skw; w.sidx = sidx; w.M = p.M; w.T = p.T;
+    w.U = to.U; w.W = to.W; w.slices = to.slices; w.g = to.g; w.skey = skw; w.sidx = sidx; w.M = p.M; w.T = p.T;
     w.in_idx = p.in_safe; w.coeffs = fused ? coeffs_out : coeffs_in; w.alpha = alpha;
     w.prows = p.pb_rows; w.pkeys = p.pb_keys; w.skip_alone = p.own_rows; w.dev = dev;
     const bool two = alone && ws_owner->overlap && ensure_side_stream(ws_owner) == W2V_OK;
@@ -606,7 +615,7 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
         }
         {
             Phase ph(ws_owner, W2V_PH_APPLY, side);
-            launch_apply(apply, sh->g, shared, side);
+            launch_apply(apply, to.g, shared, side);
         }
         if (two) (void)hipEventRecord(ws_owner->ev_tails, side);
         {
@@ -622,7 +631,7 @@ void queue_adjust(w2v_shard* ws_owner, w2v_shard* sh, Plan& p, const uint32_t* s
     for (bool first = true, any = true; any; first = false) {
         Phase ph(ws_owner, first ? W2V_PH_WSIDE : W2V_PH_APPLY, st);
         AdjustStage x;
-        x.g = sh->g;
+        x.g = to.g; x.slices = to.slices;
         TailArgs wt{}, ut{};
         const bool higher = !first && ws.slots > 0, u_level = us.slots > 0;
         if (first) {
@@ -680,16 +689,11 @@ extern "C" int w2v_shard_create_ex(uint32_t V, uint32_t d_total, uint32_t col_be
     // multiple of 128 bytes when that adds at most an eighth (d = 60: +20 % gather rate; d = 300:
     // the benchmark step 2.8 % shorter for 6.7 % more memory; d = 200: 2 % for 12 %).
     // W2V_ROW_ALIGN_FLOATS overrides the granularity (for experiments).
-    uint32_t align4 = 1;                     // row stride granularity in float4
-    {
-        uint32_t padded = ((sh->g.d4 + 7) / 8) * 8;
-        if ((padded - sh->g.d4) * 8 <= sh->g.d4) align4 = 8;
-    }
+    sh->g.stride4 = row_stride4(sh->g.d4);
     if (const char* env = getenv("W2V_ROW_ALIGN_FLOATS")) {
         long v = atol(env);
-        if (v >= 4 && v <= 256 && (v % 4) == 0) align4 = (uint32_t)v / 4;
+        if (v >= 4 && v <= 256 && (v % 4) == 0) sh->g.stride4 = (sh->g.d4 + v / 4 - 1) / (v / 4) * (v / 4);
     }
-    sh->g.stride4 = ((sh->g.d4 + align4 - 1) / align4) * align4;
     if (const char* env = getenv("W2V_NO_OVERLAP")) sh->overlap = (atoi(env) == 0);
     if (const char* env = getenv("W2V_NO_OWN_ROWS")) sh->own_rows = (atoi(env) == 0);
 
@@ -1014,7 +1018,7 @@ extern "C" int w2v_adjust(w2v_shard* sh, const uint32_t* in_idx, const uint32_t*
         rc = queue_keys_and_sorts(sh, p, in_idx, out_idx, k, seed, &sku, &perm, &skw, &sidx, &join, st);
         if (rc) return rc;
     }
-    queue_adjust(sh, sh, p, sku, perm, skw, sidx, coeffs, nullptr, false, alpha, nullptr, join, st);
+    queue_adjust(sh, Target{sh->U, sh->W, nullptr, sh->g}, p, sku, perm, skw, sidx, coeffs, nullptr, false, alpha, nullptr, join, st);
     HIP_TRY(hipGetLastError());
     return W2V_OK;
 }
@@ -1022,6 +1026,28 @@ extern "C" int w2v_adjust(w2v_shard* sh, const uint32_t* in_idx, const uint32_t*
 // ---------------------------------------------------------------------------------------------
 // one client step
 // ---------------------------------------------------------------------------------------------
+// Several column shards of one process as one matrix of joint rows, so that a step is that of a single shard: a
+// pair's output rows are read once for its dots and its input side, and there is one set of launches.  Up to
+// 1024 floats in all, which a lane group holds.  (k = 5, five shards of 60 columns, 100 003 pairs, one shard after
+// the other 745 us a step, as one 502; two of 50, 3001 pairs 148, 60;
+// two of 150, 2^20 pairs 4830, 3580; five of 102 or 103, 50 003 pairs 740, 490; nothing measured was slower.)
+static bool take_as_one(w2v_shard* const* shards, uint32_t S, Slices* sl, RowGeom* g) {
+    if (S > SLICES_MAX) return false;
+    uint32_t at = 0;
+    for (uint32_t s = 0; s < S; ++s) {
+        for (uint32_t r = 0; r < s; ++r)
+            if (shards[r] == shards[s]) return false;            // (listed twice, it is updated twice, in order)
+        sl->first[s] = at; sl->d4[s] = shards[s]->g.d4; sl->stride4[s] = shards[s]->g.stride4;
+        sl->M[0][s] = shards[s]->U; sl->M[1][s] = shards[s]->W;
+        at += shards[s]->g.stride4;
+        if (at > W2V_D_MAX / 4) return false;
+    }
+    sl->count = S;
+    g->d4 = at;
+    g->stride4 = row_stride4(at);
+    return true;
+}
+
 extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const uint32_t* in_idx,
                                    const uint32_t* out_idx, uint32_t n, uint32_t k, uint64_t seed,
                                    float alpha, double* loss, void* stream) {
@@ -1046,13 +1072,25 @@ extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const u
         if (loss) launch_loss_from_dots(nullptr, 0, k + 1, nullptr, loss, st);
         return W2V_OK;
     }
-    const bool fused = (S == 1);
-    const uint32_t own = (fused && s0->own_rows) ? s0->V : 0u;
-    const uint32_t S_dots = fused ? (loss ? 1u : 0u) : S;    // fused: the dots are kept for the loss only
-    Plan sz = make_plan(nullptr, n, k, stride_max, S_dots, true, true, own);
+    Slices sl{};
+    Target to{s0->U, s0->W, nullptr, s0->g};
+    bool fused = (S == 1);
+    if (S > 1 && take_as_one(shards, S, &sl, &to.g)) { fused = true; to.slices = &sl; }
+    Plan sz{};
+    auto plan = [&](char* base) {
+        return make_plan(base, n, k, fused ? to.g.stride4 : stride_max,
+                         fused ? (loss ? 1u : 0u) : S,               // fused: the dots are kept for the loss only
+                         true, true, fused && s0->own_rows ? s0->V : 0u);
+    };
+    sz = plan(nullptr);
     rc = ensure_ws(s0, sz.bytes);
+    if (rc == W2V_ERR_ALLOC && S > 1 && fused) {          // (one shard after the other needs less scratch)
+        fused = false;
+        sz = plan(nullptr);
+        rc = ensure_ws(s0, sz.bytes);
+    }
     if (rc) return rc;
-    Plan p = make_plan(s0->ws, n, k, stride_max, S_dots, true, true, own);
+    Plan p = plan(s0->ws);
     uint32_t *sku, *perm, *skw, *sidx;
     bool join = false;
     // a set computed by w2v_prefetch_minibatch on shard 0 (every shard holds the same noise table)
@@ -1070,7 +1108,7 @@ extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const u
         if (rc) return rc;
     }
     if (fused) {
-        queue_adjust(s0, s0, p, sku, perm, skw, sidx, nullptr, p.coeffs, true, alpha, loss, join, st);
+        queue_adjust(s0, to, p, sku, perm, skw, sidx, nullptr, p.coeffs, true, alpha, loss, join, st);
     } else {
         PartialPtrs pp{};
         {
@@ -1086,7 +1124,7 @@ extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const u
             launch_coeffs(pp, S, n, p.T, p.coeffs, p.loss_tmp, loss, st);
         }
         for (uint32_t s = 0; s < S; ++s)
-            queue_adjust(s0, shards[s], p, sku, perm, skw, sidx, p.coeffs, nullptr, false, alpha, nullptr, join, st);
+            queue_adjust(s0, Target{shards[s]->U, shards[s]->W, nullptr, shards[s]->g}, p, sku, perm, skw, sidx, p.coeffs, nullptr, false, alpha, nullptr, join, st);
     }
     HIP_TRY(hipGetLastError());
     return W2V_OK;
@@ -1388,7 +1426,7 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
         a.n = p.n; a.T = p.T; a.coeffs_in = coeffs_in; a.coeffs_out = coeffs_out;
         a.dots_out = fused ? dots_out : nullptr; a.delta = p.E; a.dkey = p.dkey;
         a.prows = p.pa_rows; a.pkeys = p.pa_keys; a.fused = fused;
-        if (fused && p.own_rows) { a.W_update = sh->W; a.alpha = alpha; }   // source: the hidden vector
+        a.own_rows = fused && p.own_rows; a.alpha = alpha;                  // (source: the hidden vector)
         const FillJob f = wseg_fill_job(p.pb_keys, p.M);
         a.clear_keys = f.p; a.clear_count = f.count;
         launch_useg(a, st);

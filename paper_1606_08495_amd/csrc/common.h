@@ -44,6 +44,15 @@ struct RowGeom {
     uint32_t stride4;   // float4 between consecutive rows
 };
 
+// The matrices of column shards side by side: a joint row is the rows of all slices one after the other, whole
+// strides, slice s from float4 number first[s] on.  Rows in scratch (delta buffer, partial rows) are contiguous.
+constexpr uint32_t SLICES_MAX = 32;
+struct Slices {
+    uint32_t count;
+    uint32_t first[SLICES_MAX], d4[SLICES_MAX], stride4[SLICES_MAX];
+    float* M[2][SLICES_MAX];                  // input vectors, output vectors
+};
+
 constexpr uint32_t KEY_NONE = 0xFFFFFFFFu;   // "no destination" in partial-sum key arrays
 constexpr uint32_t KEY_ZERO = 0x80000000u;   // flag: slot belongs to the row but holds no data
 constexpr uint32_t KEY_MASK = 0x7FFFFFFFu;
@@ -169,6 +178,7 @@ uint32_t wseg_slots_most(uint32_t M);                    // output side
 // and uses those coefficients.
 struct USideArgs {
     const float* U; const float* W; RowGeom g;
+    const Slices* slices;        // fused only, optional: the matrices of several shards, instead of U, W and W_update
     const uint32_t* skey; const uint32_t* perm; const uint32_t* keys; uint32_t n; uint32_t T;
     const float* coeffs_in;      // unfused: coefficients to use
     float* coeffs_out;           // fused: coefficients written here [n][T]
@@ -176,10 +186,10 @@ struct USideArgs {
     float* delta; uint32_t* dkey;
     float* prows; uint32_t* pkeys;
     bool fused;
-    // fused only, optional (W_update != null): keys carrying KEY_ALONE name rows that no other slot
+    // fused only, optional (own_rows): keys carrying KEY_ALONE name rows that no other slot
     // of the minibatch names; the kernel then writes W[row] += alpha * g * u itself (nobody else
     // reads or writes that row in this minibatch) and the output side must leave those slots out.
-    float* W_update; float alpha;
+    bool own_rows; float alpha;
     const CallScalars* dev;      // optional: the learning rate is read from here
     uint32_t* clear_keys; uint32_t clear_count;   // words set to KEY_NONE on the way (wseg_fill_job)
 };
@@ -194,6 +204,7 @@ void launch_loss_from_dots(const float* dots, uint32_t n, uint32_t T, double* tm
 // inside a chunk; cut runs go to the partial slots.
 struct WSideArgs {
     const float* U; float* W; RowGeom g;
+    const Slices* slices;        // optional, instead of U and W
     const uint32_t* skey; const uint32_t* sidx; uint32_t M; uint32_t T;
     bool skip_alone;             // entries whose neighbours carry other keys are handled elsewhere
     const uint32_t* in_idx; const float* coeffs; float alpha;
@@ -208,7 +219,7 @@ void launch_wseg(const WSideArgs& a, hipStream_t st);
 // Higher levels (both sides): entries are partial rows src_rows[i] with destination src_keys[i]
 // (KEY_NONE = nothing, KEY_ZERO flag = belongs to the run but empty).
 struct TailArgs {
-    float* M; RowGeom g; float alpha;
+    float* M; const Slices* slices; RowGeom g; float alpha;      // slices (optional): instead of M, their output vectors
     const float* src_rows; const uint32_t* src_keys; uint32_t entries;
     float* prows; uint32_t* pkeys;
     // input side only (in a joint launch): finished sums go to the delta buffer (rows, keys) instead of
@@ -221,7 +232,7 @@ void launch_input_tail(const TailArgs& a, hipStream_t st);       // with defer_r
 
 // U[dkey[ps]] += alpha * delta[ps] wherever dkey[ps] != KEY_NONE.
 struct ApplyDelta {
-    float* U; const float* delta; const uint32_t* dkey; uint32_t n; float alpha;
+    float* U; const Slices* slices; const float* delta; const uint32_t* dkey; uint32_t n; float alpha;
     const CallScalars* dev;
 };
 void launch_apply(const ApplyDelta& x, RowGeom g, bool shared, hipStream_t st);   // shared: memory is, one row in flight
@@ -233,6 +244,7 @@ void launch_apply(const ApplyDelta& x, RowGeom g, bool shared, hipStream_t st); 
 // (loss_step 1: dots -> block sums in loss_tmp; 2: block sums -> *loss_out).
 struct AdjustStage {
     RowGeom g{0, 0};
+    const Slices* slices = nullptr;      // of wfirst, wtail and apply alike
     const WSideArgs* wfirst = nullptr; const TailArgs* wtail = nullptr; const TailArgs* utail = nullptr;
     const ApplyDelta* apply = nullptr;
     uint32_t loss_step = 0; const float* dots = nullptr; uint32_t n = 0, T = 0;

@@ -13,6 +13,7 @@
 #include "loss.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace w2v {
 
@@ -71,6 +72,11 @@ uint32_t useg_slots_most(uint32_t T, uint32_t n) {
                     slots_after(before_step, useg_pairs_per_chunk(T, 1, before_step)));
 }
 
+// The kernels that reach into the matrices exist for one matrix and for slices.
+template <class F> static void with_slices(const Slices* sl, F&& call) {
+    if (sl) call(SliceArgs{*sl}); else call(OneMatrix{});
+}
+
 struct SegArgs {
     const float4* src;          // output side, level 1: U; higher levels: partial rows of the level below
     float4* dst;                // matrix updated in place
@@ -123,8 +129,8 @@ template <int G, int NV, int THREADS> struct TailLds {
     uint32_t out_key[2];                                  // the block's own head and tail slot
 };
 
-template <int G, int NV, int THREADS, bool DEFER>
-__device__ __forceinline__ void tail_body(const SegArgs& a, uint32_t vb, TailLds<G, NV, THREADS>& lds) {
+template <int G, int NV, int THREADS, bool DEFER, class SL>
+__device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32_t vb, TailLds<G, NV, THREADS>& lds) {
     constexpr int GROUPS = THREADS / G, CB = tail_block(G), C = CB / GROUPS;
     constexpr int D = NV == 1 && (DEFER || C == 8) ? 8 : (NV <= 2 ? 4 : 2);
     static_assert(C % 2 == 0, "a border's two slots fall into one part");
@@ -136,6 +142,7 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, uint32_t vb, TailLds
     const bool more = base + CB < a.entries;              // a block follows
     const uint32_t d4 = a.g.d4;
     const uint64_t s4 = a.g.stride4;
+    const Rows<G, NV, SL, 1> dst(sl, a.dst, a.g, l);      // (DEFER: not used)
     int any = 0;
     for (int i = threadIdx.x; i < CB + 2; i += THREADS) {
         const int64_t pos = (int64_t)base - 1 + i;
@@ -169,7 +176,7 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, uint32_t vb, TailLds
                 out[v].z = fmaf(alpha, acc[v].z, old[v].z);
                 out[v].w = fmaf(alpha, acc[v].w, old[v].w);
             }
-            store_row<G, NV>(a.dst + (uint64_t)key * s4, (uint32_t)s4, l, out);
+            dst.store(key, out);
         }
     };
     // ---- each group's part ----
@@ -203,7 +210,7 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, uint32_t vb, TailLds
             const bool cm = !DEFER && (f & TL_COMPLETE);
             const uint32_t i = f & TL_POS;
             load_row_if<G, NV>((f & TL_HAS) != 0, a.src + (uint64_t)(base + i) * s4, d4, l, sv);
-            load_row_if<G, NV>(cm, a.dst + (uint64_t)(cm ? K((int)i) : 0u) * s4, d4, l, dv);
+            if (!DEFER) dst.load_if(cm, cm ? K((int)i) : 0u, dv);
         };
 #pragma unroll
         for (int t = 0; t < D; ++t) fetch(t, srcv[t], dstv[t]);
@@ -244,7 +251,7 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, uint32_t vb, TailLds
         if (k == KEY_MASK || (raw0 & KEY_ZERO)) continue; // (flagged: the run began earlier)
         const bool came_in = block_before == k;
         float4 old[NV];
-        load_row_if<G, NV>(!DEFER && !came_in, a.dst + (uint64_t)k * s4, d4, l, old);
+        if (!DEFER) dst.load_if(!came_in, k, old);
         clear<NV>(acc);
         int i = start;
         uint32_t raw = raw0, next;
@@ -276,10 +283,10 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, uint32_t vb, TailLds
     }
 }
 
-template <int G, int NV, int THREADS>
-__global__ __launch_bounds__(THREADS) void tail_kernel(SegArgs a) {
+template <int G, int NV, int THREADS, class SL>
+__global__ __launch_bounds__(THREADS) void tail_kernel(SegArgs a, SL sl) {
     __shared__ TailLds<G, NV, THREADS> lds;
-    tail_body<G, NV, THREADS, false>(a, blockIdx.x, lds);
+    tail_body<G, NV, THREADS, false>(a, sl, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -313,8 +320,8 @@ uint32_t wseg_slots_most(uint32_t M) {
     return std::max(slots_after(M, wseg_entries_per_chunk(M)), slots_after(before_step, wseg_entries_per_chunk(before_step)));
 }
 
-template <int G, int NV, int D>
-__device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
+template <int G, int NV, int D, class SL>
+__device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32_t vb) {
     constexpr int WOWN_THREADS = adj_threads(G);
     constexpr int GROUPS = WOWN_THREADS / G;
     constexpr int C = WOWN_C;
@@ -383,6 +390,8 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
     if (!active || count == 0) return;
     const uint32_t d4 = a.g.d4;
     const uint64_t s4 = a.g.stride4;
+    const Rows<G, NV, SL, 0> src(sl, a.src, a.g, l);
+    const Rows<G, NV, SL, 1> dst(sl, a.dst, a.g, l);
     const uint32_t cell = (uint32_t)(base >> a.cell_log2);
     const uint32_t head_slot = 2 * cell - 1, tail_slot = 2 * cell;   // used only when they exist
 
@@ -397,7 +406,7 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
             out[v].z = fmaf(alpha, acc[v].z, old[v].z);
             out[v].w = fmaf(alpha, acc[v].w, old[v].w);
         }
-        store_row_nt<G, NV>(a.dst + (uint64_t)row * s4, (uint32_t)s4, l, out);
+        dst.store_nt(row, out);
     };
     auto fetch = [&](int idx, float4 (&sv)[NV], float4 (&dv)[NV]) {
         const bool on = idx < count;
@@ -408,8 +417,8 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
         // Destination rows are read and written once per minibatch: with the non-temporal hint they
         // do not push the source rows (a few hundred MB that are read again and again) out of the
         // caches -- measured -7 % on this kernel; the same hint on the source rows costs +25 %.
-        load_row_if<G, NV>(on, a.src + (uint64_t)sr * s4, d4, l, sv);
-        load_row_nt_if<G, NV>(cm, a.dst + (uint64_t)dk * s4, d4, l, dv);
+        src.load_if(on, sr, sv);
+        dst.load_nt_if(cm, dk, dv);
     };
 #pragma unroll
     for (int t = 0; t < D; ++t) fetch(t, srcv[t], dstv[t]);
@@ -459,8 +468,7 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
             if (b < cnt) {
 #pragma unroll
                 for (int t = 0; t < S; ++t)
-                    load_row_if<G, NV>(b + t < cnt, a.src + (uint64_t)__shfl(sr, b + t, G) * s4, d4, l,
-                                       t < D ? srcv[t % D] : dstv[t % D]);
+                    src.load_if(b + t < cnt, __shfl(sr, b + t, G), t < D ? srcv[t % D] : dstv[t % D]);
 #pragma unroll
                 for (int t = 0; t < S; ++t) axpy<NV>(__shfl(cf, b + t, G), t < D ? srcv[t % D] : dstv[t % D], acc);
             }
@@ -471,7 +479,7 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
     if (!last_in_head) {
         if (ended) {                                      // the whole run lay inside the cell
             float4 old[NV];
-            load_row_nt_if<G, NV>(true, a.dst + (uint64_t)key * s4, d4, l, old);
+            dst.load_nt_if(true, key, old);
             finish_row(key, old);
         } else {                                          // first piece of a run that leaves the cell
             store_row<G, NV>(a.prows + (uint64_t)tail_slot * s4, d4, l, acc);
@@ -486,9 +494,9 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, uint32_t vb) {
     }
 }
 
-template <int G, int NV, int D>
-__global__ __launch_bounds__(adj_threads(G)) void wown_kernel(SegArgs a) {
-    wown_body<G, NV, D>(a, blockIdx.x);
+template <int G, int NV, int D, class SL>
+__global__ __launch_bounds__(adj_threads(G)) void wown_kernel(SegArgs a, SL sl) {
+    wown_body<G, NV, D>(a, sl, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* __restrict__ x, uint32_t n,
@@ -534,10 +542,11 @@ void launch_wseg(const WSideArgs& w, hipStream_t st) {
     const SegArgs a = seg_args_of(w);
     uint32_t nchunks = (w.M + WOWN_C - 1) / WOWN_C;
 #define CALL(G, NV)                                                                              \
-    hipLaunchKernelGGL((wown_kernel<G, NV, (NV <= 2 ? 4 : 2)>),                                   \
-                       dim3(blocks_for((uint64_t)nchunks * G, adj_threads(G))),                 \
-                       dim3(adj_threads(G)), 0,                                                 \
-                       st, a)
+    with_slices(w.slices, [&](const auto& sl) {                                                   \
+        hipLaunchKernelGGL((wown_kernel<G, NV, (NV <= 2 ? 4 : 2), std::decay_t<decltype(sl)>>),  \
+                           dim3(blocks_for((uint64_t)nchunks * G, adj_threads(G))),               \
+                           dim3(adj_threads(G)), 0, st, a, sl);                                  \
+    })
     W2V_DISPATCH_GEOM(w.g.d4, CALL);
 #undef CALL
 }
@@ -546,8 +555,10 @@ void launch_tail(const TailArgs& t, hipStream_t st, bool shared) {
     if (t.entries == 0) return;
     const SegArgs a = seg_args_of(t);
 #define CALL_THREADS(G, NV, THREADS)                                                             \
-    hipLaunchKernelGGL((tail_kernel<G, NV, THREADS>), dim3(blocks_for(t.entries, tail_block(G))), \
-                       dim3(THREADS), 0, st, a)
+    with_slices(t.slices, [&](const auto& sl) {                                                   \
+        hipLaunchKernelGGL((tail_kernel<G, NV, THREADS, std::decay_t<decltype(sl)>>),             \
+                           dim3(blocks_for(t.entries, tail_block(G))), dim3(THREADS), 0, st, a, sl); \
+    })
 #define CALL(G, NV)                                                                              \
     do { if (shared) CALL_THREADS(G, NV, adj_threads(G)); else CALL_THREADS(G, NV, tail_threads(G, NV)); } while (0)
     W2V_DISPATCH_GEOM(t.g.d4, CALL);
@@ -567,14 +578,15 @@ struct ApplyArgs {
     const CallScalars* dev;
 };
 
-template <int G, int NV, int THREADS, int D>
-__device__ __forceinline__ void apply_body(const ApplyArgs& a, uint32_t vb) {
+template <int G, int NV, int THREADS, int D, class SL>
+__device__ __forceinline__ void apply_body(const ApplyArgs& a, const SL& sl, uint32_t vb) {
     const float alpha = a.dev ? a.dev->alpha : a.alpha;
     const int l = threadIdx.x % G;
     const uint32_t base = (vb * (uint32_t)THREADS + threadIdx.x) / G * APPLY_P;
     const uint32_t mine = l < APPLY_P && base + l < a.n ? a.dkey[base + l] : KEY_NONE;
     const int lane0 = ((int)(threadIdx.x & 63) / G) * G;
     uint32_t todo = (uint32_t)(__ballot(mine != KEY_NONE) >> lane0) & ((1u << APPLY_P) - 1u);
+    const Rows<G, NV, SL, 0> U(sl, a.U, a.g, l);
     while (todo) {
         float4 dv[D][NV], uv[D][NV];
         uint32_t key[D];
@@ -585,31 +597,33 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, uint32_t vb) {
             todo &= todo - 1;                              // (0 stays 0)
             key[t] = on ? (uint32_t)__shfl(mine, e, G) : KEY_NONE;
             load_row_if<G, NV>(on, a.delta + (uint64_t)(on ? base + e : 0u) * a.g.stride4, a.g.d4, l, dv[t]);
-            load_row_if<G, NV>(on, a.U + (uint64_t)(on ? key[t] : 0u) * a.g.stride4, a.g.d4, l, uv[t]);
+            U.load_if(on, on ? key[t] : 0u, uv[t]);
         }
 #pragma unroll
         for (int t = 0; t < D; ++t) {
             if (key[t] == KEY_NONE) continue;
             axpy<NV>(alpha, dv[t], uv[t]);
-            store_row<G, NV>(a.U + (uint64_t)key[t] * a.g.stride4, a.g.stride4, l, uv[t]);
+            U.store(key[t], uv[t]);
         }
     }
 }
 
 // On its own, beside the output side's levels on another stream.  Where it shares the memory with them and
 // with announced sorts, one row in flight per group (benchmark step with four 3.177 ms, two 3.179, one 3.168).
-template <int G, int NV, int D>
-__global__ __launch_bounds__(adj_threads(G)) void apply_kernel(ApplyArgs a) {
-    apply_body<G, NV, adj_threads(G), D>(a, blockIdx.x);
+template <int G, int NV, int D, class SL>
+__global__ __launch_bounds__(adj_threads(G)) void apply_kernel(ApplyArgs a, SL sl) {
+    apply_body<G, NV, adj_threads(G), D>(a, sl, blockIdx.x);
 }
 
 void launch_apply(const ApplyDelta& x, RowGeom g, bool shared, hipStream_t st) {
     if (x.n == 0) return;
     const ApplyArgs a{(float4*)x.U, g, (const float4*)x.delta, x.dkey, x.n, x.alpha, x.dev};
 #define CALL_ROWS(G, NV, D)                                                                               \
-    hipLaunchKernelGGL((apply_kernel<G, NV, D>),                                                          \
-                       dim3(blocks_for((uint64_t)blocks_for(x.n, APPLY_P) * G, adj_threads(G))),          \
-                       dim3(adj_threads(G)), 0, st, a)
+    with_slices(x.slices, [&](const auto& sl) {                                                            \
+        hipLaunchKernelGGL((apply_kernel<G, NV, D, std::decay_t<decltype(sl)>>),                          \
+                           dim3(blocks_for((uint64_t)blocks_for(x.n, APPLY_P) * G, adj_threads(G))),      \
+                           dim3(adj_threads(G)), 0, st, a, sl);                                           \
+    })
 #define CALL(G, NV) do { if (shared) CALL_ROWS(G, NV, 1); else CALL_ROWS(G, NV, (NV <= 2 ? 4 : 2)); } while (0)
     W2V_DISPATCH_GEOM(g.d4, CALL);
 #undef CALL
@@ -638,14 +652,14 @@ struct StageDev {
 constexpr int stage_threads(int G, int NV, bool first) { return first ? adj_threads(G) : tail_threads(G, NV); }
 
 // (at two float4 per lane the output side's walk fills 96 registers, five wavefronts per SIMD: keep it so)
-template <int G, int NV, bool FIRST>
-__global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? 5 : 1)) void adjust_stage_kernel(StageDev s) {
+template <int G, int NV, bool FIRST, class SL>
+__global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? (SL::ONE ? 5 : 4) : 1)) void adjust_stage_kernel(StageDev s, SL sl) {
     constexpr int D = NV <= 2 ? 4 : 2, THREADS = stage_threads(G, NV, FIRST);
     __shared__ TailLds<G, NV, THREADS> lds;
     __shared__ double red[THREADS / 64];
     uint32_t b = blockIdx.x;                               // the input side's level first: its blocks run longest
     if (b < s.u_blocks) {
-        tail_body<G, NV, THREADS, true>(s.u, b, lds);
+        tail_body<G, NV, THREADS, true>(s.u, OneMatrix{}, b, lds);
         return;
     }
     b -= s.u_blocks;
@@ -656,12 +670,12 @@ __global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? 5 
     }
     b -= s.loss_blocks;
     if (b < s.w_blocks) {
-        if (FIRST) wown_body<G, NV, D>(s.w, b);
-        else tail_body<G, NV, THREADS, false>(s.w, b, lds);
+        if (FIRST) wown_body<G, NV, D>(s.w, sl, b);
+        else tail_body<G, NV, THREADS, false>(s.w, sl, b, lds);
         return;
     }
     b -= s.w_blocks;
-    if (!FIRST) apply_body<G, NV, THREADS, D>(s.apply, b);
+    if (!FIRST) apply_body<G, NV, THREADS, D>(s.apply, sl, b);
 }
 
 // The input side's levels alone, beside the output side's walk on another stream: blocks no larger than
@@ -669,7 +683,7 @@ __global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? 5 
 template <int G, int NV>
 __global__ __launch_bounds__(adj_threads(G)) void input_tail_kernel(SegArgs a) {
     __shared__ TailLds<G, NV, adj_threads(G)> lds;
-    tail_body<G, NV, adj_threads(G), true>(a, blockIdx.x, lds);
+    tail_body<G, NV, adj_threads(G), true>(a, OneMatrix{}, blockIdx.x, lds);
 }
 
 void launch_input_tail(const TailArgs& t, hipStream_t st) {
@@ -682,8 +696,8 @@ void launch_input_tail(const TailArgs& t, hipStream_t st) {
 #undef CALL
 }
 
-template <int G, int NV>
-static void launch_stage_shape(StageDev s, bool first, hipStream_t st) {
+template <int G, int NV, class SL>
+static void launch_stage_shape(StageDev s, const SL& sl, bool first, hipStream_t st) {
     if (first) s.w_blocks = blocks_for((uint64_t)((s.w.entries + WOWN_C - 1) / WOWN_C) * G, adj_threads(G));
     else s.w_blocks = blocks_for(s.w.entries, tail_block(G));
     s.u_blocks = blocks_for(s.u.entries, tail_block(G));
@@ -691,8 +705,8 @@ static void launch_stage_shape(StageDev s, bool first, hipStream_t st) {
     const dim3 grid(s.w_blocks + s.u_blocks + s.apply_blocks + s.loss_blocks);
     if (grid.x == 0) return;
     const dim3 block(stage_threads(G, NV, first));
-    if (first) hipLaunchKernelGGL((adjust_stage_kernel<G, NV, true>), grid, block, 0, st, s);
-    else hipLaunchKernelGGL((adjust_stage_kernel<G, NV, false>), grid, block, 0, st, s);
+    if (first) hipLaunchKernelGGL((adjust_stage_kernel<G, NV, true, SL>), grid, block, 0, st, s, sl);
+    else hipLaunchKernelGGL((adjust_stage_kernel<G, NV, false, SL>), grid, block, 0, st, s, sl);
 }
 
 // (Its own launch keeps its registers to itself, and the levels run beside it; against that, events between
@@ -717,7 +731,7 @@ void launch_adjust_stage(const AdjustStage& x, hipStream_t st) {
         s.nb = blocks_for(s.total, loss_terms_of(s.total)); s.loss_out = x.loss_out;
         s.loss_blocks = x.loss_step == 1 ? s.nb : 1u;
     }
-#define CALL(G, NV) launch_stage_shape<G, NV>(s, first, st)
+#define CALL(G, NV) with_slices(x.slices, [&](const auto& sl) { launch_stage_shape<G, NV>(s, sl, first, st); })
     W2V_DISPATCH_GEOM(x.g.d4, CALL);
 #undef CALL
 }
@@ -758,8 +772,8 @@ __device__ __forceinline__ void coefficients(const float (&sdot)[N], uint32_t j0
 }
 
 
-template <int G, int NV, int TB, bool FUSED, bool OWN>
-__global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_t CP) {
+template <int G, int NV, int TB, bool FUSED, bool OWN, class SL>
+__global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_t CP, SL sl) {
     constexpr bool NEED_U = FUSED || OWN;      // the pair's input row: for the dots, for own rows
     const float alpha = a.dev ? a.dev->alpha : a.alpha;
     constexpr int GROUPS = USEG_THREADS / G;
@@ -800,8 +814,8 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
 
     const uint32_t d4 = a.g.d4;
     const uint64_t s4 = a.g.stride4;
-    const float4* U4p = (const float4*)a.U;
-    const float4* W4p = (const float4*)a.W;
+    const Rows<G, NV, SL, 0> U(sl, (const float4*)a.U, a.g, l);
+    const Rows<G, NV, SL, 1> W(sl, (const float4*)a.W, a.g, l);
     float4* delta = (float4*)a.delta;
     float4* prows = (float4*)a.prows;
 
@@ -818,9 +832,9 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
     for (int t = 0; t < TB; ++t) {
         bool on = (uint32_t)t < T;
         uint32_t r = on ? (s_key[grp][t] & ~ALONE) : 0u;
-        load_row_if<G, NV>(on, W4p + (uint64_t)r * s4, d4, l, w[t]);
+        W.load_if(on, r, w[t]);
     }
-    if (NEED_U) load_row<G, NV>(U4p + (uint64_t)key * s4, d4, l, u);
+    if (NEED_U) U.load(key, u);
 
     for (uint32_t pi = 0; pi < cnt; ++pi) {
         const uint32_t ps = ps0 + pi;
@@ -829,7 +843,7 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
         if (l == 0) a.dkey[ps] = KEY_NONE;
         if (NEED_U) {                                  // the next pair's input row, ahead of need
             bool more = pi + 1 < cnt;
-            load_row_if<G, NV>(more, U4p + (uint64_t)(more ? next : 0u) * s4, d4, l, un);
+            U.load_if(more, more ? next : 0u, un);
         }
         for (uint32_t jb = 0; jb < T; jb += TB) {
             const bool last_batch = jb + TB >= T;
@@ -868,7 +882,7 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
                             out[v].z = fmaf(alpha, fmaf(gco[t], u[v].z, 0.f), w[t][v].z);
                             out[v].w = fmaf(alpha, fmaf(gco[t], u[v].w, 0.f), w[t][v].w);
                         }
-                        store_row_nt<G, NV>((float4*)a.W_update + (uint64_t)(rr & ~ALONE) * s4, (uint32_t)s4, l, out);
+                        W.store_nt(rr & ~ALONE, out);
                     }
                 }
                 // this register set is free again: fetch the matching row of the following batch
@@ -877,7 +891,7 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
                 // (the non-temporal hint for rows named once, which pays in the fixed-T kernel,
                 // costs 25 % here: the branch breaks up this loop's batched loads)
                 uint32_t r = on ? (s_key[grp][npi * T + nj] & ~ALONE) : 0u;
-                load_row_if<G, NV>(on, W4p + (uint64_t)r * s4, d4, l, w[t]);
+                W.load_if(on, r, w[t]);
             }
         }
         if (next != key) {                       // the run of `key` ends with this pair
@@ -924,8 +938,8 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
 // Register budget for five wavefronts per SIMD: at two float4 per lane the fused form would take
 // 102 registers and run four; held to 96 it spills five and is 1.6 % faster.  (Six: 30 % slower.
 // The same squeeze on the generic kernel or on the output-side kernel costs more than it gives.)
-template <int G, int NV, int T, int PB, bool FUSED, bool OWN>
-__global__ __launch_bounds__(USEG_THREADS, 5) void useg_multi_kernel(USideArgs a, uint32_t CP) {
+template <int G, int NV, int T, int PB, bool FUSED, bool OWN, class SL>
+__global__ __launch_bounds__(USEG_THREADS, (SL::ONE ? 5 : 4)) void useg_multi_kernel(USideArgs a, uint32_t CP, SL sl) {
     constexpr bool NEED_U = FUSED || OWN;
     const float alpha = a.dev ? a.dev->alpha : a.alpha;
     constexpr int GROUPS = USEG_THREADS / G;
@@ -963,8 +977,8 @@ __global__ __launch_bounds__(USEG_THREADS, 5) void useg_multi_kernel(USideArgs a
 
     const uint32_t d4 = a.g.d4;
     const uint64_t s4 = a.g.stride4;
-    const float4* U4p = (const float4*)a.U;
-    const float4* W4p = (const float4*)a.W;
+    const Rows<G, NV, SL, 0> U(sl, (const float4*)a.U, a.g, l);
+    const Rows<G, NV, SL, 1> W(sl, (const float4*)a.W, a.g, l);
     float4* delta = (float4*)a.delta;
     float4* prows = (float4*)a.prows;
 
@@ -984,7 +998,7 @@ __global__ __launch_bounds__(USEG_THREADS, 5) void useg_multi_kernel(USideArgs a
             const bool live = pi < cnt;
             if (NEED_U) {
                 const uint32_t k_in = live ? s_skey[grp][pi + 1] : 0u;
-                load_row_if<G, NV>(live, U4p + (uint64_t)k_in * s4, d4, l, u[b]);
+                U.load_if(live, k_in, u[b]);
             }
 #pragma unroll
             for (int j = 0; j < T; ++j) {
@@ -992,8 +1006,8 @@ __global__ __launch_bounds__(USEG_THREADS, 5) void useg_multi_kernel(USideArgs a
                 const uint32_t r = rk & ~ALONE;
                 // a row that no other slot names is read here once and written once: the
                 // non-temporal hint keeps it out of the caches' way (-7 % on this kernel)
-                if (rk & ALONE) load_row_nt_if<G, NV>(live, W4p + (uint64_t)r * s4, d4, l, w[b][j]);
-                else load_row_if<G, NV>(live, W4p + (uint64_t)r * s4, d4, l, w[b][j]);
+                if (rk & ALONE) W.load_nt_if(live, r, w[b][j]);
+                else W.load_if(live, r, w[b][j]);
             }
         }
 #pragma unroll
@@ -1036,8 +1050,7 @@ __global__ __launch_bounds__(USEG_THREADS, 5) void useg_multi_kernel(USideArgs a
                                 out[v].z = fmaf(alpha, fmaf(gco[j], u[b][v].z, 0.f), w[b][j][v].z);
                                 out[v].w = fmaf(alpha, fmaf(gco[j], u[b][v].w, 0.f), w[b][j][v].w);
                             }
-                            store_row_nt<G, NV>((float4*)a.W_update + (uint64_t)(r & ~ALONE) * s4, (uint32_t)s4,
-                                                l, out);
+                            W.store_nt(r & ~ALONE, out);
                         }
                     }
                 }
@@ -1080,54 +1093,52 @@ constexpr int USEG_PB = 1;     // pairs per batch of the fixed-T kernel (1 measu
 // A fixed-T kernel exists for k = 5 (the paper's and the benchmark's number of negatives); other T
 // take the generic kernel (fixed-T variants for k = 10 and 25 measured no better, or worse).
 
-template <int G, int NV, int T>
-static void launch_useg_fixed(const USideArgs& a, uint32_t CP, dim3 grid, dim3 block, hipStream_t st) {
-    const bool own = a.W_update != nullptr;      // (only the fused form takes rows over)
-    if (a.fused && own)
-        hipLaunchKernelGGL((useg_multi_kernel<G, NV, T, USEG_PB, true, true>), grid, block, 0, st, a, CP);
+template <int G, int NV, int T, class SL>
+static void launch_useg_fixed(const USideArgs& a, const SL& sl, uint32_t CP, dim3 grid, dim3 block, hipStream_t st) {
+    if (a.fused && a.own_rows)                   // (only the fused form takes rows over, or slices)
+        hipLaunchKernelGGL((useg_multi_kernel<G, NV, T, USEG_PB, true, true, SL>), grid, block, 0, st, a, CP, sl);
     else if (a.fused)
-        hipLaunchKernelGGL((useg_multi_kernel<G, NV, T, USEG_PB, true, false>), grid, block, 0, st, a, CP);
-    else
-        hipLaunchKernelGGL((useg_multi_kernel<G, NV, T, USEG_PB, false, false>), grid, block, 0, st, a, CP);
+        hipLaunchKernelGGL((useg_multi_kernel<G, NV, T, USEG_PB, true, false, SL>), grid, block, 0, st, a, CP, sl);
+    else if constexpr (SL::ONE)
+        hipLaunchKernelGGL((useg_multi_kernel<G, NV, T, USEG_PB, false, false, SL>), grid, block, 0, st, a, CP, sl);
 }
 
-template <int G, int NV>
-static void launch_useg_shape(const USideArgs& a, hipStream_t st) {
+template <int G, int NV, class SL>
+static void launch_useg_shape(const USideArgs& a, const SL& sl, hipStream_t st) {
     const uint32_t CP = useg_pairs_per_chunk(a.T, a.g.d4, a.n);
     const uint32_t nchunks = (a.n + CP - 1) / CP;
     dim3 grid(blocks_for((uint64_t)nchunks * G, USEG_THREADS)), block(USEG_THREADS);
     if constexpr (NV <= 2) {
-        if (a.T == 6) return launch_useg_fixed<G, NV, 6>(a, CP, grid, block, st);
+        if (a.T == 6) return launch_useg_fixed<G, NV, 6>(a, sl, CP, grid, block, st);
     }
     constexpr int TB = NV == 1 ? 9 : (NV == 2 ? 6 : 4);     // rows requested per batch
-    const bool own = a.W_update != nullptr;      // (only the fused form takes rows over)
     if constexpr (NV == 1) {
         // The fused kernel with one float4 per lane has registers for up to thirteen rows in
         // flight: of 9, 11 and 13 rows per batch, take the one that needs the fewest batches per
         // pair and then leaves the fewest empty places in them (k = 10: one batch of 11 instead of
         // 9 + 2, input-side kernel 3 % faster; k = 25: 13 + 13 instead of 9 + 9 + 8, 1 %).
-        if (a.fused && own) {
+        if (a.fused && a.own_rows) {
             int best = 9;
             uint32_t best_nb = (a.T + 8) / 9, best_waste = best_nb * 9 - a.T;
             for (int tb : {11, 13}) {
                 const uint32_t nb = (a.T + tb - 1) / tb, waste = nb * tb - a.T;
                 if (nb < best_nb || (nb == best_nb && waste < best_waste)) { best = tb; best_nb = nb; best_waste = waste; }
             }
-            if (best == 11) { hipLaunchKernelGGL((useg_kernel<G, NV, 11, true, true>), grid, block, 0, st, a, CP); return; }
-            if (best == 13) { hipLaunchKernelGGL((useg_kernel<G, NV, 13, true, true>), grid, block, 0, st, a, CP); return; }
+            if (best == 11) { hipLaunchKernelGGL((useg_kernel<G, NV, 11, true, true, SL>), grid, block, 0, st, a, CP, sl); return; }
+            if (best == 13) { hipLaunchKernelGGL((useg_kernel<G, NV, 13, true, true, SL>), grid, block, 0, st, a, CP, sl); return; }
         }
     }
-    if (a.fused && own)
-        hipLaunchKernelGGL((useg_kernel<G, NV, TB, true, true>), grid, block, 0, st, a, CP);
+    if (a.fused && a.own_rows)                   // (only the fused form takes rows over, or slices)
+        hipLaunchKernelGGL((useg_kernel<G, NV, TB, true, true, SL>), grid, block, 0, st, a, CP, sl);
     else if (a.fused)
-        hipLaunchKernelGGL((useg_kernel<G, NV, TB, true, false>), grid, block, 0, st, a, CP);
-    else
-        hipLaunchKernelGGL((useg_kernel<G, NV, TB, false, false>), grid, block, 0, st, a, CP);
+        hipLaunchKernelGGL((useg_kernel<G, NV, TB, true, false, SL>), grid, block, 0, st, a, CP, sl);
+    else if constexpr (SL::ONE)
+        hipLaunchKernelGGL((useg_kernel<G, NV, TB, false, false, SL>), grid, block, 0, st, a, CP, sl);
 }
 
 void launch_useg(const USideArgs& a, hipStream_t st) {
     if (a.n == 0) return;
-#define SHAPE(G, NV) launch_useg_shape<G, NV>(a, st)
+#define SHAPE(G, NV) with_slices(a.slices, [&](const auto& sl) { launch_useg_shape<G, NV>(a, sl, st); })
     W2V_DISPATCH_GEOM(a.g.d4, SHAPE);
 #undef SHAPE
 }

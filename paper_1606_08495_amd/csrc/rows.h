@@ -69,6 +69,82 @@ __device__ __forceinline__ void store_row(float4* __restrict__ row, uint32_t d4,
     }
 }
 
+// This lane's part of the rows of a matrix (WHICH: 0 input, 1 output vectors): of one matrix, or of the slices of
+// several shards.  Of slices a lane keeps an address and a stride for each of its float4, as they may lie in
+// different matrices.  store() writes the whole stride of a row, the pad as zeros.
+struct OneMatrix { static constexpr bool ONE = true; };
+struct SliceArgs : Slices { static constexpr bool ONE = false; };
+template <int G, int NV, class SL, int WHICH> struct Rows;
+
+template <int G, int NV, int WHICH> struct Rows<G, NV, OneMatrix, WHICH> {
+    float4* M; uint64_t s4; uint32_t d4; int l;
+    __device__ __forceinline__ Rows(const OneMatrix&, const float4* m, RowGeom g, int lane)
+        : M(const_cast<float4*>(m)), s4(g.stride4), d4(g.d4), l(lane) {}
+    __device__ __forceinline__ void load_if(bool on, uint32_t row, float4 (&r)[NV]) const {
+        load_row_if<G, NV>(on, M + (uint64_t)row * s4, d4, l, r);
+    }
+    __device__ __forceinline__ void load(uint32_t row, float4 (&r)[NV]) const {
+        load_row<G, NV>(M + (uint64_t)row * s4, d4, l, r);
+    }
+    __device__ __forceinline__ void load_nt_if(bool on, uint32_t row, float4 (&r)[NV]) const {
+        load_row_nt_if<G, NV>(on, M + (uint64_t)row * s4, d4, l, r);
+    }
+    __device__ __forceinline__ void store(uint32_t row, const float4 (&r)[NV]) const {
+        store_row<G, NV>(M + (uint64_t)row * s4, (uint32_t)s4, l, r);
+    }
+    __device__ __forceinline__ void store_nt(uint32_t row, const float4 (&r)[NV]) const {
+        store_row_nt<G, NV>(M + (uint64_t)row * s4, (uint32_t)s4, l, r);
+    }
+};
+
+template <int G, int NV, int WHICH> struct Rows<G, NV, SliceArgs, WHICH> {
+    float4* at[NV]; uint32_t s4[NV]; bool data[NV], inside[NV];      // (data: not the pad; its loads give zero)
+    __device__ __forceinline__ Rows(const SliceArgs& sl, const float4*, RowGeom g, int lane) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            const uint32_t i = (uint32_t)lane + (uint32_t)(G * v);
+            at[v] = nullptr; s4[v] = 0; data[v] = false; inside[v] = i < g.d4;
+            for (uint32_t s = 0; s < sl.count; ++s) {
+                if (i >= sl.first[s]) {
+                    at[v] = (float4*)sl.M[WHICH][s] + (i - sl.first[s]);
+                    s4[v] = sl.stride4[s];
+                    data[v] = i - sl.first[s] < sl.d4[s];
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void load_if(bool on, uint32_t row, float4 (&r)[NV]) const {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) r[v] = on && data[v] ? at[v][(uint64_t)row * s4[v]] : f4zero();
+    }
+    __device__ __forceinline__ void load(uint32_t row, float4 (&r)[NV]) const { load_if(true, row, r); }
+    __device__ __forceinline__ void load_nt_if(bool on, uint32_t row, float4 (&r)[NV]) const {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            if (on && data[v]) {
+                const v4f x = __builtin_nontemporal_load((const v4f*)at[v] + (uint64_t)row * s4[v]);
+                r[v] = make_float4(x.x, x.y, x.z, x.w);
+            } else {
+                r[v] = f4zero();
+            }
+        }
+    }
+    __device__ __forceinline__ void store(uint32_t row, const float4 (&r)[NV]) const {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if (inside[v]) at[v][(uint64_t)row * s4[v]] = r[v];
+    }
+    __device__ __forceinline__ void store_nt(uint32_t row, const float4 (&r)[NV]) const {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+            if (inside[v]) {
+                v4f x = {r[v].x, r[v].y, r[v].z, r[v].w};
+                __builtin_nontemporal_store(x, (v4f*)at[v] + (uint64_t)row * s4[v]);
+            }
+        }
+    }
+};
+
 template <int NV>
 __device__ __forceinline__ float dot_part(const float4 (&a)[NV], const float4 (&b)[NV]) {
     float s = 0.f;

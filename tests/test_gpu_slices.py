@@ -1,0 +1,80 @@
+"""Several column shards trained in one process as one matrix of joint rows, against the same step through
+dotprod, coefficients and adjust of each shard."""
+import numpy as np
+import pytest
+import torch
+
+from paper_1606_08495_amd import w2v
+from util import all_rows, dev, vec_error, zipf_counts
+
+pytestmark = pytest.mark.gpu
+
+TOL = 1e-5                  # fp32 sums in another order: up to 3e-7 of a row's length
+
+
+def make_shard(V, d, seed, counts, d_total=None, col_begin=0):
+    sh = w2v.Shard(V, d, seed, d_total=d_total, col_begin=col_begin, init_mode=1)
+    sh.set_counts(counts, 0.0)
+    return sh
+
+
+def steps(shards, ins, outs, k, form):
+    losses, alpha = [], min(0.03, 3.0 / ins[0].numel())      # (frequent rows move by less than their size)
+    for h, (a, b) in enumerate(zip(ins, outs)):
+        if form == "joint":
+            loss = torch.zeros(1, dtype=torch.float64, device="cuda")
+            w2v.train_minibatch(shards, a, b, k, 70 + h, alpha, loss=loss)
+        else:
+            dots = [s.dotprod(a, b, k, 70 + h) for s in shards]
+            g, loss = shards[0].coeffs(dots, k, want_loss=True)
+            for s in shards:
+                s.adjust(a, b, k, 70 + h, g, alpha)
+        losses.append(float(loss))
+    return losses
+
+
+# widths: padded and unpadded strides, a slice in two lane groups' float4, one to four float4 a lane, the widest
+# joint row and one past it, more slices than lanes of a float4
+CASES = [([60] * 5, 3001, 5), ([1, 2], 17, 5), ([7, 143, 150], 1500, 5), ([30, 30], 999, 5), ([102, 103, 102, 103, 102], 700, 3),
+         ([300, 400], 500, 12), ([512, 512], 300, 1), ([512, 513], 300, 1), ([4] * 32, 800, 5), ([33] * 7, 2500, 0),
+         ([60, 100, 140], 180_000, 5)]
+
+
+@pytest.mark.parametrize("widths,n,k", CASES)
+def test_joint_step_matches_each_shard_on_its_own(widths, n, k):
+    print("slices", widths, n, k, flush=True)
+    rng = np.random.default_rng(n)
+    V, d = 2500, sum(widths)
+    begins = np.concatenate([[0], np.cumsum(widths)[:-1]])
+    counts = zipf_counts(V)
+    sets = [[make_shard(V, w, 5, counts, d_total=d, col_begin=int(b)) for w, b in zip(widths, begins)] for _ in range(2)]
+    ins = [dev(np.minimum(rng.zipf(1.3, n), V) - 1) for _ in range(2)]
+    outs = [dev(rng.integers(0, V, n)) for _ in range(2)]
+    for s in sets[0] + sets[1]:                     # rows of unit size: the dots count
+        for which in (0, 1):
+            rows = torch.arange(V, dtype=torch.int32, device="cuda")
+            g = torch.Generator(device="cuda").manual_seed(7 + which)
+            x = torch.randn(V, d, device="cuda", generator=g) * d ** -0.5
+            i = (sets[0] + sets[1]).index(s) % len(widths)
+            s.set_rows(which, rows, x[:, begins[i]:begins[i] + widths[i]].contiguous())
+    la, lb = steps(sets[0], ins, outs, k, "joint"), steps(sets[1], ins, outs, k, "apart")
+    assert np.allclose(la, lb, rtol=1e-6)
+    for a, b in zip(*sets):
+        for which in (0, 1):
+            assert vec_error(all_rows(a, which), all_rows(b, which)) <= TOL
+        a.status()
+    for s in sets[0] + sets[1]:
+        s.destroy()
+
+
+def test_a_shard_listed_twice_is_updated_twice():
+    rng = np.random.default_rng(3)
+    V, n, k = 300, 900, 5
+    counts = zipf_counts(V)
+    a, b = make_shard(V, 40, 5, counts), make_shard(V, 40, 5, counts)
+    ins, outs = [dev(rng.integers(0, V, n))], [dev(rng.integers(0, V, n))]
+    assert steps([a, a], ins, outs, k, "joint") == steps([b, b], ins, outs, k, "apart")
+    for which in (0, 1):
+        assert np.array_equal(all_rows(a, which), all_rows(b, which))
+    a.destroy()
+    b.destroy()
