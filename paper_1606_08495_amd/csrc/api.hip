@@ -519,8 +519,8 @@ struct Target { float* U; float* W; const Slices* slices; RowGeom g; };
 // only).  The input-side kernel first (it also clears the output side's border slots, unless the call's
 // first launch has: good for one shard's update); then launches that each carry one walk of the output
 // side together with one higher level of the input side and one step of the loss, which depend on
-// different things.  The input side's levels park their sums in the delta buffer, which is written back
-// beside the first output-side level after they are done (and after the level-1 walk, which reads U).
+// different things.  Beside the level-1 walk, which reads U, the input side's levels park their sums in the
+// delta buffer, which is written back beside the levels that follow.
 // `join_sorts`: the output-side order comes from the shard's second stream.
 void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t* sku,
                   const uint32_t* perm, const uint32_t* skw, const uint32_t* sidx,
@@ -568,9 +568,10 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
         std::swap(x.src_rows, x.dst_rows);
         std::swap(x.src_keys, x.dst_keys);
     };
-    auto input_level = [&]() {
+    auto input_level = [&](bool defer) {
         TailArgs t{to.U, to.slices, to.g, alpha, us.src_rows, us.src_keys, us.slots, us.dst_rows, us.dst_keys};
-        t.defer_rows = p.delta; t.defer_keys = p.dkey; t.level = ++us.level; t.cp = cp; t.dev = dev;
+        if (defer) { t.defer_rows = p.delta; t.defer_keys = p.dkey; t.cp = cp; }
+        t.level = ++us.level; t.dev = dev;
         return t;
     };
     auto w_level = [&]() {
@@ -601,7 +602,7 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
         {
             Phase ph(ws_owner, W2V_PH_APPLY, side);
             while (us.slots) {
-                launch_input_tail(input_level(), side);
+                launch_input_tail(input_level(true), side);
                 advance(us);
             }
         }
@@ -641,9 +642,10 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
             x.wtail = &wt;
         }
         if (u_level) {
-            ut = input_level();
+            ut = input_level(first);
             x.utail = &ut;
-        } else if (!first && !applied) {
+        }
+        if (!first && !applied) {
             x.apply = &apply;
             applied = true;
         }

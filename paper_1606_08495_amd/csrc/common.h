@@ -222,8 +222,8 @@ struct TailArgs {
     float* M; const Slices* slices; RowGeom g; float alpha;      // slices (optional): instead of M, their output vectors
     const float* src_rows; const uint32_t* src_keys; uint32_t entries;
     float* prows; uint32_t* pkeys;
-    // input side only (in a joint launch): finished sums go to the delta buffer (rows, keys) instead of
-    // into M; level = 1 for the first pass over the input-side kernel's slots, cp = its pairs per chunk
+    // input side only, beside the output side's first walk: finished sums go to the delta buffer (rows, keys)
+    // instead of into M; level = 1 for the first pass over the input-side kernel's slots, cp = its pairs per chunk
     float* defer_rows = nullptr; uint32_t* defer_keys = nullptr; uint32_t level = 0, cp = 0;
     const CallScalars* dev = nullptr;      // optional: the learning rate is read from here
 };
@@ -239,7 +239,7 @@ void launch_apply(const ApplyDelta& x, RowGeom g, bool shared, hipStream_t st); 
 
 // Parts of one update that do not depend on each other, in ONE launch (each may be absent): the
 // output side's level-1 kernel (wfirst; its border slots already cleared) or one of its higher
-// levels (wtail), one higher level of the input side (utail, with defer_rows), the write-back of the
+// levels (wtail), one higher level of the input side (utail; with defer_rows beside wfirst), the write-back of the
 // delta buffer (not beside wfirst, which reads U), and one step of the loss of the fused form
 // (loss_step 1: dots -> block sums in loss_tmp; 2: block sums -> *loss_out).
 struct AdjustStage {

@@ -129,7 +129,7 @@ template <int G, int NV, int THREADS> struct TailLds {
     uint32_t out_key[2];                                  // the block's own head and tail slot
 };
 
-template <int G, int NV, int THREADS, bool DEFER, class SL>
+template <int G, int NV, int THREADS, bool DEFER, int WHICH, class SL>
 __device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32_t vb, TailLds<G, NV, THREADS>& lds) {
     constexpr int GROUPS = THREADS / G, CB = tail_block(G), C = CB / GROUPS;
     constexpr int D = NV == 1 && (DEFER || C == 8) ? 8 : (NV <= 2 ? 4 : 2);
@@ -142,7 +142,7 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32
     const bool more = base + CB < a.entries;              // a block follows
     const uint32_t d4 = a.g.d4;
     const uint64_t s4 = a.g.stride4;
-    const Rows<G, NV, SL, 1> dst(sl, a.dst, a.g, l);      // (DEFER: not used)
+    const Rows<G, NV, SL, WHICH> dst(sl, a.dst, a.g, l);  // (DEFER: not used)
     int any = 0;
     for (int i = threadIdx.x; i < CB + 2; i += THREADS) {
         const int64_t pos = (int64_t)base - 1 + i;
@@ -286,7 +286,7 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32
 template <int G, int NV, int THREADS, class SL>
 __global__ __launch_bounds__(THREADS) void tail_kernel(SegArgs a, SL sl) {
     __shared__ TailLds<G, NV, THREADS> lds;
-    tail_body<G, NV, THREADS, false>(a, sl, blockIdx.x, lds);
+    tail_body<G, NV, THREADS, false, 1>(a, sl, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------------------------
@@ -633,8 +633,11 @@ void launch_apply(const ApplyDelta& x, RowGeom g, bool shared, hipStream_t st) {
 // ---------------------------------------------------------------------------------------------
 // One launch for parts of the update that do not depend on each other: a walk of the output side
 // (its level-1 kernel when FIRST, else one of its higher levels), one higher level of the input
-// side (which parks its sums in the delta buffer), one step of the loss, and -- once the output side's
-// first walk has read U and the input side's levels are done -- the write-back of the delta buffer.
+// side (beside the first walk, which reads U, it parks its sums in the delta buffer, later it adds them to U),
+// one step of the loss, and, once that walk is done, the write-back of the delta buffer: a row of U has one run,
+// so it gets its sum from one of these alone.  (Write-back behind all of the input side's levels instead, a launch
+// more wherever there are three: four announced steps of 65 536 pairs, d = 100, 701 us against 664, a plain
+// one of 1999, d = 300, 62 against 60.)
 // Each block does one part, told by its number.  The update is a chain of dependent launches; this
 // keeps everything that can run beside the output side out of that chain, without a second stream
 // (whose event waits cost about 10 us each: the step of 65 536 pairs, d = 100, spent 90 us of 220 on
@@ -659,7 +662,8 @@ __global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? (S
     __shared__ double red[THREADS / 64];
     uint32_t b = blockIdx.x;                               // the input side's level first: its blocks run longest
     if (b < s.u_blocks) {
-        tail_body<G, NV, THREADS, true>(s.u, OneMatrix{}, b, lds);
+        if (FIRST) tail_body<G, NV, THREADS, true, 0>(s.u, OneMatrix{}, b, lds);
+        else tail_body<G, NV, THREADS, false, 0>(s.u, sl, b, lds);
         return;
     }
     b -= s.u_blocks;
@@ -671,7 +675,7 @@ __global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? (S
     b -= s.loss_blocks;
     if (b < s.w_blocks) {
         if (FIRST) wown_body<G, NV, D>(s.w, sl, b);
-        else tail_body<G, NV, THREADS, false>(s.w, sl, b, lds);
+        else tail_body<G, NV, THREADS, false, 1>(s.w, sl, b, lds);
         return;
     }
     b -= s.w_blocks;
@@ -683,7 +687,7 @@ __global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? (S
 template <int G, int NV>
 __global__ __launch_bounds__(adj_threads(G)) void input_tail_kernel(SegArgs a) {
     __shared__ TailLds<G, NV, adj_threads(G)> lds;
-    tail_body<G, NV, adj_threads(G), true>(a, OneMatrix{}, blockIdx.x, lds);
+    tail_body<G, NV, adj_threads(G), true, 0>(a, OneMatrix{}, blockIdx.x, lds);
 }
 
 void launch_input_tail(const TailArgs& t, hipStream_t st) {
