@@ -136,11 +136,6 @@ struct w2v_shard {
     uint32_t* err = nullptr;        // sticky device flag
     uint32_t* static_ws = nullptr;  // this device's copy of the no-allocation scratch array
     uint64_t updates = 0;           // update calls seen (adjust / train_minibatch, either variant)
-    IndexPrologue* prologue_sink = nullptr;  // set while a step is captured: the first launch of the
-                                             // step is not queued but handed back (it takes the
-                                             // caller's arrays, which change from call to call)
-    const CallScalars* call_dev = nullptr;   // set while a step is captured into a graph: the
-                                    // kernels then read seed and learning rate from device memory
     // scratch: one region, carved per call
     char* ws = nullptr;
     size_t ws_cap = 0;
@@ -213,12 +208,12 @@ int ensure_ws(w2v_shard* sh, size_t bytes) { return ensure_region(sh->ws, sh->ws
 struct Phase {
     w2v_shard* sh; int phase; hipStream_t st; hipEvent_t a = nullptr, b = nullptr;
     Phase(w2v_shard* s, int ph, hipStream_t stream) : sh(s), phase(ph), st(stream) {
-        if (!sh->timing) return;
+        if (!sh || !sh->timing) return;
         a = grab(); b = grab();
         if (a && b) (void)hipEventRecord(a, st);
     }
     ~Phase() {
-        if (!sh->timing || !a || !b) return;
+        if (!sh || !sh->timing || !a || !b) return;
         (void)hipEventRecord(b, st);
         sh->spans.push_back(TimedSpan{phase, a, b});
     }
@@ -279,6 +274,7 @@ struct Plan {
     float* pe_rows; uint32_t* pe_keys;     // level 2 slots, input side (the two sides' tails may overlap)
     uint32_t slots_w1;                     // output side, level 1 slots of this minibatch
     bool wfill_done;                       // the output side's border slots are cleared already
+    bool one_stream;                       // everything on the caller's stream, and without timing spans
     size_t bytes;
 };
 
@@ -400,24 +396,24 @@ int queue_keys_and_sorts(w2v_shard* sh, Plan& p, const uint32_t* in_idx, const u
 
     const NoiseTable nt{sh->bins, sh->V};
     const bool small = group_small(p.M, p.n);
-    if (!sh->overlap || p.own_rows || small) {
+    w2v_shard* spans = p.one_stream ? nullptr : sh;
+    if (!sh->overlap || p.one_stream || p.own_rows || small) {
         // keys, checked inputs and the fills in one launch
         const SortJob jobs[2] = {{p.keys, p.M, p.wb0, p.wb1, skw, sidx},
                                  {p.in_safe, p.n, p.ub0, p.ub1, sku, perm}};
         {
-            Phase ph(sh, W2V_PH_NEG, st);
+            Phase ph(spans, W2V_PH_NEG, st);
             IndexPrologue pro{};
             pro.nt = nt; pro.out_idx = out_idx; pro.n = p.n; pro.T = p.T;
             pro.seed_lo = (uint32_t)seed; pro.seed_hi = (uint32_t)(seed >> 32);
-            pro.keys = p.keys; pro.dev = sh->call_dev; pro.in_idx = in_idx; pro.in_safe = p.in_safe;
+            pro.keys = p.keys; pro.in_idx = in_idx; pro.in_safe = p.in_safe;
             pro.err = sh->err;
             if (!small) pro.fill[0] = sort_clear_job(jobs, 2, p.sort_tmp);
             pro.fill[1] = wseg_fill_job(p.pb_keys, p.M);
             p.wfill_done = true;
-            if (sh->prologue_sink) *sh->prologue_sink = pro;
-            else launch_index_prologue(pro, st);
+            launch_index_prologue(pro, st);
         }
-        Phase ph(sh, W2V_PH_SORT, st);
+        Phase ph(spans, W2V_PH_SORT, st);
         sort_and_mark(jobs, bits, p.sort_tmp, sh->err, p.own_rows, true, &p.keys, st);
         return W2V_OK;
     }
@@ -428,7 +424,7 @@ int queue_keys_and_sorts(w2v_shard* sh, Plan& p, const uint32_t* in_idx, const u
     HIP_TRY(hipStreamWaitEvent(wst, sh->ev_fork, 0));
     {
         Phase ph(sh, W2V_PH_NEG, wst);
-        launch_dest_keys(nt, out_idx, p.n, k, seed, p.keys, sh->err, wst, sh->call_dev);
+        launch_dest_keys(nt, out_idx, p.n, k, seed, p.keys, sh->err, wst);
     }
     HIP_TRY(hipEventRecord(sh->ev_keys, wst));
     {
@@ -526,7 +522,7 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
                   const uint32_t* perm, const uint32_t* skw, const uint32_t* sidx,
                   const float* coeffs_in, float* coeffs_out, bool fused, float alpha,
                   double* loss_out, bool join_sorts, hipStream_t st) {
-    const CallScalars* dev = ws_owner->call_dev;
+    w2v_shard* spans = p.one_stream ? nullptr : ws_owner;
     const bool alone = adjust_walk_alone(p.M, to.g);
     // From 2^22 slots on the kernels after the output side's walk are bound by memory, shared with each other
     // and with the sorts of an announced minibatch, and not by their own chain of latencies: they take small
@@ -541,14 +537,13 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
         p.wfill_done = true;
     }
     {
-        Phase ph(ws_owner, W2V_PH_USIDE, st);
+        Phase ph(spans, W2V_PH_USIDE, st);
         USideArgs a{};
         a.U = to.U; a.W = to.W; a.slices = to.slices; a.g = to.g; a.skey = sku; a.perm = perm; a.keys = p.keys;
         a.n = p.n; a.T = p.T; a.coeffs_in = coeffs_in; a.coeffs_out = coeffs_out;
         a.dots_out = (fused && loss_out) ? p.dots : nullptr; a.delta = p.delta; a.dkey = p.dkey;
         a.prows = p.pa_rows; a.pkeys = p.pa_keys; a.fused = fused;
         a.own_rows = p.own_rows; a.alpha = alpha;
-        a.dev = dev;
         if (!p.wfill_done) {
             const FillJob f = wseg_fill_job(p.pb_keys, p.M);
             a.clear_keys = f.p; a.clear_count = f.count;
@@ -571,20 +566,20 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
     auto input_level = [&](bool defer) {
         TailArgs t{to.U, to.slices, to.g, alpha, us.src_rows, us.src_keys, us.slots, us.dst_rows, us.dst_keys};
         if (defer) { t.defer_rows = p.delta; t.defer_keys = p.dkey; t.cp = cp; }
-        t.level = ++us.level; t.dev = dev;
+        t.level = ++us.level;
         return t;
     };
     auto w_level = [&]() {
         TailArgs t{to.W, to.slices, to.g, alpha, ws.src_rows, ws.src_keys, ws.slots, ws.dst_rows, ws.dst_keys};
-        t.level = ++ws.level; t.dev = dev;
+        t.level = ++ws.level;
         return t;
     };
-    const ApplyDelta apply{to.U, to.slices, p.delta, p.dkey, p.n, alpha, dev};
+    const ApplyDelta apply{to.U, to.slices, p.delta, p.dkey, p.n, alpha};
     WSideArgs w{};
     w.U = to.U; w.W = to.W; w.slices = to.slices; w.g = to.g; w.skey = skw; w.sidx = sidx; w.M = p.M; w.T = p.T;
     w.in_idx = p.in_safe; w.coeffs = fused ? coeffs_out : coeffs_in; w.alpha = alpha;
-    w.prows = p.pb_rows; w.pkeys = p.pb_keys; w.skip_alone = p.own_rows; w.dev = dev;
-    const bool two = alone && ws_owner->overlap && ensure_side_stream(ws_owner) == W2V_OK;
+    w.prows = p.pb_rows; w.pkeys = p.pb_keys; w.skip_alone = p.own_rows;
+    const bool two = alone && ws_owner->overlap && !p.one_stream && ensure_side_stream(ws_owner) == W2V_OK;
     if (alone) {
         // A large minibatch: the input side's levels and the loss run beside the output side's walk on the
         // second stream, the write-back there beside the output side's levels (the same launches on one
@@ -595,19 +590,19 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
             (void)hipStreamWaitEvent(side, ws_owner->ev_coeffs, 0);
         }
         if (loss_step) {
-            Phase ph(ws_owner, W2V_PH_COEFF, side);
+            Phase ph(spans, W2V_PH_COEFF, side);
             launch_loss_from_dots(p.dots, p.n, p.T, p.loss_tmp, loss_out, side);
             loss_step = 0;
         }
         {
-            Phase ph(ws_owner, W2V_PH_APPLY, side);
+            Phase ph(spans, W2V_PH_APPLY, side);
             while (us.slots) {
                 launch_input_tail(input_level(true), side);
                 advance(us);
             }
         }
         {
-            Phase ph(ws_owner, W2V_PH_WSIDE, st);
+            Phase ph(spans, W2V_PH_WSIDE, st);
             launch_wseg(w, st);
         }
         if (two) {
@@ -615,12 +610,12 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
             (void)hipStreamWaitEvent(side, ws_owner->ev_wdone, 0);
         }
         {
-            Phase ph(ws_owner, W2V_PH_APPLY, side);
+            Phase ph(spans, W2V_PH_APPLY, side);
             launch_apply(apply, to.g, shared, side);
         }
         if (two) (void)hipEventRecord(ws_owner->ev_tails, side);
         {
-            Phase ph(ws_owner, W2V_PH_APPLY, st);
+            Phase ph(spans, W2V_PH_APPLY, st);
             while (ws.slots) {
                 launch_tail(w_level(), st, shared);
                 advance(ws);
@@ -630,7 +625,7 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
         return;
     }
     for (bool first = true, any = true; any; first = false) {
-        Phase ph(ws_owner, first ? W2V_PH_WSIDE : W2V_PH_APPLY, st);
+        Phase ph(spans, first ? W2V_PH_WSIDE : W2V_PH_APPLY, st);
         AdjustStage x;
         x.g = to.g; x.slices = to.slices;
         TailArgs wt{}, ut{};
@@ -1163,26 +1158,22 @@ extern "C" int w2v_prefetch_cancel(w2v_shard* sh) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// a training step captured once and replayed (small minibatches are bound by launches, not bytes)
+// a training step of fixed size on one stream (small minibatches are bound by launches, not bytes)
 // ---------------------------------------------------------------------------------------------
+// A run queues the step's six or seven launches itself.  (Replayed from a HIP graph they were, while a step had some
+// thirty: what the graph saves the host, its replay costs the device between one step and the next.  Eight
+// steps, d = 100, k = 5, replayed and queued, us: 500 pairs 428, 362; 4096 511, 445; 15 000 699, 625.)
 struct w2v_step_graph {
     w2v_shard* sh = nullptr;
     uint32_t n = 0, k = 0;
-    IndexPrologue first{};              // the step's first launch: queued by every run, with that
-                                        // run's arrays and seed (not part of the graph)
-    CallScalars* scalars = nullptr;     // the captured kernels read seed and learning rate from here
-    const char* ws_at_capture = nullptr; // the shard's scratch region the captured kernels point into
-    hipGraph_t graph = nullptr;
-    hipGraphExec_t exec = nullptr;
+    double* loss = nullptr;
+    const char* ws_at_creation = nullptr;
+    Plan plan(char* base) const {
+        Plan p = make_plan(base, n, k, sh->g.stride4, loss ? 1u : 0u, true, true, sh->own_rows ? sh->V : 0u);
+        p.one_stream = true;
+        return p;
+    }
 };
-
-static void free_step_graph(w2v_step_graph* g) {
-    if (!g) return;
-    if (g->exec) (void)hipGraphExecDestroy(g->exec);
-    if (g->graph) (void)hipGraphDestroy(g->graph);
-    if (g->scalars) (void)hipFree(g->scalars);
-    delete g;
-}
 
 extern "C" int w2v_step_graph_create(w2v_shard* sh, uint32_t n, uint32_t k, double* loss,
                                      w2v_step_graph** out) {
@@ -1194,51 +1185,10 @@ extern "C" int w2v_step_graph_create(w2v_shard* sh, uint32_t n, uint32_t k, doub
     if (n == 0) return fail(W2V_ERR_ARG, "a captured step needs at least one pair");
     w2v_step_graph* g = new (std::nothrow) w2v_step_graph();
     if (!g) return fail(W2V_ERR_ALLOC, "host allocation failed");
-    g->sh = sh; g->n = n; g->k = k;
-    hipStream_t cap = nullptr;
-    auto bail = [&](int code) { if (cap) (void)hipStreamDestroy(cap); free_step_graph(g); return code; };
-    hipError_t e = hipMalloc((void**)&g->scalars, 256);
-    if (e == hipSuccess) e = hipMemset(g->scalars, 0, 256);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return bail(fail(W2V_ERR_ALLOC, "allocating the scalar block of a captured step failed: %s",
-                         hipGetErrorString(e)));
-    }
-    // everything the step allocates must exist before the capture begins: its scratch ...
-    const uint32_t own = sh->own_rows ? sh->V : 0u;
-    Plan sz = make_plan(nullptr, n, k, sh->g.stride4, loss ? 1u : 0u, true, true, own);
-    rc = ensure_ws(sh, sz.bytes);
-    if (rc) return bail(rc);
-    e = hipDeviceSynchronize();
-    if (e == hipSuccess) e = hipStreamCreateWithFlags(&cap, hipStreamNonBlocking);
-    if (e != hipSuccess) return bail(fail(W2V_ERR_HIP, "set-up of the capture failed: %s", hipGetErrorString(e)));
-    // ... and the capture runs the step on ONE stream, without timing spans and without looking at
-    // announced minibatches (none can match the stand-in arrays).  The step's first launch -- keys,
-    // checked inputs, fills -- is the only one that reads the caller's arrays: it is handed back
-    // instead of captured, and every run queues it itself in front of the graph.  (Captured with its side stream,
-    // as parallel branches of the graph, a 4096-pair step replays in 0.176 ms instead of 0.115 ms:
-    // the two sorts are then separate chains of launches, and branches cost more than they hide.)
-    const bool overlap = sh->overlap, timing = sh->timing;
-    sh->overlap = false; sh->timing = false; sh->call_dev = g->scalars; sh->prologue_sink = &g->first;
-    e = hipStreamBeginCapture(cap, hipStreamCaptureModeThreadLocal);
-    if (e == hipSuccess) {
-        w2v_shard* one[1] = {sh};
-        const uint32_t* stand_in = (const uint32_t*)g->scalars;      // recorded, never read
-        rc = w2v_train_minibatch(one, 1, stand_in, stand_in, n, k, 0, 0.f, loss, cap);
-        hipError_t e2 = hipStreamEndCapture(cap, &g->graph);
-        if (rc == W2V_OK && e2 != hipSuccess) e = e2;
-    }
-    sh->overlap = overlap; sh->timing = timing; sh->call_dev = nullptr; sh->prologue_sink = nullptr;
-    if (rc == W2V_OK && e == hipSuccess && g->first.keys == nullptr)
-        rc = fail(W2V_ERR_STATE, "the captured step did not hand back its first launch");
-    if (rc) return bail(rc);
-    if (e == hipSuccess) e = hipGraphInstantiate(&g->exec, g->graph, nullptr, nullptr, 0);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return bail(fail(W2V_ERR_HIP, "capturing the step failed: %s", hipGetErrorString(e)));
-    }
-    (void)hipStreamDestroy(cap);
-    g->ws_at_capture = sh->ws;
+    g->sh = sh; g->n = n; g->k = k; g->loss = loss;
+    rc = ensure_ws(sh, g->plan(nullptr).bytes);
+    if (rc) { delete g; return rc; }
+    g->ws_at_creation = sh->ws;
     *out = g;
     return W2V_OK;
 }
@@ -1246,20 +1196,22 @@ extern "C" int w2v_step_graph_create(w2v_shard* sh, uint32_t n, uint32_t k, doub
 extern "C" int w2v_step_graph_run(w2v_step_graph* g, const uint32_t* in_idx, const uint32_t* out_idx,
                                   uint64_t seed, float alpha, void* stream) {
     if (!g || !in_idx || !out_idx) return fail(W2V_ERR_NULL, "NULL argument");
-    int rc = check_device(g->sh);
+    w2v_shard* sh = g->sh;
+    int rc = check_device(sh);
     if (rc) return rc;
-    if (g->sh->ws != g->ws_at_capture)
+    if (sh->ws != g->ws_at_creation)
         return fail(W2V_ERR_STATE, "the shard's scratch region was reallocated by a larger call after this "
                     "step was captured: create the graph again");
     hipStream_t st = (hipStream_t)stream;
-    IndexPrologue first = g->first;
-    first.in_idx = in_idx; first.out_idx = out_idx;
-    first.seed_lo = (uint32_t)seed; first.seed_hi = (uint32_t)(seed >> 32);
-    first.dev = nullptr; first.scalars_out = g->scalars; first.alpha = alpha;
-    launch_index_prologue(first, st);
-    HIP_TRY(hipGraphLaunch(g->exec, st));
-    g->sh->updates++;
-    g->sh->last_update_fused = true;
+    Plan p = g->plan(sh->ws);
+    uint32_t *sku, *perm, *skw, *sidx;
+    bool join = false;
+    rc = queue_keys_and_sorts(sh, p, in_idx, out_idx, g->k, seed, &sku, &perm, &skw, &sidx, &join, st);
+    if (rc) return rc;
+    queue_adjust(sh, Target{sh->U, sh->W, nullptr, sh->g}, p, sku, perm, skw, sidx, nullptr, p.coeffs, true, alpha,
+                 g->loss, join, st);
+    sh->updates++;
+    sh->last_update_fused = true;
     HIP_TRY(hipGetLastError());
     return W2V_OK;
 }
@@ -1267,7 +1219,7 @@ extern "C" int w2v_step_graph_run(w2v_step_graph* g, const uint32_t* in_idx, con
 extern "C" int w2v_step_graph_destroy(w2v_step_graph* g) {
     if (!g) return W2V_OK;
     (void)hipDeviceSynchronize();
-    free_step_graph(g);
+    delete g;
     return W2V_OK;
 }
 

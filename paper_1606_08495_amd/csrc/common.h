@@ -58,11 +58,6 @@ constexpr uint32_t KEY_ZERO = 0x80000000u;   // flag: slot belongs to the row bu
 constexpr uint32_t KEY_MASK = 0x7FFFFFFFu;
 constexpr uint32_t KEY_ALONE = 0x80000000u;  // slot-ordered keys: no other slot names this row
 
-// The per-call scalars a captured graph cannot take as kernel arguments (those are fixed when the
-// graph is captured): where a `dev` pointer is given, the kernels read the minibatch seed and the
-// learning rate from this block in device memory instead of from their arguments.
-struct CallScalars { uint32_t seed_lo, seed_hi; float alpha; uint32_t reserved; };
-
 // ---- launch wrappers (defined in the .hip files) -------------------------------------------------
 struct NoiseTable { const uint2* bins; uint32_t V; };   // {keep threshold, alias} per word
 
@@ -82,24 +77,20 @@ void launch_set_rows(const RowPart& part, const float* src, const uint32_t* rows
 // replaced by 0.  in_safe[p] (launch_check_inputs) is the checked copy of in_idx[p] that every
 // later kernel uses.
 void launch_dest_keys(NoiseTable nt, const uint32_t* out_idx, uint32_t n, uint32_t k, uint64_t seed,
-                      uint32_t* keys, uint32_t* err, hipStream_t st,
-                      const CallScalars* dev = nullptr);
+                      uint32_t* keys, uint32_t* err, hipStream_t st);
 // keys[sidx[i]] |= KEY_ALONE for every sorted entry i whose neighbours carry other keys.
 void launch_mark_alone(const uint32_t* skey, const uint32_t* sidx, uint32_t M, uint32_t* keys,
                        hipStream_t st);
 void launch_check_inputs(const uint32_t* in_idx, uint32_t n, uint32_t V, uint32_t* in_safe,
                          uint32_t* err, hipStream_t st);
 // launch_dest_keys + launch_check_inputs + two fills of 32-bit words in one launch (n pairs, T = k+1
-// slots each).  With `dev` the seed is read from device memory; with `scalars_out` the seed and the
-// learning rate given here are also written there, for the kernels that follow.
+// slots each).
 struct FillJob { uint32_t* p; uint32_t count; uint32_t value; };
 struct IndexPrologue {
     NoiseTable nt; const uint32_t* out_idx; uint32_t n, T; uint32_t seed_lo, seed_hi; uint32_t* keys;
-    const CallScalars* dev;
     const uint32_t* in_idx; uint32_t* in_safe;
     uint32_t* err;
     FillJob fill[2];
-    CallScalars* scalars_out; float alpha;
     uint32_t b_check, b_fill[2];        // first block of each part (set by the launcher)
 };
 void launch_index_prologue(IndexPrologue a, hipStream_t st);
@@ -190,7 +181,6 @@ struct USideArgs {
     // of the minibatch names; the kernel then writes W[row] += alpha * g * u itself (nobody else
     // reads or writes that row in this minibatch) and the output side must leave those slots out.
     bool own_rows; float alpha;
-    const CallScalars* dev;      // optional: the learning rate is read from here
     uint32_t* clear_keys; uint32_t clear_count;   // words set to KEY_NONE on the way (wseg_fill_job)
 };
 void launch_useg(const USideArgs& a, hipStream_t st);
@@ -209,7 +199,6 @@ struct WSideArgs {
     bool skip_alone;             // entries whose neighbours carry other keys are handled elsewhere
     const uint32_t* in_idx; const float* coeffs; float alpha;
     float* prows; uint32_t* pkeys;
-    const CallScalars* dev;      // optional: the learning rate is read from here
 };
 // (the cells' border slots must read KEY_NONE when the kernel starts: launch_wseg_fill writes that)
 FillJob wseg_fill_job(uint32_t* pkeys, uint32_t M);
@@ -225,7 +214,6 @@ struct TailArgs {
     // input side only, beside the output side's first walk: finished sums go to the delta buffer (rows, keys)
     // instead of into M; level = 1 for the first pass over the input-side kernel's slots, cp = its pairs per chunk
     float* defer_rows = nullptr; uint32_t* defer_keys = nullptr; uint32_t level = 0, cp = 0;
-    const CallScalars* dev = nullptr;      // optional: the learning rate is read from here
 };
 void launch_tail(const TailArgs& a, hipStream_t st, bool shared = false);    // shared: memory is, small blocks
 void launch_input_tail(const TailArgs& a, hipStream_t st);       // with defer_rows
@@ -233,7 +221,6 @@ void launch_input_tail(const TailArgs& a, hipStream_t st);       // with defer_r
 // U[dkey[ps]] += alpha * delta[ps] wherever dkey[ps] != KEY_NONE.
 struct ApplyDelta {
     float* U; const Slices* slices; const float* delta; const uint32_t* dkey; uint32_t n; float alpha;
-    const CallScalars* dev;
 };
 void launch_apply(const ApplyDelta& x, RowGeom g, bool shared, hipStream_t st);   // shared: memory is, one row in flight
 

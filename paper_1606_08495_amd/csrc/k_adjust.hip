@@ -93,7 +93,6 @@ struct SegArgs {
     // input side: finished sums are not added to dst but parked in the delta buffer
     float4* defer_rows; uint32_t* defer_keys;
     uint32_t level, cp;                // level of this pass (1 = first), pairs per input-side chunk
-    const CallScalars* dev;            // optional: the learning rate is read from here
 };
 
 // ---------------------------------------------------------------------------------------------
@@ -136,7 +135,7 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32
     static_assert(C % 2 == 0, "a border's two slots fall into one part");
     constexpr int ROW4 = G * NV;                          // float4 of a row held in LDS
     auto& s_raw = lds.raw; auto& s_list = lds.list; auto& s_rows = lds.rows; auto& s_gkey = lds.gkey;
-    const float alpha = a.dev ? a.dev->alpha : a.alpha;
+    const float alpha = a.alpha;
     const int l = threadIdx.x % G, grp = threadIdx.x / G;
     const uint32_t base = vb * (uint32_t)CB, count = min((uint32_t)CB, a.entries - base);
     const bool more = base + CB < a.entries;              // a block follows
@@ -327,7 +326,7 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32
     constexpr int C = WOWN_C;
     const int L = 1 << a.cell_log2;                        // a multiple of C
     static_assert(C == 16 && G >= 16, "grid shapes");
-    const float alpha = a.dev ? a.dev->alpha : a.alpha;
+    const float alpha = a.alpha;
     __shared__ uint32_t s_key[GROUPS][WOWN_WIN];
     __shared__ uint32_t s_srow[GROUPS][WOWN_E];
     __shared__ float s_coef[GROUPS][WOWN_E];
@@ -522,7 +521,7 @@ static SegArgs seg_args_of(const WSideArgs& w) {
     SegArgs a{};
     a.src = (const float4*)w.U; a.dst = (float4*)w.W; a.g = w.g; a.skey = w.skey; a.sidx = w.sidx;
     a.in_idx = w.in_idx; a.coeffs = w.coeffs; a.entries = w.M; a.T = w.T;
-    a.alpha = w.alpha; a.prows = (float4*)w.prows; a.pkeys = w.pkeys; a.dev = w.dev;
+    a.alpha = w.alpha; a.prows = (float4*)w.prows; a.pkeys = w.pkeys;
     a.skip_alone = w.skip_alone; a.cell_log2 = wown_cell_log2(w.M);
     return a;
 }
@@ -532,7 +531,7 @@ static SegArgs seg_args_of(const TailArgs& t) {
     a.src = (const float4*)t.src_rows; a.dst = (float4*)t.M; a.g = t.g; a.skey = t.src_keys;
     a.sidx = nullptr; a.in_idx = nullptr; a.coeffs = nullptr; a.entries = t.entries; a.T = 1;
     a.skip_alone = false;
-    a.alpha = t.alpha; a.prows = (float4*)t.prows; a.pkeys = t.pkeys; a.dev = t.dev;
+    a.alpha = t.alpha; a.prows = (float4*)t.prows; a.pkeys = t.pkeys;
     a.defer_rows = (float4*)t.defer_rows; a.defer_keys = t.defer_keys; a.level = t.level; a.cp = t.cp;
     return a;
 }
@@ -575,12 +574,11 @@ void launch_tail(const TailArgs& t, hipStream_t st, bool shared) {
 constexpr int APPLY_P = 16;
 struct ApplyArgs {
     float4* U; RowGeom g; const float4* delta; const uint32_t* dkey; uint32_t n; float alpha;
-    const CallScalars* dev;
 };
 
 template <int G, int NV, int THREADS, int D, class SL>
 __device__ __forceinline__ void apply_body(const ApplyArgs& a, const SL& sl, uint32_t vb) {
-    const float alpha = a.dev ? a.dev->alpha : a.alpha;
+    const float alpha = a.alpha;
     const int l = threadIdx.x % G;
     const uint32_t base = (vb * (uint32_t)THREADS + threadIdx.x) / G * APPLY_P;
     const uint32_t mine = l < APPLY_P && base + l < a.n ? a.dkey[base + l] : KEY_NONE;
@@ -617,7 +615,7 @@ __global__ __launch_bounds__(adj_threads(G)) void apply_kernel(ApplyArgs a, SL s
 
 void launch_apply(const ApplyDelta& x, RowGeom g, bool shared, hipStream_t st) {
     if (x.n == 0) return;
-    const ApplyArgs a{(float4*)x.U, g, (const float4*)x.delta, x.dkey, x.n, x.alpha, x.dev};
+    const ApplyArgs a{(float4*)x.U, g, (const float4*)x.delta, x.dkey, x.n, x.alpha};
 #define CALL_ROWS(G, NV, D)                                                                               \
     with_slices(x.slices, [&](const auto& sl) {                                                            \
         hipLaunchKernelGGL((apply_kernel<G, NV, D, std::decay_t<decltype(sl)>>),                          \
@@ -728,7 +726,7 @@ void launch_adjust_stage(const AdjustStage& x, hipStream_t st) {
     if (x.utail) s.u = seg_args_of(*x.utail);
     if (x.apply && !first)
         s.apply = ApplyArgs{(float4*)x.apply->U, x.g, (const float4*)x.apply->delta, x.apply->dkey, x.apply->n,
-                            x.apply->alpha, x.apply->dev};
+                            x.apply->alpha};
     s.loss_step = x.loss_step;
     if (x.loss_step) {
         s.dots = x.dots; s.total = x.n * x.T; s.T = x.T; s.block_loss = x.loss_tmp;
@@ -779,7 +777,7 @@ __device__ __forceinline__ void coefficients(const float (&sdot)[N], uint32_t j0
 template <int G, int NV, int TB, bool FUSED, bool OWN, class SL>
 __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_t CP, SL sl) {
     constexpr bool NEED_U = FUSED || OWN;      // the pair's input row: for the dots, for own rows
-    const float alpha = a.dev ? a.dev->alpha : a.alpha;
+    const float alpha = a.alpha;
     constexpr int GROUPS = USEG_THREADS / G;
     // The chunk's indices are staged in LDS first (two dependent gathers for the whole chunk), so
     // that the row loads of the main loop depend on nothing but LDS reads.
@@ -945,7 +943,7 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
 template <int G, int NV, int T, int PB, bool FUSED, bool OWN, class SL>
 __global__ __launch_bounds__(USEG_THREADS, (SL::ONE ? 5 : 4)) void useg_multi_kernel(USideArgs a, uint32_t CP, SL sl) {
     constexpr bool NEED_U = FUSED || OWN;
-    const float alpha = a.dev ? a.dev->alpha : a.alpha;
+    const float alpha = a.alpha;
     constexpr int GROUPS = USEG_THREADS / G;
     constexpr int MAXP = useg_maxp(G), MAXE = MAXP * T;
     __shared__ uint32_t s_key[GROUPS][MAXE];

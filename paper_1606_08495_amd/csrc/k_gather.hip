@@ -196,10 +196,9 @@ __device__ __forceinline__ void dest_key_item(const uint2* __restrict__ bins, ui
 
 __global__ __launch_bounds__(256) void dest_keys_kernel(const uint2* __restrict__ bins, uint32_t V,
                                                         const uint32_t* __restrict__ out_idx,
-                                                        uint32_t n, uint32_t T, uint32_t k0_arg,
-                                                        uint32_t k1_arg, uint32_t* __restrict__ keys,
-                                                        uint32_t* err, const CallScalars* dev) {
-    const uint32_t k0 = dev ? dev->seed_lo : k0_arg, k1 = dev ? dev->seed_hi : k1_arg;
+                                                        uint32_t n, uint32_t T, uint32_t k0,
+                                                        uint32_t k1, uint32_t* __restrict__ keys,
+                                                        uint32_t* err) {
     dest_key_item(bins, V, out_idx, n, T, k0, k1, keys, err, blockIdx.x * 256 + threadIdx.x);
 }
 
@@ -219,12 +218,12 @@ __global__ __launch_bounds__(256) void mark_alone_kernel(const uint32_t* __restr
 }
 
 void launch_dest_keys(NoiseTable nt, const uint32_t* out_idx, uint32_t n, uint32_t k, uint64_t seed,
-                      uint32_t* keys, uint32_t* err, hipStream_t st, const CallScalars* dev) {
+                      uint32_t* keys, uint32_t* err, hipStream_t st) {
     if (n == 0) return;
     uint32_t T = k + 1;
     hipLaunchKernelGGL(dest_keys_kernel, dim3(blocks_for((uint64_t)n * T, 256)), dim3(256), 0, st,
                        nt.bins, nt.V, out_idx, n, T, (uint32_t)seed, (uint32_t)(seed >> 32), keys,
-                       err, dev);
+                       err);
 }
 
 void launch_mark_alone(const uint32_t* skey, const uint32_t* sidx, uint32_t M, uint32_t* keys,
@@ -266,13 +265,8 @@ void launch_check_inputs(const uint32_t* in_idx, uint32_t n, uint32_t V, uint32_
 __global__ __launch_bounds__(256) void index_prologue_kernel(IndexPrologue a) {
     const uint32_t b = blockIdx.x;
     if (b < a.b_check) {
-        const uint32_t k0 = a.dev ? a.dev->seed_lo : a.seed_lo, k1 = a.dev ? a.dev->seed_hi : a.seed_hi;
-        dest_key_item(a.nt.bins, a.nt.V, a.out_idx, a.n, a.T, k0, k1, a.keys, a.err,
+        dest_key_item(a.nt.bins, a.nt.V, a.out_idx, a.n, a.T, a.seed_lo, a.seed_hi, a.keys, a.err,
                       b * 256 + threadIdx.x);
-        if (a.scalars_out && b == 0 && threadIdx.x == 0) {
-            a.scalars_out->seed_lo = a.seed_lo; a.scalars_out->seed_hi = a.seed_hi;
-            a.scalars_out->alpha = a.alpha;
-        }
     } else if (b < a.b_fill[0]) {
         check_input_item(a.in_idx, a.n, a.nt.V, a.in_safe, a.err, (b - a.b_check) * 256 + threadIdx.x);
     } else {

@@ -302,7 +302,7 @@ class Shard:
 
 
 class StepGraph:
-    """w2v_step_graph: w2v_train_minibatch on one shard for a fixed (n, k), captured once and replayed."""
+    """w2v_step_graph: w2v_train_minibatch on one shard for a fixed (n, k), prepared once."""
 
     def __init__(self, shard, n, k, loss=None):
         self.n, self.k, self.shard, self.loss = int(n), int(k), shard, loss
