@@ -142,6 +142,7 @@ struct w2v_shard {
     // scratch of the pair formation, apart from the training calls' so that the two may overlap
     char* pairs_ws = nullptr;
     size_t pairs_ws_cap = 0;
+    uint32_t* pairs_totals = nullptr;   // pinned: the kernels write what the host reads
     // second stream: the part of a call that can run beside its main kernels (key generation and
     // output-side sort; loss, the input side's higher levels, the write-back of the delta buffer),
     // forked from the caller's stream and joined back into it by events
@@ -698,6 +699,7 @@ extern "C" int w2v_shard_create_ex(uint32_t V, uint32_t d_total, uint32_t col_be
     hipError_t e = hipMalloc((void**)&sh->U, bytes);
     if (e == hipSuccess) e = hipMalloc((void**)&sh->W, bytes);
     if (e == hipSuccess) e = hipMalloc((void**)&sh->err, 256);
+    if (e == hipSuccess) e = hipHostMalloc((void**)&sh->pairs_totals, 256, hipHostMallocDefault);
     if (e != hipSuccess) {
         (void)hipGetLastError();
         int rc = fail(W2V_ERR_ALLOC, "allocating 2 x %zu bytes of vectors failed: %s", bytes,
@@ -705,13 +707,14 @@ extern "C" int w2v_shard_create_ex(uint32_t V, uint32_t d_total, uint32_t col_be
         if (sh->U) (void)hipFree(sh->U);
         if (sh->W) (void)hipFree(sh->W);
         if (sh->err) (void)hipFree(sh->err);
+        if (sh->pairs_totals) (void)hipHostFree(sh->pairs_totals);
         delete sh;
         return rc;
     }
     if (static_scratch(sh->device, &sh->static_ws) != 0) {
         int rc = fail(W2V_ERR_HIP, "hipGetSymbolAddress of the static scratch array failed on device %d",
                       sh->device);
-        (void)hipFree(sh->U); (void)hipFree(sh->W); (void)hipFree(sh->err);
+        (void)hipFree(sh->U); (void)hipFree(sh->W); (void)hipFree(sh->err); (void)hipHostFree(sh->pairs_totals);
         delete sh;
         return rc;
     }
@@ -723,7 +726,7 @@ extern "C" int w2v_shard_create_ex(uint32_t V, uint32_t d_total, uint32_t col_be
     if (le != hipSuccess || se != hipSuccess) {
         int rc = fail(W2V_ERR_HIP, "initialisation kernels failed: %s",
                       hipGetErrorString(le != hipSuccess ? le : se));
-        (void)hipFree(sh->U); (void)hipFree(sh->W); (void)hipFree(sh->err);
+        (void)hipFree(sh->U); (void)hipFree(sh->W); (void)hipFree(sh->err); (void)hipHostFree(sh->pairs_totals);
         delete sh;
         return rc;
     }
@@ -747,6 +750,7 @@ extern "C" int w2v_shard_destroy(w2v_shard* sh) {
     if (sh->err) (void)hipFree(sh->err);
     if (sh->ws) (void)hipFree(sh->ws);
     if (sh->pairs_ws) (void)hipFree(sh->pairs_ws);
+    if (sh->pairs_totals) (void)hipHostFree(sh->pairs_totals);
     if (sh->ev_fork) (void)hipEventDestroy(sh->ev_fork);
     if (sh->ev_keys) (void)hipEventDestroy(sh->ev_keys);
     if (sh->ev_join) (void)hipEventDestroy(sh->ev_join);
@@ -1763,7 +1767,7 @@ static int make_pairs_impl(w2v_shard* sh, const uint32_t* tokens, const uint64_t
         }
         return W2V_OK;
     }
-    size_t need = sizeof(uint32_t) * (pairs_scratch_u32(n_tokens, interleave) + 64) + 512;
+    size_t need = sizeof(uint32_t) * pairs_scratch_u32(n_tokens, interleave) + 512;
     rc = ensure_region(sh->pairs_ws, sh->pairs_ws_cap, need);
     if (rc) return rc;
     PairArgs a{};
@@ -1771,24 +1775,18 @@ static int make_pairs_impl(w2v_shard* sh, const uint32_t* tokens, const uint64_t
     a.token_base = token_base; a.epoch = epoch; a.seed = corpus_seed; a.B = B;
     a.keep = sh->has_tables ? sh->keep : nullptr; a.V = sh->V;
     a.in_idx = in_idx; a.out_idx = out_idx; a.capacity = capacity; a.interleave = interleave;
-    a.total_pairs = (uint32_t*)sh->pairs_ws;
-    if (cbow) {
-        a.ctx_off = cbow->ctx_off; a.centers = cbow->centers; a.cap_examples = cbow->cap_examples;
-        a.total_examples = (uint32_t*)sh->pairs_ws + 1;
-    }
-    a.scratch = (uint32_t*)sh->pairs_ws + 64;
+    HIP_TRY(hipHostGetDevicePointer((void**)&a.totals, sh->pairs_totals, 0));
+    if (cbow) { a.ctx_off = cbow->ctx_off; a.centers = cbow->centers; a.cap_examples = cbow->cap_examples; }
+    a.scratch = (uint32_t*)sh->pairs_ws;
     a.err = sh->err;
     {
         Phase ph(sh, W2V_PH_PAIRS, st);
         launch_make_pairs(a, st);
     }
     HIP_TRY(hipGetLastError());
-    uint32_t total[2] = {0, 0};
-    HIP_TRY(hipMemcpyAsync(total, a.total_pairs, sizeof(uint32_t) * (cbow ? 2 : 1),
-                           hipMemcpyDeviceToHost, st));
     HIP_TRY(hipStreamSynchronize(st));
-    *n_pairs = total[0];
-    if (cbow) *cbow->n_examples = total[1];
+    *n_pairs = sh->pairs_totals[0];
+    if (cbow) *cbow->n_examples = sh->pairs_totals[1];
     return W2V_OK;
 }
 

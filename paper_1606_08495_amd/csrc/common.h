@@ -133,15 +133,8 @@ void launch_sort_pairs(const uint32_t* keys_in, uint2* buf0, uint2* buf1, uint32
 bool group_small(uint32_t n0, uint32_t n1);      // whether arrays of n0 and n1 keys are taken that way
 void launch_group_jobs(const SortJob* jobs, int njobs, uint32_t bits, uint32_t* marked0, hipStream_t st);
 
-// Exclusive prefix sum of many uint32 whose sums per scan_tile() consecutive elements are known: the sums
-// are scanned in place (scan_scratch_u32(n) of them; total may be null; a second array of as many rides
-// along), then out[i] = exclusive prefix of in[i] >> shift.
-size_t scan_scratch_u32(uint32_t n);
-uint32_t scan_tile();
-void launch_scan_sums(uint32_t* sums, uint32_t nb, uint32_t* total, hipStream_t st, uint32_t* sums2 = nullptr,
-                      uint32_t* total2 = nullptr);
-void launch_scan_apply(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t shift, const uint32_t* sums,
-                       hipStream_t st);
+// Exclusive prefix sum of nb sums in place, and their total.
+void launch_scan_sums(uint32_t* sums, uint32_t nb, uint32_t* total, hipStream_t st);
 
 // ---- adjust ------------------------------------------------------------------------------------
 // Chunk sizes of the segmented reductions (entries per lane group).
@@ -248,10 +241,10 @@ struct PairArgs {
     uint32_t* in_idx; uint32_t* out_idx; uint64_t capacity;
     bool interleave;        // centers round-robin over the sentences instead of corpus order
     // bag-of-words examples (plain order only; in_idx may then be null): ctx_off[cap_examples+1],
-    // centers[cap_examples], *total_examples; out_idx holds the context words
-    uint32_t* ctx_off; uint32_t* centers; uint64_t cap_examples; uint32_t* total_examples;
-    uint32_t* scratch;      // pairs_scratch_u32(n_tokens, interleave) uint32
-    uint32_t* total_pairs;  // device, one uint32
+    // centers[cap_examples]; out_idx holds the context words
+    uint32_t* ctx_off; uint32_t* centers; uint64_t cap_examples;
+    uint32_t* scratch;      // pairs_scratch_u32(n_tokens, interleave) uint32, 8-byte aligned
+    uint32_t* totals;       // pairs, examples
     uint32_t* err;
 };
 size_t pairs_scratch_u32(uint32_t n_tokens, bool interleave);

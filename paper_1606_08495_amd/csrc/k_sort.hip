@@ -1,4 +1,4 @@
-// Device-wide exclusive scan and a stable least-significant-digit radix sort of (key, index)
+// Exclusive scan of a list of sums and a stable least-significant-digit radix sort of (key, index)
 // pairs, up to 8 bits per pass.  Used to group the contributions of adjust by destination row:
 // equal keys end up adjacent and, the sort being stable, in increasing order of their original
 // slot, so the order in which a row's contributions are summed is fixed by the input alone.
@@ -13,12 +13,9 @@ static inline unsigned blocks_for(uint64_t items, unsigned per_block) {
 }
 
 // ---------------------------------------------------------------------------------------------
-// Scan.  Tiles of 256 threads x 8 items: (1) per-tile sums (whoever makes the elements counts them),
-// (2) one block scans the sums with a running carry, (3) per-tile local scan plus the tile's offset.
+// Scan of a list of sums by one block with a running carry.
 // ---------------------------------------------------------------------------------------------
 constexpr int SCAN_THREADS = 256;
-constexpr int SCAN_ITEMS = 8;
-constexpr int SCAN_TILE = SCAN_THREADS * SCAN_ITEMS;
 
 // Exclusive scan of one value per thread across the first 256 threads of a block (larger blocks
 // pass through with the rest of their threads, for the barriers); returns the exclusive prefix
@@ -47,12 +44,8 @@ __device__ __forceinline__ uint32_t block_exclusive_scan(uint32_t x, uint32_t* w
 
 // (sixteen sums per thread and step: a running carry over n / 256 of them is two steps for two million)
 constexpr int SCAN_SUMS_ITEMS = 16;
-__global__ __launch_bounds__(SCAN_THREADS) void scan_sums_kernel(uint32_t* __restrict__ sums0,
-                                                                 uint32_t* __restrict__ total0,
-                                                                 uint32_t* __restrict__ sums1,
-                                                                 uint32_t* __restrict__ total1, uint32_t nb) {
-    uint32_t* __restrict__ sums = blockIdx.x ? sums1 : sums0;
-    uint32_t* __restrict__ total_out = blockIdx.x ? total1 : total0;
+__global__ __launch_bounds__(SCAN_THREADS) void scan_sums_kernel(uint32_t* __restrict__ sums,
+                                                                 uint32_t* __restrict__ total_out, uint32_t nb) {
     __shared__ uint32_t wave_sums[4];
     __shared__ uint32_t total;
     uint32_t carry = 0;
@@ -70,45 +63,11 @@ __global__ __launch_bounds__(SCAN_THREADS) void scan_sums_kernel(uint32_t* __res
         carry += total;
         __syncthreads();
     }
-    if (threadIdx.x == 0 && total_out) *total_out = carry;
+    if (threadIdx.x == 0) *total_out = carry;
 }
 
-__global__ __launch_bounds__(SCAN_THREADS) void scan_apply_kernel(const uint32_t* __restrict__ in,
-                                                                  uint32_t* __restrict__ out,
-                                                                  uint32_t n, uint32_t shift,
-                                                                  const uint32_t* __restrict__ sums) {
-    __shared__ uint32_t wave_sums[4];
-    __shared__ uint32_t total;
-    uint64_t base = (uint64_t)blockIdx.x * SCAN_TILE + (uint64_t)threadIdx.x * SCAN_ITEMS;
-    uint32_t v[SCAN_ITEMS];
-    uint32_t s = 0;
-#pragma unroll
-    for (int e = 0; e < SCAN_ITEMS; ++e) {
-        v[e] = (base + e < n) ? in[base + e] >> shift : 0u;
-        s += v[e];
-    }
-    uint32_t run = block_exclusive_scan(s, wave_sums, &total) + sums[blockIdx.x];
-#pragma unroll
-    for (int e = 0; e < SCAN_ITEMS; ++e) {
-        if (base + e < n) out[base + e] = run;
-        run += v[e];
-    }
-}
-
-size_t scan_scratch_u32(uint32_t n) { return blocks_for(n, SCAN_TILE) + 1; }
-
-void launch_scan_sums(uint32_t* sums, uint32_t nb, uint32_t* total, hipStream_t st, uint32_t* sums2,
-                      uint32_t* total2) {
-    hipLaunchKernelGGL(scan_sums_kernel, dim3(sums2 ? 2 : 1), dim3(SCAN_THREADS), 0, st, sums, total, sums2, total2, nb);
-}
-
-uint32_t scan_tile() { return SCAN_TILE; }
-
-void launch_scan_apply(const uint32_t* in, uint32_t* out, uint32_t n, uint32_t shift, const uint32_t* sums,
-                       hipStream_t st) {
-    if (n == 0) return;
-    hipLaunchKernelGGL(scan_apply_kernel, dim3(blocks_for(n, SCAN_TILE)), dim3(SCAN_THREADS), 0, st, in, out, n,
-                       shift, sums);
+void launch_scan_sums(uint32_t* sums, uint32_t nb, uint32_t* total, hipStream_t st) {
+    hipLaunchKernelGGL(scan_sums_kernel, dim3(1), dim3(SCAN_THREADS), 0, st, sums, total, nb);
 }
 
 // ---------------------------------------------------------------------------------------------
