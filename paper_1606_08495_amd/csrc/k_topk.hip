@@ -122,6 +122,7 @@ struct TopkArgs {
     uint32_t q_first;                   // first query (fold) or query tile (stream) of this launch
     const float* invq; const float* invc; const float* theta;
     uint32_t* cnt; uint32_t* pend; uint32_t cap;
+    uint32_t* bits; uint32_t pitch;              // stream: a bit per candidate of the round, `pitch` words per query
     uint32_t* err;
     // 16-bit screens
     const void* qfrag; const float* qmargin;     // rounded queries, and what to lower their thresholds by
@@ -313,6 +314,19 @@ __device__ __forceinline__ void append_tile(const TopkArgs& a, uint32_t bits, ui
     if (lost) atomicOr(a.err, 1u);
 }
 
+// The same bits, as one word per query: lane (v, fk), v < 16, holds that of query 8 (v / 4) + 4 fk + v % 4.
+__device__ __forceinline__ uint32_t tile_words(uint32_t bits, int lane) {
+    const int fr = lane & 31, fk = lane >> 5;
+    uint32_t mine = 0;
+    if (__ballot(bits != 0) == 0) return 0;                   // uniform per wavefront
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const uint64_t both = __ballot((bits >> v) & 1u);
+        if (fr == v) mine = fk ? (uint32_t)(both >> 32) : (uint32_t)both;
+    }
+    return mine;
+}
+
 // A tile's 16-bit products against the thresholds: the bits of append_tile, and how many (added to `hits`,
 // the same in every lane).  Most tiles hold none once the thresholds have risen: two instructions per
 // element tell.  level: LDS, the 32 levels of the tile's queries (+inf past Q: no bits); `unit_c` scales
@@ -351,7 +365,7 @@ __device__ __forceinline__ uint32_t screen_tile(const v16f& acc, float unit_c, f
 // 2 x 2 tiles per wavefront at four wavefronts per SIMD (128 registers, accumulators included) measured
 // best: 2 x 4 and 4 x 2 tiles (two wavefronts per SIMD) ran 9 % slower, 4 x 4 (one) 2.3 times slower --
 // this lives on having other wavefronts to switch to at its barriers.
-// OWN_LENGTHS: the candidates' inverse lengths are formed here, else they are in a.invc.
+// STREAM: the pairs are left as bits, and the candidates' inverse lengths are formed here, else they are in a.invc.
 // ---------------------------------------------------------------------------------------------
 template <int WM, int WN> struct ExactLds {
     struct Panels { float A[2][64 * WM][TK_LD], B[2][64 * WN][TK_LD]; };
@@ -360,7 +374,7 @@ template <int WM, int WN> struct ExactLds {
     __device__ ExactLds() {}
 };
 
-template <int WM, int WN, bool VEC4, bool SCORED, bool OWN_LENGTHS>
+template <int WM, int WN, bool VEC4, bool SCORED, bool STREAM>
 __device__ __forceinline__ void exact_block(const TopkArgs& a, uint32_t q0, uint32_t c0, ExactLds<WM, WN>& s) {
     constexpr int TM = 2, TN = 2, BQ = 64 * WM, BC = 64 * WN, THREADS = 64 * WM * WN;
     constexpr int RPM = THREADS / (TK_BK / 4);               // rows covered by one move of the block
@@ -368,7 +382,7 @@ __device__ __forceinline__ void exact_block(const TopkArgs& a, uint32_t q0, uint
     static_assert(BQ % RPM == 0 && BC % RPM == 0, "whole moves");
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
     const int wm = wave / WN, wn = wave % WN;
-    static_assert(THREADS >= BQ && (!OWN_LENGTHS || 32 * WM * WN == BC), "a query per thread, 32 candidates per wavefront");
+    static_assert(THREADS >= BQ && (!STREAM || 32 * WM * WN == BC), "a query per thread, 32 candidates per wavefront");
     const bool q_ok = tid < BQ && q0 + tid < a.Q;
     const float iq = q_ok ? a.invq[q0 + tid] : 0.f, th = q_ok ? a.theta[q0 + tid] : INFINITY;
     // Staging through two LDS buffers of TK_BK columns: while a panel is multiplied, the next one
@@ -402,7 +416,7 @@ __device__ __forceinline__ void exact_block(const TopkArgs& a, uint32_t q0, uint
         }
     };
     float inv = 0.f;
-    if (OWN_LENGTHS) {
+    if (STREAM) {
         const uint32_t c = c0 + wave * 32 + (lane & 31);
         inv = inv_length(pair_square<VEC4>(a.Cm + (uint64_t)(c < a.c_end ? c : 0u) * a.d, c < a.c_end, a.d, lane >> 5));
     }
@@ -460,7 +474,7 @@ __device__ __forceinline__ void exact_block(const TopkArgs& a, uint32_t q0, uint
         }
         s.t.level[tid] = t;
     }
-    if (OWN_LENGTHS && lane < 32) s.t.invc[wave * 32 + lane] = inv;
+    if (STREAM && lane < 32) s.t.invc[wave * 32 + lane] = inv;
     __syncthreads();
 
     // filter: a score above the query's threshold joins the query's pending list.  Most tiles hold no
@@ -480,17 +494,22 @@ __device__ __forceinline__ void exact_block(const TopkArgs& a, uint32_t q0, uint
         for (int tj = 0; tj < TN; ++tj) {
             const uint32_t c = c0 + wn * 32 * TN + tj * 32 + fr;
             const bool c_ok = c < a.c_end;
-            const float ic = OWN_LENGTHS ? s.t.invc[c - c0] : (c_ok ? a.invc[c] : 0.f);
+            const float ic = STREAM ? s.t.invc[c - c0] : (c_ok ? a.invc[c] : 0.f);
             float over = -INFINITY;
 #pragma unroll
             for (int v = 0; v < 16; ++v) over = fmaxf(over, fmaf(acc[ti][tj][v], ic, -tq[v]));
-            if (__ballot(over >= 0.f) == 0) continue;        // uniform per wavefront
+            if (!STREAM && __ballot(over >= 0.f) == 0) continue;       // uniform per wavefront
             uint32_t bits = 0;
             auto score = [&](int v) { return acc[ti][tj][v] * s.t.invq[qbase + 8 * (v / 4) + v % 4] * ic; };
 #pragma unroll
             for (int v = 0; v < 16; ++v)                     // (padded queries carry +inf: never)
                 bits |= c_ok && score(v) > s.t.theta[qbase + 8 * (v / 4) + v % 4] ? 1u << v : 0u;
-            append_tile<SCORED>(a, bits, q0 + wm * 32 * TM + ti * 32, c, lane, score);
+            if constexpr (STREAM) {
+                const uint32_t word = tile_words(bits, lane), q = q0 + wm * 32 * TM + ti * 32 + 8 * (fr / 4) + 4 * fk + fr % 4;
+                if (fr < 16 && q < a.Q) a.bits[(uint64_t)q * a.pitch + (c - a.c_begin) / 32] = word;   // (c - fr: of this tile)
+            } else {
+                append_tile<SCORED>(a, bits, q0 + wm * 32 * TM + ti * 32, c, lane, score);
+            }
         }
     }
 }
@@ -604,7 +623,9 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a
 // Stream screen: a wavefront takes 32 candidates and TQ tiles of 32 queries (q_first + blockIdx.y: which).  The
 // lane pair (l, l ^ 32) walks candidate l % 32, eight columns at a time each; the rounded columns are
 // a matrix-core operand as they stand.  Four steps of candidate columns are in flight ahead of the
-// four in work; the queries' operands come from L2.
+// four in work; the queries' operands come from L2.  The pairs to look at are left as a bit each: a block
+// writes sixteen bytes per query, needs no counters, and a round may be as long as there is room for bits.
+// (With lists of four bytes a pair a search of 100 queries over 200 003 x 100 took five rounds, 193 us; now three, 123.)
 // ---------------------------------------------------------------------------------------------
 constexpr int TK_AHEAD = 4;
 template <int TQ, bool VEC4>
@@ -612,9 +633,24 @@ __global__ __launch_bounds__(256, TQ == 1 ? 4 : (TQ == 2 ? 3 : 2)) void topk_str
     __shared__ __align__(16) float s_level[TQ * 32];
     __shared__ ExactLds<2, 2> exact;
     __shared__ uint32_t s_hits, s_dense;
+    __shared__ __align__(16) uint32_t s_words[TQ * 32][4];
     const int tid = threadIdx.x, lane = tid % 64, fk = lane >> 5;
     const uint32_t qt0 = (a.q_first + blockIdx.y) * TQ;
+    const uint32_t c0 = a.c_begin + blockIdx.x * 128u;
+    const uint32_t c = c0 + (tid / 64) * 32 + (lane & 31);
+    const bool c_ok = c < a.c_end;
+    const float* row = a.Cm + (uint64_t)(c_ok ? c : 0u) * a.d;
+    float4 x[TK_AHEAD][2], nx[TK_AHEAD][2];
+    auto fetch = [&](float4 (&r)[TK_AHEAD][2], uint32_t ks) {
+#pragma unroll
+        for (int i = 0; i < TK_AHEAD; ++i) {
+            const uint32_t k = (ks + i) * TK_KS + 8 * fk;
+            r[i][0] = load_cols<VEC4>(row, c_ok, k, a.d);        // (zero past the last column)
+            r[i][1] = load_cols<VEC4>(row, c_ok, k + 4, a.d);
+        }
+    };
     const uint32_t counted = dense_so_far(a);
+    fetch(x, 0);
     for (int i = tid; i < TQ * 32; i += 256) {
         const uint32_t q = qt0 * 32 + i;
         s_level[i] = q < a.Q ? screen_level(a.theta[q], a.qmargin[q], 1.f) : INFINITY;
@@ -622,11 +658,7 @@ __global__ __launch_bounds__(256, TQ == 1 ? 4 : (TQ == 2 ? 3 : 2)) void topk_str
     tell_dense(a, counted, a.q_first + blockIdx.y + blockIdx.x == 0, &s_hits, &s_dense);
     __syncthreads();
     bool dense = s_dense != 0;                               // uniform per block
-    const uint32_t c0 = a.c_begin + blockIdx.x * 128u;
     if (!dense) {
-        const uint32_t c = c0 + (tid / 64) * 32 + (lane & 31);
-        const bool c_ok = c < a.c_end;
-        const float* row = a.Cm + (uint64_t)(c_ok ? c : 0u) * a.d;
         const uint32_t steps = topk_steps(a.d);
         const v8b* qf = (const v8b*)a.qfrag + (uint64_t)qt0 * steps * 64 + lane;
         v16f acc[TQ];
@@ -635,16 +667,6 @@ __global__ __launch_bounds__(256, TQ == 1 ? 4 : (TQ == 2 ? 3 : 2)) void topk_str
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
         float sq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, e2 = 0.f;
-        float4 x[TK_AHEAD][2], nx[TK_AHEAD][2];
-        auto fetch = [&](float4 (&r)[TK_AHEAD][2], uint32_t ks) {
-#pragma unroll
-            for (int i = 0; i < TK_AHEAD; ++i) {
-                const uint32_t k = (ks + i) * TK_KS + 8 * fk;
-                r[i][0] = load_cols<VEC4>(row, c_ok, k, a.d);    // (zero past the last column)
-                r[i][1] = load_cols<VEC4>(row, c_ok, k + 4, a.d);
-            }
-        };
-        fetch(x, 0);
         for (uint32_t ks0 = 0; ks0 < steps; ks0 += TK_AHEAD) {
             fetch(nx, ks0 + TK_AHEAD);
 #pragma unroll
@@ -676,19 +698,22 @@ __global__ __launch_bounds__(256, TQ == 1 ? 4 : (TQ == 2 ? 3 : 2)) void topk_str
         if (square > 0.f && (square < TK_TINY || ic == 0.f)) own = INFINITY;   // imprecise, or too long to square
         if (!(own >= 0.f)) own = INFINITY;
         if (!c_ok) own = -INFINITY;
-        uint32_t bits[TQ];
         int hits = 0;
 #pragma unroll
         for (int t = 0; t < TQ; ++t) {
             if (own == INFINITY || ic == 0.f)                    // products that may not be finite: the margin decides
 #pragma unroll
                 for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-            bits[t] = screen_tile(acc[t], ic, own, s_level + t * 32, lane, hits);
+            const uint32_t word = tile_words(screen_tile(acc[t], ic, own, s_level + t * 32, lane, hits), lane);
+            const int fr = lane & 31;
+            if (fr < 16) s_words[t * 32 + 8 * (fr / 4) + 4 * fk + fr % 4][tid / 64] = word;
         }
         dense = dense_block(a, hits, &s_hits, &s_dense);
-        if (!dense && hits) {
-#pragma unroll
-            for (int t = 0; t < TQ; ++t) append_tile<false>(a, bits[t], (qt0 + t) * 32, c, lane, [](int) { return 0.f; });
+        if (!dense) {
+            __syncthreads();
+            const uint32_t q = qt0 * 32 + tid;
+            if (tid < TQ * 32 && q < a.Q)                        // (the pitch is a multiple of four words)
+                *(uint4*)(a.bits + (uint64_t)q * a.pitch + blockIdx.x * 4) = *(const uint4*)s_words[tid];
         }
     }
     if (dense) exact_block<2, 2, VEC4, false, true>(a, qt0 * 32, c0, exact);
@@ -706,7 +731,7 @@ __global__ __launch_bounds__(TK_THREADS, 4) void topk_scores_kernel(TopkArgs a) 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fold: one block per query gives the listed pairs their similarities -- a lane per candidate, one
+// Fold: one block per query gives the pairs listed (or left as bits) their similarities -- a lane per candidate, one
 // 128-byte line of its row at a time; the fp32 screen has them listed already -- and merges those above
 // the threshold into the sorted best list (higher score first, equal scores by lower index), then raises
 // the threshold to the K-th best and empties the list.  Rounds come in index order, so a later candidate that only equals the K-th best
@@ -770,7 +795,10 @@ __device__ __forceinline__ float exact_score(const float* __restrict__ q, const 
     return dot * iq * inv_length(tree8(lo) + tree8(hi));
 }
 
-template <int WAVES, bool VEC4, bool SCORED>
+constexpr uint32_t FOLD_PICK = 2048;             // candidates named by bits that a block lists before it scores them
+constexpr uint32_t FOLD_CHUNK = 16;              // words: where they are more
+enum FoldFrom { FOLD_LIST, FOLD_SCORED, FOLD_BITS };
+template <int WAVES, bool VEC4, FoldFrom FROM>
 __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint32_t K, float tau,
                                                                uint64_t* __restrict__ best,
                                                                uint32_t* __restrict__ best_cnt,
@@ -779,37 +807,95 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
                                                                float* __restrict__ out_score,
                                                                uint32_t* __restrict__ out_count) {
     __shared__ uint64_t s_list[WAVES][64];
+    union Picked {
+        uint32_t pick[FROM == FOLD_BITS ? FOLD_PICK : 1];
+        uint32_t queue[FROM == FOLD_BITS ? WAVES : 1][64 + 32 * FOLD_CHUNK];
+    };
+    __shared__ Picked lds;
+    __shared__ uint32_t s_picked;
     const uint32_t q = a.q_first + blockIdx.x;
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
-    const uint32_t n_new = min(a.cnt[q], a.cap), bc = best_cnt[q];
-    if (n_new == 0 && !out_idx) return;                      // uniform per block
-    const bool alone = n_new <= 64;                          // one wavefront has them all
-    if (alone && wave) return;
+    const uint32_t bc = best_cnt[q];
     const float th = theta[q], iq = a.invq[q];
     // (key 0 is below that of every score: an empty place)
     uint64_t list = wave == 0 && (uint32_t)lane < bc ? best[(uint64_t)q * TK_LIST + lane] : 0ull;
-    for (uint32_t base = wave * 64u; base < n_new; base += 64u * WAVES) {
-        uint64_t k = 0;
-        if (base + lane < n_new) {
-            const uint64_t at = (uint64_t)q * a.cap + base + lane;
-            uint32_t c;
-            float s;
-            if (SCORED) {
-                const uint2 e = ((const uint2*)a.pend)[at];
-                s = __uint_as_float(e.x); c = e.y;
-            } else {
-                c = a.pend[at];
-                s = exact_score<VEC4>(a.Qm + (uint64_t)q * a.d, a.Cm + (uint64_t)c * a.d, a.d, iq);
-            }
-            if (s > th) k = rank_key(s, c);                  // (a similarity that is no number never passes)
+    uint32_t n_new;
+    const uint32_t words = (a.c_end - a.c_begin + 31) / 32;
+    const uint32_t* bits = a.bits + (uint64_t)q * a.pitch;
+    if constexpr (FROM == FOLD_BITS) {
+        // the candidates whose bits are set, in any order: ranks decide
+        if (threadIdx.x == 0) s_picked = 0;
+        __syncthreads();
+#pragma unroll 8
+        for (uint32_t i = threadIdx.x; i < words; i += 64 * WAVES) {
+            uint32_t word = bits[i];
+            if (word == 0) continue;
+            uint32_t at = atomicAdd(&s_picked, (uint32_t)__popc(word));
+            for (; word; word &= word - 1, ++at)
+                if (at < FOLD_PICK) lds.pick[at] = a.c_begin + i * 32 + __builtin_ctz(word);
         }
+        __syncthreads();
+        n_new = s_picked;
+    } else {
+        n_new = min(a.cnt[q], a.cap);
+    }
+    if (n_new == 0 && !out_idx) return;                      // uniform per block
+    const bool spilled = FROM == FOLD_BITS && n_new > FOLD_PICK;        // each wavefront looks through words of its own
+    const int waves = spilled ? WAVES : min(WAVES, (int)((n_new + 63) / 64));      // that have any
+    if (wave && wave >= waves) return;
+    auto score = [&](uint32_t c) { return exact_score<VEC4>(a.Qm + (uint64_t)q * a.d, a.Cm + (uint64_t)c * a.d, a.d, iq); };
+    // spilled: sixteen words at a time are turned into candidates in order, until there is one for every lane
+    uint32_t words_at = wave * FOLD_CHUNK, queued = 0, taken = 0;
+    for (uint32_t base = wave * 64u; spilled || base < n_new; base += 64u * WAVES) {
+        bool on = base + lane < n_new;
+        uint32_t c = 0;
+        float s = 0.f;
+        if constexpr (FROM == FOLD_BITS) {
+            if (spilled) {
+                uint32_t* queue = lds.queue[wave];
+                const uint32_t left = queued - taken, keep = taken + lane < queued ? queue[taken + lane] : 0u;
+                if (left < 64) {                             // (uniform per wavefront, as all of these)
+                    queue[lane] = keep;
+                    queued = left; taken = 0;
+                }
+                while (queued - taken < 64 && words_at < words) {
+                    uint32_t word = lane < (int)FOLD_CHUNK && words_at + lane < words ? bits[words_at + lane] : 0u;
+                    const uint32_t n = (uint32_t)__popc(word);
+                    uint32_t incl = n;
+#pragma unroll
+                    for (int d = 1; d < (int)FOLD_CHUNK; d <<= 1) {
+                        const uint32_t y = __shfl_up(incl, d, 64);
+                        if (lane >= d) incl += y;
+                    }
+                    for (uint32_t at = queued + incl - n; word; word &= word - 1, ++at)
+                        queue[at] = a.c_begin + (words_at + lane) * 32 + __builtin_ctz(word);
+                    queued += (uint32_t)__builtin_amdgcn_readlane((int)incl, FOLD_CHUNK - 1);
+                    words_at += FOLD_CHUNK * WAVES;
+                }
+                if (queued == taken) break;
+                on = taken + lane < queued;
+                if (on) c = queue[taken + lane];
+                taken = min(taken + 64, queued);
+            } else if (on) {
+                c = lds.pick[base + lane];
+            }
+        } else if (on && FROM == FOLD_LIST) {
+            c = a.pend[(uint64_t)q * a.cap + base + lane];
+        } else if (on) {
+            const uint2 e = ((const uint2*)a.pend)[(uint64_t)q * a.cap + base + lane];
+            s = __uint_as_float(e.x); c = e.y;
+        }
+        if (FROM != FOLD_SCORED && on) s = score(c);
+        const uint64_t k = on && s > th ? rank_key(s, c) : 0ull;       // (a similarity that is no number never passes)
         if (__ballot(k != 0)) list = merge64(list, __shfl((unsigned long long)sort64(k, lane), 63 - lane, 64), lane);
     }
-    for (int w = alone ? 0 : WAVES / 2; w >= 1; w >>= 1) {
+    int half = 1;                                            // half of the wavefronts, rounded up to a power of two
+    while (2 * half < waves) half *= 2;
+    for (int w = waves > 1 ? half : 0; w >= 1; w >>= 1) {
         __syncthreads();
         if (wave >= w && wave < 2 * w) s_list[wave][63 - lane] = list;
         __syncthreads();
-        if (wave < w) list = merge64(list, s_list[wave + w][lane], lane);
+        if (wave < w && wave + w < waves) list = merge64(list, s_list[wave + w][lane], lane);
     }
     if (wave) return;
     const uint32_t have = min(K, (uint32_t)__popcll(__ballot(list != 0)));
@@ -871,7 +957,9 @@ constexpr uint32_t WIDE_Q = 32 * TK_WTM * TK_WWM, WIDE_C = 32 * TK_WTN * TK_WWN;
 
 // How a search is served: by which screen, in rounds of how many candidates, and with how many rounded
 // queries (a whole number of the screen's tiles: 32, 64 or 128 for the stream screen, 256 for the wide one).
-struct TopkPlan { TopkScreen screen; uint64_t cap, q_up; };
+// `list`: room of a query's list, pairs of four bytes.  The stream screen needs a bit per pair, so its rounds may be
+// longer, as the same memory holds.
+struct TopkPlan { TopkScreen screen; uint64_t cap, q_up, list; };
 static uint32_t stream_tiles(uint32_t Q) { return Q <= 32 ? 1 : (Q <= 64 ? 2 : 4); }    // of 32 queries, per wavefront
 
 static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_bytes) {
@@ -884,17 +972,18 @@ static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_b
     // 900, 3800 candidates 4750, 5670 and 2990, 4230; 1000 with room for 3400 2230, 2150; 300 over 200 000
     // x 60 280, 264).  With 129 to 256 the wide screen is ahead only over few candidates, whose rows it need
     // not read twice (129 over 20 000 x 300 187, 206; over 200 000 x 60 246, 224; x 512 840, 600; x 1000
-    // 2030, 1130).  The stream screen's lists hold close to twice what the fp32 screen's do; where the rounds
-    // of many queries are short and the rounded queries take much of that, it is no longer ahead (4096 over
-    // 20 000 x 800 with room for 512 4590, fp32 3870).
-    TopkPlan p{TOPK_FP32, free_bytes / (8ull * Q) / TK_BC * TK_BC, 0};
+    // 2030, 1130).  (`cap` of the stream screen, here: what its lists would hold, close to twice what the fp32 screen's
+    // do; where the rounded queries take much of that, the fp32 screen is taken: 4096 over 20 000 x 800 with room
+    // for 512 candidates 3870, stream with lists 4590.)
+    TopkPlan p{TOPK_FP32, free_bytes / (8ull * Q) / TK_BC * TK_BC, 0, 0};
     const uint64_t cap_fp32 = p.cap;
     auto room = [&](uint64_t tile, uint64_t per_candidate, uint64_t granule, uint64_t least, TopkScreen screen) {
         const uint64_t q_up = (Q + tile - 1) / tile * tile, q_bytes = q_up * (row_bytes + 4) + 512;
         if (free_bytes <= q_bytes) return false;
         const uint64_t cap = (free_bytes - q_bytes) / per_candidate / granule * granule;
         if (cap < n_up && cap < least) return false;
-        p = TopkPlan{screen, cap, q_up};
+        const uint64_t longest = screen == TOPK_STREAM ? (free_bytes - q_bytes) / Q * 8 / TK_BC * TK_BC : cap;
+        p = TopkPlan{screen, longest, q_up, std::min<uint64_t>({cap, n_up, TK_CAND_SLICE})};
         return true;
     };
     const bool wide = Q > 2 * TK_STREAM_Q || (Q > TK_STREAM_Q && N <= (1u << 16) && topk_steps(d) <= TK_HOLD);
@@ -931,7 +1020,9 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
     char* at = ws + L.pend;
     a.pend = (uint32_t*)at;
     a.cap = (uint32_t)cap;
-    at += (cap * Q * 4 + 255) / 256 * 256;
+    a.bits = a.pend;
+    a.pitch = (uint32_t)(cap / 32);
+    at += (std::max(screen == TOPK_STREAM ? cap * Q / 8 : cap * Q * 4, plan.list * Q * 4) + 255) / 256 * 256;
     void* qfrag = nullptr; float* qmargin = nullptr; void* cfrag = nullptr; float* cmargin = nullptr;
     if (screen != TOPK_FP32) {
         qfrag = at; at += q_up * row_bytes;
@@ -989,9 +1080,9 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
         // (4096 x 20 000, K = 64: 1047 -> 614 us in all; 4096 x 200 000, K = 30: 1540 -> 1360).  Below some 10^5
         // pairs the fp32 product is not faster: 300 x 100 000 328 us, 334 with TK_EXACT_ROUND 50 000.
         // (Where tau prunes from the start, nothing is known of how many pairs pass: screened.)
-        const bool exact_round = screen == TOPK_FP32 || (many && tau <= 0.f && 2ull * m <= cap &&
+        const bool exact_round = screen == TOPK_FP32 || (many && tau <= 0.f && 2ull * m <= plan.list &&
                                                          share > 0.01 && share * m * Q > TK_EXACT_ROUND);
-        a.cap = (uint32_t)(exact_round && screen != TOPK_FP32 ? cap / 2 : cap);       // (eight bytes a pair instead of four)
+        a.cap = (uint32_t)(screen == TOPK_FP32 ? cap : exact_round ? plan.list / 2 : plan.list);   // (eight bytes a pair or four)
         if (screen == TOPK_WIDE && !exact_round) {
             a.nq_tiles = (Q + WIDE_Q - 1) / WIDE_Q;
             a.nc_tiles = (m + WIDE_C - 1) / WIDE_C;
@@ -1032,13 +1123,15 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
         }
         const bool last = begin + len >= N;
         uint32_t* oi = last ? out_idx : nullptr;
-#define W2V_FOLD(WAVES, VEC4, SCORED)                                                                      \
-    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4, SCORED>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first)), \
+        const bool bits = screen == TOPK_STREAM && !exact_round;
+#define W2V_FOLD(WAVES, VEC4, FROM)                                                                        \
+    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4, FROM>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first)), \
                        dim3(64 * WAVES), 0, st, a, K, tau, best, best_cnt, theta, oi, out_score, out_count)
         for (a.q_first = 0; a.q_first < Q; a.q_first += TK_FOLD_SLICE) {
-            if (exact_round) W2V_FOLD(4, false, true);
-            else if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(4, true, false); else W2V_FOLD(4, false, false); }
-            else { if (vec4) W2V_FOLD(16, true, false); else W2V_FOLD(16, false, false); }
+            if (exact_round) W2V_FOLD(4, false, FOLD_SCORED);
+            else if (!bits) { if (vec4) W2V_FOLD(4, true, FOLD_LIST); else W2V_FOLD(4, false, FOLD_LIST); }
+            else if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(4, true, FOLD_BITS); else W2V_FOLD(4, false, FOLD_BITS); }
+            else { if (vec4) W2V_FOLD(16, true, FOLD_BITS); else W2V_FOLD(16, false, FOLD_BITS); }
         }
 #undef W2V_FOLD
     }
