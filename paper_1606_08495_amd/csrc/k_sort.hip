@@ -75,7 +75,7 @@ void launch_scan_sums(uint32_t* sums, uint32_t nb, uint32_t* total, hipStream_t 
 //   fill      : clears the digit totals, the tile tickets and the first tile-state array
 //   totals    : one read of the keys gives, for every pass at once, how many keys carry each digit
 //               (the totals do not depend on the order the earlier passes leave behind)
-//   pass x P  : ONE launch per pass.  A block takes the next tile of 256 x ITEMS consecutive elements
+//   pass x P  : ONE launch per pass.  A block takes the next tile of THREADS x ITEMS consecutive elements
 //               (ticket counter), ranks its elements among the tile's elements of the same digit in
 //               tile order (-> stable), and learns how many elements of each digit the tiles before
 //               it hold by looking back over the tile states: a tile first publishes its own digit
@@ -99,13 +99,26 @@ constexpr int SORT_MAX_PASSES = 4;
 constexpr uint32_t SORT_SPIN_LIMIT = 1u << 22;       // fruitless look-back polls before giving up (~ a second)
 constexpr int LB_WINDOW = 8;                         // tiles examined per look-back round
 constexpr uint64_t ST_PARTIAL = 1ull << 62, ST_INCLUSIVE = 2ull << 62, ST_VALUE = (1ull << 62) - 1;
-// Tile shapes.  Large inputs: 512 threads x 16 elements = 8192 per tile -- with 256 digits a digit's
-// run in a tile is 32 elements, 256 bytes, on average (tiles of 4096 measured 15 % slower, and
-// 1024 threads x 8 or 512 x 8 slower still).  Below SORT_SMALL_N elements: 256 x 4, so that small
-// sorts still spread over the chip (2^18 keys: 51 us against 60; from 2^20 keys on the large shape
-// wins, 77 us against 123: fewer tiles, shorter look-back).
-static inline int sort_shape_for(uint64_t n) { return n < SORT_SMALL_N ? 0 : 1; }
-static inline uint32_t sort_tile_of(int shape) { return shape == 0 ? 1024u : 8192u; }
+// Tile shapes.  A pass over few tiles is a chain of latencies -- a tile's own work, then the look-back, eight tiles a
+// round trip -- so the tiles are as large as still leaves the chip enough of them, and their threads many: what
+// a tile does between its loads and its counts is short then.  Joint sort of 6 n + n keys of 20 bits, us, all launches:
+// keys       140 000  280 000  459 000  700 000  1.05 M  1.84 M  3.67 M  7.34 M
+// 256 x 4         41       52       67       88     116     181     293     507   (so up to 2^19 keys before)
+// 512 x 16        55       58       60       67      74      86     122     210   (and from there on)
+// 1024 x 2        35       41       48       62      77     111     183     320
+// 1024 x 4        38       42       46       54      64      95     163     274
+// 1024 x 8        46       49       52       57      63      77     127     226
+// (1024 x 16 alone 109 and 194 at the two largest; its blocks fill a compute unit, which beside row kernels they seldom
+// get to themselves: benchmark step 3.110 ms against 3.098 with 512 x 16, dotprod and adjust of 60 columns 1.097, 1.111.)
+// (Look-back windows of 4 tiles the same, of 16 and 32 up to 40 % slower.)
+struct SortShape { uint32_t below, threads, items; };           // for less than `below` keys in all
+constexpr SortShape SORT_SHAPES[] = {{300000u, 1024, 2}, {1u << 20, 1024, 4}, {2500000u, 1024, 8}, {0xFFFFFFFFu, 512, 16}};
+static inline int sort_shape_for(uint64_t n) {
+    int s = 0;
+    while (s < 3 && n >= SORT_SHAPES[s].below) ++s;
+    return s;
+}
+static inline uint32_t sort_tile_of(int shape) { return SORT_SHAPES[shape].threads * SORT_SHAPES[shape].items; }
 
 struct SortJobDev {
     const uint32_t* keys_in;     // the caller's keys (pass 0 reads them; never written)
@@ -329,12 +342,15 @@ __global__ __launch_bounds__(THREADS) void sort_pass_kernel(SortArgs a, uint32_t
 static inline uint32_t sort_tiles(uint32_t n, int shape) { return blocks_for(n, sort_tile_of(shape)); }
 
 // Scratch of calls over arrays of up to n0 and n1 elements, together or each alone, in uint32 (the
-// region must be 8-byte aligned).  Past SORT_SMALL_N in all, one of the arrays alone (or a smaller call
-// later) may still be short enough for the small tiles, of which there are more than large ones.
+// region must be 8-byte aligned).  Reserved by tiles of 1024 below SORT_SMALL_N in all, which is more than any shape
+// has there; past it one of the arrays alone (or a smaller call later) may still be short, and arrays of up to 2^20
+// keys are cut in tiles of 4096, of which there are less than that.
+static_assert((1u << 20) / 4096 + 2 <= SORT_SMALL_N / 1024 + 1, "see above");
 size_t sort_scratch_u32(uint32_t n0, uint32_t n1) {
-    const int shape = sort_shape_for((uint64_t)n0 + n1);
-    uint64_t tiles = (uint64_t)sort_tiles(n0, shape) + sort_tiles(n1, shape);
-    if (shape != 0) tiles = std::max<uint64_t>(tiles, SORT_SMALL_N / sort_tile_of(0) + 1);
+    const uint64_t n = (uint64_t)n0 + n1;
+    const uint32_t tile = n < SORT_SMALL_N ? 1024u : 8192u;
+    uint64_t tiles = (uint64_t)blocks_for(n0, tile) + blocks_for(n1, tile);
+    if (n >= SORT_SMALL_N) tiles = std::max<uint64_t>(tiles, SORT_SMALL_N / 1024 + 1);
     return 2 * SORT_MAX_PASSES * 256 + 8 + 2 * (size_t)(2 * tiles * 256) + 16;
 }
 
@@ -404,10 +420,14 @@ void launch_sort_jobs(const SortJob* jobs, int njobs, uint32_t bits, uint32_t* t
     const uint32_t blocks1 = live > 1 ? blocks_for(a.job[1].n, SORT_THREADS * TOT_ITEMS) : 0u;
     hipLaunchKernelGGL(sort_totals_kernel, dim3(blocks0 + blocks1), dim3(SORT_THREADS), 0, st, a, blocks0);
     for (uint32_t p = 0; p < a.passes; ++p) {
-        if (shape == 0)
-            hipLaunchKernelGGL((sort_pass_kernel<256, 4>), dim3(tiles), dim3(256), 0, st, a, p);
-        else
-            hipLaunchKernelGGL((sort_pass_kernel<512, 16>), dim3(tiles), dim3(512), 0, st, a, p);
+#define W2V_PASS(SHAPE)                                                                                          \
+    hipLaunchKernelGGL((sort_pass_kernel<SORT_SHAPES[SHAPE].threads, SORT_SHAPES[SHAPE].items>), dim3(tiles),    \
+                       dim3(SORT_SHAPES[SHAPE].threads), 0, st, a, p)
+        if (shape == 0) W2V_PASS(0);
+        else if (shape == 1) W2V_PASS(1);
+        else if (shape == 2) W2V_PASS(2);
+        else W2V_PASS(3);
+#undef W2V_PASS
     }
 }
 
