@@ -18,6 +18,14 @@ __device__ __forceinline__ float softplus(float x) {
     return fmaxf(x, 0.f) + log1pf(expf(-fabsf(x)));
 }
 
+// Whether slot i, i + step, i + 2 step, ... is a pair's first: the remainder by T is taken once.
+struct SlotInPair {
+    uint32_t r, T, step;
+    __device__ __forceinline__ SlotInPair(uint32_t i, uint32_t t, uint32_t by) : r(i % t), T(t), step(by % t) {}
+    __device__ __forceinline__ bool first() const { return r == 0; }
+    __device__ __forceinline__ void next() { r += step; r -= r >= T ? T : 0u; }
+};
+
 // fixed tree over the values of a block's threads; the sum arrives in thread 0
 template <int THREADS>
 __device__ __forceinline__ double block_tree_sum(double v, double* red) {       // red[THREADS / 64]
@@ -38,9 +46,11 @@ __device__ __forceinline__ void loss_terms_block(const float* __restrict__ dots,
                                                  uint32_t vb, double* red) {
     const uint32_t terms = loss_terms_of(total), lo = vb * terms, hi = min(total - lo, terms) + lo;
     double v = 0.0;
+    SlotInPair slot(lo + threadIdx.x, T, THREADS);
     for (uint32_t i = lo + threadIdx.x; i < hi; i += THREADS) {
         const float f = dots[i];
-        v += (double)((i % T) == 0 ? softplus(-f) : softplus(f));
+        v += (double)softplus(slot.first() ? -f : f);        // (one evaluation for both kinds of slot)
+        slot.next();
     }
     const double s = block_tree_sum<THREADS>(v, red);
     if (threadIdx.x == 0) block_loss[vb] = s;
