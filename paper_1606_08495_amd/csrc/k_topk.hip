@@ -28,6 +28,7 @@
 
 #include <algorithm>
 #include <math.h>
+#include <type_traits>
 
 namespace w2v {
 
@@ -141,6 +142,11 @@ struct TopkArgs {
 // Held against read twice, whole search in us: 300 queries over 200 000 x 320 504, 549, x 300 491, 540, x 128
 // 317, 329, x 64 279, 279, x 16 229, 221 (twenty steps whatever the row holds): rows of 65 to 320 columns.
 constexpr int TK_HOLD = 20, TK_HOLD_LEAST = 5;                // steps
+// Candidates are rounded beside the products of the round before, in the registers that leaves, hence read twice, except
+// where rows are long and could be held.  Rounding apart and beside, whole search in us: 150 queries over 40 000 x 100
+// 172, 152, 500 over 300 000 x 31 332, 300, 1000 over 400 000 x 100 568, 534, 700 over 3000 x 200 141, 136, 2000 over
+// 500 000 x 512 2338, 2267; but 300 over 100 000 x 300 342, 344, 4096 over 2^20 x 300 4531, 4602.
+constexpr uint32_t TK_BESIDE = 14;                            // steps, or more than TK_HOLD
 template <bool F16>
 __device__ __forceinline__ void round_step(const float4& x, const float4& y, float inv, bool on, void* __restrict__ frag,
                                            uint64_t at, float& e2) {
@@ -187,7 +193,8 @@ __device__ __forceinline__ void round_rows(const float* __restrict__ M, uint32_t
         square = pair_square<VEC4>(p, ok, d, fk);
         inv = inv_length(square);
         const bool on = square >= TK_TINY && inv > 0.f;
-        for (uint32_t i = 0; i < steps; ++i) {
+#pragma unroll 4
+        for (uint32_t i = 0; i < steps; ++i) {               // (of a panel of four the loads are in flight together)
             const uint32_t k = i * TK_KS + 8 * fk;
             round_step<F16>(load_cols<VEC4>(p, ok, k, d), load_cols<VEC4>(p, ok, k + 4, d), inv, on, frag,
                             at + (uint64_t)i * 64, e2);
@@ -223,20 +230,20 @@ __global__ __launch_bounds__(64) void topk_queries_kernel(const float* __restric
 // The wide screen's candidates of one round (rows c_end .. the end of the last tile are zero and have
 // a margin that no threshold meets).  Bound by memory: 4 d bytes read (a second time, for the rounding,
 // out of the caches) and 2 d written per row.
+struct RoundArgs { const float* Cm; uint32_t c_begin, c_end, d, tiles; float* invc; void* frag; float* margin; };
 template <bool VEC4, int HOLD>
-__global__ __launch_bounds__(64) void topk_round_kernel(const float* __restrict__ Cm, uint32_t c_begin,
-                                                         uint32_t c_end, uint32_t d,
-                                                         float* __restrict__ invc, void* __restrict__ frag,
-                                                         float* __restrict__ margin) {
-    const uint32_t tile = blockIdx.x;
-    const int lane = threadIdx.x;
-    const uint32_t c = c_begin + tile * 32 + (lane & 31);
+__device__ __forceinline__ void round_tile(const RoundArgs& r, uint32_t tile, int lane) {
+    const uint32_t c = r.c_begin + tile * 32 + (lane & 31);
     float square, inv, lost;
-    round_rows<true, VEC4, HOLD>(Cm, c, c < c_end, d, topk_steps(d), frag, tile, lane, square, inv, lost);
+    round_rows<true, VEC4, HOLD>(r.Cm, c, c < r.c_end, r.d, topk_steps(r.d), r.frag, tile, lane, square, inv, lost);
     if (lane < 32) {
-        margin[tile * 32 + lane] = c < c_end ? lost * (TK_F16_SCALE * TK_F16_SCALE) : -INFINITY;
-        if (c < c_end) invc[c] = inv;
+        r.margin[tile * 32 + lane] = c < r.c_end ? lost * (TK_F16_SCALE * TK_F16_SCALE) : -INFINITY;
+        if (c < r.c_end) r.invc[c] = inv;
     }
+}
+template <bool VEC4, int HOLD>
+__global__ __launch_bounds__(64) void topk_round_kernel(RoundArgs r) {
+    round_tile<VEC4, HOLD>(r, blockIdx.x, threadIdx.x);
 }
 
 // 1 / |row| alone, for the fp32 screen: one wavefront per 32 rows.
@@ -520,9 +527,12 @@ __device__ __forceinline__ void exact_block(const TopkArgs& a, uint32_t q0, uint
 // written from registers and the one after is on its way from memory; one barrier per panel.
 // Block b is mapped so that the blocks an XCD receives (b mod 8) walk through the query tiles of one
 // candidate tile after the other: that tile and the queries stay in its L2.
+// After = RoundArgs: the launch's first blocks (a multiple of eight) round the candidates of the round after this one:
+// that is bound by memory and this by the matrix cores (TK_BESIDE).
 // ---------------------------------------------------------------------------------------------
-template <int TM, int TN, int WM, int WN, int WPE, bool VEC4>
-__global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a) {
+struct NoRound {};
+template <int TM, int TN, int WM, int WN, int WPE, bool VEC4, class After>
+__global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a, After after) {
     constexpr int THREADS = 64 * WM * WN, QT = TM * WM, CT = TN * WN, KC = 2;
     constexpr int PANEL = (QT + CT) * KC * 64;               // 16-byte units
     constexpr int MOVES = PANEL / THREADS;
@@ -535,7 +545,17 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a
     static_assert(QT == 2 * WM && CT == 2 * WN, "the tile of exact_block");
     const uint32_t total = a.nq_tiles * a.nc_tiles;
     const uint32_t per_xcd = (total + 7u) / 8u;
-    const uint32_t logical = (blockIdx.x % 8u) * per_xcd + blockIdx.x / 8u;
+    uint32_t block = blockIdx.x;
+    if constexpr (std::is_same<After, RoundArgs>::value) {
+        const uint32_t round_blocks = ((after.tiles + WM * WN - 1) / (WM * WN) + 7) / 8 * 8;
+        if (block < round_blocks) {                          // uniform per block
+            const uint32_t tile = block * (WM * WN) + threadIdx.x / 64;
+            if (tile < after.tiles) round_tile<VEC4, 0>(after, tile, threadIdx.x % 64);
+            return;
+        }
+        block -= round_blocks;
+    }
+    const uint32_t logical = (block % 8u) * per_xcd + block / 8u;
     if (logical >= total) return;                            // uniform per block, before any barrier
     const uint32_t qt0 = (logical % a.nq_tiles) * QT, ct0 = (logical / a.nq_tiles) * CT;
     const uint32_t counted = dense_so_far(a);
@@ -959,7 +979,8 @@ constexpr uint32_t WIDE_Q = 32 * TK_WTM * TK_WWM, WIDE_C = 32 * TK_WTN * TK_WWN;
 // queries (a whole number of the screen's tiles: 32, 64 or 128 for the stream screen, 256 for the wide one).
 // `list`: room of a query's list, pairs of four bytes.  The stream screen needs a bit per pair, so its rounds may be
 // longer, as the same memory holds.
-struct TopkPlan { TopkScreen screen; uint64_t cap, q_up, list; };
+// `ahead`: there is room for the rounded candidates of two rounds.
+struct TopkPlan { TopkScreen screen; uint64_t cap, q_up, list; bool ahead; };
 static uint32_t stream_tiles(uint32_t Q) { return Q <= 32 ? 1 : (Q <= 64 ? 2 : 4); }    // of 32 queries, per wavefront
 
 static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_bytes) {
@@ -975,22 +996,27 @@ static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_b
     // 2030, 1130).  (`cap` of the stream screen, here: what its lists would hold, close to twice what the fp32 screen's
     // do; where the rounded queries take much of that, the fp32 screen is taken: 4096 over 20 000 x 800 with room
     // for 512 candidates 3870, stream with lists 4590.)
-    TopkPlan p{TOPK_FP32, free_bytes / (8ull * Q) / TK_BC * TK_BC, 0, 0};
+    TopkPlan p{TOPK_FP32, free_bytes / (8ull * Q) / TK_BC * TK_BC, 0, 0, false};
     const uint64_t cap_fp32 = p.cap;
-    auto room = [&](uint64_t tile, uint64_t per_candidate, uint64_t granule, uint64_t least, TopkScreen screen) {
+    // (`per_round`: of the candidates' bytes, those that are better held twice, for this round and the next)
+    auto room = [&](uint64_t tile, uint64_t per_candidate, uint64_t per_round, uint64_t granule, uint64_t least, TopkScreen screen) {
         const uint64_t q_up = (Q + tile - 1) / tile * tile, q_bytes = q_up * (row_bytes + 4) + 512;
         if (free_bytes <= q_bytes) return false;
         const uint64_t cap = (free_bytes - q_bytes) / per_candidate / granule * granule;
         if (cap < n_up && cap < least) return false;
-        const uint64_t longest = screen == TOPK_STREAM ? (free_bytes - q_bytes) / Q * 8 / TK_BC * TK_BC : cap;
-        p = TopkPlan{screen, longest, q_up, std::min<uint64_t>({cap, n_up, TK_CAND_SLICE})};
+        const uint64_t twice = (free_bytes - q_bytes) / (per_candidate + per_round) / granule * granule;
+        const uint32_t steps = topk_steps(d);
+        const bool ahead = per_round && (steps <= TK_BESIDE || steps > (uint32_t)TK_HOLD) && (twice >= n_up || twice >= least);
+        const uint64_t held = ahead ? twice : cap;
+        const uint64_t longest = screen == TOPK_STREAM ? (free_bytes - q_bytes) / Q * 8 / TK_BC * TK_BC : held;
+        p = TopkPlan{screen, longest, q_up, std::min<uint64_t>({held, n_up, TK_CAND_SLICE}), ahead};
         return true;
     };
     const bool wide = Q > 2 * TK_STREAM_Q || (Q > TK_STREAM_Q && N <= (1u << 16) && topk_steps(d) <= TK_HOLD);
     const uint64_t least_wide = std::min<uint64_t>(8192, std::max<uint64_t>(1024, (1u << 22) / Q));
     const uint64_t least_stream = Q > TK_STREAM_Q ? std::max<uint64_t>(2 * TK_BC, cap_fp32 + cap_fp32 / 2) : 2 * TK_BC;
-    if (!wide || !room(WIDE_Q, 4ull * Q + row_bytes + 4, 256, least_wide, TOPK_WIDE))
-        room(32 * stream_tiles(Q), 4ull * Q, TK_BC, least_stream, TOPK_STREAM);
+    if (!wide || !room(WIDE_Q, 4ull * Q + row_bytes + 4, row_bytes + 4, 256, least_wide, TOPK_WIDE))
+        room(32 * stream_tiles(Q), 4ull * Q, 0, TK_BC, least_stream, TOPK_STREAM);
     p.cap = std::min<uint64_t>({p.cap, n_up, TK_CAND_SLICE});
     return p;
 }
@@ -1023,13 +1049,16 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
     a.bits = a.pend;
     a.pitch = (uint32_t)(cap / 32);
     at += (std::max(screen == TOPK_STREAM ? cap * Q / 8 : cap * Q * 4, plan.list * Q * 4) + 255) / 256 * 256;
-    void* qfrag = nullptr; float* qmargin = nullptr; void* cfrag = nullptr; float* cmargin = nullptr;
+    void* qfrag = nullptr; float* qmargin = nullptr; void* cfrag[2] = {nullptr, nullptr}; float* cmargin[2] = {nullptr, nullptr};
     if (screen != TOPK_FP32) {
         qfrag = at; at += q_up * row_bytes;
         qmargin = (float*)at; at += q_up * 4;
-        if (screen == TOPK_WIDE) { cfrag = at; at += cap * row_bytes; cmargin = (float*)at; at += cap * 4; }
+        for (int b = 0; screen == TOPK_WIDE && b < (plan.ahead ? 2 : 1); ++b) {
+            cfrag[b] = at; at += cap * row_bytes;
+            cmargin[b] = (float*)at; at += cap * 4;
+        }
     }
-    a.qfrag = qfrag; a.qmargin = qmargin; a.cfrag = cfrag; a.cmargin = cmargin;
+    a.qfrag = qfrag; a.qmargin = qmargin;
 
     // nothing below the threshold is ever wanted; without one, every cosine passes (-2 < -1)
     const float theta0 = tau > -2.0f ? tau : -2.0f;
@@ -1060,8 +1089,22 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
     const uint64_t growth = many || screen == TOPK_FP32 ? 4 : 16;
     uint64_t blocks_seen = 0;                  // that screened or might have
     uint64_t len = screen == TOPK_FP32 ? TK_BC : (many ? 256 : 1024);
-    for (uint64_t begin = 0; begin < N; begin += len, len = len * growth < cap ? len * growth : cap) {
-        if (len > cap) len = cap;
+    auto longer = [&](uint64_t x) { return x * growth < cap ? x * growth : cap; };
+    // With many queries an early round that would list many pairs goes through the fp32 screen, whose fold
+    // reads no rows: listing 4096 x 256 pairs of 300 columns and folding them takes 237 us, this way 85
+    // (4096 x 20 000, K = 64: 1047 -> 614 us in all; 4096 x 200 000, K = 30: 1540 -> 1360).  Below some 10^5
+    // pairs the fp32 product is not faster: 300 x 100 000 328 us, 334 with TK_EXACT_ROUND 50 000.
+    // (Where tau prunes from the start, nothing is known of how many pairs pass: screened.)
+    auto in_fp32 = [&](uint64_t begin, uint64_t len) {
+        const uint64_t m = std::min(len, N - begin);
+        const double share = begin ? std::min(1.0, (double)K / (double)begin) : 1.0;
+        return screen == TOPK_FP32 || (many && tau <= 0.f && 2 * m <= plan.list && share > 0.01 &&
+                                       share * (double)m * Q > TK_EXACT_ROUND);
+    };
+    int buffer = 0;                            // of the wide screen's rounded candidates: this round's
+    bool ready = false;                        // it holds them: rounded beside the round before
+    if (len > cap) len = cap;
+    for (uint64_t begin = 0; begin < N; begin += len, len = longer(len)) {
         a.c_begin = (uint32_t)begin;
         a.c_end = (uint32_t)(begin + len < N ? begin + len : N);
         const uint32_t m = a.c_end - a.c_begin;
@@ -1075,29 +1118,40 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
             if (blocks_seen) a.dense_skip = (uint32_t)std::min<uint64_t>(TK_NONE - 1, TK_SPARE + (blocks_seen + 1) / 2);
         }
         a.blocks = 0;
-        // With many queries an early round that would list many pairs goes through the fp32 screen, whose fold
-        // reads no rows: listing 4096 x 256 pairs of 300 columns and folding them takes 237 us, this way 85
-        // (4096 x 20 000, K = 64: 1047 -> 614 us in all; 4096 x 200 000, K = 30: 1540 -> 1360).  Below some 10^5
-        // pairs the fp32 product is not faster: 300 x 100 000 328 us, 334 with TK_EXACT_ROUND 50 000.
-        // (Where tau prunes from the start, nothing is known of how many pairs pass: screened.)
-        const bool exact_round = screen == TOPK_FP32 || (many && tau <= 0.f && 2ull * m <= plan.list &&
-                                                         share > 0.01 && share * m * Q > TK_EXACT_ROUND);
+        const bool exact_round = in_fp32(begin, len);
         a.cap = (uint32_t)(screen == TOPK_FP32 ? cap : exact_round ? plan.list / 2 : plan.list);   // (eight bytes a pair or four)
         if (screen == TOPK_WIDE && !exact_round) {
             a.nq_tiles = (Q + WIDE_Q - 1) / WIDE_Q;
             a.nc_tiles = (m + WIDE_C - 1) / WIDE_C;
-            const uint32_t tiles = a.nc_tiles * (WIDE_C / 32), total = a.nq_tiles * a.nc_tiles;
+            const uint32_t total = a.nq_tiles * a.nc_tiles;
             if (begin > 0) blocks_seen += a.blocks = total;
-            const dim3 grid(((total + 7u) / 8u) * 8u), block(64 * TK_WWM * TK_WWN);
-#define W2V_ROUND(VEC4, HOLD)                                                                              \
-    hipLaunchKernelGGL((topk_round_kernel<VEC4, HOLD>), dim3(tiles), dim3(64), 0, st, Cm, a.c_begin, a.c_end, d, \
-                       (float*)a.invc, cfrag, cmargin)
-            if (vec4 && topk_steps(d) >= TK_HOLD_LEAST && topk_steps(d) <= TK_HOLD) W2V_ROUND(true, TK_HOLD);
-            else if (vec4) W2V_ROUND(true, 0);
-            else W2V_ROUND(false, 0);
+            auto rounded = [&](uint64_t first, uint64_t count, int buf) {
+                const uint32_t end = (uint32_t)std::min<uint64_t>(first + count, N);
+                return RoundArgs{Cm, (uint32_t)first, end, d, blocks_for(end - (uint32_t)first, WIDE_C) * (WIDE_C / 32),
+                                 (float*)a.invc, cfrag[buf], cmargin[buf]};
+            };
+            if (!ready) {
+                const RoundArgs now = rounded(begin, len, buffer);
+#define W2V_ROUND(VEC4, HOLD) hipLaunchKernelGGL((topk_round_kernel<VEC4, HOLD>), dim3(now.tiles), dim3(64), 0, st, now)
+                if (vec4 && topk_steps(d) >= TK_HOLD_LEAST && topk_steps(d) <= TK_HOLD) W2V_ROUND(true, TK_HOLD);
+                else if (vec4) W2V_ROUND(true, 0);
+                else W2V_ROUND(false, 0);
 #undef W2V_ROUND
-            if (vec4) hipLaunchKernelGGL((topk_wide_kernel<TK_WTM, TK_WTN, TK_WWM, TK_WWN, TK_WWPE, true>), grid, block, 0, st, a);
-            else hipLaunchKernelGGL((topk_wide_kernel<TK_WTM, TK_WTN, TK_WWM, TK_WWN, TK_WWPE, false>), grid, block, 0, st, a);
+            }
+            a.cfrag = cfrag[buffer]; a.cmargin = cmargin[buffer];
+            buffer ^= plan.ahead ? 1 : 0;
+            RoundArgs after{};
+            const uint64_t next = begin + len;
+            ready = plan.ahead && next < N && !in_fp32(next, longer(len));
+            if (ready) after = rounded(next, longer(len), buffer);
+            const uint32_t round_blocks = (blocks_for(after.tiles, TK_WWM * TK_WWN) + 7) / 8 * 8;
+            const dim3 grid(((total + 7u) / 8u) * 8u + round_blocks), block(64 * TK_WWM * TK_WWN);
+#define W2V_WIDE(VEC4, AFTER)                                                                              \
+    hipLaunchKernelGGL((topk_wide_kernel<TK_WTM, TK_WTN, TK_WWM, TK_WWN, TK_WWPE, VEC4, std::decay_t<decltype(AFTER)>>), grid, \
+                       block, 0, st, a, AFTER)
+            if (ready) { if (vec4) W2V_WIDE(true, after); else W2V_WIDE(false, after); }
+            else { if (vec4) W2V_WIDE(true, NoRound{}); else W2V_WIDE(false, NoRound{}); }
+#undef W2V_WIDE
         } else if (screen == TOPK_STREAM && !exact_round) {
             const uint32_t tq = stream_tiles(Q);
             const uint32_t q_tiles = blocks_for(Q, 32 * tq);
