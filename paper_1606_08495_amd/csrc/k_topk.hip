@@ -94,6 +94,28 @@ __device__ __forceinline__ float4 load_cols(const float* __restrict__ row, bool 
     return r;
 }
 
+// The same from a row that may be read, and without a branch: what lies past the last column is read elsewhere in the
+// row.  (Loads behind branches cannot be counted, so that each wait is for all of them.)
+template <bool VEC4>
+__device__ __forceinline__ float4 load_cols_flat(const float* __restrict__ row, uint32_t k, uint32_t d) {
+    float4 r;
+    if (VEC4) {
+        r = *(const float4*)(row + (k < d ? k : 0u));
+    } else {
+        r.x = row[k + 0 < d ? k + 0 : 0u]; r.y = row[k + 1 < d ? k + 1 : 0u];
+        r.z = row[k + 2 < d ? k + 2 : 0u]; r.w = row[k + 3 < d ? k + 3 : 0u];
+    }
+    return r;
+}
+template <bool VEC4>
+__device__ __forceinline__ float4 cols_inside(float4 r, uint32_t k, uint32_t d) {
+    if (k + 0 >= d) r.x = 0.f;
+    if (k + (VEC4 ? 0 : 1) >= d) r.y = 0.f;
+    if (k + (VEC4 ? 0 : 2) >= d) r.z = 0.f;
+    if (k + (VEC4 ? 0 : 3) >= d) r.w = 0.f;
+    return r;
+}
+
 // Squared length of a row: sixteen chains by column number mod 16, then a fixed tree -- the same bits
 // from one lane that walks the whole row and from two lanes that take alternate groups of eight.
 __device__ __forceinline__ void square8(const float4& a, const float4& b, float (&s)[8]) {
@@ -643,15 +665,23 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a
 // Stream screen: a wavefront takes 32 candidates and TQ tiles of 32 queries (q_first + blockIdx.y: which).  The
 // lane pair (l, l ^ 32) walks candidate l % 32, eight columns at a time each; the rounded columns are
 // a matrix-core operand as they stand.  Four steps of candidate columns are in flight ahead of the
-// four in work; the queries' operands come from L2.  The pairs to look at are left as a bit each: a block
+// four in work.  The queries' operands go through two LDS buffers of as many steps, asked for one panel ahead of the
+// columns: read from memory where they are multiplied, every one of them waited for all columns on their way as well
+// (whole search, us, that way and this: 200 queries over 200 001 x 512 555, 469; 32 over 500 000 x 300 476, 436; 100 over
+// 200 003 x 100 129, 122; 250 over 100 001 x 31 155, 155).  Held to three wavefronts per SIMD at 128 queries, it spills:
+// 522 and 130.
+// The pairs to look at are left as a bit each: a block
 // writes sixteen bytes per query, needs no counters, and a round may be as long as there is room for bits.
-// (With lists of four bytes a pair a search of 100 queries over 200 003 x 100 took five rounds, 193 us; now three, 123.)
+// (With lists of four bytes a pair a search of 100 queries over 200 003 x 100 took five rounds, 193 us; with three, 123.)
 // ---------------------------------------------------------------------------------------------
 constexpr int TK_AHEAD = 4;
 template <int TQ, bool VEC4>
 __global__ __launch_bounds__(256, TQ == 1 ? 4 : (TQ == 2 ? 3 : 2)) void topk_stream_kernel(TopkArgs a) {
     __shared__ __align__(16) float s_level[TQ * 32];
-    __shared__ ExactLds<2, 2> exact;
+    constexpr int PANEL = TQ * TK_AHEAD * 64;                // 16-byte units, TQ of them a thread
+    static_assert(PANEL == TQ * 256, "a step of a tile per wavefront and move");
+    union Lds { v8b panel[2][PANEL]; ExactLds<2, 2> exact; __device__ Lds() {} };
+    __shared__ Lds lds;
     __shared__ uint32_t s_hits, s_dense;
     __shared__ __align__(16) uint32_t s_words[TQ * 32][4];
     const int tid = threadIdx.x, lane = tid % 64, fk = lane >> 5;
@@ -665,11 +695,20 @@ __global__ __launch_bounds__(256, TQ == 1 ? 4 : (TQ == 2 ? 3 : 2)) void topk_str
 #pragma unroll
         for (int i = 0; i < TK_AHEAD; ++i) {
             const uint32_t k = (ks + i) * TK_KS + 8 * fk;
-            r[i][0] = load_cols<VEC4>(row, c_ok, k, a.d);        // (zero past the last column)
-            r[i][1] = load_cols<VEC4>(row, c_ok, k + 4, a.d);
+            r[i][0] = load_cols_flat<VEC4>(row, k, a.d);
+            r[i][1] = load_cols_flat<VEC4>(row, k + 4, a.d);
         }
     };
+    const uint32_t steps = topk_steps(a.d);
+    const v8b* qf = (const v8b*)a.qfrag + (uint64_t)qt0 * steps * 64 + lane;
+    v8b qr[TQ];
+    auto fetch_queries = [&](uint32_t ks) {                  // this thread's part of the panel of steps ks ..
+        const uint32_t step = min(ks + tid / 64, steps - 1);
+#pragma unroll
+        for (int t = 0; t < TQ; ++t) qr[t] = qf[((uint64_t)t * steps + step) * 64];
+    };
     const uint32_t counted = dense_so_far(a);
+    fetch_queries(0);
     fetch(x, 0);
     for (int i = tid; i < TQ * 32; i += 256) {
         const uint32_t q = qt0 * 32 + i;
@@ -679,21 +718,28 @@ __global__ __launch_bounds__(256, TQ == 1 ? 4 : (TQ == 2 ? 3 : 2)) void topk_str
     __syncthreads();
     bool dense = s_dense != 0;                               // uniform per block
     if (!dense) {
-        const uint32_t steps = topk_steps(a.d);
-        const v8b* qf = (const v8b*)a.qfrag + (uint64_t)qt0 * steps * 64 + lane;
         v16f acc[TQ];
 #pragma unroll
         for (int t = 0; t < TQ; ++t)
 #pragma unroll
             for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
         float sq[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, e2 = 0.f;
-        for (uint32_t ks0 = 0; ks0 < steps; ks0 += TK_AHEAD) {
-            fetch(nx, ks0 + TK_AHEAD);
+        int buf = 0;
+        for (uint32_t ks0 = 0; ks0 < steps; ks0 += TK_AHEAD, buf ^= 1) {
+#pragma unroll
+            for (int t = 0; t < TQ; ++t) lds.panel[buf][t * 256 + tid] = qr[t];
+            if (ks0 + TK_AHEAD < steps) {
+                fetch_queries(ks0 + TK_AHEAD);
+                fetch(nx, ks0 + TK_AHEAD);
+            }
+            __syncthreads();                                 // (a buffer is written again a barrier after its last read)
 #pragma unroll
             for (int i = 0; i < TK_AHEAD; ++i) {
-                const uint32_t ks = ks0 + i;
+                const uint32_t ks = ks0 + i, k = ks * TK_KS + 8 * fk;
                 if (ks < steps) {
-                    const float v[8] = {x[i][0].x, x[i][0].y, x[i][0].z, x[i][0].w, x[i][1].x, x[i][1].y, x[i][1].z, x[i][1].w};
+                    const float4 xa = c_ok ? cols_inside<VEC4>(x[i][0], k, a.d) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    const float4 xb = c_ok ? cols_inside<VEC4>(x[i][1], k + 4, a.d) : make_float4(0.f, 0.f, 0.f, 0.f);
+                    const float v[8] = {xa.x, xa.y, xa.z, xa.w, xb.x, xb.y, xb.z, xb.w};
                     v8b g;
 #pragma unroll
                     for (int e = 0; e < 8; ++e) {
@@ -701,10 +747,10 @@ __global__ __launch_bounds__(256, TQ == 1 ? 4 : (TQ == 2 ? 3 : 2)) void topk_str
                         const float lost = v[e] - (float)g[e];
                         e2 = fmaf(lost, lost, e2);
                     }
-                    square8(x[i][0], x[i][1], sq);
+                    square8(xa, xb, sq);
 #pragma unroll
                     for (int t = 0; t < TQ; ++t)
-                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(qf[((uint64_t)t * steps + ks) * 64], g, acc[t], 0, 0, 0);
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lds.panel[buf][t * 256 + i * 64 + lane], g, acc[t], 0, 0, 0);
                 }
             }
 #pragma unroll
@@ -736,7 +782,7 @@ __global__ __launch_bounds__(256, TQ == 1 ? 4 : (TQ == 2 ? 3 : 2)) void topk_str
                 *(uint4*)(a.bits + (uint64_t)q * a.pitch + blockIdx.x * 4) = *(const uint4*)s_words[tid];
         }
     }
-    if (dense) exact_block<2, 2, VEC4, false, true>(a, qt0 * 32, c0, exact);
+    if (dense) exact_block<2, 2, VEC4, false, true>(a, qt0 * 32, c0, lds.exact);
 }
 
 // The fp32 screen: nothing but such blocks, mapped to XCDs as above.
