@@ -541,7 +541,7 @@ def main():
     ap.add_argument("--no-prefetch", action="store_true",
                     help="do not announce the next minibatch to the shard (w2v_prefetch_minibatch)")
     ap.add_argument("--graph", action="store_true",
-                    help="text workloads: run every step as a replay of one captured step "
+                    help="text workloads: run every step through one prepared step "
                          "(w2v_step_graph), the form meant for small minibatches")
     ap.add_argument("--pairs-per-minibatch", type=int, default=0,
                     help="override the workload's minibatch size (pairs)")
@@ -622,7 +622,7 @@ def main():
 
         def step(h):
             a, b = stream.next()
-            if step_graph is not None:          # one captured step, replayed (small minibatches)
+            if step_graph is not None:          # one prepared step (small minibatches)
                 step_graph.run(a, b, w2v.minibatch_seed(wl.seed, h), workloads.alpha_schedule(wl, h, H))
                 return a, b
             if args.prefetch_depth == 2:
@@ -766,7 +766,7 @@ def main():
         dom = max(timed, key=lambda p: per_phase[p]["ms_per_launch"] * per_phase[p]["launches"])
         dom_ms = per_phase[dom]["ms_per_launch"]
     else:
-        # a captured step records no per-phase events: the roofline entry is the whole step's, its
+        # a prepared step records no per-phase events: the roofline entry is the whole step's, its
         # bytes the sum over the row kernels
         dom, dom_ms = "step", ms_per_step
         algo["step"] = algo["uside"] + algo["wside"] + (0 if fused else algo["dot"])
