@@ -901,6 +901,17 @@ extern "C" int w2v_negatives(w2v_shard* sh, const uint32_t* out_idx, uint32_t n,
     return W2V_OK;
 }
 
+// The destination keys and the checked input words, in one launch (dotprod and adjust of 1500 pairs, d = 100, over three
+// shards 173 us, in two launches 177; 300 pairs, d = 60, 66 and 69).
+static void launch_keys_and_inputs(w2v_shard* sh, const uint32_t* in_idx, const uint32_t* out_idx, uint32_t n, uint32_t k,
+                                   uint64_t seed, uint32_t* keys, uint32_t* in_safe, hipStream_t st) {
+    IndexPrologue pro{};
+    pro.nt = NoiseTable{sh->bins, sh->V}; pro.out_idx = out_idx; pro.n = n; pro.T = k + 1;
+    pro.seed_lo = (uint32_t)seed; pro.seed_hi = (uint32_t)(seed >> 32);
+    pro.keys = keys; pro.in_idx = in_idx; pro.in_safe = in_safe; pro.err = sh->err;
+    launch_index_prologue(pro, st);
+}
+
 extern "C" int w2v_dotprod(w2v_shard* sh, const uint32_t* in_idx, const uint32_t* out_idx,
                            uint32_t n, uint32_t k, uint64_t seed, float* partial_dots,
                            void* stream) {
@@ -922,8 +933,7 @@ extern "C" int w2v_dotprod(w2v_shard* sh, const uint32_t* in_idx, const uint32_t
         p.keys = x.keys; p.in_safe = x.in_safe;
     } else {
         Phase ph(sh, W2V_PH_NEG, st);
-        launch_check_inputs(in_idx, n, sh->V, p.in_safe, sh->err, st);
-        launch_dest_keys(NoiseTable{sh->bins, sh->V}, out_idx, n, k, seed, p.keys, sh->err, st);
+        launch_keys_and_inputs(sh, in_idx, out_idx, n, k, seed, p.keys, p.in_safe, st);
     }
     {
         Phase ph(sh, W2V_PH_DOT, st);
@@ -955,8 +965,7 @@ extern "C" int w2v_dotprod_noalloc(w2v_shard* sh, const uint32_t* in_idx, const 
     hipStream_t st = (hipStream_t)stream;
     uint32_t* keys = sh->static_ws;
     uint32_t* in_safe = sh->static_ws + keys_u32;
-    launch_check_inputs(in_idx, n, sh->V, in_safe, sh->err, st);
-    launch_dest_keys(NoiseTable{sh->bins, sh->V}, out_idx, n, k, seed, keys, sh->err, st);
+    launch_keys_and_inputs(sh, in_idx, out_idx, n, k, seed, keys, in_safe, st);
     launch_dots(sh->U, sh->W, sh->g, in_safe, keys, n, k + 1, partial_dots, st);
     HIP_TRY(hipGetLastError());
     return W2V_OK;
