@@ -385,10 +385,14 @@ void sort_and_mark(const SortJob (&jobs)[2], uint32_t bits, uint32_t* sort_tmp, 
 // keys (positive word + regenerated negatives) and both sorts.
 // The fused step's input-side kernel needs both sorts (it updates the output rows that one slot names),
 // so there everything is queued on the caller's stream, both sides' keys through the same launches; and so
-// for small minibatches, whose keys are grouped in one launch.  With given coefficients that kernel needs the keys and the (small) input-side sort only: key
+// for minibatches of up to JOINT_SORT_MOST keys in all, where two chains of launches and the events between
+// streams cost more than the walk's sort hides behind the input side (dotprod and adjust, k = 5, two streams and
+// one, us: 20 000 pairs, d = 200, two shards 377, 283; 50 000, d = 60 191, 161, d = 300 470, 446; 200 000, d = 60 383, 371,
+// d = 300 1236, 1230; 350 000, d = 60 568, 563, d = 200 1381, 1392).  With given coefficients that kernel needs the keys and the (small) input-side sort only: key
 // generation and output-side sort are queued on the shard's second stream, forked by an event, while
 // the caller's stream checks the inputs and sorts the input side; it then waits for the keys, and just
 // before the first kernel that reads the output-side order for that sort (*join, join_output_sort).
+constexpr uint32_t JOINT_SORT_MOST = 1500000;
 int queue_keys_and_sorts(w2v_shard* sh, Plan& p, const uint32_t* in_idx, const uint32_t* out_idx,
                          uint32_t k, uint64_t seed, uint32_t** sku, uint32_t** perm, uint32_t** skw,
                          uint32_t** sidx, bool* join, hipStream_t st) {
@@ -398,7 +402,7 @@ int queue_keys_and_sorts(w2v_shard* sh, Plan& p, const uint32_t* in_idx, const u
     const NoiseTable nt{sh->bins, sh->V};
     const bool small = group_small(p.M, p.n);
     w2v_shard* spans = p.one_stream ? nullptr : sh;
-    if (!sh->overlap || p.one_stream || p.own_rows || small) {
+    if (!sh->overlap || p.one_stream || p.own_rows || p.M + p.n <= JOINT_SORT_MOST) {
         // keys, checked inputs and the fills in one launch
         const SortJob jobs[2] = {{p.keys, p.M, p.wb0, p.wb1, skw, sidx},
                                  {p.in_safe, p.n, p.ub0, p.ub1, sku, perm}};
