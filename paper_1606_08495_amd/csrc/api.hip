@@ -18,6 +18,28 @@
 namespace w2v {
 bool build_noise_table_host(const uint64_t* counts, uint32_t V, uint32_t* thresh, uint32_t* alias);
 void build_keep_thresholds_host(const uint64_t* counts, uint32_t V, double t, uint64_t* keep);
+
+// Grow a scratch region to at least `bytes`.  It is never shrunk: where the memory cannot be had, it is made what it was
+// again (at another address, perhaps), so that whatever it held before still fits.
+enum RegionGrowth { REGION_HOLDS, REGION_NO_MEMORY, REGION_NOT_RELEASED };
+RegionGrowth grow_region(char** region, size_t* cap, size_t bytes, int (*alloc)(void**, size_t), int (*release)(void*),
+                         int* error) {
+    if (bytes <= *cap) return REGION_HOLDS;
+    const size_t held = *cap;
+    if (*region) {
+        *error = release(*region);
+        if (*error) return REGION_NOT_RELEASED;
+    }
+    *region = nullptr; *cap = 0;
+    for (const size_t want : {bytes + bytes / 8 + 4096, bytes, held}) {
+        if (want == 0) continue;
+        void* p = nullptr;
+        const int e = alloc(&p, want);
+        if (e == 0) { *region = (char*)p; *cap = want; break; }
+        if (want >= bytes) *error = e;
+    }
+    return *cap >= bytes ? REGION_HOLDS : REGION_NO_MEMORY;
+}
 }  // namespace w2v
 
 using namespace w2v;
@@ -139,6 +161,8 @@ struct w2v_shard {
     // scratch: one region, carved per call
     char* ws = nullptr;
     size_t ws_cap = 0;
+    uint64_t ws_epoch = 0;          // how often a call that needed it has grown the region: prepared steps are of one epoch
+    size_t joint_refused = SIZE_MAX;    // scratch of joint rows that could not be had
     // scratch of the pair formation, apart from the training calls' so that the two may overlap
     char* pairs_ws = nullptr;
     size_t pairs_ws_cap = 0;
@@ -184,27 +208,31 @@ struct Carver {
     }
 };
 
-// Grow a scratch region to at least `bytes` (it is never shrunk; growing waits for the device).
+// Grow a scratch region to at least `bytes`; growing waits for the device.
 int ensure_region(char*& region, size_t& cap, size_t bytes) {
-    if (bytes <= cap) return W2V_OK;
-    if (region) { HIP_TRY(hipDeviceSynchronize()); HIP_TRY(hipFree(region)); region = nullptr; cap = 0; }
-    size_t want = bytes + bytes / 8 + 4096;
-    hipError_t e = hipMalloc((void**)&region, want);
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        want = bytes;
-        e = hipMalloc((void**)&region, want);
-    }
-    if (e != hipSuccess) {
-        (void)hipGetLastError();
-        return fail(W2V_ERR_ALLOC, "scratch allocation of %zu bytes failed: %s", want,
-                    hipGetErrorString(e));
-    }
-    cap = want;
-    return W2V_OK;
+    auto alloc = [](void** p, size_t n) -> int {
+        const hipError_t e = hipMalloc(p, n);
+        if (e != hipSuccess) (void)hipGetLastError();
+        return (int)e;
+    };
+    auto release = [](void* p) -> int {
+        const hipError_t e = hipDeviceSynchronize();
+        return (int)(e != hipSuccess ? e : hipFree(p));
+    };
+    int e = 0;
+    const RegionGrowth g = grow_region(&region, &cap, bytes, alloc, release, &e);
+    if (g == REGION_HOLDS) return W2V_OK;
+    return fail(g == REGION_NO_MEMORY ? W2V_ERR_ALLOC : W2V_ERR_HIP, "scratch allocation of %zu bytes failed: %s", bytes,
+                hipGetErrorString((hipError_t)e));
 }
 
-int ensure_ws(w2v_shard* sh, size_t bytes) { return ensure_region(sh->ws, sh->ws_cap, bytes); }
+// `extra`: a smaller region would have served this call too (prepared steps stay valid, which use what is there).
+int ensure_ws(w2v_shard* sh, size_t bytes, bool extra = false) {
+    const size_t held = sh->ws_cap;
+    const int rc = ensure_region(sh->ws, sh->ws_cap, bytes);
+    if (sh->ws_cap != held && !extra) sh->ws_epoch++;
+    return rc;
+}
 
 struct Phase {
     w2v_shard* sh; int phase; hipStream_t st; hipEvent_t a = nullptr, b = nullptr;
@@ -1088,23 +1116,32 @@ extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const u
     }
     Slices sl{};
     Target to{s0->U, s0->W, nullptr, s0->g};
-    bool fused = (S == 1);
-    if (S > 1 && take_as_one(shards, S, &sl, &to.g)) { fused = true; to.slices = &sl; }
-    Plan sz{};
-    auto plan = [&](char* base) {
+    auto plan = [&](char* base, bool fused) {
         return make_plan(base, n, k, fused ? to.g.stride4 : stride_max,
                          fused ? (loss ? 1u : 0u) : S,               // fused: the dots are kept for the loss only
                          true, true, fused && s0->own_rows ? s0->V : 0u);
     };
-    sz = plan(nullptr);
-    rc = ensure_ws(s0, sz.bytes);
-    if (rc == W2V_ERR_ALLOC && S > 1 && fused) {          // (one shard after the other needs less scratch)
-        fused = false;
-        sz = plan(nullptr);
-        rc = ensure_ws(s0, sz.bytes);
+    bool fused = S == 1 || take_as_one(shards, S, &sl, &to.g);
+    if (S > 1 && fused) {
+        to.slices = &sl;
+        // One shard after the other needs less scratch.  What serves that is not grown while the caller captures, and
+        // not tried again once it could not be had: a step would wait for the device and allocate each time.
+        const size_t need = plan(nullptr, true).bytes;
+        const bool apart_fits = plan(nullptr, false).bytes <= s0->ws_cap;
+        if (need > s0->ws_cap) {
+            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+            if (apart_fits && hipStreamIsCapturing(st, &capture) != hipSuccess) (void)hipGetLastError();
+            if (need >= s0->joint_refused || capture != hipStreamCaptureStatusNone) fused = false;
+        }
+        if (fused) {
+            rc = ensure_ws(s0, need, apart_fits);
+            if (rc == W2V_ERR_ALLOC) { s0->joint_refused = need; fused = false; }
+            else if (rc) return rc;
+        }
     }
+    rc = ensure_ws(s0, plan(nullptr, fused).bytes);
     if (rc) return rc;
-    Plan p = plan(s0->ws);
+    Plan p = plan(s0->ws, fused);
     uint32_t *sku, *perm, *skw, *sidx;
     bool join = false;
     // a set computed by w2v_prefetch_minibatch on shard 0 (every shard holds the same noise table)
@@ -1184,7 +1221,7 @@ struct w2v_step_graph {
     w2v_shard* sh = nullptr;
     uint32_t n = 0, k = 0;
     double* loss = nullptr;
-    const char* ws_at_creation = nullptr;
+    uint64_t epoch = 0;                 // of the shard's scratch, when this was made
     Plan plan(char* base) const {
         Plan p = make_plan(base, n, k, sh->g.stride4, loss ? 1u : 0u, true, true, sh->own_rows ? sh->V : 0u);
         p.one_stream = true;
@@ -1205,7 +1242,7 @@ extern "C" int w2v_step_graph_create(w2v_shard* sh, uint32_t n, uint32_t k, doub
     g->sh = sh; g->n = n; g->k = k; g->loss = loss;
     rc = ensure_ws(sh, g->plan(nullptr).bytes);
     if (rc) { delete g; return rc; }
-    g->ws_at_creation = sh->ws;
+    g->epoch = sh->ws_epoch;
     *out = g;
     return W2V_OK;
 }
@@ -1216,7 +1253,7 @@ extern "C" int w2v_step_graph_run(w2v_step_graph* g, const uint32_t* in_idx, con
     w2v_shard* sh = g->sh;
     int rc = check_device(sh);
     if (rc) return rc;
-    if (sh->ws != g->ws_at_creation)
+    if (sh->ws_epoch != g->epoch || g->plan(nullptr).bytes > sh->ws_cap)
         return fail(W2V_ERR_STATE, "the shard's scratch region was reallocated by a larger call after this "
                     "step was captured: create the graph again");
     hipStream_t st = (hipStream_t)stream;

@@ -78,3 +78,81 @@ def test_a_shard_listed_twice_is_updated_twice():
         assert np.array_equal(all_rows(a, which), all_rows(b, which))
     a.destroy()
     b.destroy()
+
+
+def test_joint_step_leaves_a_prepared_step_valid():
+    """Joint rows take more scratch than one shard after the other, which had room in what the prepared step reserved."""
+    rng = np.random.default_rng(4)
+    V, n, k = 500, 4000, 5
+    counts = zipf_counts(V)
+    sets = [[make_shard(V, 60, 5, counts, d_total=120, col_begin=60 * i) for i in range(2)] for _ in range(2)]
+    a, b = dev(rng.integers(0, V, n)), dev(rng.integers(0, V, n))
+    graph = w2v.StepGraph(sets[0][0], n, k)
+    for one, shards in zip((lambda: graph.run(a, b, 9, 0.01), lambda: w2v.train_minibatch(sets[1][:1], a, b, k, 9, 0.01)), sets):
+        w2v.train_minibatch(shards, a, b, k, 8, 0.01)
+        one()
+    for x, y in zip(*sets):
+        for which in (0, 1):
+            assert np.array_equal(all_rows(x, which), all_rows(y, which))
+    graph.destroy()
+    for s in sets[0] + sets[1]:
+        s.destroy()
+
+
+def test_without_memory_for_joint_rows_the_shards_are_trained_apart():
+    """Scratch of joint rows (16 x 64 columns, some 2.5 GB) that cannot be had: the step takes each shard on its own,
+    and the scratch that a prepared step reserved stays."""
+    rng = np.random.default_rng(5)
+    V, n, k, S = 2000, 1 << 19, 5, 16
+    counts = zipf_counts(V)
+    sets = [[make_shard(V, 64, 5, counts, d_total=64 * S, col_begin=64 * i) for i in range(S)] for _ in range(2)]
+    a, b = dev(rng.integers(0, V, n)), dev(rng.integers(0, V, n))
+    big = dev(rng.integers(0, V, 2 * n))
+    loss = [torch.zeros(1, dtype=torch.float64, device="cuda") for _ in range(2)]
+    graph = w2v.StepGraph(sets[0][0], 2 * n, k)
+    w2v.train_minibatch(sets[1], a, b, k, 7, 1e-4, loss=loss[1])
+    w2v.train_minibatch(sets[1][:1], big, big, k, 8, 1e-4)
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    hog = torch.empty(torch.cuda.mem_get_info()[0] - (1 << 30), dtype=torch.uint8, device="cuda")
+    free = []
+    for h in range(3):
+        w2v.train_minibatch(sets[0], a, b, k, 7, 1e-4 if h == 0 else 0.0, loss=loss[0] if h == 0 else None)
+        free.append(torch.cuda.mem_get_info()[0])
+    graph.run(big, big, 8, 1e-4)
+    torch.cuda.synchronize()
+    del hog
+    torch.cuda.empty_cache()
+    assert free[0] == free[1] == free[2] and free[0] > 1 << 29        # (joint rows would have left less)
+    assert abs(float(loss[0]) - float(loss[1])) <= 1e-6 * abs(float(loss[1]))
+    for x, y in zip(*sets):
+        for which in (0, 1):
+            assert vec_error(all_rows(x, which), all_rows(y, which)) <= TOL
+        x.status()
+    graph.destroy()
+    for s in sets[0] + sets[1]:
+        s.destroy()
+
+
+def test_a_captured_step_over_shards_grows_nothing():
+    """Scratch that holds one shard after the other, but not joint rows: under capture the step makes do with it."""
+    rng = np.random.default_rng(6)
+    V, n, k = 500, 1500, 5
+    counts = zipf_counts(V)
+    sets = [[make_shard(V, 60, 5, counts, d_total=300, col_begin=60 * i) for i in range(5)] for _ in range(2)]
+    a, b = dev(rng.integers(0, V, n)), dev(rng.integers(0, V, n))
+    more = dev(rng.integers(0, V, 2 * n))
+    w2v.train_minibatch(sets[0][:1], more, more, k, 8, 0.0)      # one shard's scratch for twice the pairs, a fifth of the columns
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph):
+        w2v.train_minibatch(sets[0], a, b, k, 9, 0.01)
+    for replay in range(3):
+        graph.replay()
+        torch.cuda.synchronize()
+        w2v.train_minibatch(sets[1], a, b, k, 9, 0.01)
+        for x, y in zip(*sets):
+            for which in (0, 1):
+                assert vec_error(all_rows(x, which), all_rows(y, which)) <= (replay + 1) * TOL
+    for s in sets[0] + sets[1]:
+        s.destroy()

@@ -142,6 +142,37 @@ def test_scratch_of_a_minibatch_holds_every_smaller_one():
             held = sort_scratch(n0, n1)
 
 
+@pytest.mark.parametrize("free,asked,held_after", [(10_000, 50_000, 10_000), (60_000, 50_000, 50_000), (100_000, 50_000, 60_346)])
+@pytest.mark.parametrize("same_address", [False, True])
+def test_a_region_that_cannot_grow_is_left_as_large_as_it_was(free, asked, held_after, same_address):
+    """What a prepared step was promised stays there: against an allocator of `free` bytes, of which 10 000 are held,
+    that gives out new addresses or the first that is free again."""
+    alloc_t = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.POINTER(ctypes.c_void_p), ctypes.c_size_t)
+    release_t = ctypes.CFUNCTYPE(ctypes.c_int, ctypes.c_void_p)
+    blocks, made = {4096: 10_000}, [0]
+
+    def alloc(p, n):
+        if sum(blocks.values()) + n > free:
+            return 2
+        made[0] += 1
+        at = 4096 if same_address else 4096 + (made[0] << 32)
+        assert at not in blocks
+        blocks[at], p[0] = n, at
+        return 0
+
+    def release(p):
+        del blocks[p]
+        return 0
+
+    fn = ctypes.CDLL(w2v.LIB_PATH)._ZN3w2v11grow_regionEPPcPmmPFiPPvmEPFiS3_EPi
+    fn.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.POINTER(ctypes.c_size_t), ctypes.c_size_t, alloc_t, release_t,
+                   ctypes.POINTER(ctypes.c_int)]
+    region, cap, error = ctypes.c_void_p(4096), ctypes.c_size_t(10_000), ctypes.c_int(0)
+    rc = fn(region, cap, asked, alloc_t(alloc), release_t(release), error)
+    assert (rc == 0) == (held_after >= asked) and (rc == 0 or error.value == 2)
+    assert cap.value == held_after and blocks == {region.value: held_after}
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("d,big,small,k", [(300, 20_165, 20_164, 25), (300, 98_304, 98_303, 5)])
 def test_a_smaller_minibatch_leaves_a_captured_step_valid(d, big, small, k):
