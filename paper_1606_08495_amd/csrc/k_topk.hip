@@ -59,7 +59,9 @@ constexpr float TK_TINY = 1e-30f;         // squared lengths below this are not 
 // the blocks so far have, the rounds that follow do not screen.
 // Vectors around one direction, noise 0.03 of the components, K = 30; us, in brackets with every pair in fp32:
 // 4096 queries over 200 000 x 300 4760 [4550], 300 1070 [880], 100 530 [700], 7 480 [485]; with hits of a
-// tile of 32 x 32 above 128 re-formed by its own wavefront, as it was, 13 200, 1970, 14 600, 390.  What the
+// tile of 32 x 32 above 128 re-formed by its own wavefront, as it was, 13 200, 1970, 14 600, 390.  Rows of 100 columns,
+// whose next round is rounded beside the products: 4096 queries 2055, 1000 739, 300 504; where a round that does not
+// screen is left out of the count, so that the next one screens again, 2175, 790, 549.  What the
 // count costs where nothing is crowded: a barrier per block, 2 % at most (300 queries over 200 000 x 16).
 // (TK_DENSE_WIDE 256, 1024, 2048 on the first at noise 0.1: 3.90, 3.91, 5.05 ms against 3.74.
 // TK_DENSE_STREAM 8, 16: 10 queries over 100 000 x 300, noise 0.3, 303 and 483 us against 302.
@@ -614,7 +616,7 @@ __global__ __launch_bounds__(64 * WM * WN, WPE) void topk_wide_kernel(TopkArgs a
             for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
     fetch(0);
     stash(0);
-    tell_dense(a, counted, blockIdx.x == 0, &s_hits, &s_dense);
+    tell_dense(a, counted, block == 0, &s_hits, &s_dense);       // (the first that screens)
     if (panels > 1) fetch(1);
     __syncthreads();
     bool dense = s_dense != 0;                               // uniform per block

@@ -245,6 +245,25 @@ def test_crowded_similarities(Q, N, spread):
         assert np.array_equal(gi, np.tile(np.arange(30, dtype=np.uint32), (Q, 1)))
 
 
+@pytest.mark.parametrize("Q,N,d", [(512, 60_160, 100), (512, 60_160, 7), (512, 60_160, 300), (512, 21_760, 400), (100, 148_480, 100)])
+def test_crowded_rounds_stay_counted(Q, N, d):
+    """Every block that screens or might have, from the second round on, is counted as crowded where all similarities are:
+    by itself, or by the first block of a round that does not screen.  (The count lies behind the flag word in the
+    workspace.)  Rows with and without the next round's rounding beside the products, and few queries."""
+    say("crowded", Q, N, d)
+    rng = np.random.default_rng(8)
+    base = rng.standard_normal(d)
+    q, c = (torch.from_numpy((base + 1e-4 * rng.standard_normal((n, d))).astype(np.float32)).cuda() for n in (Q, N))
+    ws = torch.zeros(int(w2v.lib().w2v_topk_cosine_workspace(Q, N, 32768)), dtype=torch.uint8, device="cuda")
+    w2v.topk_cosine(q, c, 30, 0.5, workspace=ws)
+    up = lambda n: (n + 255) // 256 * 256
+    at = 2 * up(4 * Q) + up(4 * N) + 2 * up(4 * Q)              # 1 / |query|, 1 / |candidate|, thresholds, two counts
+    counted = int(ws[at + 4:at + 8].view(torch.int32).item())
+    wide = screen_of(Q, N, d, ws.numel()) == 2
+    begin, tiles = (256, -(-Q // 256)) if wide else (1024, -(-Q // 128))
+    assert (N - begin) % 128 == 0 and counted == tiles * (N - begin) // 128
+
+
 @pytest.mark.parametrize("Q", [40, 140])
 def test_rows_without_a_usable_length(Q):
     """Zero, tiny, huge, infinite and NaN rows on either side."""
