@@ -148,6 +148,7 @@ struct TopkArgs {
     const float* invq; const float* invc; const float* theta;
     uint32_t* cnt; uint32_t* pend; uint32_t cap;
     uint32_t* bits; uint32_t pitch;              // stream: a bit per candidate of the round, `pitch` words per query
+    uint64_t* parts;                             // fold: best lists of the blocks that share a query
     uint32_t* err;
     // 16-bit screens
     const void* qfrag; const float* qmargin;     // rounded queries, and what to lower their thresholds by
@@ -805,6 +806,12 @@ __global__ __launch_bounds__(TK_THREADS, 4) void topk_scores_kernel(TopkArgs a) 
 // the threshold to the K-th best and empties the list.  Rounds come in index order, so a later candidate that only equals the K-th best
 // never enters.  Each wavefront keeps its own 64 best, sorted across its lanes; the lists are merged
 // through LDS at the end.  `out_idx` (last round): the results are written as well.
+// Bits may name any share of a long round: where similarities rise with the index, nearly all of it passes thresholds as
+// old as the round before.  Past FOLD_PICK candidates gridDim.y blocks share the query (fold_parts; with fewer all but
+// the first have only counted), and the last one done merges their lists.  Rising order, K = 30, us, with rounds as short
+// as lists of four bytes a pair allow, with the long ones and one block a query, and shared: 1 query over 200 000 x 100
+// 1760, 2570, 392, over 10^6 3250, 9900, 1140; 100 queries 1820, 1545, 950 and 3520, 6250, 4140; 200 over 200 000
+// 1720, 2240, 1790 (what many queries still lose are the reads of the rows that pass).
 // ---------------------------------------------------------------------------------------------
 // (score, index) as one number that grows with the rank: order-preserving bits of the score, then ~index
 __device__ __forceinline__ uint64_t rank_key(float s, uint32_t c) {
@@ -865,6 +872,9 @@ __device__ __forceinline__ float exact_score(const float* __restrict__ q, const 
 
 constexpr uint32_t FOLD_PICK = 2048;             // candidates named by bits that a block lists before it scores them
 constexpr uint32_t FOLD_CHUNK = 16;              // words: where they are more
+// candidates of a round for every block of a query (a block more costs what it takes to count: 100 queries over 200 003 x
+// 100, not crowded, 116.6 us, in five blocks each 116.9, and two in the round before 117.2)
+static uint32_t fold_share(uint32_t Q) { return Q <= 32 ? 1u << 13 : 1u << 15; }
 enum FoldFrom { FOLD_LIST, FOLD_SCORED, FOLD_BITS };
 template <int WAVES, bool VEC4, FoldFrom FROM>
 __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint32_t K, float tau,
@@ -883,10 +893,11 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
     __shared__ uint32_t s_picked;
     const uint32_t q = a.q_first + blockIdx.x;
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
+    const uint32_t part = FROM == FOLD_BITS ? blockIdx.y : 0u, n_parts = FROM == FOLD_BITS ? gridDim.y : 1u;
     const uint32_t bc = best_cnt[q];
     const float th = theta[q], iq = a.invq[q];
     // (key 0 is below that of every score: an empty place)
-    uint64_t list = wave == 0 && (uint32_t)lane < bc ? best[(uint64_t)q * TK_LIST + lane] : 0ull;
+    uint64_t list = part == 0 && wave == 0 && (uint32_t)lane < bc ? best[(uint64_t)q * TK_LIST + lane] : 0ull;
     uint32_t n_new;
     const uint32_t words = (a.c_end - a.c_begin + 31) / 32;
     const uint32_t* bits = a.bits + (uint64_t)q * a.pitch;
@@ -904,6 +915,7 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
         }
         __syncthreads();
         n_new = s_picked;
+        if (part && n_new <= FOLD_PICK) return;              // uniform per block; all blocks of a query count the same
     } else {
         n_new = min(a.cnt[q], a.cap);
     }
@@ -913,7 +925,7 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
     if (wave && wave >= waves) return;
     auto score = [&](uint32_t c) { return exact_score<VEC4>(a.Qm + (uint64_t)q * a.d, a.Cm + (uint64_t)c * a.d, a.d, iq); };
     // spilled: sixteen words at a time are turned into candidates in order, until there is one for every lane
-    uint32_t words_at = wave * FOLD_CHUNK, queued = 0, taken = 0;
+    uint32_t words_at = (part * WAVES + wave) * FOLD_CHUNK, queued = 0, taken = 0;
     for (uint32_t base = wave * 64u; spilled || base < n_new; base += 64u * WAVES) {
         bool on = base + lane < n_new;
         uint32_t c = 0;
@@ -938,7 +950,7 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
                     for (uint32_t at = queued + incl - n; word; word &= word - 1, ++at)
                         queue[at] = a.c_begin + (words_at + lane) * 32 + __builtin_ctz(word);
                     queued += (uint32_t)__builtin_amdgcn_readlane((int)incl, FOLD_CHUNK - 1);
-                    words_at += FOLD_CHUNK * WAVES;
+                    words_at += FOLD_CHUNK * WAVES * n_parts;
                 }
                 if (queued == taken) break;
                 on = taken + lane < queued;
@@ -966,6 +978,18 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
         if (wave < w && wave + w < waves) list = merge64(list, s_list[wave + w][lane], lane);
     }
     if (wave) return;
+    if (FROM == FOLD_BITS && spilled && n_parts > 1) {       // (a.cnt is zero: the lists it counts are not used here)
+        uint64_t* lists = a.parts + (uint64_t)q * n_parts * TK_LIST;
+        __hip_atomic_store(lists + part * TK_LIST + lane, list, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        __threadfence();
+        uint32_t done = 0;
+        if (lane == 0) done = __hip_atomic_fetch_add(&a.cnt[q], 1u, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        if ((uint32_t)__builtin_amdgcn_readfirstlane((int)done) + 1 < n_parts) return;
+        __threadfence();
+        for (uint32_t p = 0; p < n_parts; ++p)
+            if (p != part)
+                list = merge64(list, __hip_atomic_load(lists + p * TK_LIST + (63 - lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT), lane);
+    }
     const uint32_t have = min(K, (uint32_t)__popcll(__ballot(list != 0)));
     if ((uint32_t)lane >= have) list = 0;
     best[(uint64_t)q * TK_LIST + lane] = list;
@@ -1027,8 +1051,14 @@ constexpr uint32_t WIDE_Q = 32 * TK_WTM * TK_WWM, WIDE_C = 32 * TK_WTN * TK_WWN;
 // queries (a whole number of the screen's tiles: 32, 64 or 128 for the stream screen, 256 for the wide one).
 // `list`: room of a query's list, pairs of four bytes.  The stream screen needs a bit per pair, so its rounds may be
 // longer, as the same memory holds.
-// `ahead`: there is room for the rounded candidates of two rounds.
-struct TopkPlan { TopkScreen screen; uint64_t cap, q_up, list; bool ahead; };
+// `ahead`: there is room for the rounded candidates of two rounds.  `parts`: blocks that may share a query's fold.
+struct TopkPlan { TopkScreen screen; uint64_t cap, q_up, list; bool ahead; uint32_t parts; };
+// As many as fill the chip (a block has sixteen wavefronts up to TK_STREAM_Q queries, four past that), where there
+// are few queries; a sixteenth of the room that the bits have at most.
+static uint32_t fold_parts(uint32_t Q, uint64_t room) {
+    const uint32_t parts = Q > 2 * TK_STREAM_Q ? 1u : std::min(16u, (Q > TK_STREAM_Q ? 2048u : 512u) / Q);
+    return (uint64_t)Q * parts * TK_LIST * 8 <= room / 16 ? parts : 1u;
+}
 static uint32_t stream_tiles(uint32_t Q) { return Q <= 32 ? 1 : (Q <= 64 ? 2 : 4); }    // of 32 queries, per wavefront
 
 static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_bytes) {
@@ -1044,7 +1074,7 @@ static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_b
     // 2030, 1130).  (`cap` of the stream screen, here: what its lists would hold, close to twice what the fp32 screen's
     // do; where the rounded queries take much of that, the fp32 screen is taken: 4096 over 20 000 x 800 with room
     // for 512 candidates 3870, stream with lists 4590.)
-    TopkPlan p{TOPK_FP32, free_bytes / (8ull * Q) / TK_BC * TK_BC, 0, 0, false};
+    TopkPlan p{TOPK_FP32, free_bytes / (8ull * Q) / TK_BC * TK_BC, 0, 0, false, 1};
     const uint64_t cap_fp32 = p.cap;
     // (`per_round`: of the candidates' bytes, those that are better held twice, for this round and the next)
     auto room = [&](uint64_t tile, uint64_t per_candidate, uint64_t per_round, uint64_t granule, uint64_t least, TopkScreen screen) {
@@ -1055,9 +1085,16 @@ static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_b
         const uint64_t twice = (free_bytes - q_bytes) / (per_candidate + per_round) / granule * granule;
         const uint32_t steps = topk_steps(d);
         const bool ahead = per_round && (steps <= TK_BESIDE || steps > (uint32_t)TK_HOLD) && (twice >= n_up || twice >= least);
-        const uint64_t held = ahead ? twice : cap;
-        const uint64_t longest = screen == TOPK_STREAM ? (free_bytes - q_bytes) / Q * 8 / TK_BC * TK_BC : held;
-        p = TopkPlan{screen, longest, q_up, std::min<uint64_t>({held, n_up, TK_CAND_SLICE}), ahead};
+        uint64_t held = ahead ? twice : cap, longest = held;
+        uint32_t parts = 1;
+        if (screen == TOPK_STREAM) {
+            uint64_t bytes = free_bytes - q_bytes;
+            parts = fold_parts(Q, bytes);
+            if (parts > 1) bytes -= (uint64_t)Q * parts * TK_LIST * 8 + 256;
+            held = std::min(held, bytes / per_candidate / granule * granule);
+            longest = bytes / Q * 8 / TK_BC * TK_BC;
+        }
+        p = TopkPlan{screen, longest, q_up, std::min<uint64_t>({held, n_up, TK_CAND_SLICE}), ahead, parts};
         return true;
     };
     const bool wide = Q > 2 * TK_STREAM_Q || (Q > TK_STREAM_Q && N <= (1u << 16) && topk_steps(d) <= TK_HOLD);
@@ -1097,6 +1134,7 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
     a.bits = a.pend;
     a.pitch = (uint32_t)(cap / 32);
     at += (std::max(screen == TOPK_STREAM ? cap * Q / 8 : cap * Q * 4, plan.list * Q * 4) + 255) / 256 * 256;
+    if (plan.parts > 1) { a.parts = (uint64_t*)at; at += (uint64_t)Q * plan.parts * TK_LIST * 8; }
     void* qfrag = nullptr; float* qmargin = nullptr; void* cfrag[2] = {nullptr, nullptr}; float* cmargin[2] = {nullptr, nullptr};
     if (screen != TOPK_FP32) {
         qfrag = at; at += q_up * row_bytes;
@@ -1226,8 +1264,9 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
         const bool last = begin + len >= N;
         uint32_t* oi = last ? out_idx : nullptr;
         const bool bits = screen == TOPK_STREAM && !exact_round;
+        const uint32_t parts = bits ? std::max(1u, std::min(plan.parts, m / fold_share(Q))) : 1u;
 #define W2V_FOLD(WAVES, VEC4, FROM)                                                                        \
-    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4, FROM>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first)), \
+    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4, FROM>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first), parts), \
                        dim3(64 * WAVES), 0, st, a, K, tau, best, best_cnt, theta, oi, out_score, out_count)
         for (a.q_first = 0; a.q_first < Q; a.q_first += TK_FOLD_SLICE) {
             if (exact_round) W2V_FOLD(4, false, FOLD_SCORED);

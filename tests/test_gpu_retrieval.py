@@ -264,6 +264,21 @@ def test_crowded_rounds_stay_counted(Q, N, d):
     assert (N - begin) % 128 == 0 and counted == tiles * (N - begin) // 128
 
 
+# rounds of 1024, 16 384 and the rest: of one block to a query, of two to sixteen; past 32 queries a block for every 32 768
+# candidates, past 128 of four wavefronts
+@pytest.mark.parametrize("Q,N", [(1, 120_000), (7, 34_000), (31, 1 << 18), (128, 120_000), (129, 120_000), (256, 120_001)])
+def test_long_rounds_of_rising_similarities(Q, N):
+    """Nearly all of a round passes the thresholds of the one before: its candidates are shared by several blocks."""
+    say("rising", Q, N)
+    rng = np.random.default_rng(9)
+    Qm = (rng.standard_normal(12) + 0.02 * rng.standard_normal((Q, 12))).astype(np.float32)
+    C = (Qm[0] + np.linspace(3.0, 0.05, N)[:, None] * rng.standard_normal((N, 12))).astype(np.float32)
+    C[-50:-25] = C[-25:]                                       # equal similarities, ranked by index
+    gi, _, gc = screens_agree(Qm, C, 30, -2.0)
+    assert gi.min() > N // 2 and np.all(gc == 30)
+    screens_agree(Qm, C, 64, 0.9)
+
+
 @pytest.mark.parametrize("Q", [40, 140])
 def test_rows_without_a_usable_length(Q):
     """Zero, tiny, huge, infinite and NaN rows on either side."""
