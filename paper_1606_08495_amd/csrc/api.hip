@@ -400,9 +400,8 @@ int ensure_set(w2v_shard* sh, IndexSet& x, uint32_t n, uint32_t M) {
 void sort_and_mark(const SortJob (&jobs)[2], uint32_t bits, uint32_t* sort_tmp, uint32_t* err, bool marks,
                    bool cleared, uint32_t** keys, hipStream_t st) {
     if (group_small(jobs[0].n, jobs[1].n)) {
-        uint32_t* copy = marks ? (uint32_t*)jobs[0].buf1 : nullptr;
-        launch_group_jobs(jobs, 2, bits, copy, st);
-        if (copy) *keys = copy;
+        launch_group_jobs(jobs, 2, bits, marks, st);
+        if (marks) *keys = (uint32_t*)jobs[0].buf1;
         return;
     }
     launch_sort_jobs(jobs, 2, bits, sort_tmp, err, st, cleared);

@@ -128,10 +128,10 @@ void launch_sort_pairs(const uint32_t* keys_in, uint2* buf0, uint2* buf1, uint32
                        hipStream_t st);
 
 // One or two small arrays in one launch and without scratch: equal keys adjacent, slots in increasing order
-// among them, keys in no particular order.  Keys and slots end up in buf0 as above; marked0 (may be null, not
-// in buf0): the keys of the first array in slot order, with KEY_ALONE on those that occur once.
+// among them, keys in no particular order.  Keys and slots end up in buf0 as above; with mark0 the keys of the first
+// array end up in its buf1 too, in slot order, with KEY_ALONE on those that occur once.
 bool group_small(uint32_t n0, uint32_t n1);      // whether arrays of n0 and n1 keys are taken that way
-void launch_group_jobs(const SortJob* jobs, int njobs, uint32_t bits, uint32_t* marked0, hipStream_t st);
+void launch_group_jobs(const SortJob* jobs, int njobs, uint32_t bits, bool mark0, hipStream_t st);
 
 // Exclusive prefix sum of nb sums in place, and their total.
 void launch_scan_sums(uint32_t* sums, uint32_t nb, uint32_t* total, hipStream_t st);

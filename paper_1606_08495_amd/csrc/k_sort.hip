@@ -447,7 +447,10 @@ void launch_sort_pairs(const uint32_t* keys_in, uint2* buf0, uint2* buf1, uint32
 // elements by counting each one's place against all others, more digit by digit in LDS.  The output is in
 // bucket order, then key order: all that the update needs is that equal keys are adjacent.
 // Each wavefront lists its stretch of the keys, at most GS_SUB of them.  Where one finds more (a very frequent
-// word), the key in the middle of that wavefront's list is written out by itself and the rest listed anew.
+// word), the key in the middle of that wavefront's list is written out by itself and the rest listed anew.  After
+// GS_ALONE such keys (many different words of one bucket) the slots of the rest are listed in global memory and sorted
+// there, 1024 at a time: a step of 40 000 pairs whose words all fall into one bucket, on either side, takes 0.58 ms
+// (a pass over all keys for each of them, 770).
 // Bound by latency: a launch, three memory round trips, the fetch of its code -- hence loops that are
 // not unrolled (with the keys held in registers and everything unrolled, 8 kB of straight code, it took 18 us
 // for 28 672 keys, 13.7 this way).
@@ -458,12 +461,15 @@ constexpr uint32_t GS_PAIRWISE = 256;
 constexpr uint32_t GS_SUB = 512;                     // list entries of a wavefront
 constexpr uint32_t GS_LIST = GS_WAVES * GS_SUB;
 constexpr int GS_LIST_ITEMS = GS_LIST / GS_THREADS;
+constexpr int GS_ALONE = 4;                          // keys written out by themselves, at most
 constexpr int GS_QUADS = 2;                          // four keys of a lane each, per step
 constexpr uint32_t GS_STEP = GS_QUADS * 256;         // keys of a wavefront's step
 
 struct GroupJobDev {
-    const uint32_t* keys; uint32_t n; uint32_t* out_keys; uint32_t* out_vals;    // keys: 16-byte aligned, readable up to a multiple of four
-    uint32_t* marked;            // optional: the keys in slot order, KEY_ALONE on those that occur once
+    const uint32_t* keys; uint32_t n;      // 16-byte aligned, readable up to a multiple of four
+    uint32_t* out;               // n keys, then n slots
+    uint32_t* other;             // n marked keys (mark: the keys in slot order, KEY_ALONE on those that occur once), then n words to spare
+    bool mark;
     uint32_t fold;               // log2 of the buckets
     uint32_t passes, width;      // of the bits above `fold`, digits of the same width
 };
@@ -474,16 +480,27 @@ __host__ __device__ inline uint32_t group_bucket(uint32_t k, uint32_t fold) {
     return (k ^ (k >> fold) ^ (k >> (2 * fold))) & (((1u << fold) - 1u) | 0x80000000u);
 }
 
-// The block's wavefronts' values (LDS, 16-byte aligned): their sum, and that of those before this one.
+// row_shr:D of every sixteen lanes, zero shifted in
+template <int D> __device__ __forceinline__ uint32_t shifted16(uint32_t x) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x110 + D, 0xf, 0xf, true);
+}
+
+// The block's wavefronts' values (LDS): their sum, and that of those before this one.  (Scalars, as is `wave`: with a
+// comparison for each wavefront held in scalar registers throughout, the kernel spills.)
+static_assert(GS_WAVES == 16, "a lane for each");
 __device__ __forceinline__ void wave_sums_of(const uint32_t* s_part, int wave, uint32_t& before, uint32_t& all) {
-    before = all = 0;
-#pragma unroll
-    for (int w = 0; w < GS_WAVES; w += 4) {
-        const uint4 q = *reinterpret_cast<const uint4*>(s_part + w);
-        const uint32_t v[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int t = 0; t < 4; ++t) { before += w + t < wave ? v[t] : 0u; all += v[t]; }
-    }
+    uint32_t x = s_part[threadIdx.x % GS_WAVES];
+    x += shifted16<1>(x); x += shifted16<2>(x); x += shifted16<4>(x); x += shifted16<8>(x);
+    all = (uint32_t)__builtin_amdgcn_readlane((int)x, GS_WAVES - 1);
+    before = wave ? (uint32_t)__builtin_amdgcn_readlane((int)x, wave - 1) : 0u;
+}
+// The largest of them, and whose it is.
+__device__ __forceinline__ void wave_most_of(const uint32_t* s_part, uint32_t& most, uint32_t& most_at) {
+    const uint32_t v = s_part[threadIdx.x % GS_WAVES];
+    uint32_t x = v;
+    x = max(x, shifted16<1>(x)); x = max(x, shifted16<2>(x)); x = max(x, shifted16<4>(x)); x = max(x, shifted16<8>(x));
+    most = (uint32_t)__builtin_amdgcn_readlane((int)x, GS_WAVES - 1);
+    most_at = (uint32_t)__builtin_ctzll(__ballot(v == most));
 }
 
 // (64 registers, two blocks to a compute unit)
@@ -499,7 +516,7 @@ __global__ __launch_bounds__(GS_THREADS, 8) void group_small_kernel(GroupArgs a)
     __shared__ __align__(16) uint32_t s_part[GS_WAVES], s_low[GS_WAVES];
     __shared__ uint32_t wave_sums[4], total_all;
     auto& s_sub = lds.sub.slot; auto& cnt = lds.cnt;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const bool second = blockIdx.x >= a.blocks0;
     const GroupJobDev& jb = a.job[second ? 1 : 0];
     const uint32_t bucket = blockIdx.x - (second ? a.blocks0 : 0u), n = jb.n, fold = jb.fold;
@@ -507,7 +524,7 @@ __global__ __launch_bounds__(GS_THREADS, 8) void group_small_kernel(GroupArgs a)
     const uint64_t below = (1ull << lane) - 1ull;
     const uint32_t steps = (n + GS_STEP - 1) / GS_STEP;      // wavefront w takes steps w steps / 16 .. (w + 1) steps / 16
     const uint32_t first = wave * steps / GS_WAVES, last = (wave + 1) * steps / GS_WAVES;
-    bool again = false;                                       // some keys are written out already
+    int alone = 0;                                            // keys written out already
     uint32_t start = 0;
     for (;;) {
         uint32_t lower = 0, mine = 0;
@@ -542,7 +559,7 @@ __global__ __launch_bounds__(GS_THREADS, 8) void group_small_kernel(GroupArgs a)
             for (int u = 0; u < GS_QUADS; ++u) {
                 const uint32_t i = step * GS_STEP + u * 256 + lane * 4;
                 uint32_t own = (bits >> (4 * u)) & 15u;
-                if (again && own) own &= ~(uint32_t)(s_done[i / 64] >> (i % 64));
+                if (alone && own) own &= ~(uint32_t)(s_done[i / 64] >> (i % 64));
                 const uint32_t c = (uint32_t)__popc(own);
                 const uint64_t m0 = __ballot(c & 1u), m1 = __ballot(c & 2u), m2 = __ballot(c & 4u);
                 uint32_t at = mine + (uint32_t)__popcll(m0 & below) + 2 * (uint32_t)__popcll(m1 & below) + 4 * (uint32_t)__popcll(m2 & below);
@@ -553,13 +570,11 @@ __global__ __launch_bounds__(GS_THREADS, 8) void group_small_kernel(GroupArgs a)
         }
         if (lane == 0) { s_part[wave] = mine; s_low[wave] = lower; }
         __syncthreads();
-        uint32_t before, count, lower_all, unused, most = 0, most_at = 0;
+        uint32_t before, count, lower_all, unused, most, most_at;
         wave_sums_of(s_part, wave, before, count);
         wave_sums_of(s_low, wave, unused, lower_all);
-#pragma unroll
-        for (int w = 0; w < GS_WAVES; ++w)
-            if (s_part[w] > most) { most = s_part[w]; most_at = w; }
-        if (!again) start = lower_all;
+        wave_most_of(s_part, most, most_at);
+        if (!alone) start = lower_all;
         if (count == 0) return;                               // (all of these are the same in every thread)
         if (most <= GS_SUB) {
             for (uint32_t i = lane; i < mine; i += 64) {
@@ -588,8 +603,8 @@ __global__ __launch_bounds__(GS_THREADS, 8) void group_small_kernel(GroupArgs a)
                 place += __shfl_xor(place, 2, 64); equal += __shfl_xor(equal, 2, 64);
                 if (threadIdx.x % 4) return;
                 const uint32_t slot = s_val[i];
-                jb.out_keys[start + place] = k; jb.out_vals[start + place] = slot;
-                if (jb.marked) jb.marked[slot] = equal == 1 ? k | KEY_ALONE : k;
+                jb.out[start + place] = k; jb.out[n + start + place] = slot;
+                if (jb.mark) jb.other[slot] = equal == 1 ? k | KEY_ALONE : k;
                 return;
             }
             // Digit by digit (the bucket and the bits above `fold` fix the rest).  Element e of lane l of wave w is
@@ -600,13 +615,13 @@ __global__ __launch_bounds__(GS_THREADS, 8) void group_small_kernel(GroupArgs a)
                 const uint32_t shift = fold + p * jb.width, dmask = (1u << jb.width) - 1u;
                 for (int i = threadIdx.x; i < GS_WAVES * 256; i += GS_THREADS) (&cnt[0][0])[i] = 0;
                 __syncthreads();
-                uint32_t k[GS_LIST_ITEMS], v[GS_LIST_ITEMS], rank[GS_LIST_ITEMS];
+                uint32_t k[GS_LIST_ITEMS], slot_rank[GS_LIST_ITEMS];      // slot, and 2^16 times its rank in the wavefront
 #pragma unroll
                 for (int e = 0; e < GS_LIST_ITEMS; ++e) {
                     if ((uint32_t)e >= items) continue;       // uniform
                     const uint32_t i = (wave * items + e) * 64 + lane;
                     const bool valid = i < count;
-                    k[e] = valid ? s_key[i] : 0u; v[e] = valid ? s_val[i] : 0u;
+                    k[e] = valid ? s_key[i] : 0u;
                     const uint32_t d = (k[e] >> shift) & dmask;
                     uint64_t same = __ballot(valid);
 #pragma unroll 1
@@ -614,9 +629,9 @@ __global__ __launch_bounds__(GS_THREADS, 8) void group_small_kernel(GroupArgs a)
                         const uint64_t bal = __ballot((d >> b) & 1u);
                         same &= ((d >> b) & 1u) ? bal : ~bal;
                     }
-                    rank[e] = 0;
+                    slot_rank[e] = 0;
                     uint32_t seen = 0;
-                    if (valid) { seen = cnt[wave][d]; rank[e] = seen + (uint32_t)__popcll(same & below); }
+                    if (valid) { seen = cnt[wave][d]; slot_rank[e] = s_val[i] | (seen + (uint32_t)__popcll(same & below)) << 16; }
                     // (every lane's read above is issued before the leader's write below: one instruction stream)
                     if (valid && (same & below) == 0) cnt[wave][d] = seen + (uint32_t)__popcll(same);
                 }
@@ -640,24 +655,85 @@ __global__ __launch_bounds__(GS_THREADS, 8) void group_small_kernel(GroupArgs a)
                 for (int e = 0; e < GS_LIST_ITEMS; ++e) {
                     if ((uint32_t)e >= items) continue;
                     if ((wave * items + e) * 64 + lane < count) {
-                        const uint32_t pos = cnt[wave][(k[e] >> shift) & dmask] + rank[e];
-                        s_key[pos] = k[e]; s_val[pos] = (uint16_t)v[e];
+                        const uint32_t pos = cnt[wave][(k[e] >> shift) & dmask] + (slot_rank[e] >> 16);
+                        s_key[pos] = k[e]; s_val[pos] = (uint16_t)slot_rank[e];
                     }
                 }
                 __syncthreads();
             }
             for (uint32_t i = threadIdx.x; i < count; i += GS_THREADS) {
                 const uint32_t k = s_key[i], slot = s_val[i];
-                jb.out_keys[start + i] = k; jb.out_vals[start + i] = slot;
+                jb.out[start + i] = k; jb.out[n + start + i] = slot;
                 const bool lone = (i == 0 || s_key[i - 1] != k) && (i + 1 == count || s_key[i + 1] != k);
-                if (jb.marked) jb.marked[slot] = lone ? k | KEY_ALONE : k;
+                if (jb.mark) jb.other[slot] = lone ? k | KEY_ALONE : k;
+            }
+            return;
+        }
+        const uint32_t lo = first * GS_STEP, hi = min(last * GS_STEP, n);
+        if (alone == GS_ALONE) {
+            // slots in order, into the array from which an even or odd number of passes ends in the output
+            uint32_t *src = jb.passes % 2 ? jb.other + n + start : jb.out + n + start, *dst = jb.passes % 2 ? jb.out + n + start : jb.other + n + start;
+            uint32_t at = before;
+#pragma unroll 1
+            for (uint32_t i0 = lo; i0 < hi; i0 += 64) {
+                const uint32_t i = i0 + lane;
+                const bool own = i < hi && group_bucket(keys[i], fold) == bucket && !((s_done[i / 64] >> (i % 64)) & 1ull);
+                const uint64_t m = __ballot(own);
+                if (own) src[at + (uint32_t)__popcll(m & below)] = i;
+                at += (uint32_t)__popcll(m);
+            }
+            __syncthreads();
+#pragma unroll 1
+            for (uint32_t p = 0; p < jb.passes; ++p) {
+                const uint32_t shift = fold + p * jb.width, dmask = (1u << jb.width) - 1u;
+                if (threadIdx.x < 256) s_key[threadIdx.x] = 0;
+                __syncthreads();
+#pragma unroll 1
+                for (uint32_t i = threadIdx.x; i < count; i += GS_THREADS) atomicAdd(&s_key[(keys[src[i]] >> shift) & dmask], 1u);
+                __syncthreads();
+                const uint32_t digit = threadIdx.x < 256 ? s_key[threadIdx.x] : 0u;
+                uint32_t run = block_exclusive_scan(digit, wave_sums, &total_all);       // where the digit's next one goes
+#pragma unroll 1
+                for (uint32_t i0 = 0; i0 < count; i0 += GS_THREADS) {
+#pragma unroll 1
+                    for (int i = threadIdx.x; i < GS_WAVES * 256; i += GS_THREADS) (&cnt[0][0])[i] = 0;
+                    __syncthreads();
+                    const bool valid = i0 + threadIdx.x < count;
+                    const uint32_t slot = valid ? src[i0 + threadIdx.x] : 0u, d = valid ? (keys[slot] >> shift) & dmask : 0u;
+                    uint64_t same = __ballot(valid);
+#pragma unroll 1
+                    for (uint32_t b = 0; b < jb.width; ++b) {
+                        const uint64_t bal = __ballot((d >> b) & 1u);
+                        same &= ((d >> b) & 1u) ? bal : ~bal;
+                    }
+                    if (valid && (same & below) == 0) cnt[wave][d] = (uint32_t)__popcll(same);
+                    __syncthreads();
+                    if (threadIdx.x < 256) {
+#pragma unroll 1
+                        for (int w = 0; w < GS_WAVES; ++w) {
+                            const uint32_t c = cnt[w][threadIdx.x];
+                            cnt[w][threadIdx.x] = run;
+                            run += c;
+                        }
+                    }
+                    __syncthreads();
+                    if (valid) dst[cnt[wave][d] + (uint32_t)__popcll(same & below)] = slot;
+                    __syncthreads();
+                }
+                uint32_t* const t = src; src = dst; dst = t;
+            }
+#pragma unroll 1
+            for (uint32_t i = threadIdx.x; i < count; i += GS_THREADS) {
+                const uint32_t slot = src[i], k = keys[slot];
+                jb.out[start + i] = k;
+                const bool lone = (i == 0 || keys[src[i - 1]] != k) && (i + 1 == count || keys[src[i + 1]] != k);
+                if (jb.mark) jb.other[slot] = lone ? k | KEY_ALONE : k;
             }
             return;
         }
         // one key by itself: lane r of a wavefront keeps the slots of its r-th 64 keys
         static_assert(GS_MOST / GS_WAVES <= 64 * 64, "a lane for every 64 keys of a wavefront");
         const uint32_t pick = keys[s_sub[most_at][GS_SUB / 2]];
-        const uint32_t lo = first * GS_STEP, hi = min(last * GS_STEP, n);
         uint64_t own = 0;
 #pragma unroll 8
         for (uint32_t i0 = lo; i0 < hi; i0 += 64) {
@@ -677,14 +753,14 @@ __global__ __launch_bounds__(GS_THREADS, 8) void group_small_kernel(GroupArgs a)
         uint32_t all;
         wave_sums_of(s_part, wave, before, all);
         const uint32_t slot0 = lo + (uint32_t)lane * 64;
-        if (slot0 < hi) s_done[slot0 / 64] = again ? s_done[slot0 / 64] | own : own;
+        if (slot0 < hi) s_done[slot0 / 64] = alone ? s_done[slot0 / 64] | own : own;
         for (uint32_t at = start + before + incl - c; own; own &= own - 1, ++at) {
             const uint32_t slot = slot0 + (uint32_t)__builtin_ctzll(own);
-            jb.out_keys[at] = pick; jb.out_vals[at] = slot;
-            if (jb.marked) jb.marked[slot] = all == 1 ? pick | KEY_ALONE : pick;
+            jb.out[at] = pick; jb.out[n + at] = slot;
+            if (jb.mark) jb.other[slot] = all == 1 ? pick | KEY_ALONE : pick;
         }
         start += all;
-        again = true;
+        ++alone;
         __syncthreads();                                      // (s_done is written, s_part read)
     }
 }
@@ -701,7 +777,7 @@ static uint32_t group_fold(uint32_t n) {
     return f;
 }
 
-void launch_group_jobs(const SortJob* jobs, int njobs, uint32_t bits, uint32_t* marked0, hipStream_t st) {
+void launch_group_jobs(const SortJob* jobs, int njobs, uint32_t bits, bool mark0, hipStream_t st) {
     GroupArgs a{};
     uint32_t blocks = 0;
     for (int i = 0; i < njobs && i < 2; ++i) {
@@ -710,7 +786,7 @@ void launch_group_jobs(const SortJob* jobs, int njobs, uint32_t bits, uint32_t* 
         *j.out_vals = (uint32_t*)j.buf0 + j.n;
         const uint32_t fold = group_fold(j.n), above = bits > fold ? bits - fold : 1;
         const uint32_t passes = (above + 7) / 8, width = (above + passes - 1) / passes;
-        a.job[i] = GroupJobDev{j.keys_in, j.n, *j.out_keys, *j.out_vals, i == 0 ? marked0 : nullptr, fold, passes, width};
+        a.job[i] = GroupJobDev{j.keys_in, j.n, (uint32_t*)j.buf0, (uint32_t*)j.buf1, mark0 && i == 0, fold, passes, width};
         blocks += j.n ? 1u << fold : 0u;
         if (i == 0) a.blocks0 = blocks;
     }
