@@ -14,7 +14,8 @@ import oracle
 from paper_1606_08495_amd import w2v, workloads
 from util import all_rows, dev, vec_error
 
-SMALL = 1 << 19              # elements from which the sort takes its large tiles
+SMALL = 1 << 19              # elements from which the sort's scratch is reserved by large tiles
+TILES = [(300_000, 2048), (1 << 20, 4096), (1 << 32, 8192)]      # below how many elements in all: elements of a tile
 
 
 def rule(mangled, n_args, restype=ctypes.c_size_t):
@@ -27,28 +28,45 @@ def sort_scratch(n0, n1=0):
     return rule("_ZN3w2v16sort_scratch_u32Ejj", 2)(n0, n1)
 
 
-def sort_need(n):
-    """uint32 words that a sort of n keys touches: digit totals, tickets, two rows of states per tile."""
-    tiles = -(-n // (1024 if n < SMALL else 8192))
-    return 2 * 4 * 256 + 8 + 2 * 2 * 256 * tiles
+def sort_need(n0, n1=0):
+    """uint32 words that a sort of n0 keys, or of n0 and n1 together, touches: digit totals, tickets, two rows of states
+    per tile."""
+    tile = next(t for below, t in TILES if n0 + n1 < below)
+    return 2 * 4 * 256 + 8 + 2 * 2 * 256 * (-(-n0 // tile) - (-n1 // tile))
 
 
 @pytest.mark.parametrize("n0,n1", [(SMALL - 1, 1), (SMALL - 1, 0), (SMALL - 1, SMALL - 1), (480_000, 80_000), (522_000, 3_000),
-                                   (300_000, 300_000), (6_000, 522_000), (SMALL, 5), (3_000_000, 400_000), (1, 1)])
+                                   (300_000, 300_000), (6_000, 522_000), (SMALL, 5), (3_000_000, 400_000), (1, 1),
+                                   (299_999, 0), (250_000, 49_999), (299_999, 1), (299_999, 299_999), (SMALL - 1, SMALL),
+                                   ((1 << 20) - 1, 0), (1 << 20, 0), ((1 << 20) - 1, 1), (299_999, (1 << 20) - 299_999),
+                                   ((1 << 20) - 1, 1_500_000), (2_499_999, 0), (2_499_999, 1), (2_500_000, 299_999)])
 def test_joint_sort_scratch_holds_each_array_alone(n0, n1):
     have = sort_scratch(n0, n1)
-    assert have >= sort_need(n0) and have >= sort_need(n1)
+    assert have >= max(sort_need(n0, n1), sort_need(n0), sort_need(n1))
     assert sort_scratch(n0) >= sort_need(n0)
 
 
-SORT_EDGES = [(80_000, 5), (87_381, 5), (500_000, 0)]          # n (k + 1) < 2^19 <= n (k + 2)
+def test_sort_scratch_holds_every_smaller_sort():
+    edges = steps_of(300_000, SMALL, 1 << 20, 2_500_000)
+    most = 0
+    for n in [s for s in edges if s < 1 << 24]:
+        most = max(most, sort_need(n))
+        assert sort_scratch(n) >= most
+        for n1 in (1, 2047, 299_999, 700_000):
+            assert sort_scratch(n, n1) >= max(most, sort_need(n, n1))
+
+
+# n (k + 1) < 2^19 <= n (k + 2), both sides sorted by the same launches; n (k + 2) > 1 500 000, each by its own from given
+# coefficients (over two shards as one matrix of joint rows: the same launches): n (k + 1) and n in the three shapes
+SORT_EDGES = [(80_000, 5), (87_381, 5), (500_000, 0), (750_001, 0), (500_001, 1), (524_288, 1), (299_999, 5), (300_000, 5),
+              (416_666, 5), (416_667, 5)]
 
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("n,k", SORT_EDGES)
 @pytest.mark.parametrize("form", ["adjust", "two shards"])
-def test_both_sides_sorted_apart_at_the_edge_of_the_small_tiles(n, k, form):
-    print("sorts apart", n, k, form, flush=True)
+def test_both_sides_sorted_at_the_edges_of_the_tiles(n, k, form):
+    print("sorts", n, k, form, flush=True)
     V, d, alpha = 3000, 8, 0.001
     rng = np.random.default_rng(n + k)
     counts = workloads.analytic_counts(V, 1.0, 10 ** 7)
