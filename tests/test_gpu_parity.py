@@ -307,11 +307,12 @@ def test_large_minibatch_whose_walk_has_its_own_launch(V, d, n, k):
 
 @pytest.mark.parametrize("form", ["adjust", "two shards"])
 def test_large_minibatch_from_given_coefficients(form):
-    """The same walk from the two-call form and over shards that use one shard's buffers, streams and events
-    one after the other; the output side's order comes from the second stream.  Two steps."""
+    """The same walk from the two-call form and over shards (too wide for joint rows) that use one shard's buffers,
+    streams and events one after the other; the output side's order comes from the second stream, past 1 500 000
+    keys of both sides.  Two steps."""
     print("large minibatch,", form, flush=True)
-    V, n, k, alpha = 3000, 180_000, 5, 0.001
-    cuts = [(0, 140)] if form == "adjust" else [(0, 132), (132, 148)]
+    V, n, k, alpha = 3000, 214_300, 5, 0.001
+    cuts = [(0, 140)] if form == "adjust" else [(0, 520), (520, 524)]
     d = sum(w for _, w in cuts)
     rng = np.random.default_rng(d)
     cdf = workloads.zipf_cdf(V, 1.1)
