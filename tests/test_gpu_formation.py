@@ -10,8 +10,10 @@ from util import dev
 pytestmark = pytest.mark.gpu
 
 
-# more than 2^16 survivors (several sums of 256 blocks), on and beside that edge; blocks of more than 6144 pairs
-@pytest.mark.parametrize("n_tok,B,sentence", [(65_536, 2, 30), (65_537, 2, 7), (200_001, 1, 25), (9000, 40, 500), (5000, 13, 5000)])
+# whole and cut blocks of centers; blocks of more than 6144 pairs; the longest text whose blocks add up the counts before
+# them, and one of which these are scanned
+@pytest.mark.parametrize("n_tok,B,sentence", [(65_536, 2, 30), (65_537, 2, 7), (200_001, 1, 25), (9000, 40, 500), (5000, 13, 5000),
+                                              (1 << 22, 1, 19), ((1 << 22) + 1, 1, 19)])
 def test_long_texts_and_wide_windows(n_tok, B, sentence):
     print("formation", n_tok, B, sentence, flush=True)
     rng = np.random.default_rng(n_tok + B)
