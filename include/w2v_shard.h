@@ -142,8 +142,11 @@ int w2v_adjust(w2v_shard* shard, const uint32_t* in_idx_dev, const uint32_t* out
 
 /* ---- one client step in this process (Appendix, "Grid based word2vec", body of the minibatch loop)
  * dotprod on each of the S shards (shards_host[S], all on one device, same V and noise table),
- * aggregation, adjust on each shard.  With S = 1, and over different shards of up to W2V_D_MAX
- * columns in all, the three phases are fused where that changes no result beyond fp32 rounding.  loss_dev as in w2v_coeffs. */
+ * aggregation, adjust on each shard.  With S = 1, and over different shards whose rows come to W2V_D_MAX
+ * floats at most, the three phases are fused where that changes no result beyond fp32 rounding.  (A row counts as long as it
+ * lies in memory: its columns rounded up to four, or to 32 where that adds at most an eighth -- sixteen shards of 60 columns
+ * are fused, seventeen are not.  Fused, several shards take more scratch than one after the other, which is what is done
+ * where that cannot be allocated, or would have to be while the stream is being captured.)  loss_dev as in w2v_coeffs. */
 int w2v_train_minibatch(w2v_shard* const* shards_host, uint32_t S, const uint32_t* in_idx_dev,
                         const uint32_t* out_idx_dev, uint32_t n, uint32_t k, uint64_t seed,
                         float alpha, double* loss_dev, void* stream);

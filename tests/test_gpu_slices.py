@@ -1,15 +1,19 @@
 """Several column shards trained in one process as one matrix of joint rows, against the same step through
-dotprod, coefficients and adjust of each shard."""
+dotprod, coefficients and adjust of each shard, and against the oracle."""
 import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_1606_08495_amd import w2v
 from util import all_rows, dev, vec_error, zipf_counts
 
 pytestmark = pytest.mark.gpu
 
-TOL = 1e-5                  # fp32 sums in another order: up to 3e-7 of a row's length
+# fp32 sums in another order.  A dot of up to 1025 terms of unit rows is off by some sqrt(1025) 2^-24 = 2e-6, a coefficient
+# by a quarter of that, and a row moves by less than its size: 5e-7; as much again for the order of a row's contributions.
+TOL = 2e-6
+ORACLE_TOL = 1e-5           # a minibatch against sums in double
 
 
 def make_shard(V, d, seed, counts, d_total=None, col_begin=0):
@@ -34,8 +38,8 @@ def steps(shards, ins, outs, k, form):
 
 
 # widths: padded and unpadded strides, a slice in two lane groups' float4, one to four float4 a lane, the widest
-# joint row and one past it, more slices than lanes of a float4
-CASES = [([60] * 5, 3001, 5), ([1, 2], 17, 5), ([7, 143, 150], 1500, 5), ([30, 30], 999, 5), ([102, 103, 102, 103, 102], 700, 3),
+# joint row and one past it (of 1024 floats with the rows' padding: 16 x 64, and 17), more slices than lanes of a float4
+CASES = [([60] * 16, 400, 5), ([60] * 17, 400, 5), ([60] * 5, 3001, 5), ([1, 2], 17, 5), ([7, 143, 150], 1500, 5), ([30, 30], 999, 5), ([102, 103, 102, 103, 102], 700, 3),
          ([300, 400], 500, 12), ([512, 512], 300, 1), ([512, 513], 300, 1), ([4] * 32, 800, 5), ([33] * 7, 2500, 0),
          ([60, 100, 140], 180_000, 5)]
 
@@ -57,8 +61,15 @@ def test_joint_step_matches_each_shard_on_its_own(widths, n, k):
             x = torch.randn(V, d, device="cuda", generator=g) * d ** -0.5
             i = (sets[0] + sets[1]).index(s) % len(widths)
             s.set_rows(which, rows, x[:, begins[i]:begins[i] + widths[i]].contiguous())
+    whole = [np.concatenate([all_rows(s, which) for s in sets[0]], axis=1) for which in (0, 1)]
     la, lb = steps(sets[0], ins, outs, k, "joint"), steps(sets[1], ins, outs, k, "apart")
     assert np.allclose(la, lb, rtol=1e-6)
+    th, al = oracle.build_alias(counts)
+    for h, (a, b) in enumerate(zip(ins, outs)):
+        ref = oracle.train_minibatch([whole[0]], [whole[1]], w2v.index_to_numpy(a), w2v.index_to_numpy(b), k, 70 + h, th, al, min(0.03, 3.0 / n))
+        assert abs(la[h] - ref) <= 1e-5 * ref
+    for which in (0, 1):
+        assert vec_error(np.concatenate([all_rows(s, which) for s in sets[0]], axis=1), whole[which]) <= 2 * ORACLE_TOL
     for a, b in zip(*sets):
         for which in (0, 1):
             assert vec_error(all_rows(a, which), all_rows(b, which)) <= TOL
