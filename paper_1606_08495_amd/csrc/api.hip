@@ -1214,8 +1214,9 @@ extern "C" int w2v_prefetch_cancel(w2v_shard* sh) {
 // a training step of fixed size on one stream (small minibatches are bound by launches, not bytes)
 // ---------------------------------------------------------------------------------------------
 // A run queues the step's six or seven launches itself.  (Replayed from a HIP graph they were, while a step had some
-// thirty: what the graph saves the host, its replay costs the device between one step and the next.  Eight
-// steps, d = 100, k = 5, replayed and queued, us: 500 pairs 428, 362; 4096 511, 445; 15 000 699, 625.)
+// thirty: the device idles some eight microseconds between one replay and the next, and the host is no faster (4096 pairs,
+// 63 us a step replayed, 47 queued).  Eight steps, d = 100, k = 5, replayed and queued, us: 500 pairs 428, 362; 4096 511,
+// 445; 15 000 699, 625.)
 struct w2v_step_graph {
     w2v_shard* sh = nullptr;
     uint32_t n = 0, k = 0;
