@@ -127,8 +127,8 @@ struct Prepared {
 // with their example numbers and weights, the destination keys, and both sorts.
 struct CbowSet {
     char* base = nullptr; size_t cap = 0;
-    uint32_t *keys = nullptr, *ctx_safe = nullptr, *ex_of = nullptr, *iota = nullptr;
-    float* weight = nullptr;
+    uint32_t *keys = nullptr, *ctx_safe = nullptr, *iota = nullptr;
+    SlotRecord* entry = nullptr;                // example number and weight of each context entry
     uint2 *wb0 = nullptr, *wb1 = nullptr;       // sort buffers of the M destinations
     uint2 *cb0 = nullptr, *cb1 = nullptr;       // sort buffers of the m context entries
     uint32_t *sort_tmp = nullptr;               // of the joint sort of both
@@ -296,6 +296,7 @@ struct Plan {
     uint2 *wb0, *wb1;                      // sort buffers, output side (M)
     uint32_t* sort_tmp; uint32_t* sort_tmp_u;
     float* coeffs; float* dots; double* loss_tmp;
+    SlotRecord* rec;                       // input row and coefficient of every slot, for the output side
     float* delta; uint32_t* dkey;
     float* pa_rows; uint32_t* pa_keys;     // input side, level 1 slots
     float* pb_rows; uint32_t* pb_keys;     // output side, level 1 slots
@@ -324,6 +325,7 @@ Plan make_plan(char* base, uint32_t n, uint32_t k, uint32_t stride4_max, uint32_
         p.sort_tmp = c.take<uint32_t>(sort_scratch_u32(p.M, n));     // (room for the joint sort)
         p.sort_tmp_u = c.take<uint32_t>(sort_scratch_u32(n));
         const size_t row = (size_t)stride4_max * 4;
+        p.rec = c.take<SlotRecord>(p.M);
         p.delta = c.take<float>((size_t)n * row);
         p.dkey = c.take<uint32_t>(n);
         p.slots_w1 = slots_after(p.M, wseg_entries_per_chunk(p.M));
@@ -552,7 +554,7 @@ struct Target { float* U; float* W; const Slices* slices; RowGeom g; };
 // `join_sorts`: the output-side order comes from the shard's second stream.
 void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t* sku,
                   const uint32_t* perm, const uint32_t* skw, const uint32_t* sidx,
-                  const float* coeffs_in, float* coeffs_out, bool fused, float alpha,
+                  const float* coeffs_in, bool fused, float alpha,
                   double* loss_out, bool join_sorts, hipStream_t st) {
     w2v_shard* spans = p.one_stream ? nullptr : ws_owner;
     const bool alone = adjust_walk_alone(p.M, to.g);
@@ -572,7 +574,7 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
         Phase ph(spans, W2V_PH_USIDE, st);
         USideArgs a{};
         a.U = to.U; a.W = to.W; a.slices = to.slices; a.g = to.g; a.skey = sku; a.perm = perm; a.keys = p.keys;
-        a.n = p.n; a.T = p.T; a.coeffs_in = coeffs_in; a.coeffs_out = coeffs_out;
+        a.n = p.n; a.T = p.T; a.coeffs_in = coeffs_in; a.rec_out = p.rec;
         a.dots_out = (fused && loss_out) ? p.dots : nullptr; a.delta = p.delta; a.dkey = p.dkey;
         a.prows = p.pa_rows; a.pkeys = p.pa_keys; a.fused = fused;
         a.own_rows = p.own_rows; a.alpha = alpha;
@@ -608,8 +610,8 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
     };
     const ApplyDelta apply{to.U, to.slices, p.delta, p.dkey, p.n, alpha};
     WSideArgs w{};
-    w.U = to.U; w.W = to.W; w.slices = to.slices; w.g = to.g; w.skey = skw; w.sidx = sidx; w.M = p.M; w.T = p.T;
-    w.in_idx = p.in_safe; w.coeffs = fused ? coeffs_out : coeffs_in; w.alpha = alpha;
+    w.U = to.U; w.W = to.W; w.slices = to.slices; w.g = to.g; w.skey = skw; w.sidx = sidx; w.M = p.M;
+    w.rec = p.rec; w.alpha = alpha;
     w.prows = p.pb_rows; w.pkeys = p.pb_keys; w.skip_alone = p.own_rows;
     const bool two = alone && ws_owner->overlap && !p.one_stream && ensure_side_stream(ws_owner) == W2V_OK;
     if (alone) {
@@ -1059,7 +1061,7 @@ extern "C" int w2v_adjust(w2v_shard* sh, const uint32_t* in_idx, const uint32_t*
         rc = queue_keys_and_sorts(sh, p, in_idx, out_idx, k, seed, &sku, &perm, &skw, &sidx, &join, st);
         if (rc) return rc;
     }
-    queue_adjust(sh, Target{sh->U, sh->W, nullptr, sh->g}, p, sku, perm, skw, sidx, coeffs, nullptr, false, alpha, nullptr, join, st);
+    queue_adjust(sh, Target{sh->U, sh->W, nullptr, sh->g}, p, sku, perm, skw, sidx, coeffs, false, alpha, nullptr, join, st);
     HIP_TRY(hipGetLastError());
     return W2V_OK;
 }
@@ -1118,7 +1120,7 @@ extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const u
     auto plan = [&](char* base, bool fused) {
         return make_plan(base, n, k, fused ? to.g.stride4 : stride_max,
                          fused ? (loss ? 1u : 0u) : S,               // fused: the dots are kept for the loss only
-                         true, true, fused && s0->own_rows ? s0->V : 0u);
+                         true, !fused, fused && s0->own_rows ? s0->V : 0u);
     };
     bool fused = S == 1 || take_as_one(shards, S, &sl, &to.g);
     if (S > 1 && fused) {
@@ -1158,7 +1160,7 @@ extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const u
         if (rc) return rc;
     }
     if (fused) {
-        queue_adjust(s0, to, p, sku, perm, skw, sidx, nullptr, p.coeffs, true, alpha, loss, join, st);
+        queue_adjust(s0, to, p, sku, perm, skw, sidx, nullptr, true, alpha, loss, join, st);
     } else {
         PartialPtrs pp{};
         {
@@ -1174,7 +1176,7 @@ extern "C" int w2v_train_minibatch(w2v_shard* const* shards, uint32_t S, const u
             launch_coeffs(pp, S, n, p.T, p.coeffs, p.loss_tmp, loss, st);
         }
         for (uint32_t s = 0; s < S; ++s)
-            queue_adjust(s0, Target{shards[s]->U, shards[s]->W, nullptr, shards[s]->g}, p, sku, perm, skw, sidx, p.coeffs, nullptr, false, alpha, nullptr, join, st);
+            queue_adjust(s0, Target{shards[s]->U, shards[s]->W, nullptr, shards[s]->g}, p, sku, perm, skw, sidx, p.coeffs, false, alpha, nullptr, join, st);
     }
     HIP_TRY(hipGetLastError());
     return W2V_OK;
@@ -1223,7 +1225,7 @@ struct w2v_step_graph {
     double* loss = nullptr;
     uint64_t epoch = 0;                 // of the shard's scratch, when this was made
     Plan plan(char* base) const {
-        Plan p = make_plan(base, n, k, sh->g.stride4, loss ? 1u : 0u, true, true, sh->own_rows ? sh->V : 0u);
+        Plan p = make_plan(base, n, k, sh->g.stride4, loss ? 1u : 0u, true, false, sh->own_rows ? sh->V : 0u);
         p.one_stream = true;
         return p;
     }
@@ -1262,7 +1264,7 @@ extern "C" int w2v_step_graph_run(w2v_step_graph* g, const uint32_t* in_idx, con
     bool join = false;
     rc = queue_keys_and_sorts(sh, p, in_idx, out_idx, g->k, seed, &sku, &perm, &skw, &sidx, &join, st);
     if (rc) return rc;
-    queue_adjust(sh, Target{sh->U, sh->W, nullptr, sh->g}, p, sku, perm, skw, sidx, nullptr, p.coeffs, true, alpha,
+    queue_adjust(sh, Target{sh->U, sh->W, nullptr, sh->g}, p, sku, perm, skw, sidx, nullptr, true, alpha,
                  g->loss, join, st);
     sh->updates++;
     sh->last_update_fused = true;
@@ -1287,10 +1289,11 @@ struct CbowPlan {
     uint32_t n, T, M, m;
     bool own_rows;                                   // fused step: rows named once go to the per-example pass
     uint32_t* keys;                                  // [M] center word + negatives per example
-    uint32_t* ctx_safe; uint32_t* ex_of; float* weight;   // [m]
+    uint32_t* ctx_safe; SlotRecord* entry;           // [m]
     uint32_t* iota;                                  // [n] 0, 1, 2, ...
     float* H; float* E; uint32_t* dkey;              // [n] rows: hidden vectors, summed output rows
     float* coeffs; float* dots; double* loss_tmp;
+    SlotRecord* rec;                                 // [M] hidden vector and coefficient of every slot
     uint2 *wb0, *wb1; uint32_t* sort_tmp_w;          // sort of the M destinations
     uint2 *cb0, *cb1; uint32_t* sort_tmp_c;          // sort of the m context entries
     float* pa_rows; uint32_t* pa_keys;               // unused slots of the per-example pass
@@ -1309,13 +1312,14 @@ CbowPlan make_cbow_plan(char* base, uint32_t n, uint32_t k, uint32_t m, uint32_t
     Carver c(base);
     const size_t row = (size_t)stride4_max * 4;
     p.keys = c.take<uint32_t>(p.M);
-    p.ctx_safe = c.take<uint32_t>(m); p.ex_of = c.take<uint32_t>(m); p.weight = c.take<float>(m);
+    p.ctx_safe = c.take<uint32_t>(m); p.entry = c.take<SlotRecord>(m);
     p.iota = c.take<uint32_t>(n);
     p.H = c.take<float>((size_t)n * row);
     if (want_coeffs) p.coeffs = c.take<float>(p.M);
     if (S_dots) p.dots = c.take<float>((size_t)S_dots * p.M);
     p.loss_tmp = c.take<double>(coeffs_loss_scratch_doubles(n, p.T));
     if (want_adjust) {
+        p.rec = c.take<SlotRecord>(p.M);
         p.E = c.take<float>((size_t)n * row);
         p.dkey = c.take<uint32_t>(n);
         p.wb0 = c.take<uint2>(p.M); p.wb1 = c.take<uint2>(p.M);
@@ -1361,8 +1365,7 @@ int queue_cbow_indices(w2v_shard* sh, CbowPlan& p, const uint32_t* ctx_off, cons
                        bool* join, hipStream_t st) {
     {
         Phase ph(sh, W2V_PH_NEG, st);
-        launch_cbow_entries(ctx_off, ctx_idx, p.n, p.m, sh->V, p.ctx_safe, p.ex_of, p.weight,
-                            sh->err, st);
+        launch_cbow_entries(ctx_off, ctx_idx, p.n, p.m, sh->V, p.ctx_safe, p.entry, sh->err, st);
         launch_iota(p.iota, p.n, st);
     }
     hipStream_t wst = st;
@@ -1421,7 +1424,7 @@ void queue_cbow_hidden(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
 // there, behind its sort, the output side on the caller's stream.
 void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint32_t* skw,
                        const uint32_t* sidx, const uint32_t* skc, const uint32_t* cidx,
-                       const float* coeffs_in, float* coeffs_out, float* dots_out, bool fused,
+                       const float* coeffs_in, float* dots_out, bool fused,
                        float alpha, double* loss_out, bool join_sorts, hipStream_t st) {
     // (loss_out: fused form only; the dots it is formed from go to dots_out)
     // border slots of both write-back kernels, cleared ahead of the per-example pass (the second
@@ -1431,7 +1434,7 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
         Phase ph(owner, W2V_PH_USIDE, st);
         USideArgs a{};
         a.U = p.H; a.W = sh->W; a.g = sh->g; a.skey = p.iota; a.perm = p.iota; a.keys = p.keys;
-        a.n = p.n; a.T = p.T; a.coeffs_in = coeffs_in; a.coeffs_out = coeffs_out;
+        a.n = p.n; a.T = p.T; a.coeffs_in = coeffs_in; a.rec_out = p.rec;
         a.dots_out = fused ? dots_out : nullptr; a.delta = p.E; a.dkey = p.dkey;
         a.prows = p.pa_rows; a.pkeys = p.pa_keys; a.fused = fused;
         a.own_rows = fused && p.own_rows; a.alpha = alpha;                  // (source: the hidden vector)
@@ -1448,8 +1451,8 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
     {
         Phase ph(owner, W2V_PH_APPLY, side);
         WSideArgs u{};
-        u.U = p.E; u.W = sh->U; u.g = sh->g; u.skey = skc; u.sidx = cidx; u.M = p.m; u.T = 1;
-        u.in_idx = p.ex_of; u.coeffs = p.weight; u.alpha = alpha;
+        u.U = p.E; u.W = sh->U; u.g = sh->g; u.skey = skc; u.sidx = cidx; u.M = p.m;
+        u.rec = p.entry; u.alpha = alpha;
         u.prows = p.pd_rows; u.pkeys = p.pd_keys;
         launch_wseg(u, side);
         run_tails(sh, sh->U, alpha, p.pd_rows, p.pd_keys, p.slots_c1, p.pe_rows, p.pe_keys, side);
@@ -1458,8 +1461,8 @@ void queue_cbow_adjust(w2v_shard* owner, w2v_shard* sh, CbowPlan& p, const uint3
     {
         Phase ph(owner, W2V_PH_WSIDE, st);
         WSideArgs w{};
-        w.U = p.H; w.W = sh->W; w.g = sh->g; w.skey = skw; w.sidx = sidx; w.M = p.M; w.T = p.T;
-        w.in_idx = p.iota; w.coeffs = fused ? coeffs_out : coeffs_in; w.alpha = alpha;
+        w.U = p.H; w.W = sh->W; w.g = sh->g; w.skey = skw; w.sidx = sidx; w.M = p.M;
+        w.rec = p.rec; w.alpha = alpha;
         w.prows = p.pb_rows; w.pkeys = p.pb_keys;
         w.skip_alone = fused && p.own_rows;
         launch_wseg(w, st);
@@ -1478,8 +1481,7 @@ int ensure_cset(w2v_shard* sh, CbowSet& x, uint32_t n, uint32_t M, uint32_t m) {
     for (int pass = 0; pass < 2; ++pass) {
         Carver c(pass ? x.base : nullptr);
         uint32_t* keys = c.take<uint32_t>(M);
-        uint32_t* ctx_safe = c.take<uint32_t>(m); uint32_t* ex_of = c.take<uint32_t>(m);
-        float* weight = c.take<float>(m);
+        uint32_t* ctx_safe = c.take<uint32_t>(m); SlotRecord* entry = c.take<SlotRecord>(m);
         uint32_t* iota = c.take<uint32_t>(n);
         uint2* wb0 = c.take<uint2>(M); uint2* wb1 = c.take<uint2>(M);
         uint2* cb0 = c.take<uint2>(m); uint2* cb1 = c.take<uint2>(m);
@@ -1489,7 +1491,7 @@ int ensure_cset(w2v_shard* sh, CbowSet& x, uint32_t n, uint32_t M, uint32_t m) {
             int rc = ensure_region(x.base, x.cap, need);
             if (rc) return rc;
         } else {
-            x.keys = keys; x.ctx_safe = ctx_safe; x.ex_of = ex_of; x.weight = weight; x.iota = iota;
+            x.keys = keys; x.ctx_safe = ctx_safe; x.entry = entry; x.iota = iota;
             x.wb0 = wb0; x.wb1 = wb1; x.cb0 = cb0; x.cb1 = cb1; x.sort_tmp = tw;
         }
     }
@@ -1513,8 +1515,7 @@ int run_cbow_prefetch_chain(w2v_shard* sh, const CbowPrepared& want, hipStream_t
     const uint32_t bits = key_bits(sh->V);
     {
         Phase ph(sh, W2V_PH_NEG, ah);
-        launch_cbow_entries(want.ctx_off, want.ctx_idx, n, m, sh->V, x.ctx_safe, x.ex_of, x.weight,
-                            sh->err, ah);
+        launch_cbow_entries(want.ctx_off, want.ctx_idx, n, m, sh->V, x.ctx_safe, x.entry, sh->err, ah);
         launch_iota(x.iota, n, ah);
         launch_dest_keys(NoiseTable{sh->bins, sh->V}, want.out_idx, n, k, want.seed, x.keys, sh->err, ah);
     }
@@ -1552,7 +1553,7 @@ int use_cbow_prepared(w2v_shard* sh, int which, CbowPlan& p, bool spend, bool fu
     CbowSet& x = sh->csets[which];
     if (spend) sh->cprep[which].valid = false;            // a set serves one update
     HIP_TRY(hipStreamWaitEvent(st, x.ready, 0));
-    p.keys = x.keys; p.ctx_safe = x.ctx_safe; p.ex_of = x.ex_of; p.weight = x.weight; p.iota = x.iota;
+    p.keys = x.keys; p.ctx_safe = x.ctx_safe; p.entry = x.entry; p.iota = x.iota;
     p.own_rows = fused && sh->cprep[which].own_rows;
     if (skw) { *skw = x.skw; *sidx = x.sidx; *skc = x.skc; *cidx = x.cidx; }
     return W2V_OK;
@@ -1628,7 +1629,7 @@ extern "C" int w2v_cbow_adjust(w2v_shard* sh, const uint32_t* ctx_off, const uin
     if (rc) return rc;
     queue_cbow_hidden(sh, sh, p, ctx_off, st);
     if (join) cbow_wait_keys(sh, st);
-    queue_cbow_adjust(sh, sh, p, skw, sidx, skc, cidx, coeffs, nullptr, nullptr, false, alpha, nullptr, join, st);
+    queue_cbow_adjust(sh, sh, p, skw, sidx, skc, cidx, coeffs, nullptr, false, alpha, nullptr, join, st);
     HIP_TRY(hipGetLastError());
     return W2V_OK;
 }
@@ -1661,10 +1662,10 @@ extern "C" int w2v_cbow_train_minibatch(w2v_shard* const* shards, uint32_t S,
     }
     const bool fused = (S == 1);
     const uint32_t S_dots = fused ? (loss ? 1u : 0u) : S;    // fused: the dots are kept for the loss only
-    CbowPlan sz = make_cbow_plan(nullptr, n, k, m, stride_max, S_dots, true, true);
+    CbowPlan sz = make_cbow_plan(nullptr, n, k, m, stride_max, S_dots, true, !fused);
     rc = ensure_ws(s0, sz.bytes);
     if (rc) return rc;
-    CbowPlan p = make_cbow_plan(s0->ws, n, k, m, stride_max, S_dots, true, true);
+    CbowPlan p = make_cbow_plan(s0->ws, n, k, m, stride_max, S_dots, true, !fused);
     p.own_rows = fused && s0->own_rows;
     uint32_t *skw, *sidx, *skc, *cidx;
     bool join = false;                  // keys and sorts come from the second stream
@@ -1674,7 +1675,7 @@ extern "C" int w2v_cbow_train_minibatch(w2v_shard* const* shards, uint32_t S,
     if (fused) {
         queue_cbow_hidden(s0, s0, p, ctx_off, st);
         if (join) cbow_wait_keys(s0, st);
-        queue_cbow_adjust(s0, s0, p, skw, sidx, skc, cidx, nullptr, p.coeffs, loss ? p.dots : nullptr, true,
+        queue_cbow_adjust(s0, s0, p, skw, sidx, skc, cidx, nullptr, loss ? p.dots : nullptr, true,
                           alpha, loss, join, st);
     } else {
         // As in the two-call protocol, every shard forms its hidden vectors once for the dots and
@@ -1694,7 +1695,7 @@ extern "C" int w2v_cbow_train_minibatch(w2v_shard* const* shards, uint32_t S,
         }
         for (uint32_t s = 0; s < S; ++s) {
             queue_cbow_hidden(s0, shards[s], p, ctx_off, st);
-            queue_cbow_adjust(s0, shards[s], p, skw, sidx, skc, cidx, p.coeffs, nullptr, nullptr, false,
+            queue_cbow_adjust(s0, shards[s], p, skw, sidx, skc, cidx, p.coeffs, nullptr, false,
                               alpha, nullptr, join, st);
         }
     }

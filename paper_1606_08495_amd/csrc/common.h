@@ -158,14 +158,16 @@ uint32_t wseg_slots_most(uint32_t M);                    // output side
 // A lane group sums coeffs[p][j] * W[keys[p][j]] over the pairs of its chunk; a run of equal keys
 // that lies inside the chunk is written to delta[first ps of run] with dkey[ps] = key (KEY_NONE
 // elsewhere); runs cut by a chunk border go to the partial slots (pkeys/prows), two per border.
-// With `fused` the group also loads u = U[key], forms the dots, writes coefficients
-// and uses those coefficients.
+// With `fused` the group also loads u = U[key], forms the dots and uses the coefficients they give.
+// What the output side needs of a slot, in one access: the input row of its pair and its coefficient.  (As two
+// arrays each contribution of the output side's order was a random line of both.)
+struct __align__(8) SlotRecord { uint32_t row; float coef; };
 struct USideArgs {
     const float* U; const float* W; RowGeom g;
     const Slices* slices;        // fused only, optional: the matrices of several shards, instead of U, W and W_update
     const uint32_t* skey; const uint32_t* perm; const uint32_t* keys; uint32_t n; uint32_t T;
     const float* coeffs_in;      // unfused: coefficients to use
-    float* coeffs_out;           // fused: coefficients written here [n][T]
+    SlotRecord* rec_out;         // written for the output side [n][T]: the pair's input row, the coefficient
     float* dots_out;             // fused, optional: the dots themselves
     float* delta; uint32_t* dkey;
     float* prows; uint32_t* pkeys;
@@ -183,14 +185,14 @@ void launch_loss_from_dots(const float* dots, uint32_t n, uint32_t T, double* tm
                            hipStream_t st);
 
 // Output-vector side, level 1.  Sorted contributions i = 0..M-1 with destination skey[i] and
-// original slot sidx[i] = p*T + j: adds alpha * sum coeffs[sidx] * U[in_idx[p]] to W[skey] for runs
+// original slot sidx[i]: adds alpha * sum rec[sidx].coef * U[rec[sidx].row] to W[skey] for runs
 // inside a chunk; cut runs go to the partial slots.
 struct WSideArgs {
     const float* U; float* W; RowGeom g;
     const Slices* slices;        // optional, instead of U and W
-    const uint32_t* skey; const uint32_t* sidx; uint32_t M; uint32_t T;
+    const uint32_t* skey; const uint32_t* sidx; uint32_t M;
     bool skip_alone;             // entries whose neighbours carry other keys are handled elsewhere
-    const uint32_t* in_idx; const float* coeffs; float alpha;
+    const SlotRecord* rec; float alpha;      // rows are range-checked words (or example numbers)
     float* prows; uint32_t* pkeys;
 };
 // (the cells' border slots must read KEY_NONE when the kernel starts: launch_wseg_fill writes that)
@@ -263,10 +265,9 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
                              uint32_t* out_count, void* workspace, size_t workspace_bytes, hipStream_t st);
 
 // ---- continuous bag of words ----------------------------------------------------------------------
-// Per context entry: checked word, example number, weight 1/|C|; offsets are validated (error flag).
+// Per context entry: checked word; example number and weight 1/|C|; offsets are validated (error flag).
 void launch_cbow_entries(const uint32_t* ctx_off, const uint32_t* ctx_idx, uint32_t n, uint32_t m,
-                         uint32_t V, uint32_t* ctx_safe, uint32_t* ex_of, float* weight,
-                         uint32_t* err, hipStream_t st);
+                         uint32_t V, uint32_t* ctx_safe, SlotRecord* entry, uint32_t* err, hipStream_t st);
 void launch_iota(uint32_t* x, uint32_t n, hipStream_t st);
 // H[p] = mean of U[ctx_safe[e]] over the entries of example p (row geometry g).
 void launch_cbow_hidden(const float* U, RowGeom g, const uint32_t* ctx_off, const uint32_t* ctx_safe,

@@ -83,9 +83,8 @@ struct SegArgs {
     RowGeom g;
     const uint32_t* skey;       // destination key per entry
     const uint32_t* sidx;       // level 1 only
-    const uint32_t* in_idx;     // level 1 only
-    const float* coeffs;        // level 1 only
-    uint32_t entries, T;
+    const SlotRecord* rec;      // level 1 only
+    uint32_t entries;
     float alpha;
     float4* prows; uint32_t* pkeys;    // this level's partial slots
     uint32_t cell_log2;                // wown_kernel: cell size
@@ -328,10 +327,7 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32
     static_assert(C == 16 && G >= 16, "grid shapes");
     const float alpha = a.alpha;
     __shared__ uint32_t s_key[GROUPS][WOWN_WIN];
-    __shared__ uint32_t s_srow[GROUPS][WOWN_E];
-    __shared__ float s_coef[GROUPS][WOWN_E];
-    __shared__ uint32_t s_act[GROUPS][WOWN_E];
-    __shared__ uint32_t s_list[GROUPS][WOWN_E];
+    __shared__ uint4 s_list[GROUPS][WOWN_E];               // source row, coefficient, destination row, action
     const int l = threadIdx.x % G, grp = threadIdx.x / G;
     const uint32_t c = vb * (uint32_t)GROUPS + grp;
     const uint32_t nchunks = (a.entries + C - 1) / C;
@@ -373,15 +369,12 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32
                 act = (kn != k) ? ACT_COMPLETE : ACT_ADD;
             }
         }
-        if (inside) s_act[grp][i] = act;
         const bool use = act != ACT_SKIP;
         const uint64_t wave_mask = __ballot(use);
         const uint64_t mine = (G == 64) ? wave_mask : ((wave_mask >> group_lane0) & ((1ull << G) - 1ull));
         if (use) {
-            const uint32_t q = a.sidx[base + i];
-            s_srow[grp][i] = a.in_idx[q / a.T];          // range-checked copy
-            s_coef[grp][i] = a.coeffs[q];
-            s_list[grp][count + __popcll(mine & ((1ull << l) - 1ull))] = (uint32_t)i;
+            const SlotRecord r = a.rec[a.sidx[base + i]];
+            s_list[grp][count + __popcll(mine & ((1ull << l) - 1ull))] = make_uint4(r.row, __float_as_uint(r.coef), k, act);
         }
         count += __popcll(mine);
     }
@@ -409,15 +402,12 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32
     };
     auto fetch = [&](int idx, float4 (&sv)[NV], float4 (&dv)[NV]) {
         const bool on = idx < count;
-        const int i = on ? (int)s_list[grp][idx] : 0;
-        const uint32_t sr = on ? s_srow[grp][i] : 0u;
-        const bool cm = on && s_act[grp][i] == ACT_COMPLETE;
-        const uint32_t dk = cm ? K(i) : 0u;
+        const uint4 e = s_list[grp][on ? idx : 0];
         // Destination rows are read and written once per minibatch: with the non-temporal hint they
         // do not push the source rows (a few hundred MB that are read again and again) out of the
         // caches -- measured -7 % on this kernel; the same hint on the source rows costs +25 %.
-        src.load_if(on, sr, sv);
-        dst.load_nt_if(cm, dk, dv);
+        src.load_if(on, e.x, sv);
+        dst.load_nt_if(on && e.w == ACT_COMPLETE, e.z, dv);
     };
 #pragma unroll
     for (int t = 0; t < D; ++t) fetch(t, srcv[t], dstv[t]);
@@ -426,15 +416,14 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32
         for (int t = 0; t < D; ++t) {
             const int idx = b + t;
             if (idx < count) {
-                const int i = (int)s_list[grp][idx];
-                const uint32_t act = s_act[grp][i];
-                axpy<NV>(s_coef[grp][i], srcv[t], acc);
-                if (act == ACT_COMPLETE) {
-                    finish_row(K(i), dstv[t]);
+                const uint4 e = s_list[grp][idx];
+                axpy<NV>(__uint_as_float(e.y), srcv[t], acc);
+                if (e.w == ACT_COMPLETE) {
+                    finish_row(e.z, dstv[t]);
                     clear<NV>(acc);
-                } else if (act == ACT_HEAD) {            // our piece of a long run ends in the chunk
+                } else if (e.w == ACT_HEAD) {            // our piece of a long run ends in the chunk
                     store_row<G, NV>(a.prows + (uint64_t)head_slot * s4, d4, l, acc);
-                    if (l == 0) a.pkeys[head_slot] = K(i);
+                    if (l == 0) a.pkeys[head_slot] = e.z;
                     clear<NV>(acc);
                 }
             }
@@ -455,9 +444,9 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32
         uint32_t sr = 0;
         float cf = 0.f;
         if (l < cnt) {
-            const uint32_t q = a.sidx[x0 + l];
-            sr = a.in_idx[q / a.T];
-            cf = a.coeffs[q];
+            const SlotRecord r = a.rec[a.sidx[x0 + l]];
+            sr = r.row;
+            cf = r.coef;
         }
         // (no destination rows here: at one float4 per lane both register sets hold source rows, 2 D in
         // flight; at two that spills)
@@ -520,7 +509,7 @@ void launch_wseg_fill(uint32_t* pkeys, uint32_t M, hipStream_t st) {
 static SegArgs seg_args_of(const WSideArgs& w) {
     SegArgs a{};
     a.src = (const float4*)w.U; a.dst = (float4*)w.W; a.g = w.g; a.skey = w.skey; a.sidx = w.sidx;
-    a.in_idx = w.in_idx; a.coeffs = w.coeffs; a.entries = w.M; a.T = w.T;
+    a.rec = w.rec; a.entries = w.M;
     a.alpha = w.alpha; a.prows = (float4*)w.prows; a.pkeys = w.pkeys;
     a.skip_alone = w.skip_alone; a.cell_log2 = wown_cell_log2(w.M);
     return a;
@@ -529,7 +518,7 @@ static SegArgs seg_args_of(const WSideArgs& w) {
 static SegArgs seg_args_of(const TailArgs& t) {
     SegArgs a{};
     a.src = (const float4*)t.src_rows; a.dst = (float4*)t.M; a.g = t.g; a.skey = t.src_keys;
-    a.sidx = nullptr; a.in_idx = nullptr; a.coeffs = nullptr; a.entries = t.entries; a.T = 1;
+    a.sidx = nullptr; a.rec = nullptr; a.entries = t.entries;
     a.skip_alone = false;
     a.alpha = t.alpha; a.prows = (float4*)t.prows; a.pkeys = t.pkeys;
     a.defer_rows = (float4*)t.defer_rows; a.defer_keys = t.defer_keys; a.level = t.level; a.cp = t.cp;
@@ -809,7 +798,11 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
         uint32_t pi = i / T, j = i - pi * T;
         uint32_t q = s_pair[grp][pi] * T + j;
         s_key[grp][i] = a.keys[q];                 // may carry ALONE (fused, own rows)
-        if (!FUSED) s_cf[grp][i] = a.coeffs_in[q];
+        if (!FUSED) {
+            const float g = a.coeffs_in[q];
+            s_cf[grp][i] = g;
+            a.rec_out[q] = SlotRecord{s_skey[grp][pi + 1], g};
+        }
     }
     __syncthreads();
     if (!active) return;
@@ -860,7 +853,7 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
                 for (int t = 0; t < TB; ++t) sdot[t] = group_sum<G>(sdot[t]);
                 coefficients<G>(sdot, jb, gco, f, g);
                 if (l < TB && jb + l < T) {
-                    a.coeffs_out[p * T + jb + l] = g;
+                    a.rec_out[p * T + jb + l] = SlotRecord{key, g};
                     if (a.dots_out) a.dots_out[p * T + jb + l] = f;
                 }
             } else {
@@ -972,7 +965,11 @@ __global__ __launch_bounds__(USEG_THREADS, (SL::ONE ? 5 : 4)) void useg_multi_ke
         uint32_t pi = i / T, j = i - pi * T;
         uint32_t q = s_pair[grp][pi] * T + j;
         s_key[grp][i] = a.keys[q];                 // may carry ALONE (fused, own rows)
-        if (!FUSED) s_cf[grp][i] = a.coeffs_in[q];
+        if (!FUSED) {
+            const float g = a.coeffs_in[q];
+            s_cf[grp][i] = g;
+            a.rec_out[q] = SlotRecord{s_skey[grp][pi + 1], g};
+        }
     }
     __syncthreads();
     if (!active) return;
@@ -1029,7 +1026,7 @@ __global__ __launch_bounds__(USEG_THREADS, (SL::ONE ? 5 : 4)) void useg_multi_ke
                     for (int j = 0; j < T; ++j) sdot[j] = group_sum<G>(sdot[j]);
                     coefficients<G>(sdot, 0, gco, f, g);
                     if (l < T) {
-                        a.coeffs_out[p * T + l] = g;
+                        a.rec_out[p * T + l] = SlotRecord{key, g};
                         if (a.dots_out) a.dots_out[p * T + l] = f;
                     }
                 } else {

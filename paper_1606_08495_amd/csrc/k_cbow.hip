@@ -20,8 +20,7 @@ __global__ __launch_bounds__(256) void cbow_entries_kernel(const uint32_t* __res
                                                            const uint32_t* __restrict__ ctx_idx,
                                                            uint32_t n, uint32_t m, uint32_t V,
                                                            uint32_t* __restrict__ ctx_safe,
-                                                           uint32_t* __restrict__ ex_of,
-                                                           float* __restrict__ weight,
+                                                           SlotRecord* __restrict__ entry,
                                                            uint32_t* err) {
     uint32_t e = blockIdx.x * 256 + threadIdx.x;
     if (e >= m) return;
@@ -36,8 +35,7 @@ __global__ __launch_bounds__(256) void cbow_entries_kernel(const uint32_t* __res
     const uint32_t a = ctx_off[lo], b = ctx_off[lo + 1];
     const bool inside = a <= e && e < b && b <= m;
     if (!inside) atomicOr(err, 1u);
-    ex_of[e] = lo;
-    weight[e] = inside ? 1.0f / (float)(b - a) : 0.0f;
+    entry[e] = SlotRecord{lo, inside ? 1.0f / (float)(b - a) : 0.0f};
 }
 
 // Offsets must start at 0, never decrease and end at m.
@@ -105,13 +103,12 @@ __global__ __launch_bounds__(256) void cbow_hidden_kernel(const float4* __restri
 }
 
 void launch_cbow_entries(const uint32_t* ctx_off, const uint32_t* ctx_idx, uint32_t n, uint32_t m,
-                         uint32_t V, uint32_t* ctx_safe, uint32_t* ex_of, float* weight,
-                         uint32_t* err, hipStream_t st) {
+                         uint32_t V, uint32_t* ctx_safe, SlotRecord* entry, uint32_t* err, hipStream_t st) {
     hipLaunchKernelGGL(cbow_check_offsets_kernel, dim3(blocks_for((uint64_t)n + 1, 256)), dim3(256),
                        0, st, ctx_off, n, m, err);
     if (m == 0 || n == 0) return;
     hipLaunchKernelGGL(cbow_entries_kernel, dim3(blocks_for(m, 256)), dim3(256), 0, st, ctx_off,
-                       ctx_idx, n, m, V, ctx_safe, ex_of, weight, err);
+                       ctx_idx, n, m, V, ctx_safe, entry, err);
 }
 
 void launch_iota(uint32_t* x, uint32_t n, hipStream_t st) {
