@@ -42,9 +42,10 @@ static_assert(tail_block(16) == tail_block(32) && tail_block(64) < tail_block(16
 uint32_t tail_entries_least() { return tail_block(64); }
 // Pairs per chunk of the input-side kernel: about useg_e(G) entries (pairs x slots), 2..useg_maxp(G)
 // pairs.  Longer chunks cut fewer runs (fewer partial rows for the higher levels: -2.7 % on the
-// benchmark step, -6 % with k = 25, against chunks of 48 entries); with sixteen groups to a block
-// (rows of up to 64 floats) the short chunks stay: there the longer ones measured 1 % slower.
-constexpr int useg_e(int G) { return G == 16 ? 48 : 192; }
+// benchmark step, -6 % with k = 25, against chunks of 48 entries); rows of up to 64 floats take shorter ones (input side
+// and walk of 2^20 pairs of d = 60, us, with 48, 96 and 192 entries: k = 5 204 + 302, 202 + 295, 206 + 293; k = 10 799 + 583, 783 + 574,
+// 784 + 564).
+constexpr int useg_e(int G) { return G == 16 ? 96 : 192; }
 constexpr int useg_maxp(int G) { return G == 16 ? 16 : 32; }            // pairs per chunk, at most
 constexpr int useg_maxe(int G) {                 // entries, at most: c T < E + T, and 2 T, T <= 65
     return useg_e(G) + 66 < 136 ? 136 : useg_e(G) + 66;
@@ -763,31 +764,42 @@ __device__ __forceinline__ void coefficients(const float (&sdot)[N], uint32_t j0
 }
 
 
-template <int G, int NV, int TB, bool FUSED, bool OWN, class SL>
-__global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_t CP, SL sl) {
+// Bound by memory where the launch fills the chip.  A pair's rows are asked for TB at a time, then used: every load of a
+// batch before the first is waited for, one batch to a lane group, many lane groups.  (With a branch around each load the
+// compiler waits for all loads before it: the same kernel with one or two rows in flight.  Input side of a step, us, that
+// way and this: 4096 pairs of d = 100 10.8, 7.0; 65 536 58, 52; 100 003 pairs over five shards of 60 columns 182, 130.)
+// PIPED: a register set is refilled as soon as its row is used.  Only where a lane group is sixteen lanes and a batch nine rows
+// or more, in four wavefronts a SIMD: k = 10, 2^20 pairs of d = 60 729 us, batch by batch 779; d = 100, k = 10, 294 and 284; d = 200,
+// k = 25, 892 and 814.
+// FULL: pairs are whole batches, and no load stands behind a branch of its own; ONE_BATCH: of one batch.
+enum Batches { ANY_BATCH, FULL_BATCHES, ONE_BATCH };
+template <int G, int NV, int TB, Batches FULL, bool FUSED, bool OWN, class SL>
+__global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FULL == ONE_BATCH ? (SL::ONE ? 5 : 4) : 1) void useg_kernel(USideArgs a, uint32_t CP, SL sl) {
     constexpr bool NEED_U = FUSED || OWN;      // the pair's input row: for the dots, for own rows
+    constexpr bool PIPED = G == 16 && FULL != ONE_BATCH;
     const float alpha = a.alpha;
     constexpr int GROUPS = USEG_THREADS / G;
     // The chunk's indices are staged in LDS first (two dependent gathers for the whole chunk), so
     // that the row loads of the main loop depend on nothing but LDS reads.
-    constexpr int USEG_MAXE = useg_maxe(G), USEG_MAXP = useg_maxp(G);
-    __shared__ uint32_t s_key[GROUPS][USEG_MAXE];                 // output row of every entry
-    __shared__ float s_cf[FUSED ? 1 : GROUPS][FUSED ? 1 : USEG_MAXE];   // given coefficients
-    __shared__ uint32_t s_pair[GROUPS][USEG_MAXP];                // pair number of every sorted pair
-    __shared__ uint32_t s_skey[GROUPS][USEG_MAXP + 2];            // input word: [0] before, [cnt+1] after
-    const int l = threadIdx.x % G, grp = threadIdx.x / G;
+    constexpr int MAXP = useg_maxp(G), MAXE = FULL == ONE_BATCH ? MAXP * TB : useg_maxe(G);
+    __shared__ uint32_t s_key[GROUPS][MAXE];                      // output row of every entry
+    __shared__ float s_cf[FUSED ? 1 : GROUPS][FUSED ? 1 : MAXE];  // given coefficients
+    __shared__ uint32_t s_pair[GROUPS][MAXP];                     // pair number of every sorted pair
+    __shared__ uint32_t s_skey[GROUPS][MAXP + 2];                 // input word: [0] before, [cnt+1] after
+    const int l = threadIdx.x % G, grp = (int)group_value<G>(threadIdx.x / G);
     const uint32_t c = blockIdx.x * (uint32_t)GROUPS + grp;
     const uint32_t nchunks = (a.n + CP - 1) / CP;
     const bool active = c < nchunks;
     const uint32_t ps0 = active ? c * CP : 0u;
     const uint32_t cnt = active ? min(CP, a.n - ps0) : 0u;
-    const uint32_t T = a.T;
+    const uint32_t T = FULL == ONE_BATCH ? TB : a.T;
     // (the output side's border slots must be clear before its kernel: a share of them per block)
     for (uint32_t i = blockIdx.x * USEG_THREADS + threadIdx.x; i < a.clear_count; i += gridDim.x * USEG_THREADS)
         a.clear_keys[i] = KEY_NONE;
     for (uint32_t i = l; i < cnt; i += G) {
         s_pair[grp][i] = a.perm[ps0 + i];
         s_skey[grp][i + 1] = a.skey[ps0 + i];
+        a.dkey[ps0 + i] = KEY_NONE;
     }
     if (active && l == 0) {
         s_skey[grp][0] = ps0 > 0 ? a.skey[ps0 - 1] : NOKEY;
@@ -814,79 +826,94 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
     float4* delta = (float4*)a.delta;
     float4* prows = (float4*)a.prows;
 
-    uint32_t key = s_skey[grp][1];
-    const bool open_head = (s_skey[grp][0] == key);
+    uint32_t key = group_value<G>(s_skey[grp][1]);
+    const bool open_head = (group_value<G>(s_skey[grp][0]) == key);
     uint32_t run_start = ps0;
     uint32_t head_key = KEY_NONE, tail_key = KEY_NONE;
     const uint32_t head_slot = 2 * c - 1, tail_slot = 2 * c;
 
-    float4 acc[NV], w[TB][NV], u[NV], un[NV];
+    // (what the lanes past a row's end hold is never stored)
+    float4 acc[NV];
     clear<NV>(acc);
-    // prologue: the first batch of rows (and u) of the chunk's first pair
+    float4 w[TB][NV], u[1][NV], un[NV];
+    uint32_t row[TB];
+    if (PIPED) {
 #pragma unroll
-    for (int t = 0; t < TB; ++t) {
-        bool on = (uint32_t)t < T;
-        uint32_t r = on ? (s_key[grp][t] & ~ALONE) : 0u;
-        W.load_if(on, r, w[t]);
+        for (int t = 0; t < TB; ++t) {
+            row[t] = (uint32_t)t < T ? s_key[grp][t] : 0u;
+            if ((uint32_t)t < T) W.template load_part<false>(row[t] & ~ALONE, w[t]);
+        }
+        if (NEED_U) U.template load_part<false>(key, u[0]);
     }
-    if (NEED_U) U.load(key, u);
-
     for (uint32_t pi = 0; pi < cnt; ++pi) {
-        const uint32_t ps = ps0 + pi;
         const uint32_t p = s_pair[grp][pi];
-        const uint32_t next = s_skey[grp][pi + 2];
-        if (l == 0) a.dkey[ps] = KEY_NONE;
-        if (NEED_U) {                                  // the next pair's input row, ahead of need
-            bool more = pi + 1 < cnt;
-            U.load_if(more, more ? next : 0u, un);
+        const uint32_t next = group_value<G>(s_skey[grp][pi + 2]);
+        if (PIPED && NEED_U) {                   // the next pair's input row, ahead of need
+            if (pi + 1 < cnt) U.template load_part<false>(next, un);
+        } else if (NEED_U) {
+            const uint32_t in[1] = {key};
+            U.template load_all<false>(in, 1u, u);
         }
         for (uint32_t jb = 0; jb < T; jb += TB) {
+            const uint32_t slots = FULL ? TB : min((uint32_t)TB, T - jb);
             const bool last_batch = jb + TB >= T;
-            const uint32_t npi = last_batch ? pi + 1 : pi;     // where the following batch starts
-            const uint32_t njb = last_batch ? 0u : jb + TB;
+            const uint32_t npi = last_batch ? pi + 1 : pi, njb = last_batch ? 0u : jb + TB;      // the batch that follows
+            if (!PIPED) {
+#pragma unroll
+                for (int t = 0; t < TB; ++t) row[t] = (uint32_t)t < slots ? group_value<G>(s_key[grp][pi * T + jb + t]) : 0u;
+            }
+            // a row that no other slot names is read here once and written once: the
+            // non-temporal hint keeps it out of the caches' way (without it, step of 2^20 pairs of d = 300, this kernel
+            // 1.98 ms, with it 1.73)
+            if (!PIPED) W.template load_all<OWN && G == 64>(row, slots, w);
             float gco[TB];
             if (FUSED) {
                 float sdot[TB], f, g;
 #pragma unroll
-                for (int t = 0; t < TB; ++t) sdot[t] = dot_part<NV>(u, w[t]);
+                for (int t = 0; t < TB; ++t) sdot[t] = dot_part_of<NV>(W, u[0], w[t]);
 #pragma unroll
                 for (int t = 0; t < TB; ++t) sdot[t] = group_sum<G>(sdot[t]);
                 coefficients<G>(sdot, jb, gco, f, g);
-                if (l < TB && jb + l < T) {
+                if ((uint32_t)l < slots) {
                     a.rec_out[p * T + jb + l] = SlotRecord{key, g};
                     if (a.dots_out) a.dots_out[p * T + jb + l] = f;
                 }
             } else {
 #pragma unroll
-                for (int t = 0; t < TB; ++t)
-                    gco[t] = (jb + t < T) ? s_cf[grp][pi * T + jb + t] : 0.f;
+                for (int t = 0; t < TB; ++t) gco[t] = (uint32_t)t < slots ? s_cf[grp][pi * T + jb + t] : 0.f;
             }
+            // An output row that no other slot names gets its whole update here, from the
+            // registers, with the same two roundings as the output-side kernel
+            // (fl(g u), then one fma with alpha); that kernel never sees the slot.
+            auto own_row = [&](int t) {
+                if (!OWN || (uint32_t)t >= slots || !(row[t] & ALONE)) return;
+                float4 out[NV];
 #pragma unroll
-            for (int t = 0; t < TB; ++t) {
-                if (jb + t < T) {
-                    axpy<NV>(gco[t], w[t], acc);
-                    // an output row that no other slot names gets its whole update here (see the
-                    // fixed-T kernel below)
-                    const uint32_t rr = OWN ? s_key[grp][pi * T + jb + t] : 0u;
-                    if (OWN && (rr & ALONE)) {
-                        float4 out[NV];
+                for (int v = 0; v < NV; ++v) {
+                    out[v].x = fmaf(alpha, fmaf(gco[t], u[0][v].x, 0.f), w[t][v].x);
+                    out[v].y = fmaf(alpha, fmaf(gco[t], u[0][v].y, 0.f), w[t][v].y);
+                    out[v].z = fmaf(alpha, fmaf(gco[t], u[0][v].z, 0.f), w[t][v].z);
+                    out[v].w = fmaf(alpha, fmaf(gco[t], u[0][v].w, 0.f), w[t][v].w);
+                }
+                W.store_part_nt(row[t] & ~ALONE, out);
+            };
+            if (PIPED) {
 #pragma unroll
-                        for (int v = 0; v < NV; ++v) {
-                            out[v].x = fmaf(alpha, fmaf(gco[t], u[v].x, 0.f), w[t][v].x);
-                            out[v].y = fmaf(alpha, fmaf(gco[t], u[v].y, 0.f), w[t][v].y);
-                            out[v].z = fmaf(alpha, fmaf(gco[t], u[v].z, 0.f), w[t][v].z);
-                            out[v].w = fmaf(alpha, fmaf(gco[t], u[v].w, 0.f), w[t][v].w);
-                        }
-                        W.store_nt(rr & ~ALONE, out);
+                for (int t = 0; t < TB; ++t) {
+                    if ((uint32_t)t < slots) axpy<NV>(gco[t], w[t], acc);
+                    own_row(t);
+                    // this register set is free again: the matching row of the following batch
+                    if (npi < cnt && njb + t < T) {
+                        row[t] = s_key[grp][npi * T + njb + t];
+                        W.template load_part<false>(row[t] & ~ALONE, w[t]);
                     }
                 }
-                // this register set is free again: fetch the matching row of the following batch
-                uint32_t nj = njb + t;
-                bool on = npi < cnt && nj < T;
-                // (the non-temporal hint for rows named once, which pays in the fixed-T kernel,
-                // costs 25 % here: the branch breaks up this loop's batched loads)
-                uint32_t r = on ? (s_key[grp][npi * T + nj] & ~ALONE) : 0u;
-                W.load_if(on, r, w[t]);
+            } else {
+#pragma unroll
+                for (int t = 0; t < TB; ++t) own_row(t);
+#pragma unroll
+                for (int t = 0; t < TB; ++t)
+                    if ((uint32_t)t < slots) axpy<NV>(gco[t], w[t], acc);
             }
         }
         if (next != key) {                       // the run of `key` ends with this pair
@@ -898,11 +925,11 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
                 if (l == 0) a.dkey[run_start] = key;
             }
             clear<NV>(acc);
-            run_start = ps + 1;
+            run_start = ps0 + pi + 1;
         }
-        if (NEED_U) {
+        if (PIPED && NEED_U) {
 #pragma unroll
-            for (int v = 0; v < NV; ++v) u[v] = un[v];
+            for (int v = 0; v < NV; ++v) u[0][v] = un[v];
         }
         key = next;
     }
@@ -923,183 +950,14 @@ __global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_
     }
 }
 
-// ---------------------------------------------------------------------------------------------
-// The same step for a compile-time number of slots per pair (T), taking PB pairs per batch: all
-// PB*T output rows and the PB input rows of a batch are requested before the first of them is
-// used, so a lane group keeps PB*(T+1) rows in flight instead of T+1.  The kernel is
-// latency-bound (rows in flight per SIMD x row size / memory latency), and registers spent on
-// rows in flight buy more than registers spent on extra resident waves.
-// ---------------------------------------------------------------------------------------------
-// Register budget for five wavefronts per SIMD: at two float4 per lane the fused form would take
-// 102 registers and run four; held to 96 it spills five and is 1.6 % faster.  (Six: 30 % slower.
-// The same squeeze on the generic kernel or on the output-side kernel costs more than it gives.)
-template <int G, int NV, int T, int PB, bool FUSED, bool OWN, class SL>
-__global__ __launch_bounds__(USEG_THREADS, (SL::ONE ? 5 : 4)) void useg_multi_kernel(USideArgs a, uint32_t CP, SL sl) {
-    constexpr bool NEED_U = FUSED || OWN;
-    const float alpha = a.alpha;
-    constexpr int GROUPS = USEG_THREADS / G;
-    constexpr int MAXP = useg_maxp(G), MAXE = MAXP * T;
-    __shared__ uint32_t s_key[GROUPS][MAXE];
-    __shared__ float s_cf[FUSED ? 1 : GROUPS][FUSED ? 1 : MAXE];
-    __shared__ uint32_t s_pair[GROUPS][MAXP];
-    __shared__ uint32_t s_skey[GROUPS][MAXP + 2];
-    const int l = threadIdx.x % G, grp = threadIdx.x / G;
-    const uint32_t c = blockIdx.x * (uint32_t)GROUPS + grp;
-    const uint32_t nchunks = (a.n + CP - 1) / CP;
-    const bool active = c < nchunks;
-    const uint32_t ps0 = active ? c * CP : 0u;
-    const uint32_t cnt = active ? min(CP, a.n - ps0) : 0u;
-    // (the output side's border slots must be clear before its kernel: a share of them per block)
-    for (uint32_t i = blockIdx.x * USEG_THREADS + threadIdx.x; i < a.clear_count; i += gridDim.x * USEG_THREADS)
-        a.clear_keys[i] = KEY_NONE;
-    for (uint32_t i = l; i < cnt; i += G) {
-        s_pair[grp][i] = a.perm[ps0 + i];
-        s_skey[grp][i + 1] = a.skey[ps0 + i];
-    }
-    if (active && l == 0) {
-        s_skey[grp][0] = ps0 > 0 ? a.skey[ps0 - 1] : NOKEY;
-        s_skey[grp][cnt + 1] = ps0 + cnt < a.n ? a.skey[ps0 + cnt] : NOKEY;
-    }
-    __syncthreads();
-    for (uint32_t i = l; i < cnt * T; i += G) {
-        uint32_t pi = i / T, j = i - pi * T;
-        uint32_t q = s_pair[grp][pi] * T + j;
-        s_key[grp][i] = a.keys[q];                 // may carry ALONE (fused, own rows)
-        if (!FUSED) {
-            const float g = a.coeffs_in[q];
-            s_cf[grp][i] = g;
-            a.rec_out[q] = SlotRecord{s_skey[grp][pi + 1], g};
-        }
-    }
-    __syncthreads();
-    if (!active) return;
-
-    const uint32_t d4 = a.g.d4;
-    const uint64_t s4 = a.g.stride4;
-    const Rows<G, NV, SL, 0> U(sl, (const float4*)a.U, a.g, l);
-    const Rows<G, NV, SL, 1> W(sl, (const float4*)a.W, a.g, l);
-    float4* delta = (float4*)a.delta;
-    float4* prows = (float4*)a.prows;
-
-    uint32_t key = s_skey[grp][1];
-    const bool open_head = (s_skey[grp][0] == key);
-    uint32_t run_start = ps0;
-    uint32_t head_key = KEY_NONE, tail_key = KEY_NONE;
-    const uint32_t head_slot = 2 * c - 1, tail_slot = 2 * c;
-
-    float4 acc[NV];
-    clear<NV>(acc);
-    for (uint32_t pb = 0; pb < cnt; pb += PB) {
-        float4 w[PB][T][NV], u[PB][NV];
-#pragma unroll
-        for (int b = 0; b < PB; ++b) {
-            const uint32_t pi = pb + b;
-            const bool live = pi < cnt;
-            if (NEED_U) {
-                const uint32_t k_in = live ? s_skey[grp][pi + 1] : 0u;
-                U.load_if(live, k_in, u[b]);
-            }
-#pragma unroll
-            for (int j = 0; j < T; ++j) {
-                const uint32_t rk = live ? s_key[grp][pi * T + j] : 0u;
-                const uint32_t r = rk & ~ALONE;
-                // a row that no other slot names is read here once and written once: the
-                // non-temporal hint keeps it out of the caches' way (-7 % on this kernel)
-                if (rk & ALONE) W.load_nt_if(live, r, w[b][j]);
-                else W.load_if(live, r, w[b][j]);
-            }
-        }
-#pragma unroll
-        for (int b = 0; b < PB; ++b) {
-            const uint32_t pi = pb + b;
-            if (pi < cnt) {
-                const uint32_t ps = ps0 + pi;
-                const uint32_t p = s_pair[grp][pi];
-                const uint32_t next = s_skey[grp][pi + 2];
-                if (l == 0) a.dkey[ps] = KEY_NONE;
-                float gco[T];
-                if (FUSED) {
-                    float sdot[T], f, g;
-#pragma unroll
-                    for (int j = 0; j < T; ++j) sdot[j] = dot_part<NV>(u[b], w[b][j]);
-#pragma unroll
-                    for (int j = 0; j < T; ++j) sdot[j] = group_sum<G>(sdot[j]);
-                    coefficients<G>(sdot, 0, gco, f, g);
-                    if (l < T) {
-                        a.rec_out[p * T + l] = SlotRecord{key, g};
-                        if (a.dots_out) a.dots_out[p * T + l] = f;
-                    }
-                } else {
-#pragma unroll
-                    for (int j = 0; j < T; ++j) gco[j] = s_cf[grp][pi * T + j];
-                }
-                // An output row that no other slot names gets its whole update here, from the
-                // registers, with the same two roundings as the output-side kernel
-                // (fl(g u), then one fma with alpha); that kernel never sees the slot.
-                if (OWN) {
-#pragma unroll
-                    for (int j = 0; j < T; ++j) {
-                        const uint32_t r = s_key[grp][pi * T + j];
-                        if (r & ALONE) {
-                            float4 out[NV];
-#pragma unroll
-                            for (int v = 0; v < NV; ++v) {
-                                out[v].x = fmaf(alpha, fmaf(gco[j], u[b][v].x, 0.f), w[b][j][v].x);
-                                out[v].y = fmaf(alpha, fmaf(gco[j], u[b][v].y, 0.f), w[b][j][v].y);
-                                out[v].z = fmaf(alpha, fmaf(gco[j], u[b][v].z, 0.f), w[b][j][v].z);
-                                out[v].w = fmaf(alpha, fmaf(gco[j], u[b][v].w, 0.f), w[b][j][v].w);
-                            }
-                            W.store_nt(r & ~ALONE, out);
-                        }
-                    }
-                }
-#pragma unroll
-                for (int j = 0; j < T; ++j) axpy<NV>(gco[j], w[b][j], acc);
-                if (next != key) {                       // the run of `key` ends with this pair
-                    if (run_start == ps0 && open_head) {
-                        store_row<G, NV>(prows + (uint64_t)head_slot * s4, d4, l, acc);
-                        head_key = key;
-                    } else {
-                        store_row<G, NV>(delta + (uint64_t)run_start * s4, d4, l, acc);
-                        if (l == 0) a.dkey[run_start] = key;
-                    }
-                    clear<NV>(acc);
-                    run_start = ps + 1;
-                }
-                key = next;
-            }
-        }
-    }
-    if (run_start < ps0 + cnt) {                 // the last run goes on into the next chunk
-        const uint32_t k_last = s_skey[grp][cnt];
-        if (run_start == ps0 && open_head) {
-            store_row<G, NV>(prows + (uint64_t)head_slot * s4, d4, l, acc);
-            head_key = k_last;
-            tail_key = k_last | KEY_ZERO;
-        } else {
-            store_row<G, NV>(prows + (uint64_t)tail_slot * s4, d4, l, acc);
-            tail_key = k_last;
-        }
-    }
-    if (l == 0) {
-        if (c > 0) a.pkeys[head_slot] = head_key;
-        if (c + 1 < nchunks) a.pkeys[tail_slot] = tail_key;
-    }
-}
-
-constexpr int USEG_PB = 1;     // pairs per batch of the fixed-T kernel (1 measured best on MI355X)
-
-// A fixed-T kernel exists for k = 5 (the paper's and the benchmark's number of negatives); other T
-// take the generic kernel (fixed-T variants for k = 10 and 25 measured no better, or worse).
-
-template <int G, int NV, int T, class SL>
-static void launch_useg_fixed(const USideArgs& a, const SL& sl, uint32_t CP, dim3 grid, dim3 block, hipStream_t st) {
+template <int G, int NV, int TB, Batches FULL, class SL>
+static void launch_useg_batch(const USideArgs& a, const SL& sl, uint32_t CP, dim3 grid, dim3 block, hipStream_t st) {
     if (a.fused && a.own_rows)                   // (only the fused form takes rows over, or slices)
-        hipLaunchKernelGGL((useg_multi_kernel<G, NV, T, USEG_PB, true, true, SL>), grid, block, 0, st, a, CP, sl);
+        hipLaunchKernelGGL((useg_kernel<G, NV, TB, FULL, true, true, SL>), grid, block, 0, st, a, CP, sl);
     else if (a.fused)
-        hipLaunchKernelGGL((useg_multi_kernel<G, NV, T, USEG_PB, true, false, SL>), grid, block, 0, st, a, CP, sl);
+        hipLaunchKernelGGL((useg_kernel<G, NV, TB, FULL, true, false, SL>), grid, block, 0, st, a, CP, sl);
     else if constexpr (SL::ONE)
-        hipLaunchKernelGGL((useg_multi_kernel<G, NV, T, USEG_PB, false, false, SL>), grid, block, 0, st, a, CP, sl);
+        hipLaunchKernelGGL((useg_kernel<G, NV, TB, FULL, false, false, SL>), grid, block, 0, st, a, CP, sl);
 }
 
 template <int G, int NV, class SL>
@@ -1107,12 +965,13 @@ static void launch_useg_shape(const USideArgs& a, const SL& sl, hipStream_t st) 
     const uint32_t CP = useg_pairs_per_chunk(a.T, a.g.d4, a.n);
     const uint32_t nchunks = (a.n + CP - 1) / CP;
     dim3 grid(blocks_for((uint64_t)nchunks * G, USEG_THREADS)), block(USEG_THREADS);
+    // (the number of slots is a constant for k = 5, the paper's and the benchmark's number of negatives)
     if constexpr (NV <= 2) {
-        if (a.T == 6) return launch_useg_fixed<G, NV, 6>(a, sl, CP, grid, block, st);
+        if (a.T == 6) return launch_useg_batch<G, NV, 6, ONE_BATCH>(a, sl, CP, grid, block, st);
     }
     constexpr int TB = NV == 1 ? 9 : (NV == 2 ? 6 : 4);     // rows requested per batch
     if constexpr (NV == 1) {
-        // The fused kernel with one float4 per lane has registers for up to thirteen rows in
+        // With one float4 per lane there are registers for up to thirteen rows in
         // flight: of 9, 11 and 13 rows per batch, take the one that needs the fewest batches per
         // pair and then leaves the fewest empty places in them (k = 10: one batch of 11 instead of
         // 9 + 2, input-side kernel 3 % faster; k = 25: 13 + 13 instead of 9 + 9 + 8, 1 %).
@@ -1123,16 +982,13 @@ static void launch_useg_shape(const USideArgs& a, const SL& sl, hipStream_t st) 
                 const uint32_t nb = (a.T + tb - 1) / tb, waste = nb * tb - a.T;
                 if (nb < best_nb || (nb == best_nb && waste < best_waste)) { best = tb; best_nb = nb; best_waste = waste; }
             }
-            if (best == 11) { hipLaunchKernelGGL((useg_kernel<G, NV, 11, true, true, SL>), grid, block, 0, st, a, CP, sl); return; }
-            if (best == 13) { hipLaunchKernelGGL((useg_kernel<G, NV, 13, true, true, SL>), grid, block, 0, st, a, CP, sl); return; }
+            if (best == 11) return a.T % 11 ? launch_useg_batch<G, NV, 11, ANY_BATCH>(a, sl, CP, grid, block, st)
+                                            : launch_useg_batch<G, NV, 11, FULL_BATCHES>(a, sl, CP, grid, block, st);
+            if (best == 13) return a.T % 13 ? launch_useg_batch<G, NV, 13, ANY_BATCH>(a, sl, CP, grid, block, st)
+                                            : launch_useg_batch<G, NV, 13, FULL_BATCHES>(a, sl, CP, grid, block, st);
         }
     }
-    if (a.fused && a.own_rows)                   // (only the fused form takes rows over, or slices)
-        hipLaunchKernelGGL((useg_kernel<G, NV, TB, true, true, SL>), grid, block, 0, st, a, CP, sl);
-    else if (a.fused)
-        hipLaunchKernelGGL((useg_kernel<G, NV, TB, true, false, SL>), grid, block, 0, st, a, CP, sl);
-    else if constexpr (SL::ONE)
-        hipLaunchKernelGGL((useg_kernel<G, NV, TB, false, false, SL>), grid, block, 0, st, a, CP, sl);
+    launch_useg_batch<G, NV, TB, ANY_BATCH>(a, sl, CP, grid, block, st);
 }
 
 void launch_useg(const USideArgs& a, hipStream_t st) {
