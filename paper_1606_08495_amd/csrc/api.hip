@@ -592,8 +592,8 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
     Side ws{p.pb_rows, p.pb_keys, p.pc_rows, p.pc_keys, p.slots_w1, 0u};
     uint32_t loss_step = (loss_out && fused) ? 1u : 0u;
     bool applied = false;
-    auto advance = [&](Side& x) {
-        x.slots = slots_after(x.slots, tail_entries_per_chunk(to.g.d4));
+    auto advance = [&](Side& x, bool joint_first = false) {
+        x.slots = slots_after(x.slots, tail_entries_per_chunk(to.g.d4, joint_first));
         std::swap(x.src_rows, x.dst_rows);
         std::swap(x.src_keys, x.dst_keys);
     };
@@ -685,7 +685,7 @@ void queue_adjust(w2v_shard* ws_owner, const Target& to, Plan& p, const uint32_t
         }
         launch_adjust_stage(x, st);
         if (higher) advance(ws);
-        if (u_level) advance(us);
+        if (u_level) advance(us, first);
         any = us.slots || ws.slots || loss_step || !applied;
     }
 }

@@ -141,7 +141,8 @@ void launch_scan_sums(uint32_t* sums, uint32_t nb, uint32_t* total, hipStream_t 
 uint32_t useg_pairs_per_chunk(uint32_t T, uint32_t d4, uint32_t n);   // by slots per pair, row geometry and minibatch size;
                                                           // smallest for the narrowest rows (d4 = 1)
 uint32_t wseg_entries_per_chunk(uint32_t M);    // by the number of contributions
-uint32_t tail_entries_per_chunk(uint32_t d4);   // by row geometry
+uint32_t tail_entries_per_chunk(uint32_t d4, bool first = false);   // by row geometry; first: the input side's first level
+                                                          // beside the output side's walk in one launch
 uint32_t tail_entries_least();                  // the least over all of them
 // Border slots of a list cut into chunks, two per border; and the most that any minibatch of up to this
 // size leaves at level 1.  Small minibatches are cut shorter, so that may be more than this size's own;

@@ -33,13 +33,19 @@ constexpr int adj_threads(int G) { return G == 16 ? 128 : 256; }      // everyth
 // a large minibatch's kernels share the memory, they have those kernels' block size and find room between
 // them (benchmark step: levels of 512 threads 46 us each, of 256 42; step 3.201 -> 3.194 ms).
 constexpr int tail_block(int G) { return G == 64 ? 128 : 256; }
+// The input side's first level beside the output side's walk: a quarter of that, eight entries to a group.  A group
+// reads its share one batch after the other, and this level was what that launch waited for (4096 pairs, d = 100: 17 us,
+// the walk alone 12); there are walks above it that take as many launches anyway.
+constexpr int tail_block_first(int G) { return tail_block(G) / 4; }
 constexpr int tail_threads(int G, int NV) { return G == 16 || NV == 2 ? 512 : (NV > 2 ? 256 : 1024); }
 constexpr uint32_t NOKEY = 0xFFFFFFFFu;   // compares unequal to every masked key
 constexpr uint32_t ALONE = KEY_ALONE;
 
-uint32_t tail_entries_per_chunk(uint32_t d4) { return d4 <= 32 ? tail_block(16) : tail_block(64); }
+uint32_t tail_entries_per_chunk(uint32_t d4, bool first) {
+    return first ? (d4 <= 32 ? tail_block_first(16) : tail_block_first(64)) : (d4 <= 32 ? tail_block(16) : tail_block(64));
+}
 static_assert(tail_block(16) == tail_block(32) && tail_block(64) < tail_block(16), "see above, and tail_entries_least");
-uint32_t tail_entries_least() { return tail_block(64); }
+uint32_t tail_entries_least() { return tail_block_first(64); }
 // Pairs per chunk of the input-side kernel: about useg_e(G) entries (pairs x slots), 2..useg_maxp(G)
 // pairs.  Longer chunks cut fewer runs (fewer partial rows for the higher levels: -2.7 % on the
 // benchmark step, -6 % with k = 25, against chunks of 48 entries); rows of up to 64 floats take shorter ones (input side
@@ -119,18 +125,18 @@ struct SegArgs {
 // ---------------------------------------------------------------------------------------------
 enum : uint32_t { TL_POS = 0xFFFFu, TL_HAS = 1u << 16, TL_COMPLETE = 1u << 17, TL_HEAD = 1u << 18 };
 
-template <int G, int NV, int THREADS> struct TailLds {
-    static constexpr int GROUPS = THREADS / G, C = tail_block(G) / GROUPS;
+template <int G, int NV, int THREADS, int CB = tail_block(G)> struct TailLds {
+    static constexpr int GROUPS = THREADS / G, C = CB / GROUPS;
     float4 rows[2 * GROUPS][G * NV];                      // head and tail piece of every part
-    uint32_t raw[tail_block(G) + 2];                      // keys of entries base - 1 .. base + CB
+    uint32_t raw[CB + 2];                                 // keys of entries base - 1 .. base + CB
     uint32_t list[GROUPS][C];
     uint32_t gkey[2 * GROUPS];
     uint32_t out_key[2];                                  // the block's own head and tail slot
 };
 
-template <int G, int NV, int THREADS, bool DEFER, int WHICH, class SL>
-__device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32_t vb, TailLds<G, NV, THREADS>& lds) {
-    constexpr int GROUPS = THREADS / G, CB = tail_block(G), C = CB / GROUPS;
+template <int G, int NV, int THREADS, bool DEFER, int WHICH, int CB, class SL>
+__device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32_t vb, TailLds<G, NV, THREADS, CB>& lds) {
+    constexpr int GROUPS = THREADS / G, C = CB / GROUPS;
     constexpr int D = NV == 1 && (DEFER || C == 8) ? 8 : (NV <= 2 ? 4 : 2);
     static_assert(C % 2 == 0, "a border's two slots fall into one part");
     constexpr int ROW4 = G * NV;                          // float4 of a row held in LDS
@@ -311,7 +317,10 @@ constexpr uint32_t WOWN_SHORT_CELLS = 1u << 19;
 static uint32_t wown_cell_log2(uint32_t M) { return M <= WOWN_SHORT_CELLS ? 5u : 6u; }
 constexpr int WOWN_WIN = 3 * WOWN_C + 2;     // keys staged: positions base-C-1 .. base+2C
 constexpr int WOWN_E = 2 * WOWN_C;           // positions summed from LDS facts: base .. base+2C-1
-enum : uint32_t { ACT_SKIP = 0, ACT_ADD = 1, ACT_COMPLETE = 2, ACT_HEAD = 3 };
+constexpr uint32_t RUN_ENDS = 0x80000000u;   // a listed entry with which a sum is complete
+// Rows in flight of a lane group, of either matrix: few, in many wavefronts (walk of 6.3 M slots of 60 columns, us, with two,
+// four and eight 313, 302, 341; 600 000 of 320 at two float4 a lane with one, two, four and eight 123, 114, 121, 216).
+constexpr int wown_depth(int NV) { return NV == 1 ? 4 : 2; }
 
 uint32_t wseg_entries_per_chunk(uint32_t M) { return 1u << wown_cell_log2(M); }
 uint32_t wseg_slots_most(uint32_t M) {
@@ -319,21 +328,30 @@ uint32_t wseg_slots_most(uint32_t M) {
     return std::max(slots_after(M, wseg_entries_per_chunk(M)), slots_after(before_step, wseg_entries_per_chunk(before_step)));
 }
 
-template <int G, int NV, int D, class SL>
+template <int G, int NV, class SL>
 __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32_t vb) {
     constexpr int WOWN_THREADS = adj_threads(G);
     constexpr int GROUPS = WOWN_THREADS / G;
     constexpr int C = WOWN_C;
+    constexpr int D = wown_depth(NV);                          // rows in flight, of either matrix
     const int L = 1 << a.cell_log2;                        // a multiple of C
     static_assert(C == 16 && G >= 16, "grid shapes");
     const float alpha = a.alpha;
     __shared__ uint32_t s_key[GROUPS][WOWN_WIN];
-    __shared__ uint4 s_list[GROUPS][WOWN_E];               // source row, coefficient, destination row, action
-    const int l = threadIdx.x % G, grp = threadIdx.x / G;
+    __shared__ SlotRecord s_rec[GROUPS][WOWN_E];           // the list: source row and coefficient,
+    __shared__ uint32_t s_dst[GROUPS][WOWN_E];             // destination row, with RUN_ENDS
+    const int l = threadIdx.x % G, l16 = threadIdx.x % 16, grp = (int)group_value<G>(threadIdx.x / G);
     const uint32_t c = vb * (uint32_t)GROUPS + grp;
     const uint32_t nchunks = (a.entries + C - 1) / C;
     const bool active = c < nchunks;
     const int64_t base = (int64_t)c * C;
+    constexpr int PER_LANE = G < WOWN_E ? WOWN_E / G : 1;
+    uint32_t slot[PER_LANE];                               // (asked for before it is known which are needed)
+#pragma unroll
+    for (int u = 0; u < PER_LANE; ++u) {
+        const int64_t pos = base + u * G + l;
+        slot[u] = active && u * G + l < WOWN_E && pos < (int64_t)a.entries ? a.sidx[pos] : 0u;
+    }
     for (int i = l; i < WOWN_WIN; i += G) {
         int64_t pos = base - C - 1 + i;
         s_key[grp][i] = (active && pos >= 0 && pos < (int64_t)a.entries) ? a.skey[pos] : NOKEY;
@@ -348,34 +366,35 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32
     const bool ext_ok = klast != NOKEY && !last_in_head && k2C != klast;
     // does the run through the chunk's last entry go on, as a long piece that this group owns?
     const bool cont = active && klast != NOKEY && kC == klast && (last_in_head ? own_head : k2C == klast);
-    // The positions this group sums are listed densely in s_list (positions that are skipped --
-    // another group's, or rows handled elsewhere -- take no place in the load pipeline below).
+    // (of a long piece the positions up to the cell's end, the window's at most, are listed; a short run has no cells)
+    const int left = (int)min((int64_t)(L - (int)(base & (L - 1))), (int64_t)a.entries - base);      // to the cell's end
+    const int reach = cont ? min(left, WOWN_E) : WOWN_E;
+    // The positions this group sums are listed densely (positions that are skipped --
+    // another group's, or rows handled elsewhere -- take no place in the loads below).
     int count = 0;
     const int group_lane0 = ((int)(threadIdx.x & 63) / G) * G;
-    for (int i0 = 0; i0 < WOWN_E; i0 += G) {
-        const int i = i0 + l;
+#pragma unroll
+    for (int u = 0; u < PER_LANE; ++u) {
+        const int i = u * G + l;
         const bool inside = i < WOWN_E;
         const uint32_t k = inside ? K(i) : NOKEY, kn = inside ? K(i + 1) : NOKEY;
-        uint32_t act = ACT_SKIP;
-        if (active && k != NOKEY && !(a.skip_alone && kn != k && K(i - 1) != k)) {
+        bool use = false, ends = kn != k;
+        if (active && k != NOKEY && i < reach && !(a.skip_alone && ends && K(i - 1) != k)) {
             if (i < C) {
-                if (head_exists && k == k0) {            // a run that came in from the left
-                    if (own_head) act = (kn != k) ? ACT_HEAD : ACT_ADD;
-                } else if (k2C != k) {                   // starts here and is short: ours entirely
-                    act = (kn != k) ? ACT_COMPLETE : ACT_ADD;
-                } else {                                 // starts here and is long: first piece
-                    act = ACT_ADD;
-                }
-            } else if (ext_ok && k == klast) {           // the rest of our last short run
-                act = (kn != k) ? ACT_COMPLETE : ACT_ADD;
+                if (head_exists && k == k0) use = own_head;    // a run that came in from the left
+                else { use = true; ends = ends && k2C != k; }  // starts here: ours entirely if short, else its first piece
+            } else if (ext_ok && k == klast) {                 // the rest of our last short run
+                use = true;
+            } else if (cont && k == klast) {                   // our long piece goes on
+                use = true; ends = false;
             }
         }
-        const bool use = act != ACT_SKIP;
         const uint64_t wave_mask = __ballot(use);
         const uint64_t mine = (G == 64) ? wave_mask : ((wave_mask >> group_lane0) & ((1ull << G) - 1ull));
         if (use) {
-            const SlotRecord r = a.rec[a.sidx[base + i]];
-            s_list[grp][count + __popcll(mine & ((1ull << l) - 1ull))] = make_uint4(r.row, __float_as_uint(r.coef), k, act);
+            const int at = count + __popcll(mine & ((1ull << l) - 1ull));
+            s_rec[grp][at] = a.rec[slot[u]];
+            s_dst[grp][at] = k | (ends ? RUN_ENDS : 0u);
         }
         count += __popcll(mine);
     }
@@ -388,7 +407,8 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32
     const uint32_t cell = (uint32_t)(base >> a.cell_log2);
     const uint32_t head_slot = 2 * cell - 1, tail_slot = 2 * cell;   // used only when they exist
 
-    float4 acc[NV], srcv[D][NV], dstv[D][NV];
+    // (what the lanes past a row's end hold is never stored)
+    float4 acc[NV];
     clear<NV>(acc);
     auto finish_row = [&](uint32_t row, const float4 (&old)[NV]) {
         float4 out[NV];
@@ -399,76 +419,84 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32
             out[v].z = fmaf(alpha, acc[v].z, old[v].z);
             out[v].w = fmaf(alpha, acc[v].w, old[v].w);
         }
-        dst.store_nt(row, out);
+        dst.store_part_nt(row, out);
     };
-    auto fetch = [&](int idx, float4 (&sv)[NV], float4 (&dv)[NV]) {
-        const bool on = idx < count;
-        const uint4 e = s_list[grp][on ? idx : 0];
-        // Destination rows are read and written once per minibatch: with the non-temporal hint they
-        // do not push the source rows (a few hundred MB that are read again and again) out of the
-        // caches -- measured -7 % on this kernel; the same hint on the source rows costs +25 %.
-        src.load_if(on, e.x, sv);
-        dst.load_nt_if(on && e.w == ACT_COMPLETE, e.z, dv);
-    };
-#pragma unroll
-    for (int t = 0; t < D; ++t) fetch(t, srcv[t], dstv[t]);
     for (int b = 0; b < count; b += D) {
-#pragma unroll
-        for (int t = 0; t < D; ++t) {
-            const int idx = b + t;
-            if (idx < count) {
-                const uint4 e = s_list[grp][idx];
-                axpy<NV>(__uint_as_float(e.y), srcv[t], acc);
-                if (e.w == ACT_COMPLETE) {
-                    finish_row(e.z, dstv[t]);
-                    clear<NV>(acc);
-                } else if (e.w == ACT_HEAD) {            // our piece of a long run ends in the chunk
-                    store_row<G, NV>(a.prows + (uint64_t)head_slot * s4, d4, l, acc);
-                    if (l == 0) a.pkeys[head_slot] = e.z;
-                    clear<NV>(acc);
+        const int at = min(b + l16, WOWN_E - 1), n = count - b;
+        const SlotRecord rec = s_rec[grp][at];
+        const uint32_t row_l = rec.row, coef_l = __float_as_uint(rec.coef), dst_l = s_dst[grp][at];
+        {
+            float4 srcv[D][NV], dstv[D][NV];
+            // Destination rows are read and written once per minibatch: with the non-temporal hint they
+            // do not push the source rows (a few hundred MB that are read again and again) out of the
+            // caches -- measured -7 % on this kernel; the same hint on the source rows costs +25 %.
+            unrolled<D>([&](auto t) {
+                constexpr int J = decltype(t)::value;
+                const uint32_t row = of_lane<G, J>(row_l);
+                if (J < n) src.template load_part<false>(row, srcv[J]);
+            });
+            unrolled<D>([&](auto t) {
+                constexpr int J = decltype(t)::value;
+                const uint32_t k = of_lane<G, J>(dst_l);
+                if (J < n && (k & RUN_ENDS)) dst.template load_part<true>(k & ~RUN_ENDS, dstv[J]);
+            });
+            unrolled<D>([&](auto t) {
+                constexpr int J = decltype(t)::value;
+                const uint32_t k = of_lane<G, J>(dst_l);
+                const float g = __uint_as_float(of_lane<G, J>(coef_l));
+                if (J < n) {
+                    axpy<NV>(g, srcv[J], acc);
+                    if (k & RUN_ENDS) {
+                        if (own_head && (k & ~RUN_ENDS) == k0) {       // our piece of a long run ends in the chunk
+                            store_row<G, NV>(a.prows + (uint64_t)head_slot * s4, d4, l, acc);
+                            if (l == 0) a.pkeys[head_slot] = k0;
+                        } else {
+                            finish_row(k & ~RUN_ENDS, dstv[J]);
+                        }
+                        clear<NV>(acc);
+                    }
                 }
-            }
-            fetch(idx + D, srcv[t], dstv[t]);
+            });
         }
     }
     if (!cont) return;
 
-    // ---- the long piece goes on past the chunk: stream through the rest of the cell ----
-    const uint32_t key = klast;
-    const int64_t limit = min((int64_t)(cell + 1) * L, (int64_t)a.entries);
-    bool ended = false;
-    for (int64_t x0 = base + C; x0 < limit; x0 += 16) {
+    // ---- the long piece goes on past the window: stream through the rest of the cell ----
+    const uint32_t key = group_value<G>(klast);
+    const int64_t limit = base + left;
+    bool ended = K(reach) != key;                          // (all of the window's positions up to there are key's, or none after)
+    for (int64_t x0 = base + WOWN_E; x0 < limit && !ended; x0 += 16) {
         const int nblk = (int)min((int64_t)16, limit - x0);
-        const bool same = l < nblk && a.skey[x0 + l] == key;
+        const bool same = l16 < nblk && a.skey[x0 + l16] == key;
         const uint32_t bits = (uint32_t)(__ballot(same) >> group_lane0) & 0xFFFFu;
         const int cnt = __builtin_ctz(~bits);             // entries of the run at the block's front
-        uint32_t sr = 0;
-        float cf = 0.f;
-        if (l < cnt) {
-            const SlotRecord r = a.rec[a.sidx[x0 + l]];
-            sr = r.row;
-            cf = r.coef;
-        }
-        // (no destination rows here: at one float4 per lane both register sets hold source rows, 2 D in
-        // flight; at two that spills)
-        constexpr int S = NV == 1 ? 2 * D : D;
-#pragma unroll
-        for (int b = 0; b < 16; b += S) {
-            if (b < cnt) {
-#pragma unroll
-                for (int t = 0; t < S; ++t)
-                    src.load_if(b + t < cnt, __shfl(sr, b + t, G), t < D ? srcv[t % D] : dstv[t % D]);
-#pragma unroll
-                for (int t = 0; t < S; ++t) axpy<NV>(__shfl(cf, b + t, G), t < D ? srcv[t % D] : dstv[t % D], acc);
-            }
-        }
-        if (cnt < nblk) { ended = true; break; }
+        SlotRecord rec{0, 0.f};
+        if (l16 < cnt) rec = a.rec[a.sidx[x0 + l16]];
+        const uint32_t row_l = rec.row, coef_l = __float_as_uint(rec.coef);
+        constexpr int S = 2 * D;                           // (no destination rows here)
+        unrolled<16 / S>([&](auto batch) {
+            constexpr int B = decltype(batch)::value * S;
+            const int n = cnt - B;
+            if (n <= 0) return;
+            float4 srcv[S][NV];
+            unrolled<S>([&](auto t) {
+                constexpr int J = decltype(t)::value;
+                const uint32_t row = of_lane<G, B + J>(row_l);
+                if (J < n) src.template load_part<false>(row, srcv[J]);
+            });
+            unrolled<S>([&](auto t) {
+                constexpr int J = decltype(t)::value;
+                const float g = __uint_as_float(of_lane<G, B + J>(coef_l));
+                if (J < n) axpy<NV>(g, srcv[J], acc);
+            });
+        });
+        ended = cnt < nblk;
     }
-    if (!ended) ended = limit >= (int64_t)a.entries || a.skey[limit] != key;
+    if (!ended && left > WOWN_E) ended = limit >= (int64_t)a.entries || a.skey[limit] != key;
     if (!last_in_head) {
         if (ended) {                                      // the whole run lay inside the cell
             float4 old[NV];
-            dst.load_nt_if(true, key, old);
+            dst.template load_part<true>(key, old);
             finish_row(key, old);
         } else {                                          // first piece of a run that leaves the cell
             store_row<G, NV>(a.prows + (uint64_t)tail_slot * s4, d4, l, acc);
@@ -483,9 +511,9 @@ __device__ __forceinline__ void wown_body(const SegArgs& a, const SL& sl, uint32
     }
 }
 
-template <int G, int NV, int D, class SL>
+template <int G, int NV, class SL>
 __global__ __launch_bounds__(adj_threads(G)) void wown_kernel(SegArgs a, SL sl) {
-    wown_body<G, NV, D>(a, sl, blockIdx.x);
+    wown_body<G, NV>(a, sl, blockIdx.x);
 }
 
 __global__ __launch_bounds__(256) void fill_u32_kernel(uint32_t* __restrict__ x, uint32_t n,
@@ -532,7 +560,7 @@ void launch_wseg(const WSideArgs& w, hipStream_t st) {
     uint32_t nchunks = (w.M + WOWN_C - 1) / WOWN_C;
 #define CALL(G, NV)                                                                              \
     with_slices(w.slices, [&](const auto& sl) {                                                   \
-        hipLaunchKernelGGL((wown_kernel<G, NV, (NV <= 2 ? 4 : 2), std::decay_t<decltype(sl)>>),  \
+        hipLaunchKernelGGL((wown_kernel<G, NV, std::decay_t<decltype(sl)>>),  \
                            dim3(blocks_for((uint64_t)nchunks * G, adj_threads(G))),               \
                            dim3(adj_threads(G)), 0, st, a, sl);                                  \
     })
@@ -642,11 +670,10 @@ struct StageDev {
 
 constexpr int stage_threads(int G, int NV, bool first) { return first ? adj_threads(G) : tail_threads(G, NV); }
 
-// (at two float4 per lane the output side's walk fills 96 registers, five wavefronts per SIMD: keep it so)
 template <int G, int NV, bool FIRST, class SL>
-__global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? (SL::ONE ? 5 : 4) : 1)) void adjust_stage_kernel(StageDev s, SL sl) {
+__global__ __launch_bounds__(stage_threads(G, NV, FIRST)) void adjust_stage_kernel(StageDev s, SL sl) {
     constexpr int D = NV <= 2 ? 4 : 2, THREADS = stage_threads(G, NV, FIRST);
-    __shared__ TailLds<G, NV, THREADS> lds;
+    __shared__ TailLds<G, NV, THREADS, FIRST ? tail_block_first(G) : tail_block(G)> lds;
     __shared__ double red[THREADS / 64];
     uint32_t b = blockIdx.x;                               // the input side's level first: its blocks run longest
     if (b < s.u_blocks) {
@@ -662,7 +689,7 @@ __global__ __launch_bounds__(stage_threads(G, NV, FIRST), (FIRST && NV == 2 ? (S
     }
     b -= s.loss_blocks;
     if (b < s.w_blocks) {
-        if (FIRST) wown_body<G, NV, D>(s.w, sl, b);
+        if constexpr (FIRST) wown_body<G, NV>(s.w, sl, b);
         else tail_body<G, NV, THREADS, false, 1>(s.w, sl, b, lds);
         return;
     }
@@ -692,7 +719,7 @@ template <int G, int NV, class SL>
 static void launch_stage_shape(StageDev s, const SL& sl, bool first, hipStream_t st) {
     if (first) s.w_blocks = blocks_for((uint64_t)((s.w.entries + WOWN_C - 1) / WOWN_C) * G, adj_threads(G));
     else s.w_blocks = blocks_for(s.w.entries, tail_block(G));
-    s.u_blocks = blocks_for(s.u.entries, tail_block(G));
+    s.u_blocks = blocks_for(s.u.entries, first ? tail_block_first(G) : tail_block(G));
     s.apply_blocks = blocks_for((uint64_t)blocks_for(s.apply.n, APPLY_P) * G, stage_threads(G, NV, first));
     const dim3 grid(s.w_blocks + s.u_blocks + s.apply_blocks + s.loss_blocks);
     if (grid.x == 0) return;
