@@ -844,6 +844,78 @@ __device__ __forceinline__ uint64_t merge64(uint64_t list, uint64_t rev, int lan
     return k;
 }
 
+// The similarities of a wavefront's candidates, lane r the one of candidate c of lane r (lanes 0 .. nr - 1, nr at least 1).
+// Rows are read 32 columns at a time by lanes side by side and go through LDS, from where each lane walks its own: a
+// lane that reads its row from memory takes a line of its own for every access, 64 to an instruction, and the fold was bound by
+// those (4096 queries over 2^20 x 300: 27 us a round, now 15; 100 over 200 003 x 100 25, now 19; one over 500 000 x 300 58, now 34).
+constexpr int FS_COLS = 32, FS_PITCH = FS_COLS + 4;      // (16-byte aligned, eight rows a pass over the banks)
+struct FoldRows { float x[65][FS_PITCH]; uint32_t c[64]; };      // row 64: the query
+template <bool VEC4, int AHEAD>
+__device__ __forceinline__ float wave_scores(const float* __restrict__ q, const float* __restrict__ Cm, uint32_t c, uint32_t nr,
+                                             uint32_t d, float iq, FoldRows& lds) {
+    constexpr int PER_ROW = VEC4 ? 8 : 32;               // lanes to a row
+    constexpr int ROWS = 64 / PER_ROW, STEPS = 64 / ROWS;
+    const uint32_t lane = threadIdx.x % 64, in_row = lane / PER_ROW, col = (lane % PER_ROW) * (VEC4 ? 4 : 1);
+    lds.c[lane] = c;
+    auto fence = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    fence();
+    typedef typename std::conditional<VEC4, float4, float>::type word;
+    struct Part { word x[STEPS], y; } part[AHEAD];       // columns asked for
+    auto none = [](uint32_t k, uint32_t d_) { return k >= d_; };
+    auto fetch = [&](uint32_t k0, Part& p) {                      // (past the last column: elsewhere in the row, zero when stored)
+        const uint32_t k = none(k0 + col, d) ? 0u : k0 + col;
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+            if ((uint32_t)(i * ROWS) >= nr) break;       // uniform
+            const uint32_t row = lds.c[min(i * ROWS + in_row, nr - 1)];
+            p.x[i] = *reinterpret_cast<const word*>(Cm + (uint64_t)row * d + k);
+        }
+        p.y = *reinterpret_cast<const word*>(q + k);
+    };
+    auto put = [&](uint32_t k0, const Part& p) {
+        const bool past = none(k0 + col, d);
+#pragma unroll
+        for (int i = 0; i < STEPS; ++i) {
+            if ((uint32_t)(i * ROWS) >= nr) break;
+            *reinterpret_cast<word*>(&lds.x[i * ROWS + in_row][col]) = past ? word{} : p.x[i];
+        }
+        if (lane < (uint32_t)PER_ROW) *reinterpret_cast<word*>(&lds.x[64][col]) = past ? word{} : p.y;
+    };
+    float dot = 0.f, lo[8], hi[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { lo[e] = 0.f; hi[e] = 0.f; }
+#pragma unroll
+    for (int t = 0; t < AHEAD; ++t)
+        if ((uint32_t)(t * FS_COLS) < d) fetch(t * FS_COLS, part[t]);
+    const uint32_t own = min(lane, nr - 1);
+#pragma unroll 1
+    for (uint32_t k1 = 0; k1 < d; k1 += AHEAD * FS_COLS) {
+#pragma unroll
+        for (int t = 0; t < AHEAD; ++t) {
+            const uint32_t k0 = k1 + t * FS_COLS;
+            if (k0 >= d) break;                          // uniform
+            put(k0, part[t]);
+            fence();
+            if (k0 + AHEAD * FS_COLS < d) fetch(k0 + AHEAD * FS_COLS, part[t]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {                // eight columns
+                const float4 u = *reinterpret_cast<const float4*>(&lds.x[own][8 * i]), v = *reinterpret_cast<const float4*>(&lds.x[own][8 * i + 4]);
+                const float4 f = *reinterpret_cast<const float4*>(&lds.x[64][8 * i]), g = *reinterpret_cast<const float4*>(&lds.x[64][8 * i + 4]);
+                dot = fmaf(f.x, u.x, dot); dot = fmaf(f.y, u.y, dot); dot = fmaf(f.z, u.z, dot); dot = fmaf(f.w, u.w, dot);
+                dot = fmaf(g.x, v.x, dot); dot = fmaf(g.y, v.y, dot); dot = fmaf(g.z, v.z, dot); dot = fmaf(g.w, v.w, dot);
+                square8(u, v, i % 2 ? hi : lo);
+            }
+            fence();
+        }
+    }
+    return dot * iq * inv_length(tree8(lo) + tree8(hi));
+}
+
+// The same by one lane from memory: of rows that are no multiple of four columns, and long, a block of sixteen wavefronts does
+// better that way than of eight through LDS (19 queries over 18 030 x 495 194 us, 207; 8 over 3249 x 51 54.9, 50.7).
 template <bool VEC4>
 __device__ __forceinline__ float exact_score(const float* __restrict__ q, const float* __restrict__ c, uint32_t d,
                                              float iq) {
@@ -870,13 +942,19 @@ __device__ __forceinline__ float exact_score(const float* __restrict__ q, const 
     return dot * iq * inv_length(tree8(lo) + tree8(hi));
 }
 
+constexpr uint32_t FOLD_LONG_ROW = 256;
 constexpr uint32_t FOLD_PICK = 2048;             // candidates named by bits that a block lists before it scores them
 constexpr uint32_t FOLD_CHUNK = 16;              // words: where they are more
 // candidates of a round for every block of a query (a block more costs what it takes to count: 100 queries over 200 003 x
 // 100, not crowded, 116.6 us, in five blocks each 116.9, and two in the round before 117.2)
 static uint32_t fold_share(uint32_t Q) { return Q <= 32 ? 1u << 13 : 1u << 15; }
+constexpr uint32_t FOLD_WORDS = 8;           // of a thread, in flight
+// Queries from which one wavefront folds a list: most lists fill one, and what LDS a block asks for says how many are on
+// the chip (4096 queries over 2^20 x 300, a round, by one, two and four wavefronts 15, 21, 34 us).  Of fewer queries a long list
+// costs more than that (600 over 200 000 x 7, crowded, the search by two and four wavefronts 325, 300 us; 300, 307 and 278).
+constexpr uint32_t FOLD_ALONE_Q = 1024;
 enum FoldFrom { FOLD_LIST, FOLD_SCORED, FOLD_BITS };
-template <int WAVES, bool VEC4, FoldFrom FROM>
+template <int WAVES, bool VEC4, FoldFrom FROM, bool BY_LANE = false>
 __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint32_t K, float tau,
                                                                uint64_t* __restrict__ best,
                                                                uint32_t* __restrict__ best_cnt,
@@ -891,6 +969,7 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
     };
     __shared__ Picked lds;
     __shared__ uint32_t s_picked;
+    __shared__ __align__(16) FoldRows s_rows[FROM == FOLD_SCORED || BY_LANE ? 1 : WAVES];
     const uint32_t q = a.q_first + blockIdx.x;
     const int lane = threadIdx.x % 64, wave = threadIdx.x / 64;
     const uint32_t part = FROM == FOLD_BITS ? blockIdx.y : 0u, n_parts = FROM == FOLD_BITS ? gridDim.y : 1u;
@@ -905,13 +984,18 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
         // the candidates whose bits are set, in any order: ranks decide
         if (threadIdx.x == 0) s_picked = 0;
         __syncthreads();
-#pragma unroll 8
-        for (uint32_t i = threadIdx.x; i < words; i += 64 * WAVES) {
-            uint32_t word = bits[i];
-            if (word == 0) continue;
-            uint32_t at = atomicAdd(&s_picked, (uint32_t)__popc(word));
-            for (; word; word &= word - 1, ++at)
-                if (at < FOLD_PICK) lds.pick[at] = a.c_begin + i * 32 + __builtin_ctz(word);
+        for (uint32_t i0 = threadIdx.x; i0 < words; i0 += FOLD_WORDS * 64 * WAVES) {
+            uint32_t word[FOLD_WORDS];                       // (asked for together, then looked at)
+#pragma unroll
+            for (uint32_t e = 0; e < FOLD_WORDS; ++e) word[e] = bits[min(i0 + e * 64 * WAVES, words - 1)];
+#pragma unroll
+            for (uint32_t e = 0; e < FOLD_WORDS; ++e) {
+                const uint32_t i = i0 + e * 64 * WAVES;
+                if (i >= words || word[e] == 0) continue;
+                uint32_t at = atomicAdd(&s_picked, (uint32_t)__popc(word[e]));
+                for (uint32_t left = word[e]; left; left &= left - 1, ++at)
+                    if (at < FOLD_PICK) lds.pick[at] = a.c_begin + i * 32 + __builtin_ctz(left);
+            }
         }
         __syncthreads();
         n_new = s_picked;
@@ -923,7 +1007,6 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
     const bool spilled = FROM == FOLD_BITS && n_new > FOLD_PICK;        // each wavefront looks through words of its own
     const int waves = spilled ? WAVES : min(WAVES, (int)((n_new + 63) / 64));      // that have any
     if (wave && wave >= waves) return;
-    auto score = [&](uint32_t c) { return exact_score<VEC4>(a.Qm + (uint64_t)q * a.d, a.Cm + (uint64_t)c * a.d, a.d, iq); };
     // spilled: sixteen words at a time are turned into candidates in order, until there is one for every lane
     uint32_t words_at = (part * WAVES + wave) * FOLD_CHUNK, queued = 0, taken = 0;
     for (uint32_t base = wave * 64u; spilled || base < n_new; base += 64u * WAVES) {
@@ -965,7 +1048,11 @@ __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint3
             const uint2 e = ((const uint2*)a.pend)[(uint64_t)q * a.cap + base + lane];
             s = __uint_as_float(e.x); c = e.y;
         }
-        if (FROM != FOLD_SCORED && on) s = score(c);
+        if constexpr (BY_LANE) {
+            if (on) s = exact_score<VEC4>(a.Qm + (uint64_t)q * a.d, a.Cm + (uint64_t)c * a.d, a.d, iq);
+        } else if constexpr (FROM != FOLD_SCORED) {          // (those that are on come first, and are some)
+            s = wave_scores<VEC4, (WAVES == 8 ? 2 : 1)>(a.Qm + (uint64_t)q * a.d, a.Cm, c, (uint32_t)__popcll(__ballot(on)), a.d, iq, s_rows[wave]);
+        }
         const uint64_t k = on && s > th ? rank_key(s, c) : 0ull;       // (a similarity that is no number never passes)
         if (__ballot(k != 0)) list = merge64(list, __shfl((unsigned long long)sort64(k, lane), 63 - lane, 64), lane);
     }
@@ -1265,14 +1352,16 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
         uint32_t* oi = last ? out_idx : nullptr;
         const bool bits = screen == TOPK_STREAM && !exact_round;
         const uint32_t parts = bits ? std::max(1u, std::min(plan.parts, m / fold_share(Q))) : 1u;
-#define W2V_FOLD(WAVES, VEC4, FROM)                                                                        \
-    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4, FROM>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first), parts), \
+#define W2V_FOLD(WAVES, VEC4, ...)                                                                         \
+    hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4, __VA_ARGS__>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first), parts), \
                        dim3(64 * WAVES), 0, st, a, K, tau, best, best_cnt, theta, oi, out_score, out_count)
         for (a.q_first = 0; a.q_first < Q; a.q_first += TK_FOLD_SLICE) {
             if (exact_round) W2V_FOLD(4, false, FOLD_SCORED);
+            else if (!bits && Q >= FOLD_ALONE_Q) { if (vec4) W2V_FOLD(1, true, FOLD_LIST); else W2V_FOLD(1, false, FOLD_LIST); }
             else if (!bits) { if (vec4) W2V_FOLD(4, true, FOLD_LIST); else W2V_FOLD(4, false, FOLD_LIST); }
-            else if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(4, true, FOLD_BITS); else W2V_FOLD(4, false, FOLD_BITS); }
-            else { if (vec4) W2V_FOLD(16, true, FOLD_BITS); else W2V_FOLD(16, false, FOLD_BITS); }
+            else if (vec4) W2V_FOLD(8, true, FOLD_BITS);
+            else if (d > FOLD_LONG_ROW && Q <= TK_STREAM_Q) W2V_FOLD(16, false, FOLD_BITS, true);
+            else W2V_FOLD(8, false, FOLD_BITS);
         }
 #undef W2V_FOLD
     }

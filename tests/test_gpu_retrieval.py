@@ -88,6 +88,21 @@ def test_topk_parity(Q, N, d, K, tau):
             assert np.array_equal(gi, ref[0]) and np.array_equal(gs, ref[1]) and np.array_equal(gc, ref[2])
 
 
+@pytest.mark.parametrize("d", [1, 3, 4, 28, 31, 32, 33, 36, 61, 64, 65, 100, 255, 257])
+def test_topk_folds_of_one_four_and_eight_wavefronts_agree(d):
+    """The fold reads rows 32 columns at a time, whole or in part, as one access of four columns or four: widths on either
+    side; by one wavefront a query, by four, and by eight from bits.  A similarity has the same bits in all."""
+    say("fold", d)
+    K, N = 30, 6000
+    Qm = workloads.embedding_like(1024, d, 11, n_clusters=40)
+    C = workloads.embedding_like(N, d, 12, n_clusters=40)
+    one = run_gpu(Qm, C, K, -2.0, 1024)
+    check_topk(Qm[:40], C, K, -2.0, *(x[:40] for x in one))
+    for Q in (1023, 9):
+        for a, b in zip(one, run_gpu(Qm[:Q], C, K, -2.0, 1024)):
+            assert np.array_equal(a[:Q], b), Q
+
+
 def test_topk_equal_similarities_rank_by_index_and_zero_vectors_score_zero():
     rng = np.random.default_rng(3)
     N, d, K = 2000, 60, 40
