@@ -66,31 +66,38 @@ __global__ __launch_bounds__(256) void cbow_hidden_kernel(const float4* __restri
                                                           const uint32_t* __restrict__ ctx_safe,
                                                           uint32_t n, uint32_t m,
                                                           float4* __restrict__ H) {
-    constexpr int UB = 4;
-    const int l = threadIdx.x % G;
+    constexpr int UB = NV == 1 ? 8 : (NV == 2 ? 4 : 2);
+    const int l = threadIdx.x % G, l16 = threadIdx.x % 16;
     const uint32_t p = (blockIdx.x * 256u + threadIdx.x) / G;
     if (p >= n) return;                                   // whole groups leave together
-    uint32_t lo = min(ctx_off[p], m);
-    uint32_t hi = min(max(ctx_off[p + 1], lo), m);
+    const Rows<G, NV, OneMatrix, 0> rows(OneMatrix{}, U, g, l);
+    const uint32_t lo = min(group_value<G>(ctx_off[p]), m);
+    const uint32_t hi = min(max(group_value<G>(ctx_off[p + 1]), lo), m);
+    // (what the lanes past a row's end hold is never stored)
     float4 acc[NV];
     clear<NV>(acc);
-    for (uint32_t e = lo; e < hi; e += UB) {
-        float4 r[UB][NV];
+    for (uint32_t e = lo; e < hi; e += 16) {              // sixteen words in one access, handed round
+        const uint32_t word = ctx_safe[min(e + (uint32_t)l16, hi - 1)];
+        unrolled<16 / UB>([&](auto batch) {
+            constexpr int B = decltype(batch)::value * UB;
+            if (e + B >= hi) return;
+            const uint32_t left = hi - (e + B);
+            float4 r[UB][NV];
+            unrolled<UB>([&](auto t) {
+                constexpr int J = decltype(t)::value;
+                const uint32_t w = of_lane<G, B + J>(word);
+                if ((uint32_t)J < left) rows.template load_part<false>(w, r[J]);
+            });
 #pragma unroll
-        for (int t = 0; t < UB; ++t) {
-            const bool on = e + t < hi;
-            const uint32_t w = on ? ctx_safe[e + t] : 0u;
-            load_row_if<G, NV>(on, U + (uint64_t)w * g.stride4, g.d4, l, r[t]);
-        }
+            for (int t = 0; t < UB; ++t)
+                if ((uint32_t)t < left) {
 #pragma unroll
-        for (int t = 0; t < UB; ++t)
-            if (e + t < hi) {
-#pragma unroll
-                for (int v = 0; v < NV; ++v) {
-                    acc[v].x += r[t][v].x; acc[v].y += r[t][v].y;
-                    acc[v].z += r[t][v].z; acc[v].w += r[t][v].w;
+                    for (int v = 0; v < NV; ++v) {
+                        acc[v].x += r[t][v].x; acc[v].y += r[t][v].y;
+                        acc[v].z += r[t][v].z; acc[v].w += r[t][v].w;
+                    }
                 }
-            }
+        });
     }
     if (hi > lo) {
         const float cnt = (float)(hi - lo);

@@ -211,10 +211,10 @@ __global__ __launch_bounds__(256) void mark_alone_kernel(const uint32_t* __restr
                                                          uint32_t M, uint32_t* __restrict__ keys) {
     uint32_t i = blockIdx.x * 256 + threadIdx.x;
     if (i >= M) return;
-    const uint32_t k = skey[i];
-    const bool left = i > 0 && skey[i - 1] == k;
-    const bool right = i + 1 < M && skey[i + 1] == k;
-    if (!left && !right) keys[sidx[i]] = k | KEY_ALONE;
+    const uint32_t k = skey[i], before = skey[max(i, 1u) - 1], after = skey[min(i + 1, M - 1)], slot = sidx[i];
+    const bool left = i > 0 && before == k;
+    const bool right = i + 1 < M && after == k;
+    if (!left && !right) keys[slot] = k | KEY_ALONE;
 }
 
 void launch_dest_keys(NoiseTable nt, const uint32_t* out_idx, uint32_t n, uint32_t k, uint64_t seed,
@@ -307,48 +307,52 @@ void launch_copy_negatives(const uint32_t* keys, uint32_t n, uint32_t k, uint32_
 // batches of TB with every load of a batch issued before the first multiply.
 // ---------------------------------------------------------------------------------------------
 constexpr int DOT_THREADS = 128;     // (256: the kernel 40 % slower beside other work, 64: the same)
-template <int G, int NV, int TB>
-__global__ __launch_bounds__(DOT_THREADS) void dots_kernel(const float4* __restrict__ U,
-                                                   const float4* __restrict__ W, RowGeom g,
+template <int G, int NV, int TB, bool FULL>
+__global__ __launch_bounds__(DOT_THREADS) void dots_kernel(const float4* __restrict__ Um, const float4* __restrict__ Wm, RowGeom g,
                                                    const uint32_t* __restrict__ in_idx,
                                                    const uint32_t* __restrict__ keys, uint32_t n,
                                                    uint32_t T, float* __restrict__ dots) {
     const int l = threadIdx.x % G;
-    uint32_t grp = (blockIdx.x * (uint32_t)DOT_THREADS + threadIdx.x) / G;
+    const uint32_t grp = group_value<G>((blockIdx.x * (uint32_t)DOT_THREADS + threadIdx.x) / G);
     const bool live = grp < n;
     const uint32_t p = live ? grp : n - 1;
-    const uint32_t wi = in_idx[p];          // already range-checked (launch_check_inputs)
-    float4 u[NV];
-    load_row<G, NV>(U + (uint64_t)wi * g.stride4, g.d4, l, u);
+    const Rows<G, NV, OneMatrix, 0> U(OneMatrix{}, Um, g, l);
+    const Rows<G, NV, OneMatrix, 1> W(OneMatrix{}, Wm, g, l);
+    const uint32_t in[1] = {group_value<G>(in_idx[p])};      // already range-checked (launch_check_inputs)
+    float4 u[1][NV], w[TB][NV];
     for (uint32_t jb = 0; jb < T; jb += TB) {
-        float4 w[TB][NV];
+        const uint32_t slots = FULL ? TB : min((uint32_t)TB, T - jb);      // (FULL: T is a multiple of TB)
+        uint32_t row[TB];                                    // (a prepared set's keys may carry the mark)
 #pragma unroll
-        for (int t = 0; t < TB; ++t) {
-            uint32_t j = jb + t;
-            bool on = j < T;
-            uint32_t r = on ? (keys[p * T + j] & ~KEY_ALONE) : 0u;   // (a prepared set may carry the mark)
-            load_row_if<G, NV>(on, W + (uint64_t)r * g.stride4, g.d4, l, w[t]);
-        }
+        for (int t = 0; t < TB; ++t) row[t] = group_value<G>(keys[p * T + min(jb + t, T - 1)]);
+        if (jb == 0) U.template load_all<false>(in, 1u, u);
+        W.template load_all<false>(row, slots, w);
         float s[TB];
 #pragma unroll
-        for (int t = 0; t < TB; ++t) s[t] = dot_part<NV>(u, w[t]);
+        for (int t = 0; t < TB; ++t) s[t] = dot_part_of<NV>(W, u[0], w[t]);
 #pragma unroll
         for (int t = 0; t < TB; ++t) s[t] = group_sum<G>(s[t]);
 #pragma unroll
         for (int t = 0; t < TB; ++t)
-            if (l == t && live && jb + t < T) dots[p * T + jb + t] = s[t];
+            if (l == t && live && (uint32_t)t < slots) dots[p * T + jb + t] = s[t];
     }
 }
 
 void launch_dots(const float* U, const float* W, RowGeom g, const uint32_t* in_idx,
                  const uint32_t* keys, uint32_t n, uint32_t T, float* dots, hipStream_t st) {
     if (n == 0) return;
-#define CALL(G, NV)                                                                               \
-    hipLaunchKernelGGL((dots_kernel<G, NV, (NV <= 2 ? 6 : 4)>),                                   \
+#define CALL_BATCH(G, NV, TB, FULL)                                                               \
+    hipLaunchKernelGGL((dots_kernel<G, NV, TB, FULL>),                                            \
                        dim3(blocks_for((uint64_t)n * G, DOT_THREADS)), dim3(DOT_THREADS), 0, st, (const float4*)U, \
                        (const float4*)W, g, in_idx, keys, n, T, dots)
+#define CALL(G, NV)                                                                               \
+    do {                                                                                          \
+        constexpr int TB = NV <= 2 ? 6 : 4;                                                       \
+        if (T % TB) CALL_BATCH(G, NV, TB, false); else CALL_BATCH(G, NV, TB, true);               \
+    } while (0)
     W2V_DISPATCH_GEOM(g.d4, CALL);
 #undef CALL
+#undef CALL_BATCH
 }
 
 // ---------------------------------------------------------------------------------------------

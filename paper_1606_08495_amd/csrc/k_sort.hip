@@ -218,15 +218,21 @@ __global__ __launch_bounds__(THREADS) void sort_pass_kernel(SortArgs a, uint32_t
 
     // element e of lane l of wave w is number w * WAVE_SPAN + e * 64 + l of the tile (n < 2^31)
     const uint32_t base = tile * (uint32_t)TILE + (uint32_t)wave * WAVE_SPAN + (uint32_t)lane;
+    // (what is past the end reads the last element and is left out below: with a branch around each load, they were
+    // waited for one by one)
     uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
+    if (first_pass) {
 #pragma unroll
-    for (int e = 0; e < ITEMS; ++e) {
-        const uint32_t i = base + (uint32_t)e * 64;
-        if (i < n) {
-            if (first_pass) { key[e] = jb.keys_in[i]; val[e] = i; }
-            else { const uint2 x = in[i]; key[e] = x.x; val[e] = x.y; }
-        } else {
-            key[e] = 0u; val[e] = 0u;
+        for (int e = 0; e < ITEMS; ++e) {
+            const uint32_t i = base + (uint32_t)e * 64;
+            key[e] = jb.keys_in[min(i, n - 1)];
+            val[e] = i;
+        }
+    } else {
+#pragma unroll
+        for (int e = 0; e < ITEMS; ++e) {
+            const uint2 x = in[min(base + (uint32_t)e * 64, n - 1)];
+            key[e] = x.x; val[e] = x.y;
         }
     }
     const uint64_t below = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
