@@ -66,6 +66,7 @@ void launch_init(float* M, uint32_t V, RowGeom g, uint32_t d_slice, uint32_t d_t
 // ---------------------------------------------------------------------------------------------
 constexpr int MOVE_ITEMS = 8;
 constexpr int MOVE_ROWS_MAX = 1024;               // rows of a block, at most (their words sit in LDS)
+constexpr uint32_t MOVE_GROUPS = 1u << 18;        // blocks of rows of several parts in x, at most (32 parts of them are less than 2^32 threads)
 enum MoveDir { MOVE_OUT, MOVE_IN };
 
 struct MovePart {                                 // one matrix and its columns on the caller's side
@@ -75,9 +76,10 @@ struct MovePart {                                 // one matrix and its columns 
     uint32_t* err;
 };
 template <int PARTS> struct MoveRows {
-    float* ext; uint32_t pitch, m, V, rows_per_block;
+    float* ext; uint32_t pitch, m, V, rows_per_block, parts, in_x;
+    bool together;                                // parts of the same rows are blocks that follow each other
     const uint32_t* rows;
-    MovePart part[PARTS];                         // one per blockIdx.y
+    MovePart part[PARTS];
 };
 
 template <int VEC> struct MoveWord;
@@ -89,8 +91,17 @@ template <int VEC, MoveDir DIR, int PARTS>
 __global__ __launch_bounds__(256) void move_rows_kernel(MoveRows<PARTS> a) {
     typedef typename MoveWord<VEC>::type word;
     __shared__ uint32_t s_row[MOVE_ROWS_MAX];
-    const MovePart& part = a.part[PARTS > 1 ? blockIdx.y : 0u];
-    const uint32_t r0 = blockIdx.x * a.rows_per_block;           // < m: the grid covers m rows exactly
+    // Where one part's columns end inside a line of the caller's rows, the parts of some rows are blocks that follow each
+    // other on one die (blocks go to the eight in turn): the line is still in that die's L2 when the next part's are written.
+    // (130 000 rows of five parts of 60 columns one part after the other 94 us, this way 71; where parts end with their
+    // lines, 200 000 rows of four of 32, 39 and 41.)
+    const uint32_t which = PARTS > 1 ? (a.together ? blockIdx.x / 8 % a.parts : blockIdx.x / a.in_x) : 0u;
+    const uint32_t group_x = a.together ? blockIdx.x / (8 * a.parts) * 8 + blockIdx.x % 8 : blockIdx.x % a.in_x;
+    const uint64_t group = PARTS > 1 ? (uint64_t)blockIdx.y * MOVE_GROUPS + group_x : blockIdx.x;
+    const MovePart& part = a.part[which];
+    const uint64_t r0_64 = group * a.rows_per_block;
+    if (r0_64 >= a.m) return;                                    // (of several parts the grid is rounded up)
+    const uint32_t r0 = (uint32_t)r0_64;
     const uint32_t nr = min(a.rows_per_block, a.m - r0);
     for (uint32_t i = threadIdx.x; i < nr; i += 256) {
         uint32_t w = a.rows[r0 + i];
@@ -131,6 +142,7 @@ static void launch_move_rows(const RowPart* parts, uint32_t S, float* ext, uint3
     uint32_t mix = pitch | (uint32_t)((uintptr_t)ext / 4), width = 0;
     for (uint32_t s = 0; s < S; ++s) {
         mix |= parts[s].width | parts[s].col;
+        a.together |= (parts[s].col | pitch | (uint32_t)((uintptr_t)ext / 4)) % 32 != 0;
         width = std::max(width, parts[s].width);
     }
     const uint32_t vec = (uintptr_t)ext % 4 ? 1 : (mix % 4 == 0 ? 4 : (mix % 2 == 0 ? 2 : 1));
@@ -145,8 +157,10 @@ static void launch_move_rows(const RowPart* parts, uint32_t S, float* ext, uint3
     const uint32_t most = std::min((uint32_t)MOVE_ROWS_MAX, std::max(1u, 256u * MOVE_ITEMS / dv_max));
     const uint32_t least = std::min(most, std::max(1u, 256u / dv_max));
     const uint32_t rb = std::min(most, std::max(least, (uint32_t)((uint64_t)m * S / 2048u)));
-    a.rows_per_block = rb;
-    const dim3 grid(blocks_for(m, rb), S), block(256);
+    a.rows_per_block = rb; a.parts = S;
+    const uint32_t groups = blocks_for(m, rb), in_x = std::min(a.together ? (groups + 7) / 8 * 8 : groups, MOVE_GROUPS);
+    a.in_x = in_x;
+    const dim3 grid(PARTS > 1 ? in_x * S : groups, PARTS > 1 ? blocks_for(groups, in_x) : 1u), block(256);
     if (vec == 4) hipLaunchKernelGGL((move_rows_kernel<4, DIR, PARTS>), grid, block, 0, st, a);
     else if (vec == 2) hipLaunchKernelGGL((move_rows_kernel<2, DIR, PARTS>), grid, block, 0, st, a);
     else hipLaunchKernelGGL((move_rows_kernel<1, DIR, PARTS>), grid, block, 0, st, a);

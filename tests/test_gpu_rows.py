@@ -59,3 +59,23 @@ def test_export_joins_slices_of_any_alignment(widths):
     assert np.array_equal(w2v.export_rows(shards, 1, dev(rows)).cpu().numpy(), want)
     odd = torch.zeros(rows.size * total + 1, device="cuda")[1:].view(rows.size, total)
     assert np.array_equal(w2v.export_rows(shards, 1, dev(rows), out=odd).cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("widths,m", [((60,) * 5, 1), ((60,) * 5, 273), ((1, 7), 8 * 256 + 1), ((4,) * 32, 4099), ((32,) * 4, 5001),
+                                      ((512, 512), (1 << 18) * 16 + 5)])
+def test_export_at_the_edges_of_the_grid(widths, m):
+    """Blocks of several parts' rows in groups of eight, the last one not full; past 2^18 of them in a second row of the grid."""
+    print("export", widths, m, flush=True)
+    V, total = 64, sum(widths)
+    shards, col = [], 0
+    for w in widths:
+        shards.append(w2v.Shard(V, w, 5, d_total=total, col_begin=col, init_mode=1))
+        col += w
+    table = torch.from_numpy(oracle.init_rows(5, total, 0, total, 0, np.arange(V, dtype=np.uint32))).cuda()
+    rows = torch.randint(0, V, (m,), dtype=torch.int32, device="cuda", generator=torch.Generator(device="cuda").manual_seed(m))
+    got = w2v.export_rows(shards, 0, rows)
+    for lo in range(0, m, 1 << 18):
+        assert torch.equal(got[lo:lo + (1 << 18)], table[rows[lo:lo + (1 << 18)].long()])
+    for sh in shards:
+        sh.status()
+        sh.destroy()
