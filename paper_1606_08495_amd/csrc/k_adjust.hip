@@ -142,7 +142,7 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32
     constexpr int ROW4 = G * NV;                          // float4 of a row held in LDS
     auto& s_raw = lds.raw; auto& s_list = lds.list; auto& s_rows = lds.rows; auto& s_gkey = lds.gkey;
     const float alpha = a.alpha;
-    const int l = threadIdx.x % G, grp = threadIdx.x / G;
+    const int l = threadIdx.x % G, grp = (int)group_value<G>(threadIdx.x / G);
     const uint32_t base = vb * (uint32_t)CB, count = min((uint32_t)CB, a.entries - base);
     const bool more = base + CB < a.entries;              // a block follows
     const uint32_t d4 = a.g.d4;
@@ -181,7 +181,7 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32
                 out[v].z = fmaf(alpha, acc[v].z, old[v].z);
                 out[v].w = fmaf(alpha, acc[v].w, old[v].w);
             }
-            dst.store(key, out);
+            dst.store_part(key, out);
         }
     };
     // ---- each group's part ----
@@ -209,32 +209,67 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32
     float4 acc[NV];
     clear<NV>(acc);
     if (listed) {
-        float4 srcv[D][NV], dstv[D][NV];
-        auto fetch = [&](int idx, float4 (&sv)[NV], float4 (&dv)[NV]) {
-            const uint32_t f = idx < listed ? s_list[grp][idx] : 0u;
-            const bool cm = !DEFER && (f & TL_COMPLETE);
-            const uint32_t i = f & TL_POS;
-            load_row_if<G, NV>((f & TL_HAS) != 0, a.src + (uint64_t)(base + i) * s4, d4, l, sv);
-            if (!DEFER) dst.load_if(cm, cm ? K((int)i) : 0u, dv);
-        };
+        // Rows of two float4 a lane and more: all loads of a batch, then its sums (first level of a 2^20-pair
+        // minibatch of 300 columns 76 -> 60 us, the second 39 -> 29).  One: most shares are a batch, asked for at once, zeros
+        // where there is nothing; the other way 2^20 pairs of 60 columns 24 -> 30 us, 2^18 of 200 33 -> 36.
+        if constexpr (NV >= 2) {
+            for (int b = 0; b < listed; b += D) {             // (all loads of a batch, then its sums)
+                float4 srcv[D][NV], dstv[D][NV];
+                uint32_t f[D];
 #pragma unroll
-        for (int t = 0; t < D; ++t) fetch(t, srcv[t], dstv[t]);
-        for (int b = 0; b < listed; b += D) {
+                for (int t = 0; t < D; ++t) f[t] = group_value<G>(s_list[grp][min(b + t, listed - 1)]);
 #pragma unroll
-            for (int t = 0; t < D; ++t) {
-                if (b + t < listed) {
-                    const uint32_t f = s_list[grp][b + t], i = f & TL_POS;
-                    if (f & TL_HAS) axpy<NV>(1.0f, srcv[t], acc);
-                    if (f & TL_COMPLETE) {
-                        finish(K((int)i), base + i, acc, dstv[t]);
-                        clear<NV>(acc);
-                    } else if (f & TL_HEAD) {             // came in from the part before and ends here
-                        store_row<G, NV>(&s_rows[2 * grp][0], ROW4, l, acc);
-                        if (l == 0) s_gkey[2 * grp] = K((int)i);
-                        clear<NV>(acc);
+                for (int t = 0; t < D; ++t)
+                    if (b + t < listed && (f[t] & TL_HAS)) load_part<G, NV>(a.src + (uint64_t)(base + (f[t] & TL_POS)) * s4, d4, l, srcv[t]);
+                if (!DEFER) {
+#pragma unroll
+                    for (int t = 0; t < D; ++t)
+                        if (b + t < listed && (f[t] & TL_COMPLETE)) dst.template load_part<false>(K((int)(f[t] & TL_POS)), dstv[t]);
+                }
+#pragma unroll
+                for (int t = 0; t < D; ++t) {
+                    if (b + t < listed) {
+                        const uint32_t i = f[t] & TL_POS;
+                        if (f[t] & TL_HAS) axpy<NV>(1.0f, srcv[t], acc);
+                        if (f[t] & TL_COMPLETE) {
+                            finish(K((int)i), base + i, acc, dstv[t]);
+                            clear<NV>(acc);
+                        } else if (f[t] & TL_HEAD) {          // came in from the part before and ends here
+                            store_row<G, NV>(&s_rows[2 * grp][0], ROW4, l, acc);
+                            if (l == 0) s_gkey[2 * grp] = K((int)i);
+                            clear<NV>(acc);
+                        }
                     }
                 }
-                if (b + D < listed) fetch(b + t + D, srcv[t], dstv[t]);
+            }
+        } else {
+            float4 srcv[D][NV], dstv[D][NV];
+            auto fetch = [&](int idx, float4 (&sv)[NV], float4 (&dv)[NV]) {
+                const uint32_t f = idx < listed ? s_list[grp][idx] : 0u;
+                const bool cm = !DEFER && (f & TL_COMPLETE);
+                const uint32_t i = f & TL_POS;
+                load_row_if<G, NV>((f & TL_HAS) != 0, a.src + (uint64_t)(base + i) * s4, d4, l, sv);
+                if (!DEFER) dst.load_if(cm, cm ? K((int)i) : 0u, dv);
+            };
+#pragma unroll
+            for (int t = 0; t < D; ++t) fetch(t, srcv[t], dstv[t]);
+            for (int b = 0; b < listed; b += D) {
+#pragma unroll
+                for (int t = 0; t < D; ++t) {
+                    if (b + t < listed) {
+                        const uint32_t f = s_list[grp][b + t], i = f & TL_POS;
+                        if (f & TL_HAS) axpy<NV>(1.0f, srcv[t], acc);
+                        if (f & TL_COMPLETE) {
+                            finish(K((int)i), base + i, acc, dstv[t]);
+                            clear<NV>(acc);
+                        } else if (f & TL_HEAD) {             // came in from the part before and ends here
+                            store_row<G, NV>(&s_rows[2 * grp][0], ROW4, l, acc);
+                            if (l == 0) s_gkey[2 * grp] = K((int)i);
+                            clear<NV>(acc);
+                        }
+                    }
+                    if (b + D < listed) fetch(b + t + D, srcv[t], dstv[t]);
+                }
             }
         }
         const uint32_t last = K(e0 + n_part - 1);
@@ -256,7 +291,7 @@ __device__ __forceinline__ void tail_body(const SegArgs& a, const SL& sl, uint32
         if (k == KEY_MASK || (raw0 & KEY_ZERO)) continue; // (flagged: the run began earlier)
         const bool came_in = block_before == k;
         float4 old[NV];
-        if (!DEFER) dst.load_if(!came_in, k, old);
+        if (!DEFER && !came_in) dst.template load_part<false>(k, old);
         clear<NV>(acc);
         int i = start;
         uint32_t raw = raw0, next;

@@ -30,6 +30,16 @@ __device__ __forceinline__ void load_row_if(bool on, const float4* __restrict__ 
     }
 }
 
+// The same where this lane holds a part of the row; what r holds elsewhere is left as it is.
+template <int G, int NV>
+__device__ __forceinline__ void load_part(const float4* __restrict__ row, uint32_t d4, int l, float4 (&r)[NV]) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) {
+        const uint32_t i = (uint32_t)l + (uint32_t)(G * v);
+        if (v + 1 < NV || i < d4) r[v] = row[i];
+    }
+}
+
 typedef float v4f __attribute__((ext_vector_type(4)));
 
 // The same with the non-temporal hint: rows that are touched once per minibatch and should not
@@ -143,6 +153,10 @@ template <int G, int NV, int WHICH> struct Rows<G, NV, OneMatrix, WHICH> {
         if (!has(NV - 1)) r[NV - 1] = f4zero();
         store_nt(row, r);
     }
+    __device__ __forceinline__ void store_part(uint32_t row, float4 (&r)[NV]) const {
+        if (!has(NV - 1)) r[NV - 1] = f4zero();
+        store(row, r);
+    }
     __device__ __forceinline__ void store(uint32_t row, const float4 (&r)[NV]) const {
         store_row<G, NV>(M + (uint64_t)row * s4, (uint32_t)s4, l, r);
     }
@@ -209,6 +223,12 @@ template <int G, int NV, int WHICH> struct Rows<G, NV, SliceArgs, WHICH> {
         for (int v = 0; v < NV; ++v)
             if (!data[v]) r[v] = f4zero();
         store_nt(row, r);
+    }
+    __device__ __forceinline__ void store_part(uint32_t row, float4 (&r)[NV]) const {
+#pragma unroll
+        for (int v = 0; v < NV; ++v)
+            if (!data[v]) r[v] = f4zero();
+        store(row, r);
     }
     __device__ __forceinline__ void load_nt_if(bool on, uint32_t row, float4 (&r)[NV]) const {
 #pragma unroll
