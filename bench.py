@@ -27,7 +27,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 # the row kernel that makes up a timed phase (names as rocprofv3 lists them)
-KERNEL_OF_PHASE = {"wside": "wown_kernel", "uside": "useg_multi_kernel / useg_kernel", "dot": "dots_kernel",
+KERNEL_OF_PHASE = {"wside": "wown_kernel", "uside": "useg_kernel", "dot": "dots_kernel",
                    "apply": "wown_kernel (input side)"}
 
 
