@@ -767,6 +767,14 @@ extern "C" int w2v_shard_create_ex(uint32_t V, uint32_t d_total, uint32_t col_be
     return W2V_OK;
 }
 
+namespace w2v {
+// Where a shard's matrix lies and how many floats apart its rows are: for checks of what a call leaves in the padding.
+const float* shard_rows(const w2v_shard* sh, int which, uint32_t* stride) {
+    *stride = sh->g.stride4 * 4;
+    return which ? sh->W : sh->U;
+}
+}  // namespace w2v
+
 extern "C" int w2v_shard_create(uint32_t V, uint32_t d_slice, uint64_t seed, w2v_shard** out) {
     return w2v_shard_create_ex(V, d_slice, 0, d_slice, seed, 0, out);
 }

@@ -654,7 +654,7 @@ __device__ __forceinline__ void apply_body(const ApplyArgs& a, const SL& sl, uin
         for (int t = 0; t < D; ++t) {
             if (key[t] == KEY_NONE) continue;
             axpy<NV>(alpha, dv[t], uv[t]);
-            U.store(key[t], uv[t]);
+            U.store_part(key[t], uv[t]);       // (joint rows: dv holds anything where U has its padding)
         }
     }
 }
@@ -894,7 +894,8 @@ __global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FULL == ONE_BATCH ? (SL::O
     uint32_t head_key = KEY_NONE, tail_key = KEY_NONE;
     const uint32_t head_slot = 2 * c - 1, tail_slot = 2 * c;
 
-    // (what the lanes past a row's end hold is never stored)
+    // (what the lanes past a row's end hold is not stored; of joint rows the padding between slices is, in the delta buffer and
+    // the partial slots, and left out when a row is written back)
     float4 acc[NV];
     clear<NV>(acc);
     float4 w[TB][NV], u[1][NV], un[NV];

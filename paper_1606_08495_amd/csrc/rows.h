@@ -96,7 +96,7 @@ template <int N, class F> __device__ __forceinline__ void unrolled(F f) { unroll
 
 // This lane's part of the rows of a matrix (WHICH: 0 input, 1 output vectors): of one matrix, or of the slices of
 // several shards.  Of slices a lane keeps an address and a stride for each of its float4, as they may lie in
-// different matrices.  store() writes the whole stride of a row, the pad as zeros.
+// different matrices.  store_part() writes the whole stride of a row, the pad as zeros.
 struct OneMatrix { static constexpr bool ONE = true; };
 struct SliceArgs : Slices { static constexpr bool ONE = false; };
 template <int G, int NV, class SL, int WHICH> struct Rows;

@@ -1,5 +1,7 @@
 """Several column shards trained in one process as one matrix of joint rows, against the same step through
 dotprod, coefficients and adjust of each shard, and against the oracle."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -166,4 +168,37 @@ def test_a_captured_step_over_shards_grows_nothing():
             for which in (0, 1):
                 assert vec_error(all_rows(x, which), all_rows(y, which)) <= (replay + 1) * TOL
     for s in sets[0] + sets[1]:
+        s.destroy()
+
+
+class Rows:
+    """All of a shard's matrix as it lies in memory, padding included (a host function, by its linker name)."""
+    def __init__(self, shard, which):
+        fn = ctypes.CDLL(w2v.LIB_PATH)._ZN3w2v10shard_rowsEPK9w2v_shardiPj
+        fn.restype, fn.argtypes = ctypes.c_void_p, [ctypes.c_void_p, ctypes.c_int, ctypes.POINTER(ctypes.c_uint32)]
+        stride = ctypes.c_uint32()
+        at = fn(shard.h, which, ctypes.byref(stride))
+        self.__cuda_array_interface__ = dict(shape=(shard.V, stride.value), typestr="<f4", data=(at, False), version=2)
+
+
+# up to four float4 a lane, padding of a whole float4 and of parts of one; the last: the write-back has a launch of its own
+@pytest.mark.parametrize("widths,n,k", [([60] * 5, 3001, 5), ([60] * 16, 400, 5), ([30, 30], 999, 5), ([27, 59, 122], 1500, 3),
+                                        ([58, 300], 700, 12), ([60, 60], 300_000, 5), ([300, 300], 180_000, 5)])
+def test_padding_stays_zero(widths, n, k):
+    """Matrices are written in whole strides; a step over several shards holds anything in the lanes of the padding."""
+    print("padding", widths, n, k, flush=True)
+    V, d = 3000, sum(widths)
+    counts = zipf_counts(V)
+    rng = np.random.default_rng(n)
+    begins = np.concatenate([[0], np.cumsum(widths)[:-1]])
+    shards = [make_shard(V, w, 5, counts, d_total=d, col_begin=int(b)) for w, b in zip(widths, begins)]
+    views = [torch.as_tensor(Rows(s, which), device="cuda")[:, w:] for s, w in zip(shards, widths) for which in (0, 1)]
+    assert any(v.shape[1] for v in views)
+    for h in range(3):
+        a, b = dev(np.minimum(rng.zipf(1.3, n), V) - 1), dev(rng.integers(0, V, n))
+        w2v.train_minibatch(shards, a, b, k, 70 + h, 1e-4)
+        for s in shards:
+            s.status()
+        assert all(bool((v.view(torch.int32) == 0).all()) for v in views), h
+    for s in shards:
         s.destroy()
