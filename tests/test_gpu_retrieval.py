@@ -88,21 +88,6 @@ def test_topk_parity(Q, N, d, K, tau):
             assert np.array_equal(gi, ref[0]) and np.array_equal(gs, ref[1]) and np.array_equal(gc, ref[2])
 
 
-@pytest.mark.parametrize("d", [1, 3, 4, 28, 31, 32, 33, 36, 61, 64, 65, 100, 255, 257])
-def test_topk_folds_of_one_four_and_eight_wavefronts_agree(d):
-    """The fold reads rows 32 columns at a time, whole or in part, as one access of four columns or four: widths on either
-    side; by one wavefront a query, by four, and by eight from bits.  A similarity has the same bits in all."""
-    say("fold", d)
-    K, N = 30, 6000
-    Qm = workloads.embedding_like(1024, d, 11, n_clusters=40)
-    C = workloads.embedding_like(N, d, 12, n_clusters=40)
-    one = run_gpu(Qm, C, K, -2.0, 1024)
-    check_topk(Qm[:40], C, K, -2.0, *(x[:40] for x in one))
-    for Q in (1023, 9):
-        for a, b in zip(one, run_gpu(Qm[:Q], C, K, -2.0, 1024)):
-            assert np.array_equal(a[:Q], b), Q
-
-
 def test_topk_equal_similarities_rank_by_index_and_zero_vectors_score_zero():
     rng = np.random.default_rng(3)
     N, d, K = 2000, 60, 40
@@ -244,6 +229,32 @@ def test_screens_list_every_pair_that_counts(Q, N, d):
     screens_agree(Qm, C, 64, 0.2)
 
 
+# a fold's wavefronts read rows 32 columns at a time, whole or in part, four columns to an access or one
+@pytest.mark.parametrize("d", [1, 3, 4, 12, 16, 17, 28, 31, 32, 33, 36, 61, 64, 65, 100, 255, 257])
+@pytest.mark.parametrize("tau", [-2.0, 0.02])
+def test_topk_folds_agree(d, tau):
+    """How many wavefronts fold a list, or the bits of a few queries, goes by the number of queries: a
+    similarity has the same bits in all.  Similarities rise with the index, so that lists are longer than a wavefront; with
+    a threshold no round is formed in fp32, without one the first."""
+    say("fold", d, tau)
+    K, N = 30, 6000
+    rng = np.random.default_rng(d)
+    base = 1.0 + rng.random(d)
+    Qm = (base + 0.1 * rng.standard_normal((4096, d))).astype(np.float32)
+    C = (base + np.linspace(8.0, 0.3, N)[:, None] * rng.standard_normal((N, d))).astype(np.float32)
+    C[-50:-25] = C[-25:]                                       # equal similarities, ranked by index
+    c, first = torch.from_numpy(C).cuda(), None
+    for Q in (4096, 4095, 1024, 1023, 300, 9):
+        nbytes = int(w2v.lib().w2v_topk_cosine_workspace(Q, N, 0)) + (Q + N + 512) * (2 * d + 128) + 32768 * Q
+        assert screen_of(Q, N, d, nbytes) == (2 if Q > 256 else 1)
+        ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
+        got = [t.cpu().numpy() for t in w2v.topk_cosine(torch.from_numpy(Qm[:Q]).cuda(), c, K, tau, workspace=ws)]
+        if first is None:
+            first = got
+            check_topk(Qm[:40], C, K, tau, got[0][:40].view(np.uint32), got[1][:40], got[2][:40])
+        assert all(np.array_equal(a[:Q].view(np.uint32), b.view(np.uint32)) for a, b in zip(first, got)), Q
+
+
 @pytest.mark.parametrize("Q,N", [(7, 9000), (7, 40_000), (200, 9000), (500, 9000)])
 @pytest.mark.parametrize("spread", [0.0, 1e-4, 1e-2])
 def test_crowded_similarities(Q, N, spread):
@@ -280,14 +291,15 @@ def test_crowded_rounds_stay_counted(Q, N, d):
 
 
 # rounds of 1024, 16 384 and the rest: of one block to a query, of two to sixteen; past 32 queries a block for every 32 768
-# candidates, past 128 of four wavefronts
-@pytest.mark.parametrize("Q,N", [(1, 120_000), (7, 34_000), (31, 1 << 18), (128, 120_000), (129, 120_000), (256, 120_001)])
-def test_long_rounds_of_rising_similarities(Q, N):
+# candidates
+@pytest.mark.parametrize("Q,N,d", [(1, 120_000, 12), (7, 34_000, 12), (31, 1 << 18, 12), (128, 120_000, 12), (129, 120_000, 12),
+                                   (256, 120_001, 12), (1, 120_000, 36), (31, 120_000, 37), (100, 120_000, 40), (200, 120_000, 33)])
+def test_long_rounds_of_rising_similarities(Q, N, d):
     """Nearly all of a round passes the thresholds of the one before: its candidates are shared by several blocks."""
-    say("rising", Q, N)
+    say("rising", Q, N, d)
     rng = np.random.default_rng(9)
-    Qm = (rng.standard_normal(12) + 0.02 * rng.standard_normal((Q, 12))).astype(np.float32)
-    C = (Qm[0] + np.linspace(3.0, 0.05, N)[:, None] * rng.standard_normal((N, 12))).astype(np.float32)
+    Qm = (rng.standard_normal(d) + 0.02 * rng.standard_normal((Q, d))).astype(np.float32)
+    C = (Qm[0] + np.linspace(3.0, 0.05, N)[:, None] * rng.standard_normal((N, d))).astype(np.float32)
     C[-50:-25] = C[-25:]                                       # equal similarities, ranked by index
     gi, _, gc = screens_agree(Qm, C, 30, -2.0)
     assert gi.min() > N // 2 and np.all(gc == 30)
