@@ -915,7 +915,8 @@ __device__ __forceinline__ float wave_scores(const float* __restrict__ q, const 
 }
 
 // The same by one lane from memory: of rows that are no multiple of four columns, and long, a block of sixteen wavefronts does
-// better that way than of eight through LDS (19 queries over 18 030 x 495 194 us, 207; 8 over 3249 x 51 54.9, 50.7).
+// better that way than of eight through LDS (19 queries over 18 030 x 495 194 us, 207; 8 over 3249 x 51 54.9, 50.7).  So do
+// rows of a line or less, which a lane reads in one or two lines anyway (fold_by_lane).
 template <bool VEC4>
 __device__ __forceinline__ float exact_score(const float* __restrict__ q, const float* __restrict__ c, uint32_t d,
                                              float iq) {
@@ -943,6 +944,14 @@ __device__ __forceinline__ float exact_score(const float* __restrict__ q, const 
 }
 
 constexpr uint32_t FOLD_LONG_ROW = 256;
+// Rows that lanes read on their own: of bits by sixteen wavefronts up to TK_STREAM_Q queries, eight past that, of a list by four.
+// Searches of 200 000 rows, us, this way and through LDS, by columns: 100 queries 7: 86, 95, 13: 96, 97, 17: 102, 98; 16: 78, 84,
+// 40: 91, 91, 52: 100, 92; 129 queries 21: 127, 117; 56, crowded, 646, 543; 200 queries 7: 116, 127; 40: 114, 122.  600 queries 7: 233, 249,
+// 27: 255, 259; 16: 266, 267, 56: 268, 264.  Where similarities rise with the index the lines would lie higher: 100 of 17 315, 420;
+// 300 of 60 1210, 1310.
+static bool fold_by_lane(bool bits, uint32_t d, bool vec4) {
+    return d <= (bits ? (vec4 ? 40u : 16u) : (vec4 ? 48u : 24u));
+}
 constexpr uint32_t FOLD_PICK = 2048;             // candidates named by bits that a block lists before it scores them
 constexpr uint32_t FOLD_CHUNK = 16;              // words: where they are more
 // candidates of a round for every block of a query (a block more costs what it takes to count: 100 queries over 200 003 x
@@ -1357,8 +1366,13 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
                        dim3(64 * WAVES), 0, st, a, K, tau, best, best_cnt, theta, oi, out_score, out_count)
         for (a.q_first = 0; a.q_first < Q; a.q_first += TK_FOLD_SLICE) {
             if (exact_round) W2V_FOLD(4, false, FOLD_SCORED);
+            else if (!bits && fold_by_lane(bits, d, vec4)) { if (vec4) W2V_FOLD(4, true, FOLD_LIST, true); else W2V_FOLD(4, false, FOLD_LIST, true); }
             else if (!bits && Q >= FOLD_ALONE_Q) { if (vec4) W2V_FOLD(1, true, FOLD_LIST); else W2V_FOLD(1, false, FOLD_LIST); }
             else if (!bits) { if (vec4) W2V_FOLD(4, true, FOLD_LIST); else W2V_FOLD(4, false, FOLD_LIST); }
+            else if (fold_by_lane(bits, d, vec4)) {
+                if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(8, true, FOLD_BITS, true); else W2V_FOLD(8, false, FOLD_BITS, true); }
+                else { if (vec4) W2V_FOLD(16, true, FOLD_BITS, true); else W2V_FOLD(16, false, FOLD_BITS, true); }
+            }
             else if (vec4) W2V_FOLD(8, true, FOLD_BITS);
             else if (d > FOLD_LONG_ROW && Q <= TK_STREAM_Q) W2V_FOLD(16, false, FOLD_BITS, true);
             else W2V_FOLD(8, false, FOLD_BITS);

@@ -229,8 +229,9 @@ def test_screens_list_every_pair_that_counts(Q, N, d):
     screens_agree(Qm, C, 64, 0.2)
 
 
-# a fold's wavefronts read rows 32 columns at a time, whole or in part, four columns to an access or one
-@pytest.mark.parametrize("d", [1, 3, 4, 12, 16, 17, 28, 31, 32, 33, 36, 61, 64, 65, 100, 255, 257])
+# a fold's wavefronts read rows 32 columns at a time, whole or in part, four columns to an access or one; lanes read rows of up to
+# 16 (of four to an access 40) columns on their own, of a list up to 24 (48)
+@pytest.mark.parametrize("d", [1, 3, 4, 12, 16, 17, 24, 25, 28, 31, 32, 33, 36, 40, 44, 48, 52, 61, 64, 65, 100, 255, 257])
 @pytest.mark.parametrize("tau", [-2.0, 0.02])
 def test_topk_folds_agree(d, tau):
     """How many wavefronts fold a list, or the bits of a few queries, goes by the number of queries: a
@@ -293,7 +294,8 @@ def test_crowded_rounds_stay_counted(Q, N, d):
 # rounds of 1024, 16 384 and the rest: of one block to a query, of two to sixteen; past 32 queries a block for every 32 768
 # candidates
 @pytest.mark.parametrize("Q,N,d", [(1, 120_000, 12), (7, 34_000, 12), (31, 1 << 18, 12), (128, 120_000, 12), (129, 120_000, 12),
-                                   (256, 120_001, 12), (1, 120_000, 36), (31, 120_000, 37), (100, 120_000, 40), (200, 120_000, 33)])
+                                   (256, 120_001, 12), (129, 120_000, 13), (1, 120_000, 44), (31, 120_000, 37), (100, 120_000, 52),
+                                   (200, 120_000, 33)])
 def test_long_rounds_of_rising_similarities(Q, N, d):
     """Nearly all of a round passes the thresholds of the one before: its candidates are shared by several blocks."""
     say("rising", Q, N, d)
