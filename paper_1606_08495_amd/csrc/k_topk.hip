@@ -958,10 +958,12 @@ constexpr uint32_t FOLD_CHUNK = 16;              // words: where they are more
 // 100, not crowded, 116.6 us, in five blocks each 116.9, and two in the round before 117.2)
 static uint32_t fold_share(uint32_t Q) { return Q <= 32 ? 1u << 13 : 1u << 15; }
 constexpr uint32_t FOLD_WORDS = 8;           // of a thread, in flight
-// Queries from which one wavefront folds a list: most lists fill one, and what LDS a block asks for says how many are on
-// the chip (4096 queries over 2^20 x 300, a round, by one, two and four wavefronts 15, 21, 34 us).  Of fewer queries a long list
-// costs more than that (600 over 200 000 x 7, crowded, the search by two and four wavefronts 325, 300 us; 300, 307 and 278).
-constexpr uint32_t FOLD_ALONE_Q = 1024;
+// Queries from which two wavefronts fold a list, and one: most lists fill one, and what LDS a block asks for says how many
+// are on the chip; long lists want the chip filled.  Searches, us, by one, two and four wavefronts: 4096 over 2^20 x 300 4497, 4552,
+// 4720; over 200 000 rows 2500 x 99 652, 682, - (x 60, crowded, 1042, 1020, -); 2000 x 60 432, 430, 438 (crowded 886, 859, 860); 1024 x 99 457, 432,
+// 449, x 300 620, 594, 579; 600 x 300 571, -, 508.  Where similarities rise with the index, and last by four without LDS: 1024 x 100
+// 6817, 4208, 3463, 4837; 2000 x 100 8778, 6686, 6559, 11 170; 3000 x 255 33.1 ms, 44.8, 44.7, 170.
+constexpr uint32_t FOLD_PAIR_Q = 1024, FOLD_ALONE_Q = 2048;
 enum FoldFrom { FOLD_LIST, FOLD_SCORED, FOLD_BITS };
 template <int WAVES, bool VEC4, FoldFrom FROM, bool BY_LANE = false>
 __global__ __launch_bounds__(64 * WAVES) void topk_fold_kernel(TopkArgs a, uint32_t K, float tau,
@@ -1368,6 +1370,7 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
             if (exact_round) W2V_FOLD(4, false, FOLD_SCORED);
             else if (!bits && fold_by_lane(bits, d, vec4)) { if (vec4) W2V_FOLD(4, true, FOLD_LIST, true); else W2V_FOLD(4, false, FOLD_LIST, true); }
             else if (!bits && Q >= FOLD_ALONE_Q) { if (vec4) W2V_FOLD(1, true, FOLD_LIST); else W2V_FOLD(1, false, FOLD_LIST); }
+            else if (!bits && Q >= FOLD_PAIR_Q) { if (vec4) W2V_FOLD(2, true, FOLD_LIST); else W2V_FOLD(2, false, FOLD_LIST); }
             else if (!bits) { if (vec4) W2V_FOLD(4, true, FOLD_LIST); else W2V_FOLD(4, false, FOLD_LIST); }
             else if (fold_by_lane(bits, d, vec4)) {
                 if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(8, true, FOLD_BITS, true); else W2V_FOLD(8, false, FOLD_BITS, true); }

@@ -241,11 +241,11 @@ def test_topk_folds_agree(d, tau):
     K, N = 30, 6000
     rng = np.random.default_rng(d)
     base = 1.0 + rng.random(d)
-    Qm = (base + 0.1 * rng.standard_normal((4096, d))).astype(np.float32)
+    Qm = (base + 0.1 * rng.standard_normal((2048, d))).astype(np.float32)
     C = (base + np.linspace(8.0, 0.3, N)[:, None] * rng.standard_normal((N, d))).astype(np.float32)
     C[-50:-25] = C[-25:]                                       # equal similarities, ranked by index
     c, first = torch.from_numpy(C).cuda(), None
-    for Q in (4096, 4095, 1024, 1023, 300, 9):
+    for Q in (2048, 2047, 1024, 1023, 300, 9):
         nbytes = int(w2v.lib().w2v_topk_cosine_workspace(Q, N, 0)) + (Q + N + 512) * (2 * d + 128) + 32768 * Q
         assert screen_of(Q, N, d, nbytes) == (2 if Q > 256 else 1)
         ws = torch.empty(nbytes, dtype=torch.uint8, device="cuda")
