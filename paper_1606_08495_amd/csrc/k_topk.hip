@@ -914,9 +914,8 @@ __device__ __forceinline__ float wave_scores(const float* __restrict__ q, const 
     return dot * iq * inv_length(tree8(lo) + tree8(hi));
 }
 
-// The same by one lane from memory: of rows that are no multiple of four columns, and long, a block of sixteen wavefronts does
-// better that way than of eight through LDS (19 queries over 18 030 x 495 194 us, 207; 8 over 3249 x 51 54.9, 50.7).  So do
-// rows of a line or less, which a lane reads in one or two lines anyway (fold_by_lane).
+// The same by one lane from memory: rows of a line or two (fold_by_lane), and long ones, no multiple of four columns, of which few
+// are asked for (fold_few).
 template <bool VEC4>
 __device__ __forceinline__ float exact_score(const float* __restrict__ q, const float* __restrict__ c, uint32_t d,
                                              float iq) {
@@ -943,7 +942,6 @@ __device__ __forceinline__ float exact_score(const float* __restrict__ q, const 
     return dot * iq * inv_length(tree8(lo) + tree8(hi));
 }
 
-constexpr uint32_t FOLD_LONG_ROW = 256;
 // Rows that lanes read on their own: of bits by sixteen wavefronts up to TK_STREAM_Q queries, eight past that, of a list by four.
 // Searches of 200 000 rows, us, this way and through LDS, by columns: 100 queries 7: 86, 95, 13: 96, 97, 17: 102, 98; 16: 78, 84,
 // 40: 91, 91, 52: 100, 92; 129 queries 21: 127, 117; 56, crowded, 646, 543; 200 queries 7: 116, 127; 40: 114, 122.  600 queries 7: 233, 249,
@@ -951,6 +949,15 @@ constexpr uint32_t FOLD_LONG_ROW = 256;
 // 300 of 60 1210, 1310.
 static bool fold_by_lane(bool bits, uint32_t d, bool vec4) {
     return d <= (bits ? (vec4 ? 40u : 16u) : (vec4 ? 48u : 24u));
+}
+// Whether so few candidates are expected that lanes read rows on their own, sixteen wavefronts to a query: as long as their lines
+// fit the L1 that is faster than four bytes at a time through LDS.  `passing`: candidates of the round times the
+// share that the thresholds let through.  The first round has only tau to go by.  Searches, us, this way throughout, by this rule and through LDS
+// throughout: 1 query over 18 030 x 511, K = 1, tau = 0.3: 168, 168, 202; 19 over 5000 x 495, K = 10, tau = 0.65 138, 138, 169; 100 over
+// 100 000 x 301, K = 30, no tau 1190, 330, 330; limit 20, 50, 100, 200, 400 on K = 10 over 5000 to 400 000 x 511, geometric mean against this way
+// throughout 1.19, 1.24, 1.24, 1.00, 1.00; 1 over 100 000 x 65, K = 1, 69, 69, 64, x 99 81, 81, 84.
+static bool fold_few(uint32_t Q, uint32_t d, bool vec4, bool first, double passing, float tau) {
+    return !vec4 && d > 96 && Q <= TK_STREAM_Q && (first ? tau > 0.f : passing <= 100.);
 }
 constexpr uint32_t FOLD_PICK = 2048;             // candidates named by bits that a block lists before it scores them
 constexpr uint32_t FOLD_CHUNK = 16;              // words: where they are more
@@ -1376,9 +1383,8 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
                 if (Q > TK_STREAM_Q) { if (vec4) W2V_FOLD(8, true, FOLD_BITS, true); else W2V_FOLD(8, false, FOLD_BITS, true); }
                 else { if (vec4) W2V_FOLD(16, true, FOLD_BITS, true); else W2V_FOLD(16, false, FOLD_BITS, true); }
             }
-            else if (vec4) W2V_FOLD(8, true, FOLD_BITS);
-            else if (d > FOLD_LONG_ROW && Q <= TK_STREAM_Q) W2V_FOLD(16, false, FOLD_BITS, true);
-            else W2V_FOLD(8, false, FOLD_BITS);
+            else if (fold_few(Q, d, vec4, begin == 0, share * m, tau)) W2V_FOLD(16, false, FOLD_BITS, true);
+            else { if (vec4) W2V_FOLD(8, true, FOLD_BITS); else W2V_FOLD(8, false, FOLD_BITS); }
         }
 #undef W2V_FOLD
     }

@@ -256,6 +256,16 @@ def test_topk_folds_agree(d, tau):
         assert all(np.array_equal(a[:Q].view(np.uint32), b.view(np.uint32)) for a, b in zip(first, got)), Q
 
 
+# long rows that are no multiple of four columns: lanes read them where few are expected (up to 128 queries, more than 96 columns,
+# up to 100 candidates of a round: (5000 - 1024) K / 1024 is 97 and 101 for K = 25 and 26, in the first round any threshold)
+@pytest.mark.parametrize("Q,d", [(3, 95), (3, 97), (128, 97), (129, 97), (3, 98), (3, 100), (40, 257), (1, 1001)])
+@pytest.mark.parametrize("K,tau", [(1, -2.0), (25, -2.0), (26, -2.0), (1, 0.3), (64, 0.3), (10, 0.65)])
+def test_few_candidates_of_long_rows(Q, d, K, tau):
+    say("few", Q, d, K, tau)
+    Qm, C = (workloads.embedding_like(n, d, seed, n_clusters=20) for n, seed in ((Q, 11), (5000, 12)))
+    screens_agree(Qm, C, K, tau)
+
+
 @pytest.mark.parametrize("Q,N", [(7, 9000), (7, 40_000), (200, 9000), (500, 9000)])
 @pytest.mark.parametrize("spread", [0.0, 1e-4, 1e-2])
 def test_crowded_similarities(Q, N, spread):
