@@ -830,20 +830,22 @@ __device__ __forceinline__ void coefficients(const float (&sdot)[N], uint32_t j0
 // batch before the first is waited for, one batch to a lane group, many lane groups.  (With a branch around each load the
 // compiler waits for all loads before it: the same kernel with one or two rows in flight.  Input side of a step, us, that
 // way and this: 4096 pairs of d = 100 10.8, 7.0; 65 536 58, 52; 100 003 pairs over five shards of 60 columns 182, 130.)
-// PIPED: a register set is refilled as soon as its row is used.  Only where a lane group is sixteen lanes and a batch nine rows
-// or more, in four wavefronts a SIMD: k = 10, 2^20 pairs of d = 60 729 us, batch by batch 779; d = 100, k = 10, 294 and 284; d = 200,
-// k = 25, 892 and 814.
-// FULL: pairs are whole batches, and no load stands behind a branch of its own; ONE_BATCH: of one batch.
-enum Batches { ANY_BATCH, FULL_BATCHES, ONE_BATCH };
-template <int G, int NV, int TB, Batches FULL, bool FUSED, bool OWN, class SL>
-__global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FULL == ONE_BATCH ? (SL::ONE ? 5 : 4) : 1) void useg_kernel(USideArgs a, uint32_t CP, SL sl) {
+// FULL_BATCHES: pairs are whole batches, and no load stands behind a branch of its own; ONE_BATCH: of one batch.
+// REFILLED: a register set is refilled as soon as its row is used, whole batches or not.  Worth it at sixteen and thirty-two lanes a row,
+// in four wavefronts a SIMD, us, batch by batch and refilled: k = 10, 2^20 pairs of d = 60 779, 705; 2^18 of d = 100 299, 280; k = 12, d = 128
+// 362, 326; k = 7, d = 100 234, 228; but 4096 pairs of d = 100, in chunks of two pairs, 13.9, 14.9, and d = 200, k = 25 538, 569.  (The number of
+// slots must stay a variable: as a constant, the refilled rows get registers of their own, are waited for and moved at the
+// batch's end, and three wavefronts fit instead of four: 729.)
+enum Batches { ANY_BATCH, FULL_BATCHES, ONE_BATCH, REFILLED };
+template <int G, int NV, int TB, Batches FORM, bool FUSED, bool OWN, class SL>
+__global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FORM == ONE_BATCH ? (SL::ONE ? 5 : 4) : 1) void useg_kernel(USideArgs a, uint32_t CP, SL sl) {
     constexpr bool NEED_U = FUSED || OWN;      // the pair's input row: for the dots, for own rows
-    constexpr bool PIPED = G == 16 && FULL != ONE_BATCH;
+    constexpr bool WHOLE = FORM == FULL_BATCHES || FORM == ONE_BATCH;
     const float alpha = a.alpha;
     constexpr int GROUPS = USEG_THREADS / G;
     // The chunk's indices are staged in LDS first (two dependent gathers for the whole chunk), so
     // that the row loads of the main loop depend on nothing but LDS reads.
-    constexpr int MAXP = useg_maxp(G), MAXE = FULL == ONE_BATCH ? MAXP * TB : useg_maxe(G);
+    constexpr int MAXP = useg_maxp(G), MAXE = FORM == ONE_BATCH ? MAXP * TB : useg_maxe(G);
     __shared__ uint32_t s_key[GROUPS][MAXE];                      // output row of every entry
     __shared__ float s_cf[FUSED ? 1 : GROUPS][FUSED ? 1 : MAXE];  // given coefficients
     __shared__ uint32_t s_pair[GROUPS][MAXP];                     // pair number of every sorted pair
@@ -854,7 +856,7 @@ __global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FULL == ONE_BATCH ? (SL::O
     const bool active = c < nchunks;
     const uint32_t ps0 = active ? c * CP : 0u;
     const uint32_t cnt = active ? min(CP, a.n - ps0) : 0u;
-    const uint32_t T = FULL == ONE_BATCH ? TB : a.T;
+    const uint32_t T = FORM == ONE_BATCH ? TB : a.T;
     // (the output side's border slots must be clear before its kernel: a share of them per block)
     for (uint32_t i = blockIdx.x * USEG_THREADS + threadIdx.x; i < a.clear_count; i += gridDim.x * USEG_THREADS)
         a.clear_keys[i] = KEY_NONE;
@@ -900,7 +902,7 @@ __global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FULL == ONE_BATCH ? (SL::O
     clear<NV>(acc);
     float4 w[TB][NV], u[1][NV], un[NV];
     uint32_t row[TB];
-    if (PIPED) {
+    if (FORM == REFILLED) {
 #pragma unroll
         for (int t = 0; t < TB; ++t) {
             row[t] = (uint32_t)t < T ? s_key[grp][t] : 0u;
@@ -911,24 +913,24 @@ __global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FULL == ONE_BATCH ? (SL::O
     for (uint32_t pi = 0; pi < cnt; ++pi) {
         const uint32_t p = s_pair[grp][pi];
         const uint32_t next = group_value<G>(s_skey[grp][pi + 2]);
-        if (PIPED && NEED_U) {                   // the next pair's input row, ahead of need
+        if (FORM == REFILLED && NEED_U) {                   // the next pair's input row, ahead of need
             if (pi + 1 < cnt) U.template load_part<false>(next, un);
         } else if (NEED_U) {
             const uint32_t in[1] = {key};
             U.template load_all<false>(in, 1u, u);
         }
         for (uint32_t jb = 0; jb < T; jb += TB) {
-            const uint32_t slots = FULL ? TB : min((uint32_t)TB, T - jb);
+            const uint32_t slots = WHOLE ? TB : min((uint32_t)TB, T - jb);
             const bool last_batch = jb + TB >= T;
             const uint32_t npi = last_batch ? pi + 1 : pi, njb = last_batch ? 0u : jb + TB;      // the batch that follows
-            if (!PIPED) {
+            if (FORM != REFILLED) {
 #pragma unroll
                 for (int t = 0; t < TB; ++t) row[t] = (uint32_t)t < slots ? group_value<G>(s_key[grp][pi * T + jb + t]) : 0u;
             }
             // a row that no other slot names is read here once and written once: the
             // non-temporal hint keeps it out of the caches' way (without it, step of 2^20 pairs of d = 300, this kernel
             // 1.98 ms, with it 1.73)
-            if (!PIPED) W.template load_all<OWN && G == 64>(row, slots, w);
+            if (FORM != REFILLED) W.template load_all<OWN && G == 64>(row, slots, w);
             float gco[TB];
             if (FUSED) {
                 float sdot[TB], f, g;
@@ -960,7 +962,7 @@ __global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FULL == ONE_BATCH ? (SL::O
                 }
                 W.store_part_nt(row[t] & ~ALONE, out);
             };
-            if (PIPED) {
+            if (FORM == REFILLED) {
 #pragma unroll
                 for (int t = 0; t < TB; ++t) {
                     if ((uint32_t)t < slots) axpy<NV>(gco[t], w[t], acc);
@@ -990,7 +992,7 @@ __global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FULL == ONE_BATCH ? (SL::O
             clear<NV>(acc);
             run_start = ps0 + pi + 1;
         }
-        if (PIPED && NEED_U) {
+        if (FORM == REFILLED && NEED_U) {
 #pragma unroll
             for (int v = 0; v < NV; ++v) u[0][v] = un[v];
         }
@@ -1013,14 +1015,27 @@ __global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FULL == ONE_BATCH ? (SL::O
     }
 }
 
-template <int G, int NV, int TB, Batches FULL, class SL>
+template <int G, int NV, int TB, Batches FORM, class SL>
+static void launch_useg_form(const USideArgs& a, const SL& sl, uint32_t CP, dim3 grid, dim3 block, hipStream_t st) {
+    if (a.fused && a.own_rows) {                 // (only the fused form takes rows over, or slices)
+        hipLaunchKernelGGL((useg_kernel<G, NV, TB, FORM, true, true, SL>), grid, block, 0, st, a, CP, sl);
+    } else if constexpr (TB <= 9) {
+        if (a.fused) hipLaunchKernelGGL((useg_kernel<G, NV, TB, FORM, true, false, SL>), grid, block, 0, st, a, CP, sl);
+        else if constexpr (SL::ONE) hipLaunchKernelGGL((useg_kernel<G, NV, TB, FORM, false, false, SL>), grid, block, 0, st, a, CP, sl);
+    }
+}
+
+template <int G, int NV, int TB, class SL>
 static void launch_useg_batch(const USideArgs& a, const SL& sl, uint32_t CP, dim3 grid, dim3 block, hipStream_t st) {
-    if (a.fused && a.own_rows)                   // (only the fused form takes rows over, or slices)
-        hipLaunchKernelGGL((useg_kernel<G, NV, TB, FULL, true, true, SL>), grid, block, 0, st, a, CP, sl);
-    else if (a.fused)
-        hipLaunchKernelGGL((useg_kernel<G, NV, TB, FULL, true, false, SL>), grid, block, 0, st, a, CP, sl);
-    else if constexpr (SL::ONE)
-        hipLaunchKernelGGL((useg_kernel<G, NV, TB, FULL, false, false, SL>), grid, block, 0, st, a, CP, sl);
+    if constexpr (G <= 32) {
+        if (G == 16 || CP > 2) return launch_useg_form<G, NV, TB, REFILLED>(a, sl, CP, grid, block, st);
+    }
+    if constexpr (G > 16) {
+        if constexpr (TB > 9) {
+            if (a.T % TB == 0) return launch_useg_form<G, NV, TB, FULL_BATCHES>(a, sl, CP, grid, block, st);
+        }
+        launch_useg_form<G, NV, TB, ANY_BATCH>(a, sl, CP, grid, block, st);
+    }
 }
 
 template <int G, int NV, class SL>
@@ -1030,7 +1045,7 @@ static void launch_useg_shape(const USideArgs& a, const SL& sl, hipStream_t st) 
     dim3 grid(blocks_for((uint64_t)nchunks * G, USEG_THREADS)), block(USEG_THREADS);
     // (the number of slots is a constant for k = 5, the paper's and the benchmark's number of negatives)
     if constexpr (NV <= 2) {
-        if (a.T == 6) return launch_useg_batch<G, NV, 6, ONE_BATCH>(a, sl, CP, grid, block, st);
+        if (a.T == 6) return launch_useg_form<G, NV, 6, ONE_BATCH>(a, sl, CP, grid, block, st);
     }
     constexpr int TB = NV == 1 ? 9 : (NV == 2 ? 6 : 4);     // rows requested per batch
     if constexpr (NV == 1) {
@@ -1045,13 +1060,11 @@ static void launch_useg_shape(const USideArgs& a, const SL& sl, hipStream_t st) 
                 const uint32_t nb = (a.T + tb - 1) / tb, waste = nb * tb - a.T;
                 if (nb < best_nb || (nb == best_nb && waste < best_waste)) { best = tb; best_nb = nb; best_waste = waste; }
             }
-            if (best == 11) return a.T % 11 ? launch_useg_batch<G, NV, 11, ANY_BATCH>(a, sl, CP, grid, block, st)
-                                            : launch_useg_batch<G, NV, 11, FULL_BATCHES>(a, sl, CP, grid, block, st);
-            if (best == 13) return a.T % 13 ? launch_useg_batch<G, NV, 13, ANY_BATCH>(a, sl, CP, grid, block, st)
-                                            : launch_useg_batch<G, NV, 13, FULL_BATCHES>(a, sl, CP, grid, block, st);
+            if (best == 11) return launch_useg_batch<G, NV, 11>(a, sl, CP, grid, block, st);
+            if (best == 13) return launch_useg_batch<G, NV, 13>(a, sl, CP, grid, block, st);
         }
     }
-    launch_useg_batch<G, NV, TB, ANY_BATCH>(a, sl, CP, grid, block, st);
+    launch_useg_batch<G, NV, TB>(a, sl, CP, grid, block, st);
 }
 
 void launch_useg(const USideArgs& a, hipStream_t st) {

@@ -26,9 +26,9 @@ def oracle_step(V, d, a, b, k, seed, counts, alpha):
                                       (128, 1, 10), (130, 1, 25), (200, 1, 5), (200, 1, 26), (256, 1, 17), (260, 1, 5), (300, 1, 5),
                                       (300, 1, 10), (300, 1, 11), (512, 1, 4), (514, 1, 5), (768, 1, 7), (770, 1, 3), (1024, 1, 6),
                                       (100, 3, 5), (300, 5, 5), (300, 5, 12), (130, 2, 21), (700, 2, 7), (300, 1, 0), (60, 2, 64)])
-def test_slots_of_a_pair_in_whole_and_part_batches(d, cuts, k):
-    print("batches", d, cuts, k, flush=True)
-    V, n, seed = 4000, 1203, 9
+def test_slots_of_a_pair_in_whole_and_part_batches(d, cuts, k, n=1203):
+    print("batches", d, cuts, k, n, flush=True)
+    V, seed = 4000, 9
     rng = np.random.default_rng(d + k)
     counts = workloads.analytic_counts(V, 1.0, 10 ** 7)
     cdf = workloads.zipf_cdf(V, 1.0)
@@ -51,6 +51,13 @@ def test_slots_of_a_pair_in_whole_and_part_batches(d, cuts, k):
             sh.status()
             sh.destroy()
         assert vec_error(got[0], U) <= BOUND and vec_error(got[1], W) <= BOUND, form
+
+
+# chunks of two pairs up to 98 303, three from there on: of rows of 17 to 32 float4 these are refilled, and one matrix or slices
+@pytest.mark.parametrize("d,cuts,k,n", [(100, 1, 10, 98_303), (100, 1, 10, 98_304), (100, 1, 7, 98_305), (128, 1, 12, 98_306), (68, 1, 25, 98_304),
+                                        (100, 1, 1, 98_307), (100, 2, 10, 98_304), (60, 1, 10, 98_306), (7, 1, 20, 98_305)])
+def test_longer_chunks_in_whole_and_part_batches(d, cuts, k, n):
+    test_slots_of_a_pair_in_whole_and_part_batches(d, cuts, k, n)
 
 
 # a chunk is 16 contributions, a window two, a cell 32 (64 from 2^19 contributions on)
