@@ -837,6 +837,7 @@ __device__ __forceinline__ void coefficients(const float (&sdot)[N], uint32_t j0
 // slots must stay a variable: as a constant, the refilled rows get registers of their own, are waited for and moved at the
 // batch's end, and three wavefronts fit instead of four: 729.)
 enum Batches { ANY_BATCH, FULL_BATCHES, ONE_BATCH, REFILLED };
+constexpr int VMCNT_0 = 0x0F70;                  // s_waitcnt for loads and stores alone
 template <int G, int NV, int TB, Batches FORM, bool FUSED, bool OWN, class SL>
 __global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FORM == ONE_BATCH ? (SL::ONE ? 5 : 4) : 1) void useg_kernel(USideArgs a, uint32_t CP, SL sl) {
     constexpr bool NEED_U = FUSED || OWN;      // the pair's input row: for the dots, for own rows
@@ -946,6 +947,10 @@ __global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FORM == ONE_BATCH ? (SL::O
             } else {
 #pragma unroll
                 for (int t = 0; t < TB; ++t) gco[t] = (uint32_t)t < slots ? s_cf[grp][pi * T + jb + t] : 0.f;
+                // (all of the batch, here: where only some rows are used, the compiler takes the others for loads in flight and waits
+                // before each of the next batch's.  With the dots all are.  k = 20, us: 4096 pairs of d = 60 24.0, 11.3, of d = 300
+                // 29.4, 23.3; 2^18 of d = 60 274, 223)
+                if (!WHOLE) __builtin_amdgcn_s_waitcnt(VMCNT_0);
             }
             // An output row that no other slot names gets its whole update here, from the
             // registers, with the same two roundings as the output-side kernel
