@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256) void iota_kernel(uint32_t* __restrict__ x, uin
 
 // ---------------------------------------------------------------------------------------------
 // Hidden vectors: one lane group per example adds the input rows of its context words in list
-// order (four loads in flight) and divides by their number.  An example without context gets zeros.
+// order (eight loads in flight, four or two of longer rows) and divides by their number.  An example without context gets zeros.
 // ---------------------------------------------------------------------------------------------
 template <int G, int NV>
 __global__ __launch_bounds__(256) void cbow_hidden_kernel(const float4* __restrict__ U, RowGeom g,

@@ -42,23 +42,8 @@ __device__ __forceinline__ void load_part(const float4* __restrict__ row, uint32
 
 typedef float v4f __attribute__((ext_vector_type(4)));
 
-// The same with the non-temporal hint: rows that are touched once per minibatch and should not
-// push reusable rows out of the caches.
-template <int G, int NV>
-__device__ __forceinline__ void load_row_nt_if(bool on, const float4* __restrict__ row, uint32_t d4,
-                                               int l, float4 (&r)[NV]) {
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        uint32_t i = (uint32_t)l + (uint32_t)(G * v);
-        if (on && i < d4) {
-            const v4f x = __builtin_nontemporal_load((const v4f*)row + i);
-            r[v] = make_float4(x.x, x.y, x.z, x.w);
-        } else {
-            r[v] = f4zero();
-        }
-    }
-}
-
+// store_row (below) with the non-temporal hint: rows that are touched once per minibatch and should not push reusable rows
+// out of the caches.
 template <int G, int NV>
 __device__ __forceinline__ void store_row_nt(float4* __restrict__ row, uint32_t d4, int l,
                                              const float4 (&r)[NV]) {
@@ -110,12 +95,6 @@ template <int G, int NV, int WHICH> struct Rows<G, NV, OneMatrix, WHICH> {
     }
     __device__ __forceinline__ void load_if(bool on, uint32_t row, float4 (&r)[NV]) const {
         load_row_if<G, NV>(on, M + (uint64_t)row * s4, d4, l, r);
-    }
-    __device__ __forceinline__ void load(uint32_t row, float4 (&r)[NV]) const {
-        load_row<G, NV>(M + (uint64_t)row * s4, d4, l, r);
-    }
-    __device__ __forceinline__ void load_nt_if(bool on, uint32_t row, float4 (&r)[NV]) const {
-        load_row_nt_if<G, NV>(on, M + (uint64_t)row * s4, d4, l, r);
     }
     // Whether float4 number v of this lane is part of a row.
     __device__ __forceinline__ bool has(int v) const { return v + 1 < NV || (uint32_t)l + (uint32_t)(G * v) < d4; }
@@ -185,7 +164,6 @@ template <int G, int NV, int WHICH> struct Rows<G, NV, SliceArgs, WHICH> {
 #pragma unroll
         for (int v = 0; v < NV; ++v) r[v] = on && data[v] ? at[v][(uint64_t)row * s4[v]] : f4zero();
     }
-    __device__ __forceinline__ void load(uint32_t row, float4 (&r)[NV]) const { load_if(true, row, r); }
     __device__ __forceinline__ bool has(int v) const { return data[v]; }
     template <bool NT, int N> __device__ __forceinline__ void load_all(const uint32_t (&key)[N], uint32_t n, float4 (&r)[N][NV]) const {
 #pragma unroll
@@ -230,17 +208,6 @@ template <int G, int NV, int WHICH> struct Rows<G, NV, SliceArgs, WHICH> {
             if (!data[v]) r[v] = f4zero();
         store(row, r);
     }
-    __device__ __forceinline__ void load_nt_if(bool on, uint32_t row, float4 (&r)[NV]) const {
-#pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            if (on && data[v]) {
-                const v4f x = __builtin_nontemporal_load((const v4f*)at[v] + (uint64_t)row * s4[v]);
-                r[v] = make_float4(x.x, x.y, x.z, x.w);
-            } else {
-                r[v] = f4zero();
-            }
-        }
-    }
     __device__ __forceinline__ void store(uint32_t row, const float4 (&r)[NV]) const {
 #pragma unroll
         for (int v = 0; v < NV; ++v)
@@ -257,20 +224,7 @@ template <int G, int NV, int WHICH> struct Rows<G, NV, SliceArgs, WHICH> {
     }
 };
 
-template <int NV>
-__device__ __forceinline__ float dot_part(const float4 (&a)[NV], const float4 (&b)[NV]) {
-    float s = 0.f;
-#pragma unroll
-    for (int v = 0; v < NV; ++v) {
-        s = fmaf(a[v].x, b[v].x, s);
-        s = fmaf(a[v].y, b[v].y, s);
-        s = fmaf(a[v].z, b[v].z, s);
-        s = fmaf(a[v].w, b[v].w, s);
-    }
-    return s;
-}
-
-// The same over what this lane has of a row (the rest of b may be anything; a's is zero or anything).
+// This lane's part of a dot product: over what it has of a row, the rest of a and b may be anything.
 template <int NV, class R>
 __device__ __forceinline__ float dot_part_of(const R& rows, const float4 (&a)[NV], const float4 (&b)[NV]) {
     float s = 0.f;
