@@ -839,7 +839,7 @@ __device__ __forceinline__ void coefficients(const float (&sdot)[N], uint32_t j0
 enum Batches { ANY_BATCH, FULL_BATCHES, ONE_BATCH, REFILLED };
 constexpr int VMCNT_0 = 0x0F70;                  // s_waitcnt for loads and stores alone
 template <int G, int NV, int TB, Batches FORM, bool FUSED, bool OWN, class SL>
-__global__ __launch_bounds__(USEG_THREADS, NV <= 2 && FORM == ONE_BATCH ? (SL::ONE ? 5 : 4) : 1) void useg_kernel(USideArgs a, uint32_t CP, SL sl) {
+__global__ __launch_bounds__(USEG_THREADS) void useg_kernel(USideArgs a, uint32_t CP, SL sl) {
     constexpr bool NEED_U = FUSED || OWN;      // the pair's input row: for the dots, for own rows
     constexpr bool WHOLE = FORM == FULL_BATCHES || FORM == ONE_BATCH;
     const float alpha = a.alpha;
