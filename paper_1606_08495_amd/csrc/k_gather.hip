@@ -94,7 +94,7 @@ __global__ __launch_bounds__(256) void move_rows_kernel(MoveRows<PARTS> a) {
     // Where one part's columns end inside a line of the caller's rows, the parts of some rows are blocks that follow each
     // other on one die (blocks go to the eight in turn): the line is still in that die's L2 when the next part's are written.
     // (130 000 rows of five parts of 60 columns one part after the other 94 us, this way 71; where parts end with their
-    // lines, 200 000 rows of four of 32, 39 and 41.)
+    // lines, 200 000 rows of four of 32, 39 and 41.  For which widths: launch_move_rows.)
     const uint32_t which = PARTS > 1 ? (a.together ? blockIdx.x / 8 % a.parts : blockIdx.x / a.in_x) : 0u;
     const uint32_t group_x = a.together ? blockIdx.x / (8 * a.parts) * 8 + blockIdx.x % 8 : blockIdx.x % a.in_x;
     const uint64_t group = PARTS > 1 ? (uint64_t)blockIdx.y * MOVE_GROUPS + group_x : blockIdx.x;
@@ -140,11 +140,20 @@ static void launch_move_rows(const RowPart* parts, uint32_t S, float* ext, uint3
     MoveRows<PARTS> a{};
     a.ext = ext; a.pitch = pitch; a.m = m; a.V = V; a.rows = rows;
     uint32_t mix = pitch | (uint32_t)((uintptr_t)ext / 4), width = 0;
+    uint64_t widths = 0;
+    bool lines_shared = false;
     for (uint32_t s = 0; s < S; ++s) {
         mix |= parts[s].width | parts[s].col;
-        a.together |= (parts[s].col | pitch | (uint32_t)((uintptr_t)ext / 4)) % 32 != 0;
+        lines_shared |= (parts[s].col | pitch | (uint32_t)((uintptr_t)ext / 4)) % 32 != 0;
         width = std::max(width, parts[s].width);
+        widths += parts[s].width;
     }
+    // Blocks of narrow parts hold the places of others with little to do, so parts are moved together where they are nearly
+    // equal, and somewhat unequal ones where the caches would not keep the shared lines anyway.  One part after the other and
+    // together, us, 100 000 and 600 000 rows: 150 + 150 columns 52, 46 and 407, 292; 200 + 100 51, 56 and 402, 359; 60 + 100 + 140 55, 51 and
+    // 428, 341; 100 + 28 21.5, 22.2 and 150, 172; 280 + 20 49, 62 and 363, 374.
+    const bool large = (uint64_t)m * pitch * 4 >= 200000000u;
+    a.together = lines_shared && 10 * widths >= (large ? 7 : 9) * (uint64_t)S * width;
     const uint32_t vec = (uintptr_t)ext % 4 ? 1 : (mix % 4 == 0 ? 4 : (mix % 2 == 0 ? 2 : 1));
     for (uint32_t s = 0; s < S; ++s) {
         const uint32_t dv = parts[s].width / vec;                 // (dv = 1: the magic is not used)

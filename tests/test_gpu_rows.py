@@ -62,9 +62,10 @@ def test_export_joins_slices_of_any_alignment(widths):
 
 
 @pytest.mark.parametrize("widths,m", [((60,) * 5, 1), ((60,) * 5, 273), ((1, 7), 8 * 256 + 1), ((4,) * 32, 4099), ((32,) * 4, 5001),
-                                      ((512, 512), (1 << 18) * 16 + 5)])
+                                      ((512, 512), (1 << 18) * 16 + 5), ((7, 8), 8 * 256 + 1), ((60, 100, 140), 166_666), ((60, 100, 140), 166_667)])
 def test_export_at_the_edges_of_the_grid(widths, m):
-    """Blocks of several parts' rows in groups of eight, the last one not full; past 2^18 of them in a second row of the grid."""
+    """Blocks of several parts' rows in groups of eight, the last one not full; past 2^18 of them in a second row of the grid.
+    Unequal widths one after the other, together from 200 MB on."""
     print("export", widths, m, flush=True)
     V, total = 64, sum(widths)
     shards, col = [], 0
