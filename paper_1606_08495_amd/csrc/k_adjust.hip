@@ -833,7 +833,10 @@ __device__ __forceinline__ void coefficients(const float (&sdot)[N], uint32_t j0
 // FULL_BATCHES: pairs are whole batches, and no load stands behind a branch of its own; ONE_BATCH: of one batch.
 // REFILLED: a register set is refilled as soon as its row is used, whole batches or not.  Worth it at sixteen and thirty-two lanes a row,
 // in four wavefronts a SIMD, us, batch by batch and refilled: k = 10, 2^20 pairs of d = 60 779, 705; 2^18 of d = 100 299, 280; k = 12, d = 128
-// 362, 326; k = 7, d = 100 234, 228; but 4096 pairs of d = 100, in chunks of two pairs, 13.9, 14.9, and d = 200, k = 25 538, 569.  (The number of
+// 362, 326; k = 7, d = 100 234, 228; but 4096 pairs of d = 100, in chunks of two pairs, 13.9, 14.9, and d = 200, k = 25 538, 569.  And at two
+// float4 a lane and more, where a small launch leaves each wavefront to hide its own latency: 4096 pairs, k = 20, d = 300 35.7, 32.9, over
+// three slices 48.4, 41.1, d = 600 60.7, 52.9; k = 15, 16 384 of d = 300 76.0, 71.5, but of d = 1000 218, 228, and steps of 65 536 of d = 300, k = 8
+// 335, 365.  (The number of
 // slots must stay a variable: as a constant, the refilled rows get registers of their own, are waited for and moved at the
 // batch's end, and three wavefronts fit instead of four: 729.)
 enum Batches { ANY_BATCH, FULL_BATCHES, ONE_BATCH, REFILLED };
@@ -1034,6 +1037,9 @@ template <int G, int NV, int TB, class SL>
 static void launch_useg_batch(const USideArgs& a, const SL& sl, uint32_t CP, dim3 grid, dim3 block, hipStream_t st) {
     if constexpr (G <= 32) {
         if (G == 16 || CP > 2) return launch_useg_form<G, NV, TB, REFILLED>(a, sl, CP, grid, block, st);
+    }
+    if constexpr (NV >= 2) {
+        if (a.n <= (NV == 2 ? 16384u : 8192u)) return launch_useg_form<G, NV, TB, REFILLED>(a, sl, CP, grid, block, st);
     }
     if constexpr (G > 16) {
         if constexpr (TB > 9) {

@@ -53,9 +53,12 @@ def test_slots_of_a_pair_in_whole_and_part_batches(d, cuts, k, n=1203):
         assert vec_error(got[0], U) <= BOUND and vec_error(got[1], W) <= BOUND, form
 
 
-# chunks of two pairs up to 98 303, three from there on: of rows of 17 to 32 float4 these are refilled, and one matrix or slices
+# chunks of two pairs up to 98 303, three from there on: of rows of 17 to 32 float4 the latter are refilled; of more than 64 up to
+# 16 384 pairs are, of more than 128 up to 8192; one matrix or slices
 @pytest.mark.parametrize("d,cuts,k,n", [(100, 1, 10, 98_303), (100, 1, 10, 98_304), (100, 1, 7, 98_305), (128, 1, 12, 98_306), (68, 1, 25, 98_304),
-                                        (100, 1, 1, 98_307), (100, 2, 10, 98_304), (60, 1, 10, 98_306), (7, 1, 20, 98_305)])
+                                        (100, 1, 1, 98_307), (100, 2, 10, 98_304), (60, 1, 10, 98_306), (7, 1, 20, 98_305), (300, 1, 9, 16_384),
+                                        (300, 1, 9, 16_385), (260, 3, 7, 16_385), (700, 1, 7, 8192), (700, 1, 7, 8193), (700, 2, 9, 8193),
+                                        (1000, 1, 6, 8193)])
 def test_longer_chunks_in_whole_and_part_batches(d, cuts, k, n):
     test_slots_of_a_pair_in_whole_and_part_batches(d, cuts, k, n)
 
