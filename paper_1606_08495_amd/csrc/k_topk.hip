@@ -800,8 +800,8 @@ __global__ __launch_bounds__(TK_THREADS, 4) void topk_scores_kernel(TopkArgs a) 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fold: one block per query gives the pairs listed (or left as bits) their similarities -- a lane per candidate, its
-// row read by lanes side by side (wave_scores) or by itself (exact_score); the fp32 screen has them listed already -- and merges those above
+// Fold: one block per query gives the pairs listed (or left as bits) their similarities -- a lane per candidate, one
+// 128-byte line of its row at a time; the fp32 screen has them listed already -- and merges those above
 // the threshold into the sorted best list (higher score first, equal scores by lower index), then raises
 // the threshold to the K-th best and empties the list.  Rounds come in index order, so a later candidate that only equals the K-th best
 // never enters.  Each wavefront keeps its own 64 best, sorted across its lanes; the lists are merged
@@ -961,7 +961,6 @@ static bool fold_few(uint32_t Q, uint32_t d, bool vec4, bool first, double passi
 }
 constexpr uint32_t FOLD_PICK = 2048;             // candidates named by bits that a block lists before it scores them
 constexpr uint32_t FOLD_CHUNK = 16;              // words: where they are more
-constexpr uint32_t TK_PARTS = 16;                // blocks that share them, at most
 // candidates of a round for every block of a query (a block more costs what it takes to count: 100 queries over 200 003 x
 // 100, not crowded, 116.6 us, in five blocks each 116.9, and two in the round before 117.2)
 static uint32_t fold_share(uint32_t Q) { return Q <= 32 ? 1u << 13 : 1u << 15; }
@@ -1159,19 +1158,11 @@ constexpr uint32_t WIDE_Q = 32 * TK_WTM * TK_WWM, WIDE_C = 32 * TK_WTN * TK_WWN;
 // longer, as the same memory holds.
 // `ahead`: there is room for the rounded candidates of two rounds.  `parts`: blocks that may share a query's fold.
 struct TopkPlan { TopkScreen screen; uint64_t cap, q_up, list; bool ahead; uint32_t parts; };
-// How many, up to `most`: what the chip holds at a time of blocks of eight wavefronts with rows in LDS, or of sixteen without, is one to a
-// compute unit, of eight without two, so `parts` of them take ceil(Q parts / that many) times 1 / parts; more only where that is a tenth
-// less (rising order, 200 000 x 300, us, one, two, three, four, five, eight and more blocks: 64 queries 3376, -, -, 1243, -, 1647; 100
-// 3380, 1942, -, -, 1748, -; 128 3372, 1987, -, 2027, -, 2325; 160 3540, -, 2705, -, -, 3197; 200 3569, 3656, -, -, 3315, -; 256 3600, 3659,
-// -, 3785, -, 3852).
-static uint32_t fold_parts(uint32_t Q, uint32_t d, uint32_t most) {
-    if (Q > 2 * TK_STREAM_Q) return 1;
-    const uint32_t at_once = fold_by_lane(true, d, d % 4 == 0) && Q > TK_STREAM_Q ? 512u : 256u;
-    auto turns = [&](uint32_t parts) { return (Q * parts + at_once - 1) / at_once; };
-    uint32_t parts = 1;
-    for (uint32_t p = 2; p <= most; ++p)
-        if (10 * turns(p) * parts <= 9 * turns(parts) * p) parts = p;
-    return parts;
+// As many as fill the chip (a block has sixteen wavefronts up to TK_STREAM_Q queries, four past that), where there
+// are few queries; a sixteenth of the room that the bits have at most.
+static uint32_t fold_parts(uint32_t Q, uint64_t room) {
+    const uint32_t parts = Q > 2 * TK_STREAM_Q ? 1u : std::min(16u, (Q > TK_STREAM_Q ? 2048u : 512u) / Q);
+    return (uint64_t)Q * parts * TK_LIST * 8 <= room / 16 ? parts : 1u;
 }
 static uint32_t stream_tiles(uint32_t Q) { return Q <= 32 ? 1 : (Q <= 64 ? 2 : 4); }    // of 32 queries, per wavefront
 
@@ -1203,8 +1194,7 @@ static TopkPlan topk_plan(uint32_t Q, uint32_t N, uint32_t d, size_t workspace_b
         uint32_t parts = 1;
         if (screen == TOPK_STREAM) {
             uint64_t bytes = free_bytes - q_bytes;
-            parts = fold_parts(Q, d, TK_PARTS);
-            if ((uint64_t)Q * parts * TK_LIST * 8 > bytes / 16) parts = 1;      // (of the room that the bits have)
+            parts = fold_parts(Q, bytes);
             if (parts > 1) bytes -= (uint64_t)Q * parts * TK_LIST * 8 + 256;
             held = std::min(held, bytes / per_candidate / granule * granule);
             longest = bytes / Q * 8 / TK_BC * TK_BC;
@@ -1379,7 +1369,7 @@ uint32_t* launch_topk_cosine(const float* Qm, uint32_t Q, const float* Cm, uint3
         const bool last = begin + len >= N;
         uint32_t* oi = last ? out_idx : nullptr;
         const bool bits = screen == TOPK_STREAM && !exact_round;
-        const uint32_t parts = bits ? fold_parts(Q, d, std::min(plan.parts, m / fold_share(Q))) : 1u;
+        const uint32_t parts = bits ? std::max(1u, std::min(plan.parts, m / fold_share(Q))) : 1u;
 #define W2V_FOLD(WAVES, VEC4, ...)                                                                         \
     hipLaunchKernelGGL((topk_fold_kernel<WAVES, VEC4, __VA_ARGS__>), dim3(std::min(TK_FOLD_SLICE, Q - a.q_first), parts), \
                        dim3(64 * WAVES), 0, st, a, K, tau, best, best_cnt, theta, oi, out_score, out_count)
