@@ -831,14 +831,14 @@ __device__ __forceinline__ void coefficients(const float (&sdot)[N], uint32_t j0
 // compiler waits for all loads before it: the same kernel with one or two rows in flight.  Input side of a step, us, that
 // way and this: 4096 pairs of d = 100 10.8, 7.0; 65 536 58, 52; 100 003 pairs over five shards of 60 columns 182, 130.)
 // FULL_BATCHES: pairs are whole batches, and no load stands behind a branch of its own; ONE_BATCH: of one batch.
-// REFILLED: a register set is refilled as soon as its row is used, whole batches or not.  Worth it at sixteen and thirty-two lanes a row,
-// in four wavefronts a SIMD, us, batch by batch and refilled: k = 10, 2^20 pairs of d = 60 779, 705; 2^18 of d = 100 299, 280; k = 12, d = 128
-// 362, 326; k = 7, d = 100 234, 228; but 4096 pairs of d = 100, in chunks of two pairs, 13.9, 14.9, and d = 200, k = 25 538, 569.  And at two
-// float4 a lane and more, where a small launch leaves each wavefront to hide its own latency: 4096 pairs, k = 20, d = 300 35.7, 32.9, over
-// three slices 48.4, 41.1, d = 600 60.7, 52.9; k = 15, 16 384 of d = 300 76.0, 71.5, but of d = 1000 218, 228, and steps of 65 536 of d = 300, k = 8
-// 335, 365.  (The number of
-// slots must stay a variable: as a constant, the refilled rows get registers of their own, are waited for and moved at the
-// batch's end, and three wavefronts fit instead of four: 729.)
+// REFILLED: a register set is refilled as soon as its row is used, whole batches or not.  Input side, us, batch by batch and refilled:
+// at thirty-two lanes a row k = 10, 2^18 pairs of d = 100 299, 282; k = 12, d = 128 364, 326; k = 7, d = 100 234, 228; but 4096 pairs of
+// d = 100, in chunks of two pairs, 13.9, 14.9.  At sixteen the same within 3 %: k = 10, 2^20 of d = 60 474, 473; k = 25, 2^18 287, 281; k = 12,
+// d = 16 108, 111.  At one float4 of sixty-four batch by batch (k = 25, d = 200 538, 569).  At two float4 a lane and more where a small launch
+// leaves each wavefront to hide its own latency: 4096 pairs, k = 20, d = 300 35.7, 32.9, over three slices 48.4, 41.1, d = 600 60.7, 52.9; k = 15,
+// 16 384 of d = 300 76.0, 71.5, but of d = 1000 218, 228, and steps of 65 536 of d = 300, k = 8 335, 365.  (The number of slots must stay a
+// variable: as a constant, the refilled rows get registers of their own, are waited for and moved at the batch's end, and three
+// wavefronts fit instead of four: 2^20 of d = 60 500.)
 enum Batches { ANY_BATCH, FULL_BATCHES, ONE_BATCH, REFILLED };
 constexpr int VMCNT_0 = 0x0F70;                  // s_waitcnt for loads and stores alone
 template <int G, int NV, int TB, Batches FORM, bool FUSED, bool OWN, class SL>

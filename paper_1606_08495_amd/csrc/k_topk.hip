@@ -800,8 +800,8 @@ __global__ __launch_bounds__(TK_THREADS, 4) void topk_scores_kernel(TopkArgs a) 
 }
 
 // ---------------------------------------------------------------------------------------------
-// Fold: one block per query gives the pairs listed (or left as bits) their similarities -- a lane per candidate, one
-// 128-byte line of its row at a time; the fp32 screen has them listed already -- and merges those above
+// Fold: one block per query gives the pairs listed (or left as bits) their similarities -- a lane per candidate, its
+// row read by lanes side by side (wave_scores) or by itself (exact_score); the fp32 screen has them listed already -- and merges those above
 // the threshold into the sorted best list (higher score first, equal scores by lower index), then raises
 // the threshold to the K-th best and empties the list.  Rounds come in index order, so a later candidate that only equals the K-th best
 // never enters.  Each wavefront keeps its own 64 best, sorted across its lanes; the lists are merged
@@ -810,8 +810,8 @@ __global__ __launch_bounds__(TK_THREADS, 4) void topk_scores_kernel(TopkArgs a) 
 // old as the round before.  Past FOLD_PICK candidates gridDim.y blocks share the query (fold_parts; with fewer all but
 // the first have only counted), and the last one done merges their lists.  Rising order, K = 30, us, with rounds as short
 // as lists of four bytes a pair allow, with the long ones and one block a query, and shared: 1 query over 200 000 x 100
-// 1760, 2570, 392, over 10^6 3250, 9900, 1140; 100 queries 1820, 1545, 950 and 3520, 6250, 4140; 200 over 200 000
-// 1720, 2240, 1790 (what many queries still lose are the reads of the rows that pass).
+// 1760, 2570, 295, over 10^6 3250, 9900, 865; 100 queries 1820, 1545, 795 and 3520, 6250, 2950; 200 over 200 000
+// 1720, 2240, 1480.
 // ---------------------------------------------------------------------------------------------
 // (score, index) as one number that grows with the rank: order-preserving bits of the score, then ~index
 __device__ __forceinline__ uint64_t rank_key(float s, uint32_t c) {
@@ -847,7 +847,8 @@ __device__ __forceinline__ uint64_t merge64(uint64_t list, uint64_t rev, int lan
 // The similarities of a wavefront's candidates, lane r the one of candidate c of lane r (lanes 0 .. nr - 1, nr at least 1).
 // Rows are read 32 columns at a time by lanes side by side and go through LDS, from where each lane walks its own: a
 // lane that reads its row from memory takes a line of its own for every access, 64 to an instruction, and the fold was bound by
-// those (4096 queries over 2^20 x 300: 27 us a round, now 15; 100 over 200 003 x 100 25, now 19; one over 500 000 x 300 58, now 34).
+// those (a round, us, that way and this: 4096 queries over 2^20 x 300 in the median 27, 15, on average, with the two early ones
+// that list hundreds of candidates a query, 36, 24; 100 over 200 003 x 100 29, 22; one over 500 000 x 300 67, 33).
 constexpr int FS_COLS = 32, FS_PITCH = FS_COLS + 4;      // (16-byte aligned, eight rows a pass over the banks)
 struct FoldRows { float x[65][FS_PITCH]; uint32_t c[64]; };      // row 64: the query
 template <bool VEC4, int AHEAD>
@@ -1158,8 +1159,11 @@ constexpr uint32_t WIDE_Q = 32 * TK_WTM * TK_WWM, WIDE_C = 32 * TK_WTN * TK_WWN;
 // longer, as the same memory holds.
 // `ahead`: there is room for the rounded candidates of two rounds.  `parts`: blocks that may share a query's fold.
 struct TopkPlan { TopkScreen screen; uint64_t cap, q_up, list; bool ahead; uint32_t parts; };
-// As many as fill the chip (a block has sixteen wavefronts up to TK_STREAM_Q queries, four past that), where there
-// are few queries; a sixteenth of the room that the bits have at most.
+// Up to sixteen where there are few queries, in a sixteenth of the room that the bits have at most.  A block of eight wavefronts with
+// rows in LDS has a compute unit to itself, so these numbers fill the chip two times over, eight past TK_STREAM_Q queries.  Where every
+// query has as much to fold, once would do (rising order, 200 000 x 300, us, filled once and as it is: 64 queries 1243, 1647; 128 1987, 2325;
+// 256 3600, 3852; 100 1942, 1748); where one of many has, its list is folded by that many compute units (129 queries over 100 000 x 301,
+// crowded: 5688, 3577).
 static uint32_t fold_parts(uint32_t Q, uint64_t room) {
     const uint32_t parts = Q > 2 * TK_STREAM_Q ? 1u : std::min(16u, (Q > TK_STREAM_Q ? 2048u : 512u) / Q);
     return (uint64_t)Q * parts * TK_LIST * 8 <= room / 16 ? parts : 1u;
